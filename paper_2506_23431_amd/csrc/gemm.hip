@@ -2,6 +2,9 @@
 // (QKV + rotary + KV append, residual add, GELU, SwiGLU, vocabulary argmax).
 #include "mfma_common.h"
 
+#include <algorithm>
+#include <cmath>
+
 #ifndef PD_GEMM_EPI   // ---- common part: weight packing, norm kernel -------------------------------
 
 // ---------------------------------------------------------------------------
@@ -829,24 +832,27 @@ static int launch_gemm_wide(const GemmArgs &a, hipStream_t s) {
 
 
 // ---------------------------------------------------------------------------
-// More than 128 rows (the context pass in chunks of up to 2048 rows): grid (column groups, K slices,
-// groups of 128 rows).  A block is NW = 8 waves (two per SIMD: a single wave issues a 16x16x32
-// multiply every 29 clocks, two or more every 19) that own NT column tiles each and share the 8 row
-// tiles of their row group: per k-tile every wave requests its share of the activation fragments
-// (high and low parts) and its own weight fragments, D k-tiles ahead, the activation fragments pass
-// through LDS (two buffers of 16 KiB), and every wave multiplies all of them with its weights.  A
-// k-tile then costs the compute unit 16 + 8 NT requests for 128 NT multiplies, against 16 + NT for
-// 16 NT when the waves cut K instead.
-// Measured (useful rate; twice that is executed with the low parts): QKV of cfg5 with 2048 rows
-// 320 us = 0.64 PFLOP/s with NT = 3 (512 blocks), gate + up 608 us = 0.61; QKV of cfg4 with 4096 rows
-// 177 us = 0.58 PFLOP/s.  An earlier version with 4 waves per block and twice the column tiles per
-// wave took nearly twice the time of the 8-wave version of its day.
+// More than 128 rows against matrices that make the multiplies the bound (the context pass, large teacher-forced
+// passes): grid (column groups, K slices, groups of 16 RT rows).  A block is NW = 8 waves (two per SIMD: a single
+// wave issues a 16x16x32 multiply every 29 clocks, two or more every 19) that own NT column tiles each and share the
+// RT row tiles of their row group: per k-tile every wave requests its share of the activation fragments (high and
+// low parts) and its own weight fragments, two k-tiles ahead; the activation fragments pass through LDS (two buffers),
+// and every wave multiplies all of them with its weights.
+// One barrier per k-tile, in the middle of its multiplies: the fragments of a k-tile go from LDS to the matrix cores
+// in groups of GS, the group after next is requested when a group has been multiplied, and behind the barrier that
+// request already goes to the next k-tile's buffer.  So a wave never stands between a barrier and its first multiply
+// waiting for LDS (with the barrier in front of the k-tile's first LDS read the same launches took: QKV, 2048 rows,
+// width 4096, 327 us, now 310; QKV, 4096 rows, width 2048, 182 -> 173; second FFN projection there 204 -> 198).
+// At these sizes the multiplies run at 1.2-1.43 PFLOP/s (high and low parts counted), what a large library product
+// reaches on this device: with operands of zeros the same launches are 20-30 % faster, so it is the power limit
+// that holds the rate, and 32x32x16 multiplies (half the operand reads) measured no better (239 against 226 us).
 // ---------------------------------------------------------------------------
-template <int NT, int D, int OCC, int EPI, bool SPLIT, int NW = 4, int TAG = 0>
-__global__ __launch_bounds__(64 * NW, OCC) void k_gemm_p(GemmArgs a) {
-  static_assert(NW == 4 || NW == 8, "4 or 8 waves");
-  constexpr int RT = 8, NA = SPLIT ? 2 * RT : RT, NAW = NA / NW;   // fragments per k-tile: all / staged by one wave
-  static_assert(D % 2 == 0 || D == 1, "stages alternate between the two LDS buffers");
+template <int RT, int NT, int EPI, bool SPLIT>
+__global__ __launch_bounds__(512, 1) void k_gemm_t(GemmArgs a) {
+  constexpr int NW = 8, NA = SPLIT ? 2 * RT : RT;     // activation fragments of a k-tile
+  constexpr int NAW = NA >= NW ? NA / NW : 1;         // staged by one wave (fewer fragments than waves: some twice, same bytes)
+  constexpr int GS = 4, NG = NA / GS;
+  static_assert(NA % GS == 0 && (NG == 1 || NG % 2 == 0), "fragment groups alternate between two register sets");
   __shared__ bf16x8 sm_x[2][NA][64];   // (vector types throughout: struct copies would keep xr in scratch memory)
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int m = lane & 15;
@@ -854,87 +860,86 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_p(GemmArgs a) {
   const int per_slice = (KT + (int)gridDim.y - 1) / (int)gridDim.y;
   const int kt0 = min((int)blockIdx.y * per_slice, KT), kt1 = min(kt0 + per_slice, KT);
   const int rt0 = blockIdx.z * RT, r0 = rt0 * 16;
-  int4 kvi[(EPI == EPI_QKV || EPI == EPI_QKV_ROPE || EPI == EPI_QKV_NORM) ? RT : 1];
-  if (EPI == EPI_QKV || EPI == EPI_QKV_ROPE || EPI == EPI_QKV_NORM) {
+  int4 kvi[(EPI == EPI_QKV || EPI == EPI_QKV_ROPE) ? RT : 1];
+  if (EPI == EPI_QKV || EPI == EPI_QKV_ROPE) {
 #pragma unroll
     for (int i = 0; i < RT; ++i) kvi[i] = a.rt.kvinfo[r0 + i * 16 + m];
   }
   const int nt0 = (blockIdx.x * NW + w) * NT;
-  int tile[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) tile[t] = min(nt0 + t, a.n_tiles - 1);   // tiles past the end repeat the last one
   floatx4 acc[NT][RT];
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int i = 0; i < RT; ++i) acc[t][i] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const uint4 *wp = (const uint4 *)a.W + lane;
-  // this wave's share of the activation fragments: fragment f = w * NAW + j is row tile f % RT of
-  // the high (f < RT) or low parts
+  const bf16x8 *wsrc[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)          // tiles past the end repeat the last one
+    wsrc[t] = (const bf16x8 *)a.W + (size_t)min(nt0 + t, a.n_tiles - 1) * KT * 64 + lane;
+  // this wave's share of the activation fragments: fragment f is row tile f % RT of the high (f < RT) or low parts
   const bf16x8 *xsrc[NAW];
 #pragma unroll
-  for (int j = 0; j < NAW; ++j) {
-    int f = w * NAW + j;
+  for (int i = 0; i < NAW; ++i) {
+    const int f = (w * NAW + i) % NA;
     const bf16_t *base = (SPLIT && f >= RT) ? a.xn_lo : a.xn;
-    xsrc[j] = (const bf16x8 *)base + (size_t)(rt0 + f % RT) * KT * 64 + lane;
+    xsrc[i] = (const bf16x8 *)base + (size_t)(rt0 + f % RT) * KT * 64 + lane;
   }
-  // D k-tiles are in flight per wave, each in registers of its own (slot = k-tile index mod D)
-  Frag xr[D][NAW];
-  Frag wr[D][NT];
   const int len = kt1 - kt0;
-  auto k_of = [&](int j) { return kt0 + min(j, len - 1); };   // steps past the end repeat the last k-tile
+  bf16x8 xr[2][NAW], wr[2][NT];         // k-tiles in flight, slot = k-tile index mod 2; past the end: the last one again
+  auto load_x = [&](int s, int j) {
+    const size_t k = (size_t)(kt0 + min(j, len - 1)) * 64;
 #pragma unroll
-  for (int d = 0; d < D; ++d) {
-    int k = len > 0 ? k_of(d) : 0;
+    for (int i = 0; i < NAW; ++i) xr[s][i] = xsrc[i][k];
+  };
+  auto load_w = [&](int s, int j) {
+    const size_t k = (size_t)(kt0 + min(j, len - 1)) * 64;
 #pragma unroll
-    for (int j = 0; j < NAW; ++j) xr[d][j].v = xsrc[j][(size_t)k * 64];
+    for (int t = 0; t < NT; ++t) wr[s][t] = wsrc[t][k];
+  };
+  auto put_x = [&](int s) {
 #pragma unroll
-    for (int t = 0; t < NT; ++t) wr[d][t].u = wp[((size_t)tile[t] * KT + k) * 64];
-  }
-  for (int j0 = 0; j0 < len; j0 += D) {
+    for (int i = 0; i < NAW; ++i) sm_x[s][(w * NAW + i) % NA][lane] = xr[s][i];
+  };
+  if (len > 0) {                        // the same for the whole block
+    load_x(0, 0); load_w(0, 0);
+    load_x(1, 1); load_w(1, 1);
+    put_x(0);
+    load_x(0, 2);
+    __syncthreads();
+    Frag xg[2][GS];
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-      if (j0 + d < len) {           // the same for every wave of the block
-        const int buf = D == 1 ? (j0 & 1) : (d & 1);
-        Frag wc[NT];
+    for (int h = 0; h < (NG == 1 ? 1 : 2); ++h)
 #pragma unroll
-        for (int j = 0; j < NAW; ++j) sm_x[buf][w * NAW + j][lane] = xr[d][j].v;
+      for (int u = 0; u < GS; ++u) xg[h][u].v = sm_x[0][h * GS + u][lane];
+    for (int j0 = 0; j0 < len; j0 += 2) {
 #pragma unroll
-        for (int t = 0; t < NT; ++t) wc[t] = wr[d][t];
-        {                           // refill the slot with the k-tile D further on
-          int k = k_of(j0 + d + D);
+      for (int d = 0; d < 2; ++d) {
+        const int j = j0 + d;
+        if (j < len) {                  // the same for every wave of the block
+          // k-tile j + 1 goes to the other buffer (its last readers, of k-tile j - 1, are behind the barrier of
+          // k-tile j - 1); the slots are refilled two k-tiles on
+          put_x(d ^ 1);
+          load_x(d ^ 1, j + 3);
+          Frag wc[NT];
 #pragma unroll
-          for (int j = 0; j < NAW; ++j) xr[d][j].v = xsrc[j][(size_t)k * 64];
-#pragma unroll
-          for (int t = 0; t < NT; ++t) wr[d][t].u = wp[((size_t)tile[t] * KT + k) * 64];
-        }
-        // one barrier per k-tile is enough with two buffers: a wave can only write k-tile i + 2 into
-        // this buffer after the barrier of k-tile i + 1, which every wave reaches after its reads of i
-        __syncthreads();
-        // The k-tile's fragments pass from LDS to the matrix cores in groups of GS (fragment f: row tile
-        // f % RT, high parts first): two groups are requested up front, and while one group is multiplied
-        // the next but one is requested into the registers of the group before it.  A wave then holds 2 GS
-        // fragments instead of all NA (which, with the accumulators and the weights in flight, did not fit
-        // the 256 registers of a wave at two waves per SIMD), and its LDS reads run under its multiplies.
-        // Products into the same accumulator (high and low part of a row tile) are NT * RT multiplies apart.
-        constexpr int GS = 4, NG = NA / GS;
-        Frag xg[2][GS];
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-          for (int u = 0; u < GS; ++u) xg[h][u].v = sm_x[buf][h * GS + u][lane];
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int gi = 0; gi < NG; ++gi) {
-#pragma unroll
-          for (int u = 0; u < GS; ++u)
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-              acc[t][(gi * GS + u) % RT] = mfma16(wc[t], xg[gi & 1][u], acc[t][(gi * GS + u) % RT]);
+          for (int t = 0; t < NT; ++t) wc[t].v = wr[d][t];
+          load_w(d, j + 2);
           __builtin_amdgcn_sched_barrier(0);
-          if (gi + 2 < NG) {
 #pragma unroll
-            for (int u = 0; u < GS; ++u) xg[gi & 1][u].v = sm_x[buf][(gi + 2) * GS + u][lane];
+          for (int gi = 0; gi < NG; ++gi) {
+#pragma unroll
+            for (int u = 0; u < GS; ++u)
+#pragma unroll
+              for (int t = 0; t < NT; ++t)
+                acc[t][(gi * GS + u) % RT] = mfma16(wc[t], xg[gi & 1][u], acc[t][(gi * GS + u) % RT]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (gi == (NG == 1 ? 0 : NG - 2)) {
+              __syncthreads();          // k-tile j + 1 is in LDS, nobody reads k-tile j there any more
+              __builtin_amdgcn_sched_barrier(0);
+            }
+            const int gn = NG == 1 ? 1 : gi + 2;      // the group that takes this one's registers
+#pragma unroll
+            for (int u = 0; u < GS; ++u)
+              xg[gi & 1][u].v = gn < NG ? sm_x[d][gn * GS + u][lane] : sm_x[d ^ 1][(gn - NG) * GS + u][lane];
             __builtin_amdgcn_sched_barrier(0);
           }
         }
@@ -946,37 +951,79 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_p(GemmArgs a) {
     if (nt0 + t < a.n_tiles) gemm_epilogue<RT, EPI>(a, nt0 + t, acc[t], kvi, lane, r0);
 }
 
-template <int NT, int EPI, bool SPLIT>
-static int launch_gemm_rows_nt(GemmArgs a, int rows, hipStream_t s) {
-  constexpr int NW = 8;
-  int KT = a.K / 32, gx = (a.n_tiles + NW * NT - 1) / (NW * NT), gz = (rows + 127) / 128, ks = 1;
-  if (EPI == EPI_RESID)     // K slices (summed by the next norm kernel) while compute units would stay empty
-    while (ks < a.max_parts && (long)gx * gz * ks < 256 && KT / (2 * ks) >= 8) ks *= 2;
-  hipLaunchKernelGGL((k_gemm_p<NT, 2, 1, EPI, SPLIT, NW>), dim3(gx, ks, gz), dim3(64 * NW), 0, s, a);
+template <int RT, int NT, int EPI, bool SPLIT>
+static int launch_gemm_t(const GemmArgs &a, int rows, int ks, hipStream_t s) {
+  dim3 grid((a.n_tiles + 8 * NT - 1) / (8 * NT), ks, (rows + 16 * RT - 1) / (16 * RT));
+  hipLaunchKernelGGL((k_gemm_t<RT, NT, EPI, SPLIT>), grid, dim3(512), 0, s, a);
   PD_CHECK_HIP(hipGetLastError());
   if (EPI == EPI_RESID && a.parts_out) *a.parts_out = ks;
   return PD_OK;
 }
 
-// Column tiles per wave (2, 3 or 4; blocks of 8 waves, one block per compute unit): what finishes
-// first by the measured time of a block per k-tile (1.03 / 1.39 / 1.93 us: close to proportional, the
-// matrix cores set the pace; QKV and FFN1 shapes of cfg4 in chunks of 4096 rows) times the rounds of
-// 256 blocks the launch needs.
+// The waves of a block cut K (k_gemm_s), RT row tiles and NT column tiles per block.
+template <int RT, int NT, int NWK, int EPI, bool SPLIT>
+static int launch_gemm_cut(GemmArgs a, int rows, int ks, hipStream_t s) {
+  a.k_share = ((a.K / 32 + ks - 1) / ks + NWK - 1) / NWK;
+  dim3 grid((a.n_tiles + NT - 1) / NT, ks, (rows + 16 * RT - 1) / (16 * RT));
+  hipLaunchKernelGGL((k_gemm_s<RT, NT, NWK, 4, EPI, SPLIT, false, true>), grid, dim3(64 * NWK), 0, s, a);
+  PD_CHECK_HIP(hipGetLastError());
+  if (EPI == EPI_RESID && a.parts_out) *a.parts_out = ks;
+  return PD_OK;
+}
+
+// Tiling of a launch of more than 128 rows: the candidate that should end first.  Both kernels' times over 15 shapes
+// (192-4096 rows, K 768-11008, N 768-12288) follow, in us, with n = blocks per compute unit and kt = k-tiles of a
+// block,
+//   waves along K (k_gemm_s)   1.5 + n (0.0071 kt KiB + 0.2 RT NT) + 0.25 per further batch of 4 k-tiles of a wave
+//   shared row tiles (k_gemm_t)  4 + n (kt max(0.03 RT NT, 0.0175 KiB) + 0.35 RT NT)
+// where KiB is what a block requests per k-tile: RT NT multiplies and their operands per k-tile, and per output
+// tile the epilogue.  The first keeps no barrier in its loop and fills the chip with small tiles: 192 rows, K 768,
+// N 3072 5.7 us against 28 with 128 x 256 tiles (24 blocks); 512 rows 9.9 against 28; from about 1024 rows the
+// requests for its operands outweigh (2048 rows: 32 against 26).
+struct RowTiling { bool cut; int rt, nt, ks; double us; };
+
+template <int EPI>
+static RowTiling choose_row_tiling(int n_tiles, int KT, int rows, int max_parts, bool split) {
+  struct Cand { bool cut; int rt, nt, nwk; };
+  static const Cand cands[] = {{true, 2, 2, 4}, {true, 2, 4, 8}, {true, 2, 6, 4},
+                               {false, 4, 1, 8}, {false, 4, 2, 8}, {false, 4, 3, 8}, {false, 4, 4, 8},
+                               {false, 8, 3, 8}, {false, 8, 4, 8}};
+  RowTiling best{false, 8, 4, 1, 1e30};
+  const int parts = split ? 2 : 1;
+  for (const Cand &c : cands)
+    for (int ks = 1; ks <= (EPI == EPI_RESID ? max_parts : 1); ks *= 2) {
+      if (ks > 1 && KT / ks < 8) break;
+      const int cols = c.cut ? c.nt : 8 * c.nt, kt = (KT + ks - 1) / ks;
+      const double blocks = (double)((n_tiles + cols - 1) / cols) * ks * ((rows + 16 * c.rt - 1) / (16 * c.rt));
+      const double q = blocks / 256, n = q <= 3 ? ceil(q) : q + 0.5;
+      const double kib = (c.cut ? c.nt : 8 * c.nt) + parts * c.rt, out = c.rt * c.nt;
+      double us;
+      if (c.cut) us = 1.5 + n * (0.0071 * kt * kib + 0.2 * out) + 0.25 * ((kt + 4 * c.nwk - 1) / (4 * c.nwk) - 1);
+      else us = 4 + n * (kt * std::max(0.015 * parts * out, 0.0175 * kib) + 0.35 * out);
+      us += 0.6 * (ks - 1) * rows * (double)n_tiles * 1.3e-5;      // what the next norm kernel pays for a slice
+      if (us < best.us) best = RowTiling{c.cut, c.rt, c.nt, ks, us};
+    }
+  return best;
+}
+
 template <int EPI, bool SPLIT>
 static int launch_gemm_rows(const GemmArgs &a, int rows, hipStream_t s) {
-  auto cost = [&](int nt, double t) {
-    long b = (long)((a.n_tiles + 8 * nt - 1) / (8 * nt)) * ((rows + 127) / 128);
-    if (EPI == EPI_RESID) {     // the K slices launch_gemm_rows_nt will choose
-      int KT = a.K / 32, ks = 1;
-      while (ks < a.max_parts && b * ks < 256 && KT / (2 * ks) >= 8) ks *= 2;
-      return (double)((b * ks + 255) / 256) * t / ks;
-    }
-    return (double)((b + 255) / 256) * t;
-  };
-  double c2 = cost(2, 1.03), c3 = cost(3, 1.39), c4 = cost(4, 1.93);
-  if (c4 <= c3 && c4 <= c2) return launch_gemm_rows_nt<4, EPI, SPLIT>(a, rows, s);
-  if (c3 <= c2) return launch_gemm_rows_nt<3, EPI, SPLIT>(a, rows, s);
-  return launch_gemm_rows_nt<2, EPI, SPLIT>(a, rows, s);
+  const RowTiling t = choose_row_tiling<EPI>(a.n_tiles, a.K / 32, rows, a.max_parts, SPLIT);
+  if (t.cut) {
+    if (t.nt == 6) return launch_gemm_cut<2, 6, 4, EPI, SPLIT>(a, rows, t.ks, s);
+    if (t.nt == 4) return launch_gemm_cut<2, 4, 8, EPI, SPLIT>(a, rows, t.ks, s);
+    return launch_gemm_cut<2, 2, 4, EPI, SPLIT>(a, rows, t.ks, s);
+  }
+  if (t.rt == 8) {
+    if (t.nt == 4) return launch_gemm_t<8, 4, EPI, SPLIT>(a, rows, t.ks, s);
+    return launch_gemm_t<8, 3, EPI, SPLIT>(a, rows, t.ks, s);
+  }
+  switch (t.nt) {
+    case 1: return launch_gemm_t<4, 1, EPI, SPLIT>(a, rows, t.ks, s);
+    case 2: return launch_gemm_t<4, 2, EPI, SPLIT>(a, rows, t.ks, s);
+    case 3: return launch_gemm_t<4, 3, EPI, SPLIT>(a, rows, t.ks, s);
+    default: return launch_gemm_t<4, 4, EPI, SPLIT>(a, rows, t.ks, s);
+  }
 }
 
 // 17-128 rows against a small weight matrix (at most 16 MB: what the L2 caches hold with room to spare).  One
@@ -1037,9 +1084,11 @@ static int launch_gemm(const GemmArgs &a, int rows, hipStream_t s) {
   if (EPI == EPI_RESID_NORM || EPI == EPI_QKV_NORM)
     PD_REQUIRE(rows <= 128 && a.R <= 128, PD_EINVAL,
                "projections that prepare or finish a norm take at most 128 rows (%d)", rows);
-  if (rows > 128) {
-    PD_REQUIRE(!a.packed, PD_EINVAL, "packed activations hold at most 8 rows (%d)", rows);
-    return a.xn_lo ? launch_gemm_rows<EPI, true>(a, rows, s) : launch_gemm_rows<EPI, false>(a, rows, s);
+  if constexpr (EPI != EPI_RESID_NORM && EPI != EPI_QKV_NORM) {
+    if (rows > 128) {
+      PD_REQUIRE(!a.packed, PD_EINVAL, "packed activations hold at most 8 rows (%d)", rows);
+      return a.xn_lo ? launch_gemm_rows<EPI, true>(a, rows, s) : launch_gemm_rows<EPI, false>(a, rows, s);
+    }
   }
   if (a.packed) {
     PD_REQUIRE(rows <= 8 && a.R <= 8, PD_EINVAL, "packed activations hold at most 8 rows (%d)", rows);

@@ -1,0 +1,50 @@
+"""Launches of more than 128 rows: every tiling the projections choose from (waves along K with 2 x 2, 2 x 4 and
+2 x 6 tiles per block; row tiles shared through LDS with 4 or 8 row tiles and 1 to 4 column tiles per wave), through
+the context pass at row counts around the edges of their row groups (32, 64 and 128 rows).  The keys and values such a
+pass leaves behind decide every logit of the decode steps that follow, which are compared with the CPU oracle."""
+
+import pytest
+
+import pd_inputs as pi
+from pd_inputs.configs import WorkloadConfig, DTYPE_BF16, FFN_SWIGLU, NORM_RMSNORM, POS_ROPE
+from parity_util import oracle_run, make_decoder, compare_teacher_forced
+
+pytestmark = pytest.mark.gpu
+
+LLAMA = dict(ffn_kind=FFN_SWIGLU, norm_kind=NORM_RMSNORM, pos_kind=POS_ROPE)
+
+
+def W(name, d, heads, ff, ctx, **kw):
+    base = dict(name=name, seed=131, dtype=DTYPE_BF16, n_layer=2, d_model=d, n_head=heads, head_dim=d // heads, d_ff=ff,
+                vocab=517, batch=1, ctx_len=ctx, n_sub=2, delta_t=1, sub_tokens=2, norm_init="random", qkv_std=0.04)
+    base.update(kw)
+    return WorkloadConfig(**base)
+
+
+# row counts beside multiples of 32, 64 and 128; the comments name the tilings the sizes lead to
+CASES = [
+    W("r129", 128, 2, 256, 129),                               # waves along K, 2 x 2, K of 4 and 8 k-tiles
+    W("r191-llama", 96, 3, 352, 191, **LLAMA),                 # 2 x 2, ragged column tiles (22 gate + up tiles)
+    W("r353", 512, 4, 2048, 353),                              # 2 x 6 and 2 x 4, two K slices
+    W("r257-llama", 1024, 8, 2816, 257, qkv_std=0.02, **LLAMA),              # 2 x 4 and 2 x 6
+    W("r1025", 512, 8, 2048, 1025),                            # shared row tiles, 4 x 1
+    W("r2047-llama", 768, 12, 2048, 2047, **LLAMA),            # 4 x 3 and 4 x 4
+    W("r2049", 512, 4, 1024, 2049),                            # 4 x 2
+    W("r4095", 1024, 16, 4096, 4095),                          # 8 x 3, 8 x 4, four K slices
+]
+
+
+@pytest.mark.parametrize("single", [False, True], ids=["pairs", "single"])
+@pytest.mark.parametrize("cfg", CASES, ids=[c.name for c in CASES])
+def test_context_pass_of_many_rows(cfg, single):
+    """Both activation forms of the context pass (pairs of bf16 values, single values): the bf16 tolerance of
+    2e-2 holds for either at these widths."""
+    from paper_2506_23431_amd import binding
+    print(f"[row-tiles] {cfg}", flush=True)
+    w, ctx = pi.make_weights(cfg, threads=4), pi.make_context(cfg)
+    outs = oracle_run(cfg, w, ctx)
+    dec = make_decoder(cfg, w)
+    dec.set_option(binding.PD_OPT_CONTEXT_SPLIT_ACT, 0 if single else 1)
+    stats = compare_teacher_forced(cfg, w, ctx, dec, outs, log=lambda m: print(m, flush=True))
+    assert stats["rows"] == cfg.batch * (cfg.n_sub * (cfg.sub_tokens + 1) - 1)
+    dec.close()
