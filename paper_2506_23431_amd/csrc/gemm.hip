@@ -546,12 +546,17 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, int nt, const f
       int r = r0 + i * 16 + m;
       float best = -INFINITY;
       int bi = 0x7fffffff;
+      // kvi: the row's {flags, subsequence, limit, request}; rows without a token have no place by subsequence
+      float *dst = a.logits;
+      if (dst && a.logits_subs > 0) dst = (kvi[i].x & ROW_VALID) ? dst + ((size_t)kvi[i].w * a.logits_subs + kvi[i].y - 1) * a.ld_logits : nullptr;
+      else if (dst) dst += (size_t)r * a.ld_logits;
+      if (r >= a.R) dst = nullptr;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         int n = n0 + j;
         float t = acc[i][j];
         if (n < a.V) {
-          if (a.logits && r < a.R) a.logits[(size_t)r * a.ld_logits + n] = t;
+          if (dst) dst[n] = t;
           if (t > best) { best = t; bi = n; }
         }
       }
@@ -628,10 +633,12 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(GemmArgs a) {
   const int gk = blockIdx.y * NW_K + wk;
   const int kt0 = min(gk * a.k_share, KT), kt1 = min(kt0 + a.k_share, KT);
   // row data of the KV-append epilogue, requested now so that it arrives with the weights
-  int4 kvi[(EPI == EPI_QKV || EPI == EPI_QKV_ROPE || EPI == EPI_QKV_NORM) ? RT : 1];
-  if (EPI == EPI_QKV || EPI == EPI_QKV_ROPE || EPI == EPI_QKV_NORM) {
+  // (EPI_LM: where the row's logits go)
+  constexpr bool QKV = EPI == EPI_QKV || EPI == EPI_QKV_ROPE || EPI == EPI_QKV_NORM;
+  int4 kvi[QKV || EPI == EPI_LM ? RT : 1];
+  if (QKV || EPI == EPI_LM) {
 #pragma unroll
-    for (int i = 0; i < RT; ++i) kvi[i] = a.rt.kvinfo[(rz + i) * 16 + m];
+    for (int i = 0; i < RT; ++i) kvi[i] = (QKV ? a.rt.kvinfo : a.rt.qinfo)[(rz + i) * 16 + m];
   }
   int tile[NT];
 #pragma unroll
@@ -860,10 +867,11 @@ __global__ __launch_bounds__(512, 1) void k_gemm_t(GemmArgs a) {
   const int per_slice = (KT + (int)gridDim.y - 1) / (int)gridDim.y;
   const int kt0 = min((int)blockIdx.y * per_slice, KT), kt1 = min(kt0 + per_slice, KT);
   const int rt0 = blockIdx.z * RT, r0 = rt0 * 16;
-  int4 kvi[(EPI == EPI_QKV || EPI == EPI_QKV_ROPE) ? RT : 1];
-  if (EPI == EPI_QKV || EPI == EPI_QKV_ROPE) {
+  constexpr bool QKV = EPI == EPI_QKV || EPI == EPI_QKV_ROPE;
+  int4 kvi[QKV || EPI == EPI_LM ? RT : 1];
+  if (QKV || EPI == EPI_LM) {
 #pragma unroll
-    for (int i = 0; i < RT; ++i) kvi[i] = a.rt.kvinfo[r0 + i * 16 + m];
+    for (int i = 0; i < RT; ++i) kvi[i] = (QKV ? a.rt.kvinfo : a.rt.qinfo)[r0 + i * 16 + m];
   }
   const int nt0 = (blockIdx.x * NW + w) * NT;
   floatx4 acc[NT][RT];

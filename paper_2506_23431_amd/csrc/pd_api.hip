@@ -146,9 +146,6 @@ static size_t carve(const pd_config *g, char *base, pd_ctx *c, const pd_encdec_c
   x->att = cv.take<float>(Rp * d);
   x->hb = cv.take<float>(Rp * ff);
   x->qkv32 = cv.take<float>(Rp * 3 * d);
-  // logits exist for decode rows only (the context pass never runs the head)
-  x->logits = cv.take<float>((size_t)((B * a_max + 15) / 16 * 16) * x->vocab_pad);
-  x->scores = x->impl == 0 ? cv.take<float>((size_t)x->R_cap * H * x->kv_cap) : nullptr;
   // split partials of the attention kernel: one (max, sum, O) record of 16 queries per (request, head,
   // query group) unit and split; the launch caps its splits so that units * splits <= part_units
   {
@@ -528,9 +525,10 @@ extern "C" int pd_get_info(pd_ctx *c, int key, void *hip_stream, int64_t *value)
 static int run_layers(pd_ctx *c, int R, int A, int nreq, int req0, int kv_override,
                       hipStream_t s) {
   int rc;
-  // fp32 path: embedding kernel; matrix-core path: the first norm kernel gathers the rows itself
+  // matrix-core path: the first norm kernel gathers the rows itself; fp32 path: the first projection does, launches
+  // of many rows have them embedded
   if (c->impl == 1) c->embed_pending = true;
-  else if ((rc = launch_embed(c, R, s))) return rc;
+  else if (simple_embeds(c, R) && (rc = launch_embed(c, R, s))) return rc;
   c->pend_parts = 0;
   c->norm_fused = false;
   for (int l = 0; l < c->cfg.n_layer; ++l) {
@@ -629,10 +627,10 @@ static int enqueue_step(pd_ctx *c, float *out_logits, hipStream_t s) {
     if (r_used <= 8) { c->packed = true; R = std::min(R, std::max(r_used, 1)); }
   }
   rc = run_layers(c, R, c->A, c->B, 0, -1, s);
-  if (!rc) rc = c->impl == 1 ? mfma_head(c, R, out_logits != nullptr, s) : simple_head(c, R, s);
+  if (!rc) rc = c->impl == 1 ? mfma_head(c, R, out_logits, true, s) : simple_head(c, R, out_logits, s);
   c->packed = false;
   if (rc) return rc;
-  return launch_commit(c, out_logits, s);
+  return launch_commit(c, s);
 }
 
 // One step, optionally replayed from a captured graph (only without logits output
@@ -756,7 +754,7 @@ extern "C" int pd_teacher_forced(pd_ctx *c, const int32_t *target, int max_len, 
       if ((rc = c->arch == 1 ? encdec_decoder_layer(c, l, n, s, n, 1, b, n) : mfma_layer(c, l, n, n, 1, b, L + n, s, &am)))
         return rc;
     float *lg = out_logits + (size_t)b * rows_cap * g.vocab;
-    if ((rc = mfma_head(c, n, true, s, lg))) return rc;
+    if ((rc = mfma_head(c, n, lg, false, s))) return rc;
     if ((rc = launch_row_nll(c, lg, n, c->loss + b, s))) return rc;
     if (out_row_nll) {
       PD_CHECK_HIP(hipMemcpyAsync(out_row_nll + (size_t)b * rows_cap, c->nll, sizeof(float) * n, hipMemcpyDeviceToHost, s));

@@ -145,8 +145,6 @@ struct pd_ctx {
   float *x;                 // [R_cap][d] residual stream
   void *xn, *q, *att, *hb;  // activations (type depends on impl)
   float *qkv32;             // simple path: [R_cap][3d]
-  float *logits;            // [decode rows][vocab] internal logits (simple path / parity output)
-  float *scores;            // simple path attention scratch
   float *att_part;          // split-K partials of the attention kernel
   int part_units;           // records of 16 queries x (head_dim + 2) floats that att_part holds
   float *ypart;             // [4][R_pad][d] split-K partial sums of the O / FFN2 projections
@@ -195,13 +193,16 @@ int launch_reset_state(pd_ctx *c, hipStream_t s);
 int launch_tick(pd_ctx *c, hipStream_t s);
 int launch_prefill_rows(pd_ctx *c, int b, int p0, int n, hipStream_t s, int L, int bidir, int b_cache);
 int launch_embed(pd_ctx *c, int R, hipStream_t s);
-int launch_commit(pd_ctx *c, float *out_logits, hipStream_t s);
+int launch_commit(pd_ctx *c, hipStream_t s);
 int launch_teacher_rows(pd_ctx *c, const int32_t *tgt_dev, int b, int ML, hipStream_t s);
 int launch_row_nll(pd_ctx *c, const float *logits, int n, double *loss_dev, hipStream_t s);
 int launch_rope_table(pd_ctx *c, hipStream_t s);
 // fp32-activation path (simple.hip)
 int simple_layer(pd_ctx *c, int l, int R, int A, int nreq, int req0, int kv_override, hipStream_t s);
-int simple_head(pd_ctx *c, int R, hipStream_t s);
+// whether rows have to be embedded by a kernel of their own before the first layer (many rows)
+bool simple_embeds(const pd_ctx *c, int R);
+// logits: NULL or the caller's [B][S][vocab] buffer, as for mfma_head
+int simple_head(pd_ctx *c, int R, float *logits, hipStream_t s);
 // MFMA path (mfma.hip)
 int mfma_pack_weights(pd_ctx *c, hipStream_t s);
 int mfma_fold_norms(pd_ctx *c, hipStream_t s);
@@ -209,8 +210,9 @@ struct AttnMode;
 // mode != NULL: not a context pass (every layer runs to its end) and the attention launch takes the mode
 int mfma_layer(pd_ctx *c, int l, int R, int A, int nreq, int req0, int kv_override, hipStream_t s,
                const AttnMode *mode = nullptr);
-// logits_to != NULL: the logits of the R rows go there ([R][vocab]) instead of the internal buffer
-int mfma_head(pd_ctx *c, int R, bool want_logits, hipStream_t s, float *logits_to = nullptr);
+// logits != NULL: the rows' logits go there, [R][vocab] in row order or, by_sub, [B][S][vocab] at the place of the
+// row's request and subsequence (rows without a token write nothing)
+int mfma_head(pd_ctx *c, int R, float *logits, bool by_sub, hipStream_t s);
 // encoder-decoder form (encdec.hip)
 int encdec_pack_weights(pd_ctx *c, hipStream_t s);
 int encdec_build_tables(pd_ctx *c, int *scratch, hipStream_t s);

@@ -283,15 +283,13 @@ int launch_embed(pd_ctx *c, int R, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// commit: Algorithm 1 lines 9-13 for one request per block, plus the optional
-// copy of this step's logits to the caller's [B][S][V] buffer.
+// commit: Algorithm 1 lines 9-13 for one request per block.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void k_commit(SchedState st, RowTables rt, int32_t *row_argmax,
-                                                 const float *part_val, const int32_t *part_idx, int n_tiles,
-                                                 int S, int M, int A, int time_max, int eos, int V) {
+__global__ __launch_bounds__(1024) void k_commit(SchedState st, const float *part_val, const int32_t *part_idx,
+                                                 int n_tiles, int S, int M, int A, int time_max, int eos, int V) {
   // Everything the block needs is requested at once, before the first use, so that the kernel costs
-  // about one memory round trip: the schedule state of the request, and (matrix-core path) the
-  // winners of the vocabulary tiles of every row, whether or not the row selects a token.
+  // about one memory round trip: the schedule state of the request, and the winners of the vocabulary
+  // tiles of every row, whether or not the row selects a token.
   __shared__ int s_arg[1024];           // s_arg[a]: argmax of row a of this request (a < A <= 1024)
   const int b = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nwave = blockDim.x >> 6;
   const int done = st.done[b], t = st.step[b], k = st.k_open[b];
@@ -305,30 +303,26 @@ __global__ __launch_bounds__(1024) void k_commit(SchedState st, RowTables rt, in
   for (int a = wave; a < A; a += nwave) {
     int r = b * A + a;
     int bi = 0x7fffffff;
-    if (part_val) {
-      const float *pv = part_val + (size_t)r * n_tiles;
-      const int32_t *pi = part_idx + (size_t)r * n_tiles;
-      float best = -INFINITY;
-      for (int t0 = lane; t0 < n_tiles; t0 += 64 * 8) {
-        float v[8]; int ix[8];
+    const float *pv = part_val + (size_t)r * n_tiles;
+    const int32_t *pi = part_idx + (size_t)r * n_tiles;
+    float best = -INFINITY;
+    for (int t0 = lane; t0 < n_tiles; t0 += 64 * 8) {
+      float v[8]; int ix[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          int tt = min(t0 + 64 * u, n_tiles - 1);        // clamped: a repeated candidate changes nothing
-          v[u] = pv[tt];
-          ix[u] = pi[tt];
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (v[u] > best || (v[u] == best && ix[u] < bi)) { best = v[u]; bi = ix[u]; }
+      for (int u = 0; u < 8; ++u) {
+        int tt = min(t0 + 64 * u, n_tiles - 1);        // clamped: a repeated candidate changes nothing
+        v[u] = pv[tt];
+        ix[u] = pi[tt];
       }
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        float ov = __shfl_xor(best, o);
-        int oi = __shfl_xor(bi, o);
-        if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
-      }
-    } else {
-      bi = row_argmax[r];               // fp32 path: the argmax kernel has decided
+      for (int u = 0; u < 8; ++u)
+        if (v[u] > best || (v[u] == best && ix[u] < bi)) { best = v[u]; bi = ix[u]; }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      float ov = __shfl_xor(best, o);
+      int oi = __shfl_xor(bi, o);
+      if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
     }
     if (lane == 0) s_arg[a] = bi;
   }
@@ -366,24 +360,8 @@ __global__ __launch_bounds__(1024) void k_commit(SchedState st, RowTables rt, in
   }
 }
 
-__global__ void k_scatter_logits(float *dst, const float *src, RowTables rt, int S, int V) {
-  int r = blockIdx.x;
-  if (!(rt.flags[r] & ROW_VALID)) return;
-  size_t o = ((size_t)rt.req[r] * S + (rt.sub[r] - 1)) * V, i = (size_t)r * V;
-  for (int v = blockIdx.y * blockDim.x + threadIdx.x; v < V; v += gridDim.y * blockDim.x)
-    dst[o + v] = src[i + v];
-}
-
-int launch_commit(pd_ctx *c, float *out_logits, hipStream_t s) {
-  if (out_logits) {
-    hipLaunchKernelGGL(k_scatter_logits, dim3(c->R, 8), dim3(256), 0, s, out_logits, c->logits,
-                       c->rows, c->S, c->cfg.vocab);
-    PD_CHECK_HIP(hipGetLastError());
-  }
-  // matrix-core path: the vocabulary projection left one winner per tile; fp32 path: row_argmax is final
-  const bool tiles = c->impl == 1;
-  hipLaunchKernelGGL(k_commit, dim3(c->B), dim3(tiles ? 1024 : 256), 0, s, c->sch, c->rows, c->row_argmax,
-                     tiles ? c->lm_part_val : nullptr, tiles ? c->lm_part_idx : nullptr, c->vocab_pad / 16,
+int launch_commit(pd_ctx *c, hipStream_t s) {
+  hipLaunchKernelGGL(k_commit, dim3(c->B), dim3(1024), 0, s, c->sch, c->lm_part_val, c->lm_part_idx, c->vocab_pad / 16,
                      c->S, c->M, c->A, c->time_max, c->cfg.eos_id, c->cfg.vocab);
   PD_CHECK_HIP(hipGetLastError());
   return PD_OK;

@@ -1,8 +1,48 @@
-// fp32-activation kernels: one straightforward kernel per operation.
-// They serve dtype 0 (fp32 weights and KV cache) and, for bf16 weights whose
-// shapes the MFMA kernels do not cover, dtype 1 with fp32 activations.
-// KV cache layout on this path: K and V each [B][H][kv_cap][hd], row-major.
+// fp32-activation kernels.  They serve dtype 0 (fp32 weights and KV cache) and, for bf16 weights whose
+// shapes the bf16 matrix-core kernels do not cover, dtype 1 with fp32 activations.
+// KV cache layout on this path: K [B][H][kv_cap][hd], V [B][H][hd][kv_cap] (a lane's four values of either are then
+// consecutive in the order in which the products want them).
+//
+// All products run on the matrix cores in fp32 (16x16x4, fp32 operands and accumulators: a chain of fused
+// multiply-adds, no reduced precision anywhere).  A lane holds four consecutive contraction values of one row of
+// either operand (one 16-byte load) and feeds them to four instructions; which contraction value meets which
+// instruction does not matter as long as both operands agree.
+// The models of this path are small, so a decode step is a chain of launches of a few microseconds each and their
+// number decides: five per layer (QKV with the norm in front of it and the KV append behind it, attention, output
+// projection, the two FFN projections, the first with its norm), the embedding read by the first of them and the
+// argmax left as one winner per 16-column tile for the commit kernel.
 #include "pd_internal.h"
+
+#include <algorithm>
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// four consecutive values as fp32 (the address is aligned to the four of them)
+__device__ __forceinline__ floatx4 ld4(const float *p) { return *(const floatx4 *)p; }
+__device__ __forceinline__ floatx4 ld4(const bf16_t *p) {
+  const uint2 u = *(const uint2 *)p;
+  return floatx4{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
+                 __uint_as_float(u.y & 0xffff0000u)};
+}
+__device__ __forceinline__ floatx4 ld4(const f16_t *p) {
+  union { uint2 u; f16_t h[4]; } v;
+  v.u = *(const uint2 *)p;
+  return floatx4{(float)v.h[0], (float)v.h[1], (float)v.h[2], (float)v.h[3]};
+}
+// values k .. k+3 of a row of n; VEC: n is a multiple of 4 and the row aligned.  Beyond the row: the values at the
+// nearest place that exists (the caller multiplies them by zero or masks them).
+template <bool VEC, typename T>
+__device__ __forceinline__ floatx4 ld_row4(const T *row, int k, int n) {
+  if (VEC) return ld4(row + min(k, n - 4));
+  floatx4 v;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = ld_f32(row, (size_t)min(k + e, n - 1));
+  return v;
+}
+
+__device__ __forceinline__ floatx4 mfma_f32(float a, float b, floatx4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
 
 // ---------------------------------------------------------------------------
 // norm: xn[r] = LayerNorm(x[r]) or RMSNorm(x[r]); one block per row
@@ -38,70 +78,292 @@ __global__ void k_norm_f32(float *xn, const float *x, const float *g, const floa
 }
 
 // ---------------------------------------------------------------------------
-// linear: y[r][n] = sum_k x[r][k] * W[n][k].  One wave per output column and
-// tile of 8 rows; lanes stride over k (coalesced weight reads).
-//   EPI 0: out = y            EPI 1: out = res + y
-//   EPI 2: out = gelu_erf(y)  EPI 3: out = silu(y) * (x . W2[n])
+// linear: y[r][n] = sum_k u(x)[r][k] * W[n][k], u = identity or the norm of the row
 // ---------------------------------------------------------------------------
-template <typename WT, int EPI>
-__global__ void k_linear(float *out, const float *x, const WT *W, const WT *W2, const float *res,
-                         int R, int N, int K, int ldo) {
-  int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  int n = blockIdx.x * (blockDim.x >> 6) + wave;
-  int r0 = blockIdx.y * 8;
-  if (n >= N) return;
-  float acc[8], acc2[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) { acc[i] = 0.f; acc2[i] = 0.f; }
-  const WT *w = W + (size_t)n * K;
-  const WT *w2 = EPI == 3 ? W2 + (size_t)n * K : nullptr;
-  for (int k = lane; k < K; k += 64) {
-    float wv = ld_f32(w, k);
-    float wv2 = EPI == 3 ? ld_f32(w2, k) : 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      int r = r0 + i;
-      float xv = r < R ? x[(size_t)r * K + k] : 0.f;
-      acc[i] = fmaf(wv, xv, acc[i]);
-      if (EPI == 3) acc2[i] = fmaf(wv2, xv, acc2[i]);
+enum { LIN_STORE = 0, LIN_RESID = 1, LIN_GELU = 2, LIN_SWIGLU = 3, LIN_QKV = 4, LIN_HEAD = 5 };
+
+struct LinArgs {
+  const float *x;                     // [R][K]
+  const void *W, *W2;                 // row-major [N][K]; W2: the up matrix of LIN_SWIGLU
+  int R, N, K;
+  const float *ng, *nb; int norm_kind; float eps;   // NORM launches: gain, bias (or NULL)
+  // rows gathered instead of read (first layer): x = tok_emb[tok] (+ pos_emb[pos]); LIN_RESID: the residual, not x
+  const void *tok_emb, *pos_emb;      // tok_emb NULL: rows of x
+  RowTables rt;
+  float *out; int ldo;
+  const float *res;                   // LIN_RESID (may be out itself)
+  void *kc, *vc, *kc_lo, *vc_lo; int d, H, hd, kv_cap; int32_t *kv_sat;   // LIN_QKV
+  float *logits; int S;               // LIN_HEAD: NULL, or [B][S][N] addressed by a row's request and subsequence
+  float *part_val; int32_t *part_idx; int n_tiles;
+};
+
+// a row of the residual stream, read or gathered
+template <typename WT>
+struct RowSrc {
+  const float *x; const WT *te, *pe; bool zero;
+  __device__ __forceinline__ RowSrc(const LinArgs &a, const float *base, int r, int ld, bool may_gather)
+      : x(base + (size_t)r * ld), te(nullptr), pe(nullptr), zero(false) {
+    if (may_gather && a.tok_emb) {
+      const int fl = a.rt.flags[r], tok = a.rt.tok[r], pos = a.rt.pos[r];      // independent loads
+      zero = !(fl & ROW_VALID);
+      te = (const WT *)a.tok_emb + (zero ? 0 : (size_t)tok * ld);
+      if (a.pos_emb) pe = (const WT *)a.pos_emb + (zero ? 0 : (size_t)pos * ld);
     }
   }
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    for (int o = 32; o > 0; o >>= 1) {
-      acc[i] += __shfl_xor(acc[i], o);
-      if (EPI == 3) acc2[i] += __shfl_xor(acc2[i], o);
-    }
+  template <bool VEC> __device__ __forceinline__ floatx4 at(int k, int n) const {
+    if (!te) return ld_row4<VEC>(x, k, n);
+    floatx4 v = ld_row4<VEC>(te, k, n);
+    if (pe) v += ld_row4<VEC>(pe, k, n);
+    return zero ? floatx4{0.f, 0.f, 0.f, 0.f} : v;
   }
-  if (lane == 0) {
+};
+
+// A block owns one 16-column tile and RT tiles of 16 rows; its NW waves cut K in steps of 16, the partial tiles are
+// summed through LDS.  VPL > 0: the rows are normalised first (K <= 256 VPL).  Every wave reads 16 / NW rows once,
+// whole (VPL quads per lane), takes mean and variance in registers (two passes) and leaves the normalised row in LDS;
+// the first weights are requested before that.  Bound by latency at the sizes of this path: enough waves that each
+// has one or two batches of requests (512 x 2048, 12 rows: 13.5 us with a wave per column, now 6-7).
+template <typename WT, typename KT, int EPI, int NW, int RT, int VPL, bool VEC>
+__global__ __launch_bounds__(64 * NW) void k_lin(LinArgs a) {
+  constexpr bool NORM = VPL > 0;
+  constexpr int NT = EPI == LIN_SWIGLU ? 2 : 1, U = 4;
+  constexpr int XLD = NORM ? 256 * VPL + 4 : 4;      // (+ 4: the 16 rows of a step lie in different banks)
+  static_assert(!NORM || RT == 1, "row statistics are taken for one row tile");
+  __shared__ floatx4 red[NW][NT * RT][64];
+  __shared__ float sm_x[NORM ? 16 : 1][XLD];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+  const int r0 = blockIdx.y * 16 * RT, n0 = blockIdx.x * 16, K = a.K;
+  const int steps = (K + 15) >> 4, share = (steps + NW - 1) / NW;
+  const int s0 = min(w * share, steps), s1 = min(s0 + share, steps);
+  const WT *wrow[NT];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      int r = r0 + i;
-      if (r >= R) break;
-      float y = acc[i];
-      if (EPI == 1) y += res[(size_t)r * ldo + n];
-      if (EPI == 2) y = 0.5f * y * (1.f + erff(y * 0.70710678118654752f));
-      if (EPI == 3) y = y / (1.f + expf(-y)) * acc2[i];
-      out[(size_t)r * ldo + n] = y;
+  for (int t = 0; t < NT; ++t) wrow[t] = (const WT *)(t ? a.W2 : a.W) + (size_t)min(n0 + m, a.N - 1) * K;
+  // weights of U steps; steps and values past the end are zero
+  auto load_w = [&](floatx4 (&wv)[NT][U], int s) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = (s + u) * 16 + 4 * g;
+        floatx4 v = ld_row4<VEC>(wrow[t], k, K);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) wv[t][u][e] = (s + u < s1 && k + e < K) ? v[e] : 0.f;
+      }
+  };
+  floatx4 wv[NT][U];
+  load_w(wv, s0);
+  // what the finishing waves need from memory is requested now: the residual rows, where a row's results go
+  floatx4 res = floatx4{0.f, 0.f, 0.f, 0.f};
+  int4 info = make_int4(0, 0, 0, 0);
+  if (w < RT) {
+    const int r = min(r0 + w * 16 + m, a.R - 1);
+    if (EPI == LIN_RESID) {
+      const RowSrc<WT> src(a, a.res, r, a.N, true);
+      res = src.template at<false>(n0 + 4 * g, a.N);
+    }
+    if (EPI == LIN_QKV) info = a.rt.kvinfo[r];        // {flags, req, slot, pos}
+    if (EPI == LIN_HEAD) info = a.rt.qinfo[r];        // {flags, sub, lim, req}
+  }
+  if constexpr (NORM) {
+    constexpr int RPW = 16 / NW;      // rows per wave
+    floatx4 xv[RPW][VPL], gv[VPL], bv[VPL];
+    float s[RPW], q[RPW];
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) {
+      const RowSrc<WT> src(a, a.x, min(r0 + w * RPW + i, a.R - 1), K, true);
+#pragma unroll
+      for (int v = 0; v < VPL; ++v) xv[i][v] = src.template at<VEC>(4 * (lane + 64 * v), K);
+    }
+#pragma unroll
+    for (int v = 0; v < VPL; ++v) {
+      gv[v] = ld_row4<VEC>(a.ng, 4 * (lane + 64 * v), K);
+      bv[v] = a.nb ? ld_row4<VEC>(a.nb, 4 * (lane + 64 * v), K) : floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) {
+      s[i] = 0.f;
+      if (a.norm_kind == 0)
+#pragma unroll
+        for (int v = 0; v < VPL; ++v)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) s[i] += 4 * (lane + 64 * v) + e < K ? xv[i][v][e] : 0.f;
+    }
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+      for (int i = 0; i < RPW; ++i) s[i] += __shfl_xor(s[i], o);
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) {
+      s[i] /= K;
+      q[i] = 0.f;
+#pragma unroll
+      for (int v = 0; v < VPL; ++v)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { const float t = xv[i][v][e] - s[i]; q[i] += 4 * (lane + 64 * v) + e < K ? t * t : 0.f; }
+    }
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+      for (int i = 0; i < RPW; ++i) q[i] += __shfl_xor(q[i], o);
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) {
+      const float rstd = rsqrtf(q[i] / K + a.eps);
+#pragma unroll
+      for (int v = 0; v < VPL; ++v) {
+        floatx4 y;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] = 4 * (lane + 64 * v) + e < K ? (xv[i][v][e] - s[i]) * rstd * gv[v][e] + bv[v][e] : 0.f;
+        *(floatx4 *)&sm_x[w * RPW + i][4 * (lane + 64 * v)] = y;
+      }
+    }
+    __syncthreads();
+  }
+  floatx4 acc[NT][RT][4];       // one per value of a lane's quad: short chains of additions
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[t][i][e] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int s = s0; s < s1; s += U) {
+    floatx4 xv[RT][U];
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+      const RowSrc<WT> src(a, a.x, min(r0 + i * 16 + m, a.R - 1), K, false);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = (s + u) * 16 + 4 * g;
+        xv[i][u] = NORM ? *(const floatx4 *)&sm_x[m][min(k, XLD - 4)] : src.template at<VEC>(k, K);
+      }
+    }
+    floatx4 wn[NT][U];
+    if (s + U < s1) load_w(wn, s + U);          // the same for the whole wave
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int t = 0; t < NT; ++t) acc[t][i][e] = mfma_f32(wv[t][u][e], xv[i][u][e], acc[t][i][e]);
+    if (s + U < s1)
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int u = 0; u < U; ++u) wv[t][u] = wn[t][u];
+  }
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int i = 0; i < RT; ++i) red[w][t * RT + i][lane] = (acc[t][i][0] + acc[t][i][1]) + (acc[t][i][2] + acc[t][i][3]);
+  __syncthreads();
+  // wave i finishes row tile i: lane (m, g) holds y[r][n .. n + 3], r = r0 + 16 i + m, n = n0 + 4 g
+  static_assert(RT <= NW, "one row tile per finishing wave");
+  if (w < RT) {
+    const int i = w;
+    floatx4 y = red[0][i][lane], y2 = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int v = 1; v < NW; ++v) y += red[v][i][lane];
+    if (EPI == LIN_SWIGLU) {
+      y2 = red[0][RT + i][lane];
+#pragma unroll
+      for (int v = 1; v < NW; ++v) y2 += red[v][RT + i][lane];
+    }
+    const int r = r0 + i * 16 + m, n = n0 + 4 * g;
+    const bool in = r < a.R;
+    if (EPI == LIN_HEAD) {
+      float best = -INFINITY;
+      int bi = 0x7fffffff;
+      float *dst = a.logits && in && (info.x & ROW_VALID) ? a.logits + ((size_t)info.w * a.S + (info.y - 1)) * a.N : nullptr;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (n + j < a.N) {
+          if (dst) dst[n + j] = y[j];
+          if (y[j] > best) { best = y[j]; bi = n + j; }
+        }
+#pragma unroll
+      for (int o = 16; o <= 32; o <<= 1) {            // the tile's winner, lowest index on ties
+        const float ov = __shfl_xor(best, o);
+        const int oi = __shfl_xor(bi, o);
+        if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
+      }
+      if (g == 0 && in) {
+        a.part_val[(size_t)r * a.n_tiles + blockIdx.x] = best;
+        a.part_idx[(size_t)r * a.n_tiles + blockIdx.x] = bi;
+      }
+      return;
+    }
+    if (!in) return;
+    if (EPI == LIN_QKV) {
+      if (!(info.x & ROW_VALID)) return;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (n + j >= a.N) continue;
+        const int sec = (n + j) / a.d, c = (n + j) - sec * a.d, h = c / a.hd;
+        if (sec == 0) { a.out[(size_t)r * a.ldo + n + j] = y[j]; continue; }
+        const size_t slab = ((size_t)info.y * a.H + h) * a.kv_cap * a.hd, dim = c - h * a.hd;
+        const size_t o = slab + (sec == 1 ? (size_t)info.z * a.hd + dim : dim * a.kv_cap + info.z);
+        KT *cache = (KT *)(sec == 1 ? a.kc : a.vc), *low = (KT *)(sec == 1 ? a.kc_lo : a.vc_lo);
+        if (sizeof(KT) == 2 && fabsf(y[j]) > 65504.f) atomicAdd(a.kv_sat, 1);   // stored saturated
+        st_f32(cache, o, y[j]);
+        if (low) {            // what the rounding of the store above left out
+          KT t;
+          st_f32(&t, 0, y[j]);
+          st_f32(low, o, y[j] - ld_f32(&t, 0));
+        }
+      }
+      return;
+    }
+    float *dst = a.out + (size_t)r * a.ldo + n;
+    if (EPI == LIN_RESID) y += res;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (n + j >= a.N) continue;
+      float v = y[j];
+      if (EPI == LIN_GELU) v = 0.5f * v * (1.f + erff(v * 0.70710678118654752f));
+      if (EPI == LIN_SWIGLU) v = v / (1.f + expf(-v)) * y2[j];
+      dst[j] = v;
     }
   }
 }
 
-template <typename WT, int EPI>
-static int run_linear(float *out, const float *x, const void *W, const void *W2, const float *res,
-                      int R, int N, int K, hipStream_t s) {
-  dim3 grid((N + 3) / 4, (R + 7) / 8);
-  hipLaunchKernelGGL((k_linear<WT, EPI>), grid, dim3(256), 0, s, out, x, (const WT *)W,
-                     (const WT *)W2, res, R, N, K, N);
+template <typename WT, typename KT, int EPI, int NW, int RT, int VPL>
+static void launch_lin(const LinArgs &a, int n_tiles, bool vec, hipStream_t s) {
+  const dim3 grid(n_tiles, (a.R + 16 * RT - 1) / (16 * RT));
+  if (vec) hipLaunchKernelGGL((k_lin<WT, KT, EPI, NW, RT, VPL, true>), grid, dim3(64 * NW), 0, s, a);
+  else hipLaunchKernelGGL((k_lin<WT, KT, EPI, NW, RT, VPL, false>), grid, dim3(64 * NW), 0, s, a);
+}
+
+// Wide loads where the rows allow them: K a multiple of 4 and every matrix aligned.  Waves along K: 16 steps each up
+// to K = 1024, 16 waves beyond.  Four row tiles per block only where that still leaves 128 blocks (a block's
+// multiplies bound it otherwise: 512 x 2048, 128 rows, 64 blocks 17.9 us, 256 blocks of one row tile 11.2;
+// 1536 x 512 192 blocks 10.7, 768 blocks 12.4).
+template <typename WT, typename KT, int EPI>
+static int run_lin(const LinArgs &a, int n_tiles, hipStream_t s) {
+  const uintptr_t mis = (uintptr_t)a.W | (uintptr_t)a.W2 | (uintptr_t)a.tok_emb | (uintptr_t)a.pos_emb;
+  const uintptr_t misv = (uintptr_t)a.ng | (uintptr_t)a.nb;
+  const bool vec = a.K % 4 == 0 && mis % (4 * sizeof(WT)) == 0 && misv % 16 == 0;
+  if constexpr (EPI != LIN_RESID) {
+    if (a.ng) {
+      if (a.K <= 256) launch_lin<WT, KT, EPI, 4, 1, 1>(a, n_tiles, vec, s);
+      else if (a.K <= 512) launch_lin<WT, KT, EPI, 8, 1, 2>(a, n_tiles, vec, s);
+      else launch_lin<WT, KT, EPI, 16, 1, 4>(a, n_tiles, vec, s);
+      PD_CHECK_HIP(hipGetLastError());
+      return PD_OK;
+    }
+  }
+  if (a.R > 32 && (long)n_tiles * ((a.R + 63) / 64) >= 128) launch_lin<WT, KT, EPI, 8, 4, 0>(a, n_tiles, vec, s);
+  else if (a.K <= 256) launch_lin<WT, KT, EPI, 4, 1, 0>(a, n_tiles, vec, s);
+  else if (a.K <= 1024) launch_lin<WT, KT, EPI, 8, 1, 0>(a, n_tiles, vec, s);
+  else launch_lin<WT, KT, EPI, 16, 1, 0>(a, n_tiles, vec, s);
   PD_CHECK_HIP(hipGetLastError());
   return PD_OK;
 }
 
 template <int EPI>
-static int linear(pd_ctx *c, float *out, const float *x, const void *W, const void *W2,
-                  const float *res, int R, int N, int K, hipStream_t s) {
-  return c->cfg.dtype == 0 ? run_linear<float, EPI>(out, x, W, W2, res, R, N, K, s)
-                           : run_linear<bf16_t, EPI>(out, x, W, W2, res, R, N, K, s);
+static int linear(pd_ctx *c, LinArgs a, const void *W, const void *W2, int R, int N, int K, hipStream_t s,
+                  int n_tiles = 0) {
+  a.W = W; a.W2 = W2; a.R = R; a.N = N; a.K = K;
+  if (!n_tiles) n_tiles = (N + 15) / 16;
+  return c->cfg.dtype == 0 ? run_lin<float, float, EPI>(a, n_tiles, s) : run_lin<bf16_t, f16_t, EPI>(a, n_tiles, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -115,200 +377,266 @@ __global__ void k_qkv_post(float *qkv, KT *kc, KT *vc, KT *kc_lo, KT *vc_lo, Row
   if (!(rt.flags[r] & ROW_VALID)) return;
   float *row = qkv + (size_t)r * 3 * d;
   int half = hd / 2;
-  size_t base = (size_t)rt.req[r] * H * kv_cap * hd + (size_t)rt.slot[r] * hd;
-  const float *cs = rope_cs ? rope_cs + (size_t)rt.pos[r] * half * 2 : nullptr;
+  const size_t base = (size_t)rt.req[r] * H * kv_cap * hd, slot = rt.slot[r];
+  const float *cs = rope_cs + (size_t)rt.pos[r] * half * 2;
   for (int i = threadIdx.x; i < H * half; i += blockDim.x) {
     int h = i / half, j = i % half;
     float q1 = row[h * hd + j], q2 = row[h * hd + j + half];
     float k1 = row[d + h * hd + j], k2 = row[d + h * hd + j + half];
-    if (cs) {
-      float cc = cs[2 * j], ss = cs[2 * j + 1];
-      float a = q1 * cc - q2 * ss, b = q2 * cc + q1 * ss;
-      q1 = a; q2 = b;
-      a = k1 * cc - k2 * ss; b = k2 * cc + k1 * ss;
-      k1 = a; k2 = b;
-      row[h * hd + j] = q1; row[h * hd + j + half] = q2;
-    }
-    size_t o = base + (size_t)h * kv_cap * hd;
+    float cc = cs[2 * j], ss = cs[2 * j + 1];
+    float a = q1 * cc - q2 * ss, b = q2 * cc + q1 * ss;
+    q1 = a; q2 = b;
+    a = k1 * cc - k2 * ss; b = k2 * cc + k1 * ss;
+    k1 = a; k2 = b;
+    row[h * hd + j] = q1; row[h * hd + j + half] = q2;
+    const size_t o = base + ((size_t)h * kv_cap + slot) * hd, ov = base + ((size_t)h * hd + j) * kv_cap + slot;
+    const size_t ov2 = ov + (size_t)half * kv_cap;
     float v1 = row[2 * d + h * hd + j], v2 = row[2 * d + h * hd + j + half];
     if (sizeof(KT) == 2) {   // half cache: count what is stored saturated
       int n_sat = (fabsf(k1) > 65504.f) + (fabsf(k2) > 65504.f) + (fabsf(v1) > 65504.f) + (fabsf(v2) > 65504.f);
       if (n_sat) atomicAdd(kv_sat, n_sat);
     }
     st_f32(kc, o + j, k1); st_f32(kc, o + j + half, k2);
-    st_f32(vc, o + j, v1); st_f32(vc, o + j + half, v2);
+    st_f32(vc, ov, v1); st_f32(vc, ov2, v2);
     if (kc_lo) {      // low halves: what the rounding of the stores above left out
       st_f32(kc_lo, o + j, k1 - ld_f32(kc, o + j)); st_f32(kc_lo, o + j + half, k2 - ld_f32(kc, o + j + half));
-      st_f32(vc_lo, o + j, v1 - ld_f32(vc, o + j)); st_f32(vc_lo, o + j + half, v2 - ld_f32(vc, o + j + half));
+      st_f32(vc_lo, ov, v1 - ld_f32(vc, ov)); st_f32(vc_lo, ov2, v2 - ld_f32(vc, ov2));
     }
   }
 }
 
 // ---------------------------------------------------------------------------
-// attention: one block per (row, head).  Key j of the row's request is visible
-// when j < lim[r] (context part) or when it is a generated-side slot (j >= L,
-// j < kv_len) whose subsequence index is <= the row's (Section 3.2).
-// Three passes over a score scratch in global memory.
+// attention: block = (head, request and group of 16 of its rows), its waves take tiles of 16 keys in turn and are
+// merged through LDS.  Key j of the row's request is visible when j < lim[r] (context part) or when it is a
+// generated-side slot (j >= L, j < n) whose subsequence index is <= the row's (Section 3.2).
+// Per key tile: S^T (16 keys x 16 queries) from the keys' rows and the queries, mask, online softmax per query,
+// O^T += V^T P^T; the score tile's registers are the operand of the second product.  Keys and values are requested
+// together, before either is used.  Bound by the one compute unit a (request, head) runs on: 32 products of 32 clocks
+// per key tile, so 16 waves and a tile or two each (12 rows, 8 heads of 64, 330 keys: 12 us; a thread per key over
+// uncoalesced key rows took 31; requesting the next tile ahead costs the registers of half the waves, 13-17 us).
 // ---------------------------------------------------------------------------
+struct AttnF32Args {
+  float *out; const float *qkv;
+  const void *kc, *vc, *kc_lo, *vc_lo;
+  RowTables rt; const int32_t *kv_len; const uint16_t *gen_sub;
+  int kv_override, d, H, hd, kv_cap, gen_stride, L, A, nqg, req0;
+  float scale;
+};
+
+template <typename KT, int NHB, int NW, bool VEC>      // NHB: 16-dim blocks of a head (hd <= 16 NHB)
+__global__ __launch_bounds__(64 * NW) void k_attn_f32(AttnF32Args a) {
+  __shared__ floatx4 sm_o[NW][NHB][64];
+  __shared__ float sm_m[NW][16], sm_l[NW][16];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+  const int h = blockIdx.x, reqi = blockIdx.y / a.nqg, qg = blockIdx.y % a.nqg, req = a.req0 + reqi, hd = a.hd;
+  const int qa = qg * 16 + m;
+  const int r = reqi * a.A + min(qa, a.A - 1);          // clamped: loads stay in bounds
+  const int4 qi = a.rt.qinfo[r];                        // {flags, sub, lim, req}
+  const bool valid = qa < a.A && (qi.x & ROW_VALID);
+  const int n = a.kv_override >= 0 ? a.kv_override : a.kv_len[req];
+  const int lim = valid ? min(qi.z, n) : 0, sub = valid ? qi.y : -1;
+  // keys some query of the group sees
+  int reach = valid ? (n > a.L && sub >= 1 ? n : lim) : 0;
+  for (int o = 1; o < 16; o <<= 1) reach = max(reach, __shfl_xor(reach, o));
+  const int tiles = __builtin_amdgcn_readfirstlane((reach + 15) >> 4);
+  const size_t base = ((size_t)req * a.H + h) * a.kv_cap * hd;
+  const KT *K = (const KT *)a.kc + base, *V = (const KT *)a.vc + base;
+  const KT *Kl = a.kc_lo ? (const KT *)a.kc_lo + base : nullptr, *Vl = a.vc_lo ? (const KT *)a.vc_lo + base : nullptr;
+  const uint16_t *gs = a.gen_sub + (size_t)req * a.gen_stride;
+  const int L8 = a.L & ~7;            // entry of key slot j >= L is j - L8
+  floatx4 q[NHB];
+#pragma unroll
+  for (int c = 0; c < NHB; ++c) {
+    const floatx4 v = ld_row4<VEC>(a.qkv + (size_t)r * 3 * a.d + h * hd, 16 * c + 4 * g, hd);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) q[c][e] = 16 * c + 4 * g + e < hd ? v[e] : 0.f;
+  }
+  float m_run = -INFINITY, l_run = 0.f;
+  floatx4 o_acc[NHB];
+#pragma unroll
+  for (int i = 0; i < NHB; ++i) o_acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int t = w; t < tiles; t += NW) {
+    const int key0 = t * 16, key = key0 + 4 * g;
+    floatx4 kf[NHB], vf[NHB];         // key m, dims 16 c + 4 g .. + 3;  dim 16 i + m, keys 4 g .. + 3
+    int tag[4];
+    const size_t krow = (size_t)min(key0 + m, n - 1) * hd;
+#pragma unroll
+    for (int c = 0; c < NHB; ++c) {
+      kf[c] = ld_row4<VEC>(K + krow, 16 * c + 4 * g, hd);
+      if (Kl) kf[c] += ld_row4<VEC>(Kl + krow, 16 * c + 4 * g, hd);
+    }
+#pragma unroll
+    for (int i = 0; i < NHB; ++i) {
+      const size_t vrow = (size_t)min(16 * i + m, hd - 1) * a.kv_cap;     // (kv_cap is a multiple of 64)
+      vf[i] = ld_row4<true>(V + vrow, key, a.kv_cap);
+      if (Vl) vf[i] += ld_row4<true>(Vl + vrow, key, a.kv_cap);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) tag[e] = gs[min(max(key + e - L8, 0), a.gen_stride - 1)];
+    floatx4 se[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) se[e] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < NHB; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) se[e] = mfma_f32(kf[c][e], q[c][e], se[e]);      // (dims past the head meet a zero query)
+    floatx4 s = (se[0] + se[1]) + (se[2] + se[3]);
+    // lane (query m, g), register j  <->  key key0 + 4 g + j
+    float mloc = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int key = key0 + 4 * g + j;
+      const bool vis = key < lim || (key >= a.L && key < n && tag[j] <= sub);
+      s[j] = vis ? s[j] * a.scale : -INFINITY;
+      mloc = fmaxf(mloc, s[j]);
+    }
+    mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
+    mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+    const float m_new = fmaxf(m_run, mloc);
+    const float m_ref = m_new == -INFINITY ? 0.f : m_new;      // nothing visible yet: exp(-inf) = 0, never NaN
+    const float alpha = expf(m_run - m_ref);
+    float p[4], psum = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { p[j] = expf(s[j] - m_ref); psum += p[j]; }
+    l_run = l_run * alpha + psum;
+    m_run = m_new;
+    if (__any(alpha != 1.f))
+#pragma unroll
+      for (int i = 0; i < NHB; ++i) o_acc[i] *= alpha;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < NHB; ++i)       // (slots past the last key hold what an earlier request left there)
+        o_acc[i] = mfma_f32(key0 + 4 * g + e < n ? vf[i][e] : 0.f, p[e], o_acc[i]);
+  }
+  l_run += __shfl_xor(l_run, 16);
+  l_run += __shfl_xor(l_run, 32);
+  if (g == 0) { sm_m[w][m] = m_run; sm_l[w][m] = l_run; }
+#pragma unroll
+  for (int i = 0; i < NHB; ++i) sm_o[w][i][lane] = o_acc[i];
+  __syncthreads();
+  float M = -INFINITY, f[NW], l = 0.f;
+#pragma unroll
+  for (int v = 0; v < NW; ++v) M = fmaxf(M, sm_m[v][m]);
+#pragma unroll
+  for (int v = 0; v < NW; ++v) {
+    f[v] = sm_m[v][m] == -INFINITY ? 0.f : expf(sm_m[v][m] - M);
+    l += f[v] * sm_l[v][m];
+  }
+  if (!valid) return;
+  // lane (query m, g) of dim block i: dims 16 i + 4 g .. + 3
+  for (int i = w; i < NHB; i += NW) {
+    floatx4 o = f[0] * sm_o[0][i][lane];
+#pragma unroll
+    for (int v = 1; v < NW; ++v) o += f[v] * sm_o[v][i][lane];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (16 * i + 4 * g + j < hd) a.out[(size_t)r * a.d + h * hd + 16 * i + 4 * g + j] = o[j] / l;
+  }
+}
+
 template <typename KT>
-__global__ void k_attn(float *out, const float *qkv, const KT *kc, const KT *vc, const KT *kc_lo,
-                       const KT *vc_lo, float *scores,
-                       RowTables rt, const int32_t *kv_len, const uint16_t *gen_sub, int kv_override,
-                       int d, int H, int hd, int kv_cap, int gen_stride, int L, float scale) {
-  extern __shared__ float sm[];     // q[hd] | red[16] | o[blockDim.x]
-  float *qs = sm, *red = sm + hd, *osum = sm + hd + 16;
-  int r = blockIdx.x, h = blockIdx.y;
-  if (!(rt.flags[r] & ROW_VALID)) return;
-  int req = rt.req[r], lim = rt.lim[r], sub = rt.sub[r];
-  int n = kv_override >= 0 ? kv_override : kv_len[req];
-  const KT *K = kc + ((size_t)req * H + h) * kv_cap * hd;
-  const KT *V = vc + ((size_t)req * H + h) * kv_cap * hd;
-  const KT *Kl = kc_lo ? kc_lo + ((size_t)req * H + h) * kv_cap * hd : nullptr;
-  const KT *Vl = vc_lo ? vc_lo + ((size_t)req * H + h) * kv_cap * hd : nullptr;
-  const uint16_t *gs = gen_sub + (size_t)req * gen_stride;
-  const int L8 = L & ~7;            // entry of key slot j >= L is j - L8
-  float *sc = scores + ((size_t)r * H + h) * kv_cap;
-  for (int c = threadIdx.x; c < hd; c += blockDim.x) qs[c] = qkv[(size_t)r * 3 * d + h * hd + c];
-  __syncthreads();
-  float mx = -INFINITY;
-  for (int j = threadIdx.x; j < n; j += blockDim.x) {
-    bool vis = j < lim || (j >= L && (int)gs[j - L8] <= sub);
-    float s = -INFINITY;
-    if (vis) {
-      s = 0.f;
-      for (int c = 0; c < hd; ++c) {
-        float kv = ld_f32(K, (size_t)j * hd + c);
-        if (Kl) kv += ld_f32(Kl, (size_t)j * hd + c);
-        s = fmaf(qs[c], kv, s);
-      }
-      s *= scale;
-    }
-    sc[j] = s;
-    mx = fmaxf(mx, s);
-  }
-  for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
-  __syncthreads();
-  for (int i = 0; i < (int)(blockDim.x >> 6); ++i) mx = fmaxf(mx, red[i]);
-  float sum = 0.f;
-  for (int j = threadIdx.x; j < n; j += blockDim.x) {
-    float p = sc[j] == -INFINITY ? 0.f : expf(sc[j] - mx);
-    sc[j] = p;
-    sum += p;
-  }
-  sum = block_sum(sum, red);        // contains the barriers that publish sc[]
-  // thread (g, c): channel c, keys g, g + G, ...
-  int G = blockDim.x / hd, g = threadIdx.x / hd, c = threadIdx.x % hd;
-  float acc = 0.f;
-  if (g < G)
-    for (int j = g; j < n; j += G) {
-      float vv = ld_f32(V, (size_t)j * hd + c);
-      if (Vl) vv += ld_f32(Vl, (size_t)j * hd + c);
-      acc = fmaf(sc[j], vv, acc);
-    }
-  osum[threadIdx.x] = acc;
-  __syncthreads();
-  if (threadIdx.x < hd) {
-    float t = 0.f;
-    for (int i = 0; i < G; ++i) t += osum[i * hd + threadIdx.x];
-    out[(size_t)r * d + h * hd + threadIdx.x] = t / sum;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// argmax over a logits row, lowest index on ties; one block per row
-// ---------------------------------------------------------------------------
-__global__ void k_argmax(int32_t *row_argmax, const float *logits, const int32_t *flags, int V) {
-  __shared__ float sv[256];
-  __shared__ int si[256];
-  int r = blockIdx.x;
-  if (!(flags[r] & ROW_VALID)) return;
-  const float *p = logits + (size_t)r * V;
-  float best = -INFINITY;
-  int bi = 0x7fffffff;
-  for (int v = threadIdx.x; v < V; v += blockDim.x) {
-    float x = p[v];
-    if (x > best) { best = x; bi = v; }      // strided ascending scan keeps the lowest index
-  }
-  sv[threadIdx.x] = best; si[threadIdx.x] = bi;
-  __syncthreads();
-  for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) {
-      float ov = sv[threadIdx.x + o]; int oi = si[threadIdx.x + o];
-      if (ov > sv[threadIdx.x] || (ov == sv[threadIdx.x] && oi < si[threadIdx.x])) {
-        sv[threadIdx.x] = ov; si[threadIdx.x] = oi;
-      }
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) row_argmax[r] = si[0];
+static int attention_f32(const AttnF32Args &a, int nreq, hipStream_t s) {
+  const dim3 grid(a.H, nreq * a.nqg);
+  const bool vec = a.hd % 4 == 0;       // rows of q, keys and values then start at multiples of 16 (half: 8) bytes
+#define PD_ATTN_F32(NHB, NW)                                                                                  \
+  do {                                                                                                        \
+    if (vec) hipLaunchKernelGGL((k_attn_f32<KT, NHB, NW, true>), grid, dim3(64 * NW), 0, s, a);               \
+    else hipLaunchKernelGGL((k_attn_f32<KT, NHB, NW, false>), grid, dim3(64 * NW), 0, s, a);                  \
+  } while (0)
+  // waves per block: what the registers of a wave leave room for
+  if (a.hd <= 16) PD_ATTN_F32(1, 16);
+  else if (a.hd <= 32) PD_ATTN_F32(2, 16);
+  else if (a.hd <= 64) PD_ATTN_F32(4, 16);
+  else if (a.hd <= 128) PD_ATTN_F32(8, 8);
+  else PD_ATTN_F32(16, 4);
+#undef PD_ATTN_F32
+  PD_CHECK_HIP(hipGetLastError());
+  return PD_OK;
 }
 
 // ---------------------------------------------------------------------------
 // one transformer layer / the head, as sequences of launches
 // ---------------------------------------------------------------------------
-int simple_layer(pd_ctx *c, int l, int R, int A, int nreq, int req0, int kv_override,
-                 hipStream_t s) {
-  (void)A; (void)nreq; (void)req0;
+// At most 32 rows (decode steps) of up to 1024 values: the norms are taken inside the projections that follow them and the first layer
+// gathers its rows from the embedding tables.  With more rows a norm kernel of its own and tiles of 64 rows per block
+// are faster (every block would take the statistics of its rows again).
+static bool norm_inside(const pd_ctx *c, int R) { return R <= 32 && c->cfg.d_model <= 1024; }
+
+bool simple_embeds(const pd_ctx *c, int R) { return !norm_inside(c, R); }
+
+static int normed(pd_ctx *c, LinArgs &a, const float *gain, const float *bias, int R, hipStream_t s) {
   const pd_config &g = c->cfg;
-  const LayerPtrs &lw = c->layers[l];
-  int d = g.d_model, ff = g.d_ff, H = g.n_head, hd = g.head_dim;
-  float *xn = (float *)c->xn, *att = (float *)c->att, *hb = (float *)c->hb;
-  int rc;
-  hipLaunchKernelGGL(k_norm_f32, dim3(R), dim3(256), 0, s, xn, c->x, lw.n1g, lw.n1b, d, g.norm_kind,
+  if (norm_inside(c, R)) {
+    a.x = c->x; a.ng = gain; a.nb = g.norm_kind == 0 ? bias : nullptr; a.norm_kind = g.norm_kind; a.eps = g.norm_eps;
+    return PD_OK;
+  }
+  hipLaunchKernelGGL(k_norm_f32, dim3(R), dim3(256), 0, s, (float *)c->xn, c->x, gain, bias, g.d_model, g.norm_kind,
                      g.norm_eps, c->rows.flags);
   PD_CHECK_HIP(hipGetLastError());
-  if ((rc = linear<0>(c, c->qkv32, xn, lw.wqkv, nullptr, nullptr, R, 3 * d, d, s))) return rc;
-  const float *cs = g.pos_kind == 1 ? c->rope_cs : nullptr;
-  float scale = 1.0f / sqrtf((float)hd);
-  size_t shm = (hd + 16 + 256) * sizeof(float);
-  // context pass, last layer: only its keys and values are ever used
-  const bool kv_only = kv_override >= 0 && l == g.n_layer - 1;
-  if (g.dtype == 0) {
-    hipLaunchKernelGGL(k_qkv_post<float>, dim3(R), dim3(256), 0, s, c->qkv32, (float *)lw.kc,
-                       (float *)lw.vc, (float *)nullptr, (float *)nullptr, c->rows, cs, d, H, hd,
-                       c->kv_cap, c->kv_sat);
-    if (!kv_only) hipLaunchKernelGGL(k_attn<float>, dim3(R, H), dim3(256), shm, s, att, c->qkv32,
-                       (const float *)lw.kc, (const float *)lw.vc, (const float *)nullptr,
-                       (const float *)nullptr, c->scores, c->rows,
-                       c->sch.kv_len, c->sch.gen_sub, kv_override, d, H, hd, c->kv_cap, c->gen_stride,
-                       c->L, scale);
-  } else {
-    hipLaunchKernelGGL(k_qkv_post<f16_t>, dim3(R), dim3(256), 0, s, c->qkv32, (f16_t *)lw.kc,
-                       (f16_t *)lw.vc, (f16_t *)lw.kc_lo, (f16_t *)lw.vc_lo, c->rows, cs, d, H, hd,
-                       c->kv_cap, c->kv_sat);
-    if (!kv_only) hipLaunchKernelGGL(k_attn<f16_t>, dim3(R, H), dim3(256), shm, s, att, c->qkv32,
-                       (const f16_t *)lw.kc, (const f16_t *)lw.vc, (const f16_t *)lw.kc_lo,
-                       (const f16_t *)lw.vc_lo, c->scores, c->rows,
-                       c->sch.kv_len, c->sch.gen_sub, kv_override, d, H, hd, c->kv_cap, c->gen_stride,
-                       c->L, scale);
-  }
-  PD_CHECK_HIP(hipGetLastError());
-  if (kv_only) return PD_OK;
-  if ((rc = linear<1>(c, c->x, att, lw.wo, nullptr, c->x, R, d, d, s))) return rc;
-  hipLaunchKernelGGL(k_norm_f32, dim3(R), dim3(256), 0, s, xn, c->x, lw.n2g, lw.n2b, d, g.norm_kind,
-                     g.norm_eps, c->rows.flags);
-  PD_CHECK_HIP(hipGetLastError());
-  if (g.ffn_kind == 0) {
-    if ((rc = linear<2>(c, hb, xn, lw.w1, nullptr, nullptr, R, ff, d, s))) return rc;
-  } else {
-    if ((rc = linear<3>(c, hb, xn, lw.w1, lw.w_up, nullptr, R, ff, d, s))) return rc;
-  }
-  return linear<1>(c, c->x, hb, lw.w2, nullptr, c->x, R, d, ff, s);
+  a.x = (const float *)c->xn;
+  return PD_OK;
 }
 
-int simple_head(pd_ctx *c, int R, hipStream_t s) {
+int simple_layer(pd_ctx *c, int l, int R, int A, int nreq, int req0, int kv_override,
+                 hipStream_t s) {
   const pd_config &g = c->cfg;
+  const LayerPtrs &lw = c->layers[l];
+  const int d = g.d_model, ff = g.d_ff, H = g.n_head, hd = g.head_dim;
   int rc;
-  hipLaunchKernelGGL(k_norm_f32, dim3(R), dim3(256), 0, s, (float *)c->xn, c->x, c->fng, c->fnb,
-                     g.d_model, g.norm_kind, g.norm_eps, c->rows.flags);
-  PD_CHECK_HIP(hipGetLastError());
-  if ((rc = linear<0>(c, c->logits, (float *)c->xn, c->lm_head, nullptr, nullptr, R, g.vocab,
-                      g.d_model, s)))
-    return rc;
-  hipLaunchKernelGGL(k_argmax, dim3(R), dim3(256), 0, s, c->row_argmax, c->logits, c->rows.flags,
-                     g.vocab);
-  PD_CHECK_HIP(hipGetLastError());
-  return PD_OK;
+  LinArgs base;
+  memset(&base, 0, sizeof(base));
+  base.rt = c->rows; base.d = d; base.H = H; base.hd = hd; base.kv_cap = c->kv_cap; base.kv_sat = c->kv_sat;
+  const bool gather = l == 0 && norm_inside(c, R);
+  LinArgs a = base;
+  if ((rc = normed(c, a, lw.n1g, lw.n1b, R, s))) return rc;
+  if (gather) { a.tok_emb = c->tok_emb; a.pos_emb = c->pos_emb; }
+  a.out = c->qkv32; a.ldo = 3 * d;
+  if (g.pos_kind == 1) {
+    if ((rc = linear<LIN_STORE>(c, a, lw.wqkv, nullptr, R, 3 * d, d, s))) return rc;
+    if (g.dtype == 0)
+      hipLaunchKernelGGL(k_qkv_post<float>, dim3(R), dim3(256), 0, s, c->qkv32, (float *)lw.kc, (float *)lw.vc,
+                         (float *)nullptr, (float *)nullptr, c->rows, c->rope_cs, d, H, hd, c->kv_cap, c->kv_sat);
+    else
+      hipLaunchKernelGGL(k_qkv_post<f16_t>, dim3(R), dim3(256), 0, s, c->qkv32, (f16_t *)lw.kc, (f16_t *)lw.vc,
+                         (f16_t *)lw.kc_lo, (f16_t *)lw.vc_lo, c->rows, c->rope_cs, d, H, hd, c->kv_cap, c->kv_sat);
+    PD_CHECK_HIP(hipGetLastError());
+  } else {
+    a.kc = lw.kc; a.vc = lw.vc; a.kc_lo = lw.kc_lo; a.vc_lo = lw.vc_lo;
+    if ((rc = linear<LIN_QKV>(c, a, lw.wqkv, nullptr, R, 3 * d, d, s))) return rc;
+  }
+  // context pass, last layer: only its keys and values are ever used
+  if (kv_override >= 0 && l == g.n_layer - 1) return PD_OK;
+  AttnF32Args t;
+  memset(&t, 0, sizeof(t));
+  t.out = (float *)c->att; t.qkv = c->qkv32; t.kc = lw.kc; t.vc = lw.vc; t.kc_lo = lw.kc_lo; t.vc_lo = lw.vc_lo;
+  t.rt = c->rows; t.kv_len = c->sch.kv_len; t.gen_sub = c->sch.gen_sub; t.kv_override = kv_override; t.d = d; t.H = H;
+  t.hd = hd; t.kv_cap = c->kv_cap; t.gen_stride = c->gen_stride; t.L = c->L; t.A = A; t.nqg = (A + 15) / 16;
+  t.req0 = req0; t.scale = 1.0f / sqrtf((float)hd);
+  if ((rc = g.dtype == 0 ? attention_f32<float>(t, nreq, s) : attention_f32<f16_t>(t, nreq, s))) return rc;
+  a = base;
+  a.x = (const float *)c->att; a.out = c->x; a.res = c->x; a.ldo = d;
+  LinArgs o = a;
+  if (gather) { o.tok_emb = c->tok_emb; o.pos_emb = c->pos_emb; }
+  if ((rc = linear<LIN_RESID>(c, o, lw.wo, nullptr, R, d, d, s))) return rc;
+  LinArgs f = base;
+  if ((rc = normed(c, f, lw.n2g, lw.n2b, R, s))) return rc;
+  f.out = (float *)c->hb; f.ldo = ff;
+  rc = g.ffn_kind == 0 ? linear<LIN_GELU>(c, f, lw.w1, nullptr, R, ff, d, s)
+                       : linear<LIN_SWIGLU>(c, f, lw.w1, lw.w_up, R, ff, d, s);
+  if (rc) return rc;
+  a.x = (const float *)c->hb;
+  return linear<LIN_RESID>(c, a, lw.w2, nullptr, R, d, ff, s);
+}
+
+// leaves one winner per 16-column tile; the commit kernel picks the winner of each row
+int simple_head(pd_ctx *c, int R, float *logits, hipStream_t s) {
+  const pd_config &g = c->cfg;
+  LinArgs a;
+  memset(&a, 0, sizeof(a));
+  int rc;
+  a.rt = c->rows;
+  if ((rc = normed(c, a, c->fng, c->fnb, R, s))) return rc;
+  a.logits = logits; a.S = c->S; a.part_val = c->lm_part_val; a.part_idx = c->lm_part_idx; a.n_tiles = c->vocab_pad / 16;
+  return linear<LIN_HEAD>(c, a, c->lm_head, nullptr, R, g.vocab, g.d_model, s, a.n_tiles);
 }

@@ -1,0 +1,52 @@
+"""The fp32-activation kernels at the edges of their tiles: row counts beside 16, 32 and 64, widths that are and are not
+multiples of the 16-value steps or of 4 (scalar loads), head sizes of every instantiation (16-dim blocks 1, 2, 4, 8, 16
+and sizes in between), key counts beside the 16-key tiles, norms inside the projections (at most 32 rows of up to 1024
+values) and outside, rows embedded by the first projection or by a kernel.  Against the CPU oracle: 1e-4 in fp32, 2e-2
+with bf16 weights and the half cache (tests/parity_util.py)."""
+
+import pytest
+
+import pd_inputs as pi
+from pd_inputs.configs import WorkloadConfig, DTYPE_BF16, DTYPE_F32, FFN_SWIGLU, NORM_RMSNORM, POS_ROPE
+from parity_util import oracle_run, make_decoder, compare_teacher_forced
+
+pytestmark = pytest.mark.gpu
+
+LLAMA = dict(ffn_kind=FFN_SWIGLU, norm_kind=NORM_RMSNORM, pos_kind=POS_ROPE)
+
+
+def W(name, heads, hd, ff, ctx, **kw):
+    base = dict(name=name, seed=141, dtype=DTYPE_F32, n_layer=2, d_model=heads * hd, n_head=heads, head_dim=hd, d_ff=ff,
+                vocab=131, batch=1, ctx_len=ctx, n_sub=3, delta_t=1, sub_tokens=3, norm_init="random", qkv_std=0.05)
+    base.update(kw)
+    return WorkloadConfig(**base)
+
+
+CASES = [
+    W("hd2", 3, 2, 7, 15, qkv_std=0.5),                        # K = 6 and 7: scalar loads, fewer than 16 values
+    W("hd10", 5, 10, 33, 17, qkv_std=0.3),                     # K = 50, 33
+    W("hd16", 4, 16, 100, 33, batch=3),                        # K = 64, 100; rows of three requests
+    W("hd24-llama", 2, 24, 65, 31, **LLAMA),
+    W("hd32", 9, 32, 257, 129, batch=2),                       # K = 288 (8 waves); context of 128 + 1 rows
+    W("hd50", 2, 50, 300, 65),                                 # scalar keys
+    W("hd64-16rows", 2, 64, 256, 40, n_sub=8, sub_tokens=9, batch=2),    # 16 rows
+    W("hd64-33rows", 1, 64, 256, 64, n_sub=11, sub_tokens=11, batch=3),  # 33 rows: norm and embedding kernels
+    W("hd80", 7, 80, 1100, 50),                                # K = 560 (16 waves), 1100
+    W("hd96-llama", 11, 96, 1056, 47, **LLAMA),                # d = 1056: norms outside the projections
+    W("hd130", 2, 130, 96, 70),
+    W("hd256", 2, 256, 2100, 81),                              # K = 512, 2100
+    W("bf16-hd48", 3, 48, 200, 90, dtype=DTYPE_BF16, batch=2),
+    W("bf16-hd80-llama", 2, 80, 199, 33, dtype=DTYPE_BF16, **LLAMA),
+]
+
+
+@pytest.mark.parametrize("cfg", CASES, ids=[c.name for c in CASES])
+def test_fp32_kernels(cfg):
+    print(f"[fp32] {cfg}", flush=True)
+    w, ctx = pi.make_weights(cfg, threads=4), pi.make_context(cfg)
+    outs = oracle_run(cfg, w, ctx)
+    for pair_layers in ([-1, 1] if cfg.dtype == DTYPE_BF16 else [-1]):
+        dec = make_decoder(cfg, w, kv_pair_layers=pair_layers)
+        stats = compare_teacher_forced(cfg, w, ctx, dec, outs, log=lambda m: print(m, flush=True))
+        assert stats["rows"] == cfg.batch * (cfg.n_sub * (cfg.sub_tokens + 1) - 1)
+        dec.close()
