@@ -249,9 +249,9 @@ int pd_reset_decode(pd_ctx *ctx, void *hip_stream);
  *                        matrix-core passes per weight / key / value fragment; 0 uses plain bf16
  *                        activations (half the matrix-core work, larger rounding error)
  *   PD_OPT_PREFILL_CHUNK rows of the context pass per launch (0 = default: up to 4096 on the bf16
- *                        path, 128 on the fp32 path; other values are rounded up to a multiple
- *                        of 16 and capped at that default).  Results do not depend on it beyond
- *                        rounding order.
+ *                        path, 1024 on the fp32 path; other values are rounded up to a multiple
+ *                        of 16 and capped at that default).  Contexts that fit a launch more than
+ *                        once share it.  Results do not depend on it beyond rounding order.
  *   PD_OPT_FUSE_NORM     1 (default): in steps of at most 16 rows (and of up to 128 rows against small
  *                        matrices, where every block works on one row tile) the output projection adds its result
  *                        to the residual stream itself, hands gain * x and per-tile row sums to the

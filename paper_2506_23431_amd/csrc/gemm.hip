@@ -546,11 +546,12 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, int nt, const f
       int r = r0 + i * 16 + m;
       float best = -INFINITY;
       int bi = 0x7fffffff;
-      // kvi: the row's {flags, subsequence, limit, request}; rows without a token have no place by subsequence
-      float *dst = a.logits;
-      if (dst && a.logits_subs > 0) dst = (kvi[i].x & ROW_VALID) ? dst + ((size_t)kvi[i].w * a.logits_subs + kvi[i].y - 1) * a.ld_logits : nullptr;
-      else if (dst) dst += (size_t)r * a.ld_logits;
-      if (r >= a.R) dst = nullptr;
+      // kvi: the row's {flags, subsequence, limit, request}
+      float *dst = nullptr;
+      if (a.logits && r < a.R && (kvi[i].x & ROW_VALID)) {
+        const int q = a.logits_A > 0 ? r / a.logits_A : kvi[i].w;
+        dst = a.logits + ((size_t)q * a.logits_cap + (a.logits_A > 0 ? r - q * a.logits_A : kvi[i].y - 1)) * a.ld_logits;
+      }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         int n = n0 + j;

@@ -138,7 +138,7 @@ int mfma_layer(pd_ctx *c, int l, int R, int A, int nreq, int req0, int kv_overri
   return mfma_out_ffn(c, a, lw.p_wo, lw, R, s, decode_step && l + 1 < g.n_layer ? c->layers[l + 1].n1g : nullptr);
 }
 
-int mfma_head(pd_ctx *c, int R, float *logits, bool by_sub, hipStream_t s) {
+int mfma_head(pd_ctx *c, int R, float *logits, hipStream_t s, int tf_A, int tf_cap) {
   const pd_config &g = c->cfg;
   int rc;
   if ((rc = mfma_norm(c, c->fng, c->fnb, R, s))) return rc;
@@ -148,7 +148,7 @@ int mfma_head(pd_ctx *c, int R, float *logits, bool by_sub, hipStream_t s) {
   a.stream_w = c->stream_loads;
   a.xn_lo = mfma_lo(c, c->xn, g.d_model); a.K = g.d_model;
   a.n_tiles = c->vocab_pad / 16; a.V = g.vocab;
-  a.logits = logits; a.logits_subs = by_sub ? c->S : 0; a.ld_logits = g.vocab;
+  a.logits = logits; a.logits_A = tf_A; a.logits_cap = tf_A > 0 ? tf_cap : c->S; a.ld_logits = g.vocab;
   a.part_val = c->lm_part_val; a.part_idx = c->lm_part_idx;
   // leaves one winner per 16-column tile; the commit kernel picks the winner of each row
   return mfma_gemm(EPI_LM, a, R, s);

@@ -118,8 +118,9 @@ struct GemmArgs {
   RowTables rt;
   const float *rope_cs;
   int d, H, hd, kv_cap;
-  float *logits; int V, ld_logits;     // EPI_LM: optional logits [rows][ld_logits] ...
-  int logits_subs;                     // ... or, > 0, [request][logits_subs][ld_logits] by the rows' request and subsequence
+  // EPI_LM: optional logits of the rows that carry a token, [request][logits_cap][ld_logits]: a row's place is its
+  // subsequence or, logits_A > 0 (logits_A rows per request), its place among the request's rows
+  float *logits; int V, ld_logits, logits_cap, logits_A;
   float *part_val; int32_t *part_idx;  // EPI_LM: [16*RT][n_tiles] best value / index per tile
   // EPI_RESID_NORM (at most 16 rows, K not cut over blocks): x_res += y in place, out_bf / out_lo receive
   // gain * x_res as activation fragments, stats_out[row][tile] the sum and the sum of squares of x_res

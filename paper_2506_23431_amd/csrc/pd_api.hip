@@ -78,7 +78,8 @@ struct Carver {
 
 // Lays the workspace out; with base == NULL only the size is computed.
 // `e` != NULL: encoder-decoder form (g is the decoder stack's configuration derived from it).
-static size_t carve(const pd_config *g, char *base, pd_ctx *c, const pd_encdec_config *e = nullptr) {
+// `shared_chunk`: room for a context pass whose launches hold several requests' contexts (see below).
+static size_t carve_with(const pd_config *g, char *base, pd_ctx *c, const pd_encdec_config *e, bool shared_chunk) {
   pd_ctx tmp_ctx;
   pd_ctx *x = c ? c : &tmp_ctx;
   int d = g->d_model, ff = g->d_ff, H = g->n_head, hd = g->head_dim, V = g->vocab;
@@ -93,12 +94,18 @@ static size_t carve(const pd_config *g, char *base, pd_ctx *c, const pd_encdec_c
   // Rows of the context pass per launch: as many as give the many-row projection kernel a block
   // per compute unit even for small matrices (measured: the cfg4 context pass takes 0.172 s in chunks
   // of 128 rows, 0.059 s in chunks of 1024, 0.052 s in chunks of 2048 and 0.049 s in chunks of 4096),
-  // at most the 4096 (request, head, 16 rows) units of one attention launch allow.  The fp32 path
-  // keeps one score row per (row, head) and stays at 128.
+  // at most the 4096 (request, head, 16 rows) units of one attention launch allow.  Short contexts share the rows of a
+  // launch (cfg2's model, two contexts of 1024 tokens: 0.88 -> 0.60 ms; fp32, width 512, two of 257: six launches per
+  // projection become one).
   {
-    int cap = std::min(4096, 16 * (4096 / std::max(H, 1)) / 16 * 16);
-    x->prefill_chunk_cap = x->impl == 1 ? std::max(128, std::min(cap, (g->max_ctx + 127) / 128 * 128)) : 128;
+    const int most = x->impl == 1 ? 4096 : 1024;
+    const int cap = std::min(most, 16 * (4096 / std::max(H, 1)) / 16 * 16);
+    const int64_t want = (int64_t)g->max_ctx * (shared_chunk && !e ? B : 1);
+    x->prefill_chunk_cap = std::max(128, (int)std::min<int64_t>(cap, (want + 127) / 128 * 128));
+    if (x->impl == 0 && !shared_chunk) x->prefill_chunk_cap = 128;
     x->prefill_chunk = x->prefill_chunk_cap;
+    // rows of one request's training targets: what a context pass of a single request has room for
+    x->tf_rows = std::max(B * std::min(S, M + 1), std::max(128, std::min(cap, (g->max_ctx + 127) / 128 * 128)));
   }
   int a_max = std::min(S, M + 1);
   x->R_cap = std::max(B * a_max, x->prefill_chunk_cap);
@@ -145,7 +152,7 @@ static size_t carve(const pd_config *g, char *base, pd_ctx *c, const pd_encdec_c
   x->q = cv.take<float>(Rp * d);
   x->att = cv.take<float>(Rp * d);
   x->hb = cv.take<float>(Rp * ff);
-  x->qkv32 = cv.take<float>(Rp * 3 * d);
+  x->qkv32 = x->impl == 0 ? cv.take<float>(Rp * 3 * d) : nullptr;
   // split partials of the attention kernel: one (max, sum, O) record of 16 queries per (request, head,
   // query group) unit and split; the launch caps its splits so that units * splits <= part_units
   {
@@ -206,6 +213,14 @@ static size_t carve(const pd_config *g, char *base, pd_ctx *c, const pd_encdec_c
     }
   }
   return (cv.off + 255) & ~(size_t)255;
+}
+
+// Room for shared chunks unless it would push a workspace that otherwise fits the static one (pd_generate_static)
+// beyond it.
+static size_t carve(const pd_config *g, char *base, pd_ctx *c, const pd_encdec_config *e = nullptr) {
+  const bool shared = carve_with(g, nullptr, nullptr, e, true) <= PD_STATIC_WORKSPACE_BYTES ||
+                      carve_with(g, nullptr, nullptr, e, false) > PD_STATIC_WORKSPACE_BYTES;
+  return carve_with(g, base, c, e, shared);
 }
 
 extern "C" size_t pd_workspace_bytes(const pd_config *cfg) {
@@ -540,6 +555,11 @@ static int run_layers(pd_ctx *c, int R, int A, int nreq, int req0, int kv_overri
   return PD_OK;
 }
 
+// whether nreq requests of A rows each can be one launch sequence: the row buffers and the attention's units of 16 rows
+static bool fits_one_pass(const pd_ctx *c, int A, int nreq) {
+  return (int64_t)nreq * A <= c->R_cap && (int64_t)nreq * ((A + 15) / 16) * c->cfg.n_head <= c->part_units;
+}
+
 extern "C" int pd_prefill_context(pd_ctx *c, const int32_t *ctx_tokens, int B, int L, int n_sub,
                                   int delta_t, int max_sub_tokens, int time_max, void *hip_stream) {
   PD_REQUIRE(c && ctx_tokens, PD_EINVAL, "ctx or ctx_tokens is NULL");
@@ -576,13 +596,17 @@ extern "C" int pd_prefill_context(pd_ctx *c, const int32_t *ctx_tokens, int B, i
   // the context pass may carry its activations as single bf16 values (see context_pairs)
   const int split_decode = c->opt_split;
   if (!context_pairs(c)) c->opt_split = 0;
-  for (int b = 0; b < B && c->arch == 0 && !rc; ++b) {
-    const int chunk = c->opt_chunk > 0 ? c->opt_chunk : c->prefill_chunk;
+  const int chunk = c->opt_chunk > 0 ? c->opt_chunk : c->prefill_chunk;
+  for (int b = 0; b < B && c->arch == 0 && !rc;) {
+    // contexts that fit a chunk more than once share it
+    int nreq = 1;
+    while (b + nreq < B && (int64_t)(nreq + 1) * L <= chunk && fits_one_pass(c, L, nreq + 1)) ++nreq;
     for (int p0 = 0; p0 < L && !rc; p0 += chunk) {
       int n = std::min(chunk, L - p0);
-      if ((rc = launch_prefill_rows(c, b, p0, n, s, c->L, 0, b))) break;
-      rc = run_layers(c, n, n, 1, b, p0 + n, s);
+      if ((rc = launch_prefill_rows(c, b, p0, n, s, c->L, 0, b, nreq))) break;
+      rc = run_layers(c, nreq * n, n, nreq, b, p0 + n, s);
     }
+    b += nreq;
   }
   c->opt_split = split_decode;
   if (rc) return rc;
@@ -627,7 +651,7 @@ static int enqueue_step(pd_ctx *c, float *out_logits, hipStream_t s) {
     if (r_used <= 8) { c->packed = true; R = std::min(R, std::max(r_used, 1)); }
   }
   rc = run_layers(c, R, c->A, c->B, 0, -1, s);
-  if (!rc) rc = c->impl == 1 ? mfma_head(c, R, out_logits, true, s) : simple_head(c, R, out_logits, s);
+  if (!rc) rc = c->impl == 1 ? mfma_head(c, R, out_logits, s) : simple_head(c, R, out_logits, s);
   c->packed = false;
   if (rc) return rc;
   return launch_commit(c, s);
@@ -730,9 +754,9 @@ extern "C" int pd_teacher_forced(pd_ctx *c, const int32_t *target, int max_len, 
       rows[b] += n;
     }
     PD_REQUIRE(rows[b] >= 1, PD_EINVAL, "request %d has an empty target", b);
-    PD_REQUIRE(rows[b] <= c->gen_cap && rows[b] <= c->R_cap && rows[b] <= rows_cap, PD_EINVAL,
+    PD_REQUIRE(rows[b] <= c->gen_cap && rows[b] <= c->tf_rows && rows[b] <= rows_cap, PD_EINVAL,
                "request %d: %d target tokens exceed the capacity (%d cache slots, %d rows per pass, %d rows of out_logits)",
-               b, rows[b], c->gen_cap, c->R_cap, rows_cap);
+               b, rows[b], c->gen_cap, c->tf_rows, rows_cap);
   }
   hipStream_t s = (hipStream_t)hip_stream;
   drop_graph(c);
@@ -745,21 +769,26 @@ extern "C" int pd_teacher_forced(pd_ctx *c, const int32_t *target, int max_len, 
   am.coord = c->gen_coord; am.coord_stride = c->gen_stride; am.coord_req_stride = c->gen_stride;
   am.coord_off = L & ~7; am.pos0 = L;
   int rc;
-  std::vector<float> nll_host;
-  for (int b = 0; b < B; ++b) {
-    const int n = rows[b];
-    if ((rc = launch_teacher_rows(c, c->tf_target, b, max_len, s))) return rc;
+  // requests share a pass as long as their rows, each padded to the longest of the group, fit one launch sequence
+  for (int b = 0; b < B;) {
+    int A = rows[b], nreq = 1;
+    while (b + nreq < B && A < 65535 && fits_one_pass(c, std::max(A, rows[b + nreq]), nreq + 1)) A = std::max(A, rows[b + nreq++]);
+    const int R = nreq * A;
+    if ((rc = launch_teacher_rows(c, c->tf_target, b, nreq, A, max_len, s))) return rc;
     c->packed = false; c->embed_pending = true; c->pend_parts = 0; c->norm_fused = false;
     for (int l = 0; l < g.n_layer; ++l)
-      if ((rc = c->arch == 1 ? encdec_decoder_layer(c, l, n, s, n, 1, b, n) : mfma_layer(c, l, n, n, 1, b, L + n, s, &am)))
+      if ((rc = c->arch == 1 ? encdec_decoder_layer(c, l, R, s, A, nreq, b, A) : mfma_layer(c, l, R, A, nreq, b, L + A, s, &am)))
         return rc;
     float *lg = out_logits + (size_t)b * rows_cap * g.vocab;
-    if ((rc = mfma_head(c, n, lg, false, s))) return rc;
-    if ((rc = launch_row_nll(c, lg, n, c->loss + b, s))) return rc;
+    if ((rc = mfma_head(c, R, lg, s, A, rows_cap))) return rc;
+    if ((rc = launch_row_nll(c, lg, nreq, A, rows_cap, c->loss + b, s))) return rc;
     if (out_row_nll) {
-      PD_CHECK_HIP(hipMemcpyAsync(out_row_nll + (size_t)b * rows_cap, c->nll, sizeof(float) * n, hipMemcpyDeviceToHost, s));
-      PD_CHECK_HIP(hipStreamSynchronize(s));        // c->nll is reused by the next request
+      for (int q = 0; q < nreq; ++q)
+        PD_CHECK_HIP(hipMemcpyAsync(out_row_nll + (size_t)(b + q) * rows_cap, c->nll + (size_t)q * A,
+                                    sizeof(float) * rows[b + q], hipMemcpyDeviceToHost, s));
+      if (b + nreq < B) PD_CHECK_HIP(hipStreamSynchronize(s));        // c->nll is reused by the next pass
     }
+    b += nreq;
   }
   PD_CHECK_HIP(hipMemcpyAsync(out_loss, c->loss, sizeof(double) * B, hipMemcpyDeviceToHost, s));
   // the generated side of the caches and the schedule state were used as scratch: back to t = 0

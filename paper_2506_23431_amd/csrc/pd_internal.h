@@ -138,7 +138,7 @@ struct pd_ctx {
   int pair_layers;          // leading layers whose cache holds pairs of halves (kv_pair_layers resolved)
   int32_t *kv_sat;          // [1] keys / values stored saturated at the largest half since pd_create
   // capacities
-  int gen_cap, gen_stride, kv_cap, R_cap, R_pad, vocab_pad, prefill_chunk, prefill_chunk_cap;
+  int gen_cap, gen_stride, kv_cap, R_cap, R_pad, vocab_pad, prefill_chunk, prefill_chunk_cap, tf_rows;
   size_t kv_layer_bytes;    // bytes of one K (or V) cache of one layer
   // workspace carve-up
   char *ws; size_t ws_bytes;
@@ -191,11 +191,11 @@ struct pd_ctx {
 // schedule / glue (sched.hip)
 int launch_reset_state(pd_ctx *c, hipStream_t s);
 int launch_tick(pd_ctx *c, hipStream_t s);
-int launch_prefill_rows(pd_ctx *c, int b, int p0, int n, hipStream_t s, int L, int bidir, int b_cache);
+int launch_prefill_rows(pd_ctx *c, int b, int p0, int n, hipStream_t s, int L, int bidir, int b_cache, int nreq = 1);
 int launch_embed(pd_ctx *c, int R, hipStream_t s);
 int launch_commit(pd_ctx *c, hipStream_t s);
-int launch_teacher_rows(pd_ctx *c, const int32_t *tgt_dev, int b, int ML, hipStream_t s);
-int launch_row_nll(pd_ctx *c, const float *logits, int n, double *loss_dev, hipStream_t s);
+int launch_teacher_rows(pd_ctx *c, const int32_t *tgt_dev, int b, int nreq, int A, int ML, hipStream_t s);
+int launch_row_nll(pd_ctx *c, const float *logits, int nreq, int A, int cap, double *loss_dev, hipStream_t s);
 int launch_rope_table(pd_ctx *c, hipStream_t s);
 // fp32-activation path (simple.hip)
 int simple_layer(pd_ctx *c, int l, int R, int A, int nreq, int req0, int kv_override, hipStream_t s);
@@ -210,9 +210,9 @@ struct AttnMode;
 // mode != NULL: not a context pass (every layer runs to its end) and the attention launch takes the mode
 int mfma_layer(pd_ctx *c, int l, int R, int A, int nreq, int req0, int kv_override, hipStream_t s,
                const AttnMode *mode = nullptr);
-// logits != NULL: the rows' logits go there, [R][vocab] in row order or, by_sub, [B][S][vocab] at the place of the
-// row's request and subsequence (rows without a token write nothing)
-int mfma_head(pd_ctx *c, int R, float *logits, bool by_sub, hipStream_t s);
+// logits != NULL: the logits of the rows that carry a token go there; tf_A == 0: [B][S][vocab], at the place of the
+// row's request and subsequence; tf_A > 0 (teacher-forced pass, tf_A rows per request): [requests][tf_cap][vocab]
+int mfma_head(pd_ctx *c, int R, float *logits, hipStream_t s, int tf_A = 0, int tf_cap = 0);
 // encoder-decoder form (encdec.hip)
 int encdec_pack_weights(pd_ctx *c, hipStream_t s);
 int encdec_build_tables(pd_ctx *c, int *scratch, hipStream_t s);

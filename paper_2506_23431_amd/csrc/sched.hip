@@ -126,21 +126,22 @@ int launch_tick(pd_ctx *c, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// prefill rows: context tokens p0 .. p0+n-1 of request b as rows 0 .. n-1.
+// prefill rows: context tokens p0 .. p0+n-1 of each of nreq requests from b on, n rows per request.
 // Row for position p sees the keys 0..p (causal prefix), nothing generated; with `bidir` (rows of a
-// bidirectional encoder) all L keys.  Keys and values of the rows go to cache entry `b_cache`.
+// bidirectional encoder) all L keys.  Keys and values of the rows go to cache entry `b_cache` (+ the
+// request's place among the nreq).
 // ---------------------------------------------------------------------------
-__global__ void k_prefill_rows(RowTables rt, const int32_t *ctx_tok, int b, int L, int p0, int n,
+__global__ void k_prefill_rows(RowTables rt, const int32_t *ctx_tok, int b, int L, int p0, int n, int nreq,
                                int R_cap, int bidir, int b_cache) {
   int r = blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= R_cap) return;
-  if (r < n) {
-    int p = p0 + r;
-    rt.req[r] = b; rt.sub[r] = 0; rt.tok[r] = ctx_tok[(size_t)b * L + p]; rt.pos[r] = p;
+  if (r < n * nreq) {
+    const int q = r / n, p = p0 + r - q * n;
+    rt.req[r] = b + q; rt.sub[r] = 0; rt.tok[r] = ctx_tok[(size_t)(b + q) * L + p]; rt.pos[r] = p;
     const int lim = bidir ? L : p + 1;
     rt.slot[r] = p; rt.lim[r] = lim; rt.flags[r] = ROW_VALID;
-    rt.qinfo[r] = make_int4(ROW_VALID, 0, lim, b_cache);
-    rt.kvinfo[r] = make_int4(ROW_VALID, b_cache, p, p);
+    rt.qinfo[r] = make_int4(ROW_VALID, 0, lim, b_cache + q);
+    rt.kvinfo[r] = make_int4(ROW_VALID, b_cache + q, p, p);
   } else {
     rt.flags[r] = 0;
     rt.qinfo[r] = make_int4(0, -1, 0, b);
@@ -148,105 +149,150 @@ __global__ void k_prefill_rows(RowTables rt, const int32_t *ctx_tok, int b, int 
   }
 }
 
-int launch_prefill_rows(pd_ctx *c, int b, int p0, int n, hipStream_t s, int L, int bidir, int b_cache) {
+int launch_prefill_rows(pd_ctx *c, int b, int p0, int n, hipStream_t s, int L, int bidir, int b_cache, int nreq) {
   hipLaunchKernelGGL(k_prefill_rows, dim3((c->R_cap + 255) / 256), dim3(256), 0, s, c->rows,
-                     c->ctx_tok, b, L, p0, n, c->R_cap, bidir, b_cache);
+                     c->ctx_tok, b, L, p0, n, nreq, c->R_cap, bidir, b_cache);
   PD_CHECK_HIP(hipGetLastError());
   return PD_OK;
 }
 
 // ---------------------------------------------------------------------------
-// teacher-forced rows (Section 3.3, Fig. 3b): every token of request b's training target as one row,
+// teacher-forced rows (Section 3.3, Fig. 3b): every token of a request's training target as one row,
 // subsequence-major (row of token j of subsequence i: the lengths before i, plus j), at the grid
 // coordinate Algorithm 1 would feed it, tau = (i-1) dt + 1 + j.  tgt: [B][S][ML] token ids, -1 behind a
-// subsequence's last token.  Row r writes key slot L + r with its subsequence tag and coordinate;
-// next_tok[r] is the token that follows it (-1 behind the last one: a key, but no loss term).
-// One block; the schedule state of the request is used as scratch and is reset by the caller afterwards.
+// subsequence's last token.  A rows per request, requests b0 + blockIdx.x: row t of a request is row
+// blockIdx.x A + t of the launch and writes key slot L + t with its subsequence tag and coordinate;
+// next_tok[r] is the token that follows it (-1 behind the last one: a key, but no loss term).  Rows behind
+// the request's last token carry nothing, and their key slots the tag 65535, which no query reaches.
+// One block per request; its schedule state is used as scratch and is reset by the caller afterwards.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_teacher_rows(RowTables rt, SchedState st, uint16_t *gen_coord,
-                                                      int32_t *next_tok, const int32_t *tgt, int b, int S, int ML,
-                                                      int dt, int L, int gen_stride, int R_cap, int4 *qinfo_x,
-                                                      int Lx) {
+__global__ __launch_bounds__(1024) void k_teacher_rows(RowTables rt, SchedState st, uint16_t *gen_coord,
+                                                       int32_t *next_tok, const int32_t *tgt, int b0, int S, int ML,
+                                                       int A, int dt, int L, int gen_cap, int gen_stride, int R_cap,
+                                                       int4 *qinfo_x, int Lx) {
+  const int b = b0 + blockIdx.x, r0 = blockIdx.x * A, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int32_t *tb = tgt + (size_t)b * S * ML;
   int32_t *len = st.n_tok + (size_t)b * S, *off = st.n_fed + (size_t)b * S;
-  for (int i = threadIdx.x; i < S; i += blockDim.x) {
+  // a wave per subsequence finds its length 64 tokens at a time
+  for (int i = wave; i < S; i += blockDim.x >> 6) {
     int n = 0;
-    while (n < ML && tb[(size_t)i * ML + n] >= 0) ++n;
-    len[i] = n;
+    for (;;) {
+      const bool tok = n + lane < ML && tb[(size_t)i * ML + n + lane] >= 0;
+      const unsigned long long m = __ballot(tok);
+      if (m != ~0ull) { n += __ffsll(~m) - 1; break; }
+      n += 64;
+    }
+    if (lane == 0) len[i] = n;
   }
   __syncthreads();
   __shared__ int s_total;
   if (threadIdx.x == 0) {
     int acc = 0;
     for (int i = 0; i < S; ++i) { off[i] = acc; acc += len[i]; }
-    s_total = acc;
+    s_total = min(acc, A);
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < S; i += blockDim.x) {
-    for (int j = 0; j < len[i]; ++j) {
-      const int r = off[i] + j;
-      if (r >= R_cap) break;
-      const bool more = j + 1 < len[i];
-      const int fl = ROW_VALID | (more ? ROW_PRODUCE : 0), c = (i * dt + j) + i, p = L + c;
-      rt.req[r] = b; rt.sub[r] = i + 1; rt.tok[r] = tb[(size_t)i * ML + j]; rt.pos[r] = p;
-      rt.slot[r] = L + r; rt.lim[r] = L; rt.flags[r] = fl;
-      rt.qinfo[r] = make_int4(fl, i + 1, L, b);
-      rt.kvinfo[r] = make_int4(fl, b, L + r, p);
-      st.gen_sub[(size_t)b * gen_stride + (L & 7) + r] = (uint16_t)(i + 1);
-      gen_coord[(size_t)b * gen_stride + (L & 7) + r] = (uint16_t)c;
-      next_tok[r] = more ? tb[(size_t)i * ML + j + 1] : -1;
-      if (qinfo_x) qinfo_x[r] = make_int4(fl, 0, Lx, b);     // encoder-decoder form: all Lx encoder states
+  const int total = s_total;
+  for (int t = threadIdx.x; t < A; t += blockDim.x) {
+    const int r = r0 + t;
+    if (r >= R_cap) break;
+    if (t >= total) {
+      rt.flags[r] = 0; rt.qinfo[r] = make_int4(0, -1, 0, b); rt.kvinfo[r] = make_int4(0, b, 0, 0);
+      next_tok[r] = -1;
+      if (qinfo_x) qinfo_x[r] = make_int4(0, -1, 0, b);
+      if (t < gen_cap) st.gen_sub[(size_t)b * gen_stride + (L & 7) + t] = 65535;
+      continue;
     }
+    int i = 0, hi = S - 1;              // the last subsequence that starts at or before t (empty ones only at the end)
+    while (i < hi) {
+      const int mid = (i + hi + 1) >> 1;
+      if (off[mid] <= t && len[mid] > 0) i = mid; else hi = mid - 1;
+    }
+    const int j = t - off[i];
+    const bool more = j + 1 < len[i];
+    const int fl = ROW_VALID | (more ? ROW_PRODUCE : 0), c = (i * dt + j) + i, p = L + c;
+    rt.req[r] = b; rt.sub[r] = i + 1; rt.tok[r] = tb[(size_t)i * ML + j]; rt.pos[r] = p;
+    rt.slot[r] = L + t; rt.lim[r] = L; rt.flags[r] = fl;
+    rt.qinfo[r] = make_int4(fl, i + 1, L, b);
+    rt.kvinfo[r] = make_int4(fl, b, L + t, p);
+    st.gen_sub[(size_t)b * gen_stride + (L & 7) + t] = (uint16_t)(i + 1);
+    gen_coord[(size_t)b * gen_stride + (L & 7) + t] = (uint16_t)c;
+    next_tok[r] = more ? tb[(size_t)i * ML + j + 1] : -1;
+    if (qinfo_x) qinfo_x[r] = make_int4(fl, 0, Lx, b);     // encoder-decoder form: all Lx encoder states
   }
-  for (int r = s_total + threadIdx.x; r < R_cap; r += blockDim.x) {
+  if (blockIdx.x != gridDim.x - 1) return;
+  for (int r = r0 + A + threadIdx.x; r < R_cap; r += blockDim.x) {
     rt.flags[r] = 0; rt.qinfo[r] = make_int4(0, -1, 0, b); rt.kvinfo[r] = make_int4(0, b, 0, 0);
     next_tok[r] = -1;
     if (qinfo_x) qinfo_x[r] = make_int4(0, -1, 0, b);
   }
 }
 
-int launch_teacher_rows(pd_ctx *c, const int32_t *tgt_dev, int b, int ML, hipStream_t s) {
-  hipLaunchKernelGGL(k_teacher_rows, dim3(1), dim3(256), 0, s, c->rows, c->sch, c->gen_coord, c->row_argmax, tgt_dev,
-                     b, c->S, ML, c->dt, c->L, c->gen_stride, c->R_cap, c->qinfo_x, c->Lx);
+int launch_teacher_rows(pd_ctx *c, const int32_t *tgt_dev, int b, int nreq, int A, int ML, hipStream_t s) {
+  hipLaunchKernelGGL(k_teacher_rows, dim3(nreq), dim3(1024), 0, s, c->rows, c->sch, c->gen_coord, c->row_argmax, tgt_dev,
+                     b, c->S, ML, A, c->dt, c->L, c->gen_cap, c->gen_stride, c->R_cap, c->qinfo_x, c->Lx);
   PD_CHECK_HIP(hipGetLastError());
   return PD_OK;
 }
 
 // Eq. 6, one row per block: nll[r] = log sum_v exp(logits[r][v]) - logits[r][next_tok[r]], 0 for rows
-// without a successor.
-__global__ __launch_bounds__(256) void k_row_nll(float *nll, const float *logits, size_t ld, int V,
-                                                 const int32_t *next_tok) {
-  __shared__ float sh[4];
+// without a successor.  One pass over the row: every thread keeps a running maximum and the sum around it over 8
+// requests in flight at a time, the threads' pairs are merged at the end (172 rows of 50265: two passes of 256
+// threads one value at a time took 110 us, this one 18).
+__global__ __launch_bounds__(1024) void k_row_nll(float *nll, const float *logits, size_t ld, int V, int A, int cap,
+                                                  const int32_t *next_tok) {
+  constexpr int U = 8;
+  __shared__ float sh_m[16], sh_e[16];
   const int r = blockIdx.x, t = next_tok[r];
   if (t < 0) { if (threadIdx.x == 0) nll[r] = 0.f; return; }      // the same for the whole block
-  const float *row = logits + (size_t)r * ld;
-  float m = -INFINITY;
-  for (int v = threadIdx.x; v < V; v += 256) m = fmaxf(m, row[v]);
-  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
+  const float *row = logits + ((size_t)(r / A) * cap + r % A) * ld;
+  float m = -INFINITY, e = 0.f;
+  for (int v0 = threadIdx.x; v0 < V; v0 += 1024 * U) {
+    float x[U], mx = m;
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = row[min(v0 + 1024 * u, V - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (v0 + 1024 * u >= V) x[u] = -INFINITY;
+      mx = fmaxf(mx, x[u]);
+    }
+    if (mx == -INFINITY) continue;
+    e *= expf(m - mx);                  // (m = -inf, e = 0 at first)
+#pragma unroll
+    for (int u = 0; u < U; ++u) e += expf(x[u] - mx);
+    m = mx;
+  }
+  auto merge = [&](float om, float oe) {
+    const float mx = fmaxf(m, om);
+    e = (m == -INFINITY ? 0.f : e * expf(m - mx)) + (om == -INFINITY ? 0.f : oe * expf(om - mx));
+    m = mx;
+  };
+  for (int o = 32; o > 0; o >>= 1) merge(__shfl_xor(m, o), __shfl_xor(e, o));
+  if ((threadIdx.x & 63) == 0) { sh_m[threadIdx.x >> 6] = m; sh_e[threadIdx.x >> 6] = e; }
   __syncthreads();
-  m = fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
-  __syncthreads();
-  float e = 0.f;
-  for (int v = threadIdx.x; v < V; v += 256) e += expf(row[v] - m);
-  for (int o = 32; o > 0; o >>= 1) e += __shfl_xor(e, o);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = e;
-  __syncthreads();
-  if (threadIdx.x == 0) nll[r] = m + logf((sh[0] + sh[1]) + (sh[2] + sh[3])) - row[t];
+  if (threadIdx.x >= 64) return;
+  m = threadIdx.x < 16 ? sh_m[threadIdx.x] : -INFINITY;
+  e = threadIdx.x < 16 ? sh_e[threadIdx.x] : 0.f;
+  for (int o = 8; o > 0; o >>= 1) merge(__shfl_xor(m, o), __shfl_xor(e, o));
+  if (threadIdx.x == 0) nll[r] = m + logf(e) - row[t];
 }
 
-// loss of one request: the rows' terms added in row order, in double precision (deterministic)
-__global__ void k_loss_sum(double *loss, const float *nll, int n) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// loss of a request: its rows' terms added in row order, in double precision (deterministic); one wave per request
+__global__ __launch_bounds__(64) void k_loss_sum(double *loss, const float *nll, int A) {
+  const int lane = threadIdx.x;
   double acc = 0.0;
-  for (int r = 0; r < n; ++r) acc += (double)nll[r];
-  *loss = acc;
+  for (int t = 0; t < A; t += 64) {
+    const float v = t + lane < A ? nll[(size_t)blockIdx.x * A + t + lane] : 0.f;
+    for (int l = 0; l < 64; ++l) acc += (double)__shfl(v, l);
+  }
+  if (lane == 0) loss[blockIdx.x] = acc;
 }
 
-int launch_row_nll(pd_ctx *c, const float *logits, int n, double *loss_dev, hipStream_t s) {
-  hipLaunchKernelGGL(k_row_nll, dim3(n), dim3(256), 0, s, c->nll, logits, (size_t)c->cfg.vocab, c->cfg.vocab,
-                     c->row_argmax);
-  hipLaunchKernelGGL(k_loss_sum, dim3(1), dim3(64), 0, s, loss_dev, c->nll, n);
+// rows r of the last pass: request r / A, whose logits start at row (r / A) cap
+int launch_row_nll(pd_ctx *c, const float *logits, int nreq, int A, int cap, double *loss_dev, hipStream_t s) {
+  hipLaunchKernelGGL(k_row_nll, dim3(nreq * A), dim3(1024), 0, s, c->nll, logits, (size_t)c->cfg.vocab, c->cfg.vocab,
+                     A, cap, c->row_argmax);
+  hipLaunchKernelGGL(k_loss_sum, dim3(nreq), dim3(64), 0, s, loss_dev, c->nll, A);
   PD_CHECK_HIP(hipGetLastError());
   return PD_OK;
 }

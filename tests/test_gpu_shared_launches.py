@@ -1,0 +1,70 @@
+"""Requests that share launches: contexts in one context pass (as many as fit a chunk, the rest in another), training
+targets of different lengths in one teacher-forced pass (rows padded to the longest), against the CPU oracle request by
+request.  The chunk option splits the same requests into other groups; the bf16 tolerance is 2e-2, fp32 1e-4."""
+
+import numpy as np
+import pytest
+
+import pd_inputs as pi
+from oracle import training
+from oracle.model import OracleModel
+from pd_inputs.configs import WorkloadConfig, DTYPE_BF16, DTYPE_F32, FFN_SWIGLU, NORM_RMSNORM, POS_ROPE
+from parity_util import oracle_run, make_decoder, compare_teacher_forced
+
+pytestmark = pytest.mark.gpu
+
+LLAMA = dict(ffn_kind=FFN_SWIGLU, norm_kind=NORM_RMSNORM, pos_kind=POS_ROPE)
+
+
+def W(name, **kw):
+    base = dict(name=name, seed=151, dtype=DTYPE_BF16, n_layer=2, d_model=128, n_head=2, head_dim=64, d_ff=256, vocab=517,
+                batch=5, ctx_len=45, n_sub=3, delta_t=2, sub_tokens=5, norm_init="random", qkv_std=0.1)
+    base.update(kw)
+    return WorkloadConfig(**base)
+
+
+CASES = [
+    W("hd64"),                                                         # rows of a request not a multiple of 16
+    W("hd128-llama", d_model=256, n_head=2, head_dim=128, d_ff=352, ctx_len=64, qkv_std=0.05, **LLAMA),
+    W("hd32-one-token", d_model=96, n_head=3, head_dim=32, d_ff=160, ctx_len=1, batch=7),
+    W("f32", dtype=DTYPE_F32, ctx_len=77),
+    W("f32-llama", dtype=DTYPE_F32, d_model=60, n_head=5, head_dim=12, ctx_len=33, **LLAMA),
+]
+
+
+@pytest.mark.parametrize("chunk", [0, 112], ids=["all", "two-at-a-time"])
+@pytest.mark.parametrize("cfg", CASES, ids=[c.name for c in CASES])
+def test_contexts_share_a_launch(cfg, chunk):
+    from paper_2506_23431_amd import binding
+    print(f"[shared] {cfg} chunk {chunk}", flush=True)
+    w, ctx = pi.make_weights(cfg, threads=4), pi.make_context(cfg)
+    outs = oracle_run(cfg, w, ctx)
+    dec = make_decoder(cfg, w)
+    dec.set_option(binding.PD_OPT_PREFILL_CHUNK, chunk)
+    stats = compare_teacher_forced(cfg, w, ctx, dec, outs, log=lambda m: print(m, flush=True))
+    assert stats["rows"] == cfg.batch * (cfg.n_sub * (cfg.sub_tokens + 1) - 1)
+    dec.close()
+
+
+@pytest.mark.parametrize("name,lens", [
+    ("hd64", [[5, 3, 2], [2], [6, 5, 6], [1, 1], [6]]),          # 10, 2, 17, 2 and 6 rows, padded to 17
+    ("hd128-llama", [[6, 6, 6], [3, 6], [6], [2, 2, 2], [6, 4, 5]]),
+])
+def test_targets_share_a_pass(name, lens):
+    """Every request's logits, terms and loss, and nothing written behind a request's last row."""
+    cfg = next(c for c in CASES if c.name == name)
+    print(f"[shared] {cfg} targets {lens}", flush=True)
+    w, ctx = pi.make_weights(cfg, threads=4), pi.make_context(cfg)
+    rng = np.random.default_rng(3)
+    targets = [[[0] + [int(t) for t in rng.integers(1, cfg.vocab, n - 1)] for n in t] for t in lens]
+    model = OracleModel(cfg, w)
+    dec = make_decoder(cfg, w)
+    dec.prefill_context(ctx, cfg.n_sub, cfg.delta_t, cfg.sub_tokens, cfg.time_steps)
+    for _ in range(2):                # the second pass meets the tags and caches of the first
+        logits, nll, loss = dec.teacher_forced(targets)
+        for b, target in enumerate(targets):
+            want, terms, total = training.teacher_forced(model, ctx[b], target, cfg.delta_t)
+            assert np.abs(logits[b].cpu().numpy() - want).max() < 2e-2
+            assert np.abs(nll[b] - terms).max() < 4e-2 and abs(loss[b] - total) < 4e-2 * max(1, len(terms))
+        targets = [t[::-1] if i % 2 else t for i, t in enumerate(targets)]
+    dec.close()
