@@ -6,8 +6,8 @@
 // so the rule is one integer compare per key.  Prefill rows use the same kernel
 // with a causal limit instead (key index < lim).
 //
-// grid (split, head, request * query-group); block = 4 waves.  The 32-key blocks of one
-// (request, head) are dealt round-robin to the 4*nsplit waves that serve it, so the
+// grid (split, head, request * query-group); block = 4 or 8 waves.  The 32-key blocks of one
+// (request, head) are dealt round-robin to the waves of all splits that serve it, so the
 // first block of every wave is known at launch and its K/V fragments are requested
 // before anything else is read.  Per block of 32 keys: 2*(hd/32) K fragments and hd/16 V fragments
 // (1 KiB each, contiguous), two 16-key score tiles S^T = K Q^T, mask, online
@@ -58,12 +58,12 @@ __device__ __forceinline__ f16x8 ld_kv(const uint4 *p) {
   return STREAM ? __builtin_nontemporal_load((const f16x8 *)p) : *(const f16x8 *)p;
 }
 
-template <int HD, bool SPLIT, bool PAIR, bool BIAS = false, bool STREAM = false>
-__global__ __launch_bounds__(256, PAIR ? 1 : 3) void k_attn_mfma(AttnArgs a) {
+template <int HD, bool SPLIT, bool PAIR, bool BIAS = false, bool STREAM = false, int NW = 4>
+__global__ __launch_bounds__(64 * NW, PAIR ? 1 : NW == 4 ? 3 : NW / 4) void k_attn_mfma(AttnArgs a) {
   constexpr int NC = HD / 32, NHB = HD / 16, PSTR = HD + 2;   // partial: m, l, O[HD] per query
-  __shared__ float sm_m[4][16], sm_l[4][16];
+  __shared__ float sm_m[NW][16], sm_l[NW][16];
   __shared__ float sm_bias[BIAS ? BIAS_MAX : 1];
-  __shared__ floatx4 sm_o[4][HD / 16][64];
+  __shared__ floatx4 sm_o[NW][HD / 16][64];
   __shared__ uint4 sm_q[(SPLIT ? 2 : 1) * NC][64];
   int split = blockIdx.x, h = blockIdx.y, z = blockIdx.z;
   int reqi = z / a.nqg, qg = z % a.nqg, req = a.req0 + reqi;
@@ -83,21 +83,20 @@ __global__ __launch_bounds__(256, PAIR ? 1 : 3) void k_attn_mfma(AttnArgs a) {
   if (BIAS) {
     q_pos = a.rt.pos[r] - a.pos0;
     bias_pre[0] = a.bias[(size_t)h * a.bias_len + min((int)threadIdx.x, a.bias_len - 1)];
-    bias_pre[1] = a.bias[(size_t)h * a.bias_len + min((int)threadIdx.x + 256, a.bias_len - 1)];
+    bias_pre[1] = a.bias[(size_t)h * a.bias_len + min((int)threadIdx.x + 64 * NW, a.bias_len - 1)];
   }
-  // Query fragments (high and low parts) go to LDS, in operand order: the four waves share them,
+  // Query fragments (high and low parts) go to LDS, in operand order: the waves share them,
   // and keeping them out of the registers leaves room for three waves per SIMD.  Rows without a
   // token keep whatever finite numbers their q slots hold: all their keys are masked below, and
   // their output is never written.
   const size_t q_off = act_off(r, h * HD + g * 8, a.d);
-  constexpr int NQ = (NC + 3) / 4;            // fragments per wave
-  uint4 qh[NQ], qlo[SPLIT ? NQ : 1];
-#pragma unroll
-  for (int i = 0; i < NQ; ++i) {
-    int c = min(wave + 4 * i, NC - 1);
+  static_assert(NC <= 4, "one query fragment (and its low part) per wave");
+  uint4 qh, qlo;
+  {
+    const int c = min(wave, NC - 1);
     size_t off = q_off + (size_t)c * 512;     // the next 32 dims are the next fragment
-    qh[i] = *(const uint4 *)(a.q + off);
-    if (SPLIT) qlo[i] = *(const uint4 *)(a.q_lo + off);
+    qh = *(const uint4 *)(a.q + off);
+    if (SPLIT) qlo = *(const uint4 *)(a.q_lo + off);
   }
 
   const uint4 *Kp = (const uint4 *)(a.kc + ((size_t)req * a.H + h) * a.kv_cap * HD) + lane;
@@ -107,10 +106,10 @@ __global__ __launch_bounds__(256, PAIR ? 1 : 3) void k_attn_mfma(AttnArgs a) {
   // subsequence tags of the generated-side slots, 8 keys (16 bytes) per lane group
   const uint16_t *gs = a.gen_sub + (size_t)req * a.gen_stride;
   const int L8 = a.L & ~7;
-  // 32-key blocks are dealt round-robin to the 4*nsplit waves that serve this (request, head):
+  // 32-key blocks are dealt round-robin to the NW*nsplit waves that serve this (request, head):
   // whatever the current key count, no wave gets more than one block above the average
-  const int stride = 4 * a.nsplit;
-  int kb = split * 4 + wave;
+  const int stride = NW * a.nsplit;
+  int kb = split * NW + wave;
   Frag kf[2][NC], vf[NHB];
   Frag kl[PAIR ? 2 : 1][PAIR ? NC : 1], vl[PAIR ? NHB : 1];
   union { uint4 u; uint16_t s[8]; } tg, kco;
@@ -139,15 +138,14 @@ __global__ __launch_bounds__(256, PAIR ? 1 : 3) void k_attn_mfma(AttnArgs a) {
   load_k(min(kb, a.nblk_static - 1));
   load_v(min(kb, a.nblk_static - 1));
   // (waves beyond the fragment count store a copy of the last fragment: same bytes, same place)
-#pragma unroll
-  for (int i = 0; i < NQ; ++i) {
-    int c = min(wave + 4 * i, NC - 1);
-    sm_q[c][lane] = qh[i];
-    if (SPLIT) sm_q[NC + c][lane] = qlo[i];
+  {
+    const int c = min(wave, NC - 1);
+    sm_q[c][lane] = qh;
+    if (SPLIT) sm_q[NC + c][lane] = qlo;
   }
   if (BIAS) {
-    sm_bias[threadIdx.x] = bias_pre[0];
-    if (threadIdx.x + 256 < BIAS_MAX) sm_bias[threadIdx.x + 256] = bias_pre[1];
+    if (threadIdx.x < BIAS_MAX) sm_bias[threadIdx.x] = bias_pre[0];
+    if (threadIdx.x + 64 * NW < BIAS_MAX) sm_bias[threadIdx.x + 64 * NW] = bias_pre[1];
   }
   __syncthreads();
 
@@ -260,19 +258,19 @@ __global__ __launch_bounds__(256, PAIR ? 1 : 3) void k_attn_mfma(AttnArgs a) {
   l_run += __shfl_xor(l_run, 16);
   l_run += __shfl_xor(l_run, 32);
 
-  // ---- merge the 4 waves of the block (log-sum-exp) ----
+  // ---- merge the waves of the block (log-sum-exp) ----
   // every wave stores its accumulators as 16-byte quads (lane order: conflict-free); after the
-  // barrier wave w owns the 16-dim blocks w, w + 4, ... and sums the four copies of each
+  // barrier wave w owns the 16-dim blocks w, w + NW, ... and sums the NW copies of each
   if (g == 0) { sm_m[wave][n] = m_run; sm_l[wave][n] = l_run; }
 #pragma unroll
   for (int i = 0; i < NHB; ++i) sm_o[wave][i][lane] = o_acc[i];
   __syncthreads();
-  float mw[4], M = -INFINITY;
+  float mw[NW], M = -INFINITY;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) { mw[w] = sm_m[w][n]; M = fmaxf(M, mw[w]); }
-  float fw[4], lsum = 0.f;
+  for (int w = 0; w < NW; ++w) { mw[w] = sm_m[w][n]; M = fmaxf(M, mw[w]); }
+  float fw[NW], lsum = 0.f;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
+  for (int w = 0; w < NW; ++w) {
     fw[w] = mw[w] == -INFINITY ? 0.f : exp2f(mw[w] - M);
     lsum += fw[w] * sm_l[w][n];
   }
@@ -283,10 +281,10 @@ __global__ __launch_bounds__(256, PAIR ? 1 : 3) void k_attn_mfma(AttnArgs a) {
   float *pp = a.part + (unit * a.nsplit + split) * (size_t)(PSTR * 16);
   if (a.nsplit > 1 && wave == 0 && g == 0) { pp[n] = M; pp[16 + n] = lsum; }
   const float inv = 1.f / lsum;
-  for (int i = wave; i < NHB; i += 4) {
+  for (int i = wave; i < NHB; i += NW) {
     floatx4 o = fw[0] * sm_o[0][i][lane];
 #pragma unroll
-    for (int w = 1; w < 4; ++w) o += fw[w] * sm_o[w][i][lane];
+    for (int w = 1; w < NW; ++w) o += fw[w] * sm_o[w][i][lane];
     if (a.nsplit == 1) {
       float y[4] = {o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv};
       store4_split(a.out, a.out_lo, act_off(r, h * HD + i * 16 + 4 * g, a.d), y);
@@ -360,25 +358,46 @@ __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a) {
   store4_split(a.out, a.out_lo, act_off(r, h * HD + i * 16 + 4 * g, a.d), y);
 }
 
-static int pick_splits(pd_ctx *c, int units, int nblk) {
+// Work-groups per (request, head, query group), and their waves.
+static int pick_splits(pd_ctx *c, int units, int nblk, bool decode, bool pair, int *nw) {
   int cap = std::max(1, c->part_units / units);
   if (c->opt_splits > 0) return std::min(c->opt_splits, cap);
   // One block per compute unit, every wave streaming several key blocks back to back (measured at
   // 16 heads x 8k keys: 16.2 us with 256 blocks, 17.2 with 512 or 768, 18.7 with 320; at 4 x 32 heads
   // x 4k keys 256 blocks are 4 us per launch faster than 768).  Always at least one key block per wave.
-  // Up to 32 key blocks (8 per wave) a single block per (request, head) is faster than splits plus the
-  // merge kernel (measured at 12 heads, 512 + 280 keys: 0.54 against 0.59 ms for a step of 12 layers
-  // with two attentions each; at 1024 + 300 keys one split is slower than the automatic 12).
-  if (nblk <= 32) return 1;
   int want = std::max(1, 256 / units);
   int by_keys = std::max(1, nblk / 4);
-  return std::max(1, std::min(std::min(want, by_keys), cap));
+  const int splits = std::max(1, std::min(std::min(want, by_keys), cap));
+  // Short key sets: one work-group of 8 waves per unit and no merge kernel (4 us) where the longer walk of its
+  // waves, about 0.55 us per 32-key block, costs less than that.  Whole passes, 8 waves against splits of 4 waves
+  // plus merge: 12 units x 1024-1300 keys 6.89 against 7.18 ms, 128 units x 2048-2400 keys 26.6 against 27.6 ms;
+  // one work-group of 8 against 4 waves: 24 units x 700 keys 1.98 against 2.01 ms; 16 waves lose to 8 everywhere.
+  // Beyond 96 blocks a unit's keys want more than one compute unit's share of the memory system (128 units x
+  // 4096-6000 keys: 52.9 against 51.7 ms); with more units than compute units 4 waves do as well or better (288
+  // units x 384 keys 4.46 against 4.51 ms).
+  if (nblk <= 32) {
+    if (decode && !pair && units <= 256) *nw = 8;
+    return 1;
+  }
+  if (decode && !pair && units <= 256 && nblk <= 96 && nblk * 0.55 / 8 < nblk * 0.55 / (4 * splits) + 4) {
+    *nw = 8;
+    return 1;
+  }
+  return splits;
+}
+
+template <int HD, bool SPLIT, bool PAIR, bool BIAS, bool STREAM, int NW>
+static void launch_attn_nw(dim3 grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1, const AttnArgs &a) {
+  if (e0 || e1) hipExtLaunchKernelGGL((k_attn_mfma<HD, SPLIT, PAIR, BIAS, STREAM, NW>), grid, dim3(64 * NW), 0, s, e0, e1, 0, a);
+  else hipLaunchKernelGGL((k_attn_mfma<HD, SPLIT, PAIR, BIAS, STREAM, NW>), grid, dim3(64 * NW), 0, s, a);
 }
 
 template <int HD, bool SPLIT, bool PAIR, bool BIAS, bool STREAM>
-static void launch_attn(dim3 grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1, const AttnArgs &a) {
-  if (e0 || e1) hipExtLaunchKernelGGL((k_attn_mfma<HD, SPLIT, PAIR, BIAS, STREAM>), grid, dim3(256), 0, s, e0, e1, 0, a);
-  else hipLaunchKernelGGL((k_attn_mfma<HD, SPLIT, PAIR, BIAS, STREAM>), grid, dim3(256), 0, s, a);
+static void launch_attn(dim3 grid, int nw, hipStream_t s, hipEvent_t e0, hipEvent_t e1, const AttnArgs &a) {
+  if constexpr (!PAIR) {
+    if (nw == 8) return launch_attn_nw<HD, SPLIT, PAIR, BIAS, STREAM, 8>(grid, s, e0, e1, a);
+  }
+  launch_attn_nw<HD, SPLIT, PAIR, BIAS, STREAM, 4>(grid, s, e0, e1, a);
 }
 
 int mfma_attention(pd_ctx *c, const LayerPtrs &lw, int A, int nreq, int req0, int kv_override,
@@ -417,7 +436,8 @@ int mfma_attention(pd_ctx *c, const LayerPtrs &lw, int A, int nreq, int req0, in
   // the most keys this launch can meet: prefill knows it, decode takes the end of the run
   int n_keys = kv_override >= 0 ? kv_override : c->L + c->S * (c->M + 1);
   a.nblk_static = std::min((n_keys + 31) / 32, c->kv_cap / 32);
-  a.nsplit = pick_splits(c, units, a.nblk_static);
+  int nw = 4;
+  a.nsplit = pick_splits(c, units, a.nblk_static, kv_override < 0 || mode, a.kc_lo != nullptr, &nw);
   dim3 grid(a.nsplit, g.n_head, nreq * a.nqg);
   // measurement: mode 1 attaches a start and a stop event to the dispatch of the main kernel itself
   // (their difference is the kernel's execution time), mode 2 records events before the main kernel
@@ -453,16 +473,16 @@ int mfma_attention(pd_ctx *c, const LayerPtrs &lw, int A, int nreq, int req0, in
 #define PD_ATTN_ONE(HDV, ARGS)                                                                         \
   do {                                                                                                 \
     const bool sp = a.q_lo != nullptr, pr = a.kc_lo != nullptr, bi = a.bias != nullptr;                \
-    if (bi && sp) launch_attn<HDV, true, false, true, false>(grid, s, pe0, pe1, ARGS);                 \
-    else if (bi) launch_attn<HDV, false, false, true, false>(grid, s, pe0, pe1, ARGS);                 \
-    else if (pr && sp && stream) launch_attn<HDV, true, true, false, true>(grid, s, pe0, pe1, ARGS);   \
-    else if (pr && sp) launch_attn<HDV, true, true, false, false>(grid, s, pe0, pe1, ARGS);            \
-    else if (pr && stream) launch_attn<HDV, false, true, false, true>(grid, s, pe0, pe1, ARGS);        \
-    else if (pr) launch_attn<HDV, false, true, false, false>(grid, s, pe0, pe1, ARGS);                 \
-    else if (sp && stream) launch_attn<HDV, true, false, false, true>(grid, s, pe0, pe1, ARGS);        \
-    else if (sp) launch_attn<HDV, true, false, false, false>(grid, s, pe0, pe1, ARGS);                 \
-    else if (stream) launch_attn<HDV, false, false, false, true>(grid, s, pe0, pe1, ARGS);             \
-    else launch_attn<HDV, false, false, false, false>(grid, s, pe0, pe1, ARGS);                        \
+    if (bi && sp) launch_attn<HDV, true, false, true, false>(grid, nw, s, pe0, pe1, ARGS);                 \
+    else if (bi) launch_attn<HDV, false, false, true, false>(grid, nw, s, pe0, pe1, ARGS);                 \
+    else if (pr && sp && stream) launch_attn<HDV, true, true, false, true>(grid, nw, s, pe0, pe1, ARGS);   \
+    else if (pr && sp) launch_attn<HDV, true, true, false, false>(grid, nw, s, pe0, pe1, ARGS);            \
+    else if (pr && stream) launch_attn<HDV, false, true, false, true>(grid, nw, s, pe0, pe1, ARGS);        \
+    else if (pr) launch_attn<HDV, false, true, false, false>(grid, nw, s, pe0, pe1, ARGS);                 \
+    else if (sp && stream) launch_attn<HDV, true, false, false, true>(grid, nw, s, pe0, pe1, ARGS);        \
+    else if (sp) launch_attn<HDV, true, false, false, false>(grid, nw, s, pe0, pe1, ARGS);                 \
+    else if (stream) launch_attn<HDV, false, false, false, true>(grid, nw, s, pe0, pe1, ARGS);             \
+    else launch_attn<HDV, false, false, false, false>(grid, nw, s, pe0, pe1, ARGS);                        \
   } while (0)
 #define PD_ATTN(HDV)                                                                                   \
   do {                                                                                                 \
