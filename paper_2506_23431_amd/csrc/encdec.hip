@@ -138,10 +138,12 @@ int encdec_decoder_layer(pd_ctx *c, int l, int R, hipStream_t s, int A, int nreq
   const LayerPtrs &lw = c->layers[l];
   const int d = g.d_model;
   int rc;
-  if ((rc = mfma_norm(c, lw.n1g, nullptr, R, s))) return rc;
+  // (the previous layer's second FFN projection may have prepared this norm)
+  const bool first = c->norm_fused;
+  if (!first && (rc = mfma_norm(c, lw.n1g, nullptr, R, s))) return rc;
   GemmArgs a;
   mfma_gemm_base(c, a, R);
-  if ((rc = mfma_qkv(c, a, lw.p_wqkv, 3 * d / 16, 0, lw.kc, lw.vc, nullptr, nullptr, R, s))) return rc;
+  if ((rc = mfma_qkv(c, a, lw.p_wqkv, 3 * d / 16, 0, lw.kc, lw.vc, nullptr, nullptr, R, s, first ? lw.q1 : nullptr))) return rc;
   AttnMode self;
   memset(&self, 0, sizeof(self));
   self.L = 0; self.scale = 1.f;
@@ -161,5 +163,5 @@ int encdec_decoder_layer(pd_ctx *c, int l, int R, hipStream_t s, int A, int nreq
   memset(&cross, 0, sizeof(cross));
   cross.kc = lw.xkc; cross.vc = lw.xvc; cross.qinfo = c->qinfo_x; cross.L = c->Lx; cross.scale = 1.f;
   if ((rc = mfma_attention(c, lw, A, nreq, req0, c->Lx, s, &cross))) return rc;
-  return mfma_out_ffn(c, a, lw.p_co, lw, R, s);
+  return mfma_out_ffn(c, a, lw.p_co, lw, R, s, kv_self < 0 && l + 1 < g.n_layer ? c->layers[l + 1].n1g : nullptr);
 }

@@ -120,7 +120,7 @@ int mfma_fold_norms(pd_ctx *c, hipStream_t s) {
   for (int l = 0; l < g.n_layer; ++l) {
     LayerPtrs &lp = c->layers[l];
     if ((rc = mfma_fold(lp.c1, lp.c2, lp.p_w1, lp.n2g, g.norm_kind == 0 ? lp.n2b : nullptr, n_out, g.d_model, s))) return rc;
-    if (c->arch == 0 && (rc = mfma_fold(lp.q1, lp.q2, lp.p_wqkv, lp.n1g, g.norm_kind == 0 ? lp.n1b : nullptr, 3 * g.d_model, g.d_model, s))) return rc;
+    if ((rc = mfma_fold(lp.q1, lp.q2, lp.p_wqkv, lp.n1g, g.norm_kind == 0 ? lp.n1b : nullptr, 3 * g.d_model, g.d_model, s))) return rc;
   }
   return PD_OK;
 }
@@ -362,7 +362,7 @@ int mfma_norm(pd_ctx *c, const float *gain, const float *bias, int R, hipStream_
 // fragments of the row tiles, then the weight fragments of its tiles) into registers of their own;
 // only then the multiplies run.  A share that is not a multiple of U ends with chunks of 4, 2 and
 // 1 k-tiles, so that no load is ever conditional.
-// This file is compiled once per epilogue (PD_GEMM_EPI = 0..7: kernels and launch code of that
+// This file is compiled once per epilogue (PD_GEMM_EPI = 0..6: kernels and launch code of that
 // epilogue) and once without (weight packing, norm kernel, dispatcher).
 // ---------------------------------------------------------------------------
 // epilogue of one 16-column tile: lane holds y[r][n0 + j], r = i*16 + m, n0 = nt*16 + 4g, j = 0..3
@@ -419,7 +419,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, int nt, const f
   floatx4 acc[RT];
 #pragma unroll
   for (int i = 0; i < RT; ++i) acc[i] = acc_in[i];
-  if ((EPI == EPI_GELU || EPI == EPI_SWIGLU || EPI == EPI_QKV_NORM) && nrm) {
+  if ((EPI == EPI_GELU || EPI == EPI_SWIGLU || EPI == EPI_QKV || EPI == EPI_QKV_ROPE) && nrm) {
     // the activations were gain * x: finish the norm here (columns in the packed order of the weights)
     const float4 c1 = npre ? npre->c1 : *(const float4 *)(a.c1 + n0);
     const float4 c2 = npre ? npre->c2 : (a.c2 ? *(const float4 *)(a.c2 + n0) : make_float4(0.f, 0.f, 0.f, 0.f));
@@ -489,7 +489,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, int nt, const f
       }
       if (g < 2 && r < a.R) store4_split(a.out_bf, a.out_lo, act_off(r, nt * 8 + 4 * g, a.ld), y);
     }
-  } else if (EPI == EPI_QKV || EPI == EPI_QKV_ROPE || EPI == EPI_QKV_NORM) {
+  } else if (EPI == EPI_QKV || EPI == EPI_QKV_ROPE) {
     int sec = n0 / a.d + a.sec0, nl = n0 % a.d, h = nl / a.hd;
     int half = a.hd >> 1;
 #pragma unroll
@@ -635,7 +635,7 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(GemmArgs a) {
   const int kt0 = min(gk * a.k_share, KT), kt1 = min(kt0 + a.k_share, KT);
   // row data of the KV-append epilogue, requested now so that it arrives with the weights
   // (EPI_LM: where the row's logits go)
-  constexpr bool QKV = EPI == EPI_QKV || EPI == EPI_QKV_ROPE || EPI == EPI_QKV_NORM;
+  constexpr bool QKV = EPI == EPI_QKV || EPI == EPI_QKV_ROPE;
   int4 kvi[QKV || EPI == EPI_LM ? RT : 1];
   if (QKV || EPI == EPI_LM) {
 #pragma unroll
@@ -645,7 +645,7 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(GemmArgs a) {
 #pragma unroll
   for (int t = 0; t < NT; ++t) tile[t] = min(nt0 + t, a.n_tiles - 1);   // tiles past the end repeat the last one
   // one row tile: what the epilogue needs from memory is asked for now, so that it arrives with the weights
-  constexpr bool FUSED_IN = RT == 1 && (EPI == EPI_GELU || EPI == EPI_SWIGLU || EPI == EPI_QKV_NORM);
+  constexpr bool FUSED_IN = RT == 1 && (EPI == EPI_GELU || EPI == EPI_SWIGLU || EPI == EPI_QKV || EPI == EPI_QKV_ROPE);
   constexpr bool FUSED_OUT = RT == 1 && EPI == EPI_RESID_NORM;
   __shared__ float2 sm_stat[FUSED_IN ? NW_K : 1][16];
   float4 pre_s[PS];
@@ -752,6 +752,25 @@ static int launch_gemm_small_nt(GemmArgs a, int ks, hipStream_t s) {
   while (nwk < 16 && (long)groups * ks * nwk < 1500 && (per_block + nwk - 1) / nwk > 2) nwk *= 2;
   a.k_share = (per_block + nwk - 1) / nwk;
   dim3 grid(groups, ks);
+  // a projection that completes the rows is not cut over blocks; with 5-8 k-tiles per wave it asks for all of them at
+  // once instead of in two batches (K 3072, width 768: in two batches it cost more than the norm kernel it replaces)
+  if constexpr (EPI == EPI_RESID_NORM && NT == 1) {
+    constexpr int UL = SPLIT ? 6 : 8;
+    if (nwk == 16 && a.k_share > 4 && a.k_share <= UL) {
+#define PD_LAUNCH_U(UU)                                                                                         \
+  do {                                                                                                          \
+    if (a.stream_w)                                                                                             \
+      hipLaunchKernelGGL((k_gemm_s<RT, NT, 16, UU, EPI, SPLIT, PACK, false, true>), grid, dim3(1024), 0, s, a); \
+    else                                                                                                        \
+      hipLaunchKernelGGL((k_gemm_s<RT, NT, 16, UU, EPI, SPLIT, PACK>), grid, dim3(1024), 0, s, a);              \
+  } while (0)
+      if (a.k_share <= 6) PD_LAUNCH_U(6);
+      else PD_LAUNCH_U(UL);
+#undef PD_LAUNCH_U
+      PD_CHECK_HIP(hipGetLastError());
+      return PD_OK;
+    }
+  }
 #define PD_LAUNCH(NWK) \
   do {                                                                                            \
     if (a.stream_w)                                                                               \
@@ -1077,7 +1096,7 @@ static int launch_gemm_split(const GemmArgs &a, int rows, hipStream_t s) {
   constexpr bool zrows = EPI != EPI_LM;
   if (zrows && mfma_gemm_row_tile_blocks(a.n_tiles, a.K, rows, EPI == EPI_RESID ? a.max_parts : 1))
     return launch_gemm_zrows<EPI, SPLIT, (EPI == EPI_RESID_NORM ? 1 : 4)>(a, rows, s);
-  if (EPI == EPI_RESID_NORM || EPI == EPI_QKV_NORM)
+  if (EPI == EPI_RESID_NORM || a.stats_in)
     PD_REQUIRE(rows <= 16, PD_EINVAL, "a projection of this shape cannot prepare or finish a norm for %d rows", rows);
   switch (mfma_gemm_row_tiles(rows)) {
     case 16: return launch_gemm_small<1, EPI, SPLIT, false>(a, s);
@@ -1090,10 +1109,10 @@ static int launch_gemm_split(const GemmArgs &a, int rows, hipStream_t s) {
 
 template <int EPI>
 static int launch_gemm(const GemmArgs &a, int rows, hipStream_t s) {
-  if (EPI == EPI_RESID_NORM || EPI == EPI_QKV_NORM)
+  if (EPI == EPI_RESID_NORM || a.stats_in)
     PD_REQUIRE(rows <= 128 && a.R <= 128, PD_EINVAL,
                "projections that prepare or finish a norm take at most 128 rows (%d)", rows);
-  if constexpr (EPI != EPI_RESID_NORM && EPI != EPI_QKV_NORM) {
+  if constexpr (EPI != EPI_RESID_NORM) {
     if (rows > 128) {
       PD_REQUIRE(!a.packed, PD_EINVAL, "packed activations hold at most 8 rows (%d)", rows);
       return a.xn_lo ? launch_gemm_rows<EPI, true>(a, rows, s) : launch_gemm_rows<EPI, false>(a, rows, s);
@@ -1132,7 +1151,6 @@ int mfma_gemm_epi3(const GemmArgs &a, int rows, hipStream_t s);
 int mfma_gemm_epi4(const GemmArgs &a, int rows, hipStream_t s);
 int mfma_gemm_epi5(const GemmArgs &a, int rows, hipStream_t s);
 int mfma_gemm_epi6(const GemmArgs &a, int rows, hipStream_t s);
-int mfma_gemm_epi7(const GemmArgs &a, int rows, hipStream_t s);
 
 int mfma_gemm(int epi, const GemmArgs &a, int rows, hipStream_t s) {
   switch (epi) {
@@ -1143,7 +1161,6 @@ int mfma_gemm(int epi, const GemmArgs &a, int rows, hipStream_t s) {
     case EPI_SWIGLU: return mfma_gemm_epi4(a, rows, s);
     case EPI_LM: return mfma_gemm_epi5(a, rows, s);
     case EPI_RESID_NORM: return mfma_gemm_epi6(a, rows, s);
-    case EPI_QKV_NORM: return mfma_gemm_epi7(a, rows, s);
   }
   pd_set_error("unknown epilogue %d", epi);
   return PD_EINVAL;

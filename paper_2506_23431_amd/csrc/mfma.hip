@@ -30,11 +30,12 @@ bool mfma_can_fuse_norm(pd_ctx *c, int R) {
   return R <= 16 || mfma_gemm_row_tile_blocks(d / 16, d, R, 1);
 }
 // The second FFN projection has to give up its cut along K over blocks for this, which leaves one block
-// per 16 output columns.  With the next layer's QKV projection finishing the norm, a step of the 768 / 3072
-// shape measured 0.198 ms against 0.188 ms and one of the 2048 / 8192 shape 1.33-1.34 ms against 1.31 ms
-// (the uncut projection loses what the norm kernel took): only on request (value 2 of the option).
+// per 16 output columns.  While a wave of its 16 holds at most 8 k-tiles, all requested at once, that costs less than
+// the norm kernel (768 / 3072, whole steps: 174.6 against 184.1 us; 1024 / 4096 273 against 289; 512 / 1376 with rotary
+// positions 186 against 204; encoder-decoder 1024 / 4096 22.5 against 22.9 ms per example); beyond it does not (2048 / 8192, 16 k-tiles per
+// wave: 82.6 against 81.1 ms for 64 steps) and happens only on request (value 2 of the option).
 static bool ffn2_prepares_norm(pd_ctx *c, int R) {
-  return R <= 16 && mfma_can_fuse_norm(c, R) && c->opt_fuse_norm == 2 && c->cfg.pos_kind != 1;
+  return R <= 16 && mfma_can_fuse_norm(c, R) && (c->opt_fuse_norm == 2 || (c->cfg.d_ff <= 4096 && c->cfg.d_model <= 1024));
 }
 
 int mfma_qkv(pd_ctx *c, GemmArgs &a, const bf16_t *W, int n_tiles, int sec0, void *kc, void *vc, void *kc_lo,
@@ -48,12 +49,11 @@ int mfma_qkv(pd_ctx *c, GemmArgs &a, const bf16_t *W, int n_tiles, int sec0, voi
   if (c1) {
     a.stats_in = c->nstats; a.stats_tiles = d / 16; a.c1 = c1; a.c2 = g.norm_kind == 0 ? c2 : nullptr;
     a.norm_kind = g.norm_kind; a.norm_d = d; a.norm_eps = g.norm_eps;
-    int rc = mfma_gemm(EPI_QKV_NORM, a, R, s);
-    a.stats_in = nullptr;
-    c->norm_fused = false;
-    return rc;
   }
-  return mfma_gemm(g.pos_kind == 1 ? EPI_QKV_ROPE : EPI_QKV, a, R, s);
+  const int rc = mfma_gemm(g.pos_kind == 1 ? EPI_QKV_ROPE : EPI_QKV, a, R, s);
+  a.stats_in = nullptr;
+  if (c1) c->norm_fused = false;
+  return rc;
 }
 
 // output projection of the attention result in c->att, added to the residual stream (as split-K slices

@@ -96,8 +96,7 @@ __device__ __forceinline__ size_t v_cache_off(int key, int dim, int hd) {
 
 
 // ---- entry points between the sources of the bf16 path -------------------------------------
-enum { EPI_QKV = 0, EPI_QKV_ROPE = 1, EPI_RESID = 2, EPI_GELU = 3, EPI_SWIGLU = 4, EPI_LM = 5, EPI_RESID_NORM = 6,
-       EPI_QKV_NORM = 7 /* EPI_QKV fed gain * x: finishes the norm in its epilogue (stats_in, c1, c2) */ };
+enum { EPI_QKV = 0, EPI_QKV_ROPE = 1, EPI_RESID = 2, EPI_GELU = 3, EPI_SWIGLU = 4, EPI_LM = 5, EPI_RESID_NORM = 6 };
 
 struct GemmArgs {
   const bf16_t *W;       // packed
@@ -126,7 +125,7 @@ struct GemmArgs {
   // gain * x_res as activation fragments, stats_out[row][tile] the sum and the sum of squares of x_res
   // over the tile's 16 columns
   float *x_res; const float *gain; float2 *stats_out;
-  // EPI_GELU / EPI_SWIGLU with stats_in != NULL: the activations are gain * x (not normalised); the
+  // EPI_GELU / EPI_SWIGLU / EPI_QKV* with stats_in != NULL: the activations are gain * x (not normalised); the
   // epilogue applies the norm, y = rstd * (acc - mean * c1[n]) + c2[n], with mean and rstd of every row
   // from stats_in[row][stats_tiles] and c1 = W gain, c2 = W bias (c2 NULL: no bias)
   const float2 *stats_in; int stats_tiles; const float *c1, *c2; int norm_kind, norm_d; float norm_eps;
