@@ -337,6 +337,8 @@ __global__ __launch_bounds__(1024) void k_commit(SchedState st, const float *par
   // about one memory round trip: the schedule state of the request, and the winners of the vocabulary
   // tiles of every row, whether or not the row selects a token.
   __shared__ int s_arg[1024];           // s_arg[a]: argmax of row a of this request (a < A <= 1024)
+  __shared__ float s_best[16];
+  __shared__ int s_idx[16];
   const int b = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nwave = blockDim.x >> 6;
   const int done = st.done[b], t = st.step[b], k = st.k_open[b];
   const int i0 = threadIdx.x;           // subsequence of this thread in the first pass
@@ -345,18 +347,22 @@ __global__ __launch_bounds__(1024) void k_commit(SchedState st, const float *par
     r0 = st.row_of[b * S + i0]; fin0 = st.fin[b * S + i0]; f0 = st.force[b * S + i0];
     nt0 = st.n_tok[b * S + i0];
   }
-  // stage 1: second stage of the argmax, one wave per row; lowest index wins ties (Eq. 4)
-  for (int a = wave; a < A; a += nwave) {
+  // stage 1: second stage of the argmax, `share` waves per row (all 16 work also when there are few rows); lowest
+  // index wins ties (Eq. 4)
+  const int share = max(1, nwave / A), part = wave % share, span = (n_tiles + share - 1) / share;
+  const int t_lo = part * span, t_hi = min(t_lo + span, n_tiles);
+  for (int a = wave / share; a < A; a += max(1, nwave / share)) {
+    if (wave >= share * (nwave / share)) break;        // (waves left over when A does not divide their number)
     int r = b * A + a;
     int bi = 0x7fffffff;
     const float *pv = part_val + (size_t)r * n_tiles;
     const int32_t *pi = part_idx + (size_t)r * n_tiles;
     float best = -INFINITY;
-    for (int t0 = lane; t0 < n_tiles; t0 += 64 * 8) {
+    for (int t0 = t_lo + lane; t0 < t_hi; t0 += 64 * 8) {
       float v[8]; int ix[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        int tt = min(t0 + 64 * u, n_tiles - 1);        // clamped: a repeated candidate changes nothing
+        int tt = min(t0 + 64 * u, t_hi - 1);           // clamped: a repeated candidate changes nothing
         v[u] = pv[tt];
         ix[u] = pi[tt];
       }
@@ -370,9 +376,26 @@ __global__ __launch_bounds__(1024) void k_commit(SchedState st, const float *par
       int oi = __shfl_xor(bi, o);
       if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
     }
-    if (lane == 0) s_arg[a] = bi;
+    if (lane == 0) {
+      if (share == 1) s_arg[a] = bi;
+      else { s_best[wave] = best; s_idx[wave] = bi; }
+    }
   }
   __syncthreads();
+  if (share > 1) {                      // the same for the whole block: one row per group of waves
+    const int a = threadIdx.x;
+    if (a < A) {
+      float best = s_best[a * share];
+      int bi = s_idx[a * share];
+      for (int i = 1; i < share; ++i) {
+        const float ov = s_best[a * share + i];
+        const int oi = s_idx[a * share + i];
+        if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
+      }
+      s_arg[a] = bi;
+    }
+    __syncthreads();
+  }
   if (done) return;                     // the same for every thread of the block
   // stage 2: Algorithm 1 lines 9-13, thread i for subsequence i.  A subsequence selects a token
   // when it has a row and was unfinished when the rows were laid out.
