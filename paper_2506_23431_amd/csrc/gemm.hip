@@ -887,12 +887,6 @@ __global__ __launch_bounds__(512, 1) void k_gemm_t(GemmArgs a) {
   const int per_slice = (KT + (int)gridDim.y - 1) / (int)gridDim.y;
   const int kt0 = min((int)blockIdx.y * per_slice, KT), kt1 = min(kt0 + per_slice, KT);
   const int rt0 = blockIdx.z * RT, r0 = rt0 * 16;
-  constexpr bool QKV = EPI == EPI_QKV || EPI == EPI_QKV_ROPE;
-  int4 kvi[QKV || EPI == EPI_LM ? RT : 1];
-  if (QKV || EPI == EPI_LM) {
-#pragma unroll
-    for (int i = 0; i < RT; ++i) kvi[i] = (QKV ? a.rt.kvinfo : a.rt.qinfo)[r0 + i * 16 + m];
-  }
   const int nt0 = (blockIdx.x * NW + w) * NT;
   floatx4 acc[NT][RT];
 #pragma unroll
@@ -974,6 +968,13 @@ __global__ __launch_bounds__(512, 1) void k_gemm_t(GemmArgs a) {
       }
     }
   }
+  // row data of the epilogue (asked for here: it would cost the loop 4 RT registers)
+  constexpr bool QKV = EPI == EPI_QKV || EPI == EPI_QKV_ROPE;
+  int4 kvi[QKV || EPI == EPI_LM ? RT : 1];
+  if (QKV || (EPI == EPI_LM && a.logits)) {
+#pragma unroll
+    for (int i = 0; i < RT; ++i) kvi[i] = (QKV ? a.rt.kvinfo : a.rt.qinfo)[r0 + i * 16 + m];
+  }
 #pragma unroll
   for (int t = 0; t < NT; ++t)
     if (nt0 + t < a.n_tiles) gemm_epilogue<RT, EPI>(a, nt0 + t, acc[t], kvi, lane, r0);
@@ -1003,7 +1004,7 @@ static int launch_gemm_cut(GemmArgs a, int rows, int ks, hipStream_t s) {
 // (192-4096 rows, K 768-11008, N 768-12288) follow, in us, with n = blocks per compute unit and kt = k-tiles of a
 // block,
 //   waves along K (k_gemm_s)   1.5 + n (0.0071 kt KiB + 0.2 RT NT) + 0.25 per further batch of 4 k-tiles of a wave
-//   shared row tiles (k_gemm_t)  4 + n (kt max(0.03 RT NT, 0.0175 KiB) + 0.35 RT NT)
+//   shared row tiles (k_gemm_t)  4 + n (kt max(0.045-0.049 RT NT, 0.0175 KiB) + 0.35 RT NT)
 // where KiB is what a block requests per k-tile: RT NT multiplies and their operands per k-tile, and per output
 // tile the epilogue.  The first keeps no barrier in its loop and fills the chip with small tiles: 192 rows, K 768,
 // N 3072 5.7 us against 28 with 128 x 256 tiles (24 blocks); 512 rows 9.9 against 28; from about 1024 rows the
@@ -1027,7 +1028,7 @@ static RowTiling choose_row_tiling(int n_tiles, int KT, int rows, int max_parts,
       const double kib = (c.cut ? c.nt : 8 * c.nt) + parts * c.rt, out = c.rt * c.nt;
       double us;
       if (c.cut) us = 1.5 + n * (0.0071 * kt * kib + 0.2 * out) + 0.25 * ((kt + 4 * c.nwk - 1) / (4 * c.nwk) - 1);
-      else us = 4 + n * (kt * std::max(0.015 * parts * out, 0.0175 * kib) + 0.35 * out);
+      else us = 4 + n * (kt * std::max((c.rt == 8 ? 0.0225 : 0.0245) * parts * out, 0.0175 * kib) + 0.35 * out);
       us += 0.6 * (ks - 1) * rows * (double)n_tiles * 1.3e-5;      // what the next norm kernel pays for a slice
       if (us < best.us) best = RowTiling{c.cut, c.rt, c.nt, ks, us};
     }

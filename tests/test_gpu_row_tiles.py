@@ -30,7 +30,8 @@ CASES = [
     W("r1025", 512, 8, 2048, 1025),                            # shared row tiles, 4 x 1
     W("r2047-llama", 768, 12, 2048, 2047, **LLAMA),            # 4 x 3 and 4 x 4
     W("r2049", 512, 4, 1024, 2049),                            # 4 x 2
-    W("r4095", 1024, 16, 4096, 4095),                          # 8 x 3, 8 x 4, four K slices
+    W("r4095", 1024, 16, 4096, 4095),                          # 8 x 3, 8 x 4, 4 x 2
+    W("r192", 768, 12, 3072, 192),                             # 2 x 4, 2 x 6, four K slices
 ]
 
 
