@@ -552,12 +552,14 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, int nt, const f
         const int q = a.logits_A > 0 ? r / a.logits_A : kvi[i].w;
         dst = a.logits + ((size_t)q * a.logits_cap + (a.logits_A > 0 ? r - q * a.logits_A : kvi[i].y - 1)) * a.ld_logits;
       }
+      // (a row of logits starts at any multiple of 4 bytes: one 16-byte store, dword-aligned)
+      if (dst && n0 + 3 < a.V) *(floatx4_a4 *)(dst + n0) = floatx4_a4{acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         int n = n0 + j;
         float t = acc[i][j];
         if (n < a.V) {
-          if (dst) dst[n] = t;
+          if (dst && n0 + 3 >= a.V) dst[n] = t;
           if (t > best) { best = t; bi = n; }
         }
       }
@@ -637,7 +639,7 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(GemmArgs a) {
   // (EPI_LM: where the row's logits go)
   constexpr bool QKV = EPI == EPI_QKV || EPI == EPI_QKV_ROPE;
   int4 kvi[QKV || EPI == EPI_LM ? RT : 1];
-  if (QKV || EPI == EPI_LM) {
+  if (QKV || (EPI == EPI_LM && a.logits)) {
 #pragma unroll
     for (int i = 0; i < RT; ++i) kvi[i] = (QKV ? a.rt.kvinfo : a.rt.qinfo)[(rz + i) * 16 + m];
   }

@@ -27,6 +27,7 @@
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx4_a4 __attribute__((ext_vector_type(4), aligned(4)));   // stored at any multiple of 4 bytes
 
 union Frag {
   uint4 u;
