@@ -619,11 +619,15 @@ __device__ __forceinline__ void gemm_chunk(floatx4 (&acc)[NT][RT][NA], const uin
 // PACK (one row tile, at most 8 rows): the activation fragment carries the high parts in rows 0-7
 // and the low parts of the same 8 rows in rows 8-15, so one fragment and one multiply per k-tile
 // do the work of two; the two halves of the output tile are added before the epilogue.
+// FUSED_IN: the epilogue finishes a norm where a.stats_in is set.  The first FFN projections always carry the code; the
+// QKV projections have instances of their own for it (in the ordinary ones it cost 0.7 us of 7.8 at width 2048).
+constexpr bool norm_in_default(int rt, int epi) { return rt == 1 && (epi == EPI_GELU || epi == EPI_SWIGLU); }
 // ZROWS: the block serves row tiles blockIdx.z * RT .. + RT - 1 only (launches that spread the row tiles of a
 // step over blocks, see launch_gemm_zrows).
 // SW: weights loaded with the non-temporal hint (see ld_w; chosen per context, never with ZROWS, whose row
 // tiles re-read the weights through L2).
-template <int RT, int NT, int NW_K, int U, int EPI, bool SPLIT, bool PACK, bool ZROWS = false, bool SW = false>
+template <int RT, int NT, int NW_K, int U, int EPI, bool SPLIT, bool PACK, bool ZROWS = false, bool SW = false,
+          bool FUSED_IN = norm_in_default(RT, EPI)>
 __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(GemmArgs a) {
   static_assert(!PACK || (RT == 1 && !SPLIT), "packed activations: one row tile, one fragment");
   const int rz = ZROWS ? (int)blockIdx.z * RT : 0;          // first row tile of this block
@@ -647,7 +651,7 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(GemmArgs a) {
 #pragma unroll
   for (int t = 0; t < NT; ++t) tile[t] = min(nt0 + t, a.n_tiles - 1);   // tiles past the end repeat the last one
   // one row tile: what the epilogue needs from memory is asked for now, so that it arrives with the weights
-  constexpr bool FUSED_IN = RT == 1 && (EPI == EPI_GELU || EPI == EPI_SWIGLU || EPI == EPI_QKV || EPI == EPI_QKV_ROPE);
+  static_assert(!FUSED_IN || RT == 1, "norms are finished per row tile");
   constexpr bool FUSED_OUT = RT == 1 && EPI == EPI_RESID_NORM;
   __shared__ float2 sm_stat[FUSED_IN ? NW_K : 1][16];
   float4 pre_s[PS];
@@ -773,14 +777,18 @@ static int launch_gemm_small_nt(GemmArgs a, int ks, hipStream_t s) {
       return PD_OK;
     }
   }
-#define PD_LAUNCH(NWK) \
-  do {                                                                                            \
-    if (a.stream_w)                                                                               \
-      hipLaunchKernelGGL((k_gemm_s<RT, NT, (NWK < NT ? NT : NWK), U, EPI, SPLIT, PACK, false, true>), grid, \
-                         dim3(64 * (NWK < NT ? NT : NWK)), 0, s, a);                              \
-    else                                                                                          \
-      hipLaunchKernelGGL((k_gemm_s<RT, NT, (NWK < NT ? NT : NWK), U, EPI, SPLIT, PACK>), grid,    \
-                         dim3(64 * (NWK < NT ? NT : NWK)), 0, s, a);                              \
+  constexpr bool QKV_NORM = RT == 1 && (EPI == EPI_QKV || EPI == EPI_QKV_ROPE);
+  constexpr bool DEF = norm_in_default(RT, EPI);
+#define PD_LAUNCH_F(NWK, SWX, FI)                                                                                    \
+  hipLaunchKernelGGL((k_gemm_s<RT, NT, (NWK < NT ? NT : NWK), U, EPI, SPLIT, PACK, false, SWX, FI>), grid,           \
+                     dim3(64 * (NWK < NT ? NT : NWK)), 0, s, a)
+#define PD_LAUNCH(NWK)                                                                                               \
+  do {                                                                                                               \
+    if (QKV_NORM && a.stats_in) {                                                                                    \
+      if (a.stream_w) PD_LAUNCH_F(NWK, true, (QKV_NORM || DEF));                                                     \
+      else PD_LAUNCH_F(NWK, false, (QKV_NORM || DEF));                                                               \
+    } else if (a.stream_w) PD_LAUNCH_F(NWK, true, DEF);                                                              \
+    else PD_LAUNCH_F(NWK, false, DEF);                                                                               \
   } while (0)
   switch (nwk) {
     case 1: PD_LAUNCH(1); break;
@@ -790,6 +798,7 @@ static int launch_gemm_small_nt(GemmArgs a, int ks, hipStream_t s) {
     default: PD_LAUNCH(16); break;
   }
 #undef PD_LAUNCH
+#undef PD_LAUNCH_F
   PD_CHECK_HIP(hipGetLastError());
   if (EPI == EPI_RESID && a.parts_out) *a.parts_out = ks;
   return PD_OK;
@@ -1087,7 +1096,11 @@ static int launch_gemm_zrows(GemmArgs a, int rows, hipStream_t s) {
   const int nwk = (per_block > 16 && (per_block > 64 || (long)groups * ks * rts <= 256)) ? 8 : 4;
   a.k_share = (per_block + nwk - 1) / nwk;
   dim3 grid(groups, ks, rts);
-  if (nwk == 4) hipLaunchKernelGGL((k_gemm_s<1, NT, 4, U, EPI, SPLIT, false, true>), grid, dim3(256), 0, s, a);
+  constexpr bool DEF = norm_in_default(1, EPI), QKV_NORM = EPI == EPI_QKV || EPI == EPI_QKV_ROPE;
+  if (QKV_NORM && a.stats_in) {
+    if (nwk == 4) hipLaunchKernelGGL((k_gemm_s<1, NT, 4, U, EPI, SPLIT, false, true, false, (QKV_NORM || DEF)>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_gemm_s<1, NT, 8, U, EPI, SPLIT, false, true, false, (QKV_NORM || DEF)>), grid, dim3(512), 0, s, a);
+  } else if (nwk == 4) hipLaunchKernelGGL((k_gemm_s<1, NT, 4, U, EPI, SPLIT, false, true>), grid, dim3(256), 0, s, a);
   else hipLaunchKernelGGL((k_gemm_s<1, NT, 8, U, EPI, SPLIT, false, true>), grid, dim3(512), 0, s, a);
   PD_CHECK_HIP(hipGetLastError());
   if (EPI == EPI_RESID && a.parts_out) *a.parts_out = ks;
