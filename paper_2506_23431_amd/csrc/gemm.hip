@@ -840,8 +840,8 @@ static int launch_gemm_wide_nt(GemmArgs a, int ks, hipStream_t s) {
 template <int RT, int EPI, bool SPLIT>
 static int launch_gemm_wide(const GemmArgs &a, hipStream_t s) {
   // 4 * NT * RT KiB of LDS, at most 128-160; with 2 row tiles more than 4 column tiles measured slower
-  // (7 only with 5 row tiles: the vocabulary projection of a 72-row step then makes 449 blocks, two rounds
-  // of one block per compute unit, instead of 524 with 6, where 12 blocks run a third round alone)
+  // (7 only with 5 row tiles: the vocabulary projection of a 72-row step without low parts then makes 449 blocks,
+  // two rounds of one block per compute unit, instead of 524 with 6, where 12 blocks run a third round alone)
   constexpr int NT_MAX = RT <= 2 ? 4 : (RT <= 4 ? 8 : (RT == 5 ? 7 : 4));
   static const int nts[] = {1, 2, 3, 4, 6, 7, 8};
   int KT = a.K / 32, best_nt = 1, best_ks = 1;
@@ -871,7 +871,7 @@ static int launch_gemm_wide(const GemmArgs &a, hipStream_t s) {
 
 // ---------------------------------------------------------------------------
 // More than 128 rows against matrices that make the multiplies the bound (the context pass, large teacher-forced
-// passes): grid (column groups, K slices, groups of 16 RT rows).  A block is NW = 8 waves (two per SIMD: a single
+// passes; also the vocabulary projection of 33-128 rows, see launch_gemm_vocab): grid (column groups, K slices, groups of 16 RT rows).  A block is NW = 8 waves (two per SIMD: a single
 // wave issues a 16x16x32 multiply every 29 clocks, two or more every 19) that own NT column tiles each and share the
 // RT row tiles of their row group: per k-tile every wave requests its share of the activation fragments (high and
 // low parts) and its own weight fragments, two k-tiles ahead; the activation fragments pass through LDS (two buffers),
@@ -885,11 +885,11 @@ static int launch_gemm_wide(const GemmArgs &a, hipStream_t s) {
 // reaches on this device: with operands of zeros the same launches are 20-30 % faster, so it is the power limit
 // that holds the rate, and 32x32x16 multiplies (half the operand reads) measured no better (239 against 226 us).
 // ---------------------------------------------------------------------------
-template <int RT, int NT, int EPI, bool SPLIT>
+template <int RT, int NT, int EPI, bool SPLIT, bool SW = false>
 __global__ __launch_bounds__(512, 1) void k_gemm_t(GemmArgs a) {
   constexpr int NW = 8, NA = SPLIT ? 2 * RT : RT;     // activation fragments of a k-tile
-  constexpr int NAW = NA >= NW ? NA / NW : 1;         // staged by one wave (fewer fragments than waves: some twice, same bytes)
-  constexpr int GS = 4, NG = NA / GS;
+  constexpr int NAW = (NA + NW - 1) / NW;             // staged by one wave (not a multiple of the waves: some twice, same bytes)
+  constexpr int GS = RT == 5 ? 5 : 4, NG = NA / GS;
   static_assert(NA % GS == 0 && (NG == 1 || NG % 2 == 0), "fragment groups alternate between two register sets");
   __shared__ bf16x8 sm_x[2][NA][64];   // (vector types throughout: struct copies would keep xr in scratch memory)
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -926,7 +926,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm_t(GemmArgs a) {
   auto load_w = [&](int s, int j) {
     const size_t k = (size_t)(kt0 + min(j, len - 1)) * 64;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) wr[s][t] = wsrc[t][k];
+    for (int t = 0; t < NT; ++t) wr[s][t] = ld_w<SW>((const uint4 *)(wsrc[t] + k));
   };
   auto put_x = [&](int s) {
 #pragma unroll
@@ -1107,6 +1107,28 @@ static int launch_gemm_zrows(GemmArgs a, int rows, hipStream_t s) {
   return PD_OK;
 }
 
+// Vocabulary projection of 33-128 rows: the same kernel with all rows in one group and one or two column tiles per
+// wave.  Cut along K over 4 waves (launch_gemm_wide) every wave requests a few k-tiles, waits for all of them, multiplies,
+// and the blocks end with a sum through LDS; one stream of k-tiles per block hides both.  One layer + vocabulary, us per
+// step, before -> after: 72 rows, width 1024, 50265 words 83.3 -> 73.3 (the projection itself 40.7 -> 31), 128 rows
+// 113 -> 83, 120000 words 190 -> 138; 64 rows, width 512, 32000 words 55.6 -> 52.2; width 4096, 100000 words 315 -> 276.
+// Blocks of 128 columns want a compute unit each to be ahead: 16000 words lose (64 rows, width 2048 74.6 -> 80.2), and the
+// longer K, the more a single round of K-cut blocks hides by itself (24000 words: width 1024 59.3 -> 57.2, 2048
+// 80.9 -> 84.7; 32000 words: 2048 87.6 -> 83.7, 3072 134 -> 145; 50265 words: 3072 170 -> 163).  8 row tiles leave the
+// other kernel 4 column tiles, a second round from 1025 tiles on (24000 words, width 2048, 113 -> 105).  Two column tiles per wave
+// where one makes more than a round of blocks and a block's multiplies cover its requests (64 rows, width 1024, 50265 words
+// 67.2 with one, 72.7 with two; 72 rows of width 768 66.6 and 65.3; 128 rows of width 2048 148 and 139); three, or four k-tiles
+// ahead instead of two, measured no better.  Steps of 17-32 rows differ by less than 5 % either way and stay.
+template <int RT, int NT>
+static int launch_gemm_vocab(const GemmArgs &a, int rows, hipStream_t s) {
+  PD_REQUIRE(rows <= 16 * RT, PD_EINVAL, "%d rows in %d row tiles", rows, RT);
+  const dim3 grid((a.n_tiles + 8 * NT - 1) / (8 * NT));
+  if (a.stream_w) hipLaunchKernelGGL((k_gemm_t<RT, NT, EPI_LM, true, true>), grid, dim3(512), 0, s, a);
+  else hipLaunchKernelGGL((k_gemm_t<RT, NT, EPI_LM, true, false>), grid, dim3(512), 0, s, a);
+  PD_CHECK_HIP(hipGetLastError());
+  return PD_OK;
+}
+
 template <int EPI, bool SPLIT>
 static int launch_gemm_split(const GemmArgs &a, int rows, hipStream_t s) {
   constexpr bool zrows = EPI != EPI_LM;
@@ -1114,6 +1136,15 @@ static int launch_gemm_split(const GemmArgs &a, int rows, hipStream_t s) {
     return launch_gemm_zrows<EPI, SPLIT, (EPI == EPI_RESID_NORM ? 1 : 4)>(a, rows, s);
   if (EPI == EPI_RESID_NORM || a.stats_in)
     PD_REQUIRE(rows <= 16, PD_EINVAL, "a projection of this shape cannot prepare or finish a norm for %d rows", rows);
+  if constexpr (EPI == EPI_LM && SPLIT) {
+    const int rt = mfma_gemm_row_tiles(rows) / 16, KT = a.K / 32;
+    if (rows > 32 && (a.n_tiles >= 1500 + 12 * std::max(0, KT - 32) || (rt == 8 && a.n_tiles > 1024))) {
+      const bool two = a.n_tiles > 2048 && (rt * KT >= 160 || a.n_tiles > 4096);
+      if (rt == 4) return two ? launch_gemm_vocab<4, 2>(a, rows, s) : launch_gemm_vocab<4, 1>(a, rows, s);
+      if (rt == 5) return two ? launch_gemm_vocab<5, 2>(a, rows, s) : launch_gemm_vocab<5, 1>(a, rows, s);
+      return two ? launch_gemm_vocab<8, 2>(a, rows, s) : launch_gemm_vocab<8, 1>(a, rows, s);
+    }
+  }
   switch (mfma_gemm_row_tiles(rows)) {
     case 16: return launch_gemm_small<1, EPI, SPLIT, false>(a, s);
     case 32: return launch_gemm_wide<2, EPI, SPLIT>(a, s);
