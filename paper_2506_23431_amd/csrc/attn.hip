@@ -376,7 +376,8 @@ static int pick_splits(pd_ctx *c, int units, int nblk, bool decode, bool pair, i
   // 4096-6000 keys: 52.9 against 51.7 ms); with more units than compute units 4 waves do as well or better (288
   // units x 384 keys 4.46 against 4.51 ms).
   if (nblk <= 32) {
-    if (decode && !pair && units <= 256) *nw = 8;
+    // (up to 4 blocks 4 waves hold one each: the other four would only add to the merge)
+    if (decode && !pair && units <= 256 && nblk > 4) *nw = 8;
     return 1;
   }
   if (decode && !pair && units <= 256 && nblk <= 96 && nblk * 0.55 / 8 < nblk * 0.55 / (4 * splits) + 4) {
