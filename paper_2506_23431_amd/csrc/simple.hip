@@ -428,7 +428,9 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(AttnF32Args a) {
   __shared__ floatx4 sm_o[NW][NHB][64];
   __shared__ float sm_m[NW][16], sm_l[NW][16];
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
-  const int h = blockIdx.x, reqi = blockIdx.y / a.nqg, qg = blockIdx.y % a.nqg, req = a.req0 + reqi, hd = a.hd;
+  // (one grid dimension: the others end at 65535, and a batch may have more requests)
+  const int h = blockIdx.x % a.H, unit = blockIdx.x / a.H, reqi = unit / a.nqg, qg = unit % a.nqg, req = a.req0 + reqi;
+  const int hd = a.hd;
   const int qa = qg * 16 + m;
   const int r = reqi * a.A + min(qa, a.A - 1);          // clamped: loads stay in bounds
   const int4 qi = a.rt.qinfo[r];                        // {flags, sub, lim, req}
@@ -537,7 +539,7 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(AttnF32Args a) {
 
 template <typename KT>
 static int attention_f32(const AttnF32Args &a, int nreq, hipStream_t s) {
-  const dim3 grid(a.H, nreq * a.nqg);
+  const dim3 grid(a.H * nreq * a.nqg);
   const bool vec = a.hd % 4 == 0;       // rows of q, keys and values then start at multiples of 16 (half: 8) bytes
 #define PD_ATTN_F32(NHB, NW)                                                                                  \
   do {                                                                                                        \

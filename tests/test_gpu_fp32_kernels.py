@@ -4,6 +4,7 @@ and sizes in between), key counts beside the 16-key tiles, norms inside the proj
 values) and outside, rows embedded by the first projection or by a kernel.  Against the CPU oracle: 1e-4 in fp32, 2e-2
 with bf16 weights and the half cache (tests/parity_util.py)."""
 
+import numpy as np
 import pytest
 
 import pd_inputs as pi
@@ -50,3 +51,18 @@ def test_fp32_kernels(cfg):
         stats = compare_teacher_forced(cfg, w, ctx, dec, outs, log=lambda m: print(m, flush=True))
         assert stats["rows"] == cfg.batch * (cfg.n_sub * (cfg.sub_tokens + 1) - 1)
         dec.close()
+
+
+def test_more_requests_than_a_grid_dimension_holds():
+    """65600 requests in one batch (the second and third grid dimension end at 65535), their contexts 16 different
+    tokens over and over: every request's logits are those of its token in a batch of 16."""
+    cfg = W("many-requests", 2, 2, 8, 1, n_layer=1, n_sub=1, sub_tokens=1, batch=16, qkv_std=0.5)
+    w = pi.make_weights(cfg, threads=4)
+    logits = {}
+    for batch in (16, 65600):
+        dec = make_decoder(cfg, w, max_batch=batch)
+        dec.prefill_context(np.arange(batch, dtype=np.int32)[:, None] % 16, 1, 1, 1, 1)
+        logits[batch] = dec.decode_step(want_logits=True)[1].cpu().numpy()
+        dec.close()
+    want = np.tile(logits[16], (65600 // 16, 1, 1))
+    assert np.abs(logits[65600] - want).max() < 1e-4

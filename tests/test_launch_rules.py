@@ -1,0 +1,200 @@
+"""The rules by which launches are shaped (csrc/launch_rules.h), compiled by the host compiler alone: against times measured
+for every shape a rule chooses from, and against exhaustive search where the rule is an optimum of its own estimate."""
+
+import ctypes as C
+import itertools
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2506_23431_amd", "csrc")
+
+SOURCE = r"""
+#include "launch_rules.h"
+extern "C" {
+void attn(int hd, int units, int nblk, int cap, int decode, int pair, int streamed, int *out) {
+  const AttnShape s = attn_shape(hd, units, nblk, cap, decode, pair, streamed);
+  out[0] = s.splits; out[1] = s.waves;
+}
+int groups(const int *rows, int n, double pass_us, double row_us, int row_cap, int most, int *out) {
+  const std::vector<int> g = teacher_groups(std::vector<int>(rows, rows + n), PassCost{pass_us, row_us},
+                                            [&](int a, int k) { return a * k <= row_cap && k <= most; });
+  for (size_t i = 0; i < g.size(); ++i) out[i] = g[i];
+  return (int)g.size();
+}
+void pass_cost(int n_layer, double weights, int parts, double *out) {
+  const PassCost c = teacher_pass_cost(n_layer, weights, parts);
+  out[0] = c.pass_us; out[1] = c.row_us;
+}
+void tiling(int n_tiles, int kt, int rows, int max_slices, int split, int kind, int *out) {
+  const RowTiling t = row_tiling(n_tiles, kt, rows, max_slices, split, (RowOutput)kind);
+  out[0] = t.cut; out[1] = t.rt; out[2] = t.nt; out[3] = t.ks;
+}
+int vocab(int n_tiles, int kt, int rows) { return vocab_shares_row_tiles(n_tiles, kt, rows); }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    (d / "rules.cpp").write_text(SOURCE)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC,
+                           str(d / "rules.cpp"), "-o", str(d / "rules.so")])
+    return C.CDLL(str(d / "rules.so"))
+
+
+# head size, units, key blocks, keys from memory (else from the caches); us per layer and step with one work-group of 4
+# waves per unit, of 8 waves, with splits and merge (3 layers, 4 rows per request)
+ATTENTION = [
+    (32, 8, 16, False, 22.8, 22.4, 24.9), (32, 8, 64, False, 27.4, 25.1, 24.9), (32, 64, 40, True, 32.5, 30.0, 31.2),
+    (64, 4, 5, False, 21.6, 22.0, 21.7), (64, 8, 32, False, 25.4, 24.2, 25.2), (64, 8, 72, False, 29.8, 26.9, 25.5),
+    (64, 16, 28, True, 33.6, 32.2, 32.1), (64, 16, 40, True, 35.9, 33.7, 32.1), (64, 64, 32, True, 35.1, 33.6, 34.2),
+    (64, 64, 72, True, 43.4, 39.7, 37.6), (64, 128, 96, True, 54.9, 50.5, 51.2), (64, 256, 48, True, 49.8, 49.9, 49.8),
+    (96, 8, 16, True, 30.8, 29.8, 31.1), (96, 16, 32, True, 34.6, 33.7, 31.7), (96, 64, 56, True, 45.9, 45.1, 42.1),
+    (128, 4, 12, True, 27.6, 27.2, 28.6), (128, 8, 32, True, 37.0, 36.6, 32.6), (128, 16, 64, True, 56.7, 56.5, 44.0),
+    (128, 32, 24, True, 37.5, 37.0, 35.4), (128, 64, 40, True, 45.9, 45.8, 43.2), (128, 128, 32, True, 55.8, 55.7, 57.2),
+    (128, 128, 96, True, 77.2, 77.9, 76.4), (128, 256, 20, True, 66.9, 66.3, 66.5),
+]
+
+
+@pytest.mark.parametrize("hd,units,nblk,streamed,four,eight,split", ATTENTION)
+def test_attention_shape_is_near_the_fastest_measured(rules, hd, units, nblk, streamed, four, eight, split):
+    out = (C.c_int * 2)()
+    rules.attn(hd, units, nblk, 4096 // units, 1, 0, int(streamed), out)
+    splits, waves = out
+    assert splits in (1, max(1, min(256 // units, nblk // 4))) and waves in (4, 8)
+    us = split if splits > 1 else eight if waves == 8 else four
+    assert us <= 1.03 * min(four, eight, split)
+
+
+def test_attention_shape_at_its_limits(rules):
+    out = (C.c_int * 2)()
+    for hd, units, nblk, cap, streamed in itertools.product((32, 64, 96, 128), (1, 7, 64, 256, 257, 5000), (1, 4, 7, 8, 32, 33, 96, 97, 400),
+                                                            (1, 3, 1000), (0, 1)):
+        for decode, pair in ((1, 0), (0, 0), (1, 1)):
+            rules.attn(hd, units, nblk, cap, decode, pair, streamed, out)
+            assert 1 <= out[0] <= min(cap, max(1, nblk // 4))            # partials fit, every wave has a block
+            if pair or not decode or nblk < 8 or nblk > 96 or units > 256:
+                assert out[1] == 4
+            if (pair or not decode) and nblk <= 32:
+                assert out[0] == 1
+
+
+def _groups(rules, rows, pass_us, row_us, row_cap=4096, most=1000):
+    out = (C.c_int * len(rows))()
+    n = rules.groups((C.c_int * len(rows))(*rows), len(rows), C.c_double(pass_us), C.c_double(row_us), row_cap, most, out)
+    return list(out[:n])
+
+
+def _cost(rows, groups, pass_us, row_us):
+    total, at = 0.0, 0
+    for k in groups:
+        total += pass_us + row_us * k * max(rows[at:at + k])
+        at += k
+    assert at == len(rows)
+    return total
+
+
+def test_targets_share_a_pass_only_where_padding_costs_less(rules):
+    wide = (158.0, 1.1)              # 2 layers of width 2048, 32000 words
+    assert _groups(rules, [500] + [20] * 7, *wide) == [1, 7]
+    assert _groups(rules, [20] * 7 + [500], *wide) == [7, 1]
+    assert _groups(rules, [200, 190, 180], *wide) == [3]
+    narrow = (232.0, 0.02)
+    assert _groups(rules, [500] + [20] * 7, *narrow) == [8]
+    cost = (C.c_double * 2)()
+    rules.pass_cost(2, C.c_double(166e6), 2, cost)
+    assert abs(cost[0] - wide[0]) < 12 and abs(cost[1] - wide[1]) < 0.02
+
+
+def test_target_groups_are_the_cheapest_partition(rules):
+    rng = np.random.default_rng(5)
+    for _ in range(60):
+        n = int(rng.integers(1, 9))
+        rows = [int(r) for r in np.exp(rng.uniform(0, np.log(900), n))]
+        pass_us, row_us, row_cap, most = float(rng.uniform(20, 400)), float(rng.uniform(0.05, 3)), 2048, int(rng.integers(2, 9))
+        got = _groups(rules, rows, pass_us, row_us, row_cap, most)
+        best = 1e30
+        for cuts in itertools.product((0, 1), repeat=n - 1):
+            sizes, run = [], 1
+            for c in cuts:
+                if c:
+                    sizes.append(run)
+                    run = 1
+                else:
+                    run += 1
+            sizes.append(run)
+            at, fits = 0, True
+            for k in sizes:
+                fits = fits and (k == 1 or (k <= most and k * max(rows[at:at + k]) <= row_cap))
+                at += k
+            if fits:
+                best = min(best, _cost(rows, sizes, pass_us, row_us))
+        at = 0
+        for k in got:
+            assert k == 1 or (k <= most and k * max(rows[at:at + k]) <= row_cap)
+            at += k
+        assert abs(_cost(rows, got, pass_us, row_us) - best) < 1e-6 * best
+
+
+SLICES, STORED, VOCAB = 0, 1, 2
+# column tiles, k-tiles, rows, low parts, output; the candidates within 10 % of the fastest: (waves cut K, row tiles, column
+# tiles, K slices): us
+TILINGS = [
+    (48, 96, 2048, True, SLICES, {(False, 4, 3, 4): 21.3}),
+    (48, 96, 720, True, SLICES, {(False, 4, 2, 4): 14.1}),
+    (256, 344, 720, True, SLICES, {(False, 8, 2, 2): 121.4, (False, 4, 2, 4): 121.9, (False, 8, 4, 4): 123.2,
+                                   (False, 4, 2, 2): 128.7, (False, 4, 4, 2): 130.1, (False, 8, 2, 4): 132.2,
+                                   (False, 4, 4, 4): 133.0}),
+    (256, 344, 1280, True, SLICES, {(False, 8, 3, 2): 177.6}),
+    (192, 24, 192, True, STORED, {(True, 2, 2, 1): 7.7, (True, 2, 4, 1): 7.8, (True, 2, 6, 1): 8.1}),
+    (192, 24, 720, True, STORED, {(True, 2, 6, 1): 15.7, (True, 2, 2, 1): 16.0, (True, 2, 4, 1): 16.2,
+                                  (False, 4, 1, 1): 16.6, (False, 4, 2, 1): 17.1}),
+    (144, 24, 2048, True, STORED, {(False, 4, 3, 1): 23.6}),
+    (1024, 128, 400, True, STORED, {(False, 4, 2, 1): 108.2, (False, 8, 2, 1): 109.8, (False, 4, 4, 1): 112.0}),
+    (512, 64, 4096, True, STORED, {(False, 8, 4, 1): 224.2, (False, 4, 2, 1): 227.0, (False, 4, 4, 1): 236.7,
+                                   (False, 8, 2, 1): 236.9}),
+    (512, 64, 720, False, STORED, {(False, 4, 2, 1): 43.6, (False, 4, 1, 1): 44.4, (False, 8, 2, 1): 46.3}),
+    (3144, 24, 192, True, VOCAB, {(False, 4, 1, 1): 45.2, (False, 4, 2, 1): 47.5, (False, 4, 3, 1): 49.4, (False, 8, 4, 1): 49.4}),
+    (3144, 128, 256, True, VOCAB, {(False, 8, 4, 1): 186.8}),
+    (3144, 24, 400, True, VOCAB, {(False, 4, 1, 1): 108.3, (False, 4, 2, 1): 109.5, (False, 8, 4, 1): 110.7, (False, 8, 2, 1): 116.3}),
+]
+
+
+@pytest.mark.parametrize("n_tiles,kt,rows,split,kind,near", TILINGS)
+def test_row_tiling_is_near_the_fastest_measured(rules, n_tiles, kt, rows, split, kind, near):
+    out = (C.c_int * 4)()
+    rules.tiling(n_tiles, kt, rows, 4, int(split), kind, out)
+    assert (bool(out[0]), *out[1:]) in near
+
+
+def test_row_tiling_at_its_limits(rules):
+    out = (C.c_int * 4)()
+    known = {(1, 2, 2), (1, 2, 4), (1, 2, 6), (0, 4, 1), (0, 4, 2), (0, 4, 3), (0, 4, 4), (0, 8, 2), (0, 8, 3), (0, 8, 4)}
+    for n_tiles, kt, rows, slices, split, kind in itertools.product((1, 6, 161, 8000), (1, 7, 8, 15, 16, 512), (129, 4096, 100000), (1, 2, 4),
+                                                                    (0, 1), (0, 1, 2)):
+        rules.tiling(n_tiles, kt, rows, slices, split, kind, out)
+        assert tuple(out[:3]) in known
+        assert out[3] in ((1, 2, 4) if kind == SLICES else (1,)) and out[3] <= slices and (out[3] == 1 or kt // out[3] >= 8)
+
+
+# column tiles, K, rows; us with waves that cut K and with waves that share row tiles, weights from memory
+VOCABULARY = [
+    (1500, 768, 33, 15.1, 15.5), (1500, 768, 65, 17.0, 17.9), (1624, 768, 80, 18.1, 18.1), (2500, 768, 33, 27.2, 20.1),
+    (1624, 1024, 65, 21.4, 20.7), (2000, 1536, 64, 27.0, 28.1), (1748, 1536, 33, 24.8, 26.7), (2500, 1536, 64, 42.8, 34.6),
+    (2500, 2048, 80, 53.0, 46.8), (1000, 2048, 64, 20.0, 31.0), (2000, 3072, 80, 55.3, 55.9), (3144, 768, 65, 34.5, 27.7),
+    (1028, 768, 96, 25.8, 19.2), (1028, 5120, 128, 98.1, 90.4), (1000, 2048, 96, 28.3, 38.3), (1000, 768, 128, 16.2, 19.3),
+    (3144, 1024, 128, 65.8, 36.6), (3144, 4096, 33, 96.0, 84.6), (3144, 4096, 80, 102.1, 92.2), (8000, 4096, 48, 212.5, 166.9),
+]
+
+
+@pytest.mark.parametrize("n_tiles,k,rows,cut,share", VOCABULARY)
+def test_vocabulary_kernel_is_near_the_faster_measured(rules, n_tiles, k, rows, cut, share):
+    assert (share if rules.vocab(n_tiles, k // 32, rows) else cut) <= 1.03 * min(cut, share)
+
+
+def test_few_rows_keep_waves_that_cut_k(rules):
+    assert not any(rules.vocab(n, kt, rows) for n, kt, rows in itertools.product((1, 1024, 8000, 20000), (1, 24, 128), (1, 16, 32)))
