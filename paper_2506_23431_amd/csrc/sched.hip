@@ -347,9 +347,10 @@ __global__ __launch_bounds__(1024) void k_commit(SchedState st, const float *par
     r0 = st.row_of[b * S + i0]; fin0 = st.fin[b * S + i0]; f0 = st.force[b * S + i0];
     nt0 = st.n_tok[b * S + i0];
   }
-  // stage 1: second stage of the argmax, `share` waves per row (all 16 work also when there are few rows); lowest
-  // index wins ties (Eq. 4)
-  const int share = max(1, nwave / A), part = wave % share, span = (n_tiles + share - 1) / share;
+  // stage 1: second stage of the argmax, `share` waves per row; lowest index wins ties (Eq. 4).  One wave takes the
+  // 512 tiles of a vocabulary of 8192 in one batch of requests; beyond that all 16 waves work also when there are few
+  // rows (8 rows, 50265 words 8.0 -> 6.9 us; 1000 words: 3.5 us with a wave per row, 4.2 shared)
+  const int share = n_tiles > 512 ? max(1, nwave / A) : 1, part = wave % share, span = (n_tiles + share - 1) / share;
   const int t_lo = part * span, t_hi = min(t_lo + span, n_tiles);
   for (int a = wave / share; a < A; a += max(1, nwave / share)) {
     if (wave >= share * (nwave / share)) break;        // (waves left over when A does not divide their number)

@@ -29,6 +29,9 @@ CASES = [
     W("1-row", 256, n_sub=1), W("3-rows", 256, n_sub=3), W("8-rows", 256, n_sub=8, sub_tokens=9),
     W("9-rows", 256, n_sub=9, sub_tokens=9), W("16-rows", 256, n_sub=16, sub_tokens=17),
     W("17-rows", 256, n_sub=17, sub_tokens=18),
+    W("1-row-513-tiles", 256, n_sub=1, vocab=8195), W("3-rows-513-tiles", 256, n_sub=3, vocab=8195),
+    W("5-rows-513-tiles", 256, vocab=8195), W("8-rows-600-tiles", 256, n_sub=8, sub_tokens=9, vocab=9590),
+    W("9-rows-513-tiles", 256, n_sub=9, sub_tokens=9, vocab=8195),
 ]
 
 
