@@ -76,9 +76,44 @@ struct Carver {
   }
 };
 
+// row buffers are read in tiles of 16 rows, 1/2/4/8 tiles per launch
+static void size_rows(RowSet *r, int R_cap, int part_units) {
+  r->R_cap = R_cap; r->part_units = part_units;
+  int tiles = (R_cap + 15) / 16, t2 = 1;
+  while (t2 < tiles && t2 < 8) t2 *= 2;
+  r->R_pad = std::max(tiles, t2) * 16;
+  if (r->R_pad > 128) r->R_pad = (r->R_pad + 127) / 128 * 128;     // whole row groups of 128
+}
+
+// activations, attention partials, K slices and the winners of the vocabulary tiles
+static void carve_activations(Carver &cv, const pd_config *g, int impl, int lm_parts, RowSet *r) {
+  const size_t Rp = r->R_pad, d = g->d_model;
+  r->x = cv.take<float>(Rp * d);
+  r->xn = cv.take<float>(Rp * d);
+  r->q = cv.take<float>(Rp * d);
+  r->att = cv.take<float>(Rp * d);
+  r->hb = cv.take<float>(Rp * g->d_ff);
+  r->qkv32 = impl == 0 ? cv.take<float>(Rp * 3 * d) : nullptr;
+  r->att_part = cv.take<float>((size_t)r->part_units * 16 * (g->head_dim + 2));
+  r->ypart = cv.take<float>((size_t)4 * Rp * d);
+  r->lm_part_val = cv.take<float>((size_t)lm_parts * Rp);
+  r->lm_part_idx = cv.take<int32_t>((size_t)lm_parts * Rp);
+  r->row_argmax = cv.take<int32_t>(Rp);
+  r->nll = cv.take<float>(Rp);
+}
+
+static void carve_row_tables(Carver &cv, bool encdec, RowSet *r) {
+  const size_t Rp = r->R_pad;
+  RowTables &rt = r->rows;
+  rt.req = cv.take<int32_t>(Rp); rt.sub = cv.take<int32_t>(Rp); rt.tok = cv.take<int32_t>(Rp);
+  rt.pos = cv.take<int32_t>(Rp); rt.slot = cv.take<int32_t>(Rp); rt.lim = cv.take<int32_t>(Rp);
+  rt.flags = cv.take<int32_t>(Rp); rt.qinfo = cv.take<int4>(Rp); rt.kvinfo = cv.take<int4>(Rp);
+  r->qinfo_x = encdec ? cv.take<int4>(Rp) : nullptr;
+}
+
 // Lays the workspace out; with base == NULL only the size is computed.
 // `e` != NULL: encoder-decoder form (g is the decoder stack's configuration derived from it).
-// `shared_chunk`: room for a context pass whose launches hold several requests' contexts (see below).
+// `shared_chunk`: a set of row buffers for launches that hold several requests' contexts, behind everything else.
 static size_t carve_with(const pd_config *g, char *base, pd_ctx *c, const pd_encdec_config *e, bool shared_chunk) {
   pd_ctx tmp_ctx;
   pd_ctx *x = c ? c : &tmp_ctx;
@@ -97,23 +132,22 @@ static size_t carve_with(const pd_config *g, char *base, pd_ctx *c, const pd_enc
   // at most the 4096 (request, head, 16 rows) units of one attention launch allow.  Short contexts share the rows of a
   // launch (cfg2's model, two contexts of 1024 tokens: 0.88 -> 0.60 ms; fp32, width 512, two of 257: six launches per
   // projection become one).
+  const int a_max = std::min(S, M + 1);
   {
     const int most = x->impl == 1 ? 4096 : 1024;
     const int cap = std::min(most, 16 * (4096 / std::max(H, 1)) / 16 * 16);
-    const int64_t want = (int64_t)g->max_ctx * (shared_chunk && !e ? B : 1);
-    x->prefill_chunk_cap = std::max(128, (int)std::min<int64_t>(cap, (want + 127) / 128 * 128));
-    if (x->impl == 0 && !shared_chunk) x->prefill_chunk_cap = 128;
-    x->prefill_chunk = x->prefill_chunk_cap;
+    auto rows_for = [&](int64_t n) { return std::max(128, (int)std::min<int64_t>(cap, (n + 127) / 128 * 128)); };
+    const int one = x->impl == 1 ? rows_for(g->max_ctx) : 128, shared = rows_for((int64_t)g->max_ctx * B);
+    // split partials of the attention kernel: one (max, sum, O) record of 16 queries per (request, head,
+    // query group) unit and split; the launch caps its splits so that units * splits <= part_units
+    const int units_dec = B * ((a_max + 15) / 16) * H;
+    size_rows(x, std::max(B * a_max, one), std::max({units_dec, one / 16 * H, 1024}));
+    const bool wide = shared_chunk && !e && shared > x->R_cap;
+    size_rows(&x->wide, wide ? shared : 0, std::max(shared / 16 * H, 1024));
+    x->prefill_chunk_cap = x->prefill_chunk = wide || (!e && shared <= x->R_cap) ? shared : one;
     // rows of one request's training targets: what a context pass of a single request has room for
-    x->tf_rows = std::max(B * std::min(S, M + 1), std::max(128, std::min(cap, (g->max_ctx + 127) / 128 * 128)));
+    x->tf_rows = std::max(B * a_max, rows_for(g->max_ctx));
   }
-  int a_max = std::min(S, M + 1);
-  x->R_cap = std::max(B * a_max, x->prefill_chunk_cap);
-  // row buffers are read in tiles of 16 rows, 1/2/4/8 tiles per launch
-  int tiles = (x->R_cap + 15) / 16, t2 = 1;
-  while (t2 < tiles && t2 < 8) t2 *= 2;
-  x->R_pad = std::max(tiles, t2) * 16;
-  if (x->R_pad > 128) x->R_pad = (x->R_pad + 127) / 128 * 128;     // whole row groups of 128
   x->vocab_pad = (V + 63) / 64 * 64;
   size_t es = g->dtype == 0 ? 4 : 2;
   x->kv_layer_bytes = (size_t)B * H * x->kv_cap * hd * es;
@@ -129,7 +163,7 @@ static size_t carve_with(const pd_config *g, char *base, pd_ctx *c, const pd_enc
     x->layers[l].xvc = e ? cv.take<char>(x->kv_layer_bytes) : nullptr;
   }
   x->arch = e ? 1 : 0;
-  x->gen_coord = nullptr; x->qinfo_x = nullptr;
+  x->gen_coord = nullptr;
   if (e) {
     EncDecState &ed = x->ed;
     ed.n_enc_layer = e->n_enc_layer; ed.rel_buckets = e->rel_buckets; ed.rel_max_distance = e->rel_max_distance;
@@ -146,33 +180,11 @@ static size_t carve_with(const pd_config *g, char *base, pd_ctx *c, const pd_enc
   x->bias0 = cv.take<float>(H);
   x->loss = cv.take<double>(B);
   x->tf_target = cv.take<int32_t>((size_t)B * S * (M + 2));
-  size_t Rp = x->R_pad;
-  x->x = cv.take<float>(Rp * d);
-  x->xn = cv.take<float>(Rp * d);
-  x->q = cv.take<float>(Rp * d);
-  x->att = cv.take<float>(Rp * d);
-  x->hb = cv.take<float>(Rp * ff);
-  x->qkv32 = x->impl == 0 ? cv.take<float>(Rp * 3 * d) : nullptr;
-  // split partials of the attention kernel: one (max, sum, O) record of 16 queries per (request, head,
-  // query group) unit and split; the launch caps its splits so that units * splits <= part_units
-  {
-    int units_dec = B * ((a_max + 15) / 16) * H, units_pre = (x->prefill_chunk_cap / 16) * H;
-    x->part_units = std::max(std::max(units_dec, units_pre), 1024);
-  }
-  x->att_part = cv.take<float>((size_t)x->part_units * 16 * (hd + 2));
-  x->ypart = cv.take<float>((size_t)4 * Rp * d);
-  x->lm_parts = (x->vocab_pad / 16);
-  x->lm_part_val = cv.take<float>((size_t)x->lm_parts * Rp);
-  x->lm_part_idx = cv.take<int32_t>((size_t)x->lm_parts * Rp);
-  x->row_argmax = cv.take<int32_t>(Rp);
-  x->nll = cv.take<float>(Rp);
+  x->lm_parts = x->vocab_pad / 16;
+  carve_activations(cv, g, x->impl, x->lm_parts, x);
   x->rope_rows = g->pos_kind == 1 ? g->max_pos : 0;
   x->rope_cs = g->pos_kind == 1 ? cv.take<float>((size_t)x->rope_rows * hd) : nullptr;
-  RowTables &rt = x->rows;
-  rt.req = cv.take<int32_t>(Rp); rt.sub = cv.take<int32_t>(Rp); rt.tok = cv.take<int32_t>(Rp);
-  rt.pos = cv.take<int32_t>(Rp); rt.slot = cv.take<int32_t>(Rp); rt.lim = cv.take<int32_t>(Rp);
-  rt.flags = cv.take<int32_t>(Rp); rt.qinfo = cv.take<int4>(Rp); rt.kvinfo = cv.take<int4>(Rp);
-  if (e) x->qinfo_x = cv.take<int4>(Rp);
+  carve_row_tables(cv, e != nullptr, x);
   SchedState &st = x->sch;
   st.step = cv.take<int32_t>(B); st.k_open = cv.take<int32_t>(B);
   st.n_tok = cv.take<int32_t>((size_t)B * S); st.n_fed = cv.take<int32_t>((size_t)B * S);
@@ -199,7 +211,7 @@ static size_t carve_with(const pd_config *g, char *base, pd_ctx *c, const pd_enc
       lp.cx1 = e ? cv.take<float>(dd) : nullptr;
       lp.q1 = cv.take<float>(3 * dd); lp.q2 = cv.take<float>(3 * dd);
     }
-    x->nstats = cv.take<float2>(std::min<size_t>(Rp, 128) * (d / 16));   // steps of up to 128 rows hand norms over
+    x->nstats = cv.take<float2>(std::min(x->R_pad, 128) * (d / 16));   // steps of up to 128 rows hand norms over
     x->p_lm_head = cv.take<bf16_t>((size_t)x->vocab_pad * d);
     if (e) {
       for (LayerPtrs &lp : x->ed.enc) {
@@ -211,6 +223,10 @@ static size_t carve_with(const pd_config *g, char *base, pd_ctx *c, const pd_enc
         lp.p_cq = cv.take<bf16_t>(dd * d); lp.p_ckv = cv.take<bf16_t>(2 * dd * d); lp.p_co = cv.take<bf16_t>(dd * d);
       }
     }
+  }
+  if (x->wide.R_cap) {
+    carve_activations(cv, g, x->impl, x->lm_parts, &x->wide);
+    carve_row_tables(cv, false, &x->wide);
   }
   return (cv.off + 255) & ~(size_t)255;
 }
@@ -556,9 +572,25 @@ static int run_layers(pd_ctx *c, int R, int A, int nreq, int req0, int kv_overri
 }
 
 // whether nreq requests of A rows each can be one launch sequence: the row buffers and the attention's units of 16 rows
-static bool fits_one_pass(const pd_ctx *c, int A, int nreq) {
-  return (int64_t)nreq * A <= c->R_cap && (int64_t)nreq * ((A + 15) / 16) * c->cfg.n_head <= c->part_units;
+static bool holds(const RowSet &r, int n_head, int A, int nreq) {
+  return (int64_t)nreq * A <= r.R_cap && (int64_t)nreq * ((A + 15) / 16) * n_head <= r.part_units;
 }
+static bool fits_one_pass(const pd_ctx *c, int A, int nreq) {
+  return holds(*c, c->cfg.n_head, A, nreq) || holds(c->wide, c->cfg.n_head, A, nreq);
+}
+
+// For its lifetime the context works on the set of row buffers that a pass of nreq requests of A rows needs.
+struct PassRows {
+  pd_ctx *c;
+  bool wide;
+  PassRows(pd_ctx *ctx, int A, int nreq)
+      : c(ctx), wide(!holds(*ctx, ctx->cfg.n_head, A, nreq) && holds(ctx->wide, ctx->cfg.n_head, A, nreq)) {
+    if (wide) std::swap(static_cast<RowSet &>(*c), c->wide);
+  }
+  ~PassRows() {
+    if (wide) std::swap(static_cast<RowSet &>(*c), c->wide);
+  }
+};
 
 extern "C" int pd_prefill_context(pd_ctx *c, const int32_t *ctx_tokens, int B, int L, int n_sub,
                                   int delta_t, int max_sub_tokens, int time_max, void *hip_stream) {
@@ -603,6 +635,7 @@ extern "C" int pd_prefill_context(pd_ctx *c, const int32_t *ctx_tokens, int B, i
     while (b + nreq < B && (int64_t)(nreq + 1) * L <= chunk && fits_one_pass(c, L, nreq + 1)) ++nreq;
     for (int p0 = 0; p0 < L && !rc; p0 += chunk) {
       int n = std::min(chunk, L - p0);
+      const PassRows rows(c, n, nreq);
       if ((rc = launch_prefill_rows(c, b, p0, n, s, c->L, 0, b, nreq))) break;
       rc = run_layers(c, nreq * n, n, nreq, b, p0 + n, s);
     }
@@ -774,6 +807,7 @@ extern "C" int pd_teacher_forced(pd_ctx *c, const int32_t *target, int max_len, 
     int A = rows[b], nreq = 1;
     while (b + nreq < B && A < 65535 && fits_one_pass(c, std::max(A, rows[b + nreq]), nreq + 1)) A = std::max(A, rows[b + nreq++]);
     const int R = nreq * A;
+    const PassRows buffers(c, A, nreq);
     if ((rc = launch_teacher_rows(c, c->tf_target, b, nreq, A, max_len, s))) return rc;
     c->packed = false; c->embed_pending = true; c->pend_parts = 0; c->norm_fused = false;
     for (int l = 0; l < g.n_layer; ++l)

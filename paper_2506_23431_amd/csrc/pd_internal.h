@@ -128,8 +128,29 @@ struct EncDecState {
   uint16_t *enc_coord;             // [kv_cap] entry j = j: coordinates of the encoder's keys
 };
 
-struct pd_ctx {
+// Buffers with a place per row of a launch sequence.
+struct RowSet {
+  int R_cap, R_pad;         // rows; rows the buffers are padded to
+  float *x;                 // [R_cap][d] residual stream
+  void *xn, *q, *att, *hb;  // activations (type depends on impl)
+  float *qkv32;             // simple path: [R_cap][3d]
+  float *att_part;          // split-K partials of the attention kernel
+  int part_units;           // records of 16 queries x (head_dim + 2) floats that att_part holds
+  float *ypart;             // [4][R_pad][d] split-K partial sums of the O / FFN2 projections
+  float *lm_part_val; int32_t *lm_part_idx;
+  int32_t *row_argmax;      // [R_cap] argmax of each row's logits
+  float *nll;               // [R_pad] loss term of each row
+  RowTables rows;
+  int4 *qinfo_x;            // [R] row table of the attention over the encoder states
+};
+
+struct pd_ctx : RowSet {    // (the set in use: decode steps, passes over one request)
   pd_config cfg;
+  // Launches with rows of several contexts or training targets have a set of their own (R_cap 0: none).  Were the first one
+  // as large, the few rows of a decode step would lie further apart, and its launches, which find no address
+  // translation from the step before, would take longer (width 2048, 32000 words, 32 rows, one layer: 80.7 us per
+  // step against 77.6 when rows for 24 contexts of 64 tokens share the buffers; width 4096, 16 rows 236 against 233).
+  RowSet wide;
   const void *tok_emb, *pos_emb, *lm_head;
   bf16_t *p_lm_head;
   const float *fng, *fnb;
@@ -138,16 +159,10 @@ struct pd_ctx {
   int pair_layers;          // leading layers whose cache holds pairs of halves (kv_pair_layers resolved)
   int32_t *kv_sat;          // [1] keys / values stored saturated at the largest half since pd_create
   // capacities
-  int gen_cap, gen_stride, kv_cap, R_cap, R_pad, vocab_pad, prefill_chunk, prefill_chunk_cap, tf_rows;
+  int gen_cap, gen_stride, kv_cap, vocab_pad, prefill_chunk, prefill_chunk_cap, tf_rows;
   size_t kv_layer_bytes;    // bytes of one K (or V) cache of one layer
   // workspace carve-up
   char *ws; size_t ws_bytes;
-  float *x;                 // [R_cap][d] residual stream
-  void *xn, *q, *att, *hb;  // activations (type depends on impl)
-  float *qkv32;             // simple path: [R_cap][3d]
-  float *att_part;          // split-K partials of the attention kernel
-  int part_units;           // records of 16 queries x (head_dim + 2) floats that att_part holds
-  float *ypart;             // [4][R_pad][d] split-K partial sums of the O / FFN2 projections
   int pend_parts;           // slices of ypart the next norm kernel has to add to x
   float2 *nstats;           // [16][d/16] per-tile row sums left by the output projection for the next norm
   bool packed;              // this launch sequence keeps activations as packed pairs (at most 8 rows):
@@ -157,11 +172,9 @@ struct pd_ctx {
                             // values are loaded with the non-temporal hint (PD_OPT_STREAM_LOADS)
   bool norm_fused;          // the last residual projection left gain * x and per-tile row sums for the next
                             // norm: the projection that follows finishes it, no norm kernel runs
-  float *lm_part_val; int32_t *lm_part_idx; int lm_parts;
-  int32_t *row_argmax;      // [R_cap] argmax of each row's logits
+  int lm_parts;
   float *rope_cs;           // [max_pos][hd/2][2] cos, sin
   int rope_rows;
-  RowTables rows;
   SchedState sch;
   int32_t *ctx_tok;         // [B][L] device copy of the context ids
   // decode parameters fixed by prefill
@@ -171,10 +184,8 @@ struct pd_ctx {
   int arch, Lx;
   EncDecState ed;
   uint16_t *gen_coord;      // [B][gen_stride] grid coordinate (t - 1) + (i - 1) of each generated-side KV slot
-  int4 *qinfo_x;            // [R] row table of the attention over the encoder states
   // teacher-forced forward (Section 3.3)
   float *bias0;             // [H] zeros: the one-entry "no bias" table of the kernels that carry coordinates
-  float *nll;               // [R_pad] loss term of each row
   double *loss;             // [B]
   int32_t *tf_target;       // [B][S][M + 2] device copy of the training targets
   bool prefilled;
