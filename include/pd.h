@@ -85,7 +85,10 @@ typedef struct {
 
 /* Bytes of device workspace pd_create needs for this configuration (KV caches in
  * the library's own layout, re-packed weights for the bf16 path, activations,
- * schedule state).  Returns 0 if the configuration is invalid. */
+ * schedule state).  Returns 0 if the configuration is invalid.
+ * With max_batch > 1 this counts row buffers for several contexts per launch of the context pass (up to
+ * 4096 rows, 1024 on the fp32 path).  pd_create also takes a workspace without that room (as long as it holds the
+ * rows of one context): every context then has launches of its own. */
 size_t pd_workspace_bytes(const pd_config *cfg);
 
 /* Creates a context on the current device.  `dev_workspace` (device, 256-byte

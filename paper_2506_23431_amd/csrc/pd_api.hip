@@ -231,11 +231,13 @@ static size_t carve_with(const pd_config *g, char *base, pd_ctx *c, const pd_enc
   return (cv.off + 255) & ~(size_t)255;
 }
 
-// Room for shared chunks unless it would push a workspace that otherwise fits the static one (pd_generate_static)
-// beyond it.
-static size_t carve(const pd_config *g, char *base, pd_ctx *c, const pd_encdec_config *e = nullptr) {
-  const bool shared = carve_with(g, nullptr, nullptr, e, true) <= PD_STATIC_WORKSPACE_BYTES ||
-                      carve_with(g, nullptr, nullptr, e, false) > PD_STATIC_WORKSPACE_BYTES;
+// Room for shared chunks where the workspace given has it: 24 contexts of 384 tokens, 6 layers of width 768 707 MB
+// against 519 MB with a launch sequence per context, and buffers of the smaller size stay good.  pd_workspace_bytes asks
+// for it unless it would push a workspace that otherwise fits the static one (pd_generate_static) beyond it.
+static size_t carve(const pd_config *g, char *base, pd_ctx *c, const pd_encdec_config *e = nullptr,
+                    size_t given = SIZE_MAX) {
+  const size_t with = carve_with(g, nullptr, nullptr, e, true), without = carve_with(g, nullptr, nullptr, e, false);
+  const bool shared = with <= given && (with <= PD_STATIC_WORKSPACE_BYTES || without > PD_STATIC_WORKSPACE_BYTES);
   return carve_with(g, base, c, e, shared);
 }
 
@@ -317,7 +319,7 @@ static int create_ctx(const pd_config *cfg, const pd_weights *w, void *dev_works
   if (rc) return rc;
   PD_REQUIRE(w && out && dev_workspace, PD_EINVAL, "weights, workspace and out must not be NULL");
   PD_REQUIRE(((uintptr_t)dev_workspace & 255) == 0, PD_EINVAL, "workspace must be 256-byte aligned");
-  size_t need = carve(cfg, nullptr, nullptr);
+  size_t need = carve(cfg, nullptr, nullptr, nullptr, bytes);
   PD_REQUIRE(bytes >= need, PD_ENOMEM, "workspace too small: %zu bytes given, %zu needed", bytes, need);
   PD_REQUIRE(w->tok_emb && w->lm_head && w->final_norm_g && w->wqkv && w->wo && w->w1 && w->w2 &&
                  w->norm1_g && w->norm2_g,
@@ -337,7 +339,7 @@ static int create_ctx(const pd_config *cfg, const pd_weights *w, void *dev_works
   PD_REQUIRE(c, PD_ENOMEM, "out of host memory");
   c->cfg = *cfg;
   c->ws = (char *)dev_workspace; c->ws_bytes = bytes;
-  carve(cfg, c->ws, c);
+  carve(cfg, c->ws, c, nullptr, bytes);
   c->tok_emb = w->tok_emb; c->pos_emb = cfg->pos_kind == 0 ? w->pos_emb : nullptr;
   c->lm_head = w->lm_head; c->fng = w->final_norm_g;
   c->fnb = cfg->norm_kind == 0 ? w->final_norm_b : nullptr;

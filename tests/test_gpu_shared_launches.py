@@ -2,6 +2,8 @@
 targets of different lengths in one teacher-forced pass (rows padded to the longest), against the CPU oracle request by
 request.  The chunk option splits the same requests into other groups; the bf16 tolerance is 2e-2, fp32 1e-4."""
 
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -10,6 +12,7 @@ from oracle import training
 from oracle.model import OracleModel
 from pd_inputs.configs import WorkloadConfig, DTYPE_BF16, DTYPE_F32, FFN_SWIGLU, NORM_RMSNORM, POS_ROPE
 from parity_util import oracle_run, make_decoder, compare_teacher_forced
+from test_library import config_struct
 
 pytestmark = pytest.mark.gpu
 
@@ -44,6 +47,27 @@ def test_contexts_share_a_launch(cfg, chunk):
     stats = compare_teacher_forced(cfg, w, ctx, dec, outs, log=lambda m: print(m, flush=True))
     assert stats["rows"] == cfg.batch * (cfg.n_sub * (cfg.sub_tokens + 1) - 1)
     dec.close()
+
+
+def test_workspace_without_room_for_shared_contexts(monkeypatch):
+    """A workspace that holds the rows of one context per launch (what the library asked for before contexts shared
+    launches) is taken, the contexts then have launches of their own; a smaller one is refused."""
+    from paper_2506_23431_amd import binding
+    cfg = W("one-context-per-launch", d_model=768, n_head=12, d_ff=3072, vocab=2003, batch=24, ctx_len=200, delta_t=1,
+            sub_tokens=4, qkv_std=0.05)
+    one_context = 86428928
+    lib = binding.load()
+    assert lib.pd_workspace_bytes(C.byref(config_struct(cfg))) > one_context
+    w, ctx = pi.make_weights(cfg, threads=4), pi.make_context(cfg)
+    outs = oracle_run(cfg, w, ctx)
+    monkeypatch.setattr(lib, "pd_workspace_bytes", lambda c: one_context)
+    dec = make_decoder(cfg, w)
+    stats = compare_teacher_forced(cfg, w, ctx, dec, outs, log=lambda m: print(m, flush=True))
+    assert stats["rows"] == cfg.batch * (cfg.n_sub * (cfg.sub_tokens + 1) - 1)
+    dec.close()
+    monkeypatch.setattr(lib, "pd_workspace_bytes", lambda c: one_context // 2)
+    with pytest.raises(binding.PdError, match="workspace too small"):
+        make_decoder(cfg, w)
 
 
 @pytest.mark.parametrize("name,lens", [
