@@ -58,6 +58,12 @@ __device__ __forceinline__ f16x8 ld_kv(const uint4 *p) {
   return STREAM ? __builtin_nontemporal_load((const f16x8 *)p) : *(const f16x8 *)p;
 }
 
+// Tags and coordinates stay in one piece until they are used: taken apart or copied at their load, at the end of the block
+// before, they made every block wait there for the loads it should overlap (256 units of head size 32, 107 blocks:
+// 51 us per layer and step, 57 with it).
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void pin(u32x4 &u) { asm volatile("" : "+v"(u)); }
+
 template <int HD, bool SPLIT, bool PAIR, bool BIAS = false, bool STREAM = false, int NW = 4>
 __global__ __launch_bounds__(64 * NW, PAIR ? 1 : NW == 4 ? 3 : NW / 4) void k_attn_mfma(AttnArgs a) {
   constexpr int NC = HD / 32, NHB = HD / 16, PSTR = HD + 2;   // partial: m, l, O[HD] per query
@@ -112,7 +118,7 @@ __global__ __launch_bounds__(64 * NW, PAIR ? 1 : NW == 4 ? 3 : NW / 4) void k_at
   int kb = split * NW + wave;
   Frag kf[2][NC], vf[NHB];
   Frag kl[PAIR ? 2 : 1][PAIR ? NC : 1], vl[PAIR ? NHB : 1];
-  union { uint4 u; uint16_t s[8]; } tg, kco;
+  union { u32x4 u; uint16_t s[8]; } tg, kco;
   const uint16_t *kcp = BIAS ? a.coord + (size_t)req * a.coord_req_stride : nullptr;
   auto load_k = [&](int kbx) {
 #pragma unroll
@@ -125,8 +131,8 @@ __global__ __launch_bounds__(64 * NW, PAIR ? 1 : NW == 4 ? 3 : NW / 4) void k_at
   };
   auto load_v = [&](int kbx) {
     // tags of the lane's 8 keys (clamped: context blocks read entry 0 and never use it)
-    tg.u = *(const uint4 *)(gs + min(max(kbx * 32 + 8 * g - L8, 0), a.gen_stride - 8));
-    if (BIAS) kco.u = *(const uint4 *)(kcp + min(max(kbx * 32 + 8 * g - a.coord_off, 0), a.coord_stride - 8));
+    tg.u = *(const u32x4 *)(gs + min(max(kbx * 32 + 8 * g - L8, 0), a.gen_stride - 8));
+    if (BIAS) kco.u = *(const u32x4 *)(kcp + min(max(kbx * 32 + 8 * g - a.coord_off, 0), a.coord_stride - 8));
 #pragma unroll
     for (int i = 0; i < NHB; ++i) {
       vf[i].hv = ld_kv<STREAM>(&Vp[((size_t)kbx * NHB + i) * 64]);
@@ -200,6 +206,7 @@ __global__ __launch_bounds__(64 * NW, PAIR ? 1 : NW == 4 ? 3 : NW / 4) void k_at
     float sv[8];
     float bv[8];
     if (BIAS) {
+      pin(kco.u);
       const int q_off = q_pos + a.bias_off, last = a.bias_len - 1;
 #pragma unroll
       for (int e = 0; e < 8; ++e) bv[e] = sm_bias[min(max(q_off - (int)kco.s[e], 0), last)];
@@ -209,6 +216,7 @@ __global__ __launch_bounds__(64 * NW, PAIR ? 1 : NW == 4 ? 3 : NW / 4) void k_at
 #pragma unroll
       for (int e = 0; e < 8; ++e) sv[e] = BIAS ? s[e >> 2][e & 3] * a.scale_log2 + bv[e] : s[e >> 2][e & 3] * a.scale_log2;
     } else {
+      pin(tg.u);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         int key = key0 + e;
