@@ -366,35 +366,6 @@ __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a) {
   store4_split(a.out, a.out_lo, act_off(r, h * HD + i * 16 + 4 * g, a.d), y);
 }
 
-// Work-groups per (request, head, query group), and their waves.
-static int pick_splits(pd_ctx *c, int units, int nblk, bool decode, bool pair, int *nw) {
-  int cap = std::max(1, c->part_units / units);
-  if (c->opt_splits > 0) return std::min(c->opt_splits, cap);
-  // One block per compute unit, every wave streaming several key blocks back to back (measured at
-  // 16 heads x 8k keys: 16.2 us with 256 blocks, 17.2 with 512 or 768, 18.7 with 320; at 4 x 32 heads
-  // x 4k keys 256 blocks are 4 us per launch faster than 768).  Always at least one key block per wave.
-  int want = std::max(1, 256 / units);
-  int by_keys = std::max(1, nblk / 4);
-  const int splits = std::max(1, std::min(std::min(want, by_keys), cap));
-  // Short key sets: one work-group of 8 waves per unit and no merge kernel (4 us) where the longer walk of its
-  // waves, about 0.55 us per 32-key block, costs less than that.  Whole passes, 8 waves against splits of 4 waves
-  // plus merge: 12 units x 1024-1300 keys 6.89 against 7.18 ms, 128 units x 2048-2400 keys 26.6 against 27.6 ms;
-  // one work-group of 8 against 4 waves: 24 units x 700 keys 1.98 against 2.01 ms; 16 waves lose to 8 everywhere.
-  // Beyond 96 blocks a unit's keys want more than one compute unit's share of the memory system (128 units x
-  // 4096-6000 keys: 52.9 against 51.7 ms); with more units than compute units 4 waves do as well or better (288
-  // units x 384 keys 4.46 against 4.51 ms).
-  if (nblk <= 32) {
-    // (up to 4 blocks 4 waves hold one each: the other four would only add to the merge)
-    if (decode && !pair && units <= 256 && nblk > 4) *nw = 8;
-    return 1;
-  }
-  if (decode && !pair && units <= 256 && nblk <= 96 && nblk * 0.55 / 8 < nblk * 0.55 / (4 * splits) + 4) {
-    *nw = 8;
-    return 1;
-  }
-  return splits;
-}
-
 template <int HD, bool SPLIT, bool PAIR, bool BIAS, bool STREAM, int NW>
 static void launch_attn_nw(dim3 grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1, const AttnArgs &a) {
   if (e0 || e1) hipExtLaunchKernelGGL((k_attn_mfma<HD, SPLIT, PAIR, BIAS, STREAM, NW>), grid, dim3(64 * NW), 0, s, e0, e1, 0, a);
@@ -445,8 +416,14 @@ int mfma_attention(pd_ctx *c, const LayerPtrs &lw, int A, int nreq, int req0, in
   // the most keys this launch can meet: prefill knows it, decode takes the end of the run
   int n_keys = kv_override >= 0 ? kv_override : c->L + c->S * (c->M + 1);
   a.nblk_static = std::min((n_keys + 31) / 32, c->kv_cap / 32);
-  int nw = 4;
-  a.nsplit = pick_splits(c, units, a.nblk_static, kv_override < 0 || mode, a.kc_lo != nullptr, &nw);
+  // the shape fits the keys of the middle of the run (half of what it can generate)
+  const int nblk = kv_override >= 0 ? a.nblk_static : std::min((c->L + c->S * (c->M + 1) / 2 + 31) / 32, a.nblk_static);
+  const int cap = std::max(1, c->part_units / units);
+  const AttnShape shape = c->opt_splits > 0 ? AttnShape{std::min(c->opt_splits, cap), 4}
+                                            : attn_shape(g.head_dim, units, nblk, cap, kv_override < 0 || mode,
+                                                         a.kc_lo != nullptr, c->stream_loads);
+  const int nw = shape.waves;
+  a.nsplit = shape.splits;
   dim3 grid(a.nsplit, g.n_head, nreq * a.nqg);
   // measurement: mode 1 attaches a start and a stop event to the dispatch of the main kernel itself
   // (their difference is the kernel's execution time), mode 2 records events before the main kernel

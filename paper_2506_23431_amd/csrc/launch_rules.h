@@ -4,8 +4,6 @@
 #include <stdint.h>
 
 #include <algorithm>
-#include <cmath>
-#include <vector>
 
 // ---------------------------------------------------------------------------
 // Attention: work-groups per (request, head, query group) and waves per work-group.
@@ -47,151 +45,5 @@ inline AttnShape attn_shape(int head_dim, int units, int nblk, int cap, bool dec
     if (t < us) { us = t; best = AttnShape{1, 8}; }
   }
   if (splits > 1 && 3.4 + nblk / (4.0 * splits) * pace(4, units * splits) < us) best = AttnShape{splits, 4};
-  return best;
-}
-
-// ---------------------------------------------------------------------------
-// Teacher-forced pass: consecutive requests that share launches, their rows padded to the longest of the group.
-// ---------------------------------------------------------------------------
-struct PassCost { double pass_us, row_us; };
-
-// What a pass costs whatever its rows (9 launches per layer and a few more at 4 us, the weights once at 4.5 TB/s) and per
-// row (multiplies at 0.6 PFLOP/s).  weights: elements of all matrices; parts: 2 with low parts, else 1.  Measured, per
-// call and row: 2 layers of width 2048, 32000 words 227 us at 8 rows, +0.74 us per row (estimate 158 + 1.1); 6 of
-// width 768, 2000 words 269 us, +0.37 (232 + 0.29); 4 of width 1024 230 us, +0.38 (190 + 0.39).
-inline PassCost teacher_pass_cost(int n_layer, double weights, int parts) {
-  return PassCost{4.0 * (9 * n_layer + 5) + 2.0 * weights / 4.5e6, 2.0 * parts * weights / 0.6e9};
-}
-
-// Sizes of the groups: the consecutive partition with the least estimated time.  fits(rows per request, requests) says
-// what one launch sequence holds (not more requests where fewer did not fit).  One request of 500 rows before
-// seven of 20 is a pass of its own in wide models (padded they would be 4000 rows where 640 carry a token) and shares
-// in narrow ones, where a pass costs more than the padding.
-template <typename Fits>
-inline std::vector<int> teacher_groups(const std::vector<int> &rows, const PassCost &cost, Fits fits) {
-  constexpr int MOST = 1024;            // requests of a group (bounds the search; such a pass has as many rows)
-  const int n = (int)rows.size();
-  std::vector<double> best(n + 1, 0.0);
-  std::vector<int> size(n + 1, 0);
-  for (int i = n - 1; i >= 0; --i) {    // best[i]: requests i .. n-1
-    int longest = 0;
-    best[i] = -1.0;
-    for (int k = 1; i + k <= n && k <= MOST; ++k) {
-      longest = std::max(longest, rows[i + k - 1]);
-      if (k > 1 && !fits(longest, k)) break;
-      const double t = cost.pass_us + cost.row_us * (double)k * longest + best[i + k];
-      if (best[i] < 0 || t < best[i]) { best[i] = t; size[i] = k; }
-    }
-  }
-  std::vector<int> groups;
-  for (int i = 0; i < n; i += size[i]) groups.push_back(size[i]);
-  return groups;
-}
-
-// ---------------------------------------------------------------------------
-// Vocabulary projection of 33-128 rows with low parts: waves that share row tiles (k_gemm_t), or that cut K (k_gemm_s).
-// ---------------------------------------------------------------------------
-// k_gemm_s has two or four 16-word tiles per block and starts with every compute unit busy from 512 tiles on; each of its
-// waves holds all row tiles of its K share, so weights arrive in as few, short batches as the registers leave room for.
-// k_gemm_t has 8 or 16 tiles per block and streams the weights in order, but a block walks all of K: it wants
-// a block per compute unit and more.  Both measured at 7 row counts, K 256-5120 and 1024-128000 words, weights from the
-// caches and from memory: beyond 80 rows (8 row tiles, one wave of k_gemm_s per SIMD) k_gemm_t is the faster one from 1025
-// tiles on at every K (0.50-0.92 of the time; at 1000 tiles 0.93-1.5).  Up to 80 rows, from memory: K 768 1500 tiles
-// 1.01-1.06, 1624 0.98-1.00, 2500 0.75; K 1024 1500 0.99-1.04, 1624 0.88; K 1536 1748 1.07, 2000 1.04, 2500 0.81; K 2048
-// 1624-2000 tiles 0.95-1.19 and no gain in a whole step (width 2048, 32000 words, 64 rows 96.0 us against 94.1), 2500
-// 0.86; K 3072 2000 tiles 1.17.  (From the caches the line could lie at 1000-1500 tiles.)
-inline bool vocab_shares_row_tiles(int n_tiles, int KT, int rows) {
-  const int line = KT <= 32 ? 1600 : std::max(2048, 1500 + 12 * (KT - 32));
-  return rows > 32 && (n_tiles >= line || (rows > 80 && n_tiles > 1024));
-}
-
-// ---------------------------------------------------------------------------
-// Projections of more than 128 rows: kernel, tile and K slices of a launch.
-// ---------------------------------------------------------------------------
-// What a launch writes: K slices that the next norm kernel adds, activations or cache entries, winners (and logits).
-enum RowOutput { ROWS_SLICES = 0, ROWS_STORED = 1, ROWS_VOCAB = 2 };
-
-// cut: the waves of a block cut K (k_gemm_s), else they share row tiles (k_gemm_t); row and column tiles of a block (cut) or
-// of a wave; K slices over blocks.
-struct RowTiling { bool cut; int rt, nt, ks; };
-
-// A tiling's time in us is the sum of c[.] times: 1; rounds of blocks as many as are resident at once (`resident` per
-// compute unit, without / with low parts); those, and rounds of 256 blocks, times the k-tiles of a block; MB of weights and
-// MB of activations that reach the L2 caches from beyond; million results written (slices, activations, vocabulary).
-// A column group's blocks sit on one XCD if the blocks of a row group are a multiple of 8, else on up to 8 of them, and
-// every one fetches the weights; beyond 4 MB of weights per XCD they come again for every row group that is not in flight
-// together.  Activations reach as many XCDs as a row group has column groups, at most 8.
-// Coefficients: fit to 25000 launches (129-4096 rows, widths 256-4096, K 256-12288, N 256-50304, weights cycling through
-// 1.3 GB).  Chosen against the fastest of all candidates: 1.7 % slower on average, 20 % for one launch in a hundred.  The
-// estimate it replaces had no term for the fetches: 2048 rows, K 3072, N 768 in slices took 40.7 us where 4 x 3 tiles take
-// 30; 720 rows, K 11008, N 4096 329 against 123; 256 rows, K 4096, 50304 words 582 against 187.
-struct RowCost {
-  bool cut;
-  int rt, nt, resident[2];
-  float c[2][9];
-};
-inline const RowCost *row_costs(int *n) {
-  static const RowCost costs[] = {
-      {true, 2, 2, {5, 4},
-       {{2.03, 0, 0, 0.0351, 0.136, 0.0293, 0.493, 0.723, 0},
-        {2.3, 0, 0, 0.0581, 0.0417, 0.0382, 0.158, 0.576, 1.64}}},
-      {true, 2, 4, {1, 1},
-       {{1.97, 0.318, 0.0558, 0, 0.0758, 0.0335, 0.999, 1.36, 0},
-        {1.7, 0.662, 0.0772, 0, 0.0757, 0.0618, 0.258, 0.694, 2.2}}},
-      {true, 2, 6, {2, 2},
-       {{1.97, 0.807, 0.00982, 0.0612, 0.121, 0.0584, 0.243, 1.56, 0},
-        {2.58, 0.423, 0.00987, 0.0929, 0.0839, 0.0791, 0, 1.4, 1.35}}},
-      {false, 4, 1, {4, 3},
-       {{2.19, 0, 0.182, 0.106, 0.0682, 0, 0.836, 1.31, 0},
-        {2.65, 0, 0.145, 0.162, 0.0467, 0.0225, 0.993, 1.56, 1.12}}},
-      {false, 4, 2, {2, 2},
-       {{2.34, 0.573, 0.249, 0.119, 0.0837, 0.012, 0.663, 1.11, 0},
-        {3.09, 0.264, 0.172, 0.235, 0.0586, 0.0292, 0.81, 1.39, 1.18}}},
-      {false, 4, 3, {2, 1},
-       {{1.81, 2.23, 0.203, 0.218, 0.0892, 0.0452, 0.459, 1.16, 0},
-        {2.46, 2.58, 0.478, 0, 0.054, 0.0518, 0.298, 1.32, 1.28}}},
-      {false, 4, 4, {1, 1},
-       {{4.22, 0.797, 0.498, 0, 0.0779, 0.0553, 0.374, 1.25, 0},
-        {2.86, 3.46, 0.587, 0, 0.057, 0.0552, 0.295, 1.28, 1.34}}},
-      {false, 8, 2, {1, 1},
-       {{3.78, 1.45, 0.424, 0, 0.0637, 0.024, 0.437, 1.38, 0},
-        {3.16, 4.22, 0.596, 0, 0.0495, 0.0352, 0.276, 1.28, 1.02}}},
-      {false, 8, 3, {1, 1},
-       {{1.95, 5.22, 0.51, 0, 0.052, 0.0412, 0.285, 1.54, 0},
-        {0, 10.2, 0.778, 0, 0.0439, 0.0527, 0.0741, 1.42, 0.886}}},
-      {false, 8, 4, {1, 1},
-       {{1.3, 7.83, 0.598, 0, 0.0619, 0.0436, 0.336, 1.66, 0},
-        {2.97, 9.5, 1.02, 0, 0.039, 0.0754, 0.0751, 1.53, 0.999}}}};
-  *n = (int)(sizeof(costs) / sizeof(costs[0]));
-  return costs;
-}
-
-inline double row_tiling_us(const RowCost &t, int n_tiles, int KT, int rows, int ks, bool split, RowOutput out) {
-  const int wide = t.cut ? t.nt : 8 * t.nt, gx = (n_tiles + wide - 1) / wide, gz = (rows + 16 * t.rt - 1) / (16 * t.rt);
-  const int group = gx * ks, kt = (KT + ks - 1) / ks, window = 256 * t.resident[split];
-  const double blocks = (double)group * gz, w_mb = n_tiles * 16.0 * KT * 64e-6;
-  const int xcds = group % 8 == 0 ? 1 : group % 4 == 0 ? 2 : group % 2 == 0 ? 4 : 8;
-  const double together = std::max(1.0, (double)window / group);      // row groups in flight
-  const double again = std::max(1.0, gz / together) * std::min((double)xcds, together);
-  const double fetches = w_mb * xcds / 8 <= 4.0 ? std::min(xcds, gz) : std::min((double)gz, again);
-  const double act_mb = (double)rows * KT * 64e-6 * (split ? 2 : 1) * std::min(8, gx);
-  const double rounds = std::ceil(blocks / window), written = rows * (n_tiles * 16e-6);
-  const float *c = t.c[split];
-  return c[0] + rounds * (c[1] + c[2] * kt) + std::ceil(blocks / 256) * kt * c[3] + c[4] * w_mb * fetches + c[5] * act_mb +
-         c[6 + out] * written * (out == ROWS_SLICES ? ks : 1);
-}
-
-inline RowTiling row_tiling(int n_tiles, int KT, int rows, int max_slices, bool split, RowOutput out) {
-  int n;
-  const RowCost *costs = row_costs(&n);
-  RowTiling best{false, 8, 4, 1};
-  double least = 1e30;
-  for (int i = 0; i < n; ++i)
-    for (int ks = 1; ks <= (out == ROWS_SLICES ? max_slices : 1); ks *= 2) {
-      if (ks > 1 && KT / ks < 8) break;
-      const double us = row_tiling_us(costs[i], n_tiles, KT, rows, ks, split, out) +
-                        0.6 * (ks - 1) * rows * (double)n_tiles * 1.3e-5;      // what the next norm kernel pays for a slice
-      if (us < least) { least = us; best = RowTiling{costs[i].cut, costs[i].rt, costs[i].nt, ks}; }
-    }
   return best;
 }

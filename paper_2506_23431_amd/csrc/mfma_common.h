@@ -22,6 +22,7 @@
 // of the matrix core already in the register order the P^T operand of O^T = V^T P^T
 // needs: scores never leave registers between the two contractions.
 #pragma once
+#include "launch_rules.h"
 #include "pd_internal.h"
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));

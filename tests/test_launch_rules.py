@@ -6,7 +6,6 @@ import itertools
 import os
 import subprocess
 
-import numpy as np
 import pytest
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2506_23431_amd", "csrc")
@@ -18,21 +17,6 @@ void attn(int hd, int units, int nblk, int cap, int decode, int pair, int stream
   const AttnShape s = attn_shape(hd, units, nblk, cap, decode, pair, streamed);
   out[0] = s.splits; out[1] = s.waves;
 }
-int groups(const int *rows, int n, double pass_us, double row_us, int row_cap, int most, int *out) {
-  const std::vector<int> g = teacher_groups(std::vector<int>(rows, rows + n), PassCost{pass_us, row_us},
-                                            [&](int a, int k) { return a * k <= row_cap && k <= most; });
-  for (size_t i = 0; i < g.size(); ++i) out[i] = g[i];
-  return (int)g.size();
-}
-void pass_cost(int n_layer, double weights, int parts, double *out) {
-  const PassCost c = teacher_pass_cost(n_layer, weights, parts);
-  out[0] = c.pass_us; out[1] = c.row_us;
-}
-void tiling(int n_tiles, int kt, int rows, int max_slices, int split, int kind, int *out) {
-  const RowTiling t = row_tiling(n_tiles, kt, rows, max_slices, split, (RowOutput)kind);
-  out[0] = t.cut; out[1] = t.rt; out[2] = t.nt; out[3] = t.ks;
-}
-int vocab(int n_tiles, int kt, int rows) { return vocab_shares_row_tiles(n_tiles, kt, rows); }
 }
 """
 
@@ -81,120 +65,3 @@ def test_attention_shape_at_its_limits(rules):
                 assert out[1] == 4
             if (pair or not decode) and nblk <= 32:
                 assert out[0] == 1
-
-
-def _groups(rules, rows, pass_us, row_us, row_cap=4096, most=1000):
-    out = (C.c_int * len(rows))()
-    n = rules.groups((C.c_int * len(rows))(*rows), len(rows), C.c_double(pass_us), C.c_double(row_us), row_cap, most, out)
-    return list(out[:n])
-
-
-def _cost(rows, groups, pass_us, row_us):
-    total, at = 0.0, 0
-    for k in groups:
-        total += pass_us + row_us * k * max(rows[at:at + k])
-        at += k
-    assert at == len(rows)
-    return total
-
-
-def test_targets_share_a_pass_only_where_padding_costs_less(rules):
-    wide = (158.0, 1.1)              # 2 layers of width 2048, 32000 words
-    assert _groups(rules, [500] + [20] * 7, *wide) == [1, 7]
-    assert _groups(rules, [20] * 7 + [500], *wide) == [7, 1]
-    assert _groups(rules, [200, 190, 180], *wide) == [3]
-    narrow = (232.0, 0.02)
-    assert _groups(rules, [500] + [20] * 7, *narrow) == [8]
-    cost = (C.c_double * 2)()
-    rules.pass_cost(2, C.c_double(166e6), 2, cost)
-    assert abs(cost[0] - wide[0]) < 12 and abs(cost[1] - wide[1]) < 0.02
-
-
-def test_target_groups_are_the_cheapest_partition(rules):
-    rng = np.random.default_rng(5)
-    for _ in range(60):
-        n = int(rng.integers(1, 9))
-        rows = [int(r) for r in np.exp(rng.uniform(0, np.log(900), n))]
-        pass_us, row_us, row_cap, most = float(rng.uniform(20, 400)), float(rng.uniform(0.05, 3)), 2048, int(rng.integers(2, 9))
-        got = _groups(rules, rows, pass_us, row_us, row_cap, most)
-        best = 1e30
-        for cuts in itertools.product((0, 1), repeat=n - 1):
-            sizes, run = [], 1
-            for c in cuts:
-                if c:
-                    sizes.append(run)
-                    run = 1
-                else:
-                    run += 1
-            sizes.append(run)
-            at, fits = 0, True
-            for k in sizes:
-                fits = fits and (k == 1 or (k <= most and k * max(rows[at:at + k]) <= row_cap))
-                at += k
-            if fits:
-                best = min(best, _cost(rows, sizes, pass_us, row_us))
-        at = 0
-        for k in got:
-            assert k == 1 or (k <= most and k * max(rows[at:at + k]) <= row_cap)
-            at += k
-        assert abs(_cost(rows, got, pass_us, row_us) - best) < 1e-6 * best
-
-
-SLICES, STORED, VOCAB = 0, 1, 2
-# column tiles, k-tiles, rows, low parts, output; the candidates within 10 % of the fastest: (waves cut K, row tiles, column
-# tiles, K slices): us
-TILINGS = [
-    (48, 96, 2048, True, SLICES, {(False, 4, 3, 4): 21.3}),
-    (48, 96, 720, True, SLICES, {(False, 4, 2, 4): 14.1}),
-    (256, 344, 720, True, SLICES, {(False, 8, 2, 2): 121.4, (False, 4, 2, 4): 121.9, (False, 8, 4, 4): 123.2,
-                                   (False, 4, 2, 2): 128.7, (False, 4, 4, 2): 130.1, (False, 8, 2, 4): 132.2,
-                                   (False, 4, 4, 4): 133.0}),
-    (256, 344, 1280, True, SLICES, {(False, 8, 3, 2): 177.6}),
-    (192, 24, 192, True, STORED, {(True, 2, 2, 1): 7.7, (True, 2, 4, 1): 7.8, (True, 2, 6, 1): 8.1}),
-    (192, 24, 720, True, STORED, {(True, 2, 6, 1): 15.7, (True, 2, 2, 1): 16.0, (True, 2, 4, 1): 16.2,
-                                  (False, 4, 1, 1): 16.6, (False, 4, 2, 1): 17.1}),
-    (144, 24, 2048, True, STORED, {(False, 4, 3, 1): 23.6}),
-    (1024, 128, 400, True, STORED, {(False, 4, 2, 1): 108.2, (False, 8, 2, 1): 109.8, (False, 4, 4, 1): 112.0}),
-    (512, 64, 4096, True, STORED, {(False, 8, 4, 1): 224.2, (False, 4, 2, 1): 227.0, (False, 4, 4, 1): 236.7,
-                                   (False, 8, 2, 1): 236.9}),
-    (512, 64, 720, False, STORED, {(False, 4, 2, 1): 43.6, (False, 4, 1, 1): 44.4, (False, 8, 2, 1): 46.3}),
-    (3144, 24, 192, True, VOCAB, {(False, 4, 1, 1): 45.2, (False, 4, 2, 1): 47.5, (False, 4, 3, 1): 49.4, (False, 8, 4, 1): 49.4}),
-    (3144, 128, 256, True, VOCAB, {(False, 8, 4, 1): 186.8}),
-    (3144, 24, 400, True, VOCAB, {(False, 4, 1, 1): 108.3, (False, 4, 2, 1): 109.5, (False, 8, 4, 1): 110.7, (False, 8, 2, 1): 116.3}),
-]
-
-
-@pytest.mark.parametrize("n_tiles,kt,rows,split,kind,near", TILINGS)
-def test_row_tiling_is_near_the_fastest_measured(rules, n_tiles, kt, rows, split, kind, near):
-    out = (C.c_int * 4)()
-    rules.tiling(n_tiles, kt, rows, 4, int(split), kind, out)
-    assert (bool(out[0]), *out[1:]) in near
-
-
-def test_row_tiling_at_its_limits(rules):
-    out = (C.c_int * 4)()
-    known = {(1, 2, 2), (1, 2, 4), (1, 2, 6), (0, 4, 1), (0, 4, 2), (0, 4, 3), (0, 4, 4), (0, 8, 2), (0, 8, 3), (0, 8, 4)}
-    for n_tiles, kt, rows, slices, split, kind in itertools.product((1, 6, 161, 8000), (1, 7, 8, 15, 16, 512), (129, 4096, 100000), (1, 2, 4),
-                                                                    (0, 1), (0, 1, 2)):
-        rules.tiling(n_tiles, kt, rows, slices, split, kind, out)
-        assert tuple(out[:3]) in known
-        assert out[3] in ((1, 2, 4) if kind == SLICES else (1,)) and out[3] <= slices and (out[3] == 1 or kt // out[3] >= 8)
-
-
-# column tiles, K, rows; us with waves that cut K and with waves that share row tiles, weights from memory
-VOCABULARY = [
-    (1500, 768, 33, 15.1, 15.5), (1500, 768, 65, 17.0, 17.9), (1624, 768, 80, 18.1, 18.1), (2500, 768, 33, 27.2, 20.1),
-    (1624, 1024, 65, 21.4, 20.7), (2000, 1536, 64, 27.0, 28.1), (1748, 1536, 33, 24.8, 26.7), (2500, 1536, 64, 42.8, 34.6),
-    (2500, 2048, 80, 53.0, 46.8), (1000, 2048, 64, 20.0, 31.0), (2000, 3072, 80, 55.3, 55.9), (3144, 768, 65, 34.5, 27.7),
-    (1028, 768, 96, 25.8, 19.2), (1028, 5120, 128, 98.1, 90.4), (1000, 2048, 96, 28.3, 38.3), (1000, 768, 128, 16.2, 19.3),
-    (3144, 1024, 128, 65.8, 36.6), (3144, 4096, 33, 96.0, 84.6), (3144, 4096, 80, 102.1, 92.2), (8000, 4096, 48, 212.5, 166.9),
-]
-
-
-@pytest.mark.parametrize("n_tiles,k,rows,cut,share", VOCABULARY)
-def test_vocabulary_kernel_is_near_the_faster_measured(rules, n_tiles, k, rows, cut, share):
-    assert (share if rules.vocab(n_tiles, k // 32, rows) else cut) <= 1.03 * min(cut, share)
-
-
-def test_few_rows_keep_waves_that_cut_k(rules):
-    assert not any(rules.vocab(n, kt, rows) for n, kt, rows in itertools.product((1, 1024, 8000, 20000), (1, 24, 128), (1, 16, 32)))
