@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <vector>
 
 // ---------------------------------------------------------------------------
 // Attention: work-groups per (request, head, query group) and waves per work-group.
@@ -46,4 +47,42 @@ inline AttnShape attn_shape(int head_dim, int units, int nblk, int cap, bool dec
   }
   if (splits > 1 && 3.4 + nblk / (4.0 * splits) * pace(4, units * splits) < us) best = AttnShape{splits, 4};
   return best;
+}
+
+// ---------------------------------------------------------------------------
+// Teacher-forced pass: consecutive requests that share launches, their rows padded to the longest of the group.
+// ---------------------------------------------------------------------------
+struct PassCost { double pass_us, row_us; };
+
+// What a pass costs whatever its rows (9 launches per layer and a few more at 4 us, the weights once at 4.5 TB/s) and per
+// row (multiplies at 0.6 PFLOP/s).  weights: elements of all matrices; parts: 2 with low parts, else 1.  Measured, per
+// call and row: 2 layers of width 2048, 32000 words 227 us at 8 rows, +0.74 us per row (estimate 158 + 1.1); 6 of
+// width 768, 2000 words 269 us, +0.37 (232 + 0.29); 4 of width 1024 230 us, +0.38 (190 + 0.39).
+inline PassCost teacher_pass_cost(int n_layer, double weights, int parts) {
+  return PassCost{4.0 * (9 * n_layer + 5) + 2.0 * weights / 4.5e6, 2.0 * parts * weights / 0.6e9};
+}
+
+// Sizes of the groups: the consecutive partition with the least estimated time.  fits(rows per request, requests) says
+// what one launch sequence holds (not more requests where fewer did not fit).  One request of 500 rows before
+// seven of 20 is a pass of its own in wide models (padded they would be 4000 rows where 640 carry a token) and shares
+// in narrow ones, where a pass costs more than the padding.
+template <typename Fits>
+inline std::vector<int> teacher_groups(const std::vector<int> &rows, const PassCost &cost, Fits fits) {
+  constexpr int MOST = 1024;            // requests of a group (bounds the search; such a pass has as many rows)
+  const int n = (int)rows.size();
+  std::vector<double> best(n + 1, 0.0);
+  std::vector<int> size(n + 1, 0);
+  for (int i = n - 1; i >= 0; --i) {    // best[i]: requests i .. n-1
+    int longest = 0;
+    best[i] = -1.0;
+    for (int k = 1; i + k <= n && k <= MOST; ++k) {
+      longest = std::max(longest, rows[i + k - 1]);
+      if (k > 1 && !fits(longest, k)) break;
+      const double t = cost.pass_us + cost.row_us * (double)k * longest + best[i + k];
+      if (best[i] < 0 || t < best[i]) { best[i] = t; size[i] = k; }
+    }
+  }
+  std::vector<int> groups;
+  for (int i = 0; i < n; i += size[i]) groups.push_back(size[i]);
+  return groups;
 }

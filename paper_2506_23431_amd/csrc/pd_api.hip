@@ -804,11 +804,14 @@ extern "C" int pd_teacher_forced(pd_ctx *c, const int32_t *target, int max_len, 
   am.coord = c->gen_coord; am.coord_stride = c->gen_stride; am.coord_req_stride = c->gen_stride;
   am.coord_off = L & ~7; am.pos0 = L;
   int rc;
-  // requests share a pass as long as their rows, each padded to the longest of the group, fit one launch sequence
-  for (int b = 0; b < B;) {
-    int A = rows[b], nreq = 1;
-    while (b + nreq < B && A < 65535 && fits_one_pass(c, std::max(A, rows[b + nreq]), nreq + 1)) A = std::max(A, rows[b + nreq++]);
-    const int R = nreq * A;
+  // requests share a pass, their rows padded to the longest of the group, where that costs less than passes of their own
+  const double dd = (double)g.d_model * g.d_model, ff = (double)g.d_model * g.d_ff;
+  const double weights = g.n_layer * ((c->arch == 1 ? 6 : 4) * dd + (g.ffn_kind == 1 ? 3 : 2) * ff) + (double)g.vocab * g.d_model;
+  const std::vector<int> groups = teacher_groups(rows, teacher_pass_cost(g.n_layer, weights, c->opt_split ? 2 : 1),
+                                                 [&](int A, int nreq) { return A <= 65535 && fits_one_pass(c, A, nreq); });
+  int b = 0;
+  for (const int nreq : groups) {
+    const int A = *std::max_element(rows.begin() + b, rows.begin() + b + nreq), R = nreq * A;
     const PassRows buffers(c, A, nreq);
     if ((rc = launch_teacher_rows(c, c->tf_target, b, nreq, A, max_len, s))) return rc;
     c->packed = false; c->embed_pending = true; c->pend_parts = 0; c->norm_fused = false;

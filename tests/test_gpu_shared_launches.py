@@ -33,6 +33,7 @@ CASES = [
     W("f32", dtype=DTYPE_F32, ctx_len=77),
     W("f32-llama", dtype=DTYPE_F32, d_model=60, n_head=5, head_dim=12, ctx_len=33, **LLAMA),
 ]
+TARGETS = [W("long-targets", n_sub=4, delta_t=1, sub_tokens=30)]
 
 
 @pytest.mark.parametrize("chunk", [0, 112], ids=["all", "two-at-a-time"])
@@ -73,10 +74,12 @@ def test_workspace_without_room_for_shared_contexts(monkeypatch):
 @pytest.mark.parametrize("name,lens", [
     ("hd64", [[5, 3, 2], [2], [6, 5, 6], [1, 1], [6]]),          # 10, 2, 17, 2 and 6 rows, padded to 17
     ("hd128-llama", [[6, 6, 6], [3, 6], [6], [2, 2, 2], [6, 4, 5]]),
+    # 124, 1, 90, 124 and 31 rows where a pass holds 256: groups that begin behind request 0
+    ("long-targets", [[31, 31, 31, 31], [1], [30, 30, 30], [31, 31, 31, 31], [31]]),
 ])
 def test_targets_share_a_pass(name, lens):
     """Every request's logits, terms and loss, and nothing written behind a request's last row."""
-    cfg = next(c for c in CASES if c.name == name)
+    cfg = next(c for c in CASES + TARGETS if c.name == name)
     print(f"[shared] {cfg} targets {lens}", flush=True)
     w, ctx = pi.make_weights(cfg, threads=4), pi.make_context(cfg)
     rng = np.random.default_rng(3)

@@ -6,6 +6,7 @@ import itertools
 import os
 import subprocess
 
+import numpy as np
 import pytest
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2506_23431_amd", "csrc")
@@ -16,6 +17,16 @@ extern "C" {
 void attn(int hd, int units, int nblk, int cap, int decode, int pair, int streamed, int *out) {
   const AttnShape s = attn_shape(hd, units, nblk, cap, decode, pair, streamed);
   out[0] = s.splits; out[1] = s.waves;
+}
+int groups(const int *rows, int n, double pass_us, double row_us, int row_cap, int most, int *out) {
+  const std::vector<int> g = teacher_groups(std::vector<int>(rows, rows + n), PassCost{pass_us, row_us},
+                                            [&](int a, int k) { return a * k <= row_cap && k <= most; });
+  for (size_t i = 0; i < g.size(); ++i) out[i] = g[i];
+  return (int)g.size();
+}
+void pass_cost(int n_layer, double weights, int parts, double *out) {
+  const PassCost c = teacher_pass_cost(n_layer, weights, parts);
+  out[0] = c.pass_us; out[1] = c.row_us;
 }
 }
 """
@@ -65,3 +76,60 @@ def test_attention_shape_at_its_limits(rules):
                 assert out[1] == 4
             if (pair or not decode) and nblk <= 32:
                 assert out[0] == 1
+
+
+def _groups(rules, rows, pass_us, row_us, row_cap=4096, most=1000):
+    out = (C.c_int * len(rows))()
+    n = rules.groups((C.c_int * len(rows))(*rows), len(rows), C.c_double(pass_us), C.c_double(row_us), row_cap, most, out)
+    return list(out[:n])
+
+
+def _cost(rows, groups, pass_us, row_us):
+    total, at = 0.0, 0
+    for k in groups:
+        total += pass_us + row_us * k * max(rows[at:at + k])
+        at += k
+    assert at == len(rows)
+    return total
+
+
+def test_targets_share_a_pass_only_where_padding_costs_less(rules):
+    wide = (158.0, 1.1)              # 2 layers of width 2048, 32000 words
+    assert _groups(rules, [500] + [20] * 7, *wide) == [1, 7]
+    assert _groups(rules, [20] * 7 + [500], *wide) == [7, 1]
+    assert _groups(rules, [200, 190, 180], *wide) == [3]
+    narrow = (232.0, 0.02)
+    assert _groups(rules, [500] + [20] * 7, *narrow) == [8]
+    cost = (C.c_double * 2)()
+    rules.pass_cost(2, C.c_double(166e6), 2, cost)
+    assert abs(cost[0] - wide[0]) < 12 and abs(cost[1] - wide[1]) < 0.02
+
+
+def test_target_groups_are_the_cheapest_partition(rules):
+    rng = np.random.default_rng(5)
+    for _ in range(60):
+        n = int(rng.integers(1, 9))
+        rows = [int(r) for r in np.exp(rng.uniform(0, np.log(900), n))]
+        pass_us, row_us, row_cap, most = float(rng.uniform(20, 400)), float(rng.uniform(0.05, 3)), 2048, int(rng.integers(2, 9))
+        got = _groups(rules, rows, pass_us, row_us, row_cap, most)
+        best = 1e30
+        for cuts in itertools.product((0, 1), repeat=n - 1):
+            sizes, run = [], 1
+            for c in cuts:
+                if c:
+                    sizes.append(run)
+                    run = 1
+                else:
+                    run += 1
+            sizes.append(run)
+            at, fits = 0, True
+            for k in sizes:
+                fits = fits and (k == 1 or (k <= most and k * max(rows[at:at + k]) <= row_cap))
+                at += k
+            if fits:
+                best = min(best, _cost(rows, sizes, pass_us, row_us))
+        at = 0
+        for k in got:
+            assert k == 1 or (k <= most and k * max(rows[at:at + k]) <= row_cap)
+            at += k
+        assert abs(_cost(rows, got, pass_us, row_us) - best) < 1e-6 * best
