@@ -3,7 +3,6 @@
 #include "mfma_common.h"
 
 #include <algorithm>
-#include <cmath>
 
 #ifndef PD_GEMM_EPI   // ---- common part: weight packing, norm kernel -------------------------------
 
@@ -1011,44 +1010,13 @@ static int launch_gemm_cut(GemmArgs a, int rows, int ks, hipStream_t s) {
   return PD_OK;
 }
 
-// Tiling of a launch of more than 128 rows: the candidate that should end first.  Both kernels' times over 15 shapes
-// (192-4096 rows, K 768-11008, N 768-12288) follow, in us, with n = blocks per compute unit and kt = k-tiles of a
-// block,
-//   waves along K (k_gemm_s)   1.5 + n (0.0071 kt KiB + 0.2 RT NT) + 0.25 per further batch of 4 k-tiles of a wave
-//   shared row tiles (k_gemm_t)  4 + n (kt max(0.045-0.049 RT NT, 0.0175 KiB) + 0.35 RT NT)
-// where KiB is what a block requests per k-tile: RT NT multiplies and their operands per k-tile, and per output
-// tile the epilogue.  The first keeps no barrier in its loop and fills the chip with small tiles: 192 rows, K 768,
-// N 3072 5.7 us against 28 with 128 x 256 tiles (24 blocks); 512 rows 9.9 against 28; from about 1024 rows the
-// requests for its operands outweigh (2048 rows: 32 against 26).
-struct RowTiling { bool cut; int rt, nt, ks; double us; };
-
-template <int EPI>
-static RowTiling choose_row_tiling(int n_tiles, int KT, int rows, int max_parts, bool split) {
-  struct Cand { bool cut; int rt, nt, nwk; };
-  static const Cand cands[] = {{true, 2, 2, 4}, {true, 2, 4, 8}, {true, 2, 6, 4},
-                               {false, 4, 1, 8}, {false, 4, 2, 8}, {false, 4, 3, 8}, {false, 4, 4, 8},
-                               {false, 8, 3, 8}, {false, 8, 4, 8}};
-  RowTiling best{false, 8, 4, 1, 1e30};
-  const int parts = split ? 2 : 1;
-  for (const Cand &c : cands)
-    for (int ks = 1; ks <= (EPI == EPI_RESID ? max_parts : 1); ks *= 2) {
-      if (ks > 1 && KT / ks < 8) break;
-      const int cols = c.cut ? c.nt : 8 * c.nt, kt = (KT + ks - 1) / ks;
-      const double blocks = (double)((n_tiles + cols - 1) / cols) * ks * ((rows + 16 * c.rt - 1) / (16 * c.rt));
-      const double q = blocks / 256, n = q <= 3 ? ceil(q) : q + 0.5;
-      const double kib = (c.cut ? c.nt : 8 * c.nt) + parts * c.rt, out = c.rt * c.nt;
-      double us;
-      if (c.cut) us = 1.5 + n * (0.0071 * kt * kib + 0.2 * out) + 0.25 * ((kt + 4 * c.nwk - 1) / (4 * c.nwk) - 1);
-      else us = 4 + n * (kt * std::max((c.rt == 8 ? 0.0225 : 0.0245) * parts * out, 0.0175 * kib) + 0.35 * out);
-      us += 0.6 * (ks - 1) * rows * (double)n_tiles * 1.3e-5;      // what the next norm kernel pays for a slice
-      if (us < best.us) best = RowTiling{c.cut, c.rt, c.nt, ks, us};
-    }
-  return best;
-}
-
+// The tiling is the candidate that should end first (row_tiling).  Small tiles whose waves cut K keep no barrier in their loop
+// and fill the chip: 192 rows, K 768, N 3072 5.7 us against 28 with 128 x 256 tiles (24 blocks), 512 rows 9.9 against 28;
+// from about 1024 rows the requests for their operands outweigh (2048 rows: 32 against 26).
 template <int EPI, bool SPLIT>
 static int launch_gemm_rows(const GemmArgs &a, int rows, hipStream_t s) {
-  const RowTiling t = choose_row_tiling<EPI>(a.n_tiles, a.K / 32, rows, a.max_parts, SPLIT);
+  constexpr RowOutput OUT = EPI == EPI_RESID ? ROWS_SLICES : EPI == EPI_LM ? ROWS_VOCAB : ROWS_STORED;
+  const RowTiling t = row_tiling(a.n_tiles, a.K / 32, rows, a.max_parts, SPLIT, OUT);
   if (t.cut) {
     if (t.nt == 6) return launch_gemm_cut<2, 6, 4, EPI, SPLIT>(a, rows, t.ks, s);
     if (t.nt == 4) return launch_gemm_cut<2, 4, 8, EPI, SPLIT>(a, rows, t.ks, s);
@@ -1056,7 +1024,8 @@ static int launch_gemm_rows(const GemmArgs &a, int rows, hipStream_t s) {
   }
   if (t.rt == 8) {
     if (t.nt == 4) return launch_gemm_t<8, 4, EPI, SPLIT>(a, rows, t.ks, s);
-    return launch_gemm_t<8, 3, EPI, SPLIT>(a, rows, t.ks, s);
+    if (t.nt == 3) return launch_gemm_t<8, 3, EPI, SPLIT>(a, rows, t.ks, s);
+    return launch_gemm_t<8, 2, EPI, SPLIT>(a, rows, t.ks, s);
   }
   switch (t.nt) {
     case 1: return launch_gemm_t<4, 1, EPI, SPLIT>(a, rows, t.ks, s);

@@ -28,6 +28,10 @@ void pass_cost(int n_layer, double weights, int parts, double *out) {
   const PassCost c = teacher_pass_cost(n_layer, weights, parts);
   out[0] = c.pass_us; out[1] = c.row_us;
 }
+void tiling(int n_tiles, int kt, int rows, int max_slices, int split, int kind, int *out) {
+  const RowTiling t = row_tiling(n_tiles, kt, rows, max_slices, split, (RowOutput)kind);
+  out[0] = t.cut; out[1] = t.rt; out[2] = t.nt; out[3] = t.ks;
+}
 }
 """
 
@@ -133,3 +137,44 @@ def test_target_groups_are_the_cheapest_partition(rules):
             assert k == 1 or (k <= most and k * max(rows[at:at + k]) <= row_cap)
             at += k
         assert abs(_cost(rows, got, pass_us, row_us) - best) < 1e-6 * best
+
+
+SLICES, STORED, VOCAB = 0, 1, 2
+# column tiles, k-tiles, rows, low parts, output; the candidates within 10 % of the fastest: (waves cut K, row tiles, column
+# tiles, K slices): us
+TILINGS = [
+    (48, 96, 2048, True, SLICES, {(False, 4, 3, 4): 21.3}),
+    (48, 96, 720, True, SLICES, {(False, 4, 2, 4): 14.1}),
+    (256, 344, 720, True, SLICES, {(False, 8, 2, 2): 121.4, (False, 4, 2, 4): 121.9, (False, 8, 4, 4): 123.2,
+                                   (False, 4, 2, 2): 128.7, (False, 4, 4, 2): 130.1, (False, 8, 2, 4): 132.2,
+                                   (False, 4, 4, 4): 133.0}),
+    (256, 344, 1280, True, SLICES, {(False, 8, 3, 2): 177.6}),
+    (192, 24, 192, True, STORED, {(True, 2, 2, 1): 7.7, (True, 2, 4, 1): 7.8, (True, 2, 6, 1): 8.1}),
+    (192, 24, 720, True, STORED, {(True, 2, 6, 1): 15.7, (True, 2, 2, 1): 16.0, (True, 2, 4, 1): 16.2,
+                                  (False, 4, 1, 1): 16.6, (False, 4, 2, 1): 17.1}),
+    (144, 24, 2048, True, STORED, {(False, 4, 3, 1): 23.6}),
+    (1024, 128, 400, True, STORED, {(False, 4, 2, 1): 108.2, (False, 8, 2, 1): 109.8, (False, 4, 4, 1): 112.0}),
+    (512, 64, 4096, True, STORED, {(False, 8, 4, 1): 224.2, (False, 4, 2, 1): 227.0, (False, 4, 4, 1): 236.7,
+                                   (False, 8, 2, 1): 236.9}),
+    (512, 64, 720, False, STORED, {(False, 4, 2, 1): 43.6, (False, 4, 1, 1): 44.4, (False, 8, 2, 1): 46.3}),
+    (3144, 24, 192, True, VOCAB, {(False, 4, 1, 1): 45.2, (False, 4, 2, 1): 47.5, (False, 4, 3, 1): 49.4, (False, 8, 4, 1): 49.4}),
+    (3144, 128, 256, True, VOCAB, {(False, 8, 4, 1): 186.8}),
+    (3144, 24, 400, True, VOCAB, {(False, 4, 1, 1): 108.3, (False, 4, 2, 1): 109.5, (False, 8, 4, 1): 110.7, (False, 8, 2, 1): 116.3}),
+]
+
+
+@pytest.mark.parametrize("n_tiles,kt,rows,split,kind,near", TILINGS)
+def test_row_tiling_is_near_the_fastest_measured(rules, n_tiles, kt, rows, split, kind, near):
+    out = (C.c_int * 4)()
+    rules.tiling(n_tiles, kt, rows, 4, int(split), kind, out)
+    assert (bool(out[0]), *out[1:]) in near
+
+
+def test_row_tiling_at_its_limits(rules):
+    out = (C.c_int * 4)()
+    known = {(1, 2, 2), (1, 2, 4), (1, 2, 6), (0, 4, 1), (0, 4, 2), (0, 4, 3), (0, 4, 4), (0, 8, 2), (0, 8, 3), (0, 8, 4)}
+    for n_tiles, kt, rows, slices, split, kind in itertools.product((1, 6, 161, 8000), (1, 7, 8, 15, 16, 512), (129, 4096, 100000), (1, 2, 4),
+                                                                    (0, 1), (0, 1, 2)):
+        rules.tiling(n_tiles, kt, rows, slices, split, kind, out)
+        assert tuple(out[:3]) in known
+        assert out[3] in ((1, 2, 4) if kind == SLICES else (1,)) and out[3] <= slices and (out[3] == 1 or kt // out[3] >= 8)
