@@ -545,11 +545,12 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, int nt, const f
       int r = r0 + i * 16 + m;
       float best = -INFINITY;
       int bi = 0x7fffffff;
-      // kvi: the row's {flags, subsequence, limit, request}
       float *dst = nullptr;
-      if (a.logits && r < a.R && (kvi[i].x & ROW_VALID)) {
-        const int q = a.logits_A > 0 ? r / a.logits_A : kvi[i].w;
-        dst = a.logits + ((size_t)q * a.logits_cap + (a.logits_A > 0 ? r - q * a.logits_A : kvi[i].y - 1)) * a.ld_logits;
+      if (a.logits && r < a.R) {
+        const int4 qi = a.rt.qinfo[r];          // {flags, subsequence, limit, request}
+        const int q = a.logits_A > 0 ? r / a.logits_A : qi.w;
+        if (qi.x & ROW_VALID)
+          dst = a.logits + ((size_t)q * a.logits_cap + (a.logits_A > 0 ? r - q * a.logits_A : qi.y - 1)) * a.ld_logits;
       }
       // (a row of logits starts at any multiple of 4 bytes: one 16-byte store, dword-aligned)
       if (dst && n0 + 3 < a.V) *(floatx4_a4 *)(dst + n0) = floatx4_a4{acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
@@ -638,13 +639,13 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(GemmArgs a) {
   // waves along K: NW_K in this block times gridDim.y blocks (EPI_RESID only)
   const int gk = blockIdx.y * NW_K + wk;
   const int kt0 = min(gk * a.k_share, KT), kt1 = min(kt0 + a.k_share, KT);
-  // row data of the KV-append epilogue, requested now so that it arrives with the weights
-  // (EPI_LM: where the row's logits go)
+  // row data of the KV-append epilogue, requested now so that it arrives with the weights (where a row's logits go is
+  // read by the epilogue that stores them: requested here it held 4 registers per row tile in every vocabulary launch)
   constexpr bool QKV = EPI == EPI_QKV || EPI == EPI_QKV_ROPE;
-  int4 kvi[QKV || EPI == EPI_LM ? RT : 1];
-  if (QKV || (EPI == EPI_LM && a.logits)) {
+  int4 kvi[QKV ? RT : 1];
+  if (QKV) {
 #pragma unroll
-    for (int i = 0; i < RT; ++i) kvi[i] = (QKV ? a.rt.kvinfo : a.rt.qinfo)[(rz + i) * 16 + m];
+    for (int i = 0; i < RT; ++i) kvi[i] = a.rt.kvinfo[(rz + i) * 16 + m];
   }
   int tile[NT];
 #pragma unroll
@@ -980,10 +981,10 @@ __global__ __launch_bounds__(512, 1) void k_gemm_t(GemmArgs a) {
   }
   // row data of the epilogue (asked for here: it would cost the loop 4 RT registers)
   constexpr bool QKV = EPI == EPI_QKV || EPI == EPI_QKV_ROPE;
-  int4 kvi[QKV || EPI == EPI_LM ? RT : 1];
-  if (QKV || (EPI == EPI_LM && a.logits)) {
+  int4 kvi[QKV ? RT : 1];
+  if (QKV) {
 #pragma unroll
-    for (int i = 0; i < RT; ++i) kvi[i] = (QKV ? a.rt.kvinfo : a.rt.qinfo)[r0 + i * 16 + m];
+    for (int i = 0; i < RT; ++i) kvi[i] = a.rt.kvinfo[r0 + i * 16 + m];
   }
 #pragma unroll
   for (int t = 0; t < NT; ++t)
