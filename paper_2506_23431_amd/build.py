@@ -8,11 +8,12 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpd.so")
-# (source, extra defines, object name); gemm.hip is compiled once per epilogue (its kernels are many
+# (source, extra defines, object name); gemm.hip is compiled twice per epilogue (its kernels are many
 # template instances) and once for the parts all epilogues share
 SOURCES = [("pd_api.hip", [], "pd_api.o"), ("sched.hip", [], "sched.o"), ("simple.hip", [], "simple.o"),
            ("mfma.hip", [], "mfma.o"), ("attn.hip", [], "attn.o"), ("attn_ctx.hip", [], "attn_ctx.o"), ("encdec.hip", [], "encdec.o"), ("gemm.hip", [], "gemm.o")] + \
-          [("gemm.hip", [f"-DPD_GEMM_EPI={e}"], f"gemm_epi{e}.o") for e in range(7)]
+          [("gemm.hip", [f"-DPD_GEMM_EPI={e}"], f"gemm_epi{e}.o") for e in range(7)] + \
+          [("gemm.hip", [f"-DPD_GEMM_EPI={e}", "-DPD_GEMM_ROWS"], f"gemm_rows{e}.o") for e in range(6)]
 
 
 def hipcc():

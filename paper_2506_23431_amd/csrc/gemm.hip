@@ -347,6 +347,7 @@ int mfma_norm(pd_ctx *c, const float *gain, const float *bias, int R, hipStream_
 #define PD_GEMM_CAT2(a, b) a##b
 #define PD_GEMM_CAT(a, b) PD_GEMM_CAT2(a, b)
 #define PD_GEMM_ENTRY PD_GEMM_CAT(mfma_gemm_epi, PD_GEMM_EPI)
+#define PD_GEMM_ROWS_ENTRY PD_GEMM_CAT(mfma_gemm_rows_epi, PD_GEMM_EPI)
 
 // ---------------------------------------------------------------------------
 // skinny GEMM  y[r][n] = sum_k xn[r][k] W[n][k],  r < 16*RT rows (RT = 1, 2, 4, 5, 8); weights and
@@ -361,8 +362,10 @@ int mfma_norm(pd_ctx *c, const float *gain, const float *bias, int R, hipStream_
 // fragments of the row tiles, then the weight fragments of its tiles) into registers of their own;
 // only then the multiplies run.  A share that is not a multiple of U ends with chunks of 4, 2 and
 // 1 k-tiles, so that no load is ever conditional.
-// This file is compiled once per epilogue (PD_GEMM_EPI = 0..6: kernels and launch code of that
-// epilogue) and once without (weight packing, norm kernel, dispatcher).
+// This file is compiled twice per epilogue (PD_GEMM_EPI = 0..6: kernels and launch code of that epilogue; with
+// PD_GEMM_ROWS those of more than 128 rows and of the vocabulary projection of 33-128) and once without (weight packing,
+// norm kernel, dispatcher).  Two units, because what else a unit holds decides how the compiler orders and allocates a
+// kernel: in one unit with the others the QKV projection of 64 rows, width 4096, took 30.0 us instead of 29.1.
 // ---------------------------------------------------------------------------
 // epilogue of one 16-column tile: lane holds y[r][n0 + j], r = i*16 + m, n0 = nt*16 + 4g, j = 0..3
 // Mean and reciprocal standard deviation of a row from the per-tile sums the producing projection
@@ -408,7 +411,8 @@ struct ResidPre { float4 x, g; };
 // ... and for a projection that finishes a norm: c1 and c2 at the tile's columns
 struct NormPre { float4 c1, c2; };
 
-template <int RT, int EPI>
+// NORMED: instances that can finish a norm (nrm is looked at); the others carry none of its code
+template <int RT, int EPI, bool NORMED = false>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, int nt, const floatx4 (&acc_in)[RT],
                                               const int4 *kvi, int lane, int r0 = 0,
                                               const float2 *nrm = nullptr, const ResidPre *pre = nullptr,
@@ -418,7 +422,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, int nt, const f
   floatx4 acc[RT];
 #pragma unroll
   for (int i = 0; i < RT; ++i) acc[i] = acc_in[i];
-  if ((EPI == EPI_GELU || EPI == EPI_SWIGLU || EPI == EPI_QKV || EPI == EPI_QKV_ROPE) && nrm) {
+  if (NORMED && nrm) {
     // the activations were gain * x: finish the norm here (columns in the packed order of the weights)
     const float4 c1 = npre ? npre->c1 : *(const float4 *)(a.c1 + n0);
     const float4 c2 = npre ? npre->c2 : (a.c2 ? *(const float4 *)(a.c2 + n0) : make_float4(0.f, 0.f, 0.f, 0.f));
@@ -723,7 +727,7 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(GemmArgs a) {
       for (int w = 1; w < NW_K; ++w)
 #pragma unroll
         for (int i = 0; i < RT; ++i) sum[i] += red[((w * NT + t) * RT + i) * 64 + lane];
-      gemm_epilogue<RT, EPI>(a, nt0 + t, sum, kvi, lane, rz * 16, fused_norm ? nrm : nullptr,
+      gemm_epilogue<RT, EPI, FUSED_IN>(a, nt0 + t, sum, kvi, lane, rz * 16, fused_norm ? nrm : nullptr,
                              (FUSED_OUT && t == wk) ? &pre_r : nullptr, (fused_norm && t == wk) ? &pre_n : nullptr);
     }
   } else {
@@ -732,7 +736,7 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(GemmArgs a) {
 #pragma unroll
     for (int t = 0; t < NT; ++t)
       if (nt0 + t < a.n_tiles)
-        gemm_epilogue<RT, EPI>(a, nt0 + t, acc[t], kvi, lane, rz * 16, fused_norm ? nrm : nullptr,
+        gemm_epilogue<RT, EPI, FUSED_IN>(a, nt0 + t, acc[t], kvi, lane, rz * 16, fused_norm ? nrm : nullptr,
                                (FUSED_OUT && t == 0) ? &pre_r : nullptr, (fused_norm && t == 0) ? &pre_n : nullptr);
   }
 }
@@ -740,6 +744,10 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(GemmArgs a) {
 // ---------------------------------------------------------------------------
 // launch
 // ---------------------------------------------------------------------------
+#ifndef PD_GEMM_ROWS
+int PD_GEMM_ROWS_ENTRY(const GemmArgs &a, int rows, hipStream_t s);
+int mfma_gemm_rows_epi5(const GemmArgs &a, int rows, hipStream_t s);
+
 // 1 row tile.  Two column tiles per wave when that still leaves 128 or more blocks: the
 // activation fragments (2 KiB per k-tile with the low parts) are then requested once for 2 KiB of
 // weights instead of 1 KiB, and the vector-memory pipeline of a compute unit, which every request
@@ -868,6 +876,86 @@ static int launch_gemm_wide(const GemmArgs &a, hipStream_t s) {
   }
 }
 
+
+// 17-128 rows against a small weight matrix (at most 16 MB: what the L2 caches hold with room to spare).  One
+// row tile and four column tiles per block instead of all row tiles and one column tile: a k-tile then costs a
+// wave 4 weight + 2 activation requests for 4 output tiles, not 1 + 2 RT for RT, so the busiest compute unit
+// issues about half the requests (its vector-memory pipeline is what bounds these launches), all requests
+// of a wave go out in one batch, and 5 x 48 blocks fill the chip where 192 did not.  The weights are read
+// once per row tile; block ids that differ by a multiple of 8 run on the same XCD (work-groups go to the
+// XCDs round-robin), so with a number of column groups that is a multiple of 8 the row tiles of a group
+// share one L2 and the repeats stay out of HBM.  Measured at 72 rows, width 1024 (cfg3): QKV 10.9 -> 6.9 us, first
+// FFN projection 11.5 -> 9.5, output projection 4.0 (K slices of 8 k-tiles), second FFN projection 8.4 -> 7.7;
+// 0.83 -> 0.76 ms per step.
+// A projection that completes the residual rows and prepares the next norm (never cut along K over blocks)
+// takes one column tile per block, so that the launch still has a block per compute unit: 64 x 5 at width 1024.
+template <int EPI, bool SPLIT, int NT = 4>
+static int launch_gemm_zrows(GemmArgs a, int rows, hipStream_t s) {
+  constexpr int U = 4;
+  const int KT = a.K / 32, groups = (a.n_tiles + NT - 1) / NT, rts = (rows + 15) / 16;
+  // the residual projections also cut K into slices over blocks (summed by the next norm kernel) until the
+  // launch has a block per compute unit
+  int ks = 1;
+  if (EPI == EPI_RESID)
+    while (ks < a.max_parts && groups * rts * ks < 256 && KT / (2 * ks) >= 4) ks *= 2;
+  const int per_block = (KT + ks - 1) / ks;
+  // 4 or 8 waves along K (16 would leave a wave 128 registers, too few for 4 x 4 weight fragments in flight):
+  // one batch of 4 k-tiles per wave up to K = 1024 per slice, two up to 2048.  A block of 8 waves has a compute
+  // unit to itself; a launch of more than 256 blocks therefore takes 4 waves per block (two batches per wave),
+  // so that all its blocks are resident at once instead of a few left over for a second round (320 blocks at
+  // width 1024, 72 rows: first FFN projection 10.3 -> 9.3 us, second 8.1 -> 7.7)
+  const int nwk = (per_block > 16 && (per_block > 64 || (long)groups * ks * rts <= 256)) ? 8 : 4;
+  a.k_share = (per_block + nwk - 1) / nwk;
+  dim3 grid(groups, ks, rts);
+  constexpr bool DEF = norm_in_default(1, EPI), QKV_NORM = EPI == EPI_QKV || EPI == EPI_QKV_ROPE;
+  if (QKV_NORM && a.stats_in) {
+    if (nwk == 4) hipLaunchKernelGGL((k_gemm_s<1, NT, 4, U, EPI, SPLIT, false, true, false, (QKV_NORM || DEF)>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_gemm_s<1, NT, 8, U, EPI, SPLIT, false, true, false, (QKV_NORM || DEF)>), grid, dim3(512), 0, s, a);
+  } else if (nwk == 4) hipLaunchKernelGGL((k_gemm_s<1, NT, 4, U, EPI, SPLIT, false, true>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((k_gemm_s<1, NT, 8, U, EPI, SPLIT, false, true>), grid, dim3(512), 0, s, a);
+  PD_CHECK_HIP(hipGetLastError());
+  if (EPI == EPI_RESID && a.parts_out) *a.parts_out = ks;
+  return PD_OK;
+}
+
+template <int EPI, bool SPLIT>
+static int launch_gemm_split(const GemmArgs &a, int rows, hipStream_t s) {
+  constexpr bool zrows = EPI != EPI_LM;
+  if (zrows && mfma_gemm_row_tile_blocks(a.n_tiles, a.K, rows, EPI == EPI_RESID ? a.max_parts : 1))
+    return launch_gemm_zrows<EPI, SPLIT, (EPI == EPI_RESID_NORM ? 1 : 4)>(a, rows, s);
+  if (EPI == EPI_RESID_NORM || a.stats_in)
+    PD_REQUIRE(rows <= 16, PD_EINVAL, "a projection of this shape cannot prepare or finish a norm for %d rows", rows);
+  if (EPI == EPI_LM && SPLIT && vocab_shares_row_tiles(a.n_tiles, a.K / 32, rows)) return mfma_gemm_rows_epi5(a, rows, s);
+  switch (mfma_gemm_row_tiles(rows)) {
+    case 16: return launch_gemm_small<1, EPI, SPLIT, false>(a, s);
+    case 32: return launch_gemm_wide<2, EPI, SPLIT>(a, s);
+    case 64: return launch_gemm_wide<4, EPI, SPLIT>(a, s);
+    case 80: return launch_gemm_wide<5, EPI, SPLIT>(a, s);
+    default: return launch_gemm_wide<8, EPI, SPLIT>(a, s);
+  }
+}
+
+template <int EPI>
+static int launch_gemm(const GemmArgs &a, int rows, hipStream_t s) {
+  if (EPI == EPI_RESID_NORM || a.stats_in)
+    PD_REQUIRE(rows <= 128 && a.R <= 128, PD_EINVAL,
+               "projections that prepare or finish a norm take at most 128 rows (%d)", rows);
+  if constexpr (EPI != EPI_RESID_NORM) {
+    if (rows > 128) {
+      PD_REQUIRE(!a.packed, PD_EINVAL, "packed activations hold at most 8 rows (%d)", rows);
+      return PD_GEMM_ROWS_ENTRY(a, rows, s);
+    }
+  }
+  if (a.packed) {
+    PD_REQUIRE(rows <= 8 && a.R <= 8, PD_EINVAL, "packed activations hold at most 8 rows (%d)", rows);
+    return launch_gemm_small<1, EPI, false, true>(a, s);
+  }
+  return a.xn_lo ? launch_gemm_split<EPI, true>(a, rows, s) : launch_gemm_split<EPI, false>(a, rows, s);
+}
+
+int PD_GEMM_ENTRY(const GemmArgs &a, int rows, hipStream_t s) { return launch_gemm<PD_GEMM_EPI>(a, rows, s); }
+
+#else   // ---- more than 128 rows, and the vocabulary projection of 33-128 -------------------------
 
 // ---------------------------------------------------------------------------
 // More than 128 rows against matrices that make the multiplies the bound (the context pass, large teacher-forced
@@ -1036,47 +1124,7 @@ static int launch_gemm_rows(const GemmArgs &a, int rows, hipStream_t s) {
   }
 }
 
-// 17-128 rows against a small weight matrix (at most 16 MB: what the L2 caches hold with room to spare).  One
-// row tile and four column tiles per block instead of all row tiles and one column tile: a k-tile then costs a
-// wave 4 weight + 2 activation requests for 4 output tiles, not 1 + 2 RT for RT, so the busiest compute unit
-// issues about half the requests (its vector-memory pipeline is what bounds these launches), all requests
-// of a wave go out in one batch, and 5 x 48 blocks fill the chip where 192 did not.  The weights are read
-// once per row tile; block ids that differ by a multiple of 8 run on the same XCD (work-groups go to the
-// XCDs round-robin), so with a number of column groups that is a multiple of 8 the row tiles of a group
-// share one L2 and the repeats stay out of HBM.  Measured at 72 rows, width 1024 (cfg3): QKV 10.9 -> 6.9 us, first
-// FFN projection 11.5 -> 9.5, output projection 4.0 (K slices of 8 k-tiles), second FFN projection 8.4 -> 7.7;
-// 0.83 -> 0.76 ms per step.
-// A projection that completes the residual rows and prepares the next norm (never cut along K over blocks)
-// takes one column tile per block, so that the launch still has a block per compute unit: 64 x 5 at width 1024.
-template <int EPI, bool SPLIT, int NT = 4>
-static int launch_gemm_zrows(GemmArgs a, int rows, hipStream_t s) {
-  constexpr int U = 4;
-  const int KT = a.K / 32, groups = (a.n_tiles + NT - 1) / NT, rts = (rows + 15) / 16;
-  // the residual projections also cut K into slices over blocks (summed by the next norm kernel) until the
-  // launch has a block per compute unit
-  int ks = 1;
-  if (EPI == EPI_RESID)
-    while (ks < a.max_parts && groups * rts * ks < 256 && KT / (2 * ks) >= 4) ks *= 2;
-  const int per_block = (KT + ks - 1) / ks;
-  // 4 or 8 waves along K (16 would leave a wave 128 registers, too few for 4 x 4 weight fragments in flight):
-  // one batch of 4 k-tiles per wave up to K = 1024 per slice, two up to 2048.  A block of 8 waves has a compute
-  // unit to itself; a launch of more than 256 blocks therefore takes 4 waves per block (two batches per wave),
-  // so that all its blocks are resident at once instead of a few left over for a second round (320 blocks at
-  // width 1024, 72 rows: first FFN projection 10.3 -> 9.3 us, second 8.1 -> 7.7)
-  const int nwk = (per_block > 16 && (per_block > 64 || (long)groups * ks * rts <= 256)) ? 8 : 4;
-  a.k_share = (per_block + nwk - 1) / nwk;
-  dim3 grid(groups, ks, rts);
-  constexpr bool DEF = norm_in_default(1, EPI), QKV_NORM = EPI == EPI_QKV || EPI == EPI_QKV_ROPE;
-  if (QKV_NORM && a.stats_in) {
-    if (nwk == 4) hipLaunchKernelGGL((k_gemm_s<1, NT, 4, U, EPI, SPLIT, false, true, false, (QKV_NORM || DEF)>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((k_gemm_s<1, NT, 8, U, EPI, SPLIT, false, true, false, (QKV_NORM || DEF)>), grid, dim3(512), 0, s, a);
-  } else if (nwk == 4) hipLaunchKernelGGL((k_gemm_s<1, NT, 4, U, EPI, SPLIT, false, true>), grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((k_gemm_s<1, NT, 8, U, EPI, SPLIT, false, true>), grid, dim3(512), 0, s, a);
-  PD_CHECK_HIP(hipGetLastError());
-  if (EPI == EPI_RESID && a.parts_out) *a.parts_out = ks;
-  return PD_OK;
-}
-
+#if PD_GEMM_EPI == 5     // EPI_LM
 // Vocabulary projection of 33-128 rows: the same kernel with all rows in one group and one or two column tiles per
 // wave.  Cut along K over 4 waves (launch_gemm_wide) every wave requests a few k-tiles, waits for all of them, multiplies,
 // and the blocks end with a sum through LDS; one stream of k-tiles per block hides both.  One layer + vocabulary, us per
@@ -1099,51 +1147,24 @@ static int launch_gemm_vocab(const GemmArgs &a, int rows, hipStream_t s) {
   return PD_OK;
 }
 
-template <int EPI, bool SPLIT>
-static int launch_gemm_split(const GemmArgs &a, int rows, hipStream_t s) {
-  constexpr bool zrows = EPI != EPI_LM;
-  if (zrows && mfma_gemm_row_tile_blocks(a.n_tiles, a.K, rows, EPI == EPI_RESID ? a.max_parts : 1))
-    return launch_gemm_zrows<EPI, SPLIT, (EPI == EPI_RESID_NORM ? 1 : 4)>(a, rows, s);
-  if (EPI == EPI_RESID_NORM || a.stats_in)
-    PD_REQUIRE(rows <= 16, PD_EINVAL, "a projection of this shape cannot prepare or finish a norm for %d rows", rows);
-  if constexpr (EPI == EPI_LM && SPLIT) {
-    const int rt = mfma_gemm_row_tiles(rows) / 16, KT = a.K / 32;
-    if (rows > 32 && (a.n_tiles >= 1500 + 12 * std::max(0, KT - 32) || (rt == 8 && a.n_tiles > 1024))) {
-      const bool two = a.n_tiles > 2048 && (rt * KT >= 160 || a.n_tiles > 4096);
-      if (rt == 4) return two ? launch_gemm_vocab<4, 2>(a, rows, s) : launch_gemm_vocab<4, 1>(a, rows, s);
-      if (rt == 5) return two ? launch_gemm_vocab<5, 2>(a, rows, s) : launch_gemm_vocab<5, 1>(a, rows, s);
-      return two ? launch_gemm_vocab<8, 2>(a, rows, s) : launch_gemm_vocab<8, 1>(a, rows, s);
-    }
-  }
-  switch (mfma_gemm_row_tiles(rows)) {
-    case 16: return launch_gemm_small<1, EPI, SPLIT, false>(a, s);
-    case 32: return launch_gemm_wide<2, EPI, SPLIT>(a, s);
-    case 64: return launch_gemm_wide<4, EPI, SPLIT>(a, s);
-    case 80: return launch_gemm_wide<5, EPI, SPLIT>(a, s);
-    default: return launch_gemm_wide<8, EPI, SPLIT>(a, s);
-  }
+static int launch_gemm_vocab_rows(const GemmArgs &a, int rows, hipStream_t s) {
+  const int rt = mfma_gemm_row_tiles(rows) / 16, KT = a.K / 32;
+  const bool two = a.n_tiles > 2048 && (rt * KT >= 160 || a.n_tiles > 4096);
+  if (rt == 4) return two ? launch_gemm_vocab<4, 2>(a, rows, s) : launch_gemm_vocab<4, 1>(a, rows, s);
+  if (rt == 5) return two ? launch_gemm_vocab<5, 2>(a, rows, s) : launch_gemm_vocab<5, 1>(a, rows, s);
+  return two ? launch_gemm_vocab<8, 2>(a, rows, s) : launch_gemm_vocab<8, 1>(a, rows, s);
+}
+#endif
+
+int PD_GEMM_ROWS_ENTRY(const GemmArgs &a, int rows, hipStream_t s) {
+  constexpr int EPI = PD_GEMM_EPI;
+#if PD_GEMM_EPI == 5
+  if (rows <= 128) return launch_gemm_vocab_rows(a, rows, s);
+#endif
+  return a.xn_lo ? launch_gemm_rows<EPI, true>(a, rows, s) : launch_gemm_rows<EPI, false>(a, rows, s);
 }
 
-template <int EPI>
-static int launch_gemm(const GemmArgs &a, int rows, hipStream_t s) {
-  if (EPI == EPI_RESID_NORM || a.stats_in)
-    PD_REQUIRE(rows <= 128 && a.R <= 128, PD_EINVAL,
-               "projections that prepare or finish a norm take at most 128 rows (%d)", rows);
-  if constexpr (EPI != EPI_RESID_NORM) {
-    if (rows > 128) {
-      PD_REQUIRE(!a.packed, PD_EINVAL, "packed activations hold at most 8 rows (%d)", rows);
-      return a.xn_lo ? launch_gemm_rows<EPI, true>(a, rows, s) : launch_gemm_rows<EPI, false>(a, rows, s);
-    }
-  }
-  if (a.packed) {
-    PD_REQUIRE(rows <= 8 && a.R <= 8, PD_EINVAL, "packed activations hold at most 8 rows (%d)", rows);
-    return launch_gemm_small<1, EPI, false, true>(a, s);
-  }
-  return a.xn_lo ? launch_gemm_split<EPI, true>(a, rows, s) : launch_gemm_split<EPI, false>(a, rows, s);
-}
-
-// one translation unit per epilogue
-int PD_GEMM_ENTRY(const GemmArgs &a, int rows, hipStream_t s) { return launch_gemm<PD_GEMM_EPI>(a, rows, s); }
+#endif
 
 #else   // ---- common part: dispatcher ----------------------------------------------------------
 

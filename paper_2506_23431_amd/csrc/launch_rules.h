@@ -89,6 +89,15 @@ inline std::vector<int> teacher_groups(const std::vector<int> &rows, const PassC
 }
 
 // ---------------------------------------------------------------------------
+// Vocabulary projection of 33-128 rows with low parts: waves that share row tiles (k_gemm_t), or that cut K (k_gemm_s).
+// ---------------------------------------------------------------------------
+// k_gemm_t wants a compute unit per block of 8 column tiles to be ahead, and the longer K, the more a single round of K-cut
+// blocks hides by itself; beyond 80 rows k_gemm_s takes 4 column tiles per block, a second round from 1025 tiles on.
+inline bool vocab_shares_row_tiles(int n_tiles, int KT, int rows) {
+  return rows > 32 && (n_tiles >= 1500 + 12 * std::max(0, KT - 32) || (rows > 80 && n_tiles > 1024));
+}
+
+// ---------------------------------------------------------------------------
 // Projections of more than 128 rows: kernel, tile and K slices of a launch.
 // ---------------------------------------------------------------------------
 // What a launch writes: K slices that the next norm kernel adds, activations or cache entries, winners (and logits).
