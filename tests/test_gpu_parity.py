@@ -585,10 +585,10 @@ def test_separate_second_norm_kernel(name):
 
 @pytest.mark.parametrize("name", ["mfma-hd64", "mfma-hd32", "mfma-hd96", "mfma-sequential", "mfma-flat", "rms-learned"])
 def test_first_norm_prepared_by_the_previous_layer(name):
-    """Value 2 of PD_OPT_FUSE_NORM: the second FFN projection of a layer completes the residual rows and
-    hands gain * x with its row sums to the next layer's QKV projection, which finishes that layer's first
-    norm in its epilogue (steps of at most 16 rows, no rotary positions): packed pairs, separate low
-    parts, LayerNorm with bias and RMSNorm."""
+    """The second FFN projection of a layer completes the residual rows and hands gain * x with its row sums
+    to the next layer's QKV projection, which finishes that layer's first norm in its epilogue (steps of at
+    most 16 rows): packed pairs, separate low parts, LayerNorm with bias and RMSNorm.  Models of this size do
+    so by themselves; value 2 of PD_OPT_FUSE_NORM asks for it in all (wider ones: test_gpu_norm_handover.py)."""
     from paper_2506_23431_amd import binding
     cfg = CASES[name] if name in CASES else small(name, seed=52, dtype=DTYPE_BF16, d_model=160, n_head=5,
                                                    head_dim=32, d_ff=288, vocab=700, ctx_len=61, n_sub=5,

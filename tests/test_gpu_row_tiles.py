@@ -35,11 +35,15 @@ CASES = [
 ]
 
 
+WORST = {}              # largest logit difference by case and form
+
+
 @pytest.mark.parametrize("single", [False, True], ids=["pairs", "single"])
 @pytest.mark.parametrize("cfg", CASES, ids=[c.name for c in CASES])
 def test_context_pass_of_many_rows(cfg, single):
     """Both activation forms of the context pass (pairs of bf16 values, single values): the bf16 tolerance of
-    2e-2 holds for either at these widths."""
+    2e-2 holds for either at these widths, and pairs differ by less than a third of what single values do (measured: a
+    sixth or less): a product that left the low parts out would add half of it or more."""
     from paper_2506_23431_amd import binding
     print(f"[row-tiles] {cfg}", flush=True)
     w, ctx = pi.make_weights(cfg, threads=4), pi.make_context(cfg)
@@ -49,3 +53,6 @@ def test_context_pass_of_many_rows(cfg, single):
     stats = compare_teacher_forced(cfg, w, ctx, dec, outs, log=lambda m: print(m, flush=True))
     assert stats["rows"] == cfg.batch * (cfg.n_sub * (cfg.sub_tokens + 1) - 1)
     dec.close()
+    WORST[cfg.name, single] = stats["worst"]
+    if (cfg.name, not single) in WORST:
+        assert 3 * WORST[cfg.name, False] < WORST[cfg.name, True]

@@ -78,12 +78,14 @@ def test_workspace_without_room_for_shared_contexts(monkeypatch):
     ("long-targets", [[31, 31, 31, 31], [1], [30, 30, 30], [31, 31, 31, 31], [31]]),
 ])
 def test_targets_share_a_pass(name, lens):
-    """Every request's logits, terms and loss, and nothing written behind a request's last row."""
+    """Every request's logits, terms and loss, request by request; without low parts the logits are several times further
+    off, so that a product that left them out would show."""
     cfg = next(c for c in CASES + TARGETS if c.name == name)
     print(f"[shared] {cfg} targets {lens}", flush=True)
     w, ctx = pi.make_weights(cfg, threads=4), pi.make_context(cfg)
     rng = np.random.default_rng(3)
     targets = [[[0] + [int(t) for t in rng.integers(1, cfg.vocab, n - 1)] for n in t] for t in lens]
+    from paper_2506_23431_amd import binding
     model = OracleModel(cfg, w)
     dec = make_decoder(cfg, w)
     dec.prefill_context(ctx, cfg.n_sub, cfg.delta_t, cfg.sub_tokens, cfg.time_steps)
@@ -94,4 +96,41 @@ def test_targets_share_a_pass(name, lens):
             assert np.abs(logits[b].cpu().numpy() - want).max() < 2e-2
             assert np.abs(nll[b] - terms).max() < 4e-2 and abs(loss[b] - total) < 4e-2 * max(1, len(terms))
         targets = [t[::-1] if i % 2 else t for i, t in enumerate(targets)]
+    off = {}
+    for split_act in (0, 1):
+        dec.set_option(binding.PD_OPT_SPLIT_ACT, split_act)
+        logits, _, _ = dec.teacher_forced(targets)
+        off[split_act] = max(np.abs(logits[b].cpu().numpy() - training.teacher_forced(model, ctx[b], t, cfg.delta_t)[0]).max()
+                             for b, t in enumerate(targets))
+    print(f"[shared] {name}: {off}", flush=True)
+    assert 3 * off[1] < off[0]
+    dec.close()
+
+
+def test_nothing_is_written_behind_a_target():
+    """A pass pads every request's rows to the longest of its group: the caller's logits and terms keep what they held from
+    a request's last row on."""
+    import torch
+    from paper_2506_23431_amd import binding
+    cfg = CASES[0]
+    w, ctx = pi.make_weights(cfg, threads=4), pi.make_context(cfg)
+    lens, cap, mark = [[5, 3, 2], [2], [6, 5, 6], [1, 1], [6]], 20, 12345.0
+    target = np.full((cfg.batch, cfg.n_sub, 6), -1, dtype=np.int32)
+    for b, t in enumerate(lens):
+        for i, n in enumerate(t):
+            target[b, i, :n] = np.arange(n) + 2 + b
+    dec = make_decoder(cfg, w)
+    dec.prefill_context(ctx, cfg.n_sub, cfg.delta_t, cfg.sub_tokens, cfg.time_steps)
+    logits = torch.full((cfg.batch, cap, cfg.vocab), mark, device="cuda:0")
+    nll = np.full((cfg.batch, cap), mark, dtype=np.float32)
+    loss, rows = np.zeros(cfg.batch), np.zeros(cfg.batch, dtype=np.int32)
+    i32p = C.POINTER(C.c_int32)
+    assert dec.lib.pd_teacher_forced(dec.ctx, target.ctypes.data_as(i32p), 6, C.c_void_p(logits.data_ptr()), cap,
+                                     nll.ctypes.data_as(C.POINTER(C.c_float)), loss.ctypes.data_as(C.POINTER(C.c_double)),
+                                     rows.ctypes.data_as(i32p), dec._stream()) == 0
+    logits = logits.cpu().numpy()
+    assert rows.tolist() == [sum(t) for t in lens]
+    for b, n in enumerate(rows):
+        assert (logits[b, n:] == mark).all() and (nll[b, n:] == mark).all()
+        assert (logits[b, :n] != mark).all() and (nll[b, :n] != mark).all()
     dec.close()

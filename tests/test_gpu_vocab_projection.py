@@ -35,4 +35,8 @@ def test_vocabulary_projection_of_many_rows(cfg, stream):
     dec.set_option(binding.PD_OPT_STREAM_LOADS, stream)
     stats = compare_teacher_forced(cfg, w, ctx, dec, outs, log=lambda m: print(m, flush=True))
     assert stats["rows"] == cfg.batch * (cfg.n_sub * (cfg.sub_tokens + 1) - 1)
+    if stream == 0:     # without low parts (the kernel that cuts K): an order of magnitude further off
+        dec.set_option(binding.PD_OPT_SPLIT_ACT, 0)
+        single = compare_teacher_forced(cfg, w, ctx, dec, outs, tol=0.1, log=lambda m: print(m, flush=True))
+        assert 3 * stats["worst"] < single["worst"]
     dec.close()
