@@ -766,8 +766,10 @@ static int launch_gemm_small_nt(GemmArgs a, int ks, hipStream_t s) {
   while (nwk < 16 && (long)groups * ks * nwk < 1500 && (per_block + nwk - 1) / nwk > 2) nwk *= 2;
   a.k_share = (per_block + nwk - 1) / nwk;
   dim3 grid(groups, ks);
-  // a projection that completes the rows is not cut over blocks; with 5-8 k-tiles per wave it asks for all of them at
-  // once instead of in two batches (K 3072, width 768: in two batches it cost more than the norm kernel it replaces)
+  // a projection that completes the rows is not cut over blocks; with 6 k-tiles per wave (packed rows: also 8) it asks for
+  // all of them at once instead of in two batches (K 3072, width 768: in two batches it cost more than the norm kernel it
+  // replaces).  Shares of 5 and 7 take two or three batches, 4 + 1 and 4 + 2 + 1 k-tiles: the last ones are short, and
+  // whole steps at d_ff 2560 and 3584 are no slower than with the norm kernel (widths 512-1024, 8 and 12 rows).
   if constexpr (EPI == EPI_RESID_NORM && NT == 1) {
     constexpr int UL = SPLIT ? 6 : 8;
     if (nwk == 16 && a.k_share > 4 && a.k_share <= UL) {
@@ -959,11 +961,11 @@ int PD_GEMM_ENTRY(const GemmArgs &a, int rows, hipStream_t s) { return launch_ge
 
 // ---------------------------------------------------------------------------
 // More than 128 rows against matrices that make the multiplies the bound (the context pass, large teacher-forced
-// passes; also the vocabulary projection of 33-128 rows, see launch_gemm_vocab): grid (column groups, K slices, groups of 16 RT rows).  A block is NW = 8 waves (two per SIMD: a single
-// wave issues a 16x16x32 multiply every 29 clocks, two or more every 19) that own NT column tiles each and share the
-// RT row tiles of their row group: per k-tile every wave requests its share of the activation fragments (high and
-// low parts) and its own weight fragments, two k-tiles ahead; the activation fragments pass through LDS (two buffers),
-// and every wave multiplies all of them with its weights.
+// passes; also the vocabulary projection of 33-128 rows, see launch_gemm_vocab): grid (column groups, K slices, groups
+// of 16 RT rows).  A block is NW = 8 waves (two per SIMD: a single wave issues a 16x16x32 multiply every 29 clocks, two
+// or more every 19) that own NT column tiles each and share the RT row tiles of their row group: per k-tile every wave
+// requests its share of the activation fragments (high and low parts) and its own weight fragments, two k-tiles ahead;
+// the activation fragments pass through LDS (two buffers), and every wave multiplies all of them with its weights.
 // One barrier per k-tile, in the middle of its multiplies: the fragments of a k-tile go from LDS to the matrix cores
 // in groups of GS, the group after next is requested when a group has been multiplied, and behind the barrier that
 // request already goes to the next k-tile's buffer.  So a wave never stands between a barrier and its first multiply
@@ -976,7 +978,7 @@ int PD_GEMM_ENTRY(const GemmArgs &a, int rows, hipStream_t s) { return launch_ge
 template <int RT, int NT, int EPI, bool SPLIT, bool SW = false>
 __global__ __launch_bounds__(512, 1) void k_gemm_t(GemmArgs a) {
   constexpr int NW = 8, NA = SPLIT ? 2 * RT : RT;     // activation fragments of a k-tile
-  constexpr int NAW = (NA + NW - 1) / NW;             // staged by one wave (not a multiple of the waves: some twice, same bytes)
+  constexpr int NAW = (NA + NW - 1) / NW;             // staged by one wave (no multiple of the waves: some twice, same bytes)
   constexpr int GS = RT == 5 ? 5 : 4, NG = NA / GS;
   static_assert(NA % GS == 0 && (NG == 1 || NG % 2 == 0), "fragment groups alternate between two register sets");
   __shared__ bf16x8 sm_x[2][NA][64];   // (vector types throughout: struct copies would keep xr in scratch memory)
@@ -1171,7 +1173,8 @@ int PD_GEMM_ROWS_ENTRY(const GemmArgs &a, int rows, hipStream_t s) {
 // (launch_gemm_zrows)
 bool mfma_gemm_row_tile_blocks(int n_tiles, int K, int rows, int k_slices) {
   const size_t bytes = (size_t)n_tiles * 16 * K * 2;
-  return rows > 16 && rows <= 128 && (bytes <= ((size_t)16 << 20) || (rows <= 32 && bytes <= ((size_t)64 << 20))) && K / 32 <= 64 * k_slices;
+  return rows > 16 && rows <= 128 && (bytes <= ((size_t)16 << 20) || (rows <= 32 && bytes <= ((size_t)64 << 20))) &&
+         K / 32 <= 64 * k_slices;
 }
 
 int mfma_gemm_row_tiles(int rows) {
