@@ -1106,7 +1106,8 @@ static int launch_gemm_cut(GemmArgs a, int rows, int ks, hipStream_t s) {
 // from about 1024 rows the requests for their operands outweigh (2048 rows: 32 against 26).
 template <int EPI, bool SPLIT>
 static int launch_gemm_rows(const GemmArgs &a, int rows, hipStream_t s) {
-  constexpr RowOutput OUT = EPI == EPI_RESID ? ROWS_SLICES : EPI == EPI_LM ? ROWS_VOCAB : ROWS_STORED;
+  constexpr RowOutput OUT = EPI == EPI_RESID ? ROWS_SLICES : EPI == EPI_LM ? ROWS_VOCAB
+                          : EPI == EPI_SWIGLU ? ROWS_GATED : ROWS_STORED;
   const RowTiling t = row_tiling(a.n_tiles, a.K / 32, rows, a.max_parts, SPLIT, OUT);
   if (t.cut) {
     if (t.nt == 6) return launch_gemm_cut<2, 6, 4, EPI, SPLIT>(a, rows, t.ks, s);

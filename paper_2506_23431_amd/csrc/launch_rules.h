@@ -108,8 +108,9 @@ inline bool vocab_shares_row_tiles(int n_tiles, int KT, int rows) {
 // ---------------------------------------------------------------------------
 // Projections of more than 128 rows: kernel, tile and K slices of a launch.
 // ---------------------------------------------------------------------------
-// What a launch writes: K slices that the next norm kernel adds, activations or cache entries, winners (and logits).
-enum RowOutput { ROWS_SLICES = 0, ROWS_STORED = 1, ROWS_VOCAB = 2 };
+// What a launch writes: K slices that the next norm kernel adds, activations or cache entries (of gate and up tiles one
+// for two columns), winners (and logits).
+enum RowOutput { ROWS_SLICES = 0, ROWS_STORED = 1, ROWS_VOCAB = 2, ROWS_GATED = 3 };
 
 // cut: the waves of a block cut K (k_gemm_s), else they share row tiles (k_gemm_t); row and column tiles of a block (cut) or
 // of a wave; K slices over blocks.
@@ -117,51 +118,54 @@ struct RowTiling { bool cut; int rt, nt, ks; };
 
 // A tiling's time in us is the sum of c[.] times: 1; rounds of blocks as many as are resident at once (`resident` per
 // compute unit, without / with low parts); those, and rounds of 256 blocks, times the k-tiles of a block; MB of weights and
-// MB of activations that reach the L2 caches from beyond; million results written (slices, activations, vocabulary).
+// MB of activations that reach the L2 caches from beyond; million results written (slices, activations, vocabulary); GFLOP
+// issued beyond 60, where launches run at the power limit and tiles differ in the operands they move per multiply.
 // A column group's blocks sit on one XCD if the blocks of a row group are a multiple of 8, else on up to 8 of them, and
 // every one fetches the weights; beyond 4 MB of weights per XCD they come again for every row group that is not in flight
 // together.  Activations reach as many XCDs as a row group has column groups, at most 8.
-// Coefficients: fit to 25000 launches (129-4096 rows, widths 256-4096, K 256-12288, N 256-50304, weights cycling through
-// 1.3 GB).  Chosen against the fastest of all candidates: 1.7 % slower on average, 20 % for one launch in a hundred.  The
-// estimate it replaces had no term for the fetches: 2048 rows, K 3072, N 768 in slices took 40.7 us where 4 x 3 tiles take
-// 30; 720 rows, K 11008, N 4096 329 against 123; 256 rows, K 4096, 50304 words 582 against 187.
+// Coefficients with low parts: fit to 12000 launches inside context passes and decode steps (10 models of width 256-4096,
+// 129-4096 rows, vocabularies of 1000-100000 words, every tiling in every place) and, with less weight, to 20000 by
+// themselves whose weights cycle through 1.3 GB; without: to 25000 of the latter.  Chosen against the fastest of all
+// candidates in the passes: 1.8 % slower on average, 1.0 % by total time.  An estimate fitted to 15 shapes, without terms
+// for the fetches, was 12.6 and 23 % off: 2048 rows, K 3072, N 768 in slices took 40.7 us where 4 x 3 tiles take 30; 720
+// rows, K 11008, N 4096 329 against 123; 256 rows, K 4096, 50304 words 582 against 187.
 struct RowCost {
   bool cut;
   int rt, nt, resident[2];
-  float c[2][9];
+  float c[2][10];
 };
 inline const RowCost *row_costs(int *n) {
   static const RowCost costs[] = {
       {true, 2, 2, {5, 4},
-       {{2.03, 0, 0, 0.0351, 0.136, 0.0293, 0.493, 0.723, 0},
-        {2.3, 0, 0, 0.0581, 0.0417, 0.0382, 0.158, 0.576, 1.64}}},
+       {{2.03, 0, 0, 0.0351, 0.136, 0.0293, 0.493, 0.723, 0, 0},
+        {2.81, 0, 0, 0.0512, 0.0527, 0.0493, 0.36, 1.26, 0.537, 0.11}}},
       {true, 2, 4, {1, 1},
-       {{1.97, 0.318, 0.0558, 0, 0.0758, 0.0335, 0.999, 1.36, 0},
-        {1.7, 0.662, 0.0772, 0, 0.0757, 0.0618, 0.258, 0.694, 2.2}}},
+       {{1.97, 0.318, 0.0558, 0, 0.0758, 0.0335, 0.999, 1.36, 0, 0},
+        {2.67, 0.258, 0.0732, 0, 0.0688, 0.0658, 1.02, 2.08, 0.876, 0}}},
       {true, 2, 6, {2, 2},
-       {{1.97, 0.807, 0.00982, 0.0612, 0.121, 0.0584, 0.243, 1.56, 0},
-        {2.58, 0.423, 0.00987, 0.0929, 0.0839, 0.0791, 0, 1.4, 1.35}}},
+       {{1.97, 0.807, 0.00982, 0.0612, 0.121, 0.0584, 0.243, 1.56, 0, 0},
+        {3.41, 0.297, 0.00987, 0.0787, 0.0859, 0.0829, 0.252, 1.6, 0.609, 0}}},
       {false, 4, 1, {4, 3},
-       {{2.19, 0, 0.182, 0.106, 0.0682, 0, 0.836, 1.31, 0},
-        {2.65, 0, 0.145, 0.162, 0.0467, 0.0225, 0.993, 1.56, 1.12}}},
+       {{2.19, 0, 0.182, 0.106, 0.0682, 0, 0.836, 1.31, 0, 0},
+        {3.12, 0, 0.145, 0.147, 0.0388, 0.0161, 1.05, 1.49, 0.674, 0.13}}},
       {false, 4, 2, {2, 2},
-       {{2.34, 0.573, 0.249, 0.119, 0.0837, 0.012, 0.663, 1.11, 0},
-        {3.09, 0.264, 0.172, 0.235, 0.0586, 0.0292, 0.81, 1.39, 1.18}}},
+       {{2.34, 0.573, 0.249, 0.119, 0.0837, 0.012, 0.663, 1.11, 0, 0},
+        {2.91, 0.759, 0.182, 0.194, 0.0533, 0.033, 0.77, 1.44, 0.738, 0.109}}},
       {false, 4, 3, {2, 1},
-       {{1.81, 2.23, 0.203, 0.218, 0.0892, 0.0452, 0.459, 1.16, 0},
-        {2.46, 2.58, 0.478, 0, 0.054, 0.0518, 0.298, 1.32, 1.28}}},
+       {{1.81, 2.23, 0.203, 0.218, 0.0892, 0.0452, 0.459, 1.16, 0, 0},
+        {1.79, 3.06, 0.445, 0, 0.0484, 0.0551, 0.45, 1.38, 0.682, 0.0889}}},
       {false, 4, 4, {1, 1},
-       {{4.22, 0.797, 0.498, 0, 0.0779, 0.0553, 0.374, 1.25, 0},
-        {2.86, 3.46, 0.587, 0, 0.057, 0.0552, 0.295, 1.28, 1.34}}},
+       {{4.22, 0.797, 0.498, 0, 0.0779, 0.0553, 0.374, 1.25, 0, 0},
+        {2.68, 2.6, 0.572, 0, 0.0431, 0.0422, 0.609, 1.53, 1.1, 0.0739}}},
       {false, 8, 2, {1, 1},
-       {{3.78, 1.45, 0.424, 0, 0.0637, 0.024, 0.437, 1.38, 0},
-        {3.16, 4.22, 0.596, 0, 0.0495, 0.0352, 0.276, 1.28, 1.02}}},
+       {{3.78, 1.45, 0.424, 0, 0.0637, 0.024, 0.437, 1.38, 0, 0},
+        {2.15, 4.36, 0.577, 0, 0.0232, 0.0236, 0.564, 1.54, 0.725, 0.0795}}},
       {false, 8, 3, {1, 1},
-       {{1.95, 5.22, 0.51, 0, 0.052, 0.0412, 0.285, 1.54, 0},
-        {0, 10.2, 0.778, 0, 0.0439, 0.0527, 0.0741, 1.42, 0.886}}},
+       {{1.95, 5.22, 0.51, 0, 0.052, 0.0412, 0.285, 1.54, 0, 0},
+        {0.954, 7.65, 0.771, 0, 0.0189, 0.0353, 0.384, 1.63, 0.709, 0.0803}}},
       {false, 8, 4, {1, 1},
-       {{1.3, 7.83, 0.598, 0, 0.0619, 0.0436, 0.336, 1.66, 0},
-        {2.97, 9.5, 1.02, 0, 0.039, 0.0754, 0.0751, 1.53, 0.999}}}};
+       {{1.3, 7.83, 0.598, 0, 0.0619, 0.0436, 0.336, 1.66, 0, 0},
+        {2.64, 7.52, 1.02, 0, 0.0117, 0.0368, 0.448, 1.74, 0.863, 0.0729}}}};
   *n = (int)(sizeof(costs) / sizeof(costs[0]));
   return costs;
 }
@@ -175,10 +179,11 @@ inline double row_tiling_us(const RowCost &t, int n_tiles, int KT, int rows, int
   const double again = std::max(1.0, gz / together) * std::min((double)xcds, together);
   const double fetches = w_mb * xcds / 8 <= 4.0 ? std::min(xcds, gz) : std::min((double)gz, again);
   const double act_mb = (double)rows * KT * 64e-6 * (split ? 2 : 1) * std::min(8, gx);
-  const double rounds = std::ceil(blocks / window), written = rows * (n_tiles * 16e-6);
+  const double rounds = std::ceil(blocks / window), written = rows * (n_tiles * 16e-6) * (out == ROWS_GATED ? 0.5 : 1.0);
+  const double power = std::max(0.0, rows * (n_tiles * 16.0) * KT * (split ? 128e-9 : 64e-9) - 60);
   const float *c = t.c[split];
   return c[0] + rounds * (c[1] + c[2] * kt) + std::ceil(blocks / 256) * kt * c[3] + c[4] * w_mb * fetches + c[5] * act_mb +
-         c[6 + out] * written * (out == ROWS_SLICES ? ks : 1);
+         c[out == ROWS_GATED ? 7 : 6 + out] * written * (out == ROWS_SLICES ? ks : 1) + c[9] * power;
 }
 
 inline RowTiling row_tiling(int n_tiles, int KT, int rows, int max_slices, bool split, RowOutput out) {

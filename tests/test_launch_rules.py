@@ -140,7 +140,7 @@ def test_target_groups_are_the_cheapest_partition(rules):
         assert abs(_cost(rows, got, pass_us, row_us) - best) < 1e-6 * best
 
 
-SLICES, STORED, VOCAB = 0, 1, 2
+SLICES, STORED, VOCAB, GATED = 0, 1, 2, 3
 # column tiles, k-tiles, rows, low parts, output; the candidates within 10 % of the fastest: (waves cut K, row tiles, column
 # tiles, K slices): us
 TILINGS = [
@@ -161,6 +161,17 @@ TILINGS = [
     (3144, 24, 192, True, VOCAB, {(False, 4, 1, 1): 45.2, (False, 4, 2, 1): 47.5, (False, 4, 3, 1): 49.4, (False, 8, 4, 1): 49.4}),
     (3144, 128, 256, True, VOCAB, {(False, 8, 4, 1): 186.8}),
     (3144, 24, 400, True, VOCAB, {(False, 4, 1, 1): 108.3, (False, 4, 2, 1): 109.5, (False, 8, 4, 1): 110.7, (False, 8, 2, 1): 116.3}),
+    # inside context passes and decode steps
+    (48, 24, 256, True, SLICES, {(True, 2, 2, 2): 4.8, (True, 2, 2, 1): 5.1, (True, 2, 4, 2): 5.1}),
+    (48, 96, 2048, True, SLICES, {(False, 4, 3, 4): 25.5, (False, 4, 2, 2): 25.9, (False, 8, 2, 4): 26.9, (False, 4, 4, 4): 27.1}),
+    (96, 192, 1280, True, SLICES, {(False, 4, 4, 4): 44.9, (False, 8, 2, 4): 46.2}),
+    (128, 256, 400, True, SLICES, {(False, 4, 1, 4): 36.6, (False, 4, 2, 4): 39.1}),
+    (256, 344, 2048, True, SLICES, {(False, 8, 4, 2): 249.4, (False, 4, 4, 1): 261.9}),
+    (344, 32, 2048, True, GATED, {(False, 8, 3, 1): 46.0}),
+    (512, 64, 900, True, STORED, {(False, 4, 2, 1): 58.7, (False, 4, 4, 1): 61.7, (False, 8, 2, 1): 62.0}),
+    (384, 64, 4096, True, STORED, {(False, 8, 3, 1): 166.8, (False, 4, 2, 1): 168.4, (False, 4, 4, 1): 176.4, (False, 8, 2, 1): 178.8}),
+    (3141, 24, 192, True, VOCAB, {(False, 4, 1, 1): 40.9, (False, 8, 4, 1): 44.5}),
+    (1500, 32, 384, True, VOCAB, {(False, 8, 3, 1): 42.6}), (3141, 128, 256, True, VOCAB, {(False, 8, 4, 1): 162.1}),
 ]
 
 
@@ -175,7 +186,7 @@ def test_row_tiling_at_its_limits(rules):
     out = (C.c_int * 4)()
     known = {(1, 2, 2), (1, 2, 4), (1, 2, 6), (0, 4, 1), (0, 4, 2), (0, 4, 3), (0, 4, 4), (0, 8, 2), (0, 8, 3), (0, 8, 4)}
     for n_tiles, kt, rows, slices, split, kind in itertools.product((1, 6, 161, 8000), (1, 7, 8, 15, 16, 512), (129, 4096, 100000), (1, 2, 4),
-                                                                    (0, 1), (0, 1, 2)):
+                                                                    (0, 1), (0, 1, 2, 3)):
         rules.tiling(n_tiles, kt, rows, slices, split, kind, out)
         assert tuple(out[:3]) in known
         assert out[3] in ((1, 2, 4) if kind == SLICES else (1,)) and out[3] <= slices and (out[3] == 1 or kt // out[3] >= 8)
