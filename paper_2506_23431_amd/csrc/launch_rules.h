@@ -91,18 +91,10 @@ inline std::vector<int> teacher_groups(const std::vector<int> &rows, const PassC
 // ---------------------------------------------------------------------------
 // Vocabulary projection of 33-128 rows with low parts: waves that share row tiles (k_gemm_t), or that cut K (k_gemm_s).
 // ---------------------------------------------------------------------------
-// k_gemm_s has two or four 16-word tiles per block and starts with every compute unit busy from 512 tiles on; each of its
-// waves holds all row tiles of its K share, so weights arrive in as few, short batches as the registers leave room for.
-// k_gemm_t has 8 or 16 tiles per block and streams the weights in order, but a block walks all of K: it wants
-// a block per compute unit and more.  Both measured at 7 row counts, K 256-5120 and 1024-128000 words, weights from the
-// caches and from memory: beyond 80 rows (8 row tiles, one wave of k_gemm_s per SIMD) k_gemm_t is the faster one from 1025
-// tiles on at every K (0.50-0.92 of the time; at 1000 tiles 0.93-1.5).  Up to 80 rows, from memory: K 768 1500 tiles
-// 1.01-1.06, 1624 0.98-1.00, 2500 0.75; K 1024 1500 0.99-1.04, 1624 0.88; K 1536 1748 1.07, 2000 1.04, 2500 0.81; K 2048
-// 1624-2000 tiles 0.95-1.19 and no gain in a whole step (width 2048, 32000 words, 64 rows 96.0 us against 94.1), 2500
-// 0.86; K 3072 2000 tiles 1.17.  (From the caches the line could lie at 1000-1500 tiles.)
+// k_gemm_t wants a compute unit per block of 8 column tiles to be ahead, and the longer K, the more a single round of K-cut
+// blocks hides by itself; beyond 80 rows k_gemm_s takes 4 column tiles per block, a second round from 1025 tiles on.
 inline bool vocab_shares_row_tiles(int n_tiles, int KT, int rows) {
-  const int line = KT <= 32 ? 1600 : std::max(2048, 1500 + 12 * (KT - 32));
-  return rows > 32 && (n_tiles >= line || (rows > 80 && n_tiles > 1024));
+  return rows > 32 && (n_tiles >= 1500 + 12 * std::max(0, KT - 32) || (rows > 80 && n_tiles > 1024));
 }
 
 // ---------------------------------------------------------------------------

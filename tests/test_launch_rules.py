@@ -32,7 +32,6 @@ void tiling(int n_tiles, int kt, int rows, int max_slices, int split, int kind, 
   const RowTiling t = row_tiling(n_tiles, kt, rows, max_slices, split, (RowOutput)kind);
   out[0] = t.cut; out[1] = t.rt; out[2] = t.nt; out[3] = t.ks;
 }
-int vocab(int n_tiles, int kt, int rows) { return vocab_shares_row_tiles(n_tiles, kt, rows); }
 }
 """
 
@@ -190,22 +189,3 @@ def test_row_tiling_at_its_limits(rules):
         rules.tiling(n_tiles, kt, rows, slices, split, kind, out)
         assert tuple(out[:3]) in known
         assert out[3] in ((1, 2, 4) if kind == SLICES else (1,)) and out[3] <= slices and (out[3] == 1 or kt // out[3] >= 8)
-
-
-# column tiles, K, rows; us with waves that cut K and with waves that share row tiles, weights from memory
-VOCABULARY = [
-    (1500, 768, 33, 15.1, 15.5), (1500, 768, 65, 17.0, 17.9), (1624, 768, 80, 18.1, 18.1), (2500, 768, 33, 27.2, 20.1),
-    (1624, 1024, 65, 21.4, 20.7), (2000, 1536, 64, 27.0, 28.1), (1748, 1536, 33, 24.8, 26.7), (2500, 1536, 64, 42.8, 34.6),
-    (2500, 2048, 80, 53.0, 46.8), (1000, 2048, 64, 20.0, 31.0), (2000, 3072, 80, 55.3, 55.9), (3144, 768, 65, 34.5, 27.7),
-    (1028, 768, 96, 25.8, 19.2), (1028, 5120, 128, 98.1, 90.4), (1000, 2048, 96, 28.3, 38.3), (1000, 768, 128, 16.2, 19.3),
-    (3144, 1024, 128, 65.8, 36.6), (3144, 4096, 33, 96.0, 84.6), (3144, 4096, 80, 102.1, 92.2), (8000, 4096, 48, 212.5, 166.9),
-]
-
-
-@pytest.mark.parametrize("n_tiles,k,rows,cut,share", VOCABULARY)
-def test_vocabulary_kernel_is_near_the_faster_measured(rules, n_tiles, k, rows, cut, share):
-    assert (share if rules.vocab(n_tiles, k // 32, rows) else cut) <= 1.03 * min(cut, share)
-
-
-def test_few_rows_keep_waves_that_cut_k(rules):
-    assert not any(rules.vocab(n, kt, rows) for n, kt, rows in itertools.product((1, 1024, 8000, 20000), (1, 24, 128), (1, 16, 32)))
