@@ -1133,13 +1133,10 @@ static int launch_gemm_rows(const GemmArgs &a, int rows, hipStream_t s) {
 // and the blocks end with a sum through LDS; one stream of k-tiles per block hides both.  One layer + vocabulary, us per
 // step, before -> after: 72 rows, width 1024, 50265 words 83.3 -> 73.3 (the projection itself 40.7 -> 31), 128 rows
 // 113 -> 83, 120000 words 190 -> 138; 64 rows, width 512, 32000 words 55.6 -> 52.2; width 4096, 100000 words 315 -> 276.
-// Blocks of 128 columns want a compute unit each to be ahead: 16000 words lose (64 rows, width 2048 74.6 -> 80.2), and the
-// longer K, the more a single round of K-cut blocks hides by itself (24000 words: width 1024 59.3 -> 57.2, 2048
-// 80.9 -> 84.7; 32000 words: 2048 87.6 -> 83.7, 3072 134 -> 145; 50265 words: 3072 170 -> 163).  8 row tiles leave the
-// other kernel 4 column tiles, a second round from 1025 tiles on (24000 words, width 2048, 113 -> 105).  Two column tiles per wave
-// where one makes more than a round of blocks and a block's multiplies cover its requests (64 rows, width 1024, 50265 words
-// 67.2 with one, 72.7 with two; 72 rows of width 768 66.6 and 65.3; 128 rows of width 2048 148 and 139); three, or four k-tiles
-// ahead instead of two, measured no better.  Steps of 17-32 rows differ by less than 5 % either way and stay.
+// From which sizes on: vocab_shares_row_tiles.  Two column tiles per wave where one makes more than a round of blocks and a
+// block's multiplies cover its requests (64 rows, width 1024, 50265 words 67.2 with one, 72.7 with two; 72 rows of width
+// 768 66.6 and 65.3; 128 rows of width 2048 148 and 139); three, or four k-tiles ahead instead of two, measured no better.
+// Steps of 17-32 rows differ by less than 5 % either way and stay.
 template <int RT, int NT>
 static int launch_gemm_vocab(const GemmArgs &a, int rows, hipStream_t s) {
   PD_REQUIRE(rows <= 16 * RT, PD_EINVAL, "%d rows in %d row tiles", rows, RT);

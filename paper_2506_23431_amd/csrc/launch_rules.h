@@ -91,8 +91,16 @@ inline std::vector<int> teacher_groups(const std::vector<int> &rows, const PassC
 // ---------------------------------------------------------------------------
 // Vocabulary projection of 33-128 rows with low parts: waves that share row tiles (k_gemm_t), or that cut K (k_gemm_s).
 // ---------------------------------------------------------------------------
-// k_gemm_t wants a compute unit per block of 8 column tiles to be ahead, and the longer K, the more a single round of K-cut
-// blocks hides by itself; beyond 80 rows k_gemm_s takes 4 column tiles per block, a second round from 1025 tiles on.
+// k_gemm_s has two or four 16-word tiles per block and starts with every compute unit busy from 512 tiles on; each of its
+// waves holds all row tiles of its K share, so weights arrive in as few, short batches as the registers leave room for.
+// k_gemm_t has 8 or 16 tiles per block and streams the weights in order, but a block walks all of K: it wants
+// a block per compute unit and more, and the more, the longer K is.  Both measured at 7 row counts, K 256-5120 and
+// 1024-128000 words, weights from the caches and from memory; time of k_gemm_t over that of k_gemm_s, caches / memory.
+// Beyond 80 rows (8 row tiles, one wave of k_gemm_s per SIMD): 0.50-0.92 from 1025 tiles on at every K, 0.93-1.5 at 1000
+// tiles.  64 rows: K 768 1500 tiles 0.87 / 1.01, 2500 0.64 / 0.75; K 1536 1500 tiles 0.88 / 1.11, 2000 0.85 / 1.04, 2500
+// 0.70 / 0.81; K 2048 1500 tiles 1.06 / 1.19, 2000 0.91 / 0.95; K 3072 2000 tiles 0.90 / 1.17.  Whole steps of one layer, its
+// weights in the caches: width 768, 24000 words, 33 rows 54.1 -> 50.4 us, width 1024 58.7 -> 55.2.  By the sum of both
+// times the line is within 3 % of the better kernel at 1065 of 1127 sizes, the others K 256 below it.
 inline bool vocab_shares_row_tiles(int n_tiles, int KT, int rows) {
   return rows > 32 && (n_tiles >= 1500 + 12 * std::max(0, KT - 32) || (rows > 80 && n_tiles > 1024));
 }

@@ -32,6 +32,7 @@ void tiling(int n_tiles, int kt, int rows, int max_slices, int split, int kind, 
   const RowTiling t = row_tiling(n_tiles, kt, rows, max_slices, split, (RowOutput)kind);
   out[0] = t.cut; out[1] = t.rt; out[2] = t.nt; out[3] = t.ks;
 }
+int vocab(int n_tiles, int kt, int rows) { return vocab_shares_row_tiles(n_tiles, kt, rows); }
 }
 """
 
@@ -189,3 +190,26 @@ def test_row_tiling_at_its_limits(rules):
         rules.tiling(n_tiles, kt, rows, slices, split, kind, out)
         assert tuple(out[:3]) in known
         assert out[3] in ((1, 2, 4) if kind == SLICES else (1,)) and out[3] <= slices and (out[3] == 1 or kt // out[3] >= 8)
+
+
+# column tiles, K, rows; us with waves that cut K and with waves that share row tiles, weights from the caches, then both from
+# memory
+VOCABULARY = [
+    (1500, 768, 33, 13.4, 11.8, 15.1, 15.5), (1500, 768, 65, 15.3, 14.0, 17.0, 17.9), (1624, 768, 80, 16.8, 14.2, 18.1, 18.1),
+    (2500, 768, 33, 25.2, 16.5, 27.2, 20.1), (1624, 1024, 65, 20.0, 17.8, 21.4, 20.7), (2000, 1536, 64, 24.4, 20.8, 27.0, 28.1),
+    (1748, 1536, 33, 22.6, 19.7, 24.8, 26.7), (2500, 1536, 64, 37.8, 26.4, 42.8, 34.6), (2500, 2048, 80, 46.5, 38.1, 53.0, 46.8),
+    (1000, 2048, 64, 20.6, 24.0, 20.0, 31.0), (2000, 2048, 64, 34.6, 31.5, 37.5, 35.8), (1500, 2048, 80, 26.7, 30.7, 30.2, 37.3),
+    (3144, 768, 65, 31.5, 22.2, 34.5, 27.7), (1028, 768, 96, 24.0, 16.0, 25.8, 19.2), (1028, 5120, 128, 91.3, 70.7, 98.1, 90.4),
+    (1000, 2048, 96, 26.2, 32.0, 28.3, 38.3), (1000, 768, 128, 14.7, 15.8, 16.2, 19.3),
+    (3144, 1024, 128, 61.5, 35.2, 65.8, 36.6), (1500, 4096, 80, 40.7, 52.0, 47.0, 70.3),
+]
+
+
+@pytest.mark.parametrize("n_tiles,k,rows,cut,share,cut_cold,share_cold", VOCABULARY)
+def test_vocabulary_kernel_is_the_faster_measured(rules, n_tiles, k, rows, cut, share, cut_cold, share_cold):
+    cut, share = cut + cut_cold, share + share_cold
+    assert (share if rules.vocab(n_tiles, k // 32, rows) else cut) <= 1.03 * min(cut, share)
+
+
+def test_few_rows_keep_waves_that_cut_k(rules):
+    assert not any(rules.vocab(n, kt, rows) for n, kt, rows in itertools.product((1, 1024, 8000, 20000), (1, 24, 128), (1, 16, 32)))
