@@ -26,9 +26,9 @@ struct AttnShape { int splits, waves; };
 // step, 8 waves / splits: head size 64 from the caches 48 blocks 25.3 / 25.4, 72 blocks 26.9 / 25.5; 16 units from memory
 // 40 blocks 33.7 / 32.1; head size 128, 8 units 32 blocks 36.6 / 32.6, 16 units 64 blocks 56.5 / 44.0).  The choice is
 // within 1.1 us of the best of the three at all 900 points, 0.04 on average; with one pace of 0.55 us per block for every
-// head size it was up to 12.5 off, 1.06 on average.  Fewer blocks than waves: 4 waves (5 blocks 0.3-1.1 us better).  More units than
-// compute units: 4 waves do as well or better (288 units x 384 keys, 12 steps 4.46 against 4.51 ms); beyond 96 blocks a
-// unit's keys want more than one compute unit's share (128 units x 4096-6000 keys, 40 steps: 52.9 against 51.7 ms).
+// head size it was up to 12.5 off, 1.06 on average.  Fewer blocks than waves: 4 waves (5 blocks 0.3-1.1 us better).  More
+// units than compute units: 4 waves do as well or better (288 units x 384 keys, 12 steps 4.46 against 4.51 ms); beyond 96
+// blocks a unit's keys want more than one compute unit's share (128 units x 4096-6000 keys, 40 steps: 52.9 against 51.7 ms).
 // Splits: a work-group per compute unit, every wave streaming several key blocks back to back (16 heads x 8k keys 16.2 us
 // with 256 work-groups, 17.2 with 512 or 768, 18.7 with 320; 4 x 32 heads x 4k keys 256 are 4 us per launch faster than
 // 768).  Context passes and pair layers: one work-group up to 32 blocks, then splits.
@@ -55,12 +55,16 @@ inline AttnShape attn_shape(int head_dim, int units, int nblk, int cap, bool dec
 // ---------------------------------------------------------------------------
 struct PassCost { double pass_us, row_us; };
 
-// What a pass costs whatever its rows (9 launches per layer and a few more at 4 us, the weights once at 4.5 TB/s) and per
-// row (multiplies at 0.6 PFLOP/s).  weights: elements of all matrices; parts: 2 with low parts, else 1.  Measured, per
-// call and row: 2 layers of width 2048, 32000 words 227 us at 8 rows, +0.74 us per row (estimate 158 + 1.1); 6 of
-// width 768, 2000 words 269 us, +0.37 (232 + 0.29); 4 of width 1024 230 us, +0.38 (190 + 0.39).
-inline PassCost teacher_pass_cost(int n_layer, double weights, int parts) {
-  return PassCost{4.0 * (9 * n_layer + 5) + 2.0 * weights / 4.5e6, 2.0 * parts * weights / 0.6e9};
+// What a pass costs whatever its rows: 9 launches per layer and a few more at 4.3 us, the weights once at 2 TB/s (as the
+// launches of few row tiles read them).  And per row: what norms, attention and epilogues take in a layer, its multiplies,
+// the logits stored and read again for the loss.  layer, head: elements of a layer's and the vocabulary's matrices; parts:
+// 2 with low parts, else 1.  Measured beyond 128 rows, per call (some 40 us of it outside the pass) and row: 6 layers of
+// width 768, 2000 words 319 us, +0.46 per row (estimate 298 + 0.31), 50265 words 326, +0.71 (335 + 0.60); 4 of width 1024,
+// 8000 words 306, +0.31 (235 + 0.32); 2 of 2048, 32000 words 322, +0.61 (265 + 0.59); 4 of 2048 / 5504 gated, 8000 words 459,
+// +0.87 (395 + 0.86).
+inline PassCost teacher_pass_cost(int n_layer, double layer, double head, int vocab, int parts) {
+  return PassCost{4.3 * (9 * n_layer + 5) + (n_layer * layer + head) / 1e6,
+                  n_layer * (0.025 + 1.75e-9 * parts * layer) + 6e-6 * vocab};
 }
 
 // Sizes of the groups: the consecutive partition with the least estimated time.  fits(rows per request, requests) says

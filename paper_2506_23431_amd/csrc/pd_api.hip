@@ -808,8 +808,8 @@ extern "C" int pd_teacher_forced(pd_ctx *c, const int32_t *target, int max_len, 
   int rc;
   // requests share a pass, their rows padded to the longest of the group, where that costs less than passes of their own
   const double dd = (double)g.d_model * g.d_model, ff = (double)g.d_model * g.d_ff;
-  const double weights = g.n_layer * ((c->arch == 1 ? 6 : 4) * dd + (g.ffn_kind == 1 ? 3 : 2) * ff) + (double)g.vocab * g.d_model;
-  const std::vector<int> groups = teacher_groups(rows, teacher_pass_cost(g.n_layer, weights, c->opt_split ? 2 : 1),
+  const double layer = (c->arch == 1 ? 6 : 4) * dd + (g.ffn_kind == 1 ? 3 : 2) * ff, head = (double)g.vocab * g.d_model;
+  const std::vector<int> groups = teacher_groups(rows, teacher_pass_cost(g.n_layer, layer, head, g.vocab, c->opt_split ? 2 : 1),
                                                  [&](int A, int nreq) { return A <= 65535 && fits_one_pass(c, A, nreq); });
   int b = 0;
   for (const int nreq : groups) {

@@ -24,8 +24,8 @@ int groups(const int *rows, int n, double pass_us, double row_us, int row_cap, i
   for (size_t i = 0; i < g.size(); ++i) out[i] = g[i];
   return (int)g.size();
 }
-void pass_cost(int n_layer, double weights, int parts, double *out) {
-  const PassCost c = teacher_pass_cost(n_layer, weights, parts);
+void pass_cost(int n_layer, double layer, double head, int vocab, int parts, double *out) {
+  const PassCost c = teacher_pass_cost(n_layer, layer, head, vocab, parts);
   out[0] = c.pass_us; out[1] = c.row_us;
 }
 void tiling(int n_tiles, int kt, int rows, int max_slices, int split, int kind, int *out) {
@@ -99,15 +99,18 @@ def _cost(rows, groups, pass_us, row_us):
 
 
 def test_targets_share_a_pass_only_where_padding_costs_less(rules):
-    wide = (158.0, 1.1)              # 2 layers of width 2048, 32000 words
+    wide = (265.0, 0.59)             # 2 layers of width 2048, 32000 words
     assert _groups(rules, [500] + [20] * 7, *wide) == [1, 7]
     assert _groups(rules, [20] * 7 + [500], *wide) == [7, 1]
     assert _groups(rules, [200, 190, 180], *wide) == [3]
     narrow = (232.0, 0.02)
     assert _groups(rules, [500] + [20] * 7, *narrow) == [8]
     cost = (C.c_double * 2)()
-    rules.pass_cost(2, C.c_double(166e6), 2, cost)
-    assert abs(cost[0] - wide[0]) < 12 and abs(cost[1] - wide[1]) < 0.02
+    rules.pass_cost(2, C.c_double(12 * 2048 ** 2), C.c_double(32000 * 2048), 32000, 2, cost)
+    assert abs(cost[0] - wide[0]) < 1 and abs(cost[1] - wide[1]) < 0.01
+    # 2 layers of width 2048, 8000 words, targets of 40 to 320 rows: one pass 1440 us, padded to 2560 rows; three passes 1640
+    rules.pass_cost(2, C.c_double(12 * 2048 ** 2), C.c_double(8000 * 2048), 8000, 2, cost)
+    assert len(_groups(rules, list(range(40, 321, 40)), cost[0], cost[1])) <= 2
 
 
 def test_target_groups_are_the_cheapest_partition(rules):
