@@ -19,6 +19,7 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <type_traits>
 
 struct AttnArgs {
   const f16_t *q, *q_lo;    // [rows][d] fp16 high / low parts (q_lo NULL: high part only)
@@ -65,61 +66,57 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void pin(u32x4 &u) { asm volatile("" : "+v"(u)); }
 
 template <int HD, bool SPLIT, bool PAIR, bool BIAS = false, bool STREAM = false, int NW = 4>
-__global__ __launch_bounds__(64 * NW, PAIR ? 1 : NW == 4 ? 3 : NW / 4) void k_attn_mfma(AttnArgs a) {
+__global__ __launch_bounds__(64 * NW, PAIR ? 1 : NW == 4 ? 3 : NW / 4)
+void k_attn_mfma(const f16_t *hot_q, const int4 *hot_qinfo, const f16_t *hot_kc, const int32_t *hot_kv_len, uint32_t hot_q_lo,
+                 uint32_t hot_v, int hot_kv_cap, uint32_t hot_ha, uint32_t hot_nb, int hot_req0, AttnArgs a) {
   constexpr int NC = HD / 32, NHB = HD / 16, PSTR = HD + 2;   // partial: m, l, O[HD] per query
   __shared__ float sm_m[NW][16], sm_l[NW][16];
   __shared__ float sm_bias[BIAS ? BIAS_MAX : 1];
   __shared__ floatx4 sm_o[NW][HD / 16][64];
   __shared__ uint4 sm_q[(SPLIT ? 2 : 1) * NC][64];
+  const int H = hot_ha & 0xffff, A = hot_ha >> 16, nqg = (A + 15) >> 4, d = H * HD;
+  const int nsplit = hot_nb >> 20, nblk_static = hot_nb & 0xfffff;
   int split = blockIdx.x, h = blockIdx.y, z = blockIdx.z;
-  int reqi = z / a.nqg, qg = z % a.nqg, req = a.req0 + reqi;
+  int reqi = z, qg = 0;
+  if (nqg > 1) { reqi = z / nqg; qg = z - reqi * nqg; }
+  const int req = hot_req0 + reqi;
   int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   int n = lane & 15, g = lane >> 4;
 
-  // Everything the block needs to know about its queries is requested first (a few lines that sit
-  // in the L2 cache), then the first key/value block; no load below depends on the result of
-  // another, and the wait for the row data does not wait for the key/value block behind it.
+  // The rows and their queries are requested first (a few lines that sit in the L2 cache), then the first key/value
+  // block, all by arguments that arrive in registers (the first 14 words; read from memory they cost 0.25-0.35 us before
+  // the first request); the wait for the row data does not wait for the key/value block behind it.
   int qa = qg * 16 + n;                       // query index inside the request
-  bool in_req = qa < a.A;
-  int r = reqi * a.A + (in_req ? qa : 0);     // row (clamped: loads stay in bounds)
-  int4 qi = a.rt.qinfo[r];                    // {flags, sub, lim, req}
-  int n_keys = a.kv_override >= 0 ? a.kv_override : a.kv_len[req];
-  int q_pos = 0;
-  float bias_pre[2] = {0.f, 0.f};
-  if (BIAS) {
-    q_pos = a.rt.pos[r] - a.pos0;
-    bias_pre[0] = a.bias[(size_t)h * a.bias_len + min((int)threadIdx.x, a.bias_len - 1)];
-    bias_pre[1] = a.bias[(size_t)h * a.bias_len + min((int)threadIdx.x + 64 * NW, a.bias_len - 1)];
-  }
+  bool in_req = qa < A;
+  int r = reqi * A + (in_req ? qa : 0);     // row (clamped: loads stay in bounds)
+  int4 qi = hot_qinfo[r];                    // {flags, sub, lim, req}
+  int n_keys = 0;
+  if (hot_kv_len) n_keys = hot_kv_len[req];   // NULL: the number is an argument
   // Query fragments (high and low parts) go to LDS, in operand order: the waves share them,
   // and keeping them out of the registers leaves room for three waves per SIMD.  Rows without a
   // token keep whatever finite numbers their q slots hold: all their keys are masked below, and
   // their output is never written.
-  const size_t q_off = act_off(r, h * HD + g * 8, a.d);
+  const size_t q_off = act_off(r, h * HD + g * 8, d);
   static_assert(NC <= 4, "one query fragment (and its low part) per wave");
   uint4 qh, qlo;
   {
     const int c = min(wave, NC - 1);
     size_t off = q_off + (size_t)c * 512;     // the next 32 dims are the next fragment
-    qh = *(const uint4 *)(a.q + off);
-    if (SPLIT) qlo = *(const uint4 *)(a.q_lo + off);
+    qh = *(const uint4 *)(hot_q + off);
+    if (SPLIT) qlo = *((const uint4 *)(hot_q + off) + hot_q_lo);
   }
 
-  const uint4 *Kp = (const uint4 *)(a.kc + ((size_t)req * a.H + h) * a.kv_cap * HD) + lane;
-  const uint4 *Vp = (const uint4 *)(a.vc + ((size_t)req * a.H + h) * a.kv_cap * HD) + lane;
-  const uint4 *Kl = PAIR ? (const uint4 *)(a.kc_lo + ((size_t)req * a.H + h) * a.kv_cap * HD) + lane : nullptr;
-  const uint4 *Vl = PAIR ? (const uint4 *)(a.vc_lo + ((size_t)req * a.H + h) * a.kv_cap * HD) + lane : nullptr;
-  // subsequence tags of the generated-side slots, 8 keys (16 bytes) per lane group
-  const uint16_t *gs = a.gen_sub + (size_t)req * a.gen_stride;
-  const int L8 = a.L & ~7;
+  const uint4 *Kp = (const uint4 *)(hot_kc + ((size_t)req * H + h) * hot_kv_cap * HD) + lane;
+  const uint4 *Vp = Kp + hot_v;
+  const uint4 *Kl = PAIR ? (const uint4 *)(a.kc_lo + ((size_t)req * H + h) * hot_kv_cap * HD) + lane : nullptr;
+  const uint4 *Vl = PAIR ? (const uint4 *)(a.vc_lo + ((size_t)req * H + h) * hot_kv_cap * HD) + lane : nullptr;
   // 32-key blocks are dealt round-robin to the NW*nsplit waves that serve this (request, head):
   // whatever the current key count, no wave gets more than one block above the average
-  const int stride = NW * a.nsplit;
+  const int stride = NW * nsplit;
   int kb = split * NW + wave;
   Frag kf[2][NC], vf[NHB];
   Frag kl[PAIR ? 2 : 1][PAIR ? NC : 1], vl[PAIR ? NHB : 1];
   union { u32x4 u; uint16_t s[8]; } tg, kco;
-  const uint16_t *kcp = BIAS ? a.coord + (size_t)req * a.coord_req_stride : nullptr;
   auto load_k = [&](int kbx) {
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -130,9 +127,6 @@ __global__ __launch_bounds__(64 * NW, PAIR ? 1 : NW == 4 ? 3 : NW / 4) void k_at
       }
   };
   auto load_v = [&](int kbx) {
-    // tags of the lane's 8 keys (clamped: context blocks read entry 0 and never use it)
-    tg.u = *(const u32x4 *)(gs + min(max(kbx * 32 + 8 * g - L8, 0), a.gen_stride - 8));
-    if (BIAS) kco.u = *(const u32x4 *)(kcp + min(max(kbx * 32 + 8 * g - a.coord_off, 0), a.coord_stride - 8));
 #pragma unroll
     for (int i = 0; i < NHB; ++i) {
       vf[i].hv = ld_kv<STREAM>(&Vp[((size_t)kbx * NHB + i) * 64]);
@@ -141,8 +135,27 @@ __global__ __launch_bounds__(64 * NW, PAIR ? 1 : NW == 4 ? 3 : NW / 4) void k_at
   };
   // requested unconditionally (a wave beyond the last block fetches that block and ignores it), so
   // that the wait for the query rows above never has to wait for these
-  load_k(min(kb, a.nblk_static - 1));
-  load_v(min(kb, a.nblk_static - 1));
+  load_k(min(kb, nblk_static - 1));
+  load_v(min(kb, nblk_static - 1));
+  __builtin_amdgcn_sched_barrier(0);          // (arguments that are not in registers yet are waited for behind these requests)
+  // subsequence tags of the generated-side slots, 8 keys (16 bytes) per lane group
+  const uint16_t *gs = a.gen_sub + (size_t)req * a.gen_stride;
+  const int L8 = a.L & ~7;
+  const uint16_t *kcp = BIAS ? a.coord + (size_t)req * a.coord_req_stride : nullptr;
+  // tags of the lane's 8 keys (clamped: context blocks read entry 0 and never use it)
+  auto load_tags = [&](int kbx) {
+    tg.u = *(const u32x4 *)(gs + min(max(kbx * 32 + 8 * g - L8, 0), a.gen_stride - 8));
+    if (BIAS) kco.u = *(const u32x4 *)(kcp + min(max(kbx * 32 + 8 * g - a.coord_off, 0), a.coord_stride - 8));
+  };
+  load_tags(min(kb, nblk_static - 1));
+  if (!hot_kv_len) n_keys = a.kv_override;
+  int q_pos = 0;
+  float bias_pre[2] = {0.f, 0.f};
+  if (BIAS) {
+    q_pos = a.rt.pos[r] - a.pos0;
+    bias_pre[0] = a.bias[(size_t)h * a.bias_len + min((int)threadIdx.x, a.bias_len - 1)];
+    bias_pre[1] = a.bias[(size_t)h * a.bias_len + min((int)threadIdx.x + 64 * NW, a.bias_len - 1)];
+  }
   // (waves beyond the fragment count store a copy of the last fragment: same bytes, same place)
   {
     const int c = min(wave, NC - 1);
@@ -159,12 +172,12 @@ __global__ __launch_bounds__(64 * NW, PAIR ? 1 : NW == 4 ? 3 : NW / 4) void k_at
   int q_sub = qvalid ? qi.y : -1, q_lim = qvalid ? qi.z : 0;
   // keys any query of this group can see
   int reach = qvalid ? (n_keys > a.L && q_sub >= 1 ? n_keys : min(q_lim, n_keys)) : 0;
-  for (int o = 1; o < 16; o <<= 1) reach = max(reach, __shfl_xor(reach, o));
-  const int end = __builtin_amdgcn_readfirstlane(min(a.nblk_static, (reach + 31) >> 5));
+  reach = fold_row(reach, Max());
+  const int end = __builtin_amdgcn_readfirstlane(min(nblk_static, (reach + 31) >> 5));
   // keys below lim_all are visible to every query of the group that has a token (the others are
   // never written, whatever they compute): blocks below it skip the per-key test
   int lim_q = qvalid ? min(q_lim, a.L) : 0x7fffffff;
-  for (int o = 1; o < 16; o <<= 1) lim_q = min(lim_q, __shfl_xor(lim_q, o));
+  lim_q = fold_row(lim_q, Min());
   const int lim_all = __builtin_amdgcn_readfirstlane(lim_q);
 
   float m_run = -INFINITY, l_run = 0.f;
@@ -175,8 +188,11 @@ __global__ __launch_bounds__(64 * NW, PAIR ? 1 : NW == 4 ? 3 : NW / 4) void k_at
   // One block per wave is resident in registers.  The key fragments of the wave's next block are
   // requested as soon as the score products have consumed the current ones, the value fragments
   // (and tags) as soon as the output products have: the loads of block i+1 overlap the softmax
-  // and the output products of block i without a second set of registers.
-  while (kb < end) {
+  // and the output products of block i without a second set of registers.  The wave's last block is a copy of the
+  // loop's body without requests: where a branch decides on a request, the wait for the values counts on its not
+  // having been made, and every block waited for the next one's keys.
+  auto block = [&](auto more_) {
+    constexpr bool more = decltype(more_)::value;
     floatx4 s[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
     // the query fragments are re-read from LDS for every block (the empty asm keeps the compiler
     // from hoisting the reads out of the loop, which would put them back into 32 registers)
@@ -189,8 +205,8 @@ __global__ __launch_bounds__(64 * NW, PAIR ? 1 : NW == 4 ? 3 : NW / 4) void k_at
       s[0] = mfma16h(kf[0][c], qf, s[0]);
       s[1] = mfma16h(kf[1][c], qf, s[1]);
       if (PAIR) {
-        s[0] = mfma16h(kl[0][c], qf, s[0]);
-        s[1] = mfma16h(kl[1][c], qf, s[1]);
+        s[0] = mfma16h(kl[0][PAIR ? c : 0], qf, s[0]);
+        s[1] = mfma16h(kl[PAIR ? 1 : 0][PAIR ? c : 0], qf, s[1]);
       }
       if (SPLIT) {
         qf.u = sm_q[NC + c][ql_lane];
@@ -199,7 +215,6 @@ __global__ __launch_bounds__(64 * NW, PAIR ? 1 : NW == 4 ? 3 : NW / 4) void k_at
       }
     }
     const int kn = kb + stride;
-    const bool more = kn < end;
     if (more) load_k(kn);
     // lane (n, g), tile t, register j  <->  key kb*32 + 8g + 4t + j
     const int key0 = kb * 32 + 8 * g;
@@ -226,8 +241,7 @@ __global__ __launch_bounds__(64 * NW, PAIR ? 1 : NW == 4 ? 3 : NW / 4) void k_at
       }
     }
     float mloc = fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+    mloc = fold32(fold16(mloc, Max()), Max());
     const float m_new = fmaxf(m_run, mloc);
     // while nothing is visible yet the reference is 0 instead of -inf: every exponential below is
     // then exp2(-inf) = 0 and never exp2(NaN)
@@ -256,15 +270,16 @@ __global__ __launch_bounds__(64 * NW, PAIR ? 1 : NW == 4 ? 3 : NW / 4) void k_at
     for (int i = 0; i < NHB; ++i) {
       o_acc[i] = mfma16h(vf[i], pf, o_acc[i]);
       if (PAIR) {
-        o_acc[i] = mfma16h(vl[i], pf, o_acc[i]);
+        o_acc[i] = mfma16h(vl[PAIR ? i : 0], pf, o_acc[i]);
         o_acc[i] = mfma16h(vf[i], pl, o_acc[i]);
       }
     }
-    if (more) load_v(kn);
+    if (more) { load_tags(kn); load_v(kn); }
     kb = kn;
-  }
-  l_run += __shfl_xor(l_run, 16);
-  l_run += __shfl_xor(l_run, 32);
+  };
+  while (kb + stride < end) block(std::true_type());
+  if (kb < end) block(std::false_type());
+  l_run = fold32(fold16(l_run, Add()), Add());
 
   // ---- merge the waves of the block (log-sum-exp) ----
   // every wave stores its accumulators as 16-byte quads (lane order: conflict-free); after the
@@ -285,17 +300,17 @@ __global__ __launch_bounds__(64 * NW, PAIR ? 1 : NW == 4 ? 3 : NW / 4) void k_at
   if (!qvalid) return;                        // lane (n, g) writes for query n only
   // partial of this block: m[16], l[16], then O as [dim / 4][query][4 dims]: a wave's store of one
   // 16-dim block is 1 KiB of consecutive bytes
-  size_t unit = (size_t)z * a.H + h;
-  float *pp = a.part + (unit * a.nsplit + split) * (size_t)(PSTR * 16);
-  if (a.nsplit > 1 && wave == 0 && g == 0) { pp[n] = M; pp[16 + n] = lsum; }
+  size_t unit = (size_t)z * H + h;
+  float *pp = a.part + (unit * nsplit + split) * (size_t)(PSTR * 16);
+  if (nsplit > 1 && wave == 0 && g == 0) { pp[n] = M; pp[16 + n] = lsum; }
   const float inv = 1.f / lsum;
   for (int i = wave; i < NHB; i += NW) {
     floatx4 o = fw[0] * sm_o[0][i][lane];
 #pragma unroll
     for (int w = 1; w < NW; ++w) o += fw[w] * sm_o[w][i][lane];
-    if (a.nsplit == 1) {
+    if (nsplit == 1) {
       float y[4] = {o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv};
-      store4_split(a.out, a.out_lo, act_off(r, h * HD + i * 16 + 4 * g, a.d), y);
+      store4_split(a.out, a.out_lo, act_off(r, h * HD + i * 16 + 4 * g, d), y);
     } else {
       *(floatx4 *)(pp + 32 + ((i * 4 + g) * 16 + n) * 4) = o;
     }
@@ -306,26 +321,29 @@ __global__ __launch_bounds__(64 * NW, PAIR ? 1 : NW == 4 ? 3 : NW / 4) void k_at
 // the splits w, w + 4, ... online (running max, sum and 4 output dims per lane), 8 splits' loads in
 // flight at a time; the four running states are then combined through LDS.
 template <int HD>
-__global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a) {
+__global__ __launch_bounds__(256) void k_attn_merge(const float *part, const int32_t *flags, bf16_t *out, bf16_t *out_lo,
+                                                    uint32_t ha, uint32_t nsplit_nqg) {
   constexpr int PSTR = HD + 2, U = 8;
   __shared__ float sm_M[4][64], sm_L[4][64];
   __shared__ floatx4 sm_O[4][64];
-  int unit = blockIdx.x, i = blockIdx.y, z = unit / a.H, h = unit % a.H;
-  int reqi = z / a.nqg, qg = z % a.nqg;
+  const int H = ha & 0xffff, A = ha >> 16, nsplit = nsplit_nqg & 0xfff, nqg = nsplit_nqg >> 12;
+  int unit = blockIdx.x, i = blockIdx.y, z = unit / H, h = unit - z * H;
+  int reqi = z, qg = 0;
+  if (nqg > 1) { reqi = z / nqg; qg = z - reqi * nqg; }
   int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
-  int qa = qg * 16 + n, r = reqi * a.A + min(qa, a.A - 1);
-  int fl = a.rt.flags[r];
+  int qa = qg * 16 + n, r = reqi * A + min(qa, A - 1);
+  int fl = flags[r];
   const size_t sstr = (size_t)PSTR * 16;
-  const float *pb = a.part + (size_t)unit * a.nsplit * sstr;
+  const float *pb = part + (size_t)unit * nsplit * sstr;
   const int o_off = 32 + ((i * 4 + g) * 16 + n) * 4;
   float M = -INFINITY, l = 0.f;
   floatx4 o = floatx4{0.f, 0.f, 0.f, 0.f};
-  for (int s0 = wave; s0 < a.nsplit; s0 += 4 * U) {
+  for (int s0 = wave; s0 < nsplit; s0 += 4 * U) {
     float mv[U], lv[U];
     floatx4 ov[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const float *ps = pb + (size_t)min(s0 + 4 * u, a.nsplit - 1) * sstr;   // clamped: masked below
+      const float *ps = pb + (size_t)min(s0 + 4 * u, nsplit - 1) * sstr;   // clamped: masked below
       mv[u] = ps[n];
       lv[u] = ps[16 + n];
       ov[u] = *(const floatx4 *)(ps + o_off);
@@ -333,7 +351,7 @@ __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a) {
     float Mn = M;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (s0 + 4 * u >= a.nsplit) mv[u] = -INFINITY;
+      if (s0 + 4 * u >= nsplit) mv[u] = -INFINITY;
       Mn = fmaxf(Mn, mv[u]);
     }
     if (Mn != -INFINITY) {
@@ -360,16 +378,22 @@ __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a) {
     lt += f * sm_L[w][lane];
     ot += f * sm_O[w][lane];
   }
-  if (qa >= a.A || !(fl & ROW_VALID)) return;
+  if (qa >= A || !(fl & ROW_VALID)) return;
   float inv = 1.f / lt;
   float y[4] = {ot[0] * inv, ot[1] * inv, ot[2] * inv, ot[3] * inv};
-  store4_split(a.out, a.out_lo, act_off(r, h * HD + i * 16 + 4 * g, a.d), y);
+  store4_split(out, out_lo, act_off(r, h * HD + i * 16 + 4 * g, H * HD), y);
 }
 
 template <int HD, bool SPLIT, bool PAIR, bool BIAS, bool STREAM, int NW>
 static void launch_attn_nw(dim3 grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1, const AttnArgs &a) {
-  if (e0 || e1) hipExtLaunchKernelGGL((k_attn_mfma<HD, SPLIT, PAIR, BIAS, STREAM, NW>), grid, dim3(64 * NW), 0, s, e0, e1, 0, a);
-  else hipLaunchKernelGGL((k_attn_mfma<HD, SPLIT, PAIR, BIAS, STREAM, NW>), grid, dim3(64 * NW), 0, s, a);
+  const uint32_t q_lo = a.q_lo ? (uint32_t)((a.q_lo - a.q) / 8) : 0u, v = (uint32_t)((a.vc - a.kc) / 8);
+  const uint32_t ha = (uint32_t)a.H | (uint32_t)a.A << 16, nb = (uint32_t)a.nblk_static | (uint32_t)a.nsplit << 20;
+  const int32_t *kv_len = a.kv_override >= 0 ? nullptr : a.kv_len;
+  auto kernel = k_attn_mfma<HD, SPLIT, PAIR, BIAS, STREAM, NW>;
+  if (e0 || e1)
+    hipExtLaunchKernelGGL(kernel, grid, dim3(64 * NW), 0, s, e0, e1, 0, a.q, a.rt.qinfo, a.kc, kv_len, q_lo, v, a.kv_cap, ha, nb, a.req0, a);
+  else
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), 0, s, a.q, a.rt.qinfo, a.kc, kv_len, q_lo, v, a.kv_cap, ha, nb, a.req0, a);
 }
 
 template <int HD, bool SPLIT, bool PAIR, bool BIAS, bool STREAM>
@@ -424,6 +448,9 @@ int mfma_attention(pd_ctx *c, const LayerPtrs &lw, int A, int nreq, int req0, in
                                                          a.kc_lo != nullptr, c->stream_loads);
   const int nw = shape.waves;
   a.nsplit = shape.splits;
+  PD_REQUIRE(a.H < 65536 && A < 65536 && a.nblk_static < (1 << 20) && a.nsplit < (1 << 12) && a.vc > a.kc &&
+                 (uint64_t)(a.vc - a.kc) / 8 <= UINT32_MAX,
+             PD_EINVAL, "an attention launch over %d rows and %d key blocks is too large", A, a.nblk_static);
   dim3 grid(a.nsplit, g.n_head, nreq * a.nqg);
   // measurement: mode 1 attaches a start and a stop event to the dispatch of the main kernel itself
   // (their difference is the kernel's execution time), mode 2 records events before the main kernel
@@ -475,7 +502,8 @@ int mfma_attention(pd_ctx *c, const LayerPtrs &lw, int A, int nreq, int req0, in
     if (twice) PD_ATTN_ONE(HDV, a_extra);                                                              \
     PD_ATTN_ONE(HDV, a);                                                                               \
     if (a.nsplit > 1)                                                                                  \
-      hipLaunchKernelGGL(k_attn_merge<HDV>, dim3(units, HDV / 16), dim3(256), 0, s, a);                \
+      hipLaunchKernelGGL(k_attn_merge<HDV>, dim3(units, HDV / 16), dim3(256), 0, s, a.part, a.rt.flags, a.out, a.out_lo, \
+                         (uint32_t)a.H | (uint32_t)A << 16, (uint32_t)a.nsplit | (uint32_t)a.nqg << 12);   \
   } while (0)
   switch (g.head_dim) {
     case 32: PD_ATTN(32); break;

@@ -99,10 +99,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_ctx(CtxAttnArgs a) {
     reach = max(reach, q_lim[t]);
     lim_min = min(lim_min, valid ? q_lim[t] : 0x7fffffff);
   }
-  for (int o = 1; o < 16; o <<= 1) {
-    reach = max(reach, __shfl_xor(reach, o));
-    lim_min = min(lim_min, __shfl_xor(lim_min, o));
-  }
+  reach = fold_row(reach, Max());
+  lim_min = fold_row(lim_min, Min());
   const int end = __builtin_amdgcn_readfirstlane(min(nblk, (reach + 31) >> 5));
   const int lim_all = __builtin_amdgcn_readfirstlane(lim_min);   // keys below it are visible to every valid query
 
@@ -155,8 +153,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_ctx(CtxAttnArgs a) {
         sv[e] = (all_visible || key0 + e < q_lim[t]) ? x : -INFINITY;
       }
       float mloc = fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
-      mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
-      mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+      mloc = fold32(fold16(mloc, Max()), Max());
       const float m_new = fmaxf(m_run[t], mloc);
       const float m_ref = m_new == -INFINITY ? 0.f : m_new;      // nothing visible yet: exp2(-inf) = 0, never NaN
       alpha[t] = __builtin_amdgcn_exp2f(m_run[t] - m_ref);
@@ -189,8 +186,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_ctx(CtxAttnArgs a) {
 #pragma unroll
   for (int t = 0; t < QT; ++t) {
     float l = l_run[t];
-    l += __shfl_xor(l, 16);
-    l += __shfl_xor(l, 32);
+    l = fold32(fold16(l, Add()), Add());
     __syncthreads();                          // the query fragments / the previous tile's outputs are no longer read
     if (g == 0) { sm_m[wave][n] = m_run[t]; sm_l[wave][n] = l; }
 #pragma unroll

@@ -97,8 +97,8 @@ __global__ __launch_bounds__(64) void k_norm_fold(float *c1, float *c2, const bf
       if (bias) s2 = fmaf(wv, bias[k], s2);
     }
   }
-  s1 += __shfl_xor(s1, 16); s1 += __shfl_xor(s1, 32);
-  s2 += __shfl_xor(s2, 16); s2 += __shfl_xor(s2, 32);
+  s1 = fold32(fold16(s1, Add()), Add());
+  s2 = fold32(fold16(s2, Add()), Add());
   if (g == 0) {
     c1[nt * 16 + m] = s1;
     if (c2) c2[nt * 16 + m] = s2;
@@ -133,21 +133,24 @@ int mfma_fold_norms(pd_ctx *c, hipStream_t s) {
 // EMB: the row is not read from x but gathered from the embedding tables (first norm of a step:
 // x = E_tok[token] (+ E_pos[position]), zero for rows without a token) and written to x.
 template <int NG, int NP, bool EMB>     // 8-value granules per thread: d <= 2048 * NG; NP pending slices
-__global__ __launch_bounds__(256) void k_norm_bf16(bf16_t *xn, bf16_t *xn_lo, const float *x, const float *g,
-                                                   const float *b, int d, int kind, float eps,
-                                                   const int32_t *flags, int R, float *xw,
-                                                   const float *ypart, size_t part_stride,
-                                                   const bf16_t *tok_emb, const bf16_t *pos_emb,
-                                                   const int32_t *tok, const int32_t *pos) {
+__global__ __launch_bounds__(256) void k_norm_bf16(const int32_t *flags, const void *src1, const void *src2, const float *g,
+                                                   const float *b, int d, int R, int part_stride, int kind,
+                                                   const bf16_t *tok_emb, const bf16_t *pos_emb, float eps, float *xw,
+                                                   bf16_t *xn, bf16_t *xn_lo) {
+  // (the first 14 words arrive in registers: what the first requests need)
+  const float *x = (const float *)src1, *ypart = (const float *)src2;            // rows and pending slices
+  const int32_t *tok = (const int32_t *)src1, *pos = (const int32_t *)src2;      // EMB: token and position of a row
   int r = blockIdx.x;
   int fl = r < R ? flags[r] : 0;
   const float *xr = x + (size_t)r * d;
   float v[NG][8], gv[NG][8], bv[NG][8];
   const bf16_t *te = nullptr, *pe = nullptr;
   if (EMB) {
+    // (rows without a token hold an older one; the tables cover the padded rows)
+    const int tk = tok[r], ps = pos[r];
     bool has = fl & ROW_VALID;
-    te = tok_emb + (has ? (size_t)tok[r] * d : 0);
-    pe = pos_emb ? pos_emb + (has ? (size_t)pos[r] * d : 0) : nullptr;
+    te = tok_emb + (has ? (size_t)tk * d : 0);
+    pe = pos_emb ? pos_emb + (has ? (size_t)ps * d : 0) : nullptr;
   }
 #pragma unroll
   for (int i = 0; i < NG; ++i) {
@@ -177,7 +180,7 @@ __global__ __launch_bounds__(256) void k_norm_bf16(bf16_t *xn, bf16_t *xn_lo, co
       float4 y[NP > 0 ? NP : 1];
 #pragma unroll
       for (int pp = 0; pp < NP; ++pp)
-        y[pp] = in ? *(const float4 *)(ypart + pp * part_stride + (size_t)r * d + c + 4 * h)
+        y[pp] = in ? *(const float4 *)(ypart + (size_t)pp * part_stride + (size_t)r * d + c + 4 * h)
                    : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
       for (int pp = 0; pp < NP; ++pp) { t.x += y[pp].x; t.y += y[pp].y; t.z += y[pp].z; t.w += y[pp].w; }
@@ -194,7 +197,8 @@ __global__ __launch_bounds__(256) void k_norm_bf16(bf16_t *xn, bf16_t *xn_lo, co
 #pragma unroll
     for (int e = 0; e < 8; ++e) { s += v[i][e]; q += v[i][e] * v[i][e]; }
   // one reduction for both sums (values beyond d are zero)
-  for (int o = 32; o > 0; o >>= 1) { s += __shfl_xor(s, o); q += __shfl_xor(q, o); }
+  s = fold_wave(s, Add());
+  q = fold_wave(q, Add());
   __shared__ float2 sh2[4];
   if ((threadIdx.x & 63) == 0) sh2[threadIdx.x >> 6] = make_float2(s, q);
   __syncthreads();
@@ -224,10 +228,9 @@ __global__ __launch_bounds__(256) void k_norm_bf16(bf16_t *xn, bf16_t *xn_lo, co
 // bias are asked for only when the statistics are known (they sit in the caches), so a wave holds little more
 // than its row and many waves are resident.
 template <int NGW, int NP>     // granules per lane: d <= 512 * NGW; NP pending slices
-__global__ __launch_bounds__(256) void k_norm_rows(bf16_t *xn, bf16_t *xn_lo, float *x, const float *g,
-                                                   const float *b, int d, int kind, float eps,
-                                                   const int32_t *flags, int R, const float *ypart,
-                                                   size_t part_stride) {
+__global__ __launch_bounds__(256) void k_norm_rows(const int32_t *flags, float *x, const float *ypart, const float *g,
+                                                   const float *b, int d, int R, int part_stride, int kind, float eps,
+                                                   bf16_t *xn, bf16_t *xn_lo) {
   const int lane = threadIdx.x & 63, r = blockIdx.x * 4 + (threadIdx.x >> 6);
   const bool valid = r < R && (flags[r] & ROW_VALID);
   float *xr = x + (size_t)r * d;
@@ -242,7 +245,7 @@ __global__ __launch_bounds__(256) void k_norm_rows(bf16_t *xn, bf16_t *xn_lo, fl
       float4 y[NP > 0 ? NP : 1];
 #pragma unroll
       for (int pp = 0; pp < NP; ++pp)
-        y[pp] = in ? *(const float4 *)(ypart + pp * part_stride + (size_t)r * d + c + 4 * h)
+        y[pp] = in ? *(const float4 *)(ypart + (size_t)pp * part_stride + (size_t)r * d + c + 4 * h)
                    : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
       for (int pp = 0; pp < NP; ++pp) { t.x += y[pp].x; t.y += y[pp].y; t.z += y[pp].z; t.w += y[pp].w; }
@@ -255,7 +258,7 @@ __global__ __launch_bounds__(256) void k_norm_rows(bf16_t *xn, bf16_t *xn_lo, fl
   for (int i = 0; i < NGW; ++i)
 #pragma unroll
     for (int e = 0; e < 8; ++e) s1 += v[i][e];
-  for (int o = 32; o > 0; o >>= 1) s1 += __shfl_xor(s1, o);
+  s1 = fold_wave(s1, Add());
   const float mean = kind == 0 ? s1 / d : 0.f;
   float q = 0.f;
 #pragma unroll
@@ -267,7 +270,7 @@ __global__ __launch_bounds__(256) void k_norm_rows(bf16_t *xn, bf16_t *xn_lo, fl
       q += t * t;
     }
   }
-  for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o);
+  q = fold_wave(q, Add());
   const float rstd = rsqrtf(q / d + eps);
 #pragma unroll
   for (int i = 0; i < NGW; ++i) {
@@ -300,10 +303,12 @@ int mfma_norm(pd_ctx *c, const float *gain, const float *bias, int R, hipStream_
   bf16_t *xn = (bf16_t *)c->xn;
   const pd_config &g = c->cfg;
   PD_REQUIRE(d <= 2048 * 4, PD_EINVAL, "d_model %d too large for the norm kernel", d);
+  PD_REQUIRE((int64_t)c->R_pad * d <= INT32_MAX, PD_EINVAL, "%d rows of %d values are too many for the norm kernel", c->R_pad, d);
+  const int part_stride = c->R_pad * d;
   if (rows > 128 && !c->embed_pending && !c->packed) {
 #define PD_NORM_R(G, P)                                                                           \
-  hipLaunchKernelGGL((k_norm_rows<G, P>), dim3(rows / 4), dim3(256), 0, s, xn, mfma_lo(c, xn, d), c->x, gain, bias, \
-                     d, g.norm_kind, g.norm_eps, c->rows.flags, R, c->ypart, (size_t)c->R_pad * d)
+  hipLaunchKernelGGL((k_norm_rows<G, P>), dim3(rows / 4), dim3(256), 0, s, c->rows.flags, c->x, c->ypart, gain, bias, d, \
+                     R, part_stride, g.norm_kind, g.norm_eps, xn, mfma_lo(c, xn, d))
 #define PD_NORM_RP(G)                                                                            \
   switch (c->pend_parts) {                                                                       \
     case 0: PD_NORM_R(G, 0); break;                                                              \
@@ -320,9 +325,10 @@ int mfma_norm(pd_ctx *c, const float *gain, const float *bias, int R, hipStream_
     return PD_OK;
   }
 #define PD_NORM(V, P, E)                                                                         \
-  hipLaunchKernelGGL((k_norm_bf16<V, P, E>), dim3(rows), dim3(256), 0, s, xn, mfma_lo(c, xn, d), c->x, gain, bias, \
-                     d, g.norm_kind, g.norm_eps, c->rows.flags, R, c->x, c->ypart, (size_t)c->R_pad * d,   \
-                     (const bf16_t *)c->tok_emb, (const bf16_t *)c->pos_emb, c->rows.tok, c->rows.pos)
+  hipLaunchKernelGGL((k_norm_bf16<V, P, E>), dim3(rows), dim3(256), 0, s, c->rows.flags,                          \
+                     E ? (const void *)c->rows.tok : c->x, E ? (const void *)c->rows.pos : c->ypart, gain, bias, d, R,    \
+                     part_stride, g.norm_kind, (const bf16_t *)c->tok_emb, (const bf16_t *)c->pos_emb, g.norm_eps, c->x,  \
+                     xn, mfma_lo(c, xn, d))
 #define PD_NORM_P(V)                                                                             \
   if (c->embed_pending) { PD_NORM(V, 0, true); }                                                 \
   else switch (c->pend_parts) {                                                                  \
@@ -374,18 +380,18 @@ int mfma_norm(pd_ctx *c, const float *gain, const float *bias, int R, hipStream_
 // kernel start so that they arrive with the first weights; what lies beyond (very wide models) is
 // read when the sums are taken.  Fixed order, no atomics: deterministic.
 constexpr int PS = 4;
-__device__ __forceinline__ void stats_request(const GemmArgs &a, int lane, int w, int nw, float4 (&pre)[PS], int r0) {
-  const int m = r0 + (lane & 15), g = lane >> 4, npair = a.stats_tiles >> 1;
-  const float4 *sp = (const float4 *)(a.stats_in + (size_t)m * a.stats_tiles);
+__device__ __forceinline__ void stats_request(const float2 *stats, int npair, int lane, int w, int nw, float4 (&pre)[PS], int r0) {
+  const int m = r0 + (lane & 15), g = lane >> 4;
+  const float4 *sp = (const float4 *)stats + (size_t)m * npair;
 #pragma unroll
   for (int u = 0; u < PS; ++u) {
     pre[u] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (4 * (w + nw * u) < npair) pre[u] = sp[min(g + 4 * (w + nw * u), npair - 1)];   // the same for the whole wave
   }
 }
-__device__ __forceinline__ float2 stats_partial(const GemmArgs &a, int lane, int w, int nw, const float4 (&pre)[PS], int r0) {
-  const int m = r0 + (lane & 15), g = lane >> 4, npair = a.stats_tiles >> 1;
-  const float4 *sp = (const float4 *)(a.stats_in + (size_t)m * a.stats_tiles);
+__device__ __forceinline__ float2 stats_partial(const float2 *stats, int npair, int lane, int w, int nw, const float4 (&pre)[PS], int r0) {
+  const int m = r0 + (lane & 15), g = lane >> 4;
+  const float4 *sp = (const float4 *)stats + (size_t)m * npair;
   float s1 = 0.f, s2 = 0.f;
 #pragma unroll
   for (int u = 0; u < PS; ++u)
@@ -394,8 +400,8 @@ __device__ __forceinline__ float2 stats_partial(const GemmArgs &a, int lane, int
     float4 v = sp[p];
     s1 += v.x + v.z; s2 += v.y + v.w;
   }
-  s1 += __shfl_xor(s1, 16); s1 += __shfl_xor(s1, 32);
-  s2 += __shfl_xor(s2, 16); s2 += __shfl_xor(s2, 32);
+  s1 = fold32(fold16(s1, Add()), Add());
+  s2 = fold32(fold16(s2, Add()), Add());
   return make_float2(s1, s2);
 }
 __device__ __forceinline__ float2 stats_finish(const GemmArgs &a, float2 s) {
@@ -462,8 +468,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, int nt, const f
         s1 = (xn[0] + xn[1]) + (xn[2] + xn[3]);
         s2 = (xn[0] * xn[0] + xn[1] * xn[1]) + (xn[2] * xn[2] + xn[3] * xn[3]);
       }
-      s1 += __shfl_xor(s1, 16); s1 += __shfl_xor(s1, 32);
-      s2 += __shfl_xor(s2, 16); s2 += __shfl_xor(s2, 32);
+      s1 = fold32(fold16(s1, Add()), Add());
+      s2 = fold32(fold16(s2, Add()), Add());
       if (g == 0) a.stats_out[(size_t)r * a.n_tiles + nt] = make_float2(s1, s2);
     }
   } else if (EPI == EPI_GELU) {
@@ -486,9 +492,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, int nt, const f
       float y[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        float mine = acc[i][j];
-        float other = __shfl_xor(mine, 32);
-        y[j] = mine / (1.f + __expf(-mine)) * other;     // meaningful on groups 0,1
+        const Halves<float> h = halves32(acc[i][j]);     // gate and up
+        y[j] = h.lo / (1.f + __expf(-h.lo)) * h.hi;
       }
       if (g < 2 && r < a.R) store4_split(a.out_bf, a.out_lo, act_off(r, nt * 8 + 4 * g, a.ld), y);
     }
@@ -508,11 +513,10 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, int nt, const f
         const float *cs = a.rope_cs + ((size_t)(valid ? kvi[i].w : 0) * half + jj) * 2;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          float mine = acc[i][j];
-          float other = __shfl_xor(mine, 32);
+          const Halves<float> x = halves32(acc[i][j]);
           float cc = cs[2 * j], ss = cs[2 * j + 1];
           // low half: x1*c - x2*s ; high half: x2*c + x1*s
-          y[j] = g < 2 ? mine * cc - other * ss : mine * cc + other * ss;
+          y[j] = g < 2 ? x.lo * cc - x.hi * ss : x.hi * cc + x.lo * ss;
         }
       } else {
         dim0 = (nl % a.hd);
@@ -568,12 +572,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, int nt, const f
         }
       }
       // across the 4 column groups of this row; lowest index wins ties
-#pragma unroll
-      for (int o = 16; o <= 32; o <<= 1) {
-        float ov = __shfl_xor(best, o);
-        int oi = __shfl_xor(bi, o);
-        if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
-      }
+      best16(best, bi);
+      best32(best, bi);
       if (g == 0 && r < a.R) {      // row-major [row][tile]: the commit kernel reads a row's winners as one run
         a.part_val[(size_t)r * a.n_tiles + nt] = best;
         a.part_idx[(size_t)r * a.n_tiles + nt] = bi;
@@ -620,6 +620,43 @@ __device__ __forceinline__ void gemm_chunk(floatx4 (&acc)[NT][RT][NA], const uin
       }
 }
 
+// What a launch needs before it can ask for its first byte comes as scalars in front of GemmArgs: compiled with
+// -amdgpu-kernarg-preload-count the first 14 words of the arguments are in scalar registers when a wave starts.  Read from
+// memory they cost every launch 0.25-0.35 us before its first request (they are new to every cache), twice where a pointer
+// decides on the next read; a decode step is 30-270 such launches one after the other.
+#define PD_GEMM_HOT_PARAMS                                                                                        \
+  const bf16_t *hot_w, const bf16_t *hot_x, const void *hot_a, const void *hot_b, const void *hot_c, uint32_t hot_lo, \
+      uint32_t hot_k, uint32_t hot_n, int hot_r
+struct GemmHot {
+  const bf16_t *w, *x;        // weights, activations
+  const void *a, *b, *c;      // EPI_RESID_NORM: x_res, gain; finishing a norm: stats_in (else NULL), c1; EPI_QKV*: c = kvinfo
+  uint32_t lo;                // low parts behind x, in 16-byte granules
+  uint32_t k, n;              // k-tiles | k_share << 16; n_tiles | (c2 follows c1) << 24
+  int r;                      // rows
+};
+template <int EPI>
+static int gemm_hot(const GemmArgs &a, GemmHot *h) {
+  const int KT = a.K / 32;
+  PD_REQUIRE(KT < 65536 && a.k_share < 65536 && a.n_tiles < (1 << 24), PD_EINVAL, "a projection of %d x %d is too large",
+             a.n_tiles * 16, a.K);
+  PD_REQUIRE(!a.stats_in || (a.stats_tiles == 2 * KT && (!a.c2 || a.c2 == a.c1 + (size_t)a.n_tiles * 16)), PD_EINVAL,
+             "a norm is finished over the whole rows, with c2 behind c1");
+  const bool out = EPI == EPI_RESID_NORM;
+  *h = GemmHot{a.W, a.xn, out ? (const void *)a.x_res : a.stats_in, out ? a.gain : a.c1, a.rt.kvinfo,
+               a.xn_lo ? (uint32_t)((a.xn_lo - a.xn) / 8) : 0u, (uint32_t)KT | (uint32_t)a.k_share << 16,
+               (uint32_t)a.n_tiles | (a.c2 ? 1u << 24 : 0u), a.R};
+  return PD_OK;
+}
+template <int EPI, typename Kernel>
+static int launch_gemm_kernel(Kernel kernel, dim3 grid, int threads, const GemmArgs &a, hipStream_t s) {
+  GemmHot h;
+  const int rc = gemm_hot<EPI>(a, &h);
+  if (rc) return rc;
+  hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, h.w, h.x, h.a, h.b, h.c, h.lo, h.k, h.n, h.r, a);
+  PD_CHECK_HIP(hipGetLastError());
+  return PD_OK;
+}
+
 // PACK (one row tile, at most 8 rows): the activation fragment carries the high parts in rows 0-7
 // and the low parts of the same 8 rows in rows 8-15, so one fragment and one multiply per k-tile
 // do the work of two; the two halves of the output tile are added before the epilogue.
@@ -632,48 +669,51 @@ constexpr bool norm_in_default(int rt, int epi) { return rt == 1 && (epi == EPI_
 // tiles re-read the weights through L2).
 template <int RT, int NT, int NW_K, int U, int EPI, bool SPLIT, bool PACK, bool ZROWS = false, bool SW = false,
           bool FUSED_IN = norm_in_default(RT, EPI)>
-__global__ __launch_bounds__(64 * NW_K) void k_gemm_s(GemmArgs a) {
+__global__ __launch_bounds__(64 * NW_K) void k_gemm_s(PD_GEMM_HOT_PARAMS, GemmArgs a) {
   static_assert(!PACK || (RT == 1 && !SPLIT), "packed activations: one row tile, one fragment");
   const int rz = ZROWS ? (int)blockIdx.z * RT : 0;          // first row tile of this block
   __shared__ floatx4 red[NW_K > 1 ? NW_K * NT * RT * 64 : 1];
   const int wk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int nt0 = blockIdx.x * NT;
   const int m = lane & 15;
-  const int KT = a.K >> 5;
+  const int KT = hot_k & 0xffff, k_share = hot_k >> 16, n_tiles = hot_n & 0xffffff;
   // waves along K: NW_K in this block times gridDim.y blocks (EPI_RESID only)
   const int gk = blockIdx.y * NW_K + wk;
-  const int kt0 = min(gk * a.k_share, KT), kt1 = min(kt0 + a.k_share, KT);
+  const int kt0 = min(gk * k_share, KT), kt1 = min(kt0 + k_share, KT);
+  int tile[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) tile[t] = min(nt0 + t, n_tiles - 1);   // tiles past the end repeat the last one
+  const uint4 *wp = (const uint4 *)hot_w + lane;
+  const uint4 *xp = (const uint4 *)hot_x + lane + (size_t)rz * KT * 64;
+  const uint4 *xl = SPLIT ? xp + hot_lo : nullptr;
   // row data of the KV-append epilogue, requested now so that it arrives with the weights (where a row's logits go is
   // read by the epilogue that stores them: requested here it held 4 registers per row tile in every vocabulary launch)
   constexpr bool QKV = EPI == EPI_QKV || EPI == EPI_QKV_ROPE;
   int4 kvi[QKV ? RT : 1];
   if (QKV) {
 #pragma unroll
-    for (int i = 0; i < RT; ++i) kvi[i] = a.rt.kvinfo[(rz + i) * 16 + m];
+    for (int i = 0; i < RT; ++i) kvi[i] = ((const int4 *)hot_c)[(rz + i) * 16 + m];
   }
-  int tile[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) tile[t] = min(nt0 + t, a.n_tiles - 1);   // tiles past the end repeat the last one
   // one row tile: what the epilogue needs from memory is asked for now, so that it arrives with the weights
   static_assert(!FUSED_IN || RT == 1, "norms are finished per row tile");
   constexpr bool FUSED_OUT = RT == 1 && EPI == EPI_RESID_NORM;
   __shared__ float2 sm_stat[FUSED_IN ? NW_K : 1][16];
   float4 pre_s[PS];
-  const bool fused_norm = FUSED_IN && a.stats_in != nullptr;          // the same for the whole launch
+  const bool fused_norm = FUSED_IN && hot_a != nullptr;               // the same for the whole launch
   NormPre pre_n;
-  if (fused_norm) stats_request(a, lane, wk, NW_K, pre_s, rz * 16);
+  if (fused_norm) stats_request((const float2 *)hot_a, KT, lane, wk, NW_K, pre_s, rz * 16);
   if (fused_norm && wk < NT) {      // wave w < NT finishes tile nt0 + w
-    const int n0 = min(nt0 + wk, a.n_tiles - 1) * 16 + 4 * (lane >> 4);
-    pre_n.c1 = *(const float4 *)(a.c1 + n0);
-    pre_n.c2 = a.c2 ? *(const float4 *)(a.c2 + n0) : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float *c1 = (const float *)hot_b + min(nt0 + wk, n_tiles - 1) * 16 + 4 * (lane >> 4);
+    pre_n.c1 = *(const float4 *)c1;
+    pre_n.c2 = hot_n >> 24 ? *(const float4 *)(c1 + n_tiles * 16) : make_float4(0.f, 0.f, 0.f, 0.f);
   }
   ResidPre pre_r;
   if (FUSED_OUT && wk < NT) {       // wave w < NT finishes tile nt0 + w
-    const int n0 = min(nt0 + wk, a.n_tiles - 1) * 16 + 4 * (lane >> 4);
-    pre_r.g = *(const float4 *)(a.gain + n0);
+    const int n0 = min(nt0 + wk, n_tiles - 1) * 16 + 4 * (lane >> 4);
+    pre_r.g = *(const float4 *)((const float *)hot_b + n0);
     // (rows beyond R read row R - 1 and are masked where the value is used, not here: touching the
     // value now would make the wave wait for it before it has asked for its weights)
-    pre_r.x = *(const float4 *)(a.x_res + (size_t)min(rz * 16 + m, max(a.R - 1, 0)) * a.ld + n0);
+    pre_r.x = *(const float4 *)((const float *)hot_a + (size_t)min(rz * 16 + m, max(hot_r - 1, 0)) * (n_tiles * 16) + n0);
   }
   constexpr int NA = (SPLIT && NT * RT <= 2) ? 2 : 1;
   floatx4 acc2[NT][RT][NA];
@@ -681,12 +721,10 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(GemmArgs a) {
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int i = 0; i < RT; ++i) acc2[t][i][0] = acc2[t][i][NA - 1] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const uint4 *wp = (const uint4 *)a.W + lane;
-  const uint4 *xp = (const uint4 *)a.xn + lane + (size_t)rz * KT * 64;
-  const uint4 *xl = SPLIT ? (const uint4 *)a.xn_lo + lane + (size_t)rz * KT * 64 : nullptr;
   int kt = kt0;
   while (kt + U <= kt1) { gemm_chunk<RT, NT, U, SPLIT, NA, SW>(acc2, wp, xp, xl, KT, tile, kt); kt += U; }
   if (U > 4 && kt + 4 <= kt1) { gemm_chunk<RT, NT, 4, SPLIT, NA, SW>(acc2, wp, xp, xl, KT, tile, kt); kt += 4; }
+  if (U > 3 && kt + 3 <= kt1) { gemm_chunk<RT, NT, 3, SPLIT, NA, SW>(acc2, wp, xp, xl, KT, tile, kt); kt += 3; }
   if (U > 2 && kt + 2 <= kt1) { gemm_chunk<RT, NT, 2, SPLIT, NA, SW>(acc2, wp, xp, xl, KT, tile, kt); kt += 2; }
   if (U > 1 && kt < kt1) gemm_chunk<RT, NT, 1, SPLIT, NA, SW>(acc2, wp, xp, xl, KT, tile, kt);
   floatx4 acc[NT][RT];
@@ -699,7 +737,7 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(GemmArgs a) {
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[t][0][j] += __shfl_xor(acc[t][0][j], 8);
+      for (int j = 0; j < 4; ++j) acc[t][0][j] += rotate16<8>(acc[t][0][j]);
   }
   if (NW_K > 1) {
     // every wave leaves its partial tiles in LDS; wave w then sums and finishes column tiles w, w + NW_K, ...
@@ -708,7 +746,7 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(GemmArgs a) {
 #pragma unroll
       for (int i = 0; i < RT; ++i) red[((wk * NT + t) * RT + i) * 64 + lane] = acc[t][i];
     if (fused_norm) {
-      float2 sp = stats_partial(a, lane, wk, NW_K, pre_s, rz * 16);
+      float2 sp = stats_partial((const float2 *)hot_a, KT, lane, wk, NW_K, pre_s, rz * 16);
       if (lane < 16) sm_stat[wk][lane] = sp;
     }
     __syncthreads();
@@ -719,7 +757,7 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(GemmArgs a) {
       for (int w = 1; w < NW_K; ++w) { tot.x += sm_stat[w][m].x; tot.y += sm_stat[w][m].y; }
       nrm[0] = stats_finish(a, tot);
     }
-    for (int t = wk; t < NT && nt0 + t < a.n_tiles; t += NW_K) {
+    for (int t = wk; t < NT && nt0 + t < n_tiles; t += NW_K) {
       floatx4 sum[RT];
 #pragma unroll
       for (int i = 0; i < RT; ++i) sum[i] = red[((0 * NT + t) * RT + i) * 64 + lane];
@@ -732,10 +770,10 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(GemmArgs a) {
     }
   } else {
     float2 nrm[RT];
-    if (fused_norm) nrm[0] = stats_finish(a, stats_partial(a, lane, 0, 1, pre_s, rz * 16));
+    if (fused_norm) nrm[0] = stats_finish(a, stats_partial((const float2 *)hot_a, KT, lane, 0, 1, pre_s, rz * 16));
 #pragma unroll
     for (int t = 0; t < NT; ++t)
-      if (nt0 + t < a.n_tiles)
+      if (nt0 + t < n_tiles)
         gemm_epilogue<RT, EPI, FUSED_IN>(a, nt0 + t, acc[t], kvi, lane, rz * 16, fused_norm ? nrm : nullptr,
                                (FUSED_OUT && t == 0) ? &pre_r : nullptr, (fused_norm && t == 0) ? &pre_n : nullptr);
   }
@@ -773,25 +811,19 @@ static int launch_gemm_small_nt(GemmArgs a, int ks, hipStream_t s) {
   if constexpr (EPI == EPI_RESID_NORM && NT == 1) {
     constexpr int UL = SPLIT ? 6 : 8;
     if (nwk == 16 && a.k_share > 4 && a.k_share <= UL) {
-#define PD_LAUNCH_U(UU)                                                                                         \
-  do {                                                                                                          \
-    if (a.stream_w)                                                                                             \
-      hipLaunchKernelGGL((k_gemm_s<RT, NT, 16, UU, EPI, SPLIT, PACK, false, true>), grid, dim3(1024), 0, s, a); \
-    else                                                                                                        \
-      hipLaunchKernelGGL((k_gemm_s<RT, NT, 16, UU, EPI, SPLIT, PACK>), grid, dim3(1024), 0, s, a);              \
-  } while (0)
-      if (a.k_share <= 6) PD_LAUNCH_U(6);
-      else PD_LAUNCH_U(UL);
+#define PD_LAUNCH_U(UU)                                                                                               \
+  (a.stream_w ? launch_gemm_kernel<EPI>(k_gemm_s<RT, NT, 16, UU, EPI, SPLIT, PACK, false, true>, grid, 1024, a, s)    \
+              : launch_gemm_kernel<EPI>(k_gemm_s<RT, NT, 16, UU, EPI, SPLIT, PACK>, grid, 1024, a, s))
+      return a.k_share <= 6 ? PD_LAUNCH_U(6) : PD_LAUNCH_U(UL);
 #undef PD_LAUNCH_U
-      PD_CHECK_HIP(hipGetLastError());
-      return PD_OK;
     }
   }
   constexpr bool QKV_NORM = RT == 1 && (EPI == EPI_QKV || EPI == EPI_QKV_ROPE);
   constexpr bool DEF = norm_in_default(RT, EPI);
+  int rc;
 #define PD_LAUNCH_F(NWK, SWX, FI)                                                                                    \
-  hipLaunchKernelGGL((k_gemm_s<RT, NT, (NWK < NT ? NT : NWK), U, EPI, SPLIT, PACK, false, SWX, FI>), grid,           \
-                     dim3(64 * (NWK < NT ? NT : NWK)), 0, s, a)
+  rc = launch_gemm_kernel<EPI>(k_gemm_s<RT, NT, (NWK < NT ? NT : NWK), U, EPI, SPLIT, PACK, false, SWX, FI>, grid,   \
+                               64 * (NWK < NT ? NT : NWK), a, s)
 #define PD_LAUNCH(NWK)                                                                                               \
   do {                                                                                                               \
     if (QKV_NORM && a.stats_in) {                                                                                    \
@@ -809,7 +841,7 @@ static int launch_gemm_small_nt(GemmArgs a, int ks, hipStream_t s) {
   }
 #undef PD_LAUNCH
 #undef PD_LAUNCH_F
-  PD_CHECK_HIP(hipGetLastError());
+  if (rc) return rc;
   if (EPI == EPI_RESID && a.parts_out) *a.parts_out = ks;
   return PD_OK;
 }
@@ -838,11 +870,10 @@ static int launch_gemm_wide_nt(GemmArgs a, int ks, hipStream_t s) {
   constexpr int U = (NT + 2 * RT) <= 16 ? 4 : 2;
   int KT = a.K / 32, groups = (a.n_tiles + NT - 1) / NT;
   a.k_share = ((KT + ks - 1) / ks + NWK - 1) / NWK;
-  if (a.stream_w)
-    hipLaunchKernelGGL((k_gemm_s<RT, NT, NWK, U, EPI, SPLIT, false, false, true>), dim3(groups, ks), dim3(64 * NWK), 0, s, a);
-  else
-    hipLaunchKernelGGL((k_gemm_s<RT, NT, NWK, U, EPI, SPLIT, false>), dim3(groups, ks), dim3(64 * NWK), 0, s, a);
-  PD_CHECK_HIP(hipGetLastError());
+  const dim3 grid(groups, ks);
+  const int rc = a.stream_w ? launch_gemm_kernel<EPI>(k_gemm_s<RT, NT, NWK, U, EPI, SPLIT, false, false, true>, grid, 64 * NWK, a, s)
+                            : launch_gemm_kernel<EPI>(k_gemm_s<RT, NT, NWK, U, EPI, SPLIT, false>, grid, 64 * NWK, a, s);
+  if (rc) return rc;
   if (EPI == EPI_RESID && a.parts_out) *a.parts_out = ks;
   return PD_OK;
 }
@@ -910,12 +941,12 @@ static int launch_gemm_zrows(GemmArgs a, int rows, hipStream_t s) {
   a.k_share = (per_block + nwk - 1) / nwk;
   dim3 grid(groups, ks, rts);
   constexpr bool DEF = norm_in_default(1, EPI), QKV_NORM = EPI == EPI_QKV || EPI == EPI_QKV_ROPE;
-  if (QKV_NORM && a.stats_in) {
-    if (nwk == 4) hipLaunchKernelGGL((k_gemm_s<1, NT, 4, U, EPI, SPLIT, false, true, false, (QKV_NORM || DEF)>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((k_gemm_s<1, NT, 8, U, EPI, SPLIT, false, true, false, (QKV_NORM || DEF)>), grid, dim3(512), 0, s, a);
-  } else if (nwk == 4) hipLaunchKernelGGL((k_gemm_s<1, NT, 4, U, EPI, SPLIT, false, true>), grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((k_gemm_s<1, NT, 8, U, EPI, SPLIT, false, true>), grid, dim3(512), 0, s, a);
-  PD_CHECK_HIP(hipGetLastError());
+#define PD_LAUNCH(NWK, FI) launch_gemm_kernel<EPI>(k_gemm_s<1, NT, NWK, U, EPI, SPLIT, false, true, false, FI>, grid, 64 * NWK, a, s)
+  int rc;
+  if (QKV_NORM && a.stats_in) rc = nwk == 4 ? PD_LAUNCH(4, (QKV_NORM || DEF)) : PD_LAUNCH(8, (QKV_NORM || DEF));
+  else rc = nwk == 4 ? PD_LAUNCH(4, DEF) : PD_LAUNCH(8, DEF);
+#undef PD_LAUNCH
+  if (rc) return rc;
   if (EPI == EPI_RESID && a.parts_out) *a.parts_out = ks;
   return PD_OK;
 }
@@ -976,7 +1007,7 @@ int PD_GEMM_ENTRY(const GemmArgs &a, int rows, hipStream_t s) { return launch_ge
 // that holds the rate, and 32x32x16 multiplies (half the operand reads) measured no better (239 against 226 us).
 // ---------------------------------------------------------------------------
 template <int RT, int NT, int EPI, bool SPLIT, bool SW = false>
-__global__ __launch_bounds__(512, 1) void k_gemm_t(GemmArgs a) {
+__global__ __launch_bounds__(512, 1) void k_gemm_t(PD_GEMM_HOT_PARAMS, GemmArgs a) {
   constexpr int NW = 8, NA = SPLIT ? 2 * RT : RT;     // activation fragments of a k-tile
   constexpr int NAW = (NA + NW - 1) / NW;             // staged by one wave (no multiple of the waves: some twice, same bytes)
   constexpr int GS = RT == 5 ? 5 : 4, NG = NA / GS;
@@ -984,8 +1015,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm_t(GemmArgs a) {
   __shared__ bf16x8 sm_x[2][NA][64];   // (vector types throughout: struct copies would keep xr in scratch memory)
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int m = lane & 15;
-  const int KT = a.K >> 5;
-  const int per_slice = (KT + (int)gridDim.y - 1) / (int)gridDim.y;
+  const int KT = hot_k & 0xffff, per_slice = hot_k >> 16, n_tiles = hot_n & 0xffffff;
   const int kt0 = min((int)blockIdx.y * per_slice, KT), kt1 = min(kt0 + per_slice, KT);
   const int rt0 = blockIdx.z * RT, r0 = rt0 * 16;
   const int nt0 = (blockIdx.x * NW + w) * NT;
@@ -997,14 +1027,13 @@ __global__ __launch_bounds__(512, 1) void k_gemm_t(GemmArgs a) {
   const bf16x8 *wsrc[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t)          // tiles past the end repeat the last one
-    wsrc[t] = (const bf16x8 *)a.W + (size_t)min(nt0 + t, a.n_tiles - 1) * KT * 64 + lane;
+    wsrc[t] = (const bf16x8 *)hot_w + (size_t)min(nt0 + t, n_tiles - 1) * KT * 64 + lane;
   // this wave's share of the activation fragments: fragment f is row tile f % RT of the high (f < RT) or low parts
   const bf16x8 *xsrc[NAW];
 #pragma unroll
   for (int i = 0; i < NAW; ++i) {
     const int f = (w * NAW + i) % NA;
-    const bf16_t *base = (SPLIT && f >= RT) ? a.xn_lo : a.xn;
-    xsrc[i] = (const bf16x8 *)base + (size_t)(rt0 + f % RT) * KT * 64 + lane;
+    xsrc[i] = (const bf16x8 *)hot_x + (SPLIT && f >= RT ? hot_lo : 0) + (size_t)(rt0 + f % RT) * KT * 64 + lane;
   }
   const int len = kt1 - kt0;
   bf16x8 xr[2][NAW], wr[2][NT];         // k-tiles in flight, slot = k-tile index mod 2; past the end: the last one again
@@ -1074,18 +1103,19 @@ __global__ __launch_bounds__(512, 1) void k_gemm_t(GemmArgs a) {
   int4 kvi[QKV ? RT : 1];
   if (QKV) {
 #pragma unroll
-    for (int i = 0; i < RT; ++i) kvi[i] = a.rt.kvinfo[r0 + i * 16 + m];
+    for (int i = 0; i < RT; ++i) kvi[i] = ((const int4 *)hot_c)[r0 + i * 16 + m];
   }
 #pragma unroll
   for (int t = 0; t < NT; ++t)
-    if (nt0 + t < a.n_tiles) gemm_epilogue<RT, EPI>(a, nt0 + t, acc[t], kvi, lane, r0);
+    if (nt0 + t < n_tiles) gemm_epilogue<RT, EPI>(a, nt0 + t, acc[t], kvi, lane, r0);
 }
 
 template <int RT, int NT, int EPI, bool SPLIT>
-static int launch_gemm_t(const GemmArgs &a, int rows, int ks, hipStream_t s) {
+static int launch_gemm_t(GemmArgs a, int rows, int ks, hipStream_t s) {
   dim3 grid((a.n_tiles + 8 * NT - 1) / (8 * NT), ks, (rows + 16 * RT - 1) / (16 * RT));
-  hipLaunchKernelGGL((k_gemm_t<RT, NT, EPI, SPLIT>), grid, dim3(512), 0, s, a);
-  PD_CHECK_HIP(hipGetLastError());
+  a.k_share = (a.K / 32 + ks - 1) / ks;
+  const int rc = launch_gemm_kernel<EPI>(k_gemm_t<RT, NT, EPI, SPLIT>, grid, 512, a, s);
+  if (rc) return rc;
   if (EPI == EPI_RESID && a.parts_out) *a.parts_out = ks;
   return PD_OK;
 }
@@ -1095,8 +1125,8 @@ template <int RT, int NT, int NWK, int EPI, bool SPLIT>
 static int launch_gemm_cut(GemmArgs a, int rows, int ks, hipStream_t s) {
   a.k_share = ((a.K / 32 + ks - 1) / ks + NWK - 1) / NWK;
   dim3 grid((a.n_tiles + NT - 1) / NT, ks, (rows + 16 * RT - 1) / (16 * RT));
-  hipLaunchKernelGGL((k_gemm_s<RT, NT, NWK, 4, EPI, SPLIT, false, true>), grid, dim3(64 * NWK), 0, s, a);
-  PD_CHECK_HIP(hipGetLastError());
+  const int rc = launch_gemm_kernel<EPI>(k_gemm_s<RT, NT, NWK, 4, EPI, SPLIT, false, true>, grid, 64 * NWK, a, s);
+  if (rc) return rc;
   if (EPI == EPI_RESID && a.parts_out) *a.parts_out = ks;
   return PD_OK;
 }
@@ -1138,13 +1168,12 @@ static int launch_gemm_rows(const GemmArgs &a, int rows, hipStream_t s) {
 // 768 66.6 and 65.3; 128 rows of width 2048 148 and 139); three, or four k-tiles ahead instead of two, measured no better.
 // Steps of 17-32 rows differ by less than 5 % either way and stay.
 template <int RT, int NT>
-static int launch_gemm_vocab(const GemmArgs &a, int rows, hipStream_t s) {
+static int launch_gemm_vocab(GemmArgs a, int rows, hipStream_t s) {
   PD_REQUIRE(rows <= 16 * RT, PD_EINVAL, "%d rows in %d row tiles", rows, RT);
   const dim3 grid((a.n_tiles + 8 * NT - 1) / (8 * NT));
-  if (a.stream_w) hipLaunchKernelGGL((k_gemm_t<RT, NT, EPI_LM, true, true>), grid, dim3(512), 0, s, a);
-  else hipLaunchKernelGGL((k_gemm_t<RT, NT, EPI_LM, true, false>), grid, dim3(512), 0, s, a);
-  PD_CHECK_HIP(hipGetLastError());
-  return PD_OK;
+  a.k_share = a.K / 32;
+  return a.stream_w ? launch_gemm_kernel<EPI_LM>(k_gemm_t<RT, NT, EPI_LM, true, true>, grid, 512, a, s)
+                    : launch_gemm_kernel<EPI_LM>(k_gemm_t<RT, NT, EPI_LM, true, false>, grid, 512, a, s);
 }
 
 static int launch_gemm_vocab_rows(const GemmArgs &a, int rows, hipStream_t s) {

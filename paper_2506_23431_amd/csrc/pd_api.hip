@@ -206,10 +206,11 @@ static size_t carve_with(const pd_config *g, char *base, pd_ctx *c, const pd_enc
       lp.p_wo = cv.take<bf16_t>(dd * d);
       lp.p_w1 = cv.take<bf16_t>((g->ffn_kind == 1 ? 2 : 1) * (size_t)ff * d);
       lp.p_w2 = cv.take<bf16_t>(dd * ff);
-      lp.c1 = cv.take<float>((g->ffn_kind == 1 ? 2 : 1) * (size_t)ff);
-      lp.c2 = cv.take<float>((g->ffn_kind == 1 ? 2 : 1) * (size_t)ff);
+      // (one pointer reaches both)
+      const size_t n1 = (g->ffn_kind == 1 ? 2 : 1) * (size_t)ff;
+      lp.c1 = cv.take<float>(2 * n1); lp.c2 = base ? lp.c1 + n1 : nullptr;
       lp.cx1 = e ? cv.take<float>(dd) : nullptr;
-      lp.q1 = cv.take<float>(3 * dd); lp.q2 = cv.take<float>(3 * dd);
+      lp.q1 = cv.take<float>(6 * dd); lp.q2 = base ? lp.q1 + 3 * dd : nullptr;
     }
     x->nstats = cv.take<float2>(std::min(x->R_pad, 128) * (d / 16));   // steps of up to 128 rows hand norms over
     x->p_lm_head = cv.take<bf16_t>((size_t)x->vocab_pad * d);

@@ -60,6 +60,61 @@ __device__ __forceinline__ void st_f32(float *p, size_t i, float v) { p[i] = v; 
 __device__ __forceinline__ void st_f32(bf16_t *p, size_t i, float v) { p[i] = f32_to_bf16(v); }
 
 // ---------------------------------------------------------------------------
+// Exchanges between the lanes of a wave in registers (all 64 lanes active): a lane permutation through LDS takes some 100
+// clocks, and the small kernels are chains of them (a wave reduction with its barrier 0.3 us); these take 8-12.
+// ---------------------------------------------------------------------------
+template <typename T> struct Halves { T lo, hi; };
+template <typename T> __device__ __forceinline__ T as_lane(uint32_t u) { return __builtin_bit_cast(T, u); }
+// the values of lane l & ~16 and of lane l | 16, in both of them
+template <typename T> __device__ __forceinline__ Halves<T> halves16(T v) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, v);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return Halves<T>{as_lane<T>(r[0]), as_lane<T>(r[1])};
+}
+// the values of lane l & ~32 and of lane l | 32
+template <typename T> __device__ __forceinline__ Halves<T> halves32(T v) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, v);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return Halves<T>{as_lane<T>(r[0]), as_lane<T>(r[1])};
+}
+// the value N lanes before, round the 16 lanes of the row (8: lane l ^ 8)
+template <int N, typename T> __device__ __forceinline__ T rotate16(T v) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, v);
+  return as_lane<T>(__builtin_amdgcn_update_dpp(0, u, 0x120 + N, 0xf, 0xf, true));
+}
+// f over the lanes that differ in bit 4, in bit 5, over the 16 of a row (halves first: a butterfly's order), over all 64
+template <typename T, typename F> __device__ __forceinline__ T fold16(T v, F f) { const Halves<T> h = halves16(v); return f(h.lo, h.hi); }
+template <typename T, typename F> __device__ __forceinline__ T fold32(T v, F f) { const Halves<T> h = halves32(v); return f(h.lo, h.hi); }
+template <typename T, typename F> __device__ __forceinline__ T fold_row(T v, F f) {
+  v = f(v, rotate16<8>(v)); v = f(v, rotate16<4>(v)); v = f(v, rotate16<2>(v));
+  return f(v, rotate16<1>(v));
+}
+template <typename T, typename F> __device__ __forceinline__ T fold_wave(T v, F f) { return fold_row(fold16(fold32(v, f), f), f); }
+struct Add { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
+struct Max {
+  __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); }
+  __device__ __forceinline__ int operator()(int a, int b) const { return max(a, b); }
+};
+struct Min { __device__ __forceinline__ int operator()(int a, int b) const { return min(a, b); } };
+// the larger of two (value, index) candidates, the lower index on ties
+__device__ __forceinline__ void keep_best(float &best, int &idx, float ov, int oi) {
+  if (ov > best || (ov == best && oi < idx)) { best = ov; idx = oi; }
+}
+__device__ __forceinline__ void best16(float &best, int &idx) {
+  const Halves<float> v = halves16(best); const Halves<int> i = halves16(idx);
+  best = v.lo; idx = i.lo; keep_best(best, idx, v.hi, i.hi);
+}
+__device__ __forceinline__ void best32(float &best, int &idx) {
+  const Halves<float> v = halves32(best); const Halves<int> i = halves32(idx);
+  best = v.lo; idx = i.lo; keep_best(best, idx, v.hi, i.hi);
+}
+__device__ __forceinline__ void best_wave(float &best, int &idx) {
+  best32(best, idx); best16(best, idx);
+  keep_best(best, idx, rotate16<8>(best), rotate16<8>(idx)); keep_best(best, idx, rotate16<4>(best), rotate16<4>(idx));
+  keep_best(best, idx, rotate16<2>(best), rotate16<2>(idx)); keep_best(best, idx, rotate16<1>(best), rotate16<1>(idx));
+}
+
+// ---------------------------------------------------------------------------
 // per-row tables written by the schedule tick (decode) or the prefill set-up.
 // Row r of a launch belongs to request row_req[r]; invalid rows have flags == 0.
 // ---------------------------------------------------------------------------

@@ -267,13 +267,18 @@ __global__ __launch_bounds__(1024) void k_row_nll(float *nll, const float *logit
     e = (m == -INFINITY ? 0.f : e * expf(m - mx)) + (om == -INFINITY ? 0.f : oe * expf(om - mx));
     m = mx;
   };
-  for (int o = 32; o > 0; o >>= 1) merge(__shfl_xor(m, o), __shfl_xor(e, o));
+  auto merge_halves = [&](Halves<float> om, Halves<float> oe) { m = om.lo; e = oe.lo; merge(om.hi, oe.hi); };
+  merge_halves(halves32(m), halves32(e));
+  merge_halves(halves16(m), halves16(e));
+  merge(rotate16<8>(m), rotate16<8>(e)); merge(rotate16<4>(m), rotate16<4>(e));
+  merge(rotate16<2>(m), rotate16<2>(e)); merge(rotate16<1>(m), rotate16<1>(e));
   if ((threadIdx.x & 63) == 0) { sh_m[threadIdx.x >> 6] = m; sh_e[threadIdx.x >> 6] = e; }
   __syncthreads();
   if (threadIdx.x >= 64) return;
   m = threadIdx.x < 16 ? sh_m[threadIdx.x] : -INFINITY;
   e = threadIdx.x < 16 ? sh_e[threadIdx.x] : 0.f;
-  for (int o = 8; o > 0; o >>= 1) merge(__shfl_xor(m, o), __shfl_xor(e, o));
+  merge(rotate16<8>(m), rotate16<8>(e)); merge(rotate16<4>(m), rotate16<4>(e));
+  merge(rotate16<2>(m), rotate16<2>(e)); merge(rotate16<1>(m), rotate16<1>(e));
   if (threadIdx.x == 0) nll[r] = m + logf(e) - row[t];
 }
 
@@ -283,7 +288,7 @@ __global__ __launch_bounds__(64) void k_loss_sum(double *loss, const float *nll,
   double acc = 0.0;
   for (int t = 0; t < A; t += 64) {
     const float v = t + lane < A ? nll[(size_t)blockIdx.x * A + t + lane] : 0.f;
-    for (int l = 0; l < 64; ++l) acc += (double)__shfl(v, l);
+    for (int l = 0; l < 64; ++l) acc += (double)__uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), l));
   }
   if (lane == 0) loss[blockIdx.x] = acc;
 }
@@ -371,12 +376,7 @@ __global__ __launch_bounds__(1024) void k_commit(SchedState st, const float *par
       for (int u = 0; u < 8; ++u)
         if (v[u] > best || (v[u] == best && ix[u] < bi)) { best = v[u]; bi = ix[u]; }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      float ov = __shfl_xor(best, o);
-      int oi = __shfl_xor(bi, o);
-      if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
-    }
+    best_wave(best, bi);
     if (lane == 0) {
       if (share == 1) s_arg[a] = bi;
       else { s_best[wave] = best; s_idx[wave] = bi; }

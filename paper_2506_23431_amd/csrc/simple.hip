@@ -48,7 +48,7 @@ __device__ __forceinline__ floatx4 mfma_f32(float a, float b, floatx4 c) {
 // norm: xn[r] = LayerNorm(x[r]) or RMSNorm(x[r]); one block per row
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float block_sum(float v, float *sh) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  v = fold_wave(v, Add());
   int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
   __syncthreads();
   if ((threadIdx.x & 63) == 0) sh[w] = v;
@@ -188,9 +188,8 @@ __global__ __launch_bounds__(64 * NW) void k_lin(LinArgs a) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) s[i] += 4 * (lane + 64 * v) + e < K ? xv[i][v][e] : 0.f;
     }
-    for (int o = 32; o > 0; o >>= 1)
 #pragma unroll
-      for (int i = 0; i < RPW; ++i) s[i] += __shfl_xor(s[i], o);
+    for (int i = 0; i < RPW; ++i) s[i] = fold_wave(s[i], Add());
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
       s[i] /= K;
@@ -200,9 +199,8 @@ __global__ __launch_bounds__(64 * NW) void k_lin(LinArgs a) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) { const float t = xv[i][v][e] - s[i]; q[i] += 4 * (lane + 64 * v) + e < K ? t * t : 0.f; }
     }
-    for (int o = 32; o > 0; o >>= 1)
 #pragma unroll
-      for (int i = 0; i < RPW; ++i) q[i] += __shfl_xor(q[i], o);
+    for (int i = 0; i < RPW; ++i) q[i] = fold_wave(q[i], Add());
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
       const float rstd = rsqrtf(q[i] / K + a.eps);
@@ -279,12 +277,8 @@ __global__ __launch_bounds__(64 * NW) void k_lin(LinArgs a) {
           if (dst) dst[n + j] = y[j];
           if (y[j] > best) { best = y[j]; bi = n + j; }
         }
-#pragma unroll
-      for (int o = 16; o <= 32; o <<= 1) {            // the tile's winner, lowest index on ties
-        const float ov = __shfl_xor(best, o);
-        const int oi = __shfl_xor(bi, o);
-        if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
-      }
+      best16(best, bi);                               // the tile's winner, lowest index on ties
+      best32(best, bi);
       if (g == 0 && in) {
         a.part_val[(size_t)r * a.n_tiles + blockIdx.x] = best;
         a.part_idx[(size_t)r * a.n_tiles + blockIdx.x] = bi;
@@ -439,7 +433,7 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(AttnF32Args a) {
   const int lim = valid ? min(qi.z, n) : 0, sub = valid ? qi.y : -1;
   // keys some query of the group sees
   int reach = valid ? (n > a.L && sub >= 1 ? n : lim) : 0;
-  for (int o = 1; o < 16; o <<= 1) reach = max(reach, __shfl_xor(reach, o));
+  reach = fold_row(reach, Max());
   const int tiles = __builtin_amdgcn_readfirstlane((reach + 15) >> 4);
   const size_t base = ((size_t)req * a.H + h) * a.kv_cap * hd;
   const KT *K = (const KT *)a.kc + base, *V = (const KT *)a.vc + base;
@@ -492,8 +486,7 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(AttnF32Args a) {
       s[j] = vis ? s[j] * a.scale : -INFINITY;
       mloc = fmaxf(mloc, s[j]);
     }
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+    mloc = fold32(fold16(mloc, Max()), Max());
     const float m_new = fmaxf(m_run, mloc);
     const float m_ref = m_new == -INFINITY ? 0.f : m_new;      // nothing visible yet: exp(-inf) = 0, never NaN
     const float alpha = expf(m_run - m_ref);
@@ -511,8 +504,7 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(AttnF32Args a) {
       for (int i = 0; i < NHB; ++i)       // (slots past the last key hold what an earlier request left there)
         o_acc[i] = mfma_f32(key0 + 4 * g + e < n ? vf[i][e] : 0.f, p[e], o_acc[i]);
   }
-  l_run += __shfl_xor(l_run, 16);
-  l_run += __shfl_xor(l_run, 32);
+  l_run = fold32(fold16(l_run, Add()), Add());
   if (g == 0) { sm_m[w][m] = m_run; sm_l[w][m] = l_run; }
 #pragma unroll
   for (int i = 0; i < NHB; ++i) sm_o[w][i][lane] = o_acc[i];
