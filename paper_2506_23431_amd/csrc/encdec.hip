@@ -140,7 +140,8 @@ int encdec_decoder_layer(pd_ctx *c, int l, int R, hipStream_t s, int A, int nreq
   int rc;
   // (the previous layer's second FFN projection may have prepared this norm)
   const bool first = c->norm_fused;
-  if (!first && (rc = mfma_norm(c, lw.n1g, nullptr, R, s))) return rc;
+  if (!first && !c->embedded && (rc = mfma_norm(c, lw.n1g, nullptr, R, s))) return rc;
+  c->embedded = false;
   GemmArgs a;
   mfma_gemm_base(c, a, R);
   if ((rc = mfma_qkv(c, a, lw.p_wqkv, 3 * d / 16, 0, lw.kc, lw.vc, nullptr, nullptr, R, s, first ? lw.q1 : nullptr))) return rc;

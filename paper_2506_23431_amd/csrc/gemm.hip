@@ -417,12 +417,16 @@ struct ResidPre { float4 x, g; };
 // ... and for a projection that finishes a norm: c1 and c2 at the tile's columns
 struct NormPre { float4 c1, c2; };
 
+// EPI_LM: the best value of a row so far and its column, in every lane of the row
+struct Winner { float best; int idx; };
+constexpr int NO_WINNER = 0x7fffffff;
+
 // NORMED: instances that can finish a norm (nrm is looked at); the others carry none of its code
 template <int RT, int EPI, bool NORMED = false>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, int nt, const floatx4 (&acc_in)[RT],
                                               const int4 *kvi, int lane, int r0 = 0,
                                               const float2 *nrm = nullptr, const ResidPre *pre = nullptr,
-                                              const NormPre *npre = nullptr) {
+                                              const NormPre *npre = nullptr, Winner *win = nullptr) {
   int m = lane & 15, g = lane >> 4;
   int n0 = nt * 16 + 4 * g;
   floatx4 acc[RT];
@@ -574,10 +578,35 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, int nt, const f
       // across the 4 column groups of this row; lowest index wins ties
       best16(best, bi);
       best32(best, bi);
-      if (g == 0 && r < a.R) {      // row-major [row][tile]: the commit kernel reads a row's winners as one run
-        a.part_val[(size_t)r * a.n_tiles + nt] = best;
-        a.part_idx[(size_t)r * a.n_tiles + nt] = bi;
-      }
+      keep_best(win[i].best, win[i].idx, best, bi);
+    }
+  }
+}
+
+// One winner per row and block: W waves of the block hold one each.  (One per 16-column tile: the commit kernel, one block per
+// request, read 25 KB per row at 50265 words.)  Row-major [row][block]: it reads a row's winners as one run.
+template <int RT, int W>
+__device__ __forceinline__ void store_winners(const GemmArgs &a, const Winner (&win)[RT], int w, int lane, int r0) {
+  __shared__ Winner sm_win[W > 1 ? W : 1][RT * 16];
+  if (W > 1) {
+    if (w < W && lane < 16)
+#pragma unroll
+      for (int i = 0; i < RT; ++i) sm_win[w][i * 16 + lane] = win[i];
+    __syncthreads();
+    const int q = threadIdx.x, r = r0 + q;
+    if (q >= RT * 16 || r >= a.R) return;
+    Winner best = sm_win[0][q];
+#pragma unroll
+    for (int v = 1; v < W; ++v) keep_best(best.best, best.idx, sm_win[v][q].best, sm_win[v][q].idx);
+    a.part_val[(size_t)r * a.n_win + blockIdx.x] = best.best;
+    a.part_idx[(size_t)r * a.n_win + blockIdx.x] = best.idx;
+  } else if (w == 0 && lane < 16) {
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+      const int r = r0 + i * 16 + lane;
+      if (r >= a.R) continue;
+      a.part_val[(size_t)r * a.n_win + blockIdx.x] = win[i].best;
+      a.part_idx[(size_t)r * a.n_win + blockIdx.x] = win[i].idx;
     }
   }
 }
@@ -648,8 +677,10 @@ static int gemm_hot(const GemmArgs &a, GemmHot *h) {
   return PD_OK;
 }
 template <int EPI, typename Kernel>
-static int launch_gemm_kernel(Kernel kernel, dim3 grid, int threads, const GemmArgs &a, hipStream_t s) {
+static int launch_gemm_kernel(Kernel kernel, dim3 grid, int threads, GemmArgs a, hipStream_t s) {
   GemmHot h;
+  a.n_win = grid.x;
+  if (EPI == EPI_LM) *a.win_out = grid.x;
   const int rc = gemm_hot<EPI>(a, &h);
   if (rc) return rc;
   hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, h.w, h.x, h.a, h.b, h.c, h.lo, h.k, h.n, h.r, a);
@@ -739,6 +770,10 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(PD_GEMM_HOT_PARAMS, GemmAr
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[t][0][j] += rotate16<8>(acc[t][0][j]);
   }
+  Winner win[EPI == EPI_LM ? RT : 1];
+  if (EPI == EPI_LM)
+#pragma unroll
+    for (int i = 0; i < RT; ++i) win[i] = Winner{-INFINITY, NO_WINNER};
   if (NW_K > 1) {
     // every wave leaves its partial tiles in LDS; wave w then sums and finishes column tiles w, w + NW_K, ...
 #pragma unroll
@@ -766,8 +801,9 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(PD_GEMM_HOT_PARAMS, GemmAr
 #pragma unroll
         for (int i = 0; i < RT; ++i) sum[i] += red[((w * NT + t) * RT + i) * 64 + lane];
       gemm_epilogue<RT, EPI, FUSED_IN>(a, nt0 + t, sum, kvi, lane, rz * 16, fused_norm ? nrm : nullptr,
-                             (FUSED_OUT && t == wk) ? &pre_r : nullptr, (fused_norm && t == wk) ? &pre_n : nullptr);
+                             (FUSED_OUT && t == wk) ? &pre_r : nullptr, (fused_norm && t == wk) ? &pre_n : nullptr, win);
     }
+    if constexpr (EPI == EPI_LM) store_winners<RT, (NT < NW_K ? NT : NW_K)>(a, win, wk, lane, rz * 16);
   } else {
     float2 nrm[RT];
     if (fused_norm) nrm[0] = stats_finish(a, stats_partial((const float2 *)hot_a, KT, lane, 0, 1, pre_s, rz * 16));
@@ -775,7 +811,8 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(PD_GEMM_HOT_PARAMS, GemmAr
     for (int t = 0; t < NT; ++t)
       if (nt0 + t < n_tiles)
         gemm_epilogue<RT, EPI, FUSED_IN>(a, nt0 + t, acc[t], kvi, lane, rz * 16, fused_norm ? nrm : nullptr,
-                               (FUSED_OUT && t == 0) ? &pre_r : nullptr, (fused_norm && t == 0) ? &pre_n : nullptr);
+                               (FUSED_OUT && t == 0) ? &pre_r : nullptr, (fused_norm && t == 0) ? &pre_n : nullptr, win);
+    if constexpr (EPI == EPI_LM) store_winners<RT, 1>(a, win, 0, lane, rz * 16);
   }
 }
 
@@ -1105,9 +1142,14 @@ __global__ __launch_bounds__(512, 1) void k_gemm_t(PD_GEMM_HOT_PARAMS, GemmArgs 
 #pragma unroll
     for (int i = 0; i < RT; ++i) kvi[i] = ((const int4 *)hot_c)[r0 + i * 16 + m];
   }
+  Winner win[EPI == EPI_LM ? RT : 1];
+  if (EPI == EPI_LM)
+#pragma unroll
+    for (int i = 0; i < RT; ++i) win[i] = Winner{-INFINITY, NO_WINNER};
 #pragma unroll
   for (int t = 0; t < NT; ++t)
-    if (nt0 + t < n_tiles) gemm_epilogue<RT, EPI>(a, nt0 + t, acc[t], kvi, lane, r0);
+    if (nt0 + t < n_tiles) gemm_epilogue<RT, EPI>(a, nt0 + t, acc[t], kvi, lane, r0, nullptr, nullptr, nullptr, win);
+  if constexpr (EPI == EPI_LM) store_winners<RT, NW>(a, win, w, lane, r0);
 }
 
 template <int RT, int NT, int EPI, bool SPLIT>

@@ -124,9 +124,10 @@ int mfma_layer(pd_ctx *c, int l, int R, int A, int nreq, int req0, int kv_overri
   const pd_config &g = c->cfg;
   const LayerPtrs &lw = c->layers[l];
   int rc;
-  // the previous layer's second FFN projection may have prepared this norm already
+  // the previous layer's second FFN projection may have prepared this norm already, or the step's tick
   const bool finish = c->norm_fused;
-  if (!finish && (rc = mfma_norm(c, lw.n1g, lw.n1b, R, s))) return rc;
+  if (!finish && !c->embedded && (rc = mfma_norm(c, lw.n1g, lw.n1b, R, s))) return rc;
+  c->embedded = false;
   GemmArgs a;
   mfma_gemm_base(c, a, R);
   // QKV projection (+ rotary) + KV append
@@ -153,6 +154,7 @@ int mfma_head(pd_ctx *c, int R, float *logits, hipStream_t s, int tf_A, int tf_c
   a.n_tiles = c->vocab_pad / 16; a.V = g.vocab;
   a.logits = logits; a.logits_A = tf_A; a.logits_cap = tf_A > 0 ? tf_cap : c->S; a.ld_logits = g.vocab;
   a.part_val = c->lm_part_val; a.part_idx = c->lm_part_idx;
-  // leaves one winner per 16-column tile; the commit kernel picks the winner of each row
+  a.win_out = &c->lm_win;
+  // leaves one winner per block of columns; the commit kernel picks the winner of each row
   return mfma_gemm(EPI_LM, a, R, s);
 }

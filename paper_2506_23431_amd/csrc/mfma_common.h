@@ -122,7 +122,8 @@ struct GemmArgs {
   // EPI_LM: optional logits of the rows that carry a token, [request][logits_cap][ld_logits]: a row's place is its
   // subsequence or, logits_A > 0 (logits_A rows per request), its place among the request's rows
   float *logits; int V, ld_logits, logits_cap, logits_A;
-  float *part_val; int32_t *part_idx;  // EPI_LM: [16*RT][n_tiles] best value / index per tile
+  float *part_val; int32_t *part_idx;  // EPI_LM: [rows][n_win] best value / index of a block's columns
+  int n_win; int *win_out;             // blocks of the launch (set by it)
   // EPI_RESID_NORM (at most 16 rows, K not cut over blocks): x_res += y in place, out_bf / out_lo receive
   // gain * x_res as activation fragments, stats_out[row][tile] the sum and the sum of squares of x_res
   // over the tile's 16 columns

@@ -259,7 +259,7 @@ __global__ void k_fill_zero(uint4 *p, size_t n16) {
 // the workspace, re-packing the weights.  `c` has its configuration, pointers and carve-up.
 static int finish_create(pd_ctx *c, size_t need, void *hip_stream, bool no_alloc, pd_ctx **out) {
   c->prefilled = false; c->host_steps = 0;
-  c->embed_pending = false; c->norm_fused = false; c->packed = false;
+  c->embed_pending = false; c->embedded = false; c->norm_fused = false; c->packed = false;
   c->opt_splits = 0; c->opt_graph = 0; c->opt_profile = 0; c->opt_split = 1; c->opt_chunk = 0; c->opt_fuse_norm = 1;
   c->opt_ctx_split = 1; c->opt_ctx_attn = 1;
   c->graph_exec = nullptr; c->graph_ready = false; c->ev_used = 0; c->h_pinned = nullptr;
@@ -280,7 +280,7 @@ static int finish_create(pd_ctx *c, size_t need, void *hip_stream, bool no_alloc
   }
   hipStream_t s = (hipStream_t)hip_stream;
   auto fail = [&](int code) { (void)pd_destroy(c); return code; };
-  const size_t n_stage = 2 * (size_t)c->cfg.max_batch * c->cfg.max_sub + 16;
+  const size_t n_stage = 2 * (size_t)c->cfg.max_batch * c->cfg.max_sub + c->cfg.max_batch + 16;
   hipError_t e = hipSuccess;
   c->stage_pinned = !no_alloc;
   if (no_alloc) {
@@ -561,9 +561,9 @@ extern "C" int pd_get_info(pd_ctx *c, int key, void *hip_stream, int64_t *value)
 static int run_layers(pd_ctx *c, int R, int A, int nreq, int req0, int kv_override,
                       hipStream_t s) {
   int rc;
-  // matrix-core path: the first norm kernel gathers the rows itself; fp32 path: the first projection does, launches
+  // matrix-core path: the first norm kernel gathers the rows itself (or the tick has); fp32 path: the first projection does, launches
   // of many rows have them embedded
-  if (c->impl == 1) c->embed_pending = true;
+  if (c->impl == 1) c->embed_pending = !c->embedded;
   else if (simple_embeds(c, R) && (rc = launch_embed(c, R, s))) return rc;
   c->pend_parts = 0;
   c->norm_fused = false;
@@ -677,32 +677,45 @@ static int rows_bound(const pd_ctx *c, int64_t t) {
   return std::min(n, c->A);
 }
 
-static int enqueue_step(pd_ctx *c, float *out_logits, hipStream_t s) {
-  int rc;
-  if ((rc = launch_tick(c, s))) return rc;
-  // Row indices in use this step: b * A + a.  When they all stay below 8 the matrix-core path keeps
-  // every activation as a packed pair (half the fragments and multiplies in the projections).  A
-  // captured graph is replayed for every step, so it keeps the general layout.
-  int R = c->R;
+// Row indices in use at step t: b * A + a.  When they all stay below 8 the matrix-core path keeps
+// every activation as a packed pair (half the fragments and multiplies in the projections).  A
+// captured graph is replayed for every step, so it keeps the general layout.
+struct StepRows { int R; bool packed; };
+static StepRows step_rows(const pd_ctx *c, int64_t t) {
   if (c->impl == 1 && c->opt_split && !c->opt_graph) {
-    int r_used = c->B == 1 ? rows_bound(c, (int64_t)c->host_steps + 1) : c->R;
-    if (r_used <= 8) { c->packed = true; R = std::min(R, std::max(r_used, 1)); }
+    const int used = c->B == 1 ? rows_bound(c, t) : c->R;
+    if (used <= 8) return StepRows{std::min(c->R, std::max(used, 1)), true};
   }
-  rc = run_layers(c, R, c->A, c->B, 0, -1, s);
-  if (!rc) rc = c->impl == 1 ? mfma_head(c, R, out_logits, s) : simple_head(c, R, out_logits, s);
-  c->packed = false;
-  if (rc) return rc;
-  return launch_commit(c, s);
+  return StepRows{c->R, false};
 }
 
-// One step, optionally replayed from a captured graph (only without logits output
-// and without profiling events, which cannot be recorded into a graph here).
-static int run_step(pd_ctx *c, float *out_logits, hipStream_t s) {
-  if (!c->opt_graph || out_logits || c->opt_profile) return enqueue_step(c, out_logits, s);
+// What a step exchanges with the host: tokens that replace the selected ones, logits, tokens and ended requests (NULL: none).
+struct StepIO { const int32_t *force; float *logits; int32_t *tok, *done; };
+
+// `ticked`: the launch that ended the step before has begun this one; `more`: the next step is enqueued right behind this
+// one, so that the launch that ends this one begins it.
+static int enqueue_step(pd_ctx *c, const StepIO &io, bool ticked, bool more, hipStream_t s) {
+  int rc;
+  const int64_t t = (int64_t)c->host_steps + 1;
+  const StepRows now = step_rows(c, t);
+  if (!ticked && (rc = launch_turn(c, false, true, now.packed, nullptr, nullptr, nullptr, s))) return rc;
+  c->packed = now.packed;
+  c->embedded = turn_embeds(c);
+  rc = run_layers(c, now.R, c->A, c->B, 0, -1, s);
+  c->embedded = false;
+  if (!rc) rc = c->impl == 1 ? mfma_head(c, now.R, io.logits, s) : simple_head(c, now.R, io.logits, s);
+  c->packed = false;
+  if (rc) return rc;
+  return launch_turn(c, true, more, more && step_rows(c, t + 1).packed, io.force, io.tok, io.done, s);
+}
+
+// One step replayed from a captured graph.
+static int replay_step(pd_ctx *c, hipStream_t s) {
   if (!c->graph_ready) {
     hipGraph_t graph = nullptr;
     PD_CHECK_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-    int rc = enqueue_step(c, nullptr, s);
+    // (the captured commit looks at the device copy of the forced tokens, which steps without any leave at -1)
+    int rc = enqueue_step(c, StepIO{c->sch.force, nullptr, nullptr, nullptr}, false, false, s);
     hipError_t e = hipStreamEndCapture(s, &graph);
     if (rc) { if (graph) (void)hipGraphDestroy(graph); return rc; }
     PD_CHECK_HIP(e);
@@ -714,6 +727,8 @@ static int run_step(pd_ctx *c, float *out_logits, hipStream_t s) {
   PD_CHECK_HIP(hipGraphLaunch(c->graph_exec, s));
   return PD_OK;
 }
+// (without logits output and without profiling events, which cannot be recorded into a graph here)
+static bool replays(const pd_ctx *c, const float *out_logits) { return c->opt_graph && !out_logits && !c->opt_profile; }
 
 extern "C" int pd_decode_step(pd_ctx *c, const int32_t *force_tokens, int32_t *out_tokens,
                               float *out_logits, int32_t *out_all_done, void *hip_stream) {
@@ -725,22 +740,33 @@ extern "C" int pd_decode_step(pd_ctx *c, const int32_t *force_tokens, int32_t *o
     for (size_t i = 0; i < bs; ++i)
       PD_REQUIRE(force_tokens[i] < c->cfg.vocab, PD_EINVAL, "force token %zu = %d out of range", i,
                  force_tokens[i]);
-    // the staging buffer may still be in flight from the previous call
+    // the staging buffer may still be in use by the previous call
     PD_CHECK_HIP(hipStreamSynchronize(s));
     memcpy(c->h_pinned, force_tokens, bs * sizeof(int32_t));
-    PD_CHECK_HIP(hipMemcpyAsync(c->sch.force, c->h_pinned, bs * sizeof(int32_t),
-                                hipMemcpyHostToDevice, s));
   }
-  int rc = run_step(c, out_logits, s);
+  // Tokens, forced and appended, pass through mapped host memory that the step's last launch reads and writes itself; a
+  // replayed step and a context without such memory copy them.
+  int32_t *h_tok = c->h_pinned + bs, *h_done = c->h_pinned + 2 * bs;
+  const bool replay = replays(c, out_logits), mapped = c->stage_pinned && !replay, outputs = out_tokens || out_all_done;
+  if (force_tokens && !mapped)
+    PD_CHECK_HIP(hipMemcpyAsync(c->sch.force, c->h_pinned, bs * sizeof(int32_t), hipMemcpyHostToDevice, s));
+  StepIO io{nullptr, out_logits, nullptr, nullptr};
+  if (force_tokens) io.force = mapped ? c->h_pinned : c->sch.force;
+  if (mapped && outputs) { io.tok = h_tok; io.done = h_done; }
+  int rc = replay ? replay_step(c, s) : enqueue_step(c, io, false, false, s);
   if (rc) return rc;
   c->host_steps++;
-  if (out_tokens || out_all_done) {
-    int32_t *h_tok = c->h_pinned + bs, *h_done = c->h_pinned + 2 * bs;
-    PD_CHECK_HIP(hipMemcpyAsync(h_tok, c->sch.step_tok, bs * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    PD_CHECK_HIP(hipMemcpyAsync(h_done, c->sch.all_done, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+  if (outputs) {
+    int ended = 0;
+    if (!mapped) {
+      PD_CHECK_HIP(hipMemcpyAsync(h_tok, c->sch.step_tok, bs * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+      PD_CHECK_HIP(hipMemcpyAsync(h_done, c->sch.all_done, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    }
     PD_CHECK_HIP(hipStreamSynchronize(s));
+    for (int b = 0; b < c->B && mapped; ++b) ended += h_done[b];
+    if (!mapped) ended = *h_done;
     if (out_tokens) memcpy(out_tokens, h_tok, bs * sizeof(int32_t));
-    if (out_all_done) *out_all_done = (*h_done >= c->B) ? 1 : 0;
+    if (out_all_done) *out_all_done = ended >= c->B ? 1 : 0;
   }
   return PD_OK;
 }
@@ -749,8 +775,12 @@ extern "C" int pd_decode_steps(pd_ctx *c, int n_steps, void *hip_stream) {
   PD_REQUIRE(c, PD_EINVAL, "ctx is NULL");
   PD_REQUIRE(c->prefilled, PD_ESTATE, "pd_decode_steps before pd_prefill_context");
   PD_REQUIRE(n_steps >= 0, PD_EINVAL, "n_steps must be >= 0");
+  // (one launch ends a step and begins the next; the state between calls is that of a step that has ended)
+  const bool replay = replays(c, nullptr), joined = c->S <= 1024;
   for (int i = 0; i < n_steps; ++i) {
-    int rc = run_step(c, nullptr, (hipStream_t)hip_stream);
+    int rc = replay ? replay_step(c, (hipStream_t)hip_stream)
+                    : enqueue_step(c, StepIO{nullptr, nullptr, nullptr, nullptr}, joined && i > 0, joined && i + 1 < n_steps,
+                                   (hipStream_t)hip_stream);
     if (rc) return rc;
     c->host_steps++;
   }
@@ -869,7 +899,7 @@ extern "C" int pd_generate(pd_ctx *c, const int32_t *ctx_tokens, int B, int L, i
     finished = (*h_done >= B) || t >= bound;
   }
   if (bound == 0) {            // time_max == 0: one tick marks the requests terminated
-    if ((rc = launch_tick(c, s))) return rc;
+    if ((rc = launch_turn(c, false, true, false, nullptr, nullptr, nullptr, s))) return rc;
   }
   std::vector<int32_t> grid((size_t)B * S * (M + 1)), ntok((size_t)B * S), fin((size_t)B * S), steps(B);
   PD_CHECK_HIP(hipMemcpyAsync(grid.data(), c->sch.grid, grid.size() * 4, hipMemcpyDeviceToHost, s));

@@ -223,11 +223,13 @@ struct pd_ctx : RowSet {    // (the set in use: decode steps, passes over one re
   bool packed;              // this launch sequence keeps activations as packed pairs (at most 8 rows):
                             // high parts in rows 0-7 of a 16-row fragment, low parts in rows 8-15
   bool embed_pending;       // matrix-core path: the next norm kernel gathers x from the embedding tables
+  bool embedded;            // the step's tick has gathered x and left its first norm in xn
   int stream_loads;         // 1: a decode step touches more bytes than the last-level cache holds: weights, keys and
                             // values are loaded with the non-temporal hint (PD_OPT_STREAM_LOADS)
   bool norm_fused;          // the last residual projection left gain * x and per-tile row sums for the next
                             // norm: the projection that follows finishes it, no norm kernel runs
-  int lm_parts;
+  int lm_parts;             // winners per row the buffers have room for
+  int lm_win;               // winners per row the last vocabulary projection left
   float *rope_cs;           // [max_pos][hd/2][2] cos, sin
   int rope_rows;
   SchedState sch;
@@ -256,10 +258,12 @@ struct pd_ctx : RowSet {    // (the set in use: decode steps, passes over one re
 // ---- launchers (each returns PD_OK or an error code) -----------------------
 // schedule / glue (sched.hip)
 int launch_reset_state(pd_ctx *c, hipStream_t s);
-int launch_tick(pd_ctx *c, hipStream_t s);
+// end of a step (commit), start of the next (tick), or both in one launch; see k_turn.  packed: layout of the step that begins
+int launch_turn(pd_ctx *c, bool commit, bool tick, bool packed, const int32_t *force, int32_t *out_tok, int32_t *out_done,
+                hipStream_t s);
+bool turn_embeds(const pd_ctx *c);
 int launch_prefill_rows(pd_ctx *c, int b, int p0, int n, hipStream_t s, int L, int bidir, int b_cache, int nreq = 1);
 int launch_embed(pd_ctx *c, int R, hipStream_t s);
-int launch_commit(pd_ctx *c, hipStream_t s);
 int launch_teacher_rows(pd_ctx *c, const int32_t *tgt_dev, int b, int nreq, int A, int ML, hipStream_t s);
 int launch_row_nll(pd_ctx *c, const float *logits, int nreq, int A, int cap, double *loss_dev, hipStream_t s);
 int launch_rope_table(pd_ctx *c, hipStream_t s);

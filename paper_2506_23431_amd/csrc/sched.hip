@@ -30,102 +30,6 @@ int launch_reset_state(pd_ctx *c, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// tick: Algorithm 1 lines 5-7 plus the row list of this time-step.
-// One wave per request: lane i looks after subsequences i, i + 64, ...; rows are numbered in
-// subsequence order with a ballot and a population count.
-// A subsequence has a row when it holds a token that was not fed yet: its newest
-// token (coordinate tau = t).  A subsequence that finished in the previous step is
-// fed once more so that its last token enters the KV cache; that row selects no token.
-// ---------------------------------------------------------------------------
-// Encoder-decoder form (qinfo_x != NULL): L is 0 (the decoder's own cache holds generated tokens only);
-// every row also gets an entry of a second table for the attention over the Lx encoder states, and
-// every new key slot its grid coordinate (t - 1) + (i - 1), whose difference between a query and a
-// visible key is their Manhattan distance (Section 4.3).
-__global__ __launch_bounds__(64) void k_tick(SchedState st, RowTables rt, int S, int dt, int M, int L, int A,
-                                             int time_max, int bos, int gen_cap, int gen_stride,
-                                             uint16_t *gen_coord, int4 *qinfo_x, int Lx) {
-  // one wave per request: lane i looks after subsequences i, i + 64, ...
-  __shared__ int s_k, s_t;
-  const int b = blockIdx.x, lane = threadIdx.x;
-  for (int a = lane; a < A; a += 64) {
-    rt.flags[b * A + a] = 0;
-    rt.qinfo[b * A + a] = make_int4(0, -1, 0, b);
-    rt.kvinfo[b * A + a] = make_int4(0, b, 0, 0);
-    if (qinfo_x) qinfo_x[b * A + a] = make_int4(0, -1, 0, b);
-  }
-  for (int i = lane; i < S; i += 64) { st.row_of[b * S + i] = -1; st.step_tok[b * S + i] = -1; }
-  if (lane == 0) {
-    st.n_rows[b] = 0;
-    int k = -1, t = 0;
-    if (!st.done[b]) {
-      t = st.step[b] + 1;
-      if (t > time_max) {          // only reachable with time_max == 0
-        st.done[b] = 1;
-        atomicAdd(st.all_done, 1);
-      } else {
-        st.step[b] = t;
-        k = st.k_open[b];
-        if ((t - 1) % dt == 0 && k < S) {      // Algorithm 1, lines 5-7: open subsequence k + 1
-          st.grid[(size_t)(b * S + k) * (M + 1)] = bos;
-          st.n_tok[b * S + k] = 1; st.n_fed[b * S + k] = 0; st.fin[b * S + k] = 0;
-          ++k;
-          st.k_open[b] = k;
-        }
-      }
-    }
-    s_k = k; s_t = t;
-  }
-  __syncthreads();
-  const int k = s_k, t = s_t;
-  if (k < 0) return;
-  // rows in subsequence order: the first min(A, free slots) subsequences that hold an unfed token
-  const int ng = st.n_gen[b];
-  int a_base = 0;
-  for (int i0 = 0; i0 < k; i0 += 64) {
-    int i = i0 + lane;
-    int nt = 0, fin = 0;
-    bool has = false;
-    if (i < k) {
-      nt = st.n_tok[b * S + i];
-      fin = st.fin[b * S + i];
-      has = nt > st.n_fed[b * S + i];
-    }
-    unsigned long long m = __ballot(has);
-    int a = a_base + __popcll(m & ((1ull << lane) - 1));
-    if (has && a < A && ng + a < gen_cap) {
-      int r = b * A + a, fl = ROW_VALID | (fin ? 0 : ROW_PRODUCE);
-      rt.req[r] = b; rt.sub[r] = i + 1;
-      rt.tok[r] = st.grid[(size_t)(b * S + i) * (M + 1) + nt - 1];
-      rt.pos[r] = L + (t - 1) + i;
-      rt.slot[r] = L + ng + a;
-      rt.lim[r] = L;
-      rt.flags[r] = fl;
-      rt.qinfo[r] = make_int4(fl, i + 1, L, b);
-      rt.kvinfo[r] = make_int4(fl, b, L + ng + a, L + (t - 1) + i);
-      st.gen_sub[(size_t)b * gen_stride + (L & 7) + ng + a] = (uint16_t)(i + 1);
-      if (qinfo_x) {
-        qinfo_x[r] = make_int4(fl, 0, Lx, b);
-        gen_coord[(size_t)b * gen_stride + ng + a] = (uint16_t)((t - 1) + i);
-      }
-      st.n_fed[b * S + i] = nt;
-      st.row_of[b * S + i] = r;
-    }
-    a_base += __popcll(m);
-  }
-  if (lane == 0) {
-    int a = min(a_base, min(A, max(gen_cap - ng, 0)));
-    st.n_gen[b] = ng + a; st.kv_len[b] = L + ng + a; st.n_rows[b] = a;
-  }
-}
-
-int launch_tick(pd_ctx *c, hipStream_t s) {
-  hipLaunchKernelGGL(k_tick, dim3(c->B), dim3(64), 0, s, c->sch, c->rows, c->S, c->dt, c->M, c->L,
-                     c->A, c->time_max, c->cfg.bos_id, c->gen_cap, c->gen_stride, c->gen_coord, c->qinfo_x, c->Lx);
-  PD_CHECK_HIP(hipGetLastError());
-  return PD_OK;
-}
-
-// ---------------------------------------------------------------------------
 // prefill rows: context tokens p0 .. p0+n-1 of each of nreq requests from b on, n rows per request.
 // Row for position p sees the keys 0..p (causal prefix), nothing generated; with `bidir` (rows of a
 // bidirectional encoder) all L keys.  Keys and values of the rows go to cache entry `b_cache` (+ the
@@ -334,105 +238,307 @@ int launch_embed(pd_ctx *c, int R, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// commit: Algorithm 1 lines 9-13 for one request per block.
+// The turn from one time-step to the next, one block of 16 waves per request, in any of its parts:
+//   COMMIT  the end of step t: Algorithm 1 lines 9-13
+//   TICK    the start of step t + 1: lines 5-7 and the row list of the step.  A subsequence has a row when it holds a token that
+//           was not fed yet: its newest token (coordinate tau = t).  A subsequence that finished in the step before is fed
+//           once more so that its last token enters the KV cache; that row selects no token.  Rows in subsequence order,
+//           the first min(A, free slots) of them.
+//   NGW > 0 the first norm of step t + 1: x = E_tok[token] (+ E_pos[position]) of every row and its norm, a wave per row (at
+//           most 512 NGW values, TURN_ROWS rows per request)
+// In the middle of a run all three are one launch: a chain of dependent reads through one compute unit, where each launch of
+// its own cost its boundary and its way from and to memory again (width 768, 8 rows, 50265 words: commit, tick and norm
+// 7.0 + 3.8 + 4.6 us, together 10.0; width 2048, commit and tick 6.3 + 4.1, together 7.4).
+// Encoder-decoder form (qinfo_x != NULL): L is 0 (the decoder's own cache holds generated tokens only);
+// every row also gets an entry of a second table for the attention over the Lx encoder states, and
+// every new key slot its grid coordinate (t - 1) + (i - 1), whose difference between a query and a
+// visible key is their Manhattan distance (Section 4.3).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void k_commit(SchedState st, const float *part_val, const int32_t *part_idx,
-                                                 int n_tiles, int S, int M, int A, int time_max, int eos, int V) {
-  // Everything the block needs is requested at once, before the first use, so that the kernel costs
-  // about one memory round trip: the schedule state of the request, and the winners of the vocabulary
-  // tiles of every row, whether or not the row selects a token.
-  __shared__ int s_arg[1024];           // s_arg[a]: argmax of row a of this request (a < A <= 1024)
+constexpr int TURN_ROWS = 32;
+
+struct TurnArgs {
+  SchedState st; RowTables rt;
+  int dt, M, L, time_max, bos, eos, V, gen_cap, gen_stride, Lx;
+  uint16_t *gen_coord; int4 *qinfo_x;
+  const int32_t *force;      // tokens that replace the selected ones where >= 0 (device or mapped host memory), or NULL
+  int32_t *out_tok, *out_done;   // mapped host memory for the tokens appended and the requests that have ended, or NULL
+  const bf16_t *tok_emb, *pos_emb; const float *g, *b;
+  int d, kind, row_end; float eps;   // row_end: rows the layout of the activations has room for
+  float *x; bf16_t *xn, *xn_lo;
+};
+
+template <bool COMMIT, bool TICK, int NGW>
+__global__ __launch_bounds__(1024) void k_turn(const float *part_val, const int32_t *part_idx, const int32_t *row_of,
+                                               const int32_t *n_tok, const int32_t *fin_of, const int32_t *n_fed,
+                                               int n_win, uint32_t sa, TurnArgs a) {
+  const SchedState &st = a.st;
+  const RowTables &rt = a.rt;
+  const int S = sa >> 16, A = sa & 0xffff;
+  __shared__ int s_arg[COMMIT ? 1024 : 1];            // s_arg[a]: argmax of row a of this request (a < A <= 1024)
   __shared__ float s_best[16];
-  __shared__ int s_idx[16];
-  const int b = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nwave = blockDim.x >> 6;
-  const int done = st.done[b], t = st.step[b], k = st.k_open[b];
+  __shared__ int s_idx[16], s_cnt[16];
+  __shared__ int s_tok[NGW ? TURN_ROWS : 1], s_pos[NGW ? TURN_ROWS : 1];
+  const int b = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  // Everything the block needs is requested at once, before the first use: the schedule state of the request, and the
+  // winners of the vocabulary's groups of columns of every row, whether or not the row selects a token.
   const int i0 = threadIdx.x;           // subsequence of this thread in the first pass
-  int r0 = -1, fin0 = 0, f0 = -1, nt0 = 0;
+  int r0 = -1, fin0 = 0, f0 = -1, nt0 = 0, fed0 = 0;
   if (i0 < S) {
-    r0 = st.row_of[b * S + i0]; fin0 = st.fin[b * S + i0]; f0 = st.force[b * S + i0];
-    nt0 = st.n_tok[b * S + i0];
+    if (COMMIT) r0 = row_of[b * S + i0];
+    fin0 = fin_of[b * S + i0];
+    nt0 = n_tok[b * S + i0];
+    if (TICK) fed0 = n_fed[b * S + i0];
+    if (COMMIT && a.force) f0 = a.force[b * S + i0];
   }
-  // stage 1: second stage of the argmax, `share` waves per row; lowest index wins ties (Eq. 4).  One wave takes the
-  // 512 tiles of a vocabulary of 8192 in one batch of requests; beyond that all 16 waves work also when there are few
-  // rows (8 rows, 50265 words 8.0 -> 6.9 us; 1000 words: 3.5 us with a wave per row, 4.2 shared)
-  const int share = n_tiles > 512 ? max(1, nwave / A) : 1, part = wave % share, span = (n_tiles + share - 1) / share;
-  const int t_lo = part * span, t_hi = min(t_lo + span, n_tiles);
-  for (int a = wave / share; a < A; a += max(1, nwave / share)) {
-    if (wave >= share * (nwave / share)) break;        // (waves left over when A does not divide their number)
-    int r = b * A + a;
-    int bi = 0x7fffffff;
-    const float *pv = part_val + (size_t)r * n_tiles;
-    const int32_t *pi = part_idx + (size_t)r * n_tiles;
-    float best = -INFINITY;
-    for (int t0 = t_lo + lane; t0 < t_hi; t0 += 64 * 8) {
-      float v[8]; int ix[8];
+  int done = st.done[b], k = st.k_open[b];
+  const int t = st.step[b], ng = TICK ? st.n_gen[b] : 0;
+  int new_tok = 0;                      // token this thread's subsequence was given in this step
+  bool given = false;
+  if (COMMIT) {
+    // stage 1: second stage of the argmax, `share` waves per row; lowest index wins ties (Eq. 4).  One wave takes 512
+    // winners in one batch of requests; beyond that all 16 waves work also when there are few rows
+    // (shares of a power of two: divisions by a variable are chains of 30 instructions)
+    const int lg = n_win <= 512 || A > 8 ? 0 : A > 4 ? 1 : A > 2 ? 2 : A > 1 ? 3 : 4, share = 1 << lg;
+    const int span = (n_win + share - 1) >> lg, t_lo = (wave & (share - 1)) * span, t_hi = min(t_lo + span, n_win);
+    for (int q = wave >> lg; q < A; q += 16 >> lg) {
+      const int r = b * A + q;
+      int bi = 0x7fffffff;
+      const float *pv = part_val + (size_t)r * n_win;
+      const int32_t *pi = part_idx + (size_t)r * n_win;
+      float best = -INFINITY;
+      for (int t0 = t_lo + lane; t0 < t_hi; t0 += 64 * 8) {
+        float v[8]; int ix[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        int tt = min(t0 + 64 * u, t_hi - 1);           // clamped: a repeated candidate changes nothing
-        v[u] = pv[tt];
-        ix[u] = pi[tt];
-      }
+        for (int u = 0; u < 8; ++u) {
+          int tt = min(t0 + 64 * u, t_hi - 1);          // clamped: a repeated candidate changes nothing
+          v[u] = pv[tt];
+          ix[u] = pi[tt];
+        }
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (v[u] > best || (v[u] == best && ix[u] < bi)) { best = v[u]; bi = ix[u]; }
-    }
-    best_wave(best, bi);
-    if (lane == 0) {
-      if (share == 1) s_arg[a] = bi;
-      else { s_best[wave] = best; s_idx[wave] = bi; }
-    }
-  }
-  __syncthreads();
-  if (share > 1) {                      // the same for the whole block: one row per group of waves
-    const int a = threadIdx.x;
-    if (a < A) {
-      float best = s_best[a * share];
-      int bi = s_idx[a * share];
-      for (int i = 1; i < share; ++i) {
-        const float ov = s_best[a * share + i];
-        const int oi = s_idx[a * share + i];
-        if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
+        for (int u = 0; u < 8; ++u) keep_best(best, bi, v[u], ix[u]);
       }
-      s_arg[a] = bi;
+      best_wave(best, bi);
+      if (lane == 0) {
+        if (share == 1) s_arg[q] = bi;
+        else { s_best[wave] = best; s_idx[wave] = bi; }
+      }
     }
     __syncthreads();
-  }
-  if (done) return;                     // the same for every thread of the block
-  // stage 2: Algorithm 1 lines 9-13, thread i for subsequence i.  A subsequence selects a token
-  // when it has a row and was unfinished when the rows were laid out.
-  int open_unfinished = 0;
-  for (int i = i0; i < S; i += blockDim.x) {
-    int r = r0, fin = fin0, f = f0, nt = nt0;
-    if (i != i0) {
-      r = st.row_of[b * S + i]; fin = st.fin[b * S + i]; f = st.force[b * S + i]; nt = st.n_tok[b * S + i];
-    }
-    if (i < k) {
-      if (r >= 0 && fin == 0) {
-        int tok = f >= 0 ? f : s_arg[r - b * A];
-        // non-finite logits leave the argmax without a winner: keep the id inside the vocabulary so
-        // that the next embedding gather stays in bounds
-        if (tok < 0 || tok >= V) tok = 0;
-        st.grid[(size_t)(b * S + i) * (M + 1) + nt] = tok;
-        st.n_tok[b * S + i] = nt + 1;
-        st.step_tok[b * S + i] = tok;
-        if (eos >= 0 && tok == eos) fin = 1;
-        else if (nt >= M) fin = 2;                     // nt generated tokens now held
-        st.fin[b * S + i] = fin;
+    if (share > 1) {                    // the same for the whole block: one row per group of waves
+      const int q = threadIdx.x;
+      if (q < A) {
+        float best = s_best[q << lg];
+        int bi = s_idx[q << lg];
+        for (int i = 1; i < share; ++i) keep_best(best, bi, s_best[(q << lg) + i], s_idx[(q << lg) + i]);
+        s_arg[q] = bi;
       }
-      if (fin == 0) open_unfinished = 1;
+      __syncthreads();
     }
-    st.force[b * S + i] = -1;
+    // stage 2: Algorithm 1 lines 9-13, thread i for subsequence i.  A subsequence selects a token
+    // when it has a row and was unfinished when the rows were laid out.
+    int open_unfinished = 0;
+    for (int i = i0; i < S; i += 1024) {
+      int r = r0, fin = fin0, f = f0, nt = nt0, tok = -1;
+      if (i != i0) {
+        r = row_of[b * S + i]; fin = fin_of[b * S + i]; nt = n_tok[b * S + i];
+        f = a.force ? a.force[b * S + i] : -1;
+      }
+      if (i < k && !done) {
+        if (r >= 0 && fin == 0) {
+          tok = f >= 0 ? f : s_arg[r - b * A];
+          // non-finite logits leave the argmax without a winner: keep the id inside the vocabulary so
+          // that the next embedding gather stays in bounds
+          if (tok < 0 || tok >= a.V) tok = 0;
+          st.grid[(size_t)(b * S + i) * (a.M + 1) + nt] = tok;
+          st.n_tok[b * S + i] = nt + 1;
+          if (!TICK) st.step_tok[b * S + i] = tok;
+          if (a.eos >= 0 && tok == a.eos) fin = 1;
+          else if (nt >= a.M) fin = 2;                   // nt generated tokens now held
+          st.fin[b * S + i] = fin;
+          if (i == i0) { nt0 = nt + 1; fin0 = fin; new_tok = tok; given = true; }
+        }
+        if (fin == 0) open_unfinished = 1;
+      }
+      if (a.force == st.force) st.force[b * S + i] = -1;
+      if (a.out_tok) a.out_tok[b * S + i] = tok;
+    }
+    const int any_unfinished = __syncthreads_or(open_unfinished);
+    if (!done && ((k > 0 && !any_unfinished) || t >= a.time_max)) {
+      done = 1;                         // the same for every thread of the block
+      if (threadIdx.x == 0) {
+        st.done[b] = 1; st.steps[b] = t;
+        atomicAdd(st.all_done, 1);
+      }
+    }
+    if (a.out_done && threadIdx.x == 0) a.out_done[b] = done;
   }
-  int any_unfinished = __syncthreads_or(open_unfinished);
-  if (threadIdx.x == 0 && ((k > 0 && !any_unfinished) || t >= time_max)) {
-    st.done[b] = 1; st.steps[b] = t;
-    atomicAdd(st.all_done, 1);
+  if (!TICK) return;
+
+  const int tn = t + 1;                 // the step that begins
+  if (!done && tn > a.time_max) {       // only reachable with time_max == 0
+    done = 1;
+    if (threadIdx.x == 0) { st.done[b] = 1; atomicAdd(st.all_done, 1); }
+  }
+  const bool opens = !done && (tn - 1) % a.dt == 0 && k < S;      // Algorithm 1, lines 5-7: open subsequence k + 1
+  if (opens) ++k;
+  int a_base = 0;                       // rows of the subsequences before this pass
+  for (int i1 = 0; i1 < S; i1 += 1024) {
+    const int i = i1 + i0;
+    int nt = nt0, fin = fin0, fed = fed0;
+    if (i1 > 0 && i < S) { nt = n_tok[b * S + i]; fin = fin_of[b * S + i]; fed = n_fed[b * S + i]; }
+    int tok = new_tok;
+    bool have_tok = i1 == 0 && given;
+    if (opens && i == k - 1) {
+      nt = 1; fin = 0; fed = 0; tok = a.bos; have_tok = true;
+      st.grid[(size_t)(b * S + i) * (a.M + 1)] = a.bos;
+      st.n_tok[b * S + i] = 1; st.fin[b * S + i] = 0; st.n_fed[b * S + i] = 0;
+    }
+    const bool has = !done && i < k && nt > fed;
+    const unsigned long long m = __ballot(has);
+    if (i1 > 0) __syncthreads();        // the counts of the pass before have been read
+    if (lane == 0) s_cnt[wave] = __popcll(m);
+    __syncthreads();
+    int q = a_base + __popcll(m & ((1ull << lane) - 1));
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      if (w < wave) q += s_cnt[w];
+      a_base += s_cnt[w];
+    }
+    if (i >= S) continue;
+    int r = -1;
+    if (has && q < A && ng + q < a.gen_cap) {
+      r = b * A + q;
+      const int fl = ROW_VALID | (fin ? 0 : ROW_PRODUCE), pos = a.L + (tn - 1) + i, slot = a.L + ng + q;
+      if (!have_tok) tok = st.grid[(size_t)(b * S + i) * (a.M + 1) + nt - 1];
+      rt.req[r] = b; rt.sub[r] = i + 1; rt.tok[r] = tok; rt.pos[r] = pos; rt.slot[r] = slot; rt.lim[r] = a.L;
+      rt.flags[r] = fl;
+      rt.qinfo[r] = make_int4(fl, i + 1, a.L, b);
+      rt.kvinfo[r] = make_int4(fl, b, slot, pos);
+      st.gen_sub[(size_t)b * a.gen_stride + (a.L & 7) + ng + q] = (uint16_t)(i + 1);
+      if (a.qinfo_x) {
+        a.qinfo_x[r] = make_int4(fl, 0, a.Lx, b);
+        a.gen_coord[(size_t)b * a.gen_stride + ng + q] = (uint16_t)((tn - 1) + i);
+      }
+      st.n_fed[b * S + i] = nt;
+      if (NGW) { s_tok[q] = tok; s_pos[q] = pos; }
+    }
+    st.row_of[b * S + i] = r;
+    st.step_tok[b * S + i] = -1;
+  }
+  const int rows = min(a_base, min(A, max(a.gen_cap - ng, 0)));
+  for (int q = rows + i0; q < A; q += 1024) {
+    rt.flags[b * A + q] = 0;
+    rt.qinfo[b * A + q] = make_int4(0, -1, 0, b);
+    rt.kvinfo[b * A + q] = make_int4(0, b, 0, 0);
+    if (a.qinfo_x) a.qinfo_x[b * A + q] = make_int4(0, -1, 0, b);
+  }
+  if (threadIdx.x == 0) {
+    st.n_rows[b] = rows;
+    if (!done) {
+      st.step[b] = tn; st.k_open[b] = k;
+      st.n_gen[b] = ng + rows; st.kv_len[b] = a.L + ng + rows;
+    }
+  }
+  if constexpr (NGW > 0) {
+    // A wave per row; rows without a token are zero; what lies behind the last request's rows is never stored by any projection
+    const int d = a.d;
+    float gv[NGW][8], bv[NGW][8];
+#pragma unroll
+    for (int n = 0; n < NGW; ++n) {
+      const int c = (lane + 64 * n) * 8;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const float4 tg = c < d ? *(const float4 *)(a.g + c + 4 * h) : make_float4(0.f, 0.f, 0.f, 0.f);
+        const float4 tb = c < d && a.kind == 0 && a.b ? *(const float4 *)(a.b + c + 4 * h) : make_float4(0.f, 0.f, 0.f, 0.f);
+        gv[n][4 * h] = tg.x; gv[n][4 * h + 1] = tg.y; gv[n][4 * h + 2] = tg.z; gv[n][4 * h + 3] = tg.w;
+        bv[n][4 * h] = tb.x; bv[n][4 * h + 1] = tb.y; bv[n][4 * h + 2] = tb.z; bv[n][4 * h + 3] = tb.w;
+      }
+    }
+    __syncthreads();                    // tokens and positions of the rows
+    for (int q = wave; q < A; q += 16) {
+      const int r = b * A + q;
+      if (r >= a.row_end) break;
+      const bool has = q < rows;        // the same for the whole wave
+      const bf16_t *te = a.tok_emb + (has ? (size_t)s_tok[q] * d : 0);
+      const bf16_t *pe = a.pos_emb ? a.pos_emb + (has ? (size_t)s_pos[q] * d : 0) : nullptr;
+      Frag et[NGW], ep[NGW];
+#pragma unroll
+      for (int n = 0; n < NGW; ++n) {
+        const int c = (lane + 64 * n) * 8;
+        et[n].u = has && c < d ? *(const uint4 *)(te + c) : make_uint4(0, 0, 0, 0);
+        ep[n].u = has && c < d && pe ? *(const uint4 *)(pe + c) : make_uint4(0, 0, 0, 0);
+      }
+      float v[NGW][8], s1 = 0.f, s2 = 0.f;
+#pragma unroll
+      for (int n = 0; n < NGW; ++n)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          v[n][e] = bf16_to_f32(et[n].h[e]) + bf16_to_f32(ep[n].h[e]);
+          s1 += v[n][e]; s2 += v[n][e] * v[n][e];
+        }
+      s1 = fold_wave(s1, Add());
+      s2 = fold_wave(s2, Add());
+      const float mean = a.kind == 0 ? s1 / d : 0.f;
+      const float rstd = rsqrtf(fmaxf(s2 / d - mean * mean, 0.f) + a.eps);
+#pragma unroll
+      for (int n = 0; n < NGW; ++n) {
+        const int c = (lane + 64 * n) * 8;
+        if (c >= d) continue;
+        Frag hi, lo;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float y = has ? (v[n][e] - mean) * rstd * gv[n][e] + bv[n][e] : 0.f;
+          hi.h[e] = f32_to_bf16(y);
+          lo.h[e] = f32_to_bf16(bf16_residual(y, hi.h[e]));
+        }
+        *(float4 *)(a.x + (size_t)r * d + c) = make_float4(v[n][0], v[n][1], v[n][2], v[n][3]);
+        *(float4 *)(a.x + (size_t)r * d + c + 4) = make_float4(v[n][4], v[n][5], v[n][6], v[n][7]);
+        const size_t off = act_off(r, c, d);
+        *(uint4 *)(a.xn + off) = hi.u;
+        if (a.xn_lo) *(uint4 *)(a.xn_lo + off) = lo.u;
+      }
+    }
   }
 }
 
-int launch_commit(pd_ctx *c, hipStream_t s) {
-  hipLaunchKernelGGL(k_commit, dim3(c->B), dim3(1024), 0, s, c->sch, c->lm_part_val, c->lm_part_idx, c->vocab_pad / 16,
-                     c->S, c->M, c->A, c->time_max, c->cfg.eos_id, c->cfg.vocab);
+// Whether a step's tick also gathers and normalises its rows: one compute unit does that for all rows of a request, and a
+// lane holds at most 16 values of a row (32 do not fit the registers of 16 waves: width 2048, 8 rows 17.8 us, commit and tick
+// 7.4 with the norm kernel's 4.0 behind them; two waves per row are no faster than one, width 768 11.0 against 10.0).
+bool turn_embeds(const pd_ctx *c) { return c->impl == 1 && c->cfg.d_model <= 1024 && c->A <= TURN_ROWS; }
+
+int launch_turn(pd_ctx *c, bool commit, bool tick, bool packed, const int32_t *force, int32_t *out_tok, int32_t *out_done,
+                hipStream_t s) {
+  const pd_config &g = c->cfg;
+  const bool embed = tick && turn_embeds(c);
+  PD_REQUIRE(c->S < 65536 && c->A <= 1024 && !(commit && tick && c->S > 1024), PD_EINVAL, "%d subsequences, %d rows", c->S, c->A);
+  TurnArgs a;
+  memset(&a, 0, sizeof(a));
+  a.st = c->sch; a.rt = c->rows; a.dt = c->dt; a.M = c->M; a.L = c->L; a.time_max = c->time_max; a.bos = g.bos_id; a.eos = g.eos_id;
+  a.V = g.vocab; a.gen_cap = c->gen_cap; a.gen_stride = c->gen_stride; a.Lx = c->Lx; a.gen_coord = c->gen_coord;
+  a.qinfo_x = c->qinfo_x; a.force = force; a.out_tok = out_tok; a.out_done = out_done;
+  int ngw = 0;
+  if (embed) {
+    const bool was = c->packed;
+    c->packed = packed;                 // (the step that begins decides on the layout)
+    a.xn_lo = mfma_lo(c, c->xn, g.d_model);
+    c->packed = was;
+    a.tok_emb = (const bf16_t *)c->tok_emb; a.pos_emb = (const bf16_t *)c->pos_emb; a.g = c->layers[0].n1g; a.b = c->layers[0].n1b;
+    a.d = g.d_model; a.kind = g.norm_kind; a.eps = g.norm_eps; a.x = c->x; a.xn = (bf16_t *)c->xn;
+    a.row_end = packed ? 8 : c->R_pad;  // (packed: behind them lie the low parts)
+    ngw = a.d <= 512 ? 1 : 2;
+  }
+#define PD_TURN(C, T, N)                                                                                              \
+  hipLaunchKernelGGL((k_turn<C, T, N>), dim3(c->B), dim3(1024), 0, s, c->lm_part_val, c->lm_part_idx, c->sch.row_of,   \
+                     c->sch.n_tok, c->sch.fin, c->sch.n_fed, c->lm_win, (uint32_t)c->S << 16 | (uint32_t)c->A, a)
+#define PD_TURN_N(C)                                                                                                  \
+  if (ngw == 0) PD_TURN(C, true, 0);                                                                                  \
+  else if (ngw == 1) PD_TURN(C, true, 1);                                                                             \
+  else PD_TURN(C, true, 2);
+  if (!tick) PD_TURN(true, false, 0);
+  else if (commit) { PD_TURN_N(true) }
+  else { PD_TURN_N(false) }
+#undef PD_TURN_N
+#undef PD_TURN
   PD_CHECK_HIP(hipGetLastError());
   return PD_OK;
 }

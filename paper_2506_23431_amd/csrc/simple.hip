@@ -632,5 +632,6 @@ int simple_head(pd_ctx *c, int R, float *logits, hipStream_t s) {
   a.rt = c->rows;
   if ((rc = normed(c, a, c->fng, c->fnb, R, s))) return rc;
   a.logits = logits; a.S = c->S; a.part_val = c->lm_part_val; a.part_idx = c->lm_part_idx; a.n_tiles = c->vocab_pad / 16;
+  c->lm_win = a.n_tiles;
   return linear<LIN_HEAD>(c, a, c->lm_head, nullptr, R, g.vocab, g.d_model, s, a.n_tiles);
 }
