@@ -80,7 +80,8 @@ __global__ void k_norm_f32(float *xn, const float *x, const float *g, const floa
 // ---------------------------------------------------------------------------
 // linear: y[r][n] = sum_k u(x)[r][k] * W[n][k], u = identity or the norm of the row
 // ---------------------------------------------------------------------------
-enum { LIN_STORE = 0, LIN_RESID = 1, LIN_GELU = 2, LIN_SWIGLU = 3, LIN_QKV = 4, LIN_HEAD = 5 };
+enum { LIN_STORE = 0, LIN_RESID = 1, LIN_GELU = 2, LIN_SWIGLU = 3, LIN_QKV = 4, LIN_HEAD = 5, LIN_SLICE = 6 };
+constexpr int SLICES = 4;      // LIN_SLICE: cuts of K over blocks
 
 struct LinArgs {
   const float *x;                     // [R][K]
@@ -92,6 +93,8 @@ struct LinArgs {
   RowTables rt;
   float *out; int ldo;
   const float *res;                   // LIN_RESID (may be out itself)
+  // slices [SLICES][slice_stride] that the rows of x (of the residual) still lack, or NULL; LIN_SLICE: where its own go
+  const float *pend; size_t slice_stride;
   void *kc, *vc, *kc_lo, *vc_lo; int d, H, hd, kv_cap; int32_t *kv_sat;   // LIN_QKV
   float *logits; int S;               // LIN_HEAD: NULL, or [B][S][N] addressed by a row's request and subsequence
   float *part_val; int32_t *part_idx; int n_tiles;
@@ -100,9 +103,10 @@ struct LinArgs {
 // a row of the residual stream, read or gathered
 template <typename WT>
 struct RowSrc {
-  const float *x; const WT *te, *pe; bool zero;
+  const float *x, *pend; size_t stride; const WT *te, *pe; bool zero;
   __device__ __forceinline__ RowSrc(const LinArgs &a, const float *base, int r, int ld, bool may_gather)
-      : x(base + (size_t)r * ld), te(nullptr), pe(nullptr), zero(false) {
+      : x(base + (size_t)r * ld), pend(nullptr), stride(a.slice_stride), te(nullptr), pe(nullptr), zero(false) {
+    if (may_gather && a.pend) pend = a.pend + (size_t)r * ld;
     if (may_gather && a.tok_emb) {
       const int fl = a.rt.flags[r], tok = a.rt.tok[r], pos = a.rt.pos[r];      // independent loads
       zero = !(fl & ROW_VALID);
@@ -111,7 +115,16 @@ struct RowSrc {
     }
   }
   template <bool VEC> __device__ __forceinline__ floatx4 at(int k, int n) const {
-    if (!te) return ld_row4<VEC>(x, k, n);
+    if (!te) {
+      floatx4 v = ld_row4<VEC>(x, k, n);
+      if (pend) {                       // the same for the whole launch
+        floatx4 p[SLICES];
+#pragma unroll
+        for (int i = 0; i < SLICES; ++i) p[i] = ld_row4<VEC>(pend + i * stride, k, n);
+        v += (p[0] + p[1]) + (p[2] + p[3]);
+      }
+      return v;
+    }
     floatx4 v = ld_row4<VEC>(te, k, n);
     if (pe) v += ld_row4<VEC>(pe, k, n);
     return zero ? floatx4{0.f, 0.f, 0.f, 0.f} : v;
@@ -121,10 +134,12 @@ struct RowSrc {
 // A block owns one 16-column tile and RT tiles of 16 rows; its NW waves cut K in steps of 16, the partial tiles are
 // summed through LDS.  VPL > 0: the rows are normalised first (K <= 256 VPL).  Every wave reads 16 / NW rows once,
 // whole (VPL quads per lane), takes mean and variance in registers (two passes) and leaves the normalised row in LDS;
-// the first weights are requested before that.  Bound by latency at the sizes of this path: enough waves that each
+// the first weights are requested before that (by the leading arguments, which arrive in registers).  Bound by latency at the sizes of this path: enough waves that each
 // has one or two batches of requests (512 x 2048, 12 rows: 13.5 us with a wave per column, now 6-7).
 template <typename WT, typename KT, int EPI, int NW, int RT, int VPL, bool VEC>
-__global__ __launch_bounds__(64 * NW) void k_lin(LinArgs a) {
+__global__ __launch_bounds__(64 * NW) void k_lin(const float *hot_x, const void *hot_w, const void *hot_w2, const float *hot_g,
+                                                   const float *hot_b, const int4 *hot_info, int R, int K, LinArgs a) {
+  const int N = a.N;
   constexpr bool NORM = VPL > 0;
   constexpr int NT = EPI == LIN_SWIGLU ? 2 : 1, U = 4;
   constexpr int XLD = NORM ? 256 * VPL + 4 : 4;      // (+ 4: the 16 rows of a step lie in different banks)
@@ -132,12 +147,13 @@ __global__ __launch_bounds__(64 * NW) void k_lin(LinArgs a) {
   __shared__ floatx4 red[NW][NT * RT][64];
   __shared__ float sm_x[NORM ? 16 : 1][XLD];
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
-  const int r0 = blockIdx.y * 16 * RT, n0 = blockIdx.x * 16, K = a.K;
-  const int steps = (K + 15) >> 4, share = (steps + NW - 1) / NW;
-  const int s0 = min(w * share, steps), s1 = min(s0 + share, steps);
+  const int r0 = blockIdx.y * 16 * RT, n0 = blockIdx.x * 16;
+  const int all = (K + 15) >> 4, steps = EPI == LIN_SLICE ? (all + SLICES - 1) / SLICES : all, share = (steps + NW - 1) / NW;
+  const int b0 = EPI == LIN_SLICE ? min((int)blockIdx.z * steps, all) : 0, b1 = min(b0 + steps, all);
+  const int s0 = min(b0 + w * share, b1), s1 = min(s0 + share, b1);
   const WT *wrow[NT];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) wrow[t] = (const WT *)(t ? a.W2 : a.W) + (size_t)min(n0 + m, a.N - 1) * K;
+  for (int t = 0; t < NT; ++t) wrow[t] = (const WT *)(t ? hot_w2 : hot_w) + (size_t)min(n0 + m, N - 1) * K;
   // weights of U steps; steps and values past the end are zero
   auto load_w = [&](floatx4 (&wv)[NT][U], int s) {
 #pragma unroll
@@ -156,13 +172,13 @@ __global__ __launch_bounds__(64 * NW) void k_lin(LinArgs a) {
   floatx4 res = floatx4{0.f, 0.f, 0.f, 0.f};
   int4 info = make_int4(0, 0, 0, 0);
   if (w < RT) {
-    const int r = min(r0 + w * 16 + m, a.R - 1);
+    const int r = min(r0 + w * 16 + m, R - 1);
     if (EPI == LIN_RESID) {
-      const RowSrc<WT> src(a, a.res, r, a.N, true);
-      res = src.template at<false>(n0 + 4 * g, a.N);
+      const RowSrc<WT> src(a, a.res, r, N, true);
+      res = src.template at<false>(n0 + 4 * g, N);
     }
-    if (EPI == LIN_QKV) info = a.rt.kvinfo[r];        // {flags, req, slot, pos}
-    if (EPI == LIN_HEAD) info = a.rt.qinfo[r];        // {flags, sub, lim, req}
+    if (EPI == LIN_QKV) info = hot_info[r];        // {flags, req, slot, pos}
+    if (EPI == LIN_HEAD) info = hot_info[r];        // {flags, sub, lim, req}
   }
   if constexpr (NORM) {
     constexpr int RPW = 16 / NW;      // rows per wave
@@ -170,14 +186,14 @@ __global__ __launch_bounds__(64 * NW) void k_lin(LinArgs a) {
     float s[RPW], q[RPW];
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
-      const RowSrc<WT> src(a, a.x, min(r0 + w * RPW + i, a.R - 1), K, true);
+      const RowSrc<WT> src(a, hot_x, min(r0 + w * RPW + i, R - 1), K, true);
 #pragma unroll
       for (int v = 0; v < VPL; ++v) xv[i][v] = src.template at<VEC>(4 * (lane + 64 * v), K);
     }
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
-      gv[v] = ld_row4<VEC>(a.ng, 4 * (lane + 64 * v), K);
-      bv[v] = a.nb ? ld_row4<VEC>(a.nb, 4 * (lane + 64 * v), K) : floatx4{0.f, 0.f, 0.f, 0.f};
+      gv[v] = ld_row4<VEC>(hot_g, 4 * (lane + 64 * v), K);
+      bv[v] = hot_b ? ld_row4<VEC>(hot_b, 4 * (lane + 64 * v), K) : floatx4{0.f, 0.f, 0.f, 0.f};
     }
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
@@ -225,7 +241,7 @@ __global__ __launch_bounds__(64 * NW) void k_lin(LinArgs a) {
     floatx4 xv[RT][U];
 #pragma unroll
     for (int i = 0; i < RT; ++i) {
-      const RowSrc<WT> src(a, a.x, min(r0 + i * 16 + m, a.R - 1), K, false);
+      const RowSrc<WT> src(a, hot_x, min(r0 + i * 16 + m, R - 1), K, false);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int k = (s + u) * 16 + 4 * g;
@@ -266,14 +282,14 @@ __global__ __launch_bounds__(64 * NW) void k_lin(LinArgs a) {
       for (int v = 1; v < NW; ++v) y2 += red[v][RT + i][lane];
     }
     const int r = r0 + i * 16 + m, n = n0 + 4 * g;
-    const bool in = r < a.R;
+    const bool in = r < R;
     if (EPI == LIN_HEAD) {
       float best = -INFINITY;
       int bi = 0x7fffffff;
-      float *dst = a.logits && in && (info.x & ROW_VALID) ? a.logits + ((size_t)info.w * a.S + (info.y - 1)) * a.N : nullptr;
+      float *dst = a.logits && in && (info.x & ROW_VALID) ? a.logits + ((size_t)info.w * a.S + (info.y - 1)) * N : nullptr;
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        if (n + j < a.N) {
+        if (n + j < N) {
           if (dst) dst[n + j] = y[j];
           if (y[j] > best) { best = y[j]; bi = n + j; }
         }
@@ -290,7 +306,7 @@ __global__ __launch_bounds__(64 * NW) void k_lin(LinArgs a) {
       if (!(info.x & ROW_VALID)) return;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        if (n + j >= a.N) continue;
+        if (n + j >= N) continue;
         const int sec = (n + j) / a.d, c = (n + j) - sec * a.d, h = c / a.hd;
         if (sec == 0) { a.out[(size_t)r * a.ldo + n + j] = y[j]; continue; }
         const size_t slab = ((size_t)info.y * a.H + h) * a.kv_cap * a.hd, dim = c - h * a.hd;
@@ -306,11 +322,11 @@ __global__ __launch_bounds__(64 * NW) void k_lin(LinArgs a) {
       }
       return;
     }
-    float *dst = a.out + (size_t)r * a.ldo + n;
+    float *dst = a.out + (size_t)r * a.ldo + n + (EPI == LIN_SLICE ? blockIdx.z * a.slice_stride : 0);
     if (EPI == LIN_RESID) y += res;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      if (n + j >= a.N) continue;
+      if (n + j >= N) continue;
       float v = y[j];
       if (EPI == LIN_GELU) v = 0.5f * v * (1.f + erff(v * 0.70710678118654752f));
       if (EPI == LIN_SWIGLU) v = v / (1.f + expf(-v)) * y2[j];
@@ -321,9 +337,10 @@ __global__ __launch_bounds__(64 * NW) void k_lin(LinArgs a) {
 
 template <typename WT, typename KT, int EPI, int NW, int RT, int VPL>
 static void launch_lin(const LinArgs &a, int n_tiles, bool vec, hipStream_t s) {
-  const dim3 grid(n_tiles, (a.R + 16 * RT - 1) / (16 * RT));
-  if (vec) hipLaunchKernelGGL((k_lin<WT, KT, EPI, NW, RT, VPL, true>), grid, dim3(64 * NW), 0, s, a);
-  else hipLaunchKernelGGL((k_lin<WT, KT, EPI, NW, RT, VPL, false>), grid, dim3(64 * NW), 0, s, a);
+  const dim3 grid(n_tiles, (a.R + 16 * RT - 1) / (16 * RT), EPI == LIN_SLICE ? SLICES : 1);
+  const int4 *info = EPI == LIN_QKV ? a.rt.kvinfo : a.rt.qinfo;
+  auto kernel = vec ? k_lin<WT, KT, EPI, NW, RT, VPL, true> : k_lin<WT, KT, EPI, NW, RT, VPL, false>;
+  hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), 0, s, a.x, a.W, a.W2, a.ng, a.nb, info, a.R, a.K, a);
 }
 
 // Wide loads where the rows allow them: K a multiple of 4 and every matrix aligned.  Waves along K: 16 steps each up
@@ -335,6 +352,11 @@ static int run_lin(const LinArgs &a, int n_tiles, hipStream_t s) {
   const uintptr_t mis = (uintptr_t)a.W | (uintptr_t)a.W2 | (uintptr_t)a.tok_emb | (uintptr_t)a.pos_emb;
   const uintptr_t misv = (uintptr_t)a.ng | (uintptr_t)a.nb;
   const bool vec = a.K % 4 == 0 && mis % (4 * sizeof(WT)) == 0 && misv % 16 == 0;
+  if constexpr (EPI == LIN_SLICE) {
+    launch_lin<WT, KT, EPI, 8, 1, 0>(a, n_tiles, vec, s);
+    PD_CHECK_HIP(hipGetLastError());
+    return PD_OK;
+  }
   if constexpr (EPI != LIN_RESID) {
     if (a.ng) {
       if (a.K <= 256) launch_lin<WT, KT, EPI, 4, 1, 1>(a, n_tiles, vec, s);
@@ -406,8 +428,9 @@ __global__ void k_qkv_post(float *qkv, KT *kc, KT *vc, KT *kc_lo, KT *vc_lo, Row
 // Per key tile: S^T (16 keys x 16 queries) from the keys' rows and the queries, mask, online softmax per query,
 // O^T += V^T P^T; the score tile's registers are the operand of the second product.  Keys and values are requested
 // together, before either is used.  Bound by the one compute unit a (request, head) runs on: 32 products of 32 clocks
-// per key tile, so 16 waves and a tile or two each (12 rows, 8 heads of 64, 330 keys: 12 us; a thread per key over
-// uncoalesced key rows took 31; requesting the next tile ahead costs the registers of half the waves, 13-17 us).
+// per key tile, so 16 waves and a tile or two each (12 rows, 8 heads of 64, 330 keys: 10.7 us, 12 with all waves merging
+// and expf; a thread per key over uncoalesced key rows took 31; requesting the next tile ahead costs the registers of half
+// the waves, 13-17 us).
 // ---------------------------------------------------------------------------
 struct AttnF32Args {
   float *out; const float *qkv;
@@ -417,56 +440,77 @@ struct AttnF32Args {
   float scale;
 };
 
+// e^x as 2^(x log2 e) with the product's rounding error carried along: two units in the last place
+__device__ __forceinline__ float exp_f32(float x) {
+  const float t = x * 1.44269504f, e = fmaf(x, 1.44269504f, -t);
+  const float r = __builtin_amdgcn_exp2f(t);
+  return x == -INFINITY ? 0.f : fmaf(r, e * 0.69314718f, r);
+}
+
 template <typename KT, int NHB, int NW, bool VEC>      // NHB: 16-dim blocks of a head (hd <= 16 NHB)
-__global__ __launch_bounds__(64 * NW) void k_attn_f32(AttnF32Args a) {
+__global__ __launch_bounds__(64 * NW) void k_attn_f32(const float *hot_qkv, const void *hot_k, const void *hot_v,
+                                                      const int4 *hot_qinfo, const int32_t *hot_kv_len, int hot_hd, int kv_cap,
+                                                      uint32_t hot_ha, int hot_req0, AttnF32Args a) {
   __shared__ floatx4 sm_o[NW][NHB][64];
   __shared__ float sm_m[NW][16], sm_l[NW][16];
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
   // (one grid dimension: the others end at 65535, and a batch may have more requests)
-  const int h = blockIdx.x % a.H, unit = blockIdx.x / a.H, reqi = unit / a.nqg, qg = unit % a.nqg, req = a.req0 + reqi;
-  const int hd = a.hd;
+  const int H = hot_ha & 0xffff, A = hot_ha >> 16, nqg = (A + 15) >> 4, unit = blockIdx.x / H, h = blockIdx.x - unit * H;
+  int reqi = unit, qg = 0;
+  if (nqg > 1) { reqi = unit / nqg; qg = unit - reqi * nqg; }
+  const int req = hot_req0 + reqi, hd = hot_hd, d = H * hd;
   const int qa = qg * 16 + m;
-  const int r = reqi * a.A + min(qa, a.A - 1);          // clamped: loads stay in bounds
-  const int4 qi = a.rt.qinfo[r];                        // {flags, sub, lim, req}
-  const bool valid = qa < a.A && (qi.x & ROW_VALID);
-  const int n = a.kv_override >= 0 ? a.kv_override : a.kv_len[req];
+  const int r = reqi * A + min(qa, A - 1);              // clamped: loads stay in bounds
+  const int4 qi = hot_qinfo[r];                         // {flags, sub, lim, req}
+  int n = 0;
+  if (hot_kv_len) n = hot_kv_len[req];                  // NULL: the number is an argument
+  floatx4 q[NHB];
+#pragma unroll
+  for (int c = 0; c < NHB; ++c) q[c] = ld_row4<VEC>(hot_qkv + (size_t)r * 3 * d + h * hd, 16 * c + 4 * g, hd);
+  // the first keys and values are requested before anything is known about the rows (what lies behind the last key is
+  // masked; it is allocated and holds finite numbers)
+  const size_t base = ((size_t)req * H + h) * kv_cap * hd;
+  const KT *K = (const KT *)hot_k + base, *V = (const KT *)hot_v + base;
+  floatx4 kf[NHB], vf[NHB];             // key m, dims 16 c + 4 g .. + 3;  dim 16 i + m, keys 4 g .. + 3
+  auto load = [&](int t) {
+    const size_t krow = (size_t)min(t * 16 + m, kv_cap - 1) * hd;
+#pragma unroll
+    for (int c = 0; c < NHB; ++c) kf[c] = ld_row4<VEC>(K + krow, 16 * c + 4 * g, hd);
+#pragma unroll
+    for (int i = 0; i < NHB; ++i)       // (kv_cap is a multiple of 64)
+      vf[i] = ld_row4<true>(V + (size_t)min(16 * i + m, hd - 1) * kv_cap, t * 16 + 4 * g, kv_cap);
+  };
+  load(w);
+  __builtin_amdgcn_sched_barrier(0);
+  const KT *Kl = a.kc_lo ? (const KT *)a.kc_lo + base : nullptr, *Vl = a.vc_lo ? (const KT *)a.vc_lo + base : nullptr;
+  const uint16_t *gs = a.gen_sub + (size_t)req * a.gen_stride;
+  const int L8 = a.L & ~7;            // entry of key slot j >= L is j - L8
+  if (!hot_kv_len) n = a.kv_override;
+  const bool valid = qa < A && (qi.x & ROW_VALID);
   const int lim = valid ? min(qi.z, n) : 0, sub = valid ? qi.y : -1;
   // keys some query of the group sees
   int reach = valid ? (n > a.L && sub >= 1 ? n : lim) : 0;
   reach = fold_row(reach, Max());
   const int tiles = __builtin_amdgcn_readfirstlane((reach + 15) >> 4);
-  const size_t base = ((size_t)req * a.H + h) * a.kv_cap * hd;
-  const KT *K = (const KT *)a.kc + base, *V = (const KT *)a.vc + base;
-  const KT *Kl = a.kc_lo ? (const KT *)a.kc_lo + base : nullptr, *Vl = a.vc_lo ? (const KT *)a.vc_lo + base : nullptr;
-  const uint16_t *gs = a.gen_sub + (size_t)req * a.gen_stride;
-  const int L8 = a.L & ~7;            // entry of key slot j >= L is j - L8
-  floatx4 q[NHB];
 #pragma unroll
-  for (int c = 0; c < NHB; ++c) {
-    const floatx4 v = ld_row4<VEC>(a.qkv + (size_t)r * 3 * a.d + h * hd, 16 * c + 4 * g, hd);
+  for (int c = 0; c < NHB; ++c)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) q[c][e] = 16 * c + 4 * g + e < hd ? v[e] : 0.f;
-  }
+    for (int e = 0; e < 4; ++e) q[c][e] = 16 * c + 4 * g + e < hd ? q[c][e] : 0.f;
   float m_run = -INFINITY, l_run = 0.f;
   floatx4 o_acc[NHB];
 #pragma unroll
   for (int i = 0; i < NHB; ++i) o_acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
   for (int t = w; t < tiles; t += NW) {
     const int key0 = t * 16, key = key0 + 4 * g;
-    floatx4 kf[NHB], vf[NHB];         // key m, dims 16 c + 4 g .. + 3;  dim 16 i + m, keys 4 g .. + 3
     int tag[4];
-    const size_t krow = (size_t)min(key0 + m, n - 1) * hd;
+    if (Kl) {
+      const size_t krow = (size_t)min(key0 + m, kv_cap - 1) * hd;
 #pragma unroll
-    for (int c = 0; c < NHB; ++c) {
-      kf[c] = ld_row4<VEC>(K + krow, 16 * c + 4 * g, hd);
-      if (Kl) kf[c] += ld_row4<VEC>(Kl + krow, 16 * c + 4 * g, hd);
+      for (int c = 0; c < NHB; ++c) kf[c] += ld_row4<VEC>(Kl + krow, 16 * c + 4 * g, hd);
     }
+    if (Vl)
 #pragma unroll
-    for (int i = 0; i < NHB; ++i) {
-      const size_t vrow = (size_t)min(16 * i + m, hd - 1) * a.kv_cap;     // (kv_cap is a multiple of 64)
-      vf[i] = ld_row4<true>(V + vrow, key, a.kv_cap);
-      if (Vl) vf[i] += ld_row4<true>(Vl + vrow, key, a.kv_cap);
-    }
+      for (int i = 0; i < NHB; ++i) vf[i] += ld_row4<true>(Vl + (size_t)min(16 * i + m, hd - 1) * kv_cap, key, kv_cap);
 #pragma unroll
     for (int e = 0; e < 4; ++e) tag[e] = gs[min(max(key + e - L8, 0), a.gen_stride - 1)];
     floatx4 se[4];
@@ -489,10 +533,10 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(AttnF32Args a) {
     mloc = fold32(fold16(mloc, Max()), Max());
     const float m_new = fmaxf(m_run, mloc);
     const float m_ref = m_new == -INFINITY ? 0.f : m_new;      // nothing visible yet: exp(-inf) = 0, never NaN
-    const float alpha = expf(m_run - m_ref);
+    const float alpha = exp_f32(m_run - m_ref);
     float p[4], psum = 0.f;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) { p[j] = expf(s[j] - m_ref); psum += p[j]; }
+    for (int j = 0; j < 4; ++j) { p[j] = exp_f32(s[j] - m_ref); psum += p[j]; }
     l_run = l_run * alpha + psum;
     m_run = m_new;
     if (__any(alpha != 1.f))
@@ -503,18 +547,20 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(AttnF32Args a) {
 #pragma unroll
       for (int i = 0; i < NHB; ++i)       // (slots past the last key hold what an earlier request left there)
         o_acc[i] = mfma_f32(key0 + 4 * g + e < n ? vf[i][e] : 0.f, p[e], o_acc[i]);
+    if (t + NW < tiles) load(t + NW);   // the same for the whole wave
   }
   l_run = fold32(fold16(l_run, Add()), Add());
   if (g == 0) { sm_m[w][m] = m_run; sm_l[w][m] = l_run; }
 #pragma unroll
   for (int i = 0; i < NHB; ++i) sm_o[w][i][lane] = o_acc[i];
   __syncthreads();
+  if (w >= NHB) return;                 // a wave per 16 dims merges (all 16 doing the weights took 2.7 us)
   float M = -INFINITY, f[NW], l = 0.f;
 #pragma unroll
   for (int v = 0; v < NW; ++v) M = fmaxf(M, sm_m[v][m]);
 #pragma unroll
   for (int v = 0; v < NW; ++v) {
-    f[v] = sm_m[v][m] == -INFINITY ? 0.f : expf(sm_m[v][m] - M);
+    f[v] = sm_m[v][m] == -INFINITY ? 0.f : exp_f32(sm_m[v][m] - M);
     l += f[v] * sm_l[v][m];
   }
   if (!valid) return;
@@ -525,18 +571,22 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(AttnF32Args a) {
     for (int v = 1; v < NW; ++v) o += f[v] * sm_o[v][i][lane];
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      if (16 * i + 4 * g + j < hd) a.out[(size_t)r * a.d + h * hd + 16 * i + 4 * g + j] = o[j] / l;
+      if (16 * i + 4 * g + j < hd) a.out[(size_t)r * d + h * hd + 16 * i + 4 * g + j] = o[j] / l;
   }
 }
 
 template <typename KT>
 static int attention_f32(const AttnF32Args &a, int nreq, hipStream_t s) {
   const dim3 grid(a.H * nreq * a.nqg);
+  const int32_t *kv_len = a.kv_override >= 0 ? nullptr : a.kv_len;
+  PD_REQUIRE(a.H < 65536 && a.A < 65536, PD_EINVAL, "%d heads, %d rows per request", a.H, a.A);
+  const uint32_t ha = (uint32_t)a.H | (uint32_t)a.A << 16;
   const bool vec = a.hd % 4 == 0;       // rows of q, keys and values then start at multiples of 16 (half: 8) bytes
 #define PD_ATTN_F32(NHB, NW)                                                                                  \
   do {                                                                                                        \
-    if (vec) hipLaunchKernelGGL((k_attn_f32<KT, NHB, NW, true>), grid, dim3(64 * NW), 0, s, a);               \
-    else hipLaunchKernelGGL((k_attn_f32<KT, NHB, NW, false>), grid, dim3(64 * NW), 0, s, a);                  \
+    auto kernel = vec ? k_attn_f32<KT, NHB, NW, true> : k_attn_f32<KT, NHB, NW, false>;                       \
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), 0, s, a.qkv, a.kc, a.vc, a.rt.qinfo, kv_len, a.hd, a.kv_cap, ha,  \
+                       a.req0, a);                                                                            \
   } while (0)
   // waves per block: what the registers of a wave leave room for
   if (a.hd <= 16) PD_ATTN_F32(1, 16);
@@ -552,6 +602,10 @@ static int attention_f32(const AttnF32Args &a, int nreq, hipStream_t s) {
 // ---------------------------------------------------------------------------
 // one transformer layer / the head, as sequences of launches
 // ---------------------------------------------------------------------------
+// The second FFN projection of such a step is cut along K over SLICES blocks from d_ff 1024 on: a block per 16 columns alone
+// draws its weights and rows through one compute unit (width 512, d_ff 2048, 12 rows: 32 blocks 10.4 us, 128 blocks 4.4).
+// The slices are added where the rows are read next, by the norms inside the projections (QKV 6.4 -> 7.7, head 9.0 -> 12.0) and the output
+// projection, which completes the residual.
 // At most 32 rows (decode steps) of up to 1024 values: the norms are taken inside the projections that follow them and the first layer
 // gathers its rows from the embedding tables.  With more rows a norm kernel of its own and tiles of 64 rows per block
 // are faster (every block would take the statistics of its rows again).
@@ -581,10 +635,13 @@ int simple_layer(pd_ctx *c, int l, int R, int A, int nreq, int req0, int kv_over
   LinArgs base;
   memset(&base, 0, sizeof(base));
   base.rt = c->rows; base.d = d; base.H = H; base.hd = hd; base.kv_cap = c->kv_cap; base.kv_sat = c->kv_sat;
+  base.slice_stride = (size_t)c->R_pad * d;
+  const float *pend = c->pend_parts ? c->ypart : nullptr;        // what the layer before left out of x
   const bool gather = l == 0 && norm_inside(c, R);
   LinArgs a = base;
   if ((rc = normed(c, a, lw.n1g, lw.n1b, R, s))) return rc;
   if (gather) { a.tok_emb = c->tok_emb; a.pos_emb = c->pos_emb; }
+  a.pend = pend;
   a.out = c->qkv32; a.ldo = 3 * d;
   if (g.pos_kind == 1) {
     if ((rc = linear<LIN_STORE>(c, a, lw.wqkv, nullptr, R, 3 * d, d, s))) return rc;
@@ -612,6 +669,8 @@ int simple_layer(pd_ctx *c, int l, int R, int A, int nreq, int req0, int kv_over
   a.x = (const float *)c->att; a.out = c->x; a.res = c->x; a.ldo = d;
   LinArgs o = a;
   if (gather) { o.tok_emb = c->tok_emb; o.pos_emb = c->pos_emb; }
+  o.pend = pend;                        // the residual is completed here
+  c->pend_parts = 0;
   if ((rc = linear<LIN_RESID>(c, o, lw.wo, nullptr, R, d, d, s))) return rc;
   LinArgs f = base;
   if ((rc = normed(c, f, lw.n2g, lw.n2b, R, s))) return rc;
@@ -620,6 +679,11 @@ int simple_layer(pd_ctx *c, int l, int R, int A, int nreq, int req0, int kv_over
                        : linear<LIN_SWIGLU>(c, f, lw.w1, lw.w_up, R, ff, d, s);
   if (rc) return rc;
   a.x = (const float *)c->hb;
+  if (norm_inside(c, R) && ff >= 1024) {
+    a.out = c->ypart;
+    c->pend_parts = SLICES;
+    return linear<LIN_SLICE>(c, a, lw.w2, nullptr, R, d, ff, s);
+  }
   return linear<LIN_RESID>(c, a, lw.w2, nullptr, R, d, ff, s);
 }
 
@@ -630,7 +694,10 @@ int simple_head(pd_ctx *c, int R, float *logits, hipStream_t s) {
   memset(&a, 0, sizeof(a));
   int rc;
   a.rt = c->rows;
+  a.slice_stride = (size_t)c->R_pad * g.d_model;
   if ((rc = normed(c, a, c->fng, c->fnb, R, s))) return rc;
+  if (c->pend_parts) a.pend = c->ypart;
+  c->pend_parts = 0;
   a.logits = logits; a.S = c->S; a.part_val = c->lm_part_val; a.part_idx = c->lm_part_idx; a.n_tiles = c->vocab_pad / 16;
   c->lm_win = a.n_tiles;
   return linear<LIN_HEAD>(c, a, c->lm_head, nullptr, R, g.vocab, g.d_model, s, a.n_tiles);
