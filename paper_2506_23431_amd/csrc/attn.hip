@@ -65,18 +65,24 @@ __device__ __forceinline__ f16x8 ld_kv(const uint4 *p) {
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void pin(u32x4 &u) { asm volatile("" : "+v"(u)); }
 
-template <int HD, bool SPLIT, bool PAIR, bool BIAS = false, bool STREAM = false, int NW = 4>
+// VS = 2: two blocks per (request, head, query group), each with half of the dims of the values: both take all scores (the
+// second reads the keys from the L2 cache it shares with the first, whose number differs by heads x groups, a multiple of 8),
+// so that nothing is merged and a compute unit draws three quarters of the bytes.
+template <int HD, bool SPLIT, bool PAIR, bool BIAS = false, bool STREAM = false, int NW = 4, int VS = 1>
 __global__ __launch_bounds__(64 * NW, PAIR ? 1 : NW == 4 ? 3 : NW / 4)
 void k_attn_mfma(const f16_t *hot_q, const int4 *hot_qinfo, const f16_t *hot_kc, const int32_t *hot_kv_len, uint32_t hot_q_lo,
                  uint32_t hot_v, int hot_kv_cap, uint32_t hot_ha, uint32_t hot_nb, int hot_req0, AttnArgs a) {
-  constexpr int NC = HD / 32, NHB = HD / 16, PSTR = HD + 2;   // partial: m, l, O[HD] per query
+  constexpr int NC = HD / 32, NHB = HD / 16 / VS, PSTR = HD + 2;   // partial: m, l, O[HD] per query
+  static_assert(HD / 16 % VS == 0 && (VS == 1 || !PAIR), "whole 16-dim blocks; pair layers keep theirs together");
   __shared__ float sm_m[NW][16], sm_l[NW][16];
   __shared__ float sm_bias[BIAS ? BIAS_MAX : 1];
-  __shared__ floatx4 sm_o[NW][HD / 16][64];
+  __shared__ floatx4 sm_o[NW][NHB][64];
   __shared__ uint4 sm_q[(SPLIT ? 2 : 1) * NC][64];
   const int H = hot_ha & 0xffff, A = hot_ha >> 16, nqg = (A + 15) >> 4, d = H * HD;
   const int nsplit = hot_nb >> 20, nblk_static = hot_nb & 0xfffff;
-  int split = blockIdx.x, h = blockIdx.y, z = blockIdx.z;
+  // (halves: heads, groups, halves of the dims; no splits)
+  const int split = VS == 1 ? blockIdx.x : 0, h = VS == 1 ? blockIdx.y : blockIdx.x, z = VS == 1 ? blockIdx.z : blockIdx.y;
+  const int hb0 = VS == 1 ? 0 : (int)blockIdx.z * NHB;        // first 16-dim block of this block
   int reqi = z, qg = 0;
   if (nqg > 1) { reqi = z / nqg; qg = z - reqi * nqg; }
   const int req = hot_req0 + reqi;
@@ -107,7 +113,7 @@ void k_attn_mfma(const f16_t *hot_q, const int4 *hot_qinfo, const f16_t *hot_kc,
   }
 
   const uint4 *Kp = (const uint4 *)(hot_kc + ((size_t)req * H + h) * hot_kv_cap * HD) + lane;
-  const uint4 *Vp = Kp + hot_v;
+  const uint4 *Vp = Kp + hot_v + hb0 * 64;
   const uint4 *Kl = PAIR ? (const uint4 *)(a.kc_lo + ((size_t)req * H + h) * hot_kv_cap * HD) + lane : nullptr;
   const uint4 *Vl = PAIR ? (const uint4 *)(a.vc_lo + ((size_t)req * H + h) * hot_kv_cap * HD) + lane : nullptr;
   // 32-key blocks are dealt round-robin to the NW*nsplit waves that serve this (request, head):
@@ -129,7 +135,7 @@ void k_attn_mfma(const f16_t *hot_q, const int4 *hot_qinfo, const f16_t *hot_kc,
   auto load_v = [&](int kbx) {
 #pragma unroll
     for (int i = 0; i < NHB; ++i) {
-      vf[i].hv = ld_kv<STREAM>(&Vp[((size_t)kbx * NHB + i) * 64]);
+      vf[i].hv = ld_kv<STREAM>(&Vp[((size_t)kbx * (NHB * VS) + i) * 64]);
       if (PAIR) vl[i].hv = ld_kv<STREAM>(&Vl[((size_t)kbx * NHB + i) * 64]);
     }
   };
@@ -288,13 +294,14 @@ void k_attn_mfma(const f16_t *hot_q, const int4 *hot_qinfo, const f16_t *hot_kc,
 #pragma unroll
   for (int i = 0; i < NHB; ++i) sm_o[wave][i][lane] = o_acc[i];
   __syncthreads();
+  if (wave >= NHB) return;                    // no block of dims left to finish
   float mw[NW], M = -INFINITY;
 #pragma unroll
   for (int w = 0; w < NW; ++w) { mw[w] = sm_m[w][n]; M = fmaxf(M, mw[w]); }
   float fw[NW], lsum = 0.f;
 #pragma unroll
   for (int w = 0; w < NW; ++w) {
-    fw[w] = mw[w] == -INFINITY ? 0.f : exp2f(mw[w] - M);
+    fw[w] = mw[w] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw[w] - M);
     lsum += fw[w] * sm_l[w][n];
   }
   if (!qvalid) return;                        // lane (n, g) writes for query n only
@@ -310,7 +317,7 @@ void k_attn_mfma(const f16_t *hot_q, const int4 *hot_qinfo, const f16_t *hot_kc,
     for (int w = 1; w < NW; ++w) o += fw[w] * sm_o[w][i][lane];
     if (nsplit == 1) {
       float y[4] = {o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv};
-      store4_split(a.out, a.out_lo, act_off(r, h * HD + i * 16 + 4 * g, d), y);
+      store4_split(a.out, a.out_lo, act_off(r, h * HD + (hb0 + i) * 16 + 4 * g, d), y);
     } else {
       *(floatx4 *)(pp + 32 + ((i * 4 + g) * 16 + n) * 4) = o;
     }
@@ -384,12 +391,12 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float *part, const int
   store4_split(out, out_lo, act_off(r, h * HD + i * 16 + 4 * g, H * HD), y);
 }
 
-template <int HD, bool SPLIT, bool PAIR, bool BIAS, bool STREAM, int NW>
+template <int HD, bool SPLIT, bool PAIR, bool BIAS, bool STREAM, int NW, int VS = 1>
 static void launch_attn_nw(dim3 grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1, const AttnArgs &a) {
   const uint32_t q_lo = a.q_lo ? (uint32_t)((a.q_lo - a.q) / 8) : 0u, v = (uint32_t)((a.vc - a.kc) / 8);
   const uint32_t ha = (uint32_t)a.H | (uint32_t)a.A << 16, nb = (uint32_t)a.nblk_static | (uint32_t)a.nsplit << 20;
   const int32_t *kv_len = a.kv_override >= 0 ? nullptr : a.kv_len;
-  auto kernel = k_attn_mfma<HD, SPLIT, PAIR, BIAS, STREAM, NW>;
+  auto kernel = k_attn_mfma<HD, SPLIT, PAIR, BIAS, STREAM, NW, VS>;
   if (e0 || e1)
     hipExtLaunchKernelGGL(kernel, grid, dim3(64 * NW), 0, s, e0, e1, 0, a.q, a.rt.qinfo, a.kc, kv_len, q_lo, v, a.kv_cap, ha, nb, a.req0, a);
   else
@@ -397,7 +404,12 @@ static void launch_attn_nw(dim3 grid, hipStream_t s, hipEvent_t e0, hipEvent_t e
 }
 
 template <int HD, bool SPLIT, bool PAIR, bool BIAS, bool STREAM>
-static void launch_attn(dim3 grid, int nw, hipStream_t s, hipEvent_t e0, hipEvent_t e1, const AttnArgs &a) {
+static void launch_attn(dim3 grid, int nw, bool halves, hipStream_t s, hipEvent_t e0, hipEvent_t e1, const AttnArgs &a) {
+  if constexpr (!PAIR && HD / 16 % 2 == 0) {
+    const dim3 grid2(grid.y, grid.z, 2);
+    if (halves && nw == 8) return launch_attn_nw<HD, SPLIT, PAIR, BIAS, STREAM, 8, 2>(grid2, s, e0, e1, a);
+    if (halves) return launch_attn_nw<HD, SPLIT, PAIR, BIAS, STREAM, 4, 2>(grid2, s, e0, e1, a);
+  }
   if constexpr (!PAIR) {
     if (nw == 8) return launch_attn_nw<HD, SPLIT, PAIR, BIAS, STREAM, 8>(grid, s, e0, e1, a);
   }
@@ -451,6 +463,7 @@ int mfma_attention(pd_ctx *c, const LayerPtrs &lw, int A, int nreq, int req0, in
   PD_REQUIRE(a.H < 65536 && A < 65536 && a.nblk_static < (1 << 20) && a.nsplit < (1 << 12) && a.vc > a.kc &&
                  (uint64_t)(a.vc - a.kc) / 8 <= UINT32_MAX,
              PD_EINVAL, "an attention launch over %d rows and %d key blocks is too large", A, a.nblk_static);
+  const bool halves = attn_halves(shape, units, kv_override < 0 || mode, a.kc_lo != nullptr);
   dim3 grid(a.nsplit, g.n_head, nreq * a.nqg);
   // measurement: mode 1 attaches a start and a stop event to the dispatch of the main kernel itself
   // (their difference is the kernel's execution time), mode 2 records events before the main kernel
@@ -486,16 +499,16 @@ int mfma_attention(pd_ctx *c, const LayerPtrs &lw, int A, int nreq, int req0, in
 #define PD_ATTN_ONE(HDV, ARGS)                                                                         \
   do {                                                                                                 \
     const bool sp = a.q_lo != nullptr, pr = a.kc_lo != nullptr, bi = a.bias != nullptr;                \
-    if (bi && sp) launch_attn<HDV, true, false, true, false>(grid, nw, s, pe0, pe1, ARGS);                 \
-    else if (bi) launch_attn<HDV, false, false, true, false>(grid, nw, s, pe0, pe1, ARGS);                 \
-    else if (pr && sp && stream) launch_attn<HDV, true, true, false, true>(grid, nw, s, pe0, pe1, ARGS);   \
-    else if (pr && sp) launch_attn<HDV, true, true, false, false>(grid, nw, s, pe0, pe1, ARGS);            \
-    else if (pr && stream) launch_attn<HDV, false, true, false, true>(grid, nw, s, pe0, pe1, ARGS);        \
-    else if (pr) launch_attn<HDV, false, true, false, false>(grid, nw, s, pe0, pe1, ARGS);                 \
-    else if (sp && stream) launch_attn<HDV, true, false, false, true>(grid, nw, s, pe0, pe1, ARGS);        \
-    else if (sp) launch_attn<HDV, true, false, false, false>(grid, nw, s, pe0, pe1, ARGS);                 \
-    else if (stream) launch_attn<HDV, false, false, false, true>(grid, nw, s, pe0, pe1, ARGS);             \
-    else launch_attn<HDV, false, false, false, false>(grid, nw, s, pe0, pe1, ARGS);                        \
+    if (bi && sp) launch_attn<HDV, true, false, true, false>(grid, nw, halves, s, pe0, pe1, ARGS);                 \
+    else if (bi) launch_attn<HDV, false, false, true, false>(grid, nw, halves, s, pe0, pe1, ARGS);                 \
+    else if (pr && sp && stream) launch_attn<HDV, true, true, false, true>(grid, nw, halves, s, pe0, pe1, ARGS);   \
+    else if (pr && sp) launch_attn<HDV, true, true, false, false>(grid, nw, halves, s, pe0, pe1, ARGS);            \
+    else if (pr && stream) launch_attn<HDV, false, true, false, true>(grid, nw, halves, s, pe0, pe1, ARGS);        \
+    else if (pr) launch_attn<HDV, false, true, false, false>(grid, nw, halves, s, pe0, pe1, ARGS);                 \
+    else if (sp && stream) launch_attn<HDV, true, false, false, true>(grid, nw, halves, s, pe0, pe1, ARGS);        \
+    else if (sp) launch_attn<HDV, true, false, false, false>(grid, nw, halves, s, pe0, pe1, ARGS);                 \
+    else if (stream) launch_attn<HDV, false, false, false, true>(grid, nw, halves, s, pe0, pe1, ARGS);             \
+    else launch_attn<HDV, false, false, false, false>(grid, nw, halves, s, pe0, pe1, ARGS);                        \
   } while (0)
 #define PD_ATTN(HDV)                                                                                   \
   do {                                                                                                 \

@@ -50,6 +50,14 @@ inline AttnShape attn_shape(int head_dim, int units, int nblk, int cap, bool dec
   return best;
 }
 
+// Two blocks per unit, each with half of the dims of the values, where one block per unit leaves half of the chip idle (us
+// per launch, one block / two: 12 units of head size 64, 32-48 key blocks 6.6 / 6.1; 24 units, 22 blocks 6.0 / 5.4; 12 units, 16
+// blocks 4.7 / 4.4, 1-5 blocks with 4 waves 4.2 / 4.0; 128 units, 64 blocks from memory 16.5 / 14.2).  Beyond 128 units the second
+// blocks wait for the first.
+inline bool attn_halves(const AttnShape &shape, int units, bool decode, bool pair) {
+  return shape.splits == 1 && units <= 128 && decode && !pair;
+}
+
 // ---------------------------------------------------------------------------
 // Teacher-forced pass: consecutive requests that share launches, their rows padded to the longest of the group.
 // ---------------------------------------------------------------------------
