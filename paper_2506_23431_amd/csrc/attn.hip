@@ -44,6 +44,9 @@ struct AttnArgs {
   //    time half of the matrix.  tau - 2 = coordinate - subsequence tag on both sides.
   const float *bias; const uint16_t *coord;
   int bias_len, bias_off, coord_stride, coord_req_stride, coord_off, pos0;
+  // QP kernels: the projection in front; stats != NULL: it finishes a norm without bias, as in the projection kernels
+  const bf16_t *W, *xn; uint32_t xn_lo;
+  const float2 *stats; const float *c1; int norm_kind; float norm_eps;
 };
 constexpr int BIAS_MAX = 264;   // entries of one head's bias table that the kernel keeps in LDS
 
@@ -68,15 +71,26 @@ __device__ __forceinline__ void pin(u32x4 &u) { asm volatile("" : "+v"(u)); }
 // VS = 2: two blocks per (request, head, query group), each with half of the dims of the values: both take all scores (the
 // second reads the keys from the L2 cache it shares with the first, whose number differs by heads x groups, a multiple of 8),
 // so that nothing is merged and a compute unit draws three quarters of the bytes.
-template <int HD, bool SPLIT, bool PAIR, bool BIAS = false, bool STREAM = false, int NW = 4, int VS = 1>
+// QP: the block projects its queries itself from the rows in xn (the attention over the encoder states, whose queries are a
+// projection of their own): a launch and its way through memory less for a share of 16 HD weights rows per block.  The waves
+// cut K as in the projection kernels; PK: rows of at most 8, high and low parts as one fragment.  Width 768, 8 rows, 512
+// keys: 4.4 us (projection) + 4.5 -> 6.9.  With keys and values of the step projected here too a block's share of the weights is three
+// times as large and one compute unit draws it slower than 144 blocks do: width 768 12.2 us against 10.2, with few keys 9.4
+// against 8.6, width 1024 21.8 against 21.0; taken out.
+template <int HD, bool SPLIT, bool PAIR, bool BIAS = false, bool STREAM = false, int NW = 4, int VS = 1, bool QP = false, bool PK = false>
 __global__ __launch_bounds__(64 * NW, PAIR ? 1 : NW == 4 ? 3 : NW / 4)
 void k_attn_mfma(const f16_t *hot_q, const int4 *hot_qinfo, const f16_t *hot_kc, const int32_t *hot_kv_len, uint32_t hot_q_lo,
                  uint32_t hot_v, int hot_kv_cap, uint32_t hot_ha, uint32_t hot_nb, int hot_req0, AttnArgs a) {
+  // (QP: hot_q is xn, hot_q_lo the way to its low parts, hot_qinfo the weights, hot_kv_len the row sums of the norm or NULL)
   constexpr int NC = HD / 32, NHB = HD / 16 / VS, PSTR = HD + 2;   // partial: m, l, O[HD] per query
   static_assert(HD / 16 % VS == 0 && (VS == 1 || !PAIR), "whole 16-dim blocks; pair layers keep theirs together");
   __shared__ float sm_m[NW][16], sm_l[NW][16];
   __shared__ float sm_bias[BIAS ? BIAS_MAX : 1];
-  __shared__ floatx4 sm_o[NW][NHB][64];
+  constexpr int T = QP ? HD / 16 : 0;                         // column tiles projected
+  static_assert(!QP || (SPLIT && !PAIR && !BIAS && VS == 2 && NW == 8), "projecting launches: halves, 8 waves, low parts");
+  __shared__ floatx4 sm_raw[NW * (T > NHB ? T : NHB)][64];   // partial tiles of the projection, later the waves' outputs
+  floatx4 (*sm_o)[NHB][64] = (floatx4 (*)[NHB][64])sm_raw;
+  __shared__ float2 sm_stat[QP ? NW : 1][16];
   __shared__ uint4 sm_q[(SPLIT ? 2 : 1) * NC][64];
   const int H = hot_ha & 0xffff, A = hot_ha >> 16, nqg = (A + 15) >> 4, d = H * HD;
   const int nsplit = hot_nb >> 20, nblk_static = hot_nb & 0xfffff;
@@ -95,9 +109,10 @@ void k_attn_mfma(const f16_t *hot_q, const int4 *hot_qinfo, const f16_t *hot_kc,
   int qa = qg * 16 + n;                       // query index inside the request
   bool in_req = qa < A;
   int r = reqi * A + (in_req ? qa : 0);     // row (clamped: loads stay in bounds)
-  int4 qi = hot_qinfo[r];                    // {flags, sub, lim, req}
+  int4 qi;                                   // {flags, sub, lim, req}
   int n_keys = 0;
-  if (hot_kv_len) n_keys = hot_kv_len[req];   // NULL: the number is an argument
+  if (!QP) qi = hot_qinfo[r];
+  if (!QP && hot_kv_len) n_keys = hot_kv_len[req];   // NULL: the number is an argument
   // Query fragments (high and low parts) go to LDS, in operand order: the waves share them,
   // and keeping them out of the registers leaves room for three waves per SIMD.  Rows without a
   // token keep whatever finite numbers their q slots hold: all their keys are masked below, and
@@ -105,7 +120,7 @@ void k_attn_mfma(const f16_t *hot_q, const int4 *hot_qinfo, const f16_t *hot_kc,
   const size_t q_off = act_off(r, h * HD + g * 8, d);
   static_assert(NC <= 4, "one query fragment (and its low part) per wave");
   uint4 qh, qlo;
-  {
+  if (!QP) {
     const int c = min(wave, NC - 1);
     size_t off = q_off + (size_t)c * 512;     // the next 32 dims are the next fragment
     qh = *(const uint4 *)(hot_q + off);
@@ -139,6 +154,35 @@ void k_attn_mfma(const f16_t *hot_q, const int4 *hot_qinfo, const f16_t *hot_kc,
       if (PAIR) vl[i].hv = ld_kv<STREAM>(&Vl[((size_t)kbx * NHB + i) * 64]);
     }
   };
+  // ---- projection: k-tiles wave, wave + NW, ... of the block's T column tiles, two at a time ----
+  const int KT = d >> 5;
+  floatx4 pacc[T > 0 ? T : 1];
+  const uint4 *wq = (const uint4 *)hot_qinfo + lane, *px = nullptr;
+  constexpr int TA = T > 0 ? T : 1;
+  Frag pw[TA][2], pxh[2], pxl[2];
+  auto project_request = [&](int kt, int u) {
+    pxh[u].u = px[(size_t)kt * 64];
+    if (!PK) pxl[u].u = px[(size_t)kt * 64 + hot_q_lo];
+#pragma unroll
+    for (int j = 0; j < T; ++j) pw[j][u].hv = ld_kv<STREAM>(&wq[((size_t)(h * T + j) * KT + kt) * 64]);
+  };
+  auto project_multiply = [&](int u) {
+#pragma unroll
+    for (int j = 0; j < T; ++j) {
+      pacc[j] = mfma16(pw[j][u], pxh[u], pacc[j]);
+      if (!PK) pacc[j] = mfma16(pw[j][u], pxl[u], pacc[j]);
+    }
+  };
+  if constexpr (QP) {
+    const int pr = reqi * A + min(PK ? n & 7 : n, A - 1);               // (PK: lanes 8-15 of a row of 16 hold the low parts of 0-7)
+    px = (const uint4 *)hot_q + ((size_t)(pr >> 4) * KT * 64 + g * 16 + (pr & 15)) + (PK && n >= 8 ? hot_q_lo : 0);
+#pragma unroll
+    for (int j = 0; j < T; ++j) pacc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    if (wave < KT) project_request(wave, 0);                            // the same for the whole wave
+    if (wave + NW < KT) project_request(wave + NW, 1);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+
   // requested unconditionally (a wave beyond the last block fetches that block and ignores it), so
   // that the wait for the query rows above never has to wait for these
   load_k(min(kb, nblk_static - 1));
@@ -154,7 +198,7 @@ void k_attn_mfma(const f16_t *hot_q, const int4 *hot_qinfo, const f16_t *hot_kc,
     if (BIAS) kco.u = *(const u32x4 *)(kcp + min(max(kbx * 32 + 8 * g - a.coord_off, 0), a.coord_stride - 8));
   };
   load_tags(min(kb, nblk_static - 1));
-  if (!hot_kv_len) n_keys = a.kv_override;
+  if (!QP && !hot_kv_len) n_keys = a.kv_override;
   int q_pos = 0;
   float bias_pre[2] = {0.f, 0.f};
   if (BIAS) {
@@ -162,17 +206,66 @@ void k_attn_mfma(const f16_t *hot_q, const int4 *hot_qinfo, const f16_t *hot_kc,
     bias_pre[0] = a.bias[(size_t)h * a.bias_len + min((int)threadIdx.x, a.bias_len - 1)];
     bias_pre[1] = a.bias[(size_t)h * a.bias_len + min((int)threadIdx.x + 64 * NW, a.bias_len - 1)];
   }
+  if constexpr (QP) {
+    qi = a.rt.qinfo[r];
+    n_keys = a.kv_override >= 0 ? a.kv_override : a.kv_len[req];
+    // the sums of the norm: wave w, lane (n, g) takes the tile pairs g + 4 w, + 4 NW, ... of its row (fixed order)
+    const bool normed = hot_kv_len != nullptr;                          // the same for the whole launch
+    if (normed) {
+      const float4 *sp = (const float4 *)hot_kv_len + (size_t)r * KT;
+      float s1 = 0.f, s2 = 0.f;
+      for (int p = g + 4 * wave; p < KT; p += 4 * NW) { const float4 v = sp[p]; s1 += v.x + v.z; s2 += v.y + v.w; }
+      s1 = fold32(fold16(s1, Add()), Add());
+      s2 = fold32(fold16(s2, Add()), Add());
+      if (lane < 16) sm_stat[wave][lane] = make_float2(s1, s2);
+    }
+    for (int kt = wave; kt < KT; kt += 2 * NW) {
+      if (kt >= 2 * NW) {
+        project_request(kt, 0);
+        if (kt + NW < KT) project_request(kt + NW, 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      project_multiply(0);
+      if (kt + NW < KT) project_multiply(1);
+    }
+#pragma unroll
+    for (int j = 0; j < T; ++j) sm_raw[wave * T + j][lane] = pacc[j];
+    __syncthreads();
+    if (wave < T) {                                                     // wave j finishes tile j
+      floatx4 y = sm_raw[wave][lane];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) y += sm_raw[w * T + wave][lane];
+      if (PK)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] += rotate16<8>(y[e]);
+      if (normed) {
+        float2 tot = sm_stat[0][n];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) { tot.x += sm_stat[w][n].x; tot.y += sm_stat[w][n].y; }
+        const float inv_d = 1.f / (float)d, mean = a.norm_kind == 0 ? tot.x * inv_d : 0.f;
+        const float rstd = rsqrtf(fmaxf(tot.y * inv_d - mean * mean, 0.f) + a.norm_eps);
+        const float4 c1 = *(const float4 *)(a.c1 + (h * T + wave) * 16 + 4 * g);
+        y = floatx4{rstd * (y[0] - mean * c1.x), rstd * (y[1] - mean * c1.y), rstd * (y[2] - mean * c1.z), rstd * (y[3] - mean * c1.w)};
+      }
+      // queries in operand order: y[e] is dim 16 wave + 4 g + e (lanes beyond the rows hold copies, finite as those are)
+      const int dim0 = wave * 16 + 4 * g;
+      float yv[4] = {y[0], y[1], y[2], y[3]};
+      f16_t *dst = (f16_t *)&sm_q[dim0 >> 5][((dim0 & 31) >> 3) * 16 + n] + (dim0 & 7);
+      store4_split_h(dst, dst + (size_t)NC * 64 * 8, 0, yv);
+    }
+    __syncthreads();
+  }
   // (waves beyond the fragment count store a copy of the last fragment: same bytes, same place)
-  {
+  if (!QP) {
     const int c = min(wave, NC - 1);
     sm_q[c][lane] = qh;
     if (SPLIT) sm_q[NC + c][lane] = qlo;
   }
-  if (BIAS) {
+  if (BIAS && !QP) {
     if (threadIdx.x < BIAS_MAX) sm_bias[threadIdx.x] = bias_pre[0];
     if (threadIdx.x + 64 * NW < BIAS_MAX) sm_bias[threadIdx.x + 64 * NW] = bias_pre[1];
   }
-  __syncthreads();
+  if (!QP) __syncthreads();
 
   bool qvalid = in_req && (qi.x & ROW_VALID);
   int q_sub = qvalid ? qi.y : -1, q_lim = qvalid ? qi.z : 0;
@@ -416,8 +509,17 @@ static void launch_attn(dim3 grid, int nw, bool halves, hipStream_t s, hipEvent_
   launch_attn_nw<HD, SPLIT, PAIR, BIAS, STREAM, 4>(grid, s, e0, e1, a);
 }
 
+template <int HD>
+static void launch_attn_proj(int nreq, hipStream_t s, const AttnArgs &a) {
+  const uint32_t v = (uint32_t)((a.vc - a.kc) / 8), ha = (uint32_t)a.H | (uint32_t)a.A << 16, nb = (uint32_t)a.nblk_static | 1u << 20;
+  auto kernel = a.A <= 8 ? k_attn_mfma<HD, true, false, false, false, 8, 2, true, true>
+                         : k_attn_mfma<HD, true, false, false, false, 8, 2, true, false>;
+  hipLaunchKernelGGL(kernel, dim3(a.H, nreq, 2), dim3(512), 0, s, (const f16_t *)a.xn, (const int4 *)a.W, a.kc,
+                     (const int32_t *)a.stats, a.xn_lo, v, a.kv_cap, ha, nb, a.req0, a);
+}
+
 int mfma_attention(pd_ctx *c, const LayerPtrs &lw, int A, int nreq, int req0, int kv_override,
-                   hipStream_t s, const AttnMode *mode) {
+                   hipStream_t s, const AttnMode *mode, const AttnProj *proj) {
   const pd_config &g = c->cfg;
   if (kv_override >= 0 && !mode && c->opt_profile == 0) {     // context pass: many rows per request
     int rc = mfma_attention_ctx(c, lw, A, nreq, req0, kv_override, s);
@@ -464,6 +566,18 @@ int mfma_attention(pd_ctx *c, const LayerPtrs &lw, int A, int nreq, int req0, in
                  (uint64_t)(a.vc - a.kc) / 8 <= UINT32_MAX,
              PD_EINVAL, "an attention launch over %d rows and %d key blocks is too large", A, a.nblk_static);
   const bool halves = attn_halves(shape, units, kv_override < 0 || mode, a.kc_lo != nullptr);
+  if (proj) {
+    if (!halves || A > 16 || (g.head_dim != 64 && g.head_dim != 32) || !a.q_lo || c->opt_profile || c->opt_splits > 0 ||
+        g.d_model > 1024 || g.norm_kind != 1)
+      return 1;
+    a.W = proj->W; a.xn = (const bf16_t *)c->xn; a.xn_lo = (uint32_t)((mfma_lo(c, c->xn, g.d_model) - a.xn) / 8);
+    if (proj->c1) { a.stats = c->nstats; a.c1 = proj->c1; a.norm_kind = g.norm_kind; a.norm_eps = g.norm_eps; }
+    if (g.head_dim == 64) launch_attn_proj<64>(nreq, s, a);
+    else launch_attn_proj<32>(nreq, s, a);
+    PD_CHECK_HIP(hipGetLastError());
+    if (proj->c1) c->norm_fused = false;
+    return PD_OK;
+  }
   dim3 grid(a.nsplit, g.n_head, nreq * a.nqg);
   // measurement: mode 1 attaches a start and a stop event to the dispatch of the main kernel itself
   // (their difference is the kernel's execution time), mode 2 records events before the main kernel

@@ -158,11 +158,16 @@ int encdec_decoder_layer(pd_ctx *c, int l, int R, hipStream_t s, int A, int nreq
   // second cache, every one of the Lx keys visible to every row that carries a token
   const bool finish = c->norm_fused;
   if (!finish && (rc = mfma_norm(c, lw.n3g, nullptr, R, s))) return rc;
-  if ((rc = mfma_qkv(c, a, lw.p_cq, d / 16, 0, nullptr, nullptr, nullptr, nullptr, R, s, finish ? lw.cx1 : nullptr)))
-    return rc;
   AttnMode cross;
   memset(&cross, 0, sizeof(cross));
   cross.kc = lw.xkc; cross.vc = lw.xvc; cross.qinfo = c->qinfo_x; cross.L = c->Lx; cross.scale = 1.f;
-  if ((rc = mfma_attention(c, lw, A, nreq, req0, c->Lx, s, &cross))) return rc;
+  // (decode steps: the query projection inside the attention launch where the shape allows it)
+  const AttnProj xproj{lw.p_cq, finish ? lw.cx1 : nullptr};
+  rc = kv_self < 0 ? mfma_attention(c, lw, A, nreq, req0, c->Lx, s, &cross, &xproj) : 1;
+  if (rc < 0) return rc;
+  if (rc == 1) {
+    if ((rc = mfma_qkv(c, a, lw.p_cq, d / 16, 0, nullptr, nullptr, nullptr, nullptr, R, s, finish ? lw.cx1 : nullptr))) return rc;
+    if ((rc = mfma_attention(c, lw, A, nreq, req0, c->Lx, s, &cross))) return rc;
+  }
   return mfma_out_ffn(c, a, lw.p_co, lw, R, s, kv_self < 0 && l + 1 < g.n_layer ? c->layers[l + 1].n1g : nullptr);
 }
