@@ -11,6 +11,9 @@
 // same online softmax, same probabilities as single fp16 as the decode kernel; no split over blocks,
 // no partials, no subsequence tags (context rows see keys with index < their own position + 1).
 // Blocks are numbered so that the rows with the longest causal range start first.
+// Bound by vector instructions beside the products (the exponentials alone take as long as a third of those): blocks that every
+// query sees take no masks and a query tile is rescaled for maxima of its own (4096 rows over 4096 and 8192 keys, 16 heads of 128:
+// 383 -> 352 us per launch; with the scale in the exponential's multiply-add no less).
 #include "mfma_common.h"
 
 #include <algorithm>
@@ -141,38 +144,40 @@ __global__ __launch_bounds__(256, 2) void k_attn_ctx(CtxAttnArgs a) {
     // lane (n, g), tile tt, register j  <->  key kb*32 + 8g + 4tt + j
     const int key0 = kb * 32 + 8 * g;
     const bool all_visible = kb * 32 + 32 <= lim_all;
-    Frag pf[QT];
-    float alpha[QT];
-    bool rescale = false;
 #pragma unroll
-    for (int t = 0; t < QT; ++t) {
-      float sv[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float x = s[t][e >> 2][e & 3] * a.scale_log2;
-        sv[e] = (all_visible || key0 + e < q_lim[t]) ? x : -INFINITY;
-      }
-      float mloc = fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
-      mloc = fold32(fold16(mloc, Max()), Max());
-      const float m_new = fmaxf(m_run[t], mloc);
-      const float m_ref = m_new == -INFINITY ? 0.f : m_new;      // nothing visible yet: exp2(-inf) = 0, never NaN
-      alpha[t] = __builtin_amdgcn_exp2f(m_run[t] - m_ref);
-      float psum = 0.f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float p = __builtin_amdgcn_exp2f(sv[e] - m_ref);
-        psum += p;
-        pf[t].hh[e] = (f16_t)p;
-      }
-      l_run[t] = l_run[t] * alpha[t] + psum;
-      m_run[t] = m_new;
-      rescale |= alpha[t] != 1.f;
-    }
-    if (__any(rescale)) {                     // rare once the running maxima have settled
+    for (int t = 0; t < QT; ++t) { s[t][0] *= a.scale_log2; s[t][1] *= a.scale_log2; }
+    if (!all_visible) {                       // the same for the whole wave
 #pragma unroll
       for (int t = 0; t < QT; ++t)
 #pragma unroll
-        for (int i = 0; i < NHB; ++i) o_acc[t][i] *= alpha[t];
+        for (int e = 0; e < 8; ++e)
+          if (key0 + e >= q_lim[t]) s[t][e >> 2][e & 3] = -INFINITY;
+    }
+    // A tile's outputs are rescaled when one of its own queries has met a new maximum: somewhere in 32 queries that happens in
+    // almost every block of keys.  (A reference that follows only jumps beyond 2^8 saves nearly all of it, 322 us instead of
+    // 352, but then the largest probability is not exactly 1 and its rounding counts: errors 0.3 % larger.)
+    Frag pf[QT];
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+      float m = fmaxf(fmaxf(fmaxf(s[t][0][0], s[t][0][1]), fmaxf(s[t][0][2], s[t][0][3])),
+                      fmaxf(fmaxf(s[t][1][0], s[t][1][1]), fmaxf(s[t][1][2], s[t][1][3])));
+      const float m_new = fmaxf(fold32(fold16(m, Max()), Max()), m_run[t]);
+      float alpha = 1.f;
+      if (__any(m_new > m_run[t])) {
+        alpha = m_run[t] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run[t] - m_new);    // (then l and O are 0)
+        m_run[t] = m_new;
+#pragma unroll
+        for (int i = 0; i < NHB; ++i) o_acc[t][i] *= alpha;
+      }
+      const float m_ref = m_run[t] == -INFINITY ? 0.f : m_run[t];      // nothing visible yet: exp2(-inf) = 0, never NaN
+      float psum = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float p = __builtin_amdgcn_exp2f(s[t][e >> 2][e & 3] - m_ref);
+        psum += p;
+        pf[t].hh[e] = (f16_t)p;
+      }
+      l_run[t] = l_run[t] * alpha + psum;
     }
 #pragma unroll
     for (int i = 0; i < NHB; ++i)
