@@ -66,3 +66,18 @@ def test_more_requests_than_a_grid_dimension_holds():
         dec.close()
     want = np.tile(logits[16], (65600 // 16, 1, 1))
     assert np.abs(logits[65600] - want).max() < 1e-4
+
+
+@pytest.mark.parametrize("scale", [1e5, 1e6, 1e7])
+@pytest.mark.parametrize("heads,hd,ctx", [(4, 16, 70), (2, 64, 300)])
+def test_scores_far_apart(heads, hd, ctx, scale):
+    """Query and key rows scaled so that a row's scores differ by 1e6 to 1e14: one key takes the whole weight, every other
+    exponential is 0 (its argument is beyond what a 32-bit product can be reduced from), in the tiles of a wave, between
+    them and where the waves are merged."""
+    cfg = W(f"scores-{scale:g}", heads, hd, 100, ctx)
+    w, tokens = pi.make_weights(cfg, threads=4), pi.make_context(cfg)
+    for layer in w["layers"]:
+        layer["wqkv"][:2 * cfg.d_model] *= np.float32(scale)
+    dec = make_decoder(cfg, w)
+    compare_teacher_forced(cfg, w, tokens, dec, oracle_run(cfg, w, tokens), log=lambda m: print(m, flush=True))
+    dec.close()
