@@ -134,11 +134,12 @@ int mfma_fold_norms(pd_ctx *c, hipStream_t s) {
 // x = E_tok[token] (+ E_pos[position]), zero for rows without a token) and written to x.
 template <int NG, int NP, bool EMB>     // 8-value granules per thread: d <= 2048 * NG; NP pending slices
 __global__ __launch_bounds__(256) void k_norm_bf16(const int32_t *flags, const void *src1, const void *src2, const float *g,
-                                                   const float *b, int d, int R, int part_stride, int kind,
+                                                   const float *b, int d, int R, int rows_pad, int kind,
                                                    const bf16_t *tok_emb, const bf16_t *pos_emb, float eps, float *xw,
                                                    bf16_t *xn, bf16_t *xn_lo) {
   // (the first 14 words arrive in registers: what the first requests need)
   const float *x = (const float *)src1, *ypart = (const float *)src2;            // rows and pending slices
+  const size_t part_stride = (size_t)rows_pad * d;
   const int32_t *tok = (const int32_t *)src1, *pos = (const int32_t *)src2;      // EMB: token and position of a row
   int r = blockIdx.x;
   int fl = r < R ? flags[r] : 0;
@@ -180,7 +181,7 @@ __global__ __launch_bounds__(256) void k_norm_bf16(const int32_t *flags, const v
       float4 y[NP > 0 ? NP : 1];
 #pragma unroll
       for (int pp = 0; pp < NP; ++pp)
-        y[pp] = in ? *(const float4 *)(ypart + (size_t)pp * part_stride + (size_t)r * d + c + 4 * h)
+        y[pp] = in ? *(const float4 *)(ypart + pp * part_stride + (size_t)r * d + c + 4 * h)
                    : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
       for (int pp = 0; pp < NP; ++pp) { t.x += y[pp].x; t.y += y[pp].y; t.z += y[pp].z; t.w += y[pp].w; }
@@ -229,8 +230,9 @@ __global__ __launch_bounds__(256) void k_norm_bf16(const int32_t *flags, const v
 // than its row and many waves are resident.
 template <int NGW, int NP>     // granules per lane: d <= 512 * NGW; NP pending slices
 __global__ __launch_bounds__(256) void k_norm_rows(const int32_t *flags, float *x, const float *ypart, const float *g,
-                                                   const float *b, int d, int R, int part_stride, int kind, float eps,
+                                                   const float *b, int d, int R, int rows_pad, int kind, float eps,
                                                    bf16_t *xn, bf16_t *xn_lo) {
+  const size_t part_stride = (size_t)rows_pad * d;
   const int lane = threadIdx.x & 63, r = blockIdx.x * 4 + (threadIdx.x >> 6);
   const bool valid = r < R && (flags[r] & ROW_VALID);
   float *xr = x + (size_t)r * d;
@@ -245,7 +247,7 @@ __global__ __launch_bounds__(256) void k_norm_rows(const int32_t *flags, float *
       float4 y[NP > 0 ? NP : 1];
 #pragma unroll
       for (int pp = 0; pp < NP; ++pp)
-        y[pp] = in ? *(const float4 *)(ypart + (size_t)pp * part_stride + (size_t)r * d + c + 4 * h)
+        y[pp] = in ? *(const float4 *)(ypart + pp * part_stride + (size_t)r * d + c + 4 * h)
                    : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
       for (int pp = 0; pp < NP; ++pp) { t.x += y[pp].x; t.y += y[pp].y; t.z += y[pp].z; t.w += y[pp].w; }
@@ -303,12 +305,10 @@ int mfma_norm(pd_ctx *c, const float *gain, const float *bias, int R, hipStream_
   bf16_t *xn = (bf16_t *)c->xn;
   const pd_config &g = c->cfg;
   PD_REQUIRE(d <= 2048 * 4, PD_EINVAL, "d_model %d too large for the norm kernel", d);
-  PD_REQUIRE((int64_t)c->R_pad * d <= INT32_MAX, PD_EINVAL, "%d rows of %d values are too many for the norm kernel", c->R_pad, d);
-  const int part_stride = c->R_pad * d;
   if (rows > 128 && !c->embed_pending && !c->packed) {
 #define PD_NORM_R(G, P)                                                                           \
   hipLaunchKernelGGL((k_norm_rows<G, P>), dim3(rows / 4), dim3(256), 0, s, c->rows.flags, c->x, c->ypart, gain, bias, d, \
-                     R, part_stride, g.norm_kind, g.norm_eps, xn, mfma_lo(c, xn, d))
+                     R, c->R_pad, g.norm_kind, g.norm_eps, xn, mfma_lo(c, xn, d))
 #define PD_NORM_RP(G)                                                                            \
   switch (c->pend_parts) {                                                                       \
     case 0: PD_NORM_R(G, 0); break;                                                              \
@@ -327,7 +327,7 @@ int mfma_norm(pd_ctx *c, const float *gain, const float *bias, int R, hipStream_
 #define PD_NORM(V, P, E)                                                                         \
   hipLaunchKernelGGL((k_norm_bf16<V, P, E>), dim3(rows), dim3(256), 0, s, c->rows.flags,                          \
                      E ? (const void *)c->rows.tok : c->x, E ? (const void *)c->rows.pos : c->ypart, gain, bias, d, R,    \
-                     part_stride, g.norm_kind, (const bf16_t *)c->tok_emb, (const bf16_t *)c->pos_emb, g.norm_eps, c->x,  \
+                     c->R_pad, g.norm_kind, (const bf16_t *)c->tok_emb, (const bf16_t *)c->pos_emb, g.norm_eps, c->x,  \
                      xn, mfma_lo(c, xn, d))
 #define PD_NORM_P(V)                                                                             \
   if (c->embed_pending) { PD_NORM(V, 0, true); }                                                 \
