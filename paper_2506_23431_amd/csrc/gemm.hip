@@ -655,35 +655,29 @@ __device__ __forceinline__ void gemm_chunk(floatx4 (&acc)[NT][RT][NA], const uin
 // decides on the next read; a decode step is 30-270 such launches one after the other.
 #define PD_GEMM_HOT_PARAMS                                                                                        \
   const bf16_t *hot_w, const bf16_t *hot_x, const void *hot_a, const void *hot_b, const void *hot_c, uint32_t hot_lo, \
-      uint32_t hot_k, uint32_t hot_n, int hot_r
+      uint32_t hot_k, uint32_t hot_share, uint32_t hot_n
 struct GemmHot {
   const bf16_t *w, *x;        // weights, activations
   const void *a, *b, *c;      // EPI_RESID_NORM: x_res, gain; finishing a norm: stats_in (else NULL), c1; EPI_QKV*: c = kvinfo
-  uint32_t lo;                // low parts behind x, in 16-byte granules
-  uint32_t k, n;              // k-tiles | k_share << 16; n_tiles | (c2 follows c1) << 24
-  int r;                      // rows
+  GemmWords n;
 };
 template <int EPI>
-static int gemm_hot(const GemmArgs &a, GemmHot *h) {
-  const int KT = a.K / 32;
-  PD_REQUIRE(KT < 65536 && a.k_share < 65536 && a.n_tiles < (1 << 24), PD_EINVAL, "a projection of %d x %d is too large",
-             a.n_tiles * 16, a.K);
-  PD_REQUIRE(!a.stats_in || (a.stats_tiles == 2 * KT && (!a.c2 || a.c2 == a.c1 + (size_t)a.n_tiles * 16)), PD_EINVAL,
-             "a norm is finished over the whole rows, with c2 behind c1");
-  const bool out = EPI == EPI_RESID_NORM;
-  *h = GemmHot{a.W, a.xn, out ? (const void *)a.x_res : a.stats_in, out ? a.gain : a.c1, a.rt.kvinfo,
-               a.xn_lo ? (uint32_t)((a.xn_lo - a.xn) / 8) : 0u, (uint32_t)KT | (uint32_t)a.k_share << 16,
-               (uint32_t)a.n_tiles | (a.c2 ? 1u << 24 : 0u), a.R};
-  return PD_OK;
+static GemmHot gemm_hot(const GemmArgs &a) {
+  constexpr bool out = EPI == EPI_RESID_NORM;
+  return GemmHot{a.W, a.xn, out ? (const void *)a.x_res : a.stats_in, out ? a.gain : a.c1, a.rt.kvinfo,
+                 out ? gemm_words_rows(a.xn_lo ? a.xn_lo - a.xn : 0, a.K, a.k_share, a.n_tiles, a.R)
+                     : gemm_words(a.xn_lo ? a.xn_lo - a.xn : 0, a.K, a.k_share, a.n_tiles, a.c2 != nullptr)};
 }
 template <int EPI, typename Kernel>
 static int launch_gemm_kernel(Kernel kernel, dim3 grid, int threads, GemmArgs a, hipStream_t s) {
-  GemmHot h;
+  PD_REQUIRE(!a.stats_in || (a.stats_tiles == a.K / 16 && (!a.c2 || a.c2 == a.c1 + (size_t)a.n_tiles * 16)), PD_EINVAL,
+             "a norm is finished over the whole rows, with c2 behind c1");
+  PD_REQUIRE(EPI != EPI_RESID_NORM || (a.R <= 128 && a.n_tiles < 65536), PD_EINVAL, "%d rows of %d values cannot prepare a norm",
+             a.R, a.n_tiles * 16);
   a.n_win = grid.x;
   if (EPI == EPI_LM) *a.win_out = grid.x;
-  const int rc = gemm_hot<EPI>(a, &h);
-  if (rc) return rc;
-  hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, h.w, h.x, h.a, h.b, h.c, h.lo, h.k, h.n, h.r, a);
+  const GemmHot h = gemm_hot<EPI>(a);
+  hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, h.w, h.x, h.a, h.b, h.c, h.n.lo, h.n.k, h.n.share, h.n.n, a);
   PD_CHECK_HIP(hipGetLastError());
   return PD_OK;
 }
@@ -707,7 +701,8 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(PD_GEMM_HOT_PARAMS, GemmAr
   const int wk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int nt0 = blockIdx.x * NT;
   const int m = lane & 15;
-  const int KT = hot_k & 0xffff, k_share = hot_k >> 16, n_tiles = hot_n & 0xffffff;
+  constexpr bool OUT = EPI == EPI_RESID_NORM;
+  const int KT = hot_k, k_share = hot_share, n_tiles = OUT ? words_tiles_rows(hot_n) : words_tiles(hot_n);
   // waves along K: NW_K in this block times gridDim.y blocks (EPI_RESID only)
   const int gk = blockIdx.y * NW_K + wk;
   const int kt0 = min(gk * k_share, KT), kt1 = min(kt0 + k_share, KT);
@@ -716,7 +711,7 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(PD_GEMM_HOT_PARAMS, GemmAr
   for (int t = 0; t < NT; ++t) tile[t] = min(nt0 + t, n_tiles - 1);   // tiles past the end repeat the last one
   const uint4 *wp = (const uint4 *)hot_w + lane;
   const uint4 *xp = (const uint4 *)hot_x + lane + (size_t)rz * KT * 64;
-  const uint4 *xl = SPLIT ? xp + hot_lo : nullptr;
+  const uint4 *xl = SPLIT ? xp + words_granules(hot_lo) : nullptr;
   // row data of the KV-append epilogue, requested now so that it arrives with the weights (where a row's logits go is
   // read by the epilogue that stores them: requested here it held 4 registers per row tile in every vocabulary launch)
   constexpr bool QKV = EPI == EPI_QKV || EPI == EPI_QKV_ROPE;
@@ -736,7 +731,7 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(PD_GEMM_HOT_PARAMS, GemmAr
   if (fused_norm && wk < NT) {      // wave w < NT finishes tile nt0 + w
     const float *c1 = (const float *)hot_b + min(nt0 + wk, n_tiles - 1) * 16 + 4 * (lane >> 4);
     pre_n.c1 = *(const float4 *)c1;
-    pre_n.c2 = hot_n >> 24 ? *(const float4 *)(c1 + n_tiles * 16) : make_float4(0.f, 0.f, 0.f, 0.f);
+    pre_n.c2 = words_c2(hot_n) ? *(const float4 *)(c1 + n_tiles * 16) : make_float4(0.f, 0.f, 0.f, 0.f);
   }
   ResidPre pre_r;
   if (FUSED_OUT && wk < NT) {       // wave w < NT finishes tile nt0 + w
@@ -744,7 +739,7 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(PD_GEMM_HOT_PARAMS, GemmAr
     pre_r.g = *(const float4 *)((const float *)hot_b + n0);
     // (rows beyond R read row R - 1 and are masked where the value is used, not here: touching the
     // value now would make the wave wait for it before it has asked for its weights)
-    pre_r.x = *(const float4 *)((const float *)hot_a + (size_t)min(rz * 16 + m, max(hot_r - 1, 0)) * (n_tiles * 16) + n0);
+    pre_r.x = *(const float4 *)((const float *)hot_a + (size_t)min(rz * 16 + m, words_last_row(hot_n)) * (n_tiles * 16) + n0);
   }
   constexpr int NA = (SPLIT && NT * RT <= 2) ? 2 : 1;
   floatx4 acc2[NT][RT][NA];
@@ -1052,7 +1047,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm_t(PD_GEMM_HOT_PARAMS, GemmArgs 
   __shared__ bf16x8 sm_x[2][NA][64];   // (vector types throughout: struct copies would keep xr in scratch memory)
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int m = lane & 15;
-  const int KT = hot_k & 0xffff, per_slice = hot_k >> 16, n_tiles = hot_n & 0xffffff;
+  const int KT = hot_k, per_slice = hot_share, n_tiles = words_tiles(hot_n);
   const int kt0 = min((int)blockIdx.y * per_slice, KT), kt1 = min(kt0 + per_slice, KT);
   const int rt0 = blockIdx.z * RT, r0 = rt0 * 16;
   const int nt0 = (blockIdx.x * NW + w) * NT;
@@ -1070,7 +1065,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm_t(PD_GEMM_HOT_PARAMS, GemmArgs 
 #pragma unroll
   for (int i = 0; i < NAW; ++i) {
     const int f = (w * NAW + i) % NA;
-    xsrc[i] = (const bf16x8 *)hot_x + (SPLIT && f >= RT ? hot_lo : 0) + (size_t)(rt0 + f % RT) * KT * 64 + lane;
+    xsrc[i] = (const bf16x8 *)hot_x + (SPLIT && f >= RT ? words_granules(hot_lo) : 0) + (size_t)(rt0 + f % RT) * KT * 64 + lane;
   }
   const int len = kt1 - kt0;
   bf16x8 xr[2][NAW], wr[2][NT];         // k-tiles in flight, slot = k-tile index mod 2; past the end: the last one again

@@ -59,6 +59,28 @@ inline bool attn_halves(const AttnShape &shape, int units, bool decode, bool pai
 }
 
 // ---------------------------------------------------------------------------
+// Sizes that a projection kernel gets as leading arguments (four words beside five pointers fill the registers that a
+// wave starts with), wide enough for every size that a context can have.
+// ---------------------------------------------------------------------------
+struct GemmWords {
+  uint32_t lo;          // way from the activations to their low parts, in units of 64 values
+  uint32_t k, share;    // k-tiles, and those of a wave (or of a block)
+  uint32_t n;           // column tiles | c2 follows c1 (bit 31); of a projection that prepares a norm: tiles | last row << 16
+};
+constexpr GemmWords gemm_words(int64_t lo_values, int K, int k_share, int n_tiles, bool c2) {
+  return GemmWords{(uint32_t)(lo_values / 64), (uint32_t)(K / 32), (uint32_t)k_share, (uint32_t)n_tiles | (c2 ? 1u << 31 : 0u)};
+}
+constexpr GemmWords gemm_words_rows(int64_t lo_values, int K, int k_share, int n_tiles, int rows) {
+  return GemmWords{(uint32_t)(lo_values / 64), (uint32_t)(K / 32), (uint32_t)k_share,
+                   (uint32_t)n_tiles | (uint32_t)(rows > 0 ? rows - 1 : 0) << 16};
+}
+constexpr size_t words_granules(uint32_t lo) { return (size_t)lo * 8; }      // in 16-byte granules of 8 values
+constexpr int words_tiles(uint32_t n) { return (int)(n & 0x7fffffffu); }
+constexpr bool words_c2(uint32_t n) { return n >> 31; }
+constexpr int words_tiles_rows(uint32_t n) { return (int)(n & 0xffffu); }
+constexpr int words_last_row(uint32_t n) { return (int)(n >> 16); }
+
+// ---------------------------------------------------------------------------
 // Teacher-forced pass: consecutive requests that share launches, their rows padded to the longest of the group.
 // ---------------------------------------------------------------------------
 struct PassCost { double pass_us, row_us; };

@@ -39,3 +39,8 @@ def parity(cfg, gigabytes, **capacity):
 def test_row_buffers_beyond_32_bits():
     """1050000 rows of 2048 values: the K slices that the last norm adds lie 2^31 values apart."""
     parity(W("rows"), 180, max_batch=150000)
+
+
+def test_inner_width_of_65536_k_tiles():
+    """An FFN of 2^21 inner values: the second projection runs over 65536 k-tiles, in steps and in the context pass."""
+    parity(W("inner", n_layer=2, d_model=32, n_head=1, head_dim=32, d_ff=1 << 21, ctx_len=20, n_sub=3, sub_tokens=3), 10)

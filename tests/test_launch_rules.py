@@ -33,6 +33,15 @@ void tiling(int n_tiles, int kt, int rows, int max_slices, int split, int kind, 
   out[0] = t.cut; out[1] = t.rt; out[2] = t.nt; out[3] = t.ks;
 }
 int vocab(int n_tiles, int kt, int rows) { return vocab_shares_row_tiles(n_tiles, kt, rows); }
+void words(int64_t lo, int K, int share, int n_tiles, int c2, int64_t *out) {
+  const GemmWords w = gemm_words(lo, K, share, n_tiles, c2);
+  out[0] = words_granules(w.lo); out[1] = w.k; out[2] = w.share; out[3] = words_tiles(w.n); out[4] = words_c2(w.n); out[5] = 0;
+}
+void words_rows(int64_t lo, int K, int share, int n_tiles, int rows, int64_t *out) {
+  const GemmWords w = gemm_words_rows(lo, K, share, n_tiles, rows);
+  out[0] = words_granules(w.lo); out[1] = w.k; out[2] = w.share; out[3] = words_tiles_rows(w.n); out[4] = 0;
+  out[5] = words_last_row(w.n);
+}
 }
 """
 
@@ -216,3 +225,16 @@ def test_vocabulary_kernel_is_the_faster_measured(rules, n_tiles, k, rows, cut, 
 
 def test_few_rows_keep_waves_that_cut_k(rules):
     assert not any(rules.vocab(n, kt, rows) for n, kt, rows in itertools.product((1, 1024, 8000, 20000), (1, 24, 128), (1, 16, 32)))
+
+
+def test_words_of_a_projection_hold_every_size(rules):
+    """What a projection kernel unpacks is what the launch packed, up to sizes that no memory holds: 2^31 inner values, a
+    vocabulary of 2^31 words, low parts 2^38 values away."""
+    out = (C.c_int64 * 6)()
+    for lo, k, share, tiles, c2 in itertools.product((0, 64, 512, 1 << 33, (1 << 38) - 64), (32, 1 << 21, (1 << 31) - 32),
+                                                     (1, 65535, 65536, (1 << 26) - 1), (1, (1 << 24) + 1, (1 << 28) - 1), (0, 1)):
+        rules.words(C.c_int64(lo), k, share, tiles, c2, out)
+        assert list(out) == [lo // 8, k // 32, share, tiles, c2, 0]
+    for tiles, rows in itertools.product((1, 512, 65535), (0, 1, 2, 16, 128)):
+        rules.words_rows(C.c_int64(64), 64, 2, tiles, rows, out)
+        assert list(out) == [8, 2, 2, tiles, 0, max(rows - 1, 0)]
