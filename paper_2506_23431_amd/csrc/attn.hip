@@ -124,11 +124,11 @@ void k_attn_mfma(const f16_t *hot_q, const int4 *hot_qinfo, const f16_t *hot_kc,
     const int c = min(wave, NC - 1);
     size_t off = q_off + (size_t)c * 512;     // the next 32 dims are the next fragment
     qh = *(const uint4 *)(hot_q + off);
-    if (SPLIT) qlo = *((const uint4 *)(hot_q + off) + hot_q_lo);
+    if (SPLIT) qlo = *((const uint4 *)(hot_q + off) + words_granules(hot_q_lo));
   }
 
   const uint4 *Kp = (const uint4 *)(hot_kc + ((size_t)req * H + h) * hot_kv_cap * HD) + lane;
-  const uint4 *Vp = Kp + hot_v + hb0 * 64;
+  const uint4 *Vp = Kp + (size_t)hot_v * 16 + hb0 * 64;      // (in units of 256 bytes, to which caches are aligned)
   const uint4 *Kl = PAIR ? (const uint4 *)(a.kc_lo + ((size_t)req * H + h) * hot_kv_cap * HD) + lane : nullptr;
   const uint4 *Vl = PAIR ? (const uint4 *)(a.vc_lo + ((size_t)req * H + h) * hot_kv_cap * HD) + lane : nullptr;
   // 32-key blocks are dealt round-robin to the NW*nsplit waves that serve this (request, head):
@@ -162,7 +162,7 @@ void k_attn_mfma(const f16_t *hot_q, const int4 *hot_qinfo, const f16_t *hot_kc,
   Frag pw[TA][2], pxh[2], pxl[2];
   auto project_request = [&](int kt, int u) {
     pxh[u].u = px[(size_t)kt * 64];
-    if (!PK) pxl[u].u = px[(size_t)kt * 64 + hot_q_lo];
+    if (!PK) pxl[u].u = px[(size_t)kt * 64 + words_granules(hot_q_lo)];
 #pragma unroll
     for (int j = 0; j < T; ++j) pw[j][u].hv = ld_kv<STREAM>(&wq[((size_t)(h * T + j) * KT + kt) * 64]);
   };
@@ -175,7 +175,7 @@ void k_attn_mfma(const f16_t *hot_q, const int4 *hot_qinfo, const f16_t *hot_kc,
   };
   if constexpr (QP) {
     const int pr = reqi * A + min(PK ? n & 7 : n, A - 1);               // (PK: lanes 8-15 of a row of 16 hold the low parts of 0-7)
-    px = (const uint4 *)hot_q + ((size_t)(pr >> 4) * KT * 64 + g * 16 + (pr & 15)) + (PK && n >= 8 ? hot_q_lo : 0);
+    px = (const uint4 *)hot_q + ((size_t)(pr >> 4) * KT * 64 + g * 16 + (pr & 15)) + (PK && n >= 8 ? words_granules(hot_q_lo) : 0);
 #pragma unroll
     for (int j = 0; j < T; ++j) pacc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
     if (wave < KT) project_request(wave, 0);                            // the same for the whole wave
@@ -486,7 +486,7 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float *part, const int
 
 template <int HD, bool SPLIT, bool PAIR, bool BIAS, bool STREAM, int NW, int VS = 1>
 static void launch_attn_nw(dim3 grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1, const AttnArgs &a) {
-  const uint32_t q_lo = a.q_lo ? (uint32_t)((a.q_lo - a.q) / 8) : 0u, v = (uint32_t)((a.vc - a.kc) / 8);
+  const uint32_t q_lo = a.q_lo ? (uint32_t)((a.q_lo - a.q) / 64) : 0u, v = (uint32_t)((a.vc - a.kc) / 128);
   const uint32_t ha = (uint32_t)a.H | (uint32_t)a.A << 16, nb = (uint32_t)a.nblk_static | (uint32_t)a.nsplit << 20;
   const int32_t *kv_len = a.kv_override >= 0 ? nullptr : a.kv_len;
   auto kernel = k_attn_mfma<HD, SPLIT, PAIR, BIAS, STREAM, NW, VS>;
@@ -511,7 +511,7 @@ static void launch_attn(dim3 grid, int nw, bool halves, hipStream_t s, hipEvent_
 
 template <int HD>
 static void launch_attn_proj(int nreq, hipStream_t s, const AttnArgs &a) {
-  const uint32_t v = (uint32_t)((a.vc - a.kc) / 8), ha = (uint32_t)a.H | (uint32_t)a.A << 16, nb = (uint32_t)a.nblk_static | 1u << 20;
+  const uint32_t v = (uint32_t)((a.vc - a.kc) / 128), ha = (uint32_t)a.H | (uint32_t)a.A << 16, nb = (uint32_t)a.nblk_static | 1u << 20;
   auto kernel = a.A <= 8 ? k_attn_mfma<HD, true, false, false, false, 8, 2, true, true>
                          : k_attn_mfma<HD, true, false, false, false, 8, 2, true, false>;
   hipLaunchKernelGGL(kernel, dim3(a.H, nreq, 2), dim3(512), 0, s, (const f16_t *)a.xn, (const int4 *)a.W, a.kc,
@@ -563,14 +563,14 @@ int mfma_attention(pd_ctx *c, const LayerPtrs &lw, int A, int nreq, int req0, in
   const int nw = shape.waves;
   a.nsplit = shape.splits;
   PD_REQUIRE(a.H < 65536 && A < 65536 && a.nblk_static < (1 << 20) && a.nsplit < (1 << 12) && a.vc > a.kc &&
-                 (uint64_t)(a.vc - a.kc) / 8 <= UINT32_MAX,
+                 (a.vc - a.kc) % 128 == 0,
              PD_EINVAL, "an attention launch over %d rows and %d key blocks is too large", A, a.nblk_static);
   const bool halves = attn_halves(shape, units, kv_override < 0 || mode, a.kc_lo != nullptr);
   if (proj) {
     if (!halves || A > 16 || (g.head_dim != 64 && g.head_dim != 32) || !a.q_lo || c->opt_profile || c->opt_splits > 0 ||
         g.d_model > 1024 || g.norm_kind != 1)
       return 1;
-    a.W = proj->W; a.xn = (const bf16_t *)c->xn; a.xn_lo = (uint32_t)((mfma_lo(c, c->xn, g.d_model) - a.xn) / 8);
+    a.W = proj->W; a.xn = (const bf16_t *)c->xn; a.xn_lo = (uint32_t)((mfma_lo(c, c->xn, g.d_model) - a.xn) / 64);
     if (proj->c1) { a.stats = c->nstats; a.c1 = proj->c1; a.norm_kind = g.norm_kind; a.norm_eps = g.norm_eps; }
     if (g.head_dim == 64) launch_attn_proj<64>(nreq, s, a);
     else launch_attn_proj<32>(nreq, s, a);

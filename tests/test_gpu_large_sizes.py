@@ -44,3 +44,8 @@ def test_row_buffers_beyond_32_bits():
 def test_inner_width_of_65536_k_tiles():
     """An FFN of 2^21 inner values: the second projection runs over 65536 k-tiles, in steps and in the context pass."""
     parity(W("inner", n_layer=2, d_model=32, n_head=1, head_dim=32, d_ff=1 << 21, ctx_len=20, n_sub=3, sub_tokens=3), 10)
+
+
+def test_caches_more_than_64_gib_long():
+    """Values lie 68.7 GB behind their keys (64 requests of 262150 context tokens, one of them in use)."""
+    parity(W("keys", ctx_len=40, n_sub=3, sub_tokens=4), 150, max_batch=64, max_ctx=262150)
