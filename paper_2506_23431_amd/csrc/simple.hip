@@ -456,16 +456,16 @@ __device__ __forceinline__ float exp_f32(float x) {
 
 template <typename KT, int NHB, int NW, bool VEC>      // NHB: 16-dim blocks of a head (hd <= 16 NHB)
 __global__ __launch_bounds__(64 * NW) void k_attn_f32(const float *hot_qkv, const void *hot_k, const void *hot_v,
-                                                      const int4 *hot_qinfo, const int32_t *hot_kv_len, int hot_hd, int kv_cap,
-                                                      uint32_t hot_ha, int hot_req0, AttnF32Args a) {
+                                                      const int4 *hot_qinfo, const int32_t *hot_kv_len, uint32_t hot_hda, int kv_cap,
+                                                      int H, int hot_req0, AttnF32Args a) {
   __shared__ floatx4 sm_o[NW][NHB][64];
   __shared__ float sm_m[NW][16], sm_l[NW][16];
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
   // (one grid dimension: the others end at 65535, and a batch may have more requests)
-  const int H = hot_ha & 0xffff, A = hot_ha >> 16, nqg = (A + 15) >> 4, unit = blockIdx.x / H, h = blockIdx.x - unit * H;
+  const int hd = hot_hda & 0xffff, A = hot_hda >> 16, nqg = (A + 15) >> 4, unit = blockIdx.x / H, h = blockIdx.x - unit * H;
   int reqi = unit, qg = 0;
   if (nqg > 1) { reqi = unit / nqg; qg = unit - reqi * nqg; }
-  const int req = hot_req0 + reqi, hd = hot_hd, d = H * hd;
+  const int req = hot_req0 + reqi, d = H * hd;
   const int qa = qg * 16 + m;
   const int r = reqi * A + min(qa, A - 1);              // clamped: loads stay in bounds
   const int4 qi = hot_qinfo[r];                         // {flags, sub, lim, req}
@@ -586,13 +586,13 @@ template <typename KT>
 static int attention_f32(const AttnF32Args &a, int nreq, hipStream_t s) {
   const dim3 grid(a.H * nreq * a.nqg);
   const int32_t *kv_len = a.kv_override >= 0 ? nullptr : a.kv_len;
-  PD_REQUIRE(a.H < 65536 && a.A < 65536, PD_EINVAL, "%d heads, %d rows per request", a.H, a.A);
-  const uint32_t ha = (uint32_t)a.H | (uint32_t)a.A << 16;
+  PD_REQUIRE(a.A < 65536, PD_EINVAL, "%d rows per request", a.A);        // (a step has at most 1024, a context pass too)
+  const uint32_t hda = (uint32_t)a.hd | (uint32_t)a.A << 16;
   const bool vec = a.hd % 4 == 0;       // rows of q, keys and values then start at multiples of 16 (half: 8) bytes
 #define PD_ATTN_F32(NHB, NW)                                                                                  \
   do {                                                                                                        \
     auto kernel = vec ? k_attn_f32<KT, NHB, NW, true> : k_attn_f32<KT, NHB, NW, false>;                       \
-    hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), 0, s, a.qkv, a.kc, a.vc, a.rt.qinfo, kv_len, a.hd, a.kv_cap, ha,  \
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), 0, s, a.qkv, a.kc, a.vc, a.rt.qinfo, kv_len, hda, a.kv_cap, a.H,  \
                        a.req0, a);                                                                            \
   } while (0)
   // waves per block: what the registers of a wave leave room for

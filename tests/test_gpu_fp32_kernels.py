@@ -6,9 +6,10 @@ with bf16 weights and the half cache (tests/parity_util.py)."""
 
 import numpy as np
 import pytest
+import torch
 
 import pd_inputs as pi
-from pd_inputs.configs import WorkloadConfig, DTYPE_BF16, DTYPE_F32, FFN_SWIGLU, NORM_RMSNORM, POS_ROPE
+from pd_inputs.configs import WorkloadConfig, DTYPE_BF16, DTYPE_F32, FFN_GELU, FFN_SWIGLU, NORM_RMSNORM, POS_ROPE
 from parity_util import oracle_run, make_decoder, compare_teacher_forced
 
 pytestmark = pytest.mark.gpu
@@ -81,3 +82,51 @@ def test_scores_far_apart(heads, hd, ctx, scale):
     dec = make_decoder(cfg, w)
     compare_teacher_forced(cfg, w, tokens, dec, oracle_run(cfg, w, tokens), log=lambda m: print(m, flush=True))
     dec.close()
+
+
+def test_more_heads_than_16_bits_hold(monkeypatch):
+    """65600 heads of 2 values (bf16 weights, fp32 kernels).  Queries and keys are 0, so every key has the same weight; values
+    and output projection use one value of one head beyond 2^16, and what it adds to the rows is known: v = u[5] of the
+    normalised row, x[7] += the mean of v over the keys so far."""
+    from paper_2506_23431_amd import binding
+    H, d, V = 65600, 131200, 64
+    if torch.cuda.mem_get_info()[0] < 160e9:
+        torch.cuda.empty_cache()
+        if torch.cuda.mem_get_info()[0] < 160e9:
+            pytest.skip("needs 150 GB of device memory")
+    shape = WorkloadConfig(name="heads", seed=1, dtype=DTYPE_BF16, n_layer=1, d_model=d, n_head=H, head_dim=2, d_ff=16, vocab=V,
+                           ffn_kind=FFN_GELU, norm_kind=NORM_RMSNORM, ctx_len=3, n_sub=1, sub_tokens=2)
+    bf = dict(dtype=torch.bfloat16, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(3)
+    emb, head = torch.randn((V, d), generator=g, device="cuda").bfloat16(), torch.randn((V, d), generator=g, device="cuda").mul_(0.01).bfloat16()
+    channel = 2 * (H - 3) + 1
+    mats = {"wqkv": torch.zeros((3 * d, d), **bf), "wo": torch.zeros((d, d), **bf), "w1": torch.zeros((16, d), **bf),
+            "w2": torch.zeros((d, 16), **bf)}
+    mats["wqkv"][2 * d + channel, 5] = 1.0
+    mats["wo"][7, channel] = 300.0
+    ones, pos = torch.ones(d, device="cuda"), torch.zeros((16, d), **bf)
+
+    def upload(torch_, device, shape_, weights):
+        w = binding.PdWeights()
+        w.tok_emb, w.pos_emb, w.lm_head, w.final_norm_g = emb.data_ptr(), pos.data_ptr(), head.data_ptr(), ones.data_ptr()
+        arrays = []
+        for name, t in {**mats, "norm1_g": ones, "norm2_g": ones}.items():
+            arrays.append((binding.C.c_void_p * 1)(t.data_ptr()))
+            setattr(w, name, binding.C.cast(arrays[-1], binding.C.POINTER(binding.C.c_void_p)))
+        return w, [], arrays
+
+    monkeypatch.setattr(binding, "_upload_weights", upload)
+    dec = binding.PipelinedDecoder(shape, {}, max_batch=1, max_ctx=3, max_sub=1, max_sub_tokens=2, max_pos=16)
+    dec.prefill_context(np.array([[9, 21, 40]], dtype=np.int32), 1, 1, 2, 2)
+    logits = dec.decode_step(want_logits=True)[1][0, 0].double()
+    dec.close()
+    mats.clear()
+    torch.cuda.empty_cache()
+    x = emb[[9, 21, 40, 0]].double()                       # the context and <bos>
+    u = x * torch.rsqrt(x.square().mean(1, keepdim=True) + shape.norm_eps)
+    y = x[3].clone()
+    y[7] += 300.0 * u[:, 5].mean()
+    want = head.double() @ (y * torch.rsqrt(y.square().mean() + shape.norm_eps))
+    without = head.double() @ (x[3] * torch.rsqrt(x[3].square().mean() + shape.norm_eps))
+    assert float((want - without).abs().max()) > 0.1       # (the head's share is visible)
+    assert float((logits - want).abs().max()) < 2e-2
