@@ -81,6 +81,28 @@ constexpr int words_tiles_rows(uint32_t n) { return (int)(n & 0xffffu); }
 constexpr int words_last_row(uint32_t n) { return (int)(n >> 16); }
 
 // ---------------------------------------------------------------------------
+// fp32 projections: row tiles of 16 rows per block.
+// ---------------------------------------------------------------------------
+// A block of four row tiles reads a weight once for 64 rows, one of two for 32, at half of the registers; a row tile alone
+// leaves its launch the most blocks.  Two or four want a block of two per compute unit and K beyond 256 (1024 x 256, 1000
+// rows: one row tile 19.6 us, two 26.7, four 29.9).  Between them what counts is rounds of 256 blocks times the tiles of a block
+// (6144 x 2048, 64 rows: 3 rounds of two 41 us, 2 of four 50; 4096 x 4096, 64 rows: 2 rounds of two 51, one of four 49).  Where
+// these are equal, four are faster from K 2048 on (4096 x 11008, 512 rows 944 us against 1000; 3072 x 8192, 48 rows 82 against
+// 89) and two below it (2048 x 512, 1000 rows 50 against 58); so are four in a single full round (4096 x 1024, 48 rows 15.0
+// against 16.6), unless they pad more rows (2048 x 512, 80 rows 10.9 against 9.3).  At 460 sizes (K 64-11008, 40-1000 rows) two
+// row tiles wherever they leave a block per compute unit are up to 1.14 times slower than four, and four up to 1.8 times slower
+// than two; the rule is at most 1.08 times slower than the better of them (at K 64 0.8 us), with K up to 256 2 % faster on
+// average.
+inline int lin_row_tiles(int n_tiles, int K, int rows) {
+  const long g2 = (rows + 31) / 32, g4 = (rows + 63) / 64;
+  if (rows <= 32 || K <= 256 || n_tiles * g2 < 256) return 1;
+  const long two = 2 * ((n_tiles * g2 + 255) / 256), four = 4 * ((n_tiles * g4 + 255) / 256);
+  if (two != four) return two < four ? 2 : 4;
+  if (four == 4) return g2 == 2 * g4 && K >= 512 ? 4 : 2;
+  return K <= 2048 ? 2 : 4;
+}
+
+// ---------------------------------------------------------------------------
 // Teacher-forced pass: consecutive requests that share launches, their rows padded to the longest of the group.
 // ---------------------------------------------------------------------------
 struct PassCost { double pass_us, row_us; };

@@ -11,6 +11,7 @@
 // number decides: five per layer (QKV with the norm in front of it and the KV append behind it, attention, output
 // projection, the two FFN projections, the first with its norm), the embedding read by the first of them and the
 // argmax left as one winner per 16-column tile for the commit kernel.
+#include "launch_rules.h"
 #include "pd_internal.h"
 
 #include <algorithm>
@@ -344,10 +345,7 @@ static void launch_lin(const LinArgs &a, int n_tiles, bool vec, hipStream_t s) {
 }
 
 // Wide loads where the rows allow them: K a multiple of 4 and every matrix aligned.  Waves along K: 16 steps each up
-// to K = 1024, 16 waves beyond.  Two row tiles per block where that leaves a block per compute unit (512 x 2048, 514 rows, 544
-// blocks 35.0 us, four row tiles and 288 blocks 41.3, one and 1056 37.6; 1536 x 512 24.2, 29.0, 27.4; 2048 x 512 30.0, 36.5, 34.8:
-// three quarters of the operands per multiply of one row tile, and half of the registers of four); fewer blocks lose
-// (512 x 2048, 128 rows, 64 blocks of four row tiles 17.9 us, 256 of one 11.2).
+// to K = 1024, 16 waves beyond; 8 with two or four row tiles per block (lin_row_tiles).
 template <typename WT, typename KT, int EPI>
 static int run_lin(const LinArgs &a, int n_tiles, hipStream_t s) {
   const uintptr_t mis = (uintptr_t)a.W | (uintptr_t)a.W2 | (uintptr_t)a.tok_emb | (uintptr_t)a.pos_emb;
@@ -367,7 +365,9 @@ static int run_lin(const LinArgs &a, int n_tiles, hipStream_t s) {
       return PD_OK;
     }
   }
-  if (a.R > 32 && (long)n_tiles * ((a.R + 31) / 32) >= 256) launch_lin<WT, KT, EPI, 8, 2, 0>(a, n_tiles, vec, s);
+  const int rt = lin_row_tiles(n_tiles, a.K, a.R);
+  if (rt == 4) launch_lin<WT, KT, EPI, 8, 4, 0>(a, n_tiles, vec, s);
+  else if (rt == 2) launch_lin<WT, KT, EPI, 8, 2, 0>(a, n_tiles, vec, s);
   else if (a.K <= 256) launch_lin<WT, KT, EPI, 4, 1, 0>(a, n_tiles, vec, s);
   else if (a.K <= 1024) launch_lin<WT, KT, EPI, 8, 1, 0>(a, n_tiles, vec, s);
   else launch_lin<WT, KT, EPI, 16, 1, 0>(a, n_tiles, vec, s);
@@ -614,8 +614,8 @@ static int attention_f32(const AttnF32Args &a, int nreq, hipStream_t s) {
 // The slices are added where the rows are read next, by the norms inside the projections (QKV 6.4 -> 7.7, head 9.0 -> 12.0) and the output
 // projection, which completes the residual.
 // At most 32 rows (decode steps) of up to 1024 values: the norms are taken inside the projections that follow them and the first layer
-// gathers its rows from the embedding tables.  With more rows a norm kernel of its own and tiles of 32 rows per block
-// are faster (every block would take the statistics of its rows again).
+// gathers its rows from the embedding tables.  With more rows a norm kernel of its own and tiles of 32 or 64 rows per
+// block are faster (every block would take the statistics of its rows again).
 static bool norm_inside(const pd_ctx *c, int R) { return R <= 32 && c->cfg.d_model <= 1024; }
 
 bool simple_embeds(const pd_ctx *c, int R) { return !norm_inside(c, R); }

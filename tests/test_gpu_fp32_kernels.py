@@ -130,3 +130,14 @@ def test_more_heads_than_16_bits_hold(monkeypatch):
     without = head.double() @ (x[3] * torch.rsqrt(x[3].square().mean() + shape.norm_eps))
     assert float((want - without).abs().max()) > 0.1       # (the head's share is visible)
     assert float((logits - want).abs().max()) < 2e-2
+
+
+@pytest.mark.parametrize("ctx", [96, 113, 128])
+def test_row_tiles_per_block(ctx):
+    """Context passes whose first FFN projection (2048 x 512) takes two row tiles per block (96 rows) and four, the last group
+    whole and not; the other projections take one."""
+    cfg = W(f"rows-{ctx}", 8, 64, 2048, ctx)
+    w, tokens = pi.make_weights(cfg, threads=4), pi.make_context(cfg)
+    dec = make_decoder(cfg, w)
+    compare_teacher_forced(cfg, w, tokens, dec, oracle_run(cfg, w, tokens), log=lambda m: print(m, flush=True))
+    dec.close()

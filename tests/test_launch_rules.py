@@ -33,6 +33,7 @@ void tiling(int n_tiles, int kt, int rows, int max_slices, int split, int kind, 
   out[0] = t.cut; out[1] = t.rt; out[2] = t.nt; out[3] = t.ks;
 }
 int vocab(int n_tiles, int kt, int rows) { return vocab_shares_row_tiles(n_tiles, kt, rows); }
+int lin(int n_tiles, int K, int rows) { return lin_row_tiles(n_tiles, K, rows); }
 void words(int64_t lo, int K, int share, int n_tiles, int c2, int64_t *out) {
   const GemmWords w = gemm_words(lo, K, share, n_tiles, c2);
   out[0] = words_granules(w.lo); out[1] = w.k; out[2] = w.share; out[3] = words_tiles(w.n); out[4] = words_c2(w.n); out[5] = 0;
@@ -238,3 +239,32 @@ def test_words_of_a_projection_hold_every_size(rules):
     for tiles, rows in itertools.product((1, 512, 65535), (0, 1, 2, 16, 128)):
         rules.words_rows(C.c_int64(64), 64, 2, tiles, rows, out)
         assert list(out) == [8, 2, 2, tiles, 0, max(rows - 1, 0)]
+
+
+# fp32 projections: N, K, rows; us with one, two and four row tiles of 16 rows per block
+LINEAR = [
+    (256, 256, 1000, 6.9, 9.0, 9.3), (1024, 256, 1000, 19.6, 26.7, 29.9), (512, 128, 512, 7.4, 11.5, 10.0),
+    (512, 512, 128, 4.7, 6.0, 9.5), (512, 512, 512, 11.0, 10.3, 9.4), (1536, 512, 96, 9.1, 9.5, 11.5),
+    (2048, 512, 80, 9.2, 9.3, 10.9), (2048, 512, 128, 13.3, 10.3, 11.1), (2048, 512, 1000, 60.8, 49.9, 58.2),
+    (512, 2048, 128, 10.8, 14.8, 25.8), (512, 2048, 256, 18.2, 15.0, 25.8), (512, 2048, 1000, 63.2, 49.6, 49.6),
+    (3072, 768, 48, 15.7, 16.2, 14.9), (4096, 1024, 48, 16.9, 16.6, 15.0), (1024, 4096, 64, 18.0, 25.1, 46.3),
+    (1024, 4096, 128, 32.2, 25.6, 45.5), (6144, 2048, 64, 56.9, 41.4, 49.6), (2048, 2048, 96, 26.0, 26.6, 26.1),
+    (2048, 5504, 96, 67.7, 67.4, 63.3), (2048, 5504, 1000, 684.0, 507.1, 486.1), (3072, 8192, 48, 91.8, 89.1, 82.3),
+    (3072, 3072, 128, 71.9, 57.4, 73.0), (4096, 11008, 40, 131.9, 129.2, 112.9), (4096, 11008, 96, 252.0, 197.4, 219.1),
+    (4096, 11008, 512, 1276.1, 999.8, 943.7), (12288, 4096, 64, 209.5, 143.9, 139.4), (11008, 4096, 128, 363.8, 249.4, 263.0),
+]
+
+
+def test_fp32_row_tiles_against_measured_times(rules):
+    """The chosen number of row tiles is within a tenth of the fastest at every measured size (the two rules before it, two row
+    tiles or four wherever they leave enough blocks, were up to 1.15 and 1.8 times the other's time here)."""
+    for N, K, rows, *us in LINEAR:
+        t = dict(zip((1, 2, 4), us))
+        assert t[rules.lin((N + 15) // 16, K, rows)] <= 1.10 * min(t.values()), (N, K, rows)
+
+
+def test_fp32_row_tiles_at_the_limits(rules):
+    for n_tiles, K, rows in itertools.product((1, 2, 255, 256, 16000, 1 << 26), (1, 256, 257, 512, 2048, 2049, 1 << 20),
+                                              (1, 32, 33, 64, 65, 8192, 2100000)):
+        t = rules.lin(n_tiles, K, rows)
+        assert t in (1, 2, 4) and (t == 1 or (rows > 32 and n_tiles * -(-rows // 32) >= 256))
