@@ -103,6 +103,24 @@ inline int lin_row_tiles(int n_tiles, int K, int rows) {
 }
 
 // ---------------------------------------------------------------------------
+// fp32 steps of at most 32 rows: second FFN projection cut along K over 4 blocks.
+// ---------------------------------------------------------------------------
+// Uncut, a block per 16 columns draws its weights and rows through one compute unit; cut, whoever reads the rows next (QKV
+// projection or head, a block per 16 columns and row tile, all of which normalise the rows) adds four slices.  Saved, in us: 0.9
+// at d_ff 1024, where a wave of the uncut launch has two batches of requests, beyond 1.5 + 1.65 per 1024 (d_ff 2048 4.3,
+// 8192 15).  Paid: 0.3, 1.0 and 2.4 for every round of 256 reading blocks at widths up to 256, 512 and 1024.  The next layer
+// is one round or two; a head of 50000 words is 13 or 25 and costs more than any d_ff here saves at width 512 and beyond (one
+// layer, us per step, uncut / cut: width 512, d_ff 2048, 12 rows, 500 words 50.3 / 47.9, 50000 words 89.7 / 98.7; width 1024,
+// 32 rows, d_ff 1024, 50000 words 223 / 280; width 256, 8 rows, d_ff 4096, 50000 words 70.7 / 67.2).  At 1080 sizes (width 64-1024,
+// d_ff 1024-8192, 1-32 rows, 500-50000 words) the choice costs 0.04 us more than the better one on average, 2.1 at most.
+inline bool ffn2_in_slices(int d_model, int d_ff, int rows, int reader_tiles) {
+  if (d_ff < 1024 || rows > 32 || d_model > 1024) return false;
+  const double saved = d_ff > 1024 ? 1.5 + 1.65 * d_ff / 1024 : 0.9;
+  const int rounds = (int)(((long)reader_tiles * (rows > 16 ? 2 : 1) + 255) / 256);
+  return saved > rounds * (d_model <= 256 ? 0.3 : d_model <= 512 ? 1.0 : 2.4);
+}
+
+// ---------------------------------------------------------------------------
 // Teacher-forced pass: consecutive requests that share launches, their rows padded to the longest of the group.
 // ---------------------------------------------------------------------------
 struct PassCost { double pass_us, row_us; };

@@ -609,13 +609,13 @@ static int attention_f32(const AttnF32Args &a, int nreq, hipStream_t s) {
 // ---------------------------------------------------------------------------
 // one transformer layer / the head, as sequences of launches
 // ---------------------------------------------------------------------------
-// The second FFN projection of such a step is cut along K over SLICES blocks from d_ff 1024 on: a block per 16 columns alone
-// draws its weights and rows through one compute unit (width 512, d_ff 2048, 12 rows: 32 blocks 10.4 us, 128 blocks 4.4).
-// The slices are added where the rows are read next, by the norms inside the projections (QKV 6.4 -> 7.7, head 9.0 -> 12.0) and the output
-// projection, which completes the residual.
 // At most 32 rows (decode steps) of up to 1024 values: the norms are taken inside the projections that follow them and the first layer
 // gathers its rows from the embedding tables.  With more rows a norm kernel of its own and tiles of 32 or 64 rows per
 // block are faster (every block would take the statistics of its rows again).
+// The second FFN projection of such a step is cut along K over SLICES blocks where that saves more than it costs the readers
+// (ffn2_in_slices; width 512, d_ff 2048, 12 rows: 32 blocks 10.4 us, 128 blocks 4.4).  The slices are added where the rows are
+// read next, by the norms inside the projections (QKV 6.4 -> 7.7, head of 8192 words 9.0 -> 12.0) and the output projection,
+// which completes the residual.
 static bool norm_inside(const pd_ctx *c, int R) { return R <= 32 && c->cfg.d_model <= 1024; }
 
 bool simple_embeds(const pd_ctx *c, int R) { return !norm_inside(c, R); }
@@ -686,7 +686,7 @@ int simple_layer(pd_ctx *c, int l, int R, int A, int nreq, int req0, int kv_over
                        : linear<LIN_SWIGLU>(c, f, lw.w1, lw.w_up, R, ff, d, s);
   if (rc) return rc;
   a.x = (const float *)c->hb;
-  if (norm_inside(c, R) && ff >= 1024) {
+  if (norm_inside(c, R) && ffn2_in_slices(d, ff, R, l + 1 < g.n_layer ? (3 * d + 15) / 16 : c->vocab_pad / 16)) {
     a.out = c->ypart;
     c->pend_parts = SLICES;
     return linear<LIN_SLICE>(c, a, lw.w2, nullptr, R, d, ff, s);

@@ -1,7 +1,8 @@
-"""Second FFN projection of the fp32 kernels cut along K over blocks (d_ff from 1024 on, at most 32 rows): inner widths on both
-sides of the rule and of the steps of a slice (16 values) and of a wave, widths that are no multiple of 4 (scalar loads), one
-layer (only the head adds the slices) and several, 1 to 33 rows (33: uncut), gated and not, bf16 weights that only these kernels
-take.  Logits against the CPU oracle: 1e-4 (fp32), 2e-2 (bf16)."""
+"""Second FFN projection of the fp32 kernels cut along K over blocks (d_ff from 1024 on, at most 32 rows, where that saves more
+than the readers of the slices pay): inner widths on both sides of the rule and of the steps of a slice (16 values) and of a
+wave, widths that are no multiple of 4 (scalar loads), one layer (only the head adds the slices) and several, 1 to 33 rows (33:
+uncut), heads of so many words that the last layer alone is uncut, gated and not, bf16 weights that only these kernels take.
+Logits against the CPU oracle: 1e-4 (fp32), 2e-2 (bf16)."""
 
 import pytest
 
@@ -26,6 +27,9 @@ CASES = [
     W("gated-rotary", 1072, ffn_kind=FFN_SWIGLU, norm_kind=NORM_RMSNORM, pos_kind=POS_ROPE),
     W("wide", 1200, d_model=1024, n_head=16, head_dim=64, n_layer=2),
     W("bf16-weights", 1040, dtype=DTYPE_BF16, d_model=48, n_head=2, head_dim=24),
+    # uncut before a head of many words, cut in front of it; cut before the head too; uncut at 1024 from width 512 on
+    W("many-words", 1100, d_model=512, n_head=8, head_dim=64, vocab=16640), W("fewer-words", 2048, d_model=512, n_head=8, head_dim=64, vocab=8001),
+    W("wide-1024", 1024, d_model=768, n_head=12, head_dim=64, n_layer=2),
 ]
 
 

@@ -34,6 +34,7 @@ void tiling(int n_tiles, int kt, int rows, int max_slices, int split, int kind, 
 }
 int vocab(int n_tiles, int kt, int rows) { return vocab_shares_row_tiles(n_tiles, kt, rows); }
 int lin(int n_tiles, int K, int rows) { return lin_row_tiles(n_tiles, K, rows); }
+int slices(int d, int ff, int rows, int tiles) { return ffn2_in_slices(d, ff, rows, tiles); }
 void words(int64_t lo, int K, int share, int n_tiles, int c2, int64_t *out) {
   const GemmWords w = gemm_words(lo, K, share, n_tiles, c2);
   out[0] = words_granules(w.lo); out[1] = w.k; out[2] = w.share; out[3] = words_tiles(w.n); out[4] = words_c2(w.n); out[5] = 0;
@@ -268,3 +269,26 @@ def test_fp32_row_tiles_at_the_limits(rules):
                                               (1, 32, 33, 64, 65, 8192, 2100000)):
         t = rules.lin(n_tiles, K, rows)
         assert t in (1, 2, 4) and (t == 1 or (rows > 32 and n_tiles * -(-rows // 32) >= 256))
+
+
+# fp32 steps: width, d_ff, rows, words of the head that reads the rows next (0: the next layer's QKV projection); us per step
+# with the second FFN projection in slices minus us without
+FFN2 = [
+    (64, 1024, 16, 500, 0.0), (64, 1024, 32, 50000, 6.1), (64, 2048, 8, 500, -3.5), (64, 2048, 17, 50000, 2.0),
+    (64, 4096, 16, 50000, -5.0), (64, 8192, 32, 0, -17.3), (128, 1536, 16, 0, -3.7), (128, 1536, 32, 50000, 2.5),
+    (256, 1024, 17, 50000, 8.2), (256, 2048, 32, 20000, -1.1), (256, 2048, 32, 50000, 5.6), (256, 4096, 8, 50000, -2.4),
+    (512, 1024, 1, 50000, 12.1), (512, 1024, 8, 0, 0.0), (512, 2048, 16, 8000, -3.1), (512, 2048, 16, 0, -3.7),
+    (512, 2048, 8, 50000, 8.0), (512, 4096, 32, 8000, -5.8), (512, 8192, 17, 50000, 5.4), (512, 8192, 16, 20000, -13.0),
+    (768, 1024, 16, 0, 0.8), (768, 1024, 17, 0, 4.2), (768, 2048, 8, 0, -1.9), (768, 3072, 32, 50000, 43.6),
+    (768, 4096, 16, 8000, -5.2), (768, 8192, 17, 20000, 5.8), (768, 8192, 32, 0, -8.2), (1024, 1024, 32, 0, 4.9),
+    (1024, 2048, 32, 0, 2.0), (1024, 2048, 1, 0, -2.6), (1024, 3072, 32, 0, 2.1), (1024, 4096, 16, 500, -7.3),
+    (1024, 4096, 32, 50000, 49.1), (1024, 8192, 16, 20000, -5.0), (1024, 8192, 32, 500, -9.7),
+]
+
+
+def test_fp32_slices_against_measured_times(rules):
+    for d, ff, rows, words, us in FFN2:
+        cut = rules.slices(d, ff, rows, (words + 63) // 64 * 4 if words else (3 * d + 15) // 16)
+        assert us <= 2.2 if cut else us >= -1.7, (d, ff, rows, words)
+    assert not rules.slices(512, 1023, 8, 96) and not rules.slices(512, 1 << 20, 33, 96) and not rules.slices(1025, 1 << 20, 8, 96)
+    assert rules.slices(1024, 1 << 30, 32, 1 << 20) and not rules.slices(64, 1024, 32, 1 << 27)
