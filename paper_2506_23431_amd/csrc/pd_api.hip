@@ -745,7 +745,7 @@ extern "C" int pd_decode_step(pd_ctx *c, const int32_t *force_tokens, int32_t *o
     memcpy(c->h_pinned, force_tokens, bs * sizeof(int32_t));
   }
   // Tokens, forced and appended, pass through mapped host memory that the step's last launch reads and writes itself; a
-  // replayed step and a context without such memory copy them.
+  // replayed step copies them, as would a context without such memory (pd_generate_static's, which takes no single steps).
   int32_t *h_tok = c->h_pinned + bs, *h_done = c->h_pinned + 2 * bs;
   const bool replay = replays(c, out_logits), mapped = c->stage_pinned && !replay, outputs = out_tokens || out_all_done;
   if (force_tokens && !mapped)
