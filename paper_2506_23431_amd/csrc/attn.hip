@@ -44,9 +44,9 @@ struct AttnArgs {
   //    time half of the matrix.  tau - 2 = coordinate - subsequence tag on both sides.
   const float *bias; const uint16_t *coord;
   int bias_len, bias_off, coord_stride, coord_req_stride, coord_off, pos0;
-  // QP kernels: the projection in front; stats != NULL: it finishes a norm without bias, as in the projection kernels
+  // QP kernels: the projection in front; stats != NULL: it finishes a norm without mean and bias
   const bf16_t *W, *xn; uint32_t xn_lo;
-  const float2 *stats; const float *c1; int norm_kind; float norm_eps;
+  const float2 *stats; float norm_eps;
 };
 constexpr int BIAS_MAX = 264;   // entries of one head's bias table that the kernel keeps in LDS
 
@@ -90,7 +90,7 @@ void k_attn_mfma(const f16_t *hot_q, const int4 *hot_qinfo, const f16_t *hot_kc,
   static_assert(!QP || (SPLIT && !PAIR && !BIAS && VS == 2 && NW == 8), "projecting launches: halves, 8 waves, low parts");
   __shared__ floatx4 sm_raw[NW * (T > NHB ? T : NHB)][64];   // partial tiles of the projection, later the waves' outputs
   floatx4 (*sm_o)[NHB][64] = (floatx4 (*)[NHB][64])sm_raw;
-  __shared__ float2 sm_stat[QP ? NW : 1][16];
+  __shared__ float sm_stat[QP ? NW : 1][16];
   __shared__ uint4 sm_q[(SPLIT ? 2 : 1) * NC][64];
   const int H = hot_ha & 0xffff, A = hot_ha >> 16, nqg = (A + 15) >> 4, d = H * HD;
   const int nsplit = hot_nb >> 20, nblk_static = hot_nb & 0xfffff;
@@ -209,15 +209,14 @@ void k_attn_mfma(const f16_t *hot_q, const int4 *hot_qinfo, const f16_t *hot_kc,
   if constexpr (QP) {
     qi = a.rt.qinfo[r];
     n_keys = a.kv_override >= 0 ? a.kv_override : a.kv_len[req];
-    // the sums of the norm: wave w, lane (n, g) takes the tile pairs g + 4 w, + 4 NW, ... of its row (fixed order)
+    // the sums of squares: wave w, lane (n, g) takes the tile pairs g + 4 w, + 4 NW, ... of its row (fixed order)
     const bool normed = hot_kv_len != nullptr;                          // the same for the whole launch
     if (normed) {
-      const float4 *sp = (const float4 *)hot_kv_len + (size_t)r * KT;
-      float s1 = 0.f, s2 = 0.f;
-      for (int p = g + 4 * wave; p < KT; p += 4 * NW) { const float4 v = sp[p]; s1 += v.x + v.z; s2 += v.y + v.w; }
-      s1 = fold32(fold16(s1, Add()), Add());
-      s2 = fold32(fold16(s2, Add()), Add());
-      if (lane < 16) sm_stat[wave][lane] = make_float2(s1, s2);
+      const float4 *sp = (const float4 *)hot_kv_len + (size_t)r * KT;   // (sum, sum of squares) of two tiles
+      float sq = 0.f;
+      for (int p = g + 4 * wave; p < KT; p += 4 * NW) { const float4 v = sp[p]; sq += v.y + v.w; }
+      sq = fold32(fold16(sq, Add()), Add());
+      if (lane < 16) sm_stat[wave][lane] = sq;
     }
     for (int kt = wave; kt < KT; kt += 2 * NW) {
       if (kt >= 2 * NW) {
@@ -239,13 +238,10 @@ void k_attn_mfma(const f16_t *hot_q, const int4 *hot_qinfo, const f16_t *hot_kc,
 #pragma unroll
         for (int e = 0; e < 4; ++e) y[e] += rotate16<8>(y[e]);
       if (normed) {
-        float2 tot = sm_stat[0][n];
+        float tot = sm_stat[0][n];
 #pragma unroll
-        for (int w = 1; w < NW; ++w) { tot.x += sm_stat[w][n].x; tot.y += sm_stat[w][n].y; }
-        const float inv_d = 1.f / (float)d, mean = a.norm_kind == 0 ? tot.x * inv_d : 0.f;
-        const float rstd = rsqrtf(fmaxf(tot.y * inv_d - mean * mean, 0.f) + a.norm_eps);
-        const float4 c1 = *(const float4 *)(a.c1 + (h * T + wave) * 16 + 4 * g);
-        y = floatx4{rstd * (y[0] - mean * c1.x), rstd * (y[1] - mean * c1.y), rstd * (y[2] - mean * c1.z), rstd * (y[3] - mean * c1.w)};
+        for (int w = 1; w < NW; ++w) tot += sm_stat[w][n];
+        y *= rsqrtf(tot * (1.f / (float)d) + a.norm_eps);
       }
       // queries in operand order: y[e] is dim 16 wave + 4 g + e (lanes beyond the rows hold copies, finite as those are)
       const int dim0 = wave * 16 + 4 * g;
@@ -571,11 +567,11 @@ int mfma_attention(pd_ctx *c, const LayerPtrs &lw, int A, int nreq, int req0, in
         g.d_model > 1024 || g.norm_kind != 1)
       return 1;
     a.W = proj->W; a.xn = (const bf16_t *)c->xn; a.xn_lo = (uint32_t)((mfma_lo(c, c->xn, g.d_model) - a.xn) / 64);
-    if (proj->c1) { a.stats = c->nstats; a.c1 = proj->c1; a.norm_kind = g.norm_kind; a.norm_eps = g.norm_eps; }
+    if (proj->finish) { a.stats = c->nstats; a.norm_eps = g.norm_eps; }
     if (g.head_dim == 64) launch_attn_proj<64>(nreq, s, a);
     else launch_attn_proj<32>(nreq, s, a);
     PD_CHECK_HIP(hipGetLastError());
-    if (proj->c1) c->norm_fused = false;
+    if (proj->finish) c->norm_fused = false;
     return PD_OK;
   }
   dim3 grid(a.nsplit, g.n_head, nreq * a.nqg);

@@ -162,7 +162,7 @@ int encdec_decoder_layer(pd_ctx *c, int l, int R, hipStream_t s, int A, int nreq
   memset(&cross, 0, sizeof(cross));
   cross.kc = lw.xkc; cross.vc = lw.xvc; cross.qinfo = c->qinfo_x; cross.L = c->Lx; cross.scale = 1.f;
   // (decode steps: the query projection inside the attention launch where the shape allows it)
-  const AttnProj xproj{lw.p_cq, finish ? lw.cx1 : nullptr};
+  const AttnProj xproj{lw.p_cq, finish};
   rc = kv_self < 0 ? mfma_attention(c, lw, A, nreq, req0, c->Lx, s, &cross, &xproj) : 1;
   if (rc < 0) return rc;
   if (rc == 1) {

@@ -172,9 +172,9 @@ struct AttnMode {
   const float *bias; const uint16_t *coord;
   int bias_len, bias_off, coord_stride, coord_req_stride, coord_off, pos0;
 };
-// What an attention launch needs to project its queries itself from the rows in c->xn.  c1: as in mfma_qkv, NULL or the
-// rows are gain * x and the (bias-free) norm is finished here.
-struct AttnProj { const bf16_t *W; const float *c1; };
+// What an attention launch needs to project its queries itself from the rows in c->xn.  finish: those are gain * x and the
+// norm, which has no mean and no bias, is finished here.
+struct AttnProj { const bf16_t *W; bool finish; };
 // proj != NULL: PD_OK when one launch did both, 1 when the shape is not one for that (nothing was launched)
 int mfma_attention(pd_ctx *c, const LayerPtrs &lw, int A, int nreq, int req0, int kv_override,
                    hipStream_t s, const AttnMode *mode = nullptr, const AttnProj *proj = nullptr);
