@@ -670,6 +670,7 @@ static GemmHot gemm_hot(const GemmArgs &a) {
 }
 template <int EPI, typename Kernel>
 static int launch_gemm_kernel(Kernel kernel, dim3 grid, int threads, GemmArgs a, hipStream_t s) {
+  PD_REQUIRE(a.K / 32 <= WORDS_K_TILES, PD_EINVAL, "%d inner values", a.K);
   PD_REQUIRE(!a.stats_in || (a.stats_tiles == a.K / 16 && (!a.c2 || a.c2 == a.c1 + (size_t)a.n_tiles * 16)), PD_EINVAL,
              "a norm is finished over the whole rows, with c2 behind c1");
   PD_REQUIRE(EPI != EPI_RESID_NORM || (a.R <= 128 && a.n_tiles < 65536), PD_EINVAL, "%d rows of %d values cannot prepare a norm",
@@ -698,11 +699,11 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(PD_GEMM_HOT_PARAMS, GemmAr
   static_assert(!PACK || (RT == 1 && !SPLIT), "packed activations: one row tile, one fragment");
   const int rz = ZROWS ? (int)blockIdx.z * RT : 0;          // first row tile of this block
   __shared__ floatx4 red[NW_K > 1 ? NW_K * NT * RT * 64 : 1];
-  const int wk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int wk = NW_K == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int nt0 = blockIdx.x * NT;
   const int m = lane & 15;
   constexpr bool OUT = EPI == EPI_RESID_NORM;
-  const int KT = hot_k, k_share = hot_share, n_tiles = OUT ? words_tiles_rows(hot_n) : words_tiles(hot_n);
+  const int KT = words_k_tiles(hot_k), k_share = words_k_tiles(hot_share), n_tiles = OUT ? words_tiles_rows(hot_n) : words_tiles(hot_n);
   // waves along K: NW_K in this block times gridDim.y blocks (EPI_RESID only)
   const int gk = blockIdx.y * NW_K + wk;
   const int kt0 = min(gk * k_share, KT), kt1 = min(kt0 + k_share, KT);
@@ -1047,7 +1048,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm_t(PD_GEMM_HOT_PARAMS, GemmArgs 
   __shared__ bf16x8 sm_x[2][NA][64];   // (vector types throughout: struct copies would keep xr in scratch memory)
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int m = lane & 15;
-  const int KT = hot_k, per_slice = hot_share, n_tiles = words_tiles(hot_n);
+  const int KT = words_k_tiles(hot_k), per_slice = words_k_tiles(hot_share), n_tiles = words_tiles(hot_n);
   const int kt0 = min((int)blockIdx.y * per_slice, KT), kt1 = min(kt0 + per_slice, KT);
   const int rt0 = blockIdx.z * RT, r0 = rt0 * 16;
   const int nt0 = (blockIdx.x * NW + w) * NT;
