@@ -127,8 +127,9 @@ int mfma_fold_norms(pd_ctx *c, hipStream_t s) {
 // ---------------------------------------------------------------------------
 // norm -> bf16 activations.  One block per row; rows without a token become zero.
 // The row is read once into registers (gain and bias are requested at the same
-// time), so the kernel costs one memory round trip plus one block reduction (sum and sum of squares
-// together: the variance is E[x^2] - mean^2, as in the projections that finish a norm).
+// time), so that without pending slices the kernel costs one memory round trip plus one block reduction (sum and sum of squares
+// together: the variance is E[x^2] - mean^2, as in the projections that finish a norm).  With slices every four
+// completed values are stored before the next are asked for, two round trips at widths up to 2048, four up to 4096.
 // ---------------------------------------------------------------------------
 // EMB: the row is not read from x but gathered from the embedding tables (first norm of a step:
 // x = E_tok[token] (+ E_pos[position]), zero for rows without a token) and written to x.
@@ -177,7 +178,7 @@ __global__ __launch_bounds__(256) void k_norm_bf16(const int32_t *flags, const v
       }
       float4 tg = in ? *(const float4 *)(g + c + 4 * h) : make_float4(0.f, 0.f, 0.f, 0.f);
       float4 tb = (in && kind == 0 && b) ? *(const float4 *)(b + c + 4 * h) : make_float4(0.f, 0.f, 0.f, 0.f);
-      // pending split-K slices of the last projection: requested together with everything else
+      // pending split-K slices of the last projection
       float4 y[NP > 0 ? NP : 1];
 #pragma unroll
       for (int pp = 0; pp < NP; ++pp)
@@ -366,7 +367,7 @@ int mfma_norm(pd_ctx *c, const float *gain, const float *bias, int R, hipStream_
 // lives for a few microseconds up to a few tens: every load must be in flight from the first cycle
 // on.  Per chunk of U k-tiles a wave requests everything first (the high- and low-part activation
 // fragments of the row tiles, then the weight fragments of its tiles) into registers of their own;
-// only then the multiplies run.  A share that is not a multiple of U ends with chunks of 4, 2 and
+// only then the multiplies run.  A share that is not a multiple of U ends with chunks of 4, 3, 2 and
 // 1 k-tiles, so that no load is ever conditional.
 // This file is compiled twice per epilogue (PD_GEMM_EPI = 0..6: kernels and launch code of that epilogue; with
 // PD_GEMM_ROWS those of more than 128 rows and of the vocabulary projection of 33-128) and once without (weight packing,
@@ -839,7 +840,7 @@ static int launch_gemm_small_nt(GemmArgs a, int ks, hipStream_t s) {
   dim3 grid(groups, ks);
   // a projection that completes the rows is not cut over blocks; with 6 k-tiles per wave (packed rows: also 8) it asks for
   // all of them at once instead of in two batches (K 3072, width 768: in two batches it cost more than the norm kernel it
-  // replaces).  Shares of 5 and 7 take two or three batches, 4 + 1 and 4 + 2 + 1 k-tiles: the last ones are short, and
+  // replaces).  Shares of 5 and 7 take two batches, 4 + 1 and 4 + 3 k-tiles: the last ones are short, and
   // whole steps at d_ff 2560 and 3584 are no slower than with the norm kernel (widths 512-1024, 8 and 12 rows).
   if constexpr (EPI == EPI_RESID_NORM && NT == 1) {
     constexpr int UL = SPLIT ? 6 : 8;

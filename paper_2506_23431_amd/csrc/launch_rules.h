@@ -53,7 +53,9 @@ inline AttnShape attn_shape(int head_dim, int units, int nblk, int cap, bool dec
 // Two blocks per unit, each with half of the dims of the values, where one block per unit leaves half of the chip idle (us
 // per launch, one block / two: 12 units of head size 64, 32-48 key blocks 6.6 / 6.1; 24 units, 22 blocks 6.0 / 5.4; 12 units, 16
 // blocks 4.7 / 4.4, 1-5 blocks with 4 waves 4.2 / 4.0; 128 units, 64 blocks from memory 16.5 / 14.2).  Beyond 128 units the second
-// blocks wait for the first.
+// blocks wait for the first.  In whole steps less of it is left: 2-128 units, 16-4000 keys, us gained per launch at head
+// sizes 96 and 128 0.22 and 0.25 on average (-0.8 to 2.5), at 32 and 64 0.14 and 0.00 with 12 layers (-0.6 to 0.6) and -0.13 and
+// -0.04 with 3, which is what runs of one side differ by.  attn_shape weighs 8 waves without halves against splits.
 inline bool attn_halves(const AttnShape &shape, int units, bool decode, bool pair) {
   return shape.splits == 1 && units <= 128 && decode && !pair;
 }

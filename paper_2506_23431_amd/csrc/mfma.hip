@@ -33,7 +33,7 @@ bool mfma_can_fuse_norm(pd_ctx *c, int R) {
 // per 16 output columns.  While a wave of its 16 holds at most 8 k-tiles (d_ff 4096) that costs less than the norm kernel
 // (768 / 3072, whole steps: 174.6 against 184.1 us; 1024 / 4096 273 against 289; 512 / 1376 with rotary positions 186
 // against 204; encoder-decoder 1024 / 4096 22.5 against 22.9 ms per example), also where the 5 or 7 k-tiles of a wave
-// take two or three batches of requests; beyond it does not (2048 / 8192, 16 k-tiles per wave: 82.6 against 81.1 ms for 64
+// take two batches of requests; beyond it does not (2048 / 8192, 16 k-tiles per wave: 82.6 against 81.1 ms for 64
 // steps) and happens only on request (value 2 of the option).  Width 1024 is as far as the rule has been set by whole
 // workloads, not where the gain ends: 4 layers of width 1280-2048 with d_ff 1024-3072 take 5-8 % less per step on request,
 // width 2048 with d_ff 4096 1-2 %.

@@ -270,7 +270,7 @@ static int finish_create(pd_ctx *c, size_t need, void *hip_stream, bool no_alloc
     // take the non-temporal hint (PD_OPT_STREAM_LOADS overrides).
     const pd_config &g = c->cfg;
     // (encoder-decoder form: a decoder layer also reads the two d x d projections around its attention over
-    // the encoder states, and that attention's keys and values)
+    // the encoder states, and that attention's keys and values; its own cache is counted by the same capacity)
     const double attn_mats = c->arch == 1 ? 6.0 : 4.0, caches = c->arch == 1 ? 2.0 : 1.0;
     const double wbytes = 2.0 * ((double)g.n_layer * (attn_mats * g.d_model * g.d_model +
                                                       (g.ffn_kind == 1 ? 3.0 : 2.0) * g.d_model * g.d_ff) +

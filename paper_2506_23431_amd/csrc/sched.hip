@@ -279,8 +279,8 @@ __global__ __launch_bounds__(1024) void k_turn(const float *part_val, const int3
   __shared__ int s_idx[16], s_cnt[16];
   __shared__ int s_tok[NGW ? TURN_ROWS : 1], s_pos[NGW ? TURN_ROWS : 1];
   const int b = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  // Everything the block needs is requested at once, before the first use: the schedule state of the request, and the
-  // winners of the vocabulary's groups of columns of every row, whether or not the row selects a token.
+  // Asked for ahead of their use: what the threads' subsequences hold, the request's state (four scalar reads, one after the
+  // other), then the winners of the vocabulary's groups of columns of every row, whether or not the row selects a token.
   const int i0 = threadIdx.x;           // subsequence of this thread in the first pass
   int r0 = -1, fin0 = 0, f0 = -1, nt0 = 0, fed0 = 0;
   if (i0 < S) {
