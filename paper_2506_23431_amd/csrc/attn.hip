@@ -93,7 +93,7 @@ void k_attn_mfma(const f16_t *hot_q, const int4 *hot_qinfo, const f16_t *hot_kc,
   floatx4 (*sm_o)[NHB][64] = (floatx4 (*)[NHB][64])sm_raw;
   __shared__ float sm_stat[QP ? NW : 1][16];
   __shared__ uint4 sm_q[(SPLIT ? 2 : 1) * NC][64];
-  const int H = hot_ha & 0xffff, A = hot_ha >> 16, nqg = (A + 15) >> 4, d = H * HD;
+  const int H = word_heads(hot_ha), A = word_rows(hot_ha), nqg = (A + 15) >> 4, d = H * HD;
   const int nsplit = hot_nb >> 20, nblk_static = hot_nb & 0xfffff;
   // (halves: heads, groups, halves of the dims; no splits)
   const int split = VS == 1 ? blockIdx.x : 0, h = VS == 1 ? blockIdx.y : blockIdx.x, z = VS == 1 ? blockIdx.z : blockIdx.y;
@@ -419,11 +419,11 @@ void k_attn_mfma(const f16_t *hot_q, const int4 *hot_qinfo, const f16_t *hot_kc,
 // flight at a time; the four running states are then combined through LDS.
 template <int HD>
 __global__ __launch_bounds__(256) void k_attn_merge(const float *part, const int32_t *flags, bf16_t *out, bf16_t *out_lo,
-                                                    uint32_t ha, uint32_t nsplit_nqg) {
+                                                    uint32_t ha, int nsplit) {
   constexpr int PSTR = HD + 2, U = 8;
   __shared__ float sm_M[4][64], sm_L[4][64];
   __shared__ floatx4 sm_O[4][64];
-  const int H = ha & 0xffff, A = ha >> 16, nsplit = nsplit_nqg & 0xfff, nqg = nsplit_nqg >> 12;
+  const int H = word_heads(ha), A = word_rows(ha), nqg = (A + 15) >> 4;
   int unit = blockIdx.x, i = blockIdx.y, z = unit / H, h = unit - z * H;
   int reqi = z, qg = 0;
   if (nqg > 1) { reqi = z / nqg; qg = z - reqi * nqg; }
@@ -484,7 +484,7 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float *part, const int
 template <int HD, bool SPLIT, bool PAIR, bool BIAS, bool STREAM, int NW, int VS = 1>
 static void launch_attn_nw(dim3 grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1, const AttnArgs &a) {
   const uint32_t q_lo = a.q_lo ? (uint32_t)((a.q_lo - a.q) / 64) : 0u, v = (uint32_t)((a.vc - a.kc) / 128);
-  const uint32_t ha = (uint32_t)a.H | (uint32_t)a.A << 16, nb = (uint32_t)a.nblk_static | (uint32_t)a.nsplit << 20;
+  const uint32_t ha = heads_rows(a.H, a.A), nb = (uint32_t)a.nblk_static | (uint32_t)a.nsplit << 20;
   const int32_t *kv_len = a.kv_override >= 0 ? nullptr : a.kv_len;
   auto kernel = k_attn_mfma<HD, SPLIT, PAIR, BIAS, STREAM, NW, VS>;
   if (e0 || e1)
@@ -511,7 +511,7 @@ static void launch_attn(dim3 grid, int nw, bool halves, hipStream_t s, hipEvent_
 // input tokens) take 0.93-1.07 times as long per step, 1.016 on average.
 template <int HD>
 static void launch_attn_proj(int nreq, hipStream_t s, const AttnArgs &a) {
-  const uint32_t v = (uint32_t)((a.vc - a.kc) / 128), ha = (uint32_t)a.H | (uint32_t)a.A << 16, nb = (uint32_t)a.nblk_static | 1u << 20;
+  const uint32_t v = (uint32_t)((a.vc - a.kc) / 128), ha = heads_rows(a.H, a.A), nb = (uint32_t)a.nblk_static | 1u << 20;
   auto kernel = a.A <= 8 ? k_attn_mfma<HD, true, false, false, false, 8, 2, true, true>
                          : k_attn_mfma<HD, true, false, false, false, 8, 2, true, false>;
   hipLaunchKernelGGL(kernel, dim3(a.H, nreq, 2), dim3(512), 0, s, (const f16_t *)a.xn, (const int4 *)a.W, a.kc,
@@ -562,7 +562,7 @@ int mfma_attention(pd_ctx *c, const LayerPtrs &lw, int A, int nreq, int req0, in
                                                          a.kc_lo != nullptr, c->stream_loads);
   const int nw = shape.waves;
   a.nsplit = shape.splits;
-  PD_REQUIRE(a.H < 65536 && A < 65536 && a.nblk_static < (1 << 20) && a.nsplit < (1 << 12) && a.vc > a.kc &&
+  PD_REQUIRE(a.H <= 256 && A < (1 << 24) && a.nblk_static < (1 << 20) && a.nsplit < (1 << 12) && a.vc > a.kc &&
                  (a.vc - a.kc) % 128 == 0,
              PD_EINVAL, "an attention launch over %d rows and %d key blocks is too large", A, a.nblk_static);
   const bool halves = attn_halves(shape, units, kv_override < 0 || mode, a.kc_lo != nullptr);
@@ -630,7 +630,7 @@ int mfma_attention(pd_ctx *c, const LayerPtrs &lw, int A, int nreq, int req0, in
     PD_ATTN_ONE(HDV, a);                                                                               \
     if (a.nsplit > 1)                                                                                  \
       hipLaunchKernelGGL(k_attn_merge<HDV>, dim3(units, HDV / 16), dim3(256), 0, s, a.part, a.rt.flags, a.out, a.out_lo, \
-                         (uint32_t)a.H | (uint32_t)A << 16, (uint32_t)a.nsplit | (uint32_t)a.nqg << 12);   \
+                         heads_rows(a.H, A), a.nsplit);                                                        \
   } while (0)
   switch (g.head_dim) {
     case 32: PD_ATTN(32); break;

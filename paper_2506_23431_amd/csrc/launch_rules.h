@@ -87,6 +87,12 @@ constexpr bool words_c2(uint32_t n) { return n >> 31; }
 constexpr int words_tiles_rows(uint32_t n) { return (int)(n & 0xffffu); }
 constexpr int words_last_row(uint32_t n) { return (int)(n >> 16); }
 
+// ... and an attention kernel: heads (widths end at 8192, heads start at 32) and rows of a request (fewer than its cache
+// slots, which end at 2^24) in one word.
+constexpr uint32_t heads_rows(int H, int A) { return (uint32_t)(H - 1) | (uint32_t)A << 8; }
+constexpr int word_heads(uint32_t w) { return (int)(w & 0xff) + 1; }
+constexpr int word_rows(uint32_t w) { return (int)(w >> 8); }
+
 // ---------------------------------------------------------------------------
 // fp32 projections: row tiles of 16 rows per block.
 // ---------------------------------------------------------------------------

@@ -39,6 +39,10 @@ void words(int64_t lo, int K, int share, int n_tiles, int c2, int64_t *out) {
   const GemmWords w = gemm_words(lo, K, share, n_tiles, c2);
   out[0] = words_granules(w.lo); out[1] = words_k_tiles(w.k); out[2] = words_k_tiles(w.share); out[3] = words_tiles(w.n); out[4] = words_c2(w.n); out[5] = 0;
 }
+int attn_word(int H, int A) {
+  const uint32_t w = heads_rows(H, A);
+  return word_heads(w) == H && word_rows(w) == A;
+}
 void words_rows(int64_t lo, int K, int share, int n_tiles, int rows, int64_t *out) {
   const GemmWords w = gemm_words_rows(lo, K, share, n_tiles, rows);
   out[0] = words_granules(w.lo); out[1] = words_k_tiles(w.k); out[2] = words_k_tiles(w.share); out[3] = words_tiles_rows(w.n); out[4] = 0;
@@ -240,6 +244,11 @@ def test_words_of_a_projection_hold_every_size(rules):
     for tiles, rows in itertools.product((1, 512, 65535), (0, 1, 2, 16, 128)):
         rules.words_rows(C.c_int64(64), 64, 2, tiles, rows, out)
         assert list(out) == [8, 2, 2, tiles, 0, max(rows - 1, 0)]
+
+
+def test_word_of_an_attention_launch_holds_every_size(rules):
+    for H, A in itertools.product((1, 2, 255, 256), (1, 65535, 65536, (1 << 24) - 1)):
+        assert rules.attn_word(H, A)
 
 
 # fp32 projections: N, K, rows; us with one, two and four row tiles of 16 rows per block
