@@ -584,7 +584,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, int nt, const f
   }
 }
 
-// One winner per row and block: W waves of the block hold one each.  (One per 16-column tile: the commit kernel, one block per
+// One winner per row and block: W waves of the block hold one each.  (One per 16-column tile: k_turn, one block per
 // request, read 25 KB per row at 50265 words.)  Row-major [row][block]: it reads a row's winners as one run.
 template <int RT, int W>
 __device__ __forceinline__ void store_winners(const GemmArgs &a, const Winner (&win)[RT], int w, int lane, int r0) {
@@ -1036,7 +1036,7 @@ int PD_GEMM_ENTRY(const GemmArgs &a, int rows, hipStream_t s) { return launch_ge
 // request already goes to the next k-tile's buffer.  So a wave never stands between a barrier and its first multiply
 // waiting for LDS (with the barrier in front of the k-tile's first LDS read the same launches took: QKV, 2048 rows,
 // width 4096, 327 us, now 310; QKV, 4096 rows, width 2048, 182 -> 173; second FFN projection there 204 -> 198).
-// At these sizes the multiplies run at 1.2-1.43 PFLOP/s (high and low parts counted), what a large library product
+// At these sizes the multiplies run at 1.1-1.4 PFLOP/s (high and low parts counted), what a large library product
 // reaches on this device: with operands of zeros the same launches are 20-30 % faster, so it is the power limit
 // that holds the rate, and 32x32x16 multiplies (half the operand reads) measured no better (239 against 226 us).
 // ---------------------------------------------------------------------------

@@ -155,6 +155,6 @@ int mfma_head(pd_ctx *c, int R, float *logits, hipStream_t s, int tf_A, int tf_c
   a.logits = logits; a.logits_A = tf_A; a.logits_cap = tf_A > 0 ? tf_cap : c->S; a.ld_logits = g.vocab;
   a.part_val = c->lm_part_val; a.part_idx = c->lm_part_idx;
   a.win_out = &c->lm_win;
-  // leaves one winner per block of columns; the commit kernel picks the winner of each row
+  // leaves one winner per block of columns; k_turn picks the winner of each row
   return mfma_gemm(EPI_LM, a, R, s);
 }

@@ -10,7 +10,7 @@
 // The models of this path are small, so a decode step is a chain of launches of a few microseconds each and their
 // number decides: five per layer (QKV with the norm in front of it and the KV append behind it, attention, output
 // projection, the two FFN projections, the first with its norm), the embedding read by the first of them and the
-// argmax left as one winner per 16-column tile for the commit kernel.
+// argmax left as one winner per 16-column tile for k_turn.
 #include "launch_rules.h"
 #include "pd_internal.h"
 
@@ -694,7 +694,7 @@ int simple_layer(pd_ctx *c, int l, int R, int A, int nreq, int req0, int kv_over
   return linear<LIN_RESID>(c, a, lw.w2, nullptr, R, d, ff, s);
 }
 
-// leaves one winner per 16-column tile; the commit kernel picks the winner of each row
+// leaves one winner per 16-column tile; k_turn picks the winner of each row
 int simple_head(pd_ctx *c, int R, float *logits, hipStream_t s) {
   const pd_config &g = c->cfg;
   LinArgs a;
