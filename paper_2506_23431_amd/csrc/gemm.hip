@@ -126,11 +126,11 @@ int mfma_fold_norms(pd_ctx *c, hipStream_t s) {
 
 // ---------------------------------------------------------------------------
 // norm -> bf16 activations.  One block per row; rows without a token become zero.
-// The row is read once into registers (gain and bias are requested at the same
-// time), so that without pending slices the kernel costs one memory round trip plus one block reduction (sum and sum of squares
-// together: the variance is E[x^2] - mean^2, as in the projections that finish a norm).  With slices every four
-// completed values are stored before the next are asked for, two round trips at widths up to 2048, four up to 4096.
-// ---------------------------------------------------------------------------
+// The row, its pending slices, gain and bias are read once into registers, every request in flight before anything is waited
+// for, so that the kernel costs one memory round trip plus one block reduction (sum and sum of squares together: the variance
+// is E[x^2] - mean^2, as in the projections that finish a norm).  The completed row is stored behind the last use.  With
+// requests under conditions and a store between the slices' halves it took four round trips: 72 rows of width 1024, four
+// slices 3.84 -> 3.32 us.
 // EMB: the row is not read from x but gathered from the embedding tables (first norm of a step:
 // x = E_tok[token] (+ E_pos[position]), zero for rows without a token) and written to x.
 template <int NG, int NP, bool EMB>     // 8-value granules per thread: d <= 2048 * NG; NP pending slices
@@ -142,57 +142,59 @@ __global__ __launch_bounds__(256) void k_norm_bf16(const int32_t *flags, const v
   const float *x = (const float *)src1, *ypart = (const float *)src2;            // rows and pending slices
   const size_t part_stride = (size_t)rows_pad * d;
   const int32_t *tok = (const int32_t *)src1, *pos = (const int32_t *)src2;      // EMB: token and position of a row
-  int r = blockIdx.x;
-  int fl = r < R ? flags[r] : 0;
-  const float *xr = x + (size_t)r * d;
-  float v[NG][8], gv[NG][8], bv[NG][8];
+  const int r = blockIdx.x;
+  int fl = 0;
+  if (EMB) fl = r < R ? flags[r] : 0;
+  // Every request goes out before anything is waited for, at clamped places and without a branch (a load under a condition
+  // is waited for where its branch ends: four round trips instead of one).
+  const float *bias = kind == 0 && b ? b : g;
+  floatx4 xv[NG][2], tg[NG][2], tb[NG][2], y[NG][2][NP > 0 ? NP : 1];
+  Frag et[EMB ? NG : 1], ep[EMB ? NG : 1];
   const bf16_t *te = nullptr, *pe = nullptr;
   if (EMB) {
     // (rows without a token hold an older one; the tables cover the padded rows)
     const int tk = tok[r], ps = pos[r];
-    bool has = fl & ROW_VALID;
+    const bool has = fl & ROW_VALID;
     te = tok_emb + (has ? (size_t)tk * d : 0);
-    pe = pos_emb ? pos_emb + (has ? (size_t)ps * d : 0) : nullptr;
+    pe = pos_emb ? pos_emb + (has ? (size_t)ps * d : 0) : te;
   }
+  const float *xr = EMB ? nullptr : x + (size_t)r * d, *yr = NP > 0 ? ypart + (size_t)r * d : nullptr;
 #pragma unroll
   for (int i = 0; i < NG; ++i) {
-    int c = (threadIdx.x + i * 256) * 8;
-    bool in = c < d;
-    Frag et, ep;
-    if (EMB) {
-      et.u = in ? *(const uint4 *)(te + c) : make_uint4(0, 0, 0, 0);
-      ep.u = (in && pe) ? *(const uint4 *)(pe + c) : make_uint4(0, 0, 0, 0);
+    const int c = min((int)(threadIdx.x + i * 256) * 8, d - 8);
+    if (EMB) { et[i].u = *(const uint4 *)(te + c); ep[i].u = *(const uint4 *)(pe + c); }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (!EMB) xv[i][h] = *(const floatx4 *)(xr + c + 4 * h);
+#pragma unroll
+      for (int pp = 0; pp < NP; ++pp) y[i][h][pp] = *(const floatx4 *)(yr + pp * part_stride + c + 4 * h);
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      float4 t;
-      if (EMB) {
-        bool has = fl & ROW_VALID;
-        t.x = has ? bf16_to_f32(et.h[4 * h]) + bf16_to_f32(ep.h[4 * h]) : 0.f;
-        t.y = has ? bf16_to_f32(et.h[4 * h + 1]) + bf16_to_f32(ep.h[4 * h + 1]) : 0.f;
-        t.z = has ? bf16_to_f32(et.h[4 * h + 2]) + bf16_to_f32(ep.h[4 * h + 2]) : 0.f;
-        t.w = has ? bf16_to_f32(et.h[4 * h + 3]) + bf16_to_f32(ep.h[4 * h + 3]) : 0.f;
-        if (in && r < R) *(float4 *)(xw + (size_t)r * d + c + 4 * h) = t;
-      } else {
-        t = in ? *(const float4 *)(xr + c + 4 * h) : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-      float4 tg = in ? *(const float4 *)(g + c + 4 * h) : make_float4(0.f, 0.f, 0.f, 0.f);
-      float4 tb = (in && kind == 0 && b) ? *(const float4 *)(b + c + 4 * h) : make_float4(0.f, 0.f, 0.f, 0.f);
-      // pending split-K slices of the last projection
-      float4 y[NP > 0 ? NP : 1];
-#pragma unroll
-      for (int pp = 0; pp < NP; ++pp)
-        y[pp] = in ? *(const float4 *)(ypart + pp * part_stride + (size_t)r * d + c + 4 * h)
-                   : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-      for (int pp = 0; pp < NP; ++pp) { t.x += y[pp].x; t.y += y[pp].y; t.z += y[pp].z; t.w += y[pp].w; }
-      if (NP > 0 && in && r < R) *(float4 *)(xw + (size_t)r * d + c + 4 * h) = t;
-      v[i][4 * h] = t.x; v[i][4 * h + 1] = t.y; v[i][4 * h + 2] = t.z; v[i][4 * h + 3] = t.w;
-      gv[i][4 * h] = tg.x; gv[i][4 * h + 1] = tg.y; gv[i][4 * h + 2] = tg.z; gv[i][4 * h + 3] = tg.w;
-      bv[i][4 * h] = tb.x; bv[i][4 * h + 1] = tb.y; bv[i][4 * h + 2] = tb.z; bv[i][4 * h + 3] = tb.w;
+      tg[i][h] = *(const floatx4 *)(g + c + 4 * h);
+      tb[i][h] = *(const floatx4 *)(bias + c + 4 * h);
     }
   }
-  bool valid = fl & ROW_VALID;
+  __builtin_amdgcn_sched_barrier(0);
+  if (!EMB) fl = r < R ? flags[r] : 0;
+  const bool valid = fl & ROW_VALID;
+  float v[NG][8];
+#pragma unroll
+  for (int i = 0; i < NG; ++i) {
+    const bool in = (int)(threadIdx.x + i * 256) * 8 < d;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (EMB)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          xv[i][h][e] = valid ? bf16_to_f32(et[i].h[4 * h + e]) + (pos_emb ? bf16_to_f32(ep[i].h[4 * h + e]) : 0.f) : 0.f;
+      // the pending split-K slices of the last projection
+#pragma unroll
+      for (int pp = 0; pp < NP; ++pp) xv[i][h] += y[i][h][pp];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[i][4 * h + e] = in ? xv[i][h][e] : 0.f;
+    }
+  }
   float s = 0.f, q = 0.f;
 #pragma unroll
   for (int i = 0; i < NG; ++i)
@@ -215,46 +217,82 @@ __global__ __launch_bounds__(256) void k_norm_bf16(const int32_t *flags, const v
     Frag hi, lo;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      float y = valid ? (v[i][e] - mean) * rstd * gv[i][e] + bv[i][e] : 0.f;
+      const float bias_e = kind == 0 && b ? tb[i][e >> 2][e & 3] : 0.f;
+      float y = valid ? (v[i][e] - mean) * rstd * tg[i][e >> 2][e & 3] + bias_e : 0.f;
       hi.h[e] = f32_to_bf16(y);
       lo.h[e] = f32_to_bf16(bf16_residual(y, hi.h[e]));
     }
     size_t off = act_off(r, c, d);
     *(uint4 *)(xn + off) = hi.u;
     if (xn_lo) *(uint4 *)(xn_lo + off) = lo.u;
+    if ((EMB || NP > 0) && r < R) {
+      *(float4 *)(xw + (size_t)r * d + c) = make_float4(v[i][0], v[i][1], v[i][2], v[i][3]);
+      *(float4 *)(xw + (size_t)r * d + c + 4) = make_float4(v[i][4], v[i][5], v[i][6], v[i][7]);
+    }
   }
 }
 
-// The same for launches of many rows (the context pass): a wave per row, four rows per block.  Lane l takes the
-// 8-value granules l, l + 64, ... of its row, the two sums are wave reductions (no barrier, no LDS), and gain and
-// bias are asked for only when the statistics are known (they sit in the caches), so a wave holds little more
-// than its row and many waves are resident.
+// The same for launches of many rows (the context pass): a wave per row, up to four rows per block.  Lane l takes the
+// 8-value granules l, l + 64, ... of its row, and the two sums are wave reductions (no barrier, no LDS).  A batch of
+// granules, slices among them, is requested before any of it is waited for; gain and bias, up to width 2048, under the sums,
+// beyond (a lane's registers are full) when they are used.  Requests under conditions, the completed halves stored between
+// them, and four granules for every width up to 2048 took 6.2 us (192 rows of width 768, four slices; now 3.8), 11.6
+// (2048 rows; 9.5, 4.6 TB/s).
 template <int NGW, int NP>     // granules per lane: d <= 512 * NGW; NP pending slices
 __global__ __launch_bounds__(256) void k_norm_rows(const int32_t *flags, float *x, const float *ypart, const float *g,
                                                    const float *b, int d, int R, int rows_pad, int kind, float eps,
                                                    bf16_t *xn, bf16_t *xn_lo) {
   const size_t part_stride = (size_t)rows_pad * d;
-  const int lane = threadIdx.x & 63, r = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const bool valid = r < R && (flags[r] & ROW_VALID);
+  const int lane = threadIdx.x & 63, r = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   float *xr = x + (size_t)r * d;
+  const float *yr = ypart + (size_t)r * d;
+  // granules of a batch: at most 20 requests of 32 bytes a lane, at clamped places and without a branch
+  constexpr int GB = NGW * (1 + NP) <= 20 ? NGW : NGW * (1 + NP) <= 40 ? NGW / 2 : NGW * (1 + NP) <= 80 ? NGW / 4 : NGW / 8;
   float v[NGW][8];
+  int fl = 0;
 #pragma unroll
-  for (int i = 0; i < NGW; ++i) {
-    const int c = (lane + 64 * i) * 8;
-    const bool in = c < d;
+  for (int i0 = 0; i0 < NGW; i0 += GB) {
+    floatx4 xv[GB][2], y[GB][2][NP > 0 ? NP : 1];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      float4 t = in ? *(const float4 *)(xr + c + 4 * h) : make_float4(0.f, 0.f, 0.f, 0.f);
-      float4 y[NP > 0 ? NP : 1];
+    for (int j = 0; j < GB; ++j) {
+      const int c = min((lane + 64 * (i0 + j)) * 8, d - 8);
 #pragma unroll
-      for (int pp = 0; pp < NP; ++pp)
-        y[pp] = in ? *(const float4 *)(ypart + pp * part_stride + (size_t)r * d + c + 4 * h)
-                   : make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int h = 0; h < 2; ++h) {
+        xv[j][h] = *(const floatx4 *)(xr + c + 4 * h);
 #pragma unroll
-      for (int pp = 0; pp < NP; ++pp) { t.x += y[pp].x; t.y += y[pp].y; t.z += y[pp].z; t.w += y[pp].w; }
-      if (NP > 0 && in && r < R) *(float4 *)(xr + c + 4 * h) = t;
-      v[i][4 * h] = t.x; v[i][4 * h + 1] = t.y; v[i][4 * h + 2] = t.z; v[i][4 * h + 3] = t.w;
+        for (int pp = 0; pp < NP; ++pp) y[j][h][pp] = *(const floatx4 *)(yr + pp * part_stride + c + 4 * h);
+      }
     }
+    if (i0 == 0) fl = flags[min(r, R - 1)];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < GB; ++j) {
+      const bool in = (lane + 64 * (i0 + j)) * 8 < d;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int pp = 0; pp < NP; ++pp) xv[j][h] += y[j][h][pp];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[i0 + j][4 * h + e] = in ? xv[j][h][e] : 0.f;
+      }
+    }
+  }
+  const bool valid = r < R && (fl & ROW_VALID);
+  // gain and bias, whose registers were the slices': asked for under the sums where a lane has room for them
+  constexpr int NA = NGW <= 4 ? NGW : 1;
+  const float *bias = kind == 0 && b ? b : g;
+  floatx4 tg[NA][2], tb[NA][2];
+  if (NGW <= 4) {
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+      const int c = min((lane + 64 * i) * 8, d - 8);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        tg[i][h] = *(const floatx4 *)(g + c + 4 * h);
+        tb[i][h] = *(const floatx4 *)(bias + c + 4 * h);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
   }
   float s1 = 0.f;
 #pragma unroll
@@ -279,24 +317,29 @@ __global__ __launch_bounds__(256) void k_norm_rows(const int32_t *flags, float *
   for (int i = 0; i < NGW; ++i) {
     const int c = (lane + 64 * i) * 8;
     if (c >= d) continue;
-    float gv[8], bv[8];
+    const int ia = NGW <= 4 ? i : 0;
+    if (NGW > 4) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      float4 tg = *(const float4 *)(g + c + 4 * h);
-      float4 tb = (kind == 0 && b) ? *(const float4 *)(b + c + 4 * h) : make_float4(0.f, 0.f, 0.f, 0.f);
-      gv[4 * h] = tg.x; gv[4 * h + 1] = tg.y; gv[4 * h + 2] = tg.z; gv[4 * h + 3] = tg.w;
-      bv[4 * h] = tb.x; bv[4 * h + 1] = tb.y; bv[4 * h + 2] = tb.z; bv[4 * h + 3] = tb.w;
+      for (int h = 0; h < 2; ++h) {
+        tg[0][h] = *(const floatx4 *)(g + c + 4 * h);
+        tb[0][h] = *(const floatx4 *)(bias + c + 4 * h);
+      }
     }
     Frag hi, lo;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      float y = valid ? (v[i][e] - mean) * rstd * gv[e] + bv[e] : 0.f;
+      const float bias_e = kind == 0 && b ? tb[ia][e >> 2][e & 3] : 0.f;
+      float y = valid ? (v[i][e] - mean) * rstd * tg[ia][e >> 2][e & 3] + bias_e : 0.f;
       hi.h[e] = f32_to_bf16(y);
       lo.h[e] = f32_to_bf16(bf16_residual(y, hi.h[e]));
     }
     size_t off = act_off(r, c, d);
     *(uint4 *)(xn + off) = hi.u;
     if (xn_lo) *(uint4 *)(xn_lo + off) = lo.u;
+    if (NP > 0 && r < R) {
+      *(float4 *)(xr + c) = make_float4(v[i][0], v[i][1], v[i][2], v[i][3]);
+      *(float4 *)(xr + c + 4) = make_float4(v[i][4], v[i][5], v[i][6], v[i][7]);
+    }
   }
 }
 
@@ -307,8 +350,11 @@ int mfma_norm(pd_ctx *c, const float *gain, const float *bias, int R, hipStream_
   const pd_config &g = c->cfg;
   PD_REQUIRE(d <= 2048 * 4, PD_EINVAL, "d_model %d too large for the norm kernel", d);
   if (rows > 128 && !c->embed_pending && !c->packed) {
+    // (up to a row per compute unit a block of its own for each: 192 rows of width 768, four slices 4.2 us in blocks of four
+    // rows, 3.8 in blocks of one; 400 rows 4.3 and 4.5)
+    const int wpb = rows <= 256 ? 1 : 4;
 #define PD_NORM_R(G, P)                                                                           \
-  hipLaunchKernelGGL((k_norm_rows<G, P>), dim3(rows / 4), dim3(256), 0, s, c->rows.flags, c->x, c->ypart, gain, bias, d, \
+  hipLaunchKernelGGL((k_norm_rows<G, P>), dim3(rows / wpb), dim3(64 * wpb), 0, s, c->rows.flags, c->x, c->ypart, gain, bias, d, \
                      R, c->R_pad, g.norm_kind, g.norm_eps, xn, mfma_lo(c, xn, d))
 #define PD_NORM_RP(G)                                                                            \
   switch (c->pend_parts) {                                                                       \
@@ -318,7 +364,8 @@ int mfma_norm(pd_ctx *c, const float *gain, const float *bias, int R, hipStream_
     case 4: PD_NORM_R(G, 4); break;                                                              \
     default: pd_set_error("unsupported number of pending slices: %d", c->pend_parts); return PD_EINVAL; \
   }
-    if (d <= 2048) { PD_NORM_RP(4) } else if (d <= 4096) { PD_NORM_RP(8) } else { PD_NORM_RP(16) }
+    if (d <= 512) { PD_NORM_RP(1) } else if (d <= 1024) { PD_NORM_RP(2) } else if (d <= 2048) { PD_NORM_RP(4) }
+    else if (d <= 4096) { PD_NORM_RP(8) } else { PD_NORM_RP(16) }
 #undef PD_NORM_RP
 #undef PD_NORM_R
     PD_CHECK_HIP(hipGetLastError());
