@@ -130,13 +130,14 @@ int mfma_layer(pd_ctx *c, int l, int R, int A, int nreq, int req0, int kv_overri
   c->embedded = false;
   GemmArgs a;
   mfma_gemm_base(c, a, R);
+  // context pass, last layer: only its keys and values are ever used (nothing reads the queries or the residual stream of a
+  // context token there), and only they are projected: 4096 rows of width 2048 176 -> 124 us, 4082 of width 4096 360 -> 229
+  if (kv_override >= 0 && l == g.n_layer - 1 && !mode)
+    return mfma_qkv(c, a, lw.p_wqkv + (size_t)g.d_model * g.d_model, 2 * g.d_model / 16, 1, lw.kc, lw.vc, lw.kc_lo, lw.vc_lo, R, s);
   // QKV projection (+ rotary) + KV append
   if ((rc = mfma_qkv(c, a, lw.p_wqkv, 3 * g.d_model / 16, 0, lw.kc, lw.vc, lw.kc_lo, lw.vc_lo, R, s,
                      finish ? lw.q1 : nullptr, finish ? lw.q2 : nullptr)))
     return rc;
-  // context pass, last layer: only its keys and values are ever used (nothing reads the residual
-  // stream of a context token after the last layer)
-  if (kv_override >= 0 && l == g.n_layer - 1 && !mode) return PD_OK;
   if ((rc = mfma_attention(c, lw, A, nreq, req0, kv_override, s, mode))) return rc;
   const bool decode_step = kv_override < 0 && !mode;
   return mfma_out_ffn(c, a, lw.p_wo, lw, R, s, decode_step && l + 1 < g.n_layer ? c->layers[l + 1].n1g : nullptr);

@@ -97,6 +97,7 @@ struct LinArgs {
   // slices [SLICES][slice_stride] that the rows of x (of the residual) still lack, or NULL; LIN_SLICE: where its own go
   const float *pend; size_t slice_stride;
   void *kc, *vc, *kc_lo, *vc_lo; int d, H, hd, kv_cap; int32_t *kv_sat;   // LIN_QKV
+  int sec0;                           // ... section of the first column (0: Q, K, V follow; 1: K, V only)
   float *logits; int S;               // LIN_HEAD: NULL, or [B][S][N] addressed by a row's request and subsequence
   float *part_val; int32_t *part_idx; int n_tiles;
 };
@@ -308,7 +309,7 @@ __global__ __launch_bounds__(64 * NW) void k_lin(const float *hot_x, const void 
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         if (n + j >= N) continue;
-        const int sec = (n + j) / a.d, c = (n + j) - sec * a.d, h = c / a.hd;
+        const int s_in = (n + j) / a.d, sec = s_in + a.sec0, c = (n + j) - s_in * a.d, h = c / a.hd;
         if (sec == 0) { a.out[(size_t)r * a.ldo + n + j] = y[j]; continue; }
         const size_t slab = ((size_t)info.y * a.H + h) * a.kv_cap * a.hd, dim = c - h * a.hd;
         const size_t o = slab + (sec == 1 ? (size_t)info.z * a.hd + dim : dim * a.kv_cap + info.z);
@@ -649,9 +650,14 @@ int simple_layer(pd_ctx *c, int l, int R, int A, int nreq, int req0, int kv_over
   if ((rc = normed(c, a, lw.n1g, lw.n1b, R, s))) return rc;
   if (gather) { a.tok_emb = c->tok_emb; a.pos_emb = c->pos_emb; }
   a.pend = pend;
-  a.out = c->qkv32; a.ldo = 3 * d;
+  // context pass, last layer: only its keys and values are ever used, and only they are projected
+  const bool last = kv_override >= 0 && l == g.n_layer - 1;
+  const int n0 = last ? d : 0;
+  const void *wqkv = (const char *)lw.wqkv + (size_t)n0 * d * (g.dtype == 0 ? sizeof(float) : sizeof(bf16_t));
+  a.out = c->qkv32 + n0; a.ldo = 3 * d; a.sec0 = last ? 1 : 0;
   if (g.pos_kind == 1) {
-    if ((rc = linear<LIN_STORE>(c, a, lw.wqkv, nullptr, R, 3 * d, d, s))) return rc;
+    // (the rotation also turns the queries of a pass before where this one has none; nobody reads them)
+    if ((rc = linear<LIN_STORE>(c, a, wqkv, nullptr, R, 3 * d - n0, d, s))) return rc;
     if (g.dtype == 0)
       hipLaunchKernelGGL(k_qkv_post<float>, dim3(R), dim3(256), 0, s, c->qkv32, (float *)lw.kc, (float *)lw.vc,
                          (float *)nullptr, (float *)nullptr, c->rows, c->rope_cs, d, H, hd, c->kv_cap, c->kv_sat);
@@ -661,10 +667,9 @@ int simple_layer(pd_ctx *c, int l, int R, int A, int nreq, int req0, int kv_over
     PD_CHECK_HIP(hipGetLastError());
   } else {
     a.kc = lw.kc; a.vc = lw.vc; a.kc_lo = lw.kc_lo; a.vc_lo = lw.vc_lo;
-    if ((rc = linear<LIN_QKV>(c, a, lw.wqkv, nullptr, R, 3 * d, d, s))) return rc;
+    if ((rc = linear<LIN_QKV>(c, a, wqkv, nullptr, R, 3 * d - n0, d, s))) return rc;
   }
-  // context pass, last layer: only its keys and values are ever used
-  if (kv_override >= 0 && l == g.n_layer - 1) return PD_OK;
+  if (last) return PD_OK;
   AttnF32Args t;
   memset(&t, 0, sizeof(t));
   t.out = (float *)c->att; t.qkv = c->qkv32; t.kc = lw.kc; t.vc = lw.vc; t.kc_lo = lw.kc_lo; t.vc_lo = lw.vc_lo;
