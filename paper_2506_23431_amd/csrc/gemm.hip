@@ -214,17 +214,13 @@ __global__ __launch_bounds__(256) void k_norm_bf16(const int32_t *flags, const v
   for (int i = 0; i < NG; ++i) {
     int c = (threadIdx.x + i * 256) * 8;
     if (c >= d) continue;
-    Frag hi, lo;
+    float y[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const float bias_e = kind == 0 && b ? tb[i][e >> 2][e & 3] : 0.f;
-      float y = valid ? (v[i][e] - mean) * rstd * tg[i][e >> 2][e & 3] + bias_e : 0.f;
-      hi.h[e] = f32_to_bf16(y);
-      lo.h[e] = f32_to_bf16(bf16_residual(y, hi.h[e]));
+      y[e] = valid ? (v[i][e] - mean) * rstd * tg[i][e >> 2][e & 3] + bias_e : 0.f;
     }
-    size_t off = act_off(r, c, d);
-    *(uint4 *)(xn + off) = hi.u;
-    if (xn_lo) *(uint4 *)(xn_lo + off) = lo.u;
+    store8_split(xn, xn_lo, act_off(r, c, d), y);
     if ((EMB || NP > 0) && r < R) {
       *(float4 *)(xw + (size_t)r * d + c) = make_float4(v[i][0], v[i][1], v[i][2], v[i][3]);
       *(float4 *)(xw + (size_t)r * d + c + 4) = make_float4(v[i][4], v[i][5], v[i][6], v[i][7]);
@@ -325,17 +321,13 @@ __global__ __launch_bounds__(256) void k_norm_rows(const int32_t *flags, float *
         tb[0][h] = *(const floatx4 *)(bias + c + 4 * h);
       }
     }
-    Frag hi, lo;
+    float y[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const float bias_e = kind == 0 && b ? tb[ia][e >> 2][e & 3] : 0.f;
-      float y = valid ? (v[i][e] - mean) * rstd * tg[ia][e >> 2][e & 3] + bias_e : 0.f;
-      hi.h[e] = f32_to_bf16(y);
-      lo.h[e] = f32_to_bf16(bf16_residual(y, hi.h[e]));
+      y[e] = valid ? (v[i][e] - mean) * rstd * tg[ia][e >> 2][e & 3] + bias_e : 0.f;
     }
-    size_t off = act_off(r, c, d);
-    *(uint4 *)(xn + off) = hi.u;
-    if (xn_lo) *(uint4 *)(xn_lo + off) = lo.u;
+    store8_split(xn, xn_lo, act_off(r, c, d), y);
     if (NP > 0 && r < R) {
       *(float4 *)(xr + c) = make_float4(v[i][0], v[i][1], v[i][2], v[i][3]);
       *(float4 *)(xr + c + 4) = make_float4(v[i][4], v[i][5], v[i][6], v[i][7]);

@@ -46,14 +46,14 @@ __device__ __forceinline__ floatx4 mfma16h(const Frag &a, const Frag &b, floatx4
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(a.hv, b.hv, c, 0, 0, 0);
 }
 
-__device__ __forceinline__ uint32_t pack2(float lo, float hi) {
-  return (uint32_t)f32_to_bf16(lo) | ((uint32_t)f32_to_bf16(hi) << 16);
-}
-
 // Activations are carried as a pair of bf16 values, x ~ hi + lo with hi = bf16(x) and
 // lo = bf16(x - hi): two matrix-core passes over the same weight fragment then see the
 // activation to about 16 mantissa bits, which costs no extra HBM traffic.
-__device__ __forceinline__ float bf16_residual(float x, bf16_t hi) { return x - bf16_to_f32(hi); }
+struct BfPairs { uint32_t hi, lo; };      // high and low parts of two values
+__device__ __forceinline__ BfPairs split2(float x, float y) {
+  const uint32_t h = pack2(x, y);
+  return BfPairs{h, pack2(x - __uint_as_float(h << 16), y - __uint_as_float(h & 0xffff0000u))};
+}
 
 // Activation matrices [rows][K] that feed a matrix multiply are stored fragment-major too:
 // the B operand of the instruction for row tile rt (16 rows) and k-tile kt (32 values) is
@@ -65,11 +65,15 @@ __device__ __forceinline__ size_t act_off(int r, int k, int K) {
 
 // store 4 consecutive values (k multiple of 4) as hi (and, if lo != NULL, lo) bf16 quadruples
 __device__ __forceinline__ void store4_split(bf16_t *hi, bf16_t *lo, size_t off, const float y[4]) {
-  bf16_t h0 = f32_to_bf16(y[0]), h1 = f32_to_bf16(y[1]), h2 = f32_to_bf16(y[2]), h3 = f32_to_bf16(y[3]);
-  *(uint2 *)(hi + off) = make_uint2((uint32_t)h0 | ((uint32_t)h1 << 16), (uint32_t)h2 | ((uint32_t)h3 << 16));
-  if (lo)
-    *(uint2 *)(lo + off) = make_uint2(pack2(bf16_residual(y[0], h0), bf16_residual(y[1], h1)),
-                                      pack2(bf16_residual(y[2], h2), bf16_residual(y[3], h3)));
+  const BfPairs a = split2(y[0], y[1]), b = split2(y[2], y[3]);
+  *(uint2 *)(hi + off) = make_uint2(a.hi, b.hi);
+  if (lo) *(uint2 *)(lo + off) = make_uint2(a.lo, b.lo);
+}
+// ... and 8
+__device__ __forceinline__ void store8_split(bf16_t *hi, bf16_t *lo, size_t off, const float y[8]) {
+  const BfPairs a = split2(y[0], y[1]), b = split2(y[2], y[3]), c = split2(y[4], y[5]), d = split2(y[6], y[7]);
+  *(uint4 *)(hi + off) = make_uint4(a.hi, b.hi, c.hi, d.hi);
+  if (lo) *(uint4 *)(lo + off) = make_uint4(a.lo, b.lo, c.lo, d.lo);
 }
 
 // the same for fp16 pairs (queries: they meet the fp16 key cache in the matrix core)

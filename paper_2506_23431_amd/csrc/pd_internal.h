@@ -38,19 +38,19 @@ void pd_set_error(const char *fmt, ...);
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float bf16_to_f32(bf16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 
-// round-to-nearest-even; inputs are finite in this library
-__device__ __forceinline__ bf16_t f32_to_bf16(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (bf16_t)(u >> 16);
+// to nearest, ties to even, by the instruction for it: one for two values, where the sum of the bits with 0x7fff and the last
+// bit kept took four for each (every float gives the same bits, NaN stays NaN)
+__device__ __forceinline__ bf16_t f32_to_bf16(float f) { return __builtin_bit_cast(bf16_t, (__bf16)f); }
+__device__ __forceinline__ uint32_t pack2(float lo, float hi) {
+  typedef float floatx2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2{lo, hi}), bf16x2));
 }
 
 // fp16 bit patterns for the KV cache of dtype 1: same two bytes per element as bf16, 11-bit
 // significand.  Values beyond the fp16 range saturate instead of becoming infinite.
 typedef _Float16 f16_t;
-__device__ __forceinline__ f16_t f32_to_f16_sat(float f) {
-  return (f16_t)fminf(fmaxf(f, -65504.f), 65504.f);
-}
+__device__ __forceinline__ f16_t f32_to_f16_sat(float f) { return (f16_t)__builtin_amdgcn_fmed3f(f, -65504.f, 65504.f); }
 
 __device__ __forceinline__ float ld_f32(const float *p, size_t i) { return p[i]; }
 __device__ __forceinline__ float ld_f32(const f16_t *p, size_t i) { return (float)p[i]; }

@@ -484,18 +484,14 @@ __global__ __launch_bounds__(1024) void k_turn(const float *part_val, const int3
       for (int n = 0; n < NGW; ++n) {
         const int c = (lane + 64 * n) * 8;
         if (c >= d) continue;
-        Frag hi, lo;
+        float y[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const float y = has ? (v[n][e] - mean) * rstd * gv[n][e] + bv[n][e] : 0.f;
-          hi.h[e] = f32_to_bf16(y);
-          lo.h[e] = f32_to_bf16(bf16_residual(y, hi.h[e]));
+          y[e] = has ? (v[n][e] - mean) * rstd * gv[n][e] + bv[n][e] : 0.f;
         }
         *(float4 *)(a.x + (size_t)r * d + c) = make_float4(v[n][0], v[n][1], v[n][2], v[n][3]);
         *(float4 *)(a.x + (size_t)r * d + c + 4) = make_float4(v[n][4], v[n][5], v[n][6], v[n][7]);
-        const size_t off = act_off(r, c, d);
-        *(uint4 *)(a.xn + off) = hi.u;
-        if (a.xn_lo) *(uint4 *)(a.xn_lo + off) = lo.u;
+        store8_split(a.xn, a.xn_lo, act_off(r, c, d), y);
       }
     }
   }
