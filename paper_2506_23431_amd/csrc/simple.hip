@@ -15,6 +15,7 @@
 #include "pd_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
@@ -102,50 +103,74 @@ struct LinArgs {
   float *part_val; int32_t *part_idx; int n_tiles;
 };
 
-// a row of the residual stream, read or gathered
-template <typename WT>
+// Where the rows that a launch normalises (LIN_RESID: adds to) come from: a buffer, a buffer and the slices it still lacks, or the
+// embedding tables.  A part of the kernel's type: decided at run time, every row was read in branches of its own, each waited
+// for before the next row was asked for (8 rows of width 64 from the tables: QKV 6.6 -> 5.2 us, from the buffer FFN 5.2 -> 4.4).
+enum { SRC_ROWS = 0, SRC_SLICES = 1, SRC_GATHER = 2 };
+constexpr int row_parts(int src) { return src == SRC_SLICES ? 1 + SLICES : src == SRC_GATHER ? 2 : 1; }
+struct RowState { bool valid, learned; };            // SRC_GATHER: the row carries a token; positions are learned
+
+// first: buffer or token table; second: slices or position table
+template <typename WT, int SRC>
 struct RowSrc {
-  const float *x, *pend; size_t stride; const WT *te, *pe; bool zero;
-  __device__ __forceinline__ RowSrc(const LinArgs &a, const float *base, int r, int ld, bool may_gather)
-      : x(base + (size_t)r * ld), pend(nullptr), stride(a.slice_stride), te(nullptr), pe(nullptr), zero(false) {
-    if (may_gather && a.pend) pend = a.pend + (size_t)r * ld;
-    if (may_gather && a.tok_emb) {
-      const int fl = a.rt.flags[r], tok = a.rt.tok[r], pos = a.rt.pos[r];      // independent loads
-      zero = !(fl & ROW_VALID);
-      te = (const WT *)a.tok_emb + (zero ? 0 : (size_t)tok * ld);
-      if (a.pos_emb) pe = (const WT *)a.pos_emb + (zero ? 0 : (size_t)pos * ld);
+  const float *x; size_t stride; const WT *te, *pe; RowState state;
+  __device__ __forceinline__ RowSrc(const LinArgs &a, const void *first, const void *second, int r, int ld)
+      : x(nullptr), stride(0), te(nullptr), pe(nullptr), state{true, true} {
+    if (SRC == SRC_GATHER) {
+      gather(first, second, a.rt.flags[r], a.rt.tok[r], a.rt.pos[r], ld);     // (independent reads)
+    } else {
+      x = (const float *)first + (size_t)r * ld;
+      if (SRC == SRC_SLICES) { pe = (const WT *)((const float *)second + (size_t)r * ld); stride = a.slice_stride; }
     }
   }
-  template <bool VEC> __device__ __forceinline__ floatx4 at(int k, int n) const {
-    if (!te) {
-      floatx4 v = ld_row4<VEC>(x, k, n);
-      if (pend) {                       // the same for the whole launch
-        floatx4 p[SLICES];
+  __device__ __forceinline__ RowSrc(const void *first, const void *second, int fl, int tok, int pos, int ld) : x(nullptr), stride(0) {
+    gather(first, second, fl, tok, pos, ld);
+  }
+  __device__ __forceinline__ void gather(const void *first, const void *second, int fl, int tok, int pos, int ld) {
+    // (places are masked, not chosen: a choice would put a read into a branch)
+    const int has = -(fl & ROW_VALID), lp = second ? -1 : 0;
+    static_assert(ROW_VALID == 1, "a mask by negation");
+    state = RowState{has != 0, lp != 0};
+    te = (const WT *)first + (size_t)(tok & has) * ld;
+    pe = (const WT *)(second ? second : first) + (size_t)(((pos & lp) | (tok & ~lp)) & has) * ld;    // (no positions: the token's again)
+  }
+  // in two parts: the second waits for the argument struct where there are slices
+  template <bool VEC> __device__ __forceinline__ void ask(floatx4 (&q)[row_parts(SRC)], int k, int n) const {
+    q[0] = SRC == SRC_GATHER ? ld_row4<VEC>(te, k, n) : ld_row4<VEC>(x, k, n);
+  }
+  template <bool VEC> __device__ __forceinline__ void ask_rest(floatx4 (&q)[row_parts(SRC)], int k, int n) const {
 #pragma unroll
-        for (int i = 0; i < SLICES; ++i) p[i] = ld_row4<VEC>(pend + i * stride, k, n);
-        v += (p[0] + p[1]) + (p[2] + p[3]);
-      }
-      return v;
-    }
-    floatx4 v = ld_row4<VEC>(te, k, n);
-    if (pe) v += ld_row4<VEC>(pe, k, n);
-    return zero ? floatx4{0.f, 0.f, 0.f, 0.f} : v;
+    for (int i = 1; i < row_parts(SRC); ++i)
+      q[i] = SRC == SRC_GATHER ? ld_row4<VEC>(pe, k, n) : ld_row4<VEC>((const float *)pe + (i - 1) * stride, k, n);
   }
 };
+template <int SRC>
+__device__ __forceinline__ floatx4 row_value(const floatx4 (&q)[row_parts(SRC)], RowState state) {
+  constexpr int N = row_parts(SRC) - 1;
+  if (SRC == SRC_ROWS) return q[0];
+  if (SRC == SRC_SLICES) return q[0] + ((q[min(1, N)] + q[min(2, N)]) + (q[min(3, N)] + q[N]));
+  floatx4 y;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) y[e] = state.valid ? (state.learned ? q[0][e] + q[N][e] : q[0][e]) : 0.f;
+  return y;
+}
 
 // A block owns one 16-column tile and RT tiles of 16 rows; its NW waves cut K in steps of 16, the partial tiles are
 // summed through LDS.  VPL > 0: the rows are normalised first (K <= 256 VPL).  Every wave reads 16 / NW rows once,
 // whole (VPL quads per lane), takes mean and variance in registers (two passes) and leaves the normalised row in LDS;
-// the first weights are requested before that (by the leading arguments, which arrive in registers).  Bound by latency at the sizes of this path: enough waves that each
-// has one or two batches of requests (512 x 2048, 12 rows: 13.5 us with a wave per column, now 6-7).
-template <typename WT, typename KT, int EPI, int NW, int RT, int VPL, bool VEC>
-__global__ __launch_bounds__(64 * NW) void k_lin(const float *hot_x, const void *hot_w, const void *hot_w2, const float *hot_g,
+// the first weights are requested before that (by the leading arguments, which arrive in registers).  Bound by latency at the
+// sizes of this path: enough waves that each has one or two batches of requests (512 x 2048, 12 rows: 13.5 us with a wave per
+// column, 6-7 so), and every request of the first batch in flight before anything is waited for.
+template <typename WT, typename KT, int EPI, int NW, int RT, int VPL, bool VEC, int SRC>
+__global__ __launch_bounds__(64 * NW) void k_lin(const void *hot_x, const void *hot_w, const void *hot_w2, const float *hot_g,
                                                    const float *hot_b, const int4 *hot_info, int R, int K, LinArgs a) {
+  // (hot_x: the rows or, of normed gathered ones, the token table; hot_w2: the second matrix of LIN_SWIGLU, else RowSrc's second)
   const int N = a.N;
   constexpr bool NORM = VPL > 0;
   constexpr int NT = EPI == LIN_SWIGLU ? 2 : 1, U = 4;
   constexpr int XLD = NORM ? 256 * VPL + 4 : 4;      // (+ 4: the 16 rows of a step lie in different banks)
   static_assert(!NORM || RT == 1, "row statistics are taken for one row tile");
+  static_assert(SRC == SRC_ROWS || (EPI != LIN_SWIGLU && (NORM || EPI == LIN_RESID)), "rows put together: normed, or the residual");
   __shared__ floatx4 red[NW][NT * RT][64];
   __shared__ float sm_x[NORM ? 16 : 1][XLD];
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
@@ -156,47 +181,93 @@ __global__ __launch_bounds__(64 * NW) void k_lin(const float *hot_x, const void 
   const WT *wrow[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) wrow[t] = (const WT *)(t ? hot_w2 : hot_w) + (size_t)min(n0 + m, N - 1) * K;
-  // weights of U steps; steps and values past the end are zero
+  // weights of U steps (beyond the share: the last place again, not multiplied)
   auto load_w = [&](floatx4 (&wv)[NT][U], int s) {
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int k = (s + u) * 16 + 4 * g;
-        floatx4 v = ld_row4<VEC>(wrow[t], k, K);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) wv[t][u][e] = (s + u < s1 && k + e < K) ? v[e] : 0.f;
-      }
+      for (int u = 0; u < U; ++u) wv[t][u] = ld_row4<VEC>(wrow[t], min(s + u, max(s1 - 1, 0)) * 16 + 4 * g, K);
   };
   floatx4 wv[NT][U];
-  load_w(wv, s0);
-  // what the finishing waves need from memory is requested now: the residual rows, where a row's results go
-  floatx4 res = floatx4{0.f, 0.f, 0.f, 0.f};
-  int4 info = make_int4(0, 0, 0, 0);
-  if (w < RT) {
-    const int r = min(r0 + w * 16 + m, R - 1);
-    if (EPI == LIN_RESID) {
-      const RowSrc<WT> src(a, a.res, r, N, true);
-      res = src.template at<false>(n0 + 4 * g, N);
+  constexpr int RPW = NORM ? 16 / NW : 1, VP = NORM ? VPL : 1;      // rows per wave, quads per lane
+  constexpr int NSRC = NORM ? SRC : SRC_ROWS, RSRC = EPI == LIN_RESID ? SRC : SRC_ROWS;
+  floatx4 xq[RPW][VP][row_parts(NSRC)], gv[VP], bv[VP];
+  RowState xs[RPW];
+  // (rows before weights: the number of columns is in the argument struct, which is still on its way)
+  constexpr bool AHEAD = !NORM && RT == 1;           // a batch's rows are requested with its weights, else when it begins
+  floatx4 xv[RT][U];
+  auto load_x = [&](floatx4 (&xv)[RT][U], int s) {
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+      const float *row = (const float *)hot_x + (size_t)min(r0 + i * 16 + m, R - 1) * K;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = min(s + u, max(s1 - 1, 0)) * 16 + 4 * g;
+        if constexpr (NORM) xv[i][u] = *(const floatx4 *)&sm_x[m][min(k, XLD - 4)];
+        else xv[i][u] = ld_row4<VEC>(row, k, K);
+      }
     }
-    if (EPI == LIN_QKV) info = hot_info[r];        // {flags, req, slot, pos}
-    if (EPI == LIN_HEAD) info = hot_info[r];        // {flags, sub, lim, req}
-  }
+  };
+  if (AHEAD) load_x(xv, s0);
+  if constexpr (!NORM) load_w(wv, s0);
   if constexpr (NORM) {
-    constexpr int RPW = 16 / NW;      // rows per wave
-    floatx4 xv[RPW][VPL], gv[VPL], bv[VPL];
-    float s[RPW], q[RPW];
+    auto row = [&](int i) { return RowSrc<WT, NSRC>(a, hot_x, hot_w2, min(r0 + w * RPW + i, R - 1), K); };
+    if (SRC != SRC_GATHER)
 #pragma unroll
-    for (int i = 0; i < RPW; ++i) {
-      const RowSrc<WT> src(a, hot_x, min(r0 + w * RPW + i, R - 1), K, true);
+      for (int i = 0; i < RPW; ++i)
 #pragma unroll
-      for (int v = 0; v < VPL; ++v) xv[i][v] = src.template at<VEC>(4 * (lane + 64 * v), K);
-    }
+        for (int v = 0; v < VPL; ++v) row(i).template ask<VEC>(xq[i][v], 4 * (lane + 64 * v), K);
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
       gv[v] = ld_row4<VEC>(hot_g, 4 * (lane + 64 * v), K);
-      bv[v] = hot_b ? ld_row4<VEC>(hot_b, 4 * (lane + 64 * v), K) : floatx4{0.f, 0.f, 0.f, 0.f};
+      bv[v] = ld_row4<VEC>(hot_b ? hot_b : hot_g, 4 * (lane + 64 * v), K);
     }
+    int fl = 0, tok = 0, pos = 0;         // lane i: of row i (read one by one they were waited for one by one)
+    if (SRC == SRC_GATHER) {
+      const int rl = min(r0 + w * RPW + lane % RPW, R - 1);
+      fl = a.rt.flags[rl]; tok = a.rt.tok[rl]; pos = a.rt.pos[rl];
+    }
+    load_w(wv, s0);
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) {
+      const RowSrc<WT, NSRC> src = SRC == SRC_GATHER
+          ? RowSrc<WT, NSRC>(hot_x, hot_w2, __builtin_amdgcn_readlane(fl, i), __builtin_amdgcn_readlane(tok, i), __builtin_amdgcn_readlane(pos, i), K)
+          : row(i);
+      xs[i] = src.state;
+#pragma unroll
+      for (int v = 0; v < VPL; ++v) {
+        if (SRC == SRC_GATHER) src.template ask<VEC>(xq[i][v], 4 * (lane + 64 * v), K);
+        src.template ask_rest<VEC>(xq[i][v], 4 * (lane + 64 * v), K);
+      }
+    }
+  }
+  // what the finishing waves need from memory: the residual rows, where a row's results go
+  const int rf = min(r0 + min(w, RT - 1) * 16 + m, R - 1);
+  floatx4 rq[row_parts(RSRC)];
+  RowState rs{true, true};
+  if constexpr (EPI == LIN_RESID) {
+    if (w < RT) {                       // (asked for by every wave, five quads each of 16 rows: 8.1 us where 4.4 will do)
+      const RowSrc<WT, RSRC> src(a, SRC == SRC_GATHER ? a.tok_emb : (const void *)a.res, hot_w2, rf, N);
+      rs = src.state;
+      if (VEC && N % 4 == 0) {
+        src.template ask<true>(rq, n0 + 4 * g, N);
+        src.template ask_rest<true>(rq, n0 + 4 * g, N);
+      } else {
+        src.template ask<false>(rq, n0 + 4 * g, N);
+        src.template ask_rest<false>(rq, n0 + 4 * g, N);
+      }
+    }
+  }
+  int4 info = make_int4(0, 0, 0, 0);
+  if (EPI == LIN_QKV || EPI == LIN_HEAD) info = hot_info[rf];       // {flags, req, slot, pos}; {flags, sub, lim, req}
+  if constexpr (NORM) {
+    __builtin_amdgcn_sched_barrier(0);
+    floatx4 nx[RPW][VPL];
+    float s[RPW], q[RPW];
+#pragma unroll
+    for (int i = 0; i < RPW; ++i)
+#pragma unroll
+      for (int v = 0; v < VPL; ++v) nx[i][v] = row_value<NSRC>(xq[i][v], xs[i]);
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
       s[i] = 0.f;
@@ -204,7 +275,7 @@ __global__ __launch_bounds__(64 * NW) void k_lin(const float *hot_x, const void 
 #pragma unroll
         for (int v = 0; v < VPL; ++v)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) s[i] += 4 * (lane + 64 * v) + e < K ? xv[i][v][e] : 0.f;
+          for (int e = 0; e < 4; ++e) s[i] += 4 * (lane + 64 * v) + e < K ? nx[i][v][e] : 0.f;
     }
 #pragma unroll
     for (int i = 0; i < RPW; ++i) s[i] = fold_wave(s[i], Add());
@@ -215,7 +286,7 @@ __global__ __launch_bounds__(64 * NW) void k_lin(const float *hot_x, const void 
 #pragma unroll
       for (int v = 0; v < VPL; ++v)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { const float t = xv[i][v][e] - s[i]; q[i] += 4 * (lane + 64 * v) + e < K ? t * t : 0.f; }
+        for (int e = 0; e < 4; ++e) { const float t = nx[i][v][e] - s[i]; q[i] += 4 * (lane + 64 * v) + e < K ? t * t : 0.f; }
     }
 #pragma unroll
     for (int i = 0; i < RPW; ++i) q[i] = fold_wave(q[i], Add());
@@ -226,7 +297,7 @@ __global__ __launch_bounds__(64 * NW) void k_lin(const float *hot_x, const void 
       for (int v = 0; v < VPL; ++v) {
         floatx4 y;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) y[e] = 4 * (lane + 64 * v) + e < K ? (xv[i][v][e] - s[i]) * rstd * gv[v][e] + bv[v][e] : 0.f;
+        for (int e = 0; e < 4; ++e) y[e] = 4 * (lane + 64 * v) + e < K ? (nx[i][v][e] - s[i]) * rstd * gv[v][e] + (hot_b ? bv[v][e] : 0.f) : 0.f;
         *(floatx4 *)&sm_x[w * RPW + i][4 * (lane + 64 * v)] = y;
       }
     }
@@ -239,33 +310,40 @@ __global__ __launch_bounds__(64 * NW) void k_lin(const float *hot_x, const void 
     for (int i = 0; i < RT; ++i)
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[t][i][e] = floatx4{0.f, 0.f, 0.f, 0.f};
-  for (int s = s0; s < s1; s += U) {
-    floatx4 xv[RT][U];
+  // one batch of U steps; `more`: the next one's weights (and rows) are requested before it is multiplied (a copy of the body without that
+  // for the last: where a branch decided on it, the wait for this batch's values counted on its not having been made)
+  auto batch = [&](int s, auto more_) {
+    constexpr bool more = decltype(more_)::value;
+    if (!AHEAD) load_x(xv, s);
+    floatx4 wn[NT][U], xn[RT][U];
+    if (more && AHEAD) load_x(xn, s + U);
+    if (more) load_w(wn, s + U);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int i = 0; i < RT; ++i) {
-      const RowSrc<WT> src(a, hot_x, min(r0 + i * 16 + m, R - 1), K, false);
+    for (int u = 0; u < U; ++u) {
+      if (!more && s + u >= s1) break;          // the same for the whole wave
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int k = (s + u) * 16 + 4 * g;
-        xv[i][u] = NORM ? *(const floatx4 *)&sm_x[m][min(k, XLD - 4)] : src.template at<VEC>(k, K);
-      }
-    }
-    floatx4 wn[NT][U];
-    if (s + U < s1) load_w(wn, s + U);          // the same for the whole wave
+      for (int t = 0; t < NT; ++t)
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+        for (int e = 0; e < 4; ++e) wv[t][u][e] = (s + u) * 16 + 4 * g + e < K ? wv[t][u][e] : 0.f;
 #pragma unroll
       for (int i = 0; i < RT; ++i)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
           for (int t = 0; t < NT; ++t) acc[t][i][e] = mfma_f32(wv[t][u][e], xv[i][u][e], acc[t][i][e]);
-    if (s + U < s1)
+    }
+    if (more)
 #pragma unroll
-      for (int t = 0; t < NT; ++t)
+      for (int u = 0; u < U; ++u) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) wv[t][u] = wn[t][u];
-  }
+        for (int t = 0; t < NT; ++t) wv[t][u] = wn[t][u];
+        if (AHEAD) xv[0][u] = xn[0][u];
+      }
+  };
+  int st = s0;
+  for (; st + U < s1; st += U) batch(st, std::true_type());
+  if (st < s1) batch(st, std::false_type());
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -306,12 +384,19 @@ __global__ __launch_bounds__(64 * NW) void k_lin(const float *hot_x, const void 
     if (!in) return;
     if (EPI == LIN_QKV) {
       if (!(info.x & ROW_VALID)) return;
+      // (heads of whole quads: one quad is of one section and head; divisions by a variable are chains of 30 instructions)
+      const bool quads = a.hd % 4 == 0;
+      int sec = 0, c = 0, h = 0;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         if (n + j >= N) continue;
-        const int s_in = (n + j) / a.d, sec = s_in + a.sec0, c = (n + j) - s_in * a.d, h = c / a.hd;
+        if (j == 0 || !quads) {
+          const int s_in = (n + j) / a.d;
+          sec = s_in + a.sec0; c = (n + j) - s_in * a.d; h = c / a.hd;
+        }
+        const int cj = quads ? c + j : c;
         if (sec == 0) { a.out[(size_t)r * a.ldo + n + j] = y[j]; continue; }
-        const size_t slab = ((size_t)info.y * a.H + h) * a.kv_cap * a.hd, dim = c - h * a.hd;
+        const size_t slab = ((size_t)info.y * a.H + h) * a.kv_cap * a.hd, dim = cj - h * a.hd;
         const size_t o = slab + (sec == 1 ? (size_t)info.z * a.hd + dim : dim * a.kv_cap + info.z);
         KT *cache = (KT *)(sec == 1 ? a.kc : a.vc), *low = (KT *)(sec == 1 ? a.kc_lo : a.vc_lo);
         if (sizeof(KT) == 2 && fabsf(y[j]) > 65504.f) atomicAdd(a.kv_sat, 1);   // stored saturated
@@ -325,7 +410,7 @@ __global__ __launch_bounds__(64 * NW) void k_lin(const float *hot_x, const void 
       return;
     }
     float *dst = a.out + (size_t)r * a.ldo + n + (EPI == LIN_SLICE ? blockIdx.z * a.slice_stride : 0);
-    if (EPI == LIN_RESID) y += res;
+    if constexpr (EPI == LIN_RESID) y += row_value<RSRC>(rq, rs);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       if (n + j >= N) continue;
@@ -337,12 +422,25 @@ __global__ __launch_bounds__(64 * NW) void k_lin(const float *hot_x, const void 
   }
 }
 
-template <typename WT, typename KT, int EPI, int NW, int RT, int VPL>
+template <typename WT, typename KT, int EPI, int NW, int RT, int VPL, int SRC = SRC_ROWS>
 static void launch_lin(const LinArgs &a, int n_tiles, bool vec, hipStream_t s) {
   const dim3 grid(n_tiles, (a.R + 16 * RT - 1) / (16 * RT), EPI == LIN_SLICE ? SLICES : 1);
   const int4 *info = EPI == LIN_QKV ? a.rt.kvinfo : a.rt.qinfo;
-  auto kernel = vec ? k_lin<WT, KT, EPI, NW, RT, VPL, true> : k_lin<WT, KT, EPI, NW, RT, VPL, false>;
-  hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), 0, s, a.x, a.W, a.W2, a.ng, a.nb, info, a.R, a.K, a);
+  const void *x = VPL > 0 && SRC == SRC_GATHER ? a.tok_emb : a.x;
+  const void *second = SRC == SRC_GATHER ? a.pos_emb : SRC == SRC_SLICES ? (const void *)a.pend : a.W2;
+  auto kernel = vec ? k_lin<WT, KT, EPI, NW, RT, VPL, true, SRC> : k_lin<WT, KT, EPI, NW, RT, VPL, false, SRC>;
+  hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), 0, s, x, a.W, second, a.ng, a.nb, info, a.R, a.K, a);
+}
+
+// rows from where they are (see SRC_ROWS)
+template <typename WT, typename KT, int EPI, int NW, int VPL>
+static void launch_lin_from(const LinArgs &a, int n_tiles, bool vec, hipStream_t s) {
+  constexpr bool GATHERS = EPI == LIN_RESID || EPI == LIN_QKV || EPI == LIN_STORE, ADDS = GATHERS || EPI == LIN_HEAD;
+  if constexpr (GATHERS)
+    if (a.tok_emb) return launch_lin<WT, KT, EPI, NW, 1, VPL, SRC_GATHER>(a, n_tiles, vec, s);
+  if constexpr (ADDS)
+    if (a.pend) return launch_lin<WT, KT, EPI, NW, 1, VPL, SRC_SLICES>(a, n_tiles, vec, s);
+  launch_lin<WT, KT, EPI, NW, 1, VPL>(a, n_tiles, vec, s);
 }
 
 // Wide loads where the rows allow them: K a multiple of 4 and every matrix aligned.  Waves along K: 16 steps each up
@@ -359,14 +457,25 @@ static int run_lin(const LinArgs &a, int n_tiles, hipStream_t s) {
   }
   if constexpr (EPI != LIN_RESID) {
     if (a.ng) {
-      if (a.K <= 256) launch_lin<WT, KT, EPI, 4, 1, 1>(a, n_tiles, vec, s);
-      else if (a.K <= 512) launch_lin<WT, KT, EPI, 8, 1, 2>(a, n_tiles, vec, s);
-      else launch_lin<WT, KT, EPI, 16, 1, 4>(a, n_tiles, vec, s);
+      if (a.K <= 256) launch_lin_from<WT, KT, EPI, 4, 1>(a, n_tiles, vec, s);
+      else if (a.K <= 512) launch_lin_from<WT, KT, EPI, 8, 2>(a, n_tiles, vec, s);
+      else launch_lin_from<WT, KT, EPI, 16, 4>(a, n_tiles, vec, s);
       PD_CHECK_HIP(hipGetLastError());
       return PD_OK;
     }
   }
+  // (only the rows of at most 32 are gathered or lack slices)
   const int rt = lin_row_tiles(n_tiles, a.K, a.R);
+  if constexpr (EPI == LIN_RESID) {
+    if (a.tok_emb || a.pend) {
+      PD_REQUIRE(rt == 1, PD_EINVAL, "rows put together by launches of one row tile (%d rows)", a.R);
+      if (a.K <= 256) launch_lin_from<WT, KT, EPI, 4, 0>(a, n_tiles, vec, s);
+      else if (a.K <= 1024) launch_lin_from<WT, KT, EPI, 8, 0>(a, n_tiles, vec, s);
+      else launch_lin_from<WT, KT, EPI, 16, 0>(a, n_tiles, vec, s);
+      PD_CHECK_HIP(hipGetLastError());
+      return PD_OK;
+    }
+  }
   if (rt == 4) launch_lin<WT, KT, EPI, 8, 4, 0>(a, n_tiles, vec, s);
   else if (rt == 2) launch_lin<WT, KT, EPI, 8, 2, 0>(a, n_tiles, vec, s);
   else if (a.K <= 256) launch_lin<WT, KT, EPI, 4, 1, 0>(a, n_tiles, vec, s);
@@ -455,7 +564,7 @@ __device__ __forceinline__ float exp_f32(float x) {
   return ldexpf(__builtin_amdgcn_exp2f(f), (int)n);
 }
 
-template <typename KT, int NHB, int NW, bool VEC>      // NHB: 16-dim blocks of a head (hd <= 16 NHB)
+template <typename KT, int NHB, int NW, bool VEC, bool PAIR>      // NHB: 16-dim blocks of a head (hd <= 16 NHB); PAIR: low halves
 __global__ __launch_bounds__(64 * NW) void k_attn_f32(const float *hot_qkv, const void *hot_k, const void *hot_v,
                                                       const int4 *hot_qinfo, const int32_t *hot_kv_len, uint32_t hot_hda, int kv_cap,
                                                       int H, int hot_req0, AttnF32Args a) {
@@ -490,9 +599,13 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(const float *hot_qkv, cons
   };
   load(w);
   __builtin_amdgcn_sched_barrier(0);
-  const KT *Kl = a.kc_lo ? (const KT *)a.kc_lo + base : nullptr, *Vl = a.vc_lo ? (const KT *)a.vc_lo + base : nullptr;
+  const KT *Kl = PAIR ? (const KT *)a.kc_lo + base : nullptr, *Vl = PAIR ? (const KT *)a.vc_lo + base : nullptr;
   const uint16_t *gs = a.gen_sub + (size_t)req * a.gen_stride;
   const int L8 = a.L & ~7;            // entry of key slot j >= L is j - L8
+  // tags of the lane's 4 keys: 8 aligned bytes (clamped: context keys read entry 0 and never use it)
+  uint2 tg;
+  auto load_tags = [&](int t) { tg = *(const uint2 *)(gs + min(max(t * 16 + 4 * g - L8, 0), a.gen_stride - 4)); };
+  load_tags(w);
   if (!hot_kv_len) n = a.kv_override;
   const bool valid = qa < A && (qi.x & ROW_VALID);
   const int lim = valid ? min(qi.z, n) : 0, sub = valid ? qi.y : -1;
@@ -510,17 +623,14 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(const float *hot_qkv, cons
   for (int i = 0; i < NHB; ++i) o_acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
   for (int t = w; t < tiles; t += NW) {
     const int key0 = t * 16, key = key0 + 4 * g;
-    int tag[4];
-    if (Kl) {
+    if (PAIR) {
       const size_t krow = (size_t)min(key0 + m, kv_cap - 1) * hd;
 #pragma unroll
       for (int c = 0; c < NHB; ++c) kf[c] += ld_row4<VEC>(Kl + krow, 16 * c + 4 * g, hd);
-    }
-    if (Vl)
 #pragma unroll
       for (int i = 0; i < NHB; ++i) vf[i] += ld_row4<true>(Vl + (size_t)min(16 * i + m, hd - 1) * kv_cap, key, kv_cap);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) tag[e] = gs[min(max(key + e - L8, 0), a.gen_stride - 1)];
+    }
+    const int tag[4] = {(int)(tg.x & 0xffff), (int)(tg.x >> 16), (int)(tg.y & 0xffff), (int)(tg.y >> 16)};
     floatx4 se[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) se[e] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -534,7 +644,7 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(const float *hot_qkv, cons
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int key = key0 + 4 * g + j;
-      const bool vis = key < lim || (key >= a.L && key < n && tag[j] <= sub);
+      const bool vis = (key < lim) | ((key >= a.L) & (key < n) & (tag[j] <= sub));
       s[j] = vis ? s[j] * a.scale : -INFINITY;
       mloc = fmaxf(mloc, s[j]);
     }
@@ -555,7 +665,7 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(const float *hot_qkv, cons
 #pragma unroll
       for (int i = 0; i < NHB; ++i)       // (slots past the last key hold what an earlier request left there)
         o_acc[i] = mfma_f32(key0 + 4 * g + e < n ? vf[i][e] : 0.f, p[e], o_acc[i]);
-    if (t + NW < tiles) load(t + NW);   // the same for the whole wave
+    if (t + NW < tiles) { load(t + NW); load_tags(t + NW); }   // the same for the whole wave
   }
   l_run = fold32(fold16(l_run, Add()), Add());
   if (g == 0) { sm_m[w][m] = m_run; sm_l[w][m] = l_run; }
@@ -568,7 +678,7 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(const float *hot_qkv, cons
   for (int v = 0; v < NW; ++v) M = fmaxf(M, sm_m[v][m]);
 #pragma unroll
   for (int v = 0; v < NW; ++v) {
-    f[v] = sm_m[v][m] == -INFINITY ? 0.f : exp_f32(sm_m[v][m] - M);
+    f[v] = exp_f32(sm_m[v][m] - M);     // (a wave without a key, -inf: 0; a query without one is not stored)
     l += f[v] * sm_l[v][m];
   }
   if (!valid) return;
@@ -589,10 +699,12 @@ static int attention_f32(const AttnF32Args &a, int nreq, hipStream_t s) {
   const int32_t *kv_len = a.kv_override >= 0 ? nullptr : a.kv_len;
   PD_REQUIRE(a.A < 65536, PD_EINVAL, "%d rows per request", a.A);        // (a step has at most 1024, a context pass too)
   const uint32_t hda = (uint32_t)a.hd | (uint32_t)a.A << 16;
+  constexpr bool LOW = sizeof(KT) == 2; // (only half caches have low halves)
   const bool vec = a.hd % 4 == 0;       // rows of q, keys and values then start at multiples of 16 (half: 8) bytes
 #define PD_ATTN_F32(NHB, NW)                                                                                  \
   do {                                                                                                        \
-    auto kernel = vec ? k_attn_f32<KT, NHB, NW, true> : k_attn_f32<KT, NHB, NW, false>;                       \
+    auto kernel = a.kc_lo ? (vec ? k_attn_f32<KT, NHB, NW, true, LOW> : k_attn_f32<KT, NHB, NW, false, LOW>)  \
+                          : (vec ? k_attn_f32<KT, NHB, NW, true, false> : k_attn_f32<KT, NHB, NW, false, false>); \
     hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), 0, s, a.qkv, a.kc, a.vc, a.rt.qinfo, kv_len, hda, a.kv_cap, a.H,  \
                        a.req0, a);                                                                            \
   } while (0)
