@@ -98,7 +98,8 @@ struct Max {
 struct Min { __device__ __forceinline__ int operator()(int a, int b) const { return min(a, b); } };
 // the larger of two (value, index) candidates, the lower index on ties
 __device__ __forceinline__ void keep_best(float &best, int &idx, float ov, int oi) {
-  if (ov > best || (ov == best && oi < idx)) { best = ov; idx = oi; }
+  const bool take = (ov > best) | ((ov == best) & (oi < idx));       // (no branches)
+  best = take ? ov : best; idx = take ? oi : idx;
 }
 __device__ __forceinline__ void best16(float &best, int &idx) {
   const Halves<float> v = halves16(best); const Halves<int> i = halves16(idx);

@@ -248,7 +248,9 @@ int launch_embed(pd_ctx *c, int R, hipStream_t s) {
 //           most 512 NGW values, TURN_ROWS rows per request)
 // In the middle of a run all three are one launch: a chain of dependent reads through one compute unit, where each launch of
 // its own cost its boundary and its way from and to memory again (width 768, 8 rows, 50265 words: commit, tick and norm
-// 7.0 + 3.8 + 4.6 us, together 10.0; width 2048, commit and tick 6.3 + 4.1, together 7.4).
+// 7.0 + 3.8 + 4.6 us, together 10.0; width 2048, commit and tick 6.3 + 4.1, together 7.4).  Bound by that chain, of which the reads
+// that do not depend on each other now go out together and without conditions (state, gain and bias, table rows each waited for
+// before the next: 10.9 us with it, 9.4 without, both with the norm; 7.5 and 6.2 alone).
 // Encoder-decoder form (qinfo_x != NULL): L is 0 (the decoder's own cache holds generated tokens only);
 // every row also gets an entry of a second table for the attention over the Lx encoder states, and
 // every new key slot its grid coordinate (t - 1) + (i - 1), whose difference between a query and a
@@ -279,43 +281,46 @@ __global__ __launch_bounds__(1024) void k_turn(const float *part_val, const int3
   __shared__ int s_idx[16], s_cnt[16];
   __shared__ int s_tok[NGW ? TURN_ROWS : 1], s_pos[NGW ? TURN_ROWS : 1];
   const int b = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  // Asked for ahead of their use: what the threads' subsequences hold, the request's state (four scalar reads, one after the
-  // other), then the winners of the vocabulary's groups of columns of every row, whether or not the row selects a token.
+  // Asked for ahead of their use and without conditions (a read under one is waited for where it ends), first by the arguments
+  // that arrive in registers: what the threads' subsequences hold, the first winners of the vocabulary's groups of columns,
+  // whether or not their row selects a token; then the request's state.
   const int i0 = threadIdx.x;           // subsequence of this thread in the first pass
-  int r0 = -1, fin0 = 0, f0 = -1, nt0 = 0, fed0 = 0;
-  if (i0 < S) {
-    if (COMMIT) r0 = row_of[b * S + i0];
-    fin0 = fin_of[b * S + i0];
-    nt0 = n_tok[b * S + i0];
-    if (TICK) fed0 = n_fed[b * S + i0];
-    if (COMMIT && a.force) f0 = a.force[b * S + i0];
-  }
-  int done = st.done[b], k = st.k_open[b];
-  const int t = st.step[b], ng = TICK ? st.n_gen[b] : 0;
+  const int ic = b * S + min(i0, S - 1);
+  int r0 = COMMIT ? row_of[ic] : -1, fin0 = fin_of[ic], nt0 = n_tok[ic], fed0 = TICK ? n_fed[ic] : 0;
+  // second stage of the argmax, `share` waves per row; lowest index wins ties (Eq. 4).  One wave takes 512
+  // winners in one batch of requests; beyond that all 16 waves work also when there are few rows
+  // (shares of a power of two: divisions by a variable are chains of 30 instructions)
+  const int lg = n_win <= 512 || A > 8 ? 0 : A > 4 ? 1 : A > 2 ? 2 : A > 1 ? 3 : 4, share = 1 << lg;
+  const int span = (n_win + share - 1) >> lg, t_lo = (wave & (share - 1)) * span, t_hi = min(t_lo + span, n_win);
+  float wv[8]; int wx[8];
+  auto ask_winners = [&](int q, int t0) {
+    const size_t at = (size_t)(b * A + min(q, A - 1)) * n_win;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int tt = min(t0 + 64 * u, t_hi - 1);        // clamped: a repeated candidate changes nothing
+      wv[u] = part_val[at + tt];
+      wx[u] = part_idx[at + tt];
+    }
+  };
+  if (COMMIT) ask_winners(wave >> lg, t_lo + lane);
+  int zero = 0;                         // (as lanes' reads: four scalar ones are waited for one by one)
+  asm volatile("" : "+v"(zero));
+  const int done_v = st.done[b + zero], k_v = st.k_open[b + zero], t_v = st.step[b + zero], ng_v = TICK ? st.n_gen[b + zero] : 0;
+  int f0 = -1;
+  if (COMMIT && a.force) f0 = a.force[ic];
+  __builtin_amdgcn_sched_barrier(0);
   int new_tok = 0;                      // token this thread's subsequence was given in this step
   bool given = false;
+  float4 gv[NGW ? NGW : 1][2], bv[NGW ? NGW : 1][2];         // of the first norm: asked for when the winners' registers are free
   if (COMMIT) {
-    // stage 1: second stage of the argmax, `share` waves per row; lowest index wins ties (Eq. 4).  One wave takes 512
-    // winners in one batch of requests; beyond that all 16 waves work also when there are few rows
-    // (shares of a power of two: divisions by a variable are chains of 30 instructions)
-    const int lg = n_win <= 512 || A > 8 ? 0 : A > 4 ? 1 : A > 2 ? 2 : A > 1 ? 3 : 4, share = 1 << lg;
-    const int span = (n_win + share - 1) >> lg, t_lo = (wave & (share - 1)) * span, t_hi = min(t_lo + span, n_win);
+    // stage 1
     for (int q = wave >> lg; q < A; q += 16 >> lg) {
-      const int r = b * A + q;
       int bi = 0x7fffffff;
-      const float *pv = part_val + (size_t)r * n_win;
-      const int32_t *pi = part_idx + (size_t)r * n_win;
       float best = -INFINITY;
       for (int t0 = t_lo + lane; t0 < t_hi; t0 += 64 * 8) {
-        float v[8]; int ix[8];
+        if (q != wave >> lg || t0 != t_lo + lane) ask_winners(q, t0);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          int tt = min(t0 + 64 * u, t_hi - 1);          // clamped: a repeated candidate changes nothing
-          v[u] = pv[tt];
-          ix[u] = pi[tt];
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) keep_best(best, bi, v[u], ix[u]);
+        for (int u = 0; u < 8; ++u) keep_best(best, bi, wv[u], wx[u]);
       }
       best_wave(best, bi);
       if (lane == 0) {
@@ -323,6 +328,22 @@ __global__ __launch_bounds__(1024) void k_turn(const float *part_val, const int3
         else { s_best[wave] = best; s_idx[wave] = bi; }
       }
     }
+  }
+  int done = __builtin_amdgcn_readfirstlane(done_v), k = __builtin_amdgcn_readfirstlane(k_v);
+  const int t = __builtin_amdgcn_readfirstlane(t_v), ng = __builtin_amdgcn_readfirstlane(ng_v);
+  if constexpr (NGW > 0) {
+#pragma unroll
+    for (int n = 0; n < NGW; ++n) {
+      const int c = min((lane + 64 * n) * 8, a.d - 8);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        gv[n][h] = *(const float4 *)(a.g + c + 4 * h);
+        bv[n][h] = *(const float4 *)((a.kind == 0 && a.b ? a.b : a.g) + c + 4 * h);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if (COMMIT) {
     __syncthreads();
     if (share > 1) {                    // the same for the whole block: one row per group of waves
       const int q = threadIdx.x;
@@ -442,40 +463,31 @@ __global__ __launch_bounds__(1024) void k_turn(const float *part_val, const int3
   if constexpr (NGW > 0) {
     // A wave per row; rows without a token are zero; what lies behind the last request's rows is never stored by any projection
     const int d = a.d;
-    float gv[NGW][8], bv[NGW][8];
-#pragma unroll
-    for (int n = 0; n < NGW; ++n) {
-      const int c = (lane + 64 * n) * 8;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const float4 tg = c < d ? *(const float4 *)(a.g + c + 4 * h) : make_float4(0.f, 0.f, 0.f, 0.f);
-        const float4 tb = c < d && a.kind == 0 && a.b ? *(const float4 *)(a.b + c + 4 * h) : make_float4(0.f, 0.f, 0.f, 0.f);
-        gv[n][4 * h] = tg.x; gv[n][4 * h + 1] = tg.y; gv[n][4 * h + 2] = tg.z; gv[n][4 * h + 3] = tg.w;
-        bv[n][4 * h] = tb.x; bv[n][4 * h + 1] = tb.y; bv[n][4 * h + 2] = tb.z; bv[n][4 * h + 3] = tb.w;
-      }
-    }
     __syncthreads();                    // tokens and positions of the rows
     for (int q = wave; q < A; q += 16) {
       const int r = b * A + q;
       if (r >= a.row_end) break;
       const bool has = q < rows;        // the same for the whole wave
       const bf16_t *te = a.tok_emb + (has ? (size_t)s_tok[q] * d : 0);
-      const bf16_t *pe = a.pos_emb ? a.pos_emb + (has ? (size_t)s_pos[q] * d : 0) : nullptr;
+      const bf16_t *pe = a.pos_emb ? a.pos_emb + (has ? (size_t)s_pos[q] * d : 0) : te;      // (no positions: read again, not added)
       Frag et[NGW], ep[NGW];
 #pragma unroll
       for (int n = 0; n < NGW; ++n) {
-        const int c = (lane + 64 * n) * 8;
-        et[n].u = has && c < d ? *(const uint4 *)(te + c) : make_uint4(0, 0, 0, 0);
-        ep[n].u = has && c < d && pe ? *(const uint4 *)(pe + c) : make_uint4(0, 0, 0, 0);
+        const int c = min((lane + 64 * n) * 8, d - 8);
+        et[n].u = *(const uint4 *)(te + c);
+        ep[n].u = *(const uint4 *)(pe + c);
       }
+      __builtin_amdgcn_sched_barrier(0);
       float v[NGW][8], s1 = 0.f, s2 = 0.f;
 #pragma unroll
-      for (int n = 0; n < NGW; ++n)
+      for (int n = 0; n < NGW; ++n) {
+        const bool in = has && (lane + 64 * n) * 8 < d;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          v[n][e] = bf16_to_f32(et[n].h[e]) + bf16_to_f32(ep[n].h[e]);
+          v[n][e] = in ? bf16_to_f32(et[n].h[e]) + (a.pos_emb ? bf16_to_f32(ep[n].h[e]) : 0.f) : 0.f;
           s1 += v[n][e]; s2 += v[n][e] * v[n][e];
         }
+      }
       s1 = fold_wave(s1, Add());
       s2 = fold_wave(s2, Add());
       const float mean = a.kind == 0 ? s1 / d : 0.f;
@@ -487,7 +499,8 @@ __global__ __launch_bounds__(1024) void k_turn(const float *part_val, const int3
         float y[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          y[e] = has ? (v[n][e] - mean) * rstd * gv[n][e] + bv[n][e] : 0.f;
+          const float ge = ((const float *)gv[n])[e], be = a.kind == 0 && a.b ? ((const float *)bv[n])[e] : 0.f;
+          y[e] = has ? (v[n][e] - mean) * rstd * ge + be : 0.f;
         }
         *(float4 *)(a.x + (size_t)r * d + c) = make_float4(v[n][0], v[n][1], v[n][2], v[n][3]);
         *(float4 *)(a.x + (size_t)r * d + c + 4) = make_float4(v[n][4], v[n][5], v[n][6], v[n][7]);
@@ -499,7 +512,7 @@ __global__ __launch_bounds__(1024) void k_turn(const float *part_val, const int3
 
 // Whether a step's tick also gathers and normalises its rows: one compute unit does that for all rows of a request, and a
 // lane holds at most 16 values of a row (32 do not fit the registers of 16 waves: width 2048, 8 rows 17.8 us, commit and tick
-// 7.4 with the norm kernel's 4.0 behind them; two waves per row are no faster than one, width 768 11.0 against 10.0).
+// 7.4 with the norm kernel's 4.0 behind them; two waves per row are no faster than one, width 768 11.0 against 10.0; all figures before the reads went out together).
 bool turn_embeds(const pd_ctx *c) { return c->impl == 1 && c->cfg.d_model <= 1024 && c->A <= TURN_ROWS; }
 
 int launch_turn(pd_ctx *c, bool commit, bool tick, bool packed, const int32_t *force, int32_t *out_tok, int32_t *out_done,
