@@ -270,7 +270,9 @@ int pd_reset_decode(pd_ctx *ctx, void *hip_stream);
  *                        full capacity (every weight, every request's keys and values) exceed the 256 MB
  *                        last-level cache, so that nothing of them would be found there a step later (cfg4:
  *                        1.37 -> 1.31 ms per step, cfg5 6.55 -> 6.09); 0 for models the cache serves step after
- *                        step (cfg2: 0.187 ms, 0.202 with the hint).  Same results bit for bit.
+ *                        step (cfg2: 0.187 ms, 0.202 with the hint).  Chosen at creation, the first 110 MB of the
+ *                        packed weights keep ordinary loads, and their place in that cache; set here, 1 is for all.
+ *                        Same results bit for bit.
  *                        pd_get_info(PD_INFO_STREAM_LOADS) reports the setting.
  *   PD_OPT_CONTEXT_ATTN  attention kernel of the context pass (bf16 path, head_dim 64 or 128, layers without
  *                        pair caches): 1 (default) the kernel with 32 queries per block where a chunk makes

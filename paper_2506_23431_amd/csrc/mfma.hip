@@ -8,13 +8,18 @@ bf16_t *mfma_lo(pd_ctx *c, void *buf, size_t cols) {
   return c->packed ? (bf16_t *)buf + 64 : (bf16_t *)buf + (size_t)c->R_pad * cols;
 }
 
+// a launch's weights, and whether it loads them with the hint
+static void set_weights(pd_ctx *c, GemmArgs &a, const bf16_t *W) {
+  a.W = W;
+  a.stream_w = c->stream_loads && W >= c->kept_end;
+}
+
 // fields every projection of a launch sequence shares
 void mfma_gemm_base(pd_ctx *c, GemmArgs &a, int R) {
   const pd_config &g = c->cfg;
   memset(&a, 0, sizeof(a));
   a.R = R; a.rt = c->rows; a.d = g.d_model; a.H = g.n_head; a.hd = g.head_dim; a.kv_cap = c->kv_cap;
   a.packed = c->packed;
-  a.stream_w = c->stream_loads;
 }
 
 // QKV-style projection of the normalised rows in c->xn: queries to c->q, keys and values into the given
@@ -45,7 +50,8 @@ int mfma_qkv(pd_ctx *c, GemmArgs &a, const bf16_t *W, int n_tiles, int sec0, voi
              void *vc_lo, int R, hipStream_t s, const float *c1, const float *c2) {
   const pd_config &g = c->cfg;
   const int d = g.d_model;
-  a.W = W; a.xn = (const bf16_t *)c->xn; a.xn_lo = mfma_lo(c, c->xn, d); a.K = d;
+  set_weights(c, a, W);
+  a.xn = (const bf16_t *)c->xn; a.xn_lo = mfma_lo(c, c->xn, d); a.K = d;
   a.n_tiles = n_tiles; a.sec0 = sec0; a.out_bf = (bf16_t *)c->q; a.out_lo = mfma_lo(c, c->q, d);
   a.kc = (f16_t *)kc; a.vc = (f16_t *)vc; a.rope_cs = c->rope_cs;
   a.kc_lo = (f16_t *)kc_lo; a.vc_lo = (f16_t *)vc_lo; a.kv_sat = c->kv_sat;
@@ -63,7 +69,8 @@ int mfma_qkv(pd_ctx *c, GemmArgs &a, const bf16_t *W, int n_tiles, int sec0, voi
 // that the next norm kernel sums)
 int mfma_out(pd_ctx *c, GemmArgs &a, const bf16_t *p_wo, int R, hipStream_t s, const float *next_gain) {
   const int d = c->cfg.d_model;
-  a.W = p_wo; a.xn = (const bf16_t *)c->att; a.xn_lo = mfma_lo(c, c->att, d); a.K = d; a.n_tiles = d / 16; a.x = c->ypart; a.ld = d;
+  set_weights(c, a, p_wo);
+  a.xn = (const bf16_t *)c->att; a.xn_lo = mfma_lo(c, c->att, d); a.K = d; a.n_tiles = d / 16; a.x = c->ypart; a.ld = d;
   a.part_stride = (size_t)c->R_pad * d; a.max_parts = 4; a.parts_out = &c->pend_parts;
   if (next_gain && mfma_can_fuse_norm(c, R)) {
     a.x_res = c->x; a.gain = next_gain; a.stats_out = c->nstats;
@@ -79,7 +86,8 @@ int mfma_out_ffn(pd_ctx *c, GemmArgs &a, const bf16_t *p_wo, const LayerPtrs &lw
                  const float *next_gain) {
   const pd_config &g = c->cfg;
   int d = g.d_model, ff = g.d_ff, rc;
-  a.W = p_wo; a.xn = (const bf16_t *)c->att; a.xn_lo = mfma_lo(c, c->att, d); a.K = d; a.n_tiles = d / 16; a.x = c->ypart; a.ld = d;
+  set_weights(c, a, p_wo);
+  a.xn = (const bf16_t *)c->att; a.xn_lo = mfma_lo(c, c->att, d); a.K = d; a.n_tiles = d / 16; a.x = c->ypart; a.ld = d;
   a.part_stride = (size_t)c->R_pad * d; a.max_parts = 4; a.parts_out = &c->pend_parts;
   // At most 16 rows: the projection is not cut along K over blocks, so its epilogue holds the final
   // x + y.  It writes x, gain * x as the activation fragments of the FFN, and per-tile row sums; the
@@ -98,7 +106,8 @@ int mfma_out_ffn(pd_ctx *c, GemmArgs &a, const bf16_t *p_wo, const LayerPtrs &lw
   }
   // FFN
   a.xn = (const bf16_t *)c->xn; a.xn_lo = mfma_lo(c, c->xn, d); a.K = d;
-  a.out_bf = (bf16_t *)c->hb; a.out_lo = mfma_lo(c, c->hb, ff); a.ld = ff; a.W = lw.p_w1;
+  a.out_bf = (bf16_t *)c->hb; a.out_lo = mfma_lo(c, c->hb, ff); a.ld = ff;
+  set_weights(c, a, lw.p_w1);
   if (g.ffn_kind == 1) {
     a.n_tiles = 2 * ff / 16;
     rc = mfma_gemm(EPI_SWIGLU, a, R, s);
@@ -108,7 +117,8 @@ int mfma_out_ffn(pd_ctx *c, GemmArgs &a, const bf16_t *p_wo, const LayerPtrs &lw
   }
   if (rc) return rc;
   a.stats_in = nullptr;
-  a.W = lw.p_w2; a.xn = (const bf16_t *)c->hb; a.xn_lo = mfma_lo(c, c->hb, ff); a.K = ff; a.n_tiles = d / 16; a.x = c->ypart; a.ld = d;
+  set_weights(c, a, lw.p_w2);
+  a.xn = (const bf16_t *)c->hb; a.xn_lo = mfma_lo(c, c->hb, ff); a.K = ff; a.n_tiles = d / 16; a.x = c->ypart; a.ld = d;
   if (next_gain && ffn2_prepares_norm(c, R)) {
     // completes x itself and leaves gain * x with the row sums for the next layer's QKV projection
     a.x_res = c->x; a.gain = next_gain; a.stats_out = c->nstats;
@@ -149,8 +159,8 @@ int mfma_head(pd_ctx *c, int R, float *logits, hipStream_t s, int tf_A, int tf_c
   if ((rc = mfma_norm(c, c->fng, c->fnb, R, s))) return rc;
   GemmArgs a;
   memset(&a, 0, sizeof(a));
-  a.R = R; a.rt = c->rows; a.W = c->p_lm_head; a.xn = (const bf16_t *)c->xn; a.packed = c->packed;
-  a.stream_w = c->stream_loads;
+  a.R = R; a.rt = c->rows; a.xn = (const bf16_t *)c->xn; a.packed = c->packed;
+  set_weights(c, a, c->p_lm_head);
   a.xn_lo = mfma_lo(c, c->xn, g.d_model); a.K = g.d_model;
   a.n_tiles = c->vocab_pad / 16; a.V = g.vocab;
   a.logits = logits; a.logits_A = tf_A; a.logits_cap = tf_A > 0 ? tf_cap : c->S; a.ld_logits = g.vocab;
