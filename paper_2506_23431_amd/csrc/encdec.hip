@@ -101,7 +101,7 @@ int encdec_encode(pd_ctx *c, int b, hipStream_t s) {
   c->packed = false;
   c->embed_pending = true;
   c->pend_parts = 0;
-  c->norm_fused = false;
+  c->norm_fused = c->norm_halves = false;
   AttnMode am;
   memset(&am, 0, sizeof(am));
   am.L = n; am.scale = 1.f;

@@ -3,6 +3,7 @@
 #include "mfma_common.h"
 
 #include <algorithm>
+#include <type_traits>
 
 #ifndef PD_GEMM_EPI   // ---- common part: weight packing, norm kernel -------------------------------
 
@@ -722,12 +723,12 @@ static GemmHot gemm_hot(const GemmArgs &a) {
   constexpr bool out = EPI == EPI_RESID_NORM;
   return GemmHot{a.W, a.xn, out ? (const void *)a.x_res : a.stats_in, out ? a.gain : a.c1, a.rt.kvinfo,
                  out ? gemm_words_rows(a.xn_lo ? a.xn_lo - a.xn : 0, a.K, a.k_share, a.n_tiles, a.R)
-                     : gemm_words(a.xn_lo ? a.xn_lo - a.xn : 0, a.K, a.k_share, a.n_tiles, a.c2 != nullptr)};
+                     : gemm_words(a.xn_lo ? a.xn_lo - a.xn : 0, a.K, a.k_share, a.n_tiles, a.c2 != nullptr, a.stats_tiles > a.K / 16)};
 }
 template <int EPI, typename Kernel>
 static int launch_gemm_kernel(Kernel kernel, dim3 grid, int threads, GemmArgs a, hipStream_t s) {
   PD_REQUIRE(a.K / 32 <= WORDS_K_TILES, PD_EINVAL, "%d inner values", a.K);
-  PD_REQUIRE(!a.stats_in || (a.stats_tiles == a.K / 16 && (!a.c2 || a.c2 == a.c1 + (size_t)a.n_tiles * 16)), PD_EINVAL,
+  PD_REQUIRE(!a.stats_in || ((a.stats_tiles == a.K / 16 || a.stats_tiles == a.K / 8) && (!a.c2 || a.c2 == a.c1 + (size_t)a.n_tiles * 16)), PD_EINVAL,
              "a norm is finished over the whole rows, with c2 behind c1");
   PD_REQUIRE(EPI != EPI_RESID_NORM || (a.R <= 128 && a.n_tiles < 65536), PD_EINVAL, "%d rows of %d values cannot prepare a norm",
              a.R, a.n_tiles * 16);
@@ -783,8 +784,9 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(PD_GEMM_HOT_PARAMS, GemmAr
   __shared__ float2 sm_stat[FUSED_IN ? NW_K : 1][16];
   float4 pre_s[PS];
   const bool fused_norm = FUSED_IN && hot_a != nullptr;               // the same for the whole launch
+  const int npair = OUT ? 0 : KT << words_half_sums(hot_n);           // pairs of row sums
   NormPre pre_n;
-  if (fused_norm) stats_request((const float2 *)hot_a, KT, lane, wk, NW_K, pre_s, rz * 16);
+  if (fused_norm) stats_request((const float2 *)hot_a, npair, lane, wk, NW_K, pre_s, rz * 16);
   if (fused_norm && wk < NT) {      // wave w < NT finishes tile nt0 + w
     const float *c1 = (const float *)hot_b + min(nt0 + wk, n_tiles - 1) * 16 + 4 * (lane >> 4);
     pre_n.c1 = *(const float4 *)c1;
@@ -833,7 +835,7 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(PD_GEMM_HOT_PARAMS, GemmAr
 #pragma unroll
       for (int i = 0; i < RT; ++i) red[((wk * NT + t) * RT + i) * 64 + lane] = acc[t][i];
     if (fused_norm) {
-      float2 sp = stats_partial((const float2 *)hot_a, KT, lane, wk, NW_K, pre_s, rz * 16);
+      float2 sp = stats_partial((const float2 *)hot_a, npair, lane, wk, NW_K, pre_s, rz * 16);
       if (lane < 16) sm_stat[wk][lane] = sp;
     }
     __syncthreads();
@@ -858,7 +860,7 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(PD_GEMM_HOT_PARAMS, GemmAr
     if constexpr (EPI == EPI_LM) store_winners<RT, (NT < NW_K ? NT : NW_K)>(a, win, wk, lane, rz * 16);
   } else {
     float2 nrm[RT];
-    if (fused_norm) nrm[0] = stats_finish(a, stats_partial((const float2 *)hot_a, KT, lane, 0, 1, pre_s, rz * 16));
+    if (fused_norm) nrm[0] = stats_finish(a, stats_partial((const float2 *)hot_a, npair, lane, 0, 1, pre_s, rz * 16));
 #pragma unroll
     for (int t = 0; t < NT; ++t)
       if (nt0 + t < n_tiles)
@@ -867,6 +869,98 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(PD_GEMM_HOT_PARAMS, GemmAr
     if constexpr (EPI == EPI_LM) store_winners<RT, 1>(a, win, 0, lane, rz * 16);
   }
 }
+
+#if PD_GEMM_EPI == 6 && !defined(PD_GEMM_ROWS)     // EPI_RESID_NORM
+// The same product for a projection that completes at most 16 rows and prepares the next norm, which is not cut along K over
+// blocks: a block takes half of a column tile, 8 columns, so that twice as many compute units draw its weights.  One request
+// brings the 8 columns of two k-tiles (lanes m < 8 of the first, the others of the second: the fragments' granules
+// half a line at a time), and the one register pair is multiplied with the activations of either k-tile: output rows 0-7 of the
+// first product and 8-15 of the second are sums to keep, the other halves meet the wrong k-tile and are dropped.  As many
+// multiplies as with whole tiles, half the weights per compute unit, the same activations.  Row sums are left per 8 columns.
+// Bound by what a compute unit draws, twice as many activations as weights (width 2048, 8192 inner values from the caches 7.8 us,
+// cut along K 7.0 with 3.3 for the norm kernel behind it; from memory 10.9 against 7.4 + 3.2: see ffn2_handover).
+template <int NW, bool PACK, bool SW>
+__global__ __launch_bounds__(64 * NW) void k_gemm_half(PD_GEMM_HOT_PARAMS, GemmArgs a) {
+  __shared__ floatx4 red[NW][32];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+  const int tile = blockIdx.x >> 1, half = blockIdx.x & 1;
+  const int KT = words_k_tiles(hot_k), share = words_k_tiles(hot_share), n_tiles = words_tiles_rows(hot_n);      // (KT, share even)
+  const int kt0 = min(w * share, KT), kt1 = min(kt0 + share, KT);
+  const uint4 *wp = (const uint4 *)hot_w + ((size_t)tile * KT + (m >> 3)) * 64 + g * 16 + half * 8 + (m & 7);
+  const uint4 *xp = (const uint4 *)hot_x + lane, *xl = PACK ? nullptr : xp + words_granules(hot_lo);
+  const int n0 = tile * 16 + half * 8 + 4 * (g & 1);
+  ResidPre pre;
+  if (w == 0) {                         // (rows beyond the last read it and are masked where the value is used)
+    pre.g = *(const float4 *)((const float *)hot_b + n0);
+    pre.x = *(const float4 *)((const float *)hot_a + (size_t)min(m, words_last_row(hot_n)) * (n_tiles * 16) + n0);
+  }
+  floatx4 acc[2][PACK ? 1 : 2];         // k-tiles of either parity; high and low parts
+#pragma unroll
+  for (int p = 0; p < 2; ++p) acc[p][0] = acc[p][PACK ? 0 : 1] = floatx4{0.f, 0.f, 0.f, 0.f};
+  auto chunk = [&](int kt, auto u_) {
+    constexpr int U = decltype(u_)::value;
+    Frag wa[U / 2], xh[U], xo[PACK ? 1 : U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      xh[u].u = xp[(size_t)(kt + u) * 64];
+      if (!PACK) xo[u].u = xl[(size_t)(kt + u) * 64];
+    }
+#pragma unroll
+    for (int u = 0; u < U / 2; ++u) wa[u].v = ld_w<SW>(&wp[(size_t)(kt + 2 * u) * 64]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      acc[u & 1][0] = mfma16(wa[u / 2], xh[u], acc[u & 1][0]);
+      if (!PACK) acc[u & 1][PACK ? 0 : 1] = mfma16(wa[u / 2], xo[u], acc[u & 1][PACK ? 0 : 1]);
+    }
+  };
+  int kt = kt0;
+  constexpr int U = PACK ? 12 : 6;      // (16 waves leave 128 registers)
+  for (; kt + U <= kt1; kt += U) chunk(kt, std::integral_constant<int, U>());
+  if (PACK && kt + 8 <= kt1) { chunk(kt, std::integral_constant<int, 8>()); kt += 8; }
+  if (PACK && kt + 6 <= kt1) { chunk(kt, std::integral_constant<int, 6>()); kt += 6; }
+  if (kt + 4 <= kt1) { chunk(kt, std::integral_constant<int, 4>()); kt += 4; }
+  if (kt < kt1) chunk(kt, std::integral_constant<int, 2>());
+  floatx4 y;                            // lanes 0-31: columns 4 g .. + 3 of row m
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    float first = acc[0][0][j], second = acc[1][0][j];
+    if (!PACK) { first += acc[0][PACK ? 0 : 1][j]; second += acc[1][PACK ? 0 : 1][j]; }
+    y[j] = first + halves32(second).hi;
+    if (PACK) y[j] += rotate16<8>(y[j]);              // rows 8-15 hold the products with the low parts of 0-7
+  }
+  if (lane < 32) red[w][lane] = y;
+  __syncthreads();
+  if (w != 0) return;
+  y = red[0][lane & 31];
+#pragma unroll
+  for (int v = 1; v < NW; ++v) y += red[v][lane & 31];
+  const bool in = m < a.R && lane < 32;
+  float s1 = 0.f, s2 = 0.f;
+  if (in) {
+    const float x[4] = {pre.x.x + y[0], pre.x.y + y[1], pre.x.z + y[2], pre.x.w + y[3]};
+    *(float4 *)(a.x_res + (size_t)m * a.ld + n0) = make_float4(x[0], x[1], x[2], x[3]);
+    const float z[4] = {pre.g.x * x[0], pre.g.y * x[1], pre.g.z * x[2], pre.g.w * x[3]};
+    store4_split(a.out_bf, a.out_lo, act_off(m, n0, a.ld), z);
+    s1 = (x[0] + x[1]) + (x[2] + x[3]);
+    s2 = (x[0] * x[0] + x[1] * x[1]) + (x[2] * x[2] + x[3] * x[3]);
+  }
+  s1 = fold16(s1, Add());
+  s2 = fold16(s2, Add());
+  if (g == 0) a.stats_out[(size_t)m * (2 * a.n_tiles) + blockIdx.x] = make_float2(s1, s2);
+}
+
+template <int NW>
+static int launch_gemm_half(GemmArgs a, hipStream_t s) {
+  PD_REQUIRE(a.R <= 16 && a.K % 64 == 0, PD_EINVAL, "%d rows of %d inner values in halves of column tiles", a.R, a.K);
+  a.k_share = (a.K / 64 + NW - 1) / NW * 2;
+  const dim3 grid(2 * a.n_tiles);
+#define PD_HALF(P) (a.stream_w ? launch_gemm_kernel<EPI_RESID_NORM>(k_gemm_half<NW, P, true>, grid, 64 * NW, a, s)    \
+                               : launch_gemm_kernel<EPI_RESID_NORM>(k_gemm_half<NW, P, false>, grid, 64 * NW, a, s))
+  return a.packed ? PD_HALF(true) : PD_HALF(false);
+#undef PD_HALF
+}
+#endif
 
 // ---------------------------------------------------------------------------
 // launch
@@ -1059,6 +1153,9 @@ static int launch_gemm_split(const GemmArgs &a, int rows, hipStream_t s) {
 
 template <int EPI>
 static int launch_gemm(const GemmArgs &a, int rows, hipStream_t s) {
+#if PD_GEMM_EPI == 6
+  if (a.half_tiles) return launch_gemm_half<16>(a, s);
+#endif
   if (EPI == EPI_RESID_NORM || a.stats_in)
     PD_REQUIRE(rows <= 128 && a.R <= 128, PD_EINVAL,
                "projections that prepare or finish a norm take at most 128 rows (%d)", rows);

@@ -67,10 +67,12 @@ inline bool attn_halves(const AttnShape &shape, int units, bool decode, bool pai
 struct GemmWords {
   uint32_t lo;          // way from the activations to their low parts, in units of 64 values
   uint32_t k, share;    // k-tiles, and those of a wave (or of a block): 24 bits
-  uint32_t n;           // column tiles | c2 follows c1 (bit 31); of a projection that prepares a norm: tiles | last row << 16
+  uint32_t n;           // column tiles | c2 follows c1 (bit 31) | row sums of 8 columns (bit 30); of a projection that prepares a
+                        // norm: tiles | last row << 16
 };
-constexpr GemmWords gemm_words(int64_t lo_values, int K, int k_share, int n_tiles, bool c2) {
-  return GemmWords{(uint32_t)(lo_values / 64), (uint32_t)(K / 32), (uint32_t)k_share, (uint32_t)n_tiles | (c2 ? 1u << 31 : 0u)};
+constexpr GemmWords gemm_words(int64_t lo_values, int K, int k_share, int n_tiles, bool c2, bool half_sums = false) {
+  return GemmWords{(uint32_t)(lo_values / 64), (uint32_t)(K / 32), (uint32_t)k_share,
+                   (uint32_t)n_tiles | (c2 ? 1u << 31 : 0u) | (half_sums ? 1u << 30 : 0u)};
 }
 constexpr GemmWords gemm_words_rows(int64_t lo_values, int K, int k_share, int n_tiles, int rows) {
   return GemmWords{(uint32_t)(lo_values / 64), (uint32_t)(K / 32), (uint32_t)k_share,
@@ -82,7 +84,8 @@ constexpr GemmWords gemm_words_rows(int64_t lo_values, int K, int k_share, int n
 constexpr int WORDS_K_TILES = 0xffffff;
 constexpr int words_k_tiles(uint32_t k) { return (int)(k & WORDS_K_TILES); }
 constexpr size_t words_granules(uint32_t lo) { return (size_t)lo * 8; }      // in 16-byte granules of 8 values
-constexpr int words_tiles(uint32_t n) { return (int)(n & 0x7fffffffu); }
+constexpr int words_tiles(uint32_t n) { return (int)(n & 0x3fffffffu); }
+constexpr int words_half_sums(uint32_t n) { return (int)(n >> 30 & 1u); }
 constexpr bool words_c2(uint32_t n) { return n >> 31; }
 constexpr int words_tiles_rows(uint32_t n) { return (int)(n & 0xffffu); }
 constexpr int words_last_row(uint32_t n) { return (int)(n >> 16); }
@@ -92,6 +95,26 @@ constexpr int words_last_row(uint32_t n) { return (int)(n >> 16); }
 constexpr uint32_t heads_rows(int H, int A) { return (uint32_t)(H - 1) | (uint32_t)A << 8; }
 constexpr int word_heads(uint32_t w) { return (int)(w & 0xff) + 1; }
 constexpr int word_rows(uint32_t w) { return (int)(w >> 8); }
+
+// ---------------------------------------------------------------------------
+// Steps of at most 16 rows: whether the second FFN projection prepares the next layer's first norm.
+// ---------------------------------------------------------------------------
+// It has to give up its cut along K over blocks for this, which leaves one block per 16 output columns, or per 8 in halves of
+// tiles (k_gemm_half, which takes rows with low parts and inner values in pairs of k-tiles).  While a wave of 16 holds at most 8
+// k-tiles (d_ff 4096) whole tiles cost less than the norm kernel (768 / 3072, whole steps: 174.6 against 184.1 us; 1024 / 4096
+// 273 against 289; 512 / 1376 with rotary positions 186 against 204; encoder-decoder 1024 / 4096 22.5 against 22.9 ms per
+// example), also where the 5 or 7 k-tiles of a wave take two batches of requests; halves gain no more there (us per step, whole /
+// halves: width 512 181.3 / 182.3, 768 161.7 / 163.4, 1024 161.0 / 165.1).  Beyond width 1024 whole tiles leave too few blocks and
+// halves are the better: us per step with the norm kernel / whole tiles / halves, 8 rows, weights in the last-level cache:
+// width 1280, d_ff 3456 gated 208.8 / 193.9 / 193.7, 5120 210.8 / 196.2 / 194.5, 1536, 6144 146.4 / 139.3 / 135.6 (16 rows 161.5 /
+// 156.2 / 155.3), 2048, 5504 gated 176.3 / 170.5 / 168.4; from memory, 12 layers: 1536, 6144 391.2 / 395.3 / 386.5, 2048, 5504
+// 479.6 / 481.9 / 474.0.  At 2048, 8192 they gain from the cache (171.3 / 167.7 / 165.3) and lose from memory (1152.6 / 1195.7 /
+// 1170.8): a block's activations, 32 bytes per inner value, outweigh the launch saved.
+enum NormHandover { HANDOVER_NONE = 0, HANDOVER_WHOLE = 1, HANDOVER_HALVES = 2 };
+inline NormHandover ffn2_handover(int d_model, int d_ff, bool low_parts, bool on_request) {
+  if (d_model > 1024 && d_model <= 2048 && d_ff <= 6144 && d_ff % 64 == 0 && low_parts) return HANDOVER_HALVES;
+  return (d_model <= 1024 && d_ff <= 4096) || on_request ? HANDOVER_WHOLE : HANDOVER_NONE;
+}
 
 // ---------------------------------------------------------------------------
 // fp32 projections: row tiles of 16 rows per block.

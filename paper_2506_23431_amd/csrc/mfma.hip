@@ -34,18 +34,6 @@ bool mfma_can_fuse_norm(pd_ctx *c, int R) {
   const int d = c->cfg.d_model;
   return R <= 16 || mfma_gemm_row_tile_blocks(d / 16, d, R, 1);
 }
-// The second FFN projection has to give up its cut along K over blocks for this, which leaves one block
-// per 16 output columns.  While a wave of its 16 holds at most 8 k-tiles (d_ff 4096) that costs less than the norm kernel
-// (768 / 3072, whole steps: 174.6 against 184.1 us; 1024 / 4096 273 against 289; 512 / 1376 with rotary positions 186
-// against 204; encoder-decoder 1024 / 4096 22.5 against 22.9 ms per example), also where the 5 or 7 k-tiles of a wave
-// take two batches of requests; beyond it does not (2048 / 8192, 16 k-tiles per wave: 82.6 against 81.1 ms for 64
-// steps) and happens only on request (value 2 of the option).  Width 1024 is as far as the rule has been set by whole
-// workloads, not where the gain ends: 4 layers of width 1280-2048 with d_ff 1024-3072 take 5-8 % less per step on request,
-// width 2048 with d_ff 4096 1-2 %.
-static bool ffn2_prepares_norm(pd_ctx *c, int R) {
-  return R <= 16 && mfma_can_fuse_norm(c, R) && (c->opt_fuse_norm == 2 || (c->cfg.d_ff <= 4096 && c->cfg.d_model <= 1024));
-}
-
 int mfma_qkv(pd_ctx *c, GemmArgs &a, const bf16_t *W, int n_tiles, int sec0, void *kc, void *vc, void *kc_lo,
              void *vc_lo, int R, hipStream_t s, const float *c1, const float *c2) {
   const pd_config &g = c->cfg;
@@ -56,12 +44,12 @@ int mfma_qkv(pd_ctx *c, GemmArgs &a, const bf16_t *W, int n_tiles, int sec0, voi
   a.kc = (f16_t *)kc; a.vc = (f16_t *)vc; a.rope_cs = c->rope_cs;
   a.kc_lo = (f16_t *)kc_lo; a.vc_lo = (f16_t *)vc_lo; a.kv_sat = c->kv_sat;
   if (c1) {
-    a.stats_in = c->nstats; a.stats_tiles = d / 16; a.c1 = c1; a.c2 = g.norm_kind == 0 ? c2 : nullptr;
+    a.stats_in = c->nstats; a.stats_tiles = c->norm_halves ? d / 8 : d / 16; a.c1 = c1; a.c2 = g.norm_kind == 0 ? c2 : nullptr;
     a.norm_kind = g.norm_kind; a.norm_d = d; a.norm_eps = g.norm_eps;
   }
   const int rc = mfma_gemm(g.pos_kind == 1 ? EPI_QKV_ROPE : EPI_QKV, a, R, s);
   a.stats_in = nullptr;
-  if (c1) c->norm_fused = false;
+  if (c1) c->norm_fused = c->norm_halves = false;
   return rc;
 }
 
@@ -75,7 +63,7 @@ int mfma_out(pd_ctx *c, GemmArgs &a, const bf16_t *p_wo, int R, hipStream_t s, c
   if (next_gain && mfma_can_fuse_norm(c, R)) {
     a.x_res = c->x; a.gain = next_gain; a.stats_out = c->nstats;
     a.out_bf = (bf16_t *)c->xn; a.out_lo = mfma_lo(c, c->xn, d);
-    c->norm_fused = true;
+    c->norm_fused = true; c->norm_halves = false;
     return mfma_gemm(EPI_RESID_NORM, a, R, s);
   }
   return mfma_gemm(EPI_RESID, a, R, s);
@@ -119,7 +107,9 @@ int mfma_out_ffn(pd_ctx *c, GemmArgs &a, const bf16_t *p_wo, const LayerPtrs &lw
   a.stats_in = nullptr;
   set_weights(c, a, lw.p_w2);
   a.xn = (const bf16_t *)c->hb; a.xn_lo = mfma_lo(c, c->hb, ff); a.K = ff; a.n_tiles = d / 16; a.x = c->ypart; a.ld = d;
-  if (next_gain && ffn2_prepares_norm(c, R)) {
+  const NormHandover over = next_gain && R <= 16 && mfma_can_fuse_norm(c, R) ? ffn2_handover(d, ff, c->opt_split, c->opt_fuse_norm == 2) : HANDOVER_NONE;
+  if (over != HANDOVER_NONE) {
+    a.half_tiles = c->norm_halves = over == HANDOVER_HALVES;
     // completes x itself and leaves gain * x with the row sums for the next layer's QKV projection
     a.x_res = c->x; a.gain = next_gain; a.stats_out = c->nstats;
     a.out_bf = (bf16_t *)c->xn; a.out_lo = mfma_lo(c, c->xn, d);

@@ -132,6 +132,7 @@ struct GemmArgs {
   // gain * x_res as activation fragments, stats_out[row][tile] the sum and the sum of squares of x_res
   // over the tile's 16 columns
   float *x_res; const float *gain; float2 *stats_out;
+  int half_tiles;        // 1: blocks of 8 columns (with low parts or packed), row sums per 8 columns
   // EPI_GELU / EPI_SWIGLU / EPI_QKV* with stats_in != NULL: the activations are gain * x (not normalised); the
   // epilogue applies the norm, y = rstd * (acc - mean * c1[n]) + c2[n], with mean and rstd of every row
   // from stats_in[row][stats_tiles] and c1 = W gain, c2 = W bias (c2 NULL: no bias)

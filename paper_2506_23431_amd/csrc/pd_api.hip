@@ -259,7 +259,7 @@ __global__ void k_fill_zero(uint4 *p, size_t n16) {
 // the workspace, re-packing the weights.  `c` has its configuration, pointers and carve-up.
 static int finish_create(pd_ctx *c, size_t need, void *hip_stream, bool no_alloc, pd_ctx **out) {
   c->prefilled = false; c->host_steps = 0;
-  c->embed_pending = false; c->embedded = false; c->norm_fused = false; c->packed = false;
+  c->embed_pending = false; c->embedded = false; c->norm_fused = c->norm_halves = false; c->packed = false;
   c->opt_splits = 0; c->opt_graph = 0; c->opt_profile = 0; c->opt_split = 1; c->opt_chunk = 0; c->opt_fuse_norm = 1;
   c->opt_ctx_split = 1; c->opt_ctx_attn = 1;
   c->graph_exec = nullptr; c->graph_ready = false; c->ev_used = 0; c->h_pinned = nullptr;
@@ -573,7 +573,7 @@ static int run_layers(pd_ctx *c, int R, int A, int nreq, int req0, int kv_overri
   if (c->impl == 1) c->embed_pending = !c->embedded;
   else if (simple_embeds(c, R) && (rc = launch_embed(c, R, s))) return rc;
   c->pend_parts = 0;
-  c->norm_fused = false;
+  c->norm_fused = c->norm_halves = false;
   for (int l = 0; l < c->cfg.n_layer; ++l) {
     rc = c->arch == 1 ? encdec_decoder_layer(c, l, R, s)
          : c->impl == 1 ? mfma_layer(c, l, R, A, nreq, req0, kv_override, s)
@@ -854,7 +854,7 @@ extern "C" int pd_teacher_forced(pd_ctx *c, const int32_t *target, int max_len, 
     const int A = *std::max_element(rows.begin() + b, rows.begin() + b + nreq), R = nreq * A;
     const PassRows buffers(c, A, nreq);
     if ((rc = launch_teacher_rows(c, c->tf_target, b, nreq, A, max_len, s))) return rc;
-    c->packed = false; c->embed_pending = true; c->pend_parts = 0; c->norm_fused = false;
+    c->packed = false; c->embed_pending = true; c->pend_parts = 0; c->norm_fused = c->norm_halves = false;
     for (int l = 0; l < g.n_layer; ++l)
       if ((rc = c->arch == 1 ? encdec_decoder_layer(c, l, R, s, A, nreq, b, A) : mfma_layer(c, l, R, A, nreq, b, L + A, s, &am)))
         return rc;
