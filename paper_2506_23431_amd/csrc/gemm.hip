@@ -643,6 +643,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, int nt, const f
           if (t > best) { best = t; bi = n; }
         }
       }
+      if (a.logits_A > 0) continue;           // (a training target selects no tokens)
       // across the 4 column groups of this row; lowest index wins ties
       best16(best, bi);
       best32(best, bi);
@@ -655,6 +656,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &a, int nt, const f
 // request, read 25 KB per row at 50265 words.)  Row-major [row][block]: it reads a row's winners as one run.
 template <int RT, int W>
 __device__ __forceinline__ void store_winners(const GemmArgs &a, const Winner (&win)[RT], int w, int lane, int r0) {
+  if (a.logits_A > 0) return;           // the same for the whole launch
   __shared__ Winner sm_win[W > 1 ? W : 1][RT * 16];
   if (W > 1) {
     if (w < W && lane < 16)
