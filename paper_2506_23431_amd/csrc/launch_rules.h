@@ -139,6 +139,16 @@ inline int lin_row_tiles(int n_tiles, int K, int rows) {
 }
 
 // ---------------------------------------------------------------------------
+// fp32 attention: two blocks per (request, head, query group), each with all scores and half of the dims of the values.
+// ---------------------------------------------------------------------------
+// Where one block per unit leaves half of the chip idle: a block then draws three quarters of the bytes and multiplies three
+// quarters (12 rows, 16 units of head size 64, 330 keys 11.7 -> 8.7 us).  us per step of 4 layers, one block / two: 320 keys of
+// size 64, 8 units 130.3 / 122.3, 16 units 133.5 / 125.7, 200 keys, 64 units 128.5 / 127.4, 128 units 133.8 / 127.6, of size 80
+// 160.3 / 152.7, 128 153.0 / 144.6.  With heads of 32 (109.6 / 114.2, 480 keys 109.1 / 112.1) or few keys (20 + generated 113.3 /
+// 118.4) there is less to share than the second block costs.
+inline bool attn_f32_halves(int head_dim, int units, int keys) { return head_dim > 32 && units <= 128 && keys >= 160; }
+
+// ---------------------------------------------------------------------------
 // fp32 steps of at most 32 rows: second FFN projection cut along K over 4 blocks.
 // ---------------------------------------------------------------------------
 // Uncut, a block per 16 columns draws its weights and rows through one compute unit; cut, whoever reads the rows next (QKV

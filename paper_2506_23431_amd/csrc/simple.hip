@@ -539,8 +539,8 @@ __global__ void k_qkv_post(float *qkv, KT *kc, KT *vc, KT *kc_lo, KT *vc_lo, Row
 // Per key tile: S^T (16 keys x 16 queries) from the keys' rows and the queries, mask, online softmax per query,
 // O^T += V^T P^T; the score tile's registers are the operand of the second product.  Keys and values are requested
 // together, before either is used.  Bound by the one compute unit a (request, head) runs on: 32 products of 32 clocks
-// per key tile, so 16 waves and a tile or two each (12 rows, 8 heads of 64, 330 keys: 10.7 us, 12 with all waves merging
-// and expf; a thread per key over uncoalesced key rows took 31; requesting the next tile ahead costs the registers of half
+// per key tile, so 16 waves and a tile or two each, and two blocks per unit where that pays (attn_f32_halves; 12 rows,
+// 16 units of 64 dims, 330 keys: 8.7 us, 11.7 with one block, 12 more with all waves merging and expf; a thread per key over uncoalesced key rows took 31; requesting the next tile ahead costs the registers of half
 // the waves, 13-17 us).
 // ---------------------------------------------------------------------------
 struct AttnF32Args {
@@ -549,6 +549,7 @@ struct AttnF32Args {
   RowTables rt; const int32_t *kv_len; const uint16_t *gen_sub;
   int kv_override, d, H, hd, kv_cap, gen_stride, L, A, nqg, req0;
   float scale;
+  int keys;                 // (host) keys of the launch, of a step those of the middle of its run
 };
 
 // e^x for x <= 0 (or NaN) as 2^n 2^f, n the whole part of x log2 e and f the rest.  The rounded product h = x log2 e is taken
@@ -564,11 +565,15 @@ __device__ __forceinline__ float exp_f32(float x) {
   return ldexpf(__builtin_amdgcn_exp2f(f), (int)n);
 }
 
-template <typename KT, int NHB, int NW, bool VEC, bool PAIR>      // NHB: 16-dim blocks of a head (hd <= 16 NHB); PAIR: low halves
+// NHB: 16-dim blocks of a head (hd <= 16 NHB); PAIR: low halves; VS: blocks that share a unit, each with all scores and its part of
+// the values' dims (nothing to merge)
+template <typename KT, int NHB, int NW, bool VEC, bool PAIR, int VS>
 __global__ __launch_bounds__(64 * NW) void k_attn_f32(const float *hot_qkv, const void *hot_k, const void *hot_v,
                                                       const int4 *hot_qinfo, const int32_t *hot_kv_len, uint32_t hot_hda, int kv_cap,
                                                       int H, int hot_req0, AttnF32Args a) {
-  __shared__ floatx4 sm_o[NW][NHB][64];
+  constexpr int NV = NHB / VS;          // 16-dim blocks of the values here
+  static_assert(NHB % VS == 0, "whole 16-dim blocks");
+  __shared__ floatx4 sm_o[NW][NV][64];
   __shared__ float sm_m[NW][16], sm_l[NW][16];
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
   // (one grid dimension: the others end at 65535, and a batch may have more requests)
@@ -576,6 +581,7 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(const float *hot_qkv, cons
   int reqi = unit, qg = 0;
   if (nqg > 1) { reqi = unit / nqg; qg = unit - reqi * nqg; }
   const int req = hot_req0 + reqi, d = H * hd;
+  const int hb0 = VS > 1 ? (int)blockIdx.y * NV : 0;
   const int qa = qg * 16 + m;
   const int r = reqi * A + min(qa, A - 1);              // clamped: loads stay in bounds
   const int4 qi = hot_qinfo[r];                         // {flags, sub, lim, req}
@@ -588,14 +594,14 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(const float *hot_qkv, cons
   // masked; it is allocated and holds finite numbers)
   const size_t base = ((size_t)req * H + h) * kv_cap * hd;
   const KT *K = (const KT *)hot_k + base, *V = (const KT *)hot_v + base;
-  floatx4 kf[NHB], vf[NHB];             // key m, dims 16 c + 4 g .. + 3;  dim 16 i + m, keys 4 g .. + 3
+  floatx4 kf[NHB], vf[NV];              // key m, dims 16 c + 4 g .. + 3;  dim 16 (hb0 + i) + m, keys 4 g .. + 3
   auto load = [&](int t) {
     const size_t krow = (size_t)min(t * 16 + m, kv_cap - 1) * hd;
 #pragma unroll
     for (int c = 0; c < NHB; ++c) kf[c] = ld_row4<VEC>(K + krow, 16 * c + 4 * g, hd);
 #pragma unroll
-    for (int i = 0; i < NHB; ++i)       // (kv_cap is a multiple of 64)
-      vf[i] = ld_row4<true>(V + (size_t)min(16 * i + m, hd - 1) * kv_cap, t * 16 + 4 * g, kv_cap);
+    for (int i = 0; i < NV; ++i)        // (kv_cap is a multiple of 64)
+      vf[i] = ld_row4<true>(V + (size_t)min(16 * (hb0 + i) + m, hd - 1) * kv_cap, t * 16 + 4 * g, kv_cap);
   };
   load(w);
   __builtin_amdgcn_sched_barrier(0);
@@ -618,9 +624,9 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(const float *hot_qkv, cons
 #pragma unroll
     for (int e = 0; e < 4; ++e) q[c][e] = 16 * c + 4 * g + e < hd ? q[c][e] : 0.f;
   float m_run = -INFINITY, l_run = 0.f;
-  floatx4 o_acc[NHB];
+  floatx4 o_acc[NV];
 #pragma unroll
-  for (int i = 0; i < NHB; ++i) o_acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < NV; ++i) o_acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
   for (int t = w; t < tiles; t += NW) {
     const int key0 = t * 16, key = key0 + 4 * g;
     if (PAIR) {
@@ -628,7 +634,7 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(const float *hot_qkv, cons
 #pragma unroll
       for (int c = 0; c < NHB; ++c) kf[c] += ld_row4<VEC>(Kl + krow, 16 * c + 4 * g, hd);
 #pragma unroll
-      for (int i = 0; i < NHB; ++i) vf[i] += ld_row4<true>(Vl + (size_t)min(16 * i + m, hd - 1) * kv_cap, key, kv_cap);
+      for (int i = 0; i < NV; ++i) vf[i] += ld_row4<true>(Vl + (size_t)min(16 * (hb0 + i) + m, hd - 1) * kv_cap, key, kv_cap);
     }
     const int tag[4] = {(int)(tg.x & 0xffff), (int)(tg.x >> 16), (int)(tg.y & 0xffff), (int)(tg.y >> 16)};
     floatx4 se[4];
@@ -659,20 +665,20 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(const float *hot_qkv, cons
     m_run = m_new;
     if (__any(alpha != 1.f))
 #pragma unroll
-      for (int i = 0; i < NHB; ++i) o_acc[i] *= alpha;
+      for (int i = 0; i < NV; ++i) o_acc[i] *= alpha;
 #pragma unroll
     for (int e = 0; e < 4; ++e)
 #pragma unroll
-      for (int i = 0; i < NHB; ++i)       // (slots past the last key hold what an earlier request left there)
+      for (int i = 0; i < NV; ++i)        // (slots past the last key hold what an earlier request left there)
         o_acc[i] = mfma_f32(key0 + 4 * g + e < n ? vf[i][e] : 0.f, p[e], o_acc[i]);
     if (t + NW < tiles) { load(t + NW); load_tags(t + NW); }   // the same for the whole wave
   }
   l_run = fold32(fold16(l_run, Add()), Add());
   if (g == 0) { sm_m[w][m] = m_run; sm_l[w][m] = l_run; }
 #pragma unroll
-  for (int i = 0; i < NHB; ++i) sm_o[w][i][lane] = o_acc[i];
+  for (int i = 0; i < NV; ++i) sm_o[w][i][lane] = o_acc[i];
   __syncthreads();
-  if (w >= NHB) return;                 // a wave per 16 dims merges (all 16 doing the weights took 2.7 us)
+  if (w >= NV) return;                 // a wave per 16 dims merges (all 16 doing the weights took 2.7 us)
   float M = -INFINITY, f[NW], l = 0.f;
 #pragma unroll
   for (int v = 0; v < NW; ++v) M = fmaxf(M, sm_m[v][m]);
@@ -682,31 +688,37 @@ __global__ __launch_bounds__(64 * NW) void k_attn_f32(const float *hot_qkv, cons
     l += f[v] * sm_l[v][m];
   }
   if (!valid) return;
-  // lane (query m, g) of dim block i: dims 16 i + 4 g .. + 3
-  for (int i = w; i < NHB; i += NW) {
+  // lane (query m, g) of dim block i: dims 16 (hb0 + i) + 4 g .. + 3
+  for (int i = w; i < NV; i += NW) {
     floatx4 o = f[0] * sm_o[0][i][lane];
 #pragma unroll
     for (int v = 1; v < NW; ++v) o += f[v] * sm_o[v][i][lane];
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      if (16 * i + 4 * g + j < hd) a.out[(size_t)r * d + h * hd + 16 * i + 4 * g + j] = o[j] / l;
+      if (16 * (hb0 + i) + 4 * g + j < hd) a.out[(size_t)r * d + h * hd + 16 * (hb0 + i) + 4 * g + j] = o[j] / l;
   }
 }
 
 template <typename KT>
 static int attention_f32(const AttnF32Args &a, int nreq, hipStream_t s) {
-  const dim3 grid(a.H * nreq * a.nqg);
+  const int units = a.H * nreq * a.nqg;
   const int32_t *kv_len = a.kv_override >= 0 ? nullptr : a.kv_len;
   PD_REQUIRE(a.A < 65536, PD_EINVAL, "%d rows per request", a.A);        // (a step has at most 1024, a context pass too)
   const uint32_t hda = (uint32_t)a.hd | (uint32_t)a.A << 16;
   constexpr bool LOW = sizeof(KT) == 2; // (only half caches have low halves)
   const bool vec = a.hd % 4 == 0;       // rows of q, keys and values then start at multiples of 16 (half: 8) bytes
+  const bool halves = attn_f32_halves(a.hd, units, a.keys);
+#define PD_ATTN_F32_VS(NHB, NW, VS)                                                                           \
+  do {                                                                                                        \
+    auto kernel = a.kc_lo ? (vec ? k_attn_f32<KT, NHB, NW, true, LOW, VS> : k_attn_f32<KT, NHB, NW, false, LOW, VS>)  \
+                          : (vec ? k_attn_f32<KT, NHB, NW, true, false, VS> : k_attn_f32<KT, NHB, NW, false, false, VS>); \
+    hipLaunchKernelGGL(kernel, dim3(units, VS), dim3(64 * NW), 0, s, a.qkv, a.kc, a.vc, a.rt.qinfo, kv_len, hda, a.kv_cap, a.H,  \
+                       a.req0, a);                                                                            \
+  } while (0)
 #define PD_ATTN_F32(NHB, NW)                                                                                  \
   do {                                                                                                        \
-    auto kernel = a.kc_lo ? (vec ? k_attn_f32<KT, NHB, NW, true, LOW> : k_attn_f32<KT, NHB, NW, false, LOW>)  \
-                          : (vec ? k_attn_f32<KT, NHB, NW, true, false> : k_attn_f32<KT, NHB, NW, false, false>); \
-    hipLaunchKernelGGL(kernel, grid, dim3(64 * NW), 0, s, a.qkv, a.kc, a.vc, a.rt.qinfo, kv_len, hda, a.kv_cap, a.H,  \
-                       a.req0, a);                                                                            \
+    if (halves) PD_ATTN_F32_VS(NHB, NW, (NHB > 2 ? 2 : 1));                                                   \
+    else PD_ATTN_F32_VS(NHB, NW, 1);                                                                          \
   } while (0)
   // waves per block: what the registers of a wave leave room for
   if (a.hd <= 16) PD_ATTN_F32(1, 16);
@@ -715,6 +727,7 @@ static int attention_f32(const AttnF32Args &a, int nreq, hipStream_t s) {
   else if (a.hd <= 128) PD_ATTN_F32(8, 8);
   else PD_ATTN_F32(16, 4);
 #undef PD_ATTN_F32
+#undef PD_ATTN_F32_VS
   PD_CHECK_HIP(hipGetLastError());
   return PD_OK;
 }
@@ -788,6 +801,7 @@ int simple_layer(pd_ctx *c, int l, int R, int A, int nreq, int req0, int kv_over
   t.rt = c->rows; t.kv_len = c->sch.kv_len; t.gen_sub = c->sch.gen_sub; t.kv_override = kv_override; t.d = d; t.H = H;
   t.hd = hd; t.kv_cap = c->kv_cap; t.gen_stride = c->gen_stride; t.L = c->L; t.A = A; t.nqg = (A + 15) / 16;
   t.req0 = req0; t.scale = 1.0f / sqrtf((float)hd);
+  t.keys = kv_override >= 0 ? kv_override : c->L + c->S * (c->M + 1) / 2;
   if ((rc = g.dtype == 0 ? attention_f32<float>(t, nreq, s) : attention_f32<f16_t>(t, nreq, s))) return rc;
   a = base;
   a.x = (const float *)c->att; a.out = c->x; a.res = c->x; a.ldo = d;
