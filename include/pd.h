@@ -261,10 +261,10 @@ int pd_reset_decode(pd_ctx *ctx, void *hip_stream);
  *                        first FFN projection, and that projection finishes the second norm of the
  *                        layer in its epilogue (one kernel less per layer); 0: a separate norm kernel,
  *                        as in steps with more rows.  Same results up to rounding order.
- *                        In steps of at most 16 rows, models of d_model <= 1024 and d_ff <= 4096 also hand over
- *                        the first norm of the next layer the same way (second FFN projection -> QKV projection).
- *                        2: so do all others (that projection then cannot be cut along K over blocks: slower from
- *                        d_ff 8192 on, up to 8 % faster per step at widths 1280-2048 with d_ff <= 4096).
+ *                        In steps of at most 16 rows, models of d_model <= 1024 and d_ff <= 4096, and of d_model <= 2048 and
+ *                        d_ff <= 6144 (a multiple of 64), also hand over the first norm of the next layer the same way (second
+ *                        FFN projection -> QKV projection).  2: so do all others (that projection then cannot be cut along K
+ *                        over blocks: slower from d_ff 8192 on).
  *   PD_OPT_STREAM_LOADS  1: decode steps load weights, keys and values with the non-temporal hint; 0: ordinary
  *                        loads.  Chosen at creation from the configuration: 1 when the bytes a step reads at
  *                        full capacity (every weight, every request's keys and values) exceed the 256 MB
