@@ -160,14 +160,18 @@ __device__ __forceinline__ floatx4 row_value(const floatx4 (&q)[row_parts(SRC)],
 // whole (VPL quads per lane), takes mean and variance in registers (two passes) and leaves the normalised row in LDS;
 // the first weights are requested before that (by the leading arguments, which arrive in registers).  Bound by latency at the
 // sizes of this path: enough waves that each has one or two batches of requests (512 x 2048, 12 rows: 13.5 us with a wave per
-// column, 6-7 so), and every request of the first batch in flight before anything is waited for.
+// column, 6-7 so), and every request of the first batch in flight before anything is waited for, as far as registers go: 16
+// waves have 128 each, and beyond that everything in flight goes through scratch memory (rows of four quads with their slices beside
+// gain, bias and weights; two matrices beside two sets of rows; a place for every value of a scalar load.  us per step of 4
+// layers with spills / without: width 768, 12 rows 175.8 / 157.7, 1024 193.9 / 174.4, gated 1280 337.7 / 320.3, scalar
+// loads 650 346 / 310, gated 371 / 319).
 template <typename WT, typename KT, int EPI, int NW, int RT, int VPL, bool VEC, int SRC>
 __global__ __launch_bounds__(64 * NW) void k_lin(const void *hot_x, const void *hot_w, const void *hot_w2, const float *hot_g,
                                                    const float *hot_b, const int4 *hot_info, int R, int K, LinArgs a) {
   // (hot_x: the rows or, of normed gathered ones, the token table; hot_w2: the second matrix of LIN_SWIGLU, else RowSrc's second)
   const int N = a.N;
   constexpr bool NORM = VPL > 0;
-  constexpr int NT = EPI == LIN_SWIGLU ? 2 : 1, U = 4;
+  constexpr int NT = EPI == LIN_SWIGLU ? 2 : 1, U = VEC || NT == 1 ? 4 : 2;
   constexpr int XLD = NORM ? 256 * VPL + 4 : 4;      // (+ 4: the 16 rows of a step lie in different banks)
   static_assert(!NORM || RT == 1, "row statistics are taken for one row tile");
   static_assert(SRC == SRC_ROWS || (EPI != LIN_SWIGLU && (NORM || EPI == LIN_RESID)), "rows put together: normed, or the residual");
@@ -191,10 +195,12 @@ __global__ __launch_bounds__(64 * NW) void k_lin(const void *hot_x, const void *
   floatx4 wv[NT][U];
   constexpr int RPW = NORM ? 16 / NW : 1, VP = NORM ? VPL : 1;      // rows per wave, quads per lane
   constexpr int NSRC = NORM ? SRC : SRC_ROWS, RSRC = EPI == LIN_RESID ? SRC : SRC_ROWS;
+  static_assert(VP < 4 || RPW == 1, "a wave holds one row of four quads a lane");
   floatx4 xq[RPW][VP][row_parts(NSRC)], gv[VP], bv[VP];
   RowState xs[RPW];
   // (rows before weights: the number of columns is in the argument struct, which is still on its way)
-  constexpr bool AHEAD = !NORM && RT == 1;           // a batch's rows are requested with its weights, else when it begins
+  // a batch's rows are requested with its weights, or when it begins where two matrices or scalar loads leave no registers
+  constexpr bool AHEAD = !NORM && RT == 1 && NT == 1 && VEC;
   floatx4 xv[RT][U];
   auto load_x = [&](floatx4 (&xv)[RT][U], int s) {
 #pragma unroll
@@ -208,6 +214,17 @@ __global__ __launch_bounds__(64 * NW) void k_lin(const void *hot_x, const void *
       }
     }
   };
+  // gain and bias: with everything else or, where rows of four quads and their slices fill a wave's registers, under the sums
+  // (scalar loads: such rows and slices in two halves, more than 63 requests wait for each other)
+  constexpr bool LATE_GAIN = NORM && VPL == 4 && SRC == SRC_SLICES;
+  constexpr int QB = LATE_GAIN && !VEC ? VP / 2 : VP;
+  auto load_gain = [&]() {
+#pragma unroll
+    for (int v = 0; v < VP; ++v) {
+      gv[v] = ld_row4<VEC>(hot_g, 4 * (lane + 64 * v), K);
+      bv[v] = ld_row4<VEC>(hot_b ? hot_b : hot_g, 4 * (lane + 64 * v), K);
+    }
+  };
   if (AHEAD) load_x(xv, s0);
   if constexpr (!NORM) load_w(wv, s0);
   if constexpr (NORM) {
@@ -216,12 +233,8 @@ __global__ __launch_bounds__(64 * NW) void k_lin(const void *hot_x, const void *
 #pragma unroll
       for (int i = 0; i < RPW; ++i)
 #pragma unroll
-        for (int v = 0; v < VPL; ++v) row(i).template ask<VEC>(xq[i][v], 4 * (lane + 64 * v), K);
-#pragma unroll
-    for (int v = 0; v < VPL; ++v) {
-      gv[v] = ld_row4<VEC>(hot_g, 4 * (lane + 64 * v), K);
-      bv[v] = ld_row4<VEC>(hot_b ? hot_b : hot_g, 4 * (lane + 64 * v), K);
-    }
+        for (int v = 0; v < QB; ++v) row(i).template ask<VEC>(xq[i][v], 4 * (lane + 64 * v), K);
+    if (!LATE_GAIN) load_gain();
     int fl = 0, tok = 0, pos = 0;         // lane i: of row i (read one by one they were waited for one by one)
     if (SRC == SRC_GATHER) {
       const int rl = min(r0 + w * RPW + lane % RPW, R - 1);
@@ -235,7 +248,7 @@ __global__ __launch_bounds__(64 * NW) void k_lin(const void *hot_x, const void *
           : row(i);
       xs[i] = src.state;
 #pragma unroll
-      for (int v = 0; v < VPL; ++v) {
+      for (int v = 0; v < QB; ++v) {
         if (SRC == SRC_GATHER) src.template ask<VEC>(xq[i][v], 4 * (lane + 64 * v), K);
         src.template ask_rest<VEC>(xq[i][v], 4 * (lane + 64 * v), K);
       }
@@ -258,8 +271,8 @@ __global__ __launch_bounds__(64 * NW) void k_lin(const void *hot_x, const void *
       }
     }
   }
-  int4 info = make_int4(0, 0, 0, 0);
-  if (EPI == LIN_QKV || EPI == LIN_HEAD) info = hot_info[rf];       // {flags, req, slot, pos}; {flags, sub, lim, req}
+  int4 info = make_int4(0, 0, 0, 0);                                // {flags, req, slot, pos}; {flags, sub, lim, req}
+  if ((EPI == LIN_QKV || EPI == LIN_HEAD) && !LATE_GAIN) info = hot_info[rf];
   if constexpr (NORM) {
     __builtin_amdgcn_sched_barrier(0);
     floatx4 nx[RPW][VPL];
@@ -267,7 +280,24 @@ __global__ __launch_bounds__(64 * NW) void k_lin(const void *hot_x, const void *
 #pragma unroll
     for (int i = 0; i < RPW; ++i)
 #pragma unroll
-      for (int v = 0; v < VPL; ++v) nx[i][v] = row_value<NSRC>(xq[i][v], xs[i]);
+      for (int v = 0; v < QB; ++v) nx[i][v] = row_value<NSRC>(xq[i][v], xs[i]);
+    if constexpr (QB < VP) {
+      __builtin_amdgcn_sched_barrier(0);
+      const RowSrc<WT, NSRC> src(a, hot_x, hot_w2, min(r0 + w, R - 1), K);
+#pragma unroll
+      for (int v = 0; v < QB; ++v) {
+        src.template ask<VEC>(xq[0][v], 4 * (lane + 64 * (QB + v)), K);
+        src.template ask_rest<VEC>(xq[0][v], 4 * (lane + 64 * (QB + v)), K);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int v = 0; v < QB; ++v) nx[0][QB + v] = row_value<NSRC>(xq[0][v], xs[0]);
+    }
+    if (LATE_GAIN) {
+      __builtin_amdgcn_sched_barrier(0);
+      load_gain();
+      if (EPI == LIN_QKV || EPI == LIN_HEAD) info = hot_info[rf];
+    }
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
       s[i] = 0.f;
@@ -464,14 +494,13 @@ static int run_lin(const LinArgs &a, int n_tiles, hipStream_t s) {
       return PD_OK;
     }
   }
-  // (only the rows of at most 32 are gathered or lack slices)
+  // (only the rows of at most 32, of up to 1024 values, are gathered or lack slices: norm_inside)
   const int rt = lin_row_tiles(n_tiles, a.K, a.R);
   if constexpr (EPI == LIN_RESID) {
     if (a.tok_emb || a.pend) {
-      PD_REQUIRE(rt == 1, PD_EINVAL, "rows put together by launches of one row tile (%d rows)", a.R);
+      PD_REQUIRE(rt == 1 && a.K <= 1024, PD_EINVAL, "rows put together by launches of one row tile (%d rows of %d values)", a.R, a.K);
       if (a.K <= 256) launch_lin_from<WT, KT, EPI, 4, 0>(a, n_tiles, vec, s);
-      else if (a.K <= 1024) launch_lin_from<WT, KT, EPI, 8, 0>(a, n_tiles, vec, s);
-      else launch_lin_from<WT, KT, EPI, 16, 0>(a, n_tiles, vec, s);
+      else launch_lin_from<WT, KT, EPI, 8, 0>(a, n_tiles, vec, s);
       PD_CHECK_HIP(hipGetLastError());
       return PD_OK;
     }
