@@ -24,6 +24,8 @@ CASES = [
     W("96-batch", 4, 96, 170, batch=3), W("128", 2, 128, 400), W("130", 1, 130, 200), W("256", 1, 256, 170),
     W("128-units", 16, 40, 160, batch=8), W("129-units-whole", 43, 36, 160, batch=3),
     W("bf16-80", 2, 80, 200, dtype=DTYPE_BF16), W("bf16-48-16-rows", 2, 48, 200, dtype=DTYPE_BF16, batch=2, n_sub=8, sub_tokens=8),
+    W("bf16-50-scalar", 2, 50, 200, dtype=DTYPE_BF16), W("bf16-66-scalar", 2, 66, 333, dtype=DTYPE_BF16),
+    W("bf16-130-scalar", 1, 130, 170, dtype=DTYPE_BF16), W("bf16-50-scalar-129-units-whole", 43, 50, 160, batch=3, dtype=DTYPE_BF16),
 ]
 
 

@@ -1,7 +1,7 @@
 """Registers of the fp32 kernels, as the compiler left them in the built library's metadata.  A block of 16 waves has 128 per
 lane; what does not fit goes to scratch memory and back in every block, on a path whose launches last a few microseconds.
 Projections with one row tile per block (every decode step of at most 32 rows) and attention with wide loads keep
-everything in registers, whatever their rows come from."""
+everything in registers, whatever their rows come from; so does attention with scalar loads of pairs in halves of the dims."""
 
 import os
 import re
@@ -56,3 +56,9 @@ def test_attention_with_wide_loads_uses_no_scratch(scratch):
     wide = {k: v for k, v in scratch.items() if re.match(r"_Z10k_attn_f32I(f|DF16_)Li\d+ELi\d+ELb1E", k)}
     assert len(wide) >= 20
     assert {k: v for k, v in wide.items() if v} == {}
+
+
+def test_attention_with_scalar_loads_of_pairs_uses_no_scratch_in_halves(scratch):
+    halves = {k: v for k, v in scratch.items() if re.match(r"_Z10k_attn_f32IDF16_Li\d+ELi\d+ELb0ELb1ELi2E", k)}
+    assert len(halves) >= 3
+    assert {k: v for k, v in halves.items() if v} == {}
