@@ -270,8 +270,9 @@ int pd_reset_decode(pd_ctx *ctx, void *hip_stream);
  *                        full capacity (every weight, every request's keys and values) exceed the 256 MB
  *                        last-level cache, so that nothing of them would be found there a step later (cfg4:
  *                        1.37 -> 1.31 ms per step, cfg5 6.55 -> 6.09); 0 for models the cache serves step after
- *                        step (cfg2: 0.187 ms, 0.202 with the hint).  Chosen at creation, the first 110 MB of the
- *                        packed weights keep ordinary loads, and their place in that cache; set here, 1 is for all.
+ *                        step (cfg2: 0.187 ms, 0.202 with the hint).  Chosen at creation, the matrices that start within
+ *                        the first 110 MB of the packed weights and end within 210 MB keep ordinary loads, and their
+ *                        place in that cache; set here, 1 is for all.
  *                        Same results bit for bit.
  *                        pd_get_info(PD_INFO_STREAM_LOADS) reports the setting.
  *   PD_OPT_CONTEXT_ATTN  attention kernel of the context pass (bf16 path, head_dim 64 or 128, layers without
@@ -320,6 +321,8 @@ int pd_measure_read_bandwidth(const void *dev_buf, size_t buf_bytes, size_t chun
  *   PD_INFO_CONTEXT_PAIRS   1: the context pass carries its activations as bf16 pairs; 0: as single bf16
  *                           values (PD_OPT_CONTEXT_SPLIT_ACT resolved)
  *   PD_INFO_STREAM_LOADS    1: decode steps use the non-temporal hint (PD_OPT_STREAM_LOADS)
+ *   PD_INFO_KEPT_BYTES      bytes of the weights of a decode step that keep ordinary loads while the others take the
+ *                           hint (at most 210 MB; 0 without the hint)
  *   PD_INFO_KV_SATURATED    keys and values written since pd_create whose magnitude exceeded the
  *                           largest half (65504) and were stored as +-65504 (dtype 1 only; always
  *                           0 for dtype 0).  Non-zero means the 16-bit cache cannot represent
@@ -330,6 +333,7 @@ int pd_measure_read_bandwidth(const void *dev_buf, size_t buf_bytes, size_t chun
 #define PD_INFO_KV_SATURATED   3
 #define PD_INFO_CONTEXT_PAIRS  4
 #define PD_INFO_STREAM_LOADS   5
+#define PD_INFO_KEPT_BYTES     6
 int pd_get_info(pd_ctx *ctx, int key, void *hip_stream, int64_t *value);
 
 /* Message for the last error on this thread (static storage, never NULL). */

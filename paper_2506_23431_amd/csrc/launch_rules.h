@@ -1,6 +1,7 @@
 // Launch shapes that follow from sizes alone: host code without device types, so that it can be compiled and checked by
 // itself.
 #pragma once
+#include <stddef.h>
 #include <stdint.h>
 
 #include <algorithm>
@@ -115,6 +116,25 @@ inline NormHandover ffn2_handover(int d_model, int d_ff, bool low_parts, bool on
   if (d_model > 1024 && d_model <= 2048 && d_ff <= 6144 && d_ff % 64 == 0 && low_parts) return HANDOVER_HALVES;
   return (d_model <= 1024 && d_ff <= 4096) || on_request ? HANDOVER_WHOLE : HANDOVER_NONE;
 }
+
+// ---------------------------------------------------------------------------
+// Steps that read more than the last-level cache holds: packed weights that are loaded without the non-temporal hint.
+// ---------------------------------------------------------------------------
+// What is loaded without the hint stays in that cache as long as it is little enough: the matrices, from layer 0 on, that start
+// within the first 110 MB of the packed weights, unless they end beyond 210 MB.  With the hint on everything nothing survives a
+// step, without it on more than the cache nothing does either.  Where the first line lies, ms per run of 20 steps with 0 / 60 / 90 / 110 / 130 / 170 / 220 MB kept: encoder-decoder of width
+// 768, 12 layers 8.69 / 8.24 / 8.13 / 8.05 / 8.18 / 8.11 / 8.49, of 1024, 8 layers 6.62 / 6.39 / 6.31 / 6.23 / 6.27 / 6.58 / 6.96; 12
+// layers of width 1024 7.34 / 7.05 / 6.98 / 6.93 / 7.09 / 6.99 / 6.90, 6 of 2048 5.47 / 5.29 / 5.27 / 5.26 / 5.38 / 5.42 / 5.43,
+// 2 requests of 3000 keys, 6 of 1024 4.28 / 4.00 / 4.07 / 3.84 / 3.96 / 4.13 / 4.00; 24 of 2048 (4.4 GB a step) 0.3 %.
+// Where the second one lies, us per step with the matrix that crosses the first kept / not (in brackets what is kept then):
+// 2 layers of 3584 / 18944 gated [375 MB] 268.8 / 258.1, one of 2048 / 8192 before a head of 128000 words [625] 139.9 / 122.5, one of
+// 8192 [402] 182.9 / 174.2, 4 of 3584 / 9728 gated [242] 347.6 / 351.3, with 4 requests of 2000 keys 495.9 / 485.5; 3 of 3328 / 8896
+// gated [207] 256.9 / 260.2, with 8 requests of 4000 keys 542.0 / 547.4, 8 layers with 4 of 2000 879.1 / 864.3; one of 2048 before
+// 26000 words [207] with 4 requests of 4000 keys 97.7 / 100.6, with 16 198.8 / 206.0; 3 of 3072 / 8192 gated [176] 223.5 / 225.8; 4 of
+// 4096 / 11008 gated [134] 470.2 / 473.9.
+constexpr size_t KEPT_START = 55000000, KEPT_END = 105000000;      // of 2 bytes
+// first: values of packed weights before the matrix
+constexpr bool weights_kept(size_t first, size_t values) { return first < KEPT_START && first + values <= KEPT_END; }
 
 // ---------------------------------------------------------------------------
 // fp32 projections: row tiles of 16 rows per block.

@@ -8,10 +8,26 @@ bf16_t *mfma_lo(pd_ctx *c, void *buf, size_t cols) {
   return c->packed ? (bf16_t *)buf + 64 : (bf16_t *)buf + (size_t)c->R_pad * cols;
 }
 
-// a launch's weights, and whether it loads them with the hint
-static void set_weights(pd_ctx *c, GemmArgs &a, const bf16_t *W) {
+// a launch's weights [rows][K], and whether it loads them with the hint
+static bool kept(const pd_ctx *c, const bf16_t *W, size_t rows, size_t K) {
+  return c->kept_from && W >= c->kept_from && weights_kept(W - c->kept_from, rows * K);
+}
+static void set_weights(pd_ctx *c, GemmArgs &a, const bf16_t *W, size_t rows, size_t K) {
   a.W = W;
-  a.stream_w = c->stream_loads && W >= c->kept_end;
+  a.stream_w = c->stream_loads && !kept(c, W, rows, K);
+}
+// bytes of a step's weights that are loaded without the hint while the others take it
+int64_t mfma_kept_bytes(const pd_ctx *c) {
+  if (c->impl != 1 || !c->stream_loads) return 0;
+  const size_t d = c->cfg.d_model, ff = c->cfg.d_ff, up = c->cfg.ffn_kind == 1 ? 2 : 1;
+  size_t values = 0;
+  auto add = [&](const bf16_t *W, size_t rows, size_t K) { if (W && kept(c, W, rows, K)) values += rows * K; };
+  for (const LayerPtrs &lw : c->layers) {
+    add(lw.p_wqkv, 3 * d, d); add(lw.p_wo, d, d); add(lw.p_w1, up * ff, d); add(lw.p_w2, d, ff);
+    add(lw.p_cq, d, d); add(lw.p_co, d, d);
+  }
+  add(c->p_lm_head, c->vocab_pad, d);
+  return (int64_t)(values * sizeof(bf16_t));
 }
 
 // fields every projection of a launch sequence shares
@@ -38,7 +54,7 @@ int mfma_qkv(pd_ctx *c, GemmArgs &a, const bf16_t *W, int n_tiles, int sec0, voi
              void *vc_lo, int R, hipStream_t s, const float *c1, const float *c2) {
   const pd_config &g = c->cfg;
   const int d = g.d_model;
-  set_weights(c, a, W);
+  set_weights(c, a, W, n_tiles * 16, d);
   a.xn = (const bf16_t *)c->xn; a.xn_lo = mfma_lo(c, c->xn, d); a.K = d;
   a.n_tiles = n_tiles; a.sec0 = sec0; a.out_bf = (bf16_t *)c->q; a.out_lo = mfma_lo(c, c->q, d);
   a.kc = (f16_t *)kc; a.vc = (f16_t *)vc; a.rope_cs = c->rope_cs;
@@ -57,7 +73,7 @@ int mfma_qkv(pd_ctx *c, GemmArgs &a, const bf16_t *W, int n_tiles, int sec0, voi
 // that the next norm kernel sums)
 int mfma_out(pd_ctx *c, GemmArgs &a, const bf16_t *p_wo, int R, hipStream_t s, const float *next_gain) {
   const int d = c->cfg.d_model;
-  set_weights(c, a, p_wo);
+  set_weights(c, a, p_wo, d, d);
   a.xn = (const bf16_t *)c->att; a.xn_lo = mfma_lo(c, c->att, d); a.K = d; a.n_tiles = d / 16; a.x = c->ypart; a.ld = d;
   a.part_stride = (size_t)c->R_pad * d; a.max_parts = 4; a.parts_out = &c->pend_parts;
   if (next_gain && mfma_can_fuse_norm(c, R)) {
@@ -74,7 +90,7 @@ int mfma_out_ffn(pd_ctx *c, GemmArgs &a, const bf16_t *p_wo, const LayerPtrs &lw
                  const float *next_gain) {
   const pd_config &g = c->cfg;
   int d = g.d_model, ff = g.d_ff, rc;
-  set_weights(c, a, p_wo);
+  set_weights(c, a, p_wo, d, d);
   a.xn = (const bf16_t *)c->att; a.xn_lo = mfma_lo(c, c->att, d); a.K = d; a.n_tiles = d / 16; a.x = c->ypart; a.ld = d;
   a.part_stride = (size_t)c->R_pad * d; a.max_parts = 4; a.parts_out = &c->pend_parts;
   // At most 16 rows: the projection is not cut along K over blocks, so its epilogue holds the final
@@ -95,7 +111,7 @@ int mfma_out_ffn(pd_ctx *c, GemmArgs &a, const bf16_t *p_wo, const LayerPtrs &lw
   // FFN
   a.xn = (const bf16_t *)c->xn; a.xn_lo = mfma_lo(c, c->xn, d); a.K = d;
   a.out_bf = (bf16_t *)c->hb; a.out_lo = mfma_lo(c, c->hb, ff); a.ld = ff;
-  set_weights(c, a, lw.p_w1);
+  set_weights(c, a, lw.p_w1, (g.ffn_kind == 1 ? 2 : 1) * (size_t)ff, d);
   if (g.ffn_kind == 1) {
     a.n_tiles = 2 * ff / 16;
     rc = mfma_gemm(EPI_SWIGLU, a, R, s);
@@ -105,7 +121,7 @@ int mfma_out_ffn(pd_ctx *c, GemmArgs &a, const bf16_t *p_wo, const LayerPtrs &lw
   }
   if (rc) return rc;
   a.stats_in = nullptr;
-  set_weights(c, a, lw.p_w2);
+  set_weights(c, a, lw.p_w2, d, ff);
   a.xn = (const bf16_t *)c->hb; a.xn_lo = mfma_lo(c, c->hb, ff); a.K = ff; a.n_tiles = d / 16; a.x = c->ypart; a.ld = d;
   const NormHandover over = next_gain && R <= 16 && mfma_can_fuse_norm(c, R) ? ffn2_handover(d, ff, c->opt_split, c->opt_fuse_norm == 2) : HANDOVER_NONE;
   if (over != HANDOVER_NONE) {
@@ -150,7 +166,7 @@ int mfma_head(pd_ctx *c, int R, float *logits, hipStream_t s, int tf_A, int tf_c
   GemmArgs a;
   memset(&a, 0, sizeof(a));
   a.R = R; a.rt = c->rows; a.xn = (const bf16_t *)c->xn; a.packed = c->packed;
-  set_weights(c, a, c->p_lm_head);
+  set_weights(c, a, c->p_lm_head, c->vocab_pad, g.d_model);
   a.xn_lo = mfma_lo(c, c->xn, g.d_model); a.K = g.d_model;
   a.n_tiles = c->vocab_pad / 16; a.V = g.vocab;
   a.logits = logits; a.logits_A = tf_A; a.logits_cap = tf_A > 0 ? tf_cap : c->S; a.ld_logits = g.vocab;

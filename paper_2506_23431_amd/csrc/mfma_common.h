@@ -150,6 +150,7 @@ int mfma_norm(pd_ctx *c, const float *gain, const float *bias, int R, hipStream_
 // low-part twin of an activation buffer (NULL when the split is switched off)
 bf16_t *mfma_lo(pd_ctx *c, void *buf, size_t cols);
 // pieces of a layer's launch sequence (mfma.hip)
+int64_t mfma_kept_bytes(const pd_ctx *c);
 void mfma_gemm_base(pd_ctx *c, GemmArgs &a, int R);
 // c1 != NULL: the rows in c->xn are gain * x with per-tile sums in c->nstats (c->norm_fused): the epilogue finishes the norm
 int mfma_qkv(pd_ctx *c, GemmArgs &a, const bf16_t *W, int n_tiles, int sec0, void *kc, void *vc, void *kc_lo,

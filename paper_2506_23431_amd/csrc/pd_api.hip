@@ -277,13 +277,7 @@ static int finish_create(pd_ctx *c, size_t need, void *hip_stream, bool no_alloc
                                  (double)g.vocab * g.d_model);
     const double kvbytes = caches * 2.0 * g.max_batch * (double)g.n_layer * 2.0 * c->kv_cap * g.d_model;
     c->stream_loads = (c->impl == 1 && wbytes + kvbytes > 256.0 * (1 << 20)) ? 1 : 0;
-    // What is loaded without the hint stays in that cache as long as it is little enough: the first 110 MB of the packed
-    // weights, from layer 0 on.  With the hint on everything nothing survives a step, without it on more than the cache
-    // nothing does either.  ms per run of 20 steps with 0 / 60 / 90 / 110 / 130 / 170 / 220 MB kept: encoder-decoder of width
-    // 768, 12 layers 8.69 / 8.24 / 8.13 / 8.05 / 8.18 / 8.11 / 8.49, of 1024, 8 layers 6.62 / 6.39 / 6.31 / 6.23 / 6.27 / 6.58 / 6.96; 12
-    // layers of width 1024 7.34 / 7.05 / 6.98 / 6.93 / 7.09 / 6.99 / 6.90, 6 of 2048 5.47 / 5.29 / 5.27 / 5.26 / 5.38 / 5.42 / 5.43,
-    // 2 requests of 3000 keys, 6 of 1024 4.28 / 4.00 / 4.07 / 3.84 / 3.96 / 4.13 / 4.00; 24 of 2048 (4.4 GB a step) 0.3 %.
-    c->kept_end = c->stream_loads ? c->layers[0].p_wqkv + (size_t)55000000 : nullptr;
+    c->kept_from = c->stream_loads ? c->layers[0].p_wqkv : nullptr;
   }
   hipStream_t s = (hipStream_t)hip_stream;
   auto fail = [&](int code) { (void)pd_destroy(c); return code; };
@@ -511,7 +505,7 @@ extern "C" int pd_set_option(pd_ctx *c, int key, int value) {
     case PD_OPT_CONTEXT_SPLIT_ACT:
       c->opt_ctx_split = value ? 1 : 0; return PD_OK;
     case PD_OPT_STREAM_LOADS:
-      c->stream_loads = value ? 1 : 0; c->kept_end = nullptr; drop_graph(c); return PD_OK;
+      c->stream_loads = value ? 1 : 0; c->kept_from = nullptr; drop_graph(c); return PD_OK;
     case PD_OPT_CONTEXT_ATTN:
       c->opt_ctx_attn = value < 0 ? 0 : value > 2 ? 2 : value; return PD_OK;
     case PD_OPT_FUSE_NORM:
@@ -547,6 +541,7 @@ extern "C" int pd_get_info(pd_ctx *c, int key, void *hip_stream, int64_t *value)
     case PD_INFO_KV_PAIR_LAYERS: *value = c->pair_layers; return PD_OK;
     case PD_INFO_CONTEXT_PAIRS: *value = context_pairs(c) ? 1 : 0; return PD_OK;
     case PD_INFO_STREAM_LOADS: *value = c->stream_loads; return PD_OK;
+    case PD_INFO_KEPT_BYTES: *value = mfma_kept_bytes(c); return PD_OK;
     case PD_INFO_KV_SATURATED: {
       hipStream_t s = (hipStream_t)hip_stream;
       PD_CHECK_HIP(hipStreamSynchronize(s));        // the staging buffer may be in flight

@@ -1,6 +1,6 @@
-"""A model whose step reads more than the last-level cache holds: the first 110 MB of its packed weights are loaded without the
-non-temporal hint, the others with it.  The line falls inside the second layer; logits and tokens are the same bits as with the
-hint on every weight and on none, for packed, general and many rows."""
+"""A model whose step reads more than the last-level cache holds: the matrices that start within the first 110 MB of its
+packed weights are loaded without the non-temporal hint, the others with it.  Here those are the first layer's four (101 MB) and one
+of the second's (25 MB); logits and tokens are the same bits as with the hint on every weight and on none, for packed, general and many rows."""
 
 import numpy as np
 import pytest
@@ -26,6 +26,7 @@ def test_same_bits_wherever_the_hint_is(batch, n_sub):
         assert dec.get_info(binding.PD_INFO_STREAM_LOADS) == 1
         if stream is not None:
             dec.set_option(binding.PD_OPT_STREAM_LOADS, stream)
+        assert dec.get_info(binding.PD_INFO_KEPT_BYTES) == (2 * 15 * 2048 ** 2 if stream is None else 0)
         dec.prefill_context(ctx, n_sub, 1, 9, n_sub + 9)
         steps = [dec.decode_step(want_logits=True) for _ in range(n_sub + 1)]
         out[stream] = [(np.array(s[0]), s[1].clone()) for s in steps]

@@ -34,6 +34,7 @@ void tiling(int n_tiles, int kt, int rows, int max_slices, int split, int kind, 
 }
 int vocab(int n_tiles, int kt, int rows) { return vocab_shares_row_tiles(n_tiles, kt, rows); }
 int lin(int n_tiles, int K, int rows) { return lin_row_tiles(n_tiles, K, rows); }
+int kept(int64_t first, int64_t values) { return weights_kept(first, values); }
 int slices(int d, int ff, int rows, int tiles) { return ffn2_in_slices(d, ff, rows, tiles); }
 void words(int64_t lo, int K, int share, int n_tiles, int c2, int64_t *out) {
   const GemmWords w = gemm_words(lo, K, share, n_tiles, c2);
@@ -301,3 +302,32 @@ def test_fp32_slices_against_measured_times(rules):
         assert us <= 2.2 if cut else us >= -1.7, (d, ff, rows, words)
     assert not rules.slices(512, 1023, 8, 96) and not rules.slices(512, 1 << 20, 33, 96) and not rules.slices(1025, 1 << 20, 8, 96)
     assert rules.slices(1024, 1 << 30, 32, 1 << 20) and not rules.slices(64, 1024, 32, 1 << 27)
+
+
+def _matrices(d, ff, gated, n_layer, vocab):
+    """Packed weights in the order of their places: (first value, values)."""
+    at, out = 0, []
+    for _ in range(n_layer):
+        for n in (3 * d * d, d * d, (2 if gated else 1) * ff * d, ff * d):
+            out.append((at, n))
+            at += n
+    return out + [(at, (vocab + 63) // 64 * 64 * d)]
+
+
+@pytest.mark.parametrize("gated", [False, True])
+@pytest.mark.parametrize("d,ff", [(768, 3072), (1024, 4096), (2048, 8192), (3072, 8192), (3584, 18944), (4096, 11008), (8192, 28672)])
+def test_kept_weights_leave_room_in_the_cache(rules, d, ff, gated):
+    for n_layer, vocab in itertools.product((1, 2, 3, 6, 7, 8, 12, 24), (1000, 32000, 50265, 256000)):
+        m = _matrices(d, ff, gated, n_layer, vocab)
+        kept = [(a, n) for a, n in m if rules.kept(C.c_int64(a), C.c_int64(n))]
+        total = 2 * sum(n for _, n in kept)
+        assert total <= 210e6                                # of 256 MB, whatever the matrices' sizes
+        assert kept == m[:len(kept)]                         # from layer 0 on
+        if len(kept) < len(m):                               # until the next one starts or ends too late
+            assert total >= 110e6 or total + 2 * m[len(kept)][1] > 210e6
+
+
+def test_kept_weights_at_the_line(rules):
+    assert rules.kept(C.c_int64(0), C.c_int64(105000000)) and not rules.kept(C.c_int64(0), C.c_int64(105000001))
+    assert rules.kept(C.c_int64(54999999), C.c_int64(50000001)) and not rules.kept(C.c_int64(54999999), C.c_int64(50000002))
+    assert not rules.kept(C.c_int64(55000000), C.c_int64(1))
