@@ -265,14 +265,14 @@ int pd_reset_decode(pd_ctx *ctx, void *hip_stream);
  *                        d_ff <= 6144 (a multiple of 64), also hand over the first norm of the next layer the same way (second
  *                        FFN projection -> QKV projection).  2: so do all others (that projection then cannot be cut along K
  *                        over blocks: slower from d_ff 8192 on).
- *   PD_OPT_STREAM_LOADS  1: decode steps load weights, keys and values with the non-temporal hint; 0: ordinary
+ *   PD_OPT_STREAM_LOADS  1, 2: decode steps load weights, keys and values with the non-temporal hint; 0: ordinary
  *                        loads.  Chosen at creation from the configuration: 1 when the bytes a step reads at
  *                        full capacity (every weight, every request's keys and values) exceed the 256 MB
  *                        last-level cache, so that nothing of them would be found there a step later (cfg4:
  *                        1.37 -> 1.31 ms per step, cfg5 6.55 -> 6.09); 0 for models the cache serves step after
- *                        step (cfg2: 0.187 ms, 0.202 with the hint).  Chosen at creation, the matrices that start within
- *                        the first 110 MB of the packed weights and end within 210 MB keep ordinary loads, and their
- *                        place in that cache; set here, 1 is for all.
+ *                        step (cfg2: 0.187 ms, 0.202 with the hint).  Where 1 was chosen at creation, the matrices that
+ *                        start within the first 110 MB of the packed weights and end within 210 MB keep ordinary loads
+ *                        under it, and their place in that cache; 2 is for all.
  *                        Same results bit for bit.
  *                        pd_get_info(PD_INFO_STREAM_LOADS) reports the setting.
  *   PD_OPT_CONTEXT_ATTN  attention kernel of the context pass (bf16 path, head_dim 64 or 128, layers without
@@ -320,7 +320,7 @@ int pd_measure_read_bandwidth(const void *dev_buf, size_t buf_bytes, size_t chun
  *   PD_INFO_KV_PAIR_LAYERS  layers whose cache holds pairs of halves (kv_pair_layers resolved)
  *   PD_INFO_CONTEXT_PAIRS   1: the context pass carries its activations as bf16 pairs; 0: as single bf16
  *                           values (PD_OPT_CONTEXT_SPLIT_ACT resolved)
- *   PD_INFO_STREAM_LOADS    1: decode steps use the non-temporal hint (PD_OPT_STREAM_LOADS)
+ *   PD_INFO_STREAM_LOADS    1, 2: decode steps use the non-temporal hint (the value of PD_OPT_STREAM_LOADS)
  *   PD_INFO_KEPT_BYTES      bytes of the weights of a decode step that keep ordinary loads while the others take the
  *                           hint (at most 210 MB; 0 without the hint)
  *   PD_INFO_KV_SATURATED    keys and values written since pd_create whose magnitude exceeded the

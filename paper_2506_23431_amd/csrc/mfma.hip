@@ -10,7 +10,7 @@ bf16_t *mfma_lo(pd_ctx *c, void *buf, size_t cols) {
 
 // a launch's weights [rows][K], and whether it loads them with the hint
 static bool kept(const pd_ctx *c, const bf16_t *W, size_t rows, size_t K) {
-  return c->kept_from && W >= c->kept_from && weights_kept(W - c->kept_from, rows * K);
+  return c->stream_loads == 1 && c->kept_from && W >= c->kept_from && weights_kept(W - c->kept_from, rows * K);
 }
 static void set_weights(pd_ctx *c, GemmArgs &a, const bf16_t *W, size_t rows, size_t K) {
   a.W = W;
@@ -18,7 +18,7 @@ static void set_weights(pd_ctx *c, GemmArgs &a, const bf16_t *W, size_t rows, si
 }
 // bytes of a step's weights that are loaded without the hint while the others take it
 int64_t mfma_kept_bytes(const pd_ctx *c) {
-  if (c->impl != 1 || !c->stream_loads) return 0;
+  if (c->impl != 1) return 0;
   const size_t d = c->cfg.d_model, ff = c->cfg.d_ff, up = c->cfg.ffn_kind == 1 ? 2 : 1;
   size_t values = 0;
   auto add = [&](const bf16_t *W, size_t rows, size_t K) { if (W && kept(c, W, rows, K)) values += rows * K; };

@@ -505,7 +505,7 @@ extern "C" int pd_set_option(pd_ctx *c, int key, int value) {
     case PD_OPT_CONTEXT_SPLIT_ACT:
       c->opt_ctx_split = value ? 1 : 0; return PD_OK;
     case PD_OPT_STREAM_LOADS:
-      c->stream_loads = value ? 1 : 0; c->kept_from = nullptr; drop_graph(c); return PD_OK;
+      c->stream_loads = value == 2 ? 2 : value ? 1 : 0; drop_graph(c); return PD_OK;
     case PD_OPT_CONTEXT_ATTN:
       c->opt_ctx_attn = value < 0 ? 0 : value > 2 ? 2 : value; return PD_OK;
     case PD_OPT_FUSE_NORM:

@@ -226,9 +226,9 @@ struct pd_ctx : RowSet {    // (the set in use: decode steps, passes over one re
   bool embed_pending;       // matrix-core path: the next norm kernel gathers x from the embedding tables
   bool embedded;            // the step's tick has gathered x and left its first norm in xn
   int stream_loads;         // 1: a decode step touches more bytes than the last-level cache holds: weights, keys and
-                            // values are loaded with the non-temporal hint (PD_OPT_STREAM_LOADS)
+                            // values are loaded with the non-temporal hint (PD_OPT_STREAM_LOADS); 2: all of them
   const bf16_t *kept_from;  // ... except packed weights within a distance from here (weights_kept), which the cache keeps from
-                            // step to step; NULL: none
+                            // step to step; NULL: none.  Set at creation only
   bool norm_halves;         // ... the sums per 8 columns, not 16
   bool norm_fused;          // the last residual projection left gain * x and per-tile row sums for the next
                             // norm: the projection that follows finishes it, no norm kernel runs
