@@ -117,6 +117,13 @@ inline NormHandover ffn2_handover(int d_model, int d_ff, bool low_parts, bool on
   return (d_model <= 1024 && d_ff <= 4096) || on_request ? HANDOVER_WHOLE : HANDOVER_NONE;
 }
 
+// Room for the row sums (two values each) that projections of at most 128 rows leave: of every 16 columns or, at most 16 rows, of
+// every 8.
+constexpr size_t norm_sums(int rows, int d_model) {
+  const size_t whole = (size_t)(rows < 128 ? rows : 128) * (d_model / 16), halves = (size_t)16 * (d_model / 8);
+  return whole > halves ? whole : halves;
+}
+
 // ---------------------------------------------------------------------------
 // Steps that read more than the last-level cache holds: packed weights that are loaded without the non-temporal hint.
 // ---------------------------------------------------------------------------

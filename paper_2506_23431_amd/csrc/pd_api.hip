@@ -212,7 +212,7 @@ static size_t carve_with(const pd_config *g, char *base, pd_ctx *c, const pd_enc
       lp.cx1 = e ? cv.take<float>(dd) : nullptr;
       lp.q1 = cv.take<float>(6 * dd); lp.q2 = base ? lp.q1 + 3 * dd : nullptr;
     }
-    x->nstats = cv.take<float2>(std::min(x->R_pad, 128) * (d / 16));   // steps of up to 128 rows hand norms over
+    x->nstats = cv.take<float2>(norm_sums(x->R_pad, d));
     x->p_lm_head = cv.take<bf16_t>((size_t)x->vocab_pad * d);
     if (e) {
       for (LayerPtrs &lp : x->ed.enc) {

@@ -220,7 +220,8 @@ struct pd_ctx : RowSet {    // (the set in use: decode steps, passes over one re
   // workspace carve-up
   char *ws; size_t ws_bytes;
   int pend_parts;           // slices of ypart the next norm kernel has to add to x
-  float2 *nstats;           // [16][d/16] per-tile row sums left by the output projection for the next norm
+  float2 *nstats;           // row sums left by a residual projection for the next norm: [up to 128][d/16] by tiles of 16 columns, or
+                            // [16][d/8] by halves of them (norm_sums values)
   bool packed;              // this launch sequence keeps activations as packed pairs (at most 8 rows):
                             // high parts in rows 0-7 of a 16-row fragment, low parts in rows 8-15
   bool embed_pending;       // matrix-core path: the next norm kernel gathers x from the embedding tables
@@ -229,9 +230,9 @@ struct pd_ctx : RowSet {    // (the set in use: decode steps, passes over one re
                             // values are loaded with the non-temporal hint (PD_OPT_STREAM_LOADS); 2: all of them
   const bf16_t *kept_from;  // ... except packed weights within a distance from here (weights_kept), which the cache keeps from
                             // step to step; NULL: none.  Set at creation only
-  bool norm_halves;         // ... the sums per 8 columns, not 16
   bool norm_fused;          // the last residual projection left gain * x and per-tile row sums for the next
                             // norm: the projection that follows finishes it, no norm kernel runs
+  bool norm_halves;         // ... the sums per 8 columns, not 16
   int lm_parts;             // winners per row the buffers have room for
   int lm_win;               // winners per row the last vocabulary projection left
   float *rope_cs;           // [max_pos][hd/2][2] cos, sin

@@ -34,11 +34,14 @@ void tiling(int n_tiles, int kt, int rows, int max_slices, int split, int kind, 
 }
 int vocab(int n_tiles, int kt, int rows) { return vocab_shares_row_tiles(n_tiles, kt, rows); }
 int lin(int n_tiles, int K, int rows) { return lin_row_tiles(n_tiles, K, rows); }
+int64_t sums(int rows, int d) { return (int64_t)norm_sums(rows, d); }
+int handover(int d, int ff, int low, int request) { return ffn2_handover(d, ff, low, request); }
+int f32_halves(int hd, int units, int keys) { return attn_f32_halves(hd, units, keys); }
 int kept(int64_t first, int64_t values) { return weights_kept(first, values); }
 int slices(int d, int ff, int rows, int tiles) { return ffn2_in_slices(d, ff, rows, tiles); }
 void words(int64_t lo, int K, int share, int n_tiles, int c2, int64_t *out) {
-  const GemmWords w = gemm_words(lo, K, share, n_tiles, c2);
-  out[0] = words_granules(w.lo); out[1] = words_k_tiles(w.k); out[2] = words_k_tiles(w.share); out[3] = words_tiles(w.n); out[4] = words_c2(w.n); out[5] = 0;
+  const GemmWords w = gemm_words(lo, K, share, n_tiles, c2 & 1, c2 & 2);
+  out[0] = words_granules(w.lo); out[1] = words_k_tiles(w.k); out[2] = words_k_tiles(w.share); out[3] = words_tiles(w.n); out[4] = words_c2(w.n); out[5] = words_half_sums(w.n);
 }
 int attn_word(int H, int A) {
   const uint32_t w = heads_rows(H, A);
@@ -331,3 +334,32 @@ def test_kept_weights_at_the_line(rules):
     assert rules.kept(C.c_int64(0), C.c_int64(105000000)) and not rules.kept(C.c_int64(0), C.c_int64(105000001))
     assert rules.kept(C.c_int64(54999999), C.c_int64(50000001)) and not rules.kept(C.c_int64(54999999), C.c_int64(50000002))
     assert not rules.kept(C.c_int64(55000000), C.c_int64(1))
+
+
+def test_room_for_row_sums(rules):
+    rules.sums.restype = C.c_int64
+    for rows, d in itertools.product((16, 32, 64, 80, 112, 128, 256, 4096), (32, 64, 1056, 2048, 8192)):
+        room = rules.sums(rows, d)
+        assert room >= min(rows, 128) * (d // 16) and room >= 16 * (d // 8)
+        assert room == max(min(rows, 128), 32) * (d // 16)
+
+
+def test_words_tell_row_sums_of_half_tiles(rules):
+    """... beside the tiles and whether c2 follows c1 (the first bit of the flags)."""
+    out = (C.c_int64 * 6)()
+    for tiles, flags in itertools.product((1, 192, (1 << 24) + 1, (1 << 30) - 1), (0, 1, 2, 3)):
+        rules.words(C.c_int64(64), 2048, 4, tiles, flags, out)
+        assert list(out)[1:] == [64, 4, tiles, flags & 1, flags >> 1]
+
+
+# width, inner width; rows with low parts; on request: 0 norm kernel, 1 whole tiles, 2 halves
+HANDOVER = [
+    (1024, 512, 1, 0, 1), (1024, 4096, 1, 0, 1), (1024, 4128, 1, 0, 0), (1024, 4128, 1, 1, 1), (1024, 512, 0, 0, 1),
+    (1056, 64, 1, 0, 2), (1056, 96, 1, 0, 0), (1056, 96, 1, 1, 1), (1056, 64, 0, 0, 0), (1056, 64, 0, 1, 1), (1536, 6144, 1, 0, 2),
+    (1536, 6144, 1, 1, 2), (1536, 6208, 1, 0, 0), (2048, 6144, 1, 0, 2), (2080, 512, 1, 0, 0), (2080, 512, 1, 1, 1), (4096, 11008, 1, 0, 0),
+]
+
+
+@pytest.mark.parametrize("d,ff,low,request_,expect", HANDOVER)
+def test_norm_handover_on_both_sides_of_its_lines(rules, d, ff, low, request_, expect):
+    assert rules.handover(d, ff, low, request_) == expect
