@@ -172,7 +172,10 @@ inline int lin_row_tiles(int n_tiles, int K, int rows) {
 // quarters (12 rows, 16 units of head size 64, 330 keys 11.7 -> 8.7 us).  us per step of 4 layers, one block / two: 320 keys of
 // size 64, 8 units 130.3 / 122.3, 16 units 133.5 / 125.7, 200 keys, 64 units 128.5 / 127.4, 128 units 133.8 / 127.6, of size 80
 // 160.3 / 152.7, 128 153.0 / 144.6.  With heads of 32 (109.6 / 114.2, 480 keys 109.1 / 112.1) or few keys (20 + generated 113.3 /
-// 118.4) there is less to share than the second block costs.
+// 118.4) there is less to share than the second block costs, beyond 128 units the second blocks wait for the first.  The more
+// keys, the more it gives, at every head size: 160 / 700 / 2000 keys, 8 units of size 64 0.91 / 0.89 / 0.85 of the time, 128 units
+// 0.96 / 0.95 / 0.86, of size 128 0.94 / 0.88 / 0.83 and 0.96 / 0.90 / 0.82, of size 200 and 256 0.89-0.91 / 0.86; 160 units of size 64
+// 1.07 / 1.12, 256 1.10.  Scalar loads (size 50) are even at 160 keys (0.99-1.02), 0.88-0.91 at 700.
 inline bool attn_f32_halves(int head_dim, int units, int keys) { return head_dim > 32 && units <= 128 && keys >= 160; }
 
 // ---------------------------------------------------------------------------

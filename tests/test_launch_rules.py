@@ -363,3 +363,25 @@ HANDOVER = [
 @pytest.mark.parametrize("d,ff,low,request_,expect", HANDOVER)
 def test_norm_handover_on_both_sides_of_its_lines(rules, d, ff, low, request_, expect):
     assert rules.handover(d, ff, low, request_) == expect
+
+
+# fp32 attention: head size, units, context keys; us per step of 4 layers with one block per unit and with two
+F32_ATTENTION = [
+    (64, 8, 160, 122.7, 111.7), (64, 8, 700, 151.7, 135.4), (64, 8, 4000, 343.7, 277.6), (64, 64, 160, 127.6, 117.7),
+    (64, 64, 2000, 247.5, 207.5), (64, 128, 160, 180.5, 172.8), (64, 128, 700, 208.7, 197.3), (64, 128, 2000, 307.8, 265.2),
+    (64, 160, 160, 181.2, 193.5), (64, 160, 700, 213.3, 238.2), (64, 256, 320, 191.6, 210.4), (64, 256, 700, 238.6, 262.4),
+    (32, 8, 320, 109.6, 114.2), (32, 8, 480, 109.1, 112.1), (64, 8, 20, 113.3, 118.4),
+    (40, 8, 160, 118.5, 114.2), (40, 128, 700, 189.3, 180.3), (50, 128, 160, 171.3, 174.4), (50, 128, 700, 227.6, 207.2),
+    (96, 128, 160, 227.4, 217.4), (128, 8, 160, 163.0, 153.8), (128, 128, 2000, 536.5, 442.2), (200, 4, 700, 355.9, 305.5),
+    (256, 64, 160, 296.2, 268.8), (36, 160, 700, 176.1, 218.4),
+]
+
+
+@pytest.mark.parametrize("hd,units,keys,one,two", F32_ATTENTION)
+def test_f32_attention_blocks_are_near_the_fastest_measured(rules, hd, units, keys, one, two):
+    assert (two if rules.f32_halves(hd, units, keys) else one) <= 1.02 * min(one, two)
+
+
+def test_f32_attention_blocks_at_the_lines(rules):
+    for hd, units, keys, two in ((32, 8, 300, 0), (33, 8, 300, 1), (64, 128, 300, 1), (64, 129, 300, 0), (64, 8, 159, 0), (64, 8, 160, 1)):
+        assert rules.f32_halves(hd, units, keys) == two
