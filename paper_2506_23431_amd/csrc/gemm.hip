@@ -728,13 +728,13 @@ __device__ __forceinline__ void gemm_chunk(floatx4 (&acc)[NT][RT][NA], const uin
       uint32_t hot_k, uint32_t hot_share, uint32_t hot_n
 struct GemmHot {
   const bf16_t *w, *x;        // weights, activations
-  const void *a, *b, *c;      // EPI_RESID_NORM: x_res, gain; finishing a norm: stats_in (else NULL), c1; EPI_QKV*: c = kvinfo
+  const void *a, *b, *c;      // EPI_RESID_NORM: x_res, gain, sums_before; finishing a norm: stats_in (else NULL), c1; EPI_QKV*: c = kvinfo
   GemmWords n;
 };
 template <int EPI>
 static GemmHot gemm_hot(const GemmArgs &a) {
   constexpr bool out = EPI == EPI_RESID_NORM;
-  return GemmHot{a.W, a.xn, out ? (const void *)a.x_res : a.stats_in, out ? a.gain : a.c1, a.rt.kvinfo,
+  return GemmHot{a.W, a.xn, out ? (const void *)a.x_res : a.stats_in, out ? a.gain : a.c1, out ? (const void *)a.sums_before : a.rt.kvinfo,
                  out ? gemm_words_rows(a.xn_lo ? a.xn_lo - a.xn : 0, a.K, a.k_share, a.n_tiles, a.R)
                      : gemm_words(a.xn_lo ? a.xn_lo - a.xn : 0, a.K, a.k_share, a.n_tiles, a.c2 != nullptr, a.stats_tiles > a.K / 16)};
 }
@@ -892,7 +892,11 @@ __global__ __launch_bounds__(64 * NW_K) void k_gemm_s(PD_GEMM_HOT_PARAMS, GemmAr
 // multiplies as with whole tiles, half the weights per compute unit, the same activations.  Row sums are left per 8 columns.
 // Bound by what a compute unit draws, twice as many activations as weights (width 2048, 8192 inner values from the caches 7.8 us,
 // cut along K 7.0 with 3.3 for the norm kernel behind it; from memory 10.9 against 7.4 + 3.2: see ffn2_handover).
-template <int NW, bool PACK, bool SW>
+// MEAN: for a norm that subtracts the mean, rows are handed over less the mean of their first 128 values in front of the FFN (from the
+// sums that the output projection left).  The norm does not change when a row is shifted, and what is rounded to bf16 pairs
+// is about as small as what a norm kernel rounds.  With the mean in it the relative error of the projection behind, at means of 0 /
+// 1 / 3 / 10 / 36 deviations, was 2.4e-6 / 3.5e-6 / 7.7e-6 / 2.6e-5 / 1.0e-4, where a norm kernel's is 2.4e-6.
+template <int NW, bool PACK, bool SW, bool MEAN>
 __global__ __launch_bounds__(64 * NW) void k_gemm_half(PD_GEMM_HOT_PARAMS, GemmArgs a) {
   __shared__ floatx4 red[NW][32];
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
@@ -903,9 +907,11 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_half(PD_GEMM_HOT_PARAMS, GemmA
   const uint4 *xp = (const uint4 *)hot_x + lane, *xl = PACK ? nullptr : xp + words_granules(hot_lo);
   const int n0 = tile * 16 + half * 8 + 4 * (g & 1);
   ResidPre pre;
+  float4 sums;
   if (w == 0) {                         // (rows beyond the last read it and are masked where the value is used)
     pre.g = *(const float4 *)((const float *)hot_b + n0);
     pre.x = *(const float4 *)((const float *)hot_a + (size_t)min(m, words_last_row(hot_n)) * (n_tiles * 16) + n0);
+    if (MEAN) sums = ((const float4 *)hot_c)[(size_t)m * (n_tiles / 2) + g];       // of two tiles each
   }
   floatx4 acc[2][PACK ? 1 : 2];         // k-tiles of either parity; high and low parts
 #pragma unroll
@@ -949,10 +955,14 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_half(PD_GEMM_HOT_PARAMS, GemmA
 #pragma unroll
   for (int v = 1; v < NW; ++v) y += red[v][lane & 31];
   const bool in = m < a.R && lane < 32;
+  const float mean = MEAN ? fold32(fold16(sums.x + sums.z, Add()), Add()) * (1.f / 128.f) : 0.f;
   float s1 = 0.f, s2 = 0.f;
   if (in) {
-    const float x[4] = {pre.x.x + y[0], pre.x.y + y[1], pre.x.z + y[2], pre.x.w + y[3]};
+    float x[4] = {pre.x.x + y[0], pre.x.y + y[1], pre.x.z + y[2], pre.x.w + y[3]};
     *(float4 *)(a.x_res + (size_t)m * a.ld + n0) = make_float4(x[0], x[1], x[2], x[3]);
+    if (MEAN)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[j] -= mean;
     const float z[4] = {pre.g.x * x[0], pre.g.y * x[1], pre.g.z * x[2], pre.g.w * x[3]};
     store4_split(a.out_bf, a.out_lo, act_off(m, n0, a.ld), z);
     s1 = (x[0] + x[1]) + (x[2] + x[3]);
@@ -966,11 +976,13 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_half(PD_GEMM_HOT_PARAMS, GemmA
 template <int NW>
 static int launch_gemm_half(GemmArgs a, hipStream_t s) {
   PD_REQUIRE(a.R <= 16 && a.K % 64 == 0, PD_EINVAL, "%d rows of %d inner values in halves of column tiles", a.R, a.K);
+  PD_REQUIRE(!a.sums_before || (a.n_tiles >= 8 && a.n_tiles % 2 == 0), PD_EINVAL, "means of %d column tiles", a.n_tiles);
   a.k_share = (a.K / 64 + NW - 1) / NW * 2;
   const dim3 grid(2 * a.n_tiles);
-#define PD_HALF(P) (a.stream_w ? launch_gemm_kernel<EPI_RESID_NORM>(k_gemm_half<NW, P, true>, grid, 64 * NW, a, s)    \
-                               : launch_gemm_kernel<EPI_RESID_NORM>(k_gemm_half<NW, P, false>, grid, 64 * NW, a, s))
-  return a.packed ? PD_HALF(true) : PD_HALF(false);
+#define PD_HALF(P, M) (a.stream_w ? launch_gemm_kernel<EPI_RESID_NORM>(k_gemm_half<NW, P, true, M>, grid, 64 * NW, a, s)    \
+                                  : launch_gemm_kernel<EPI_RESID_NORM>(k_gemm_half<NW, P, false, M>, grid, 64 * NW, a, s))
+  if (a.sums_before) return a.packed ? PD_HALF(true, true) : PD_HALF(false, true);
+  return a.packed ? PD_HALF(true, false) : PD_HALF(false, false);
 #undef PD_HALF
 }
 #endif

@@ -117,10 +117,11 @@ inline NormHandover ffn2_handover(int d_model, int d_ff, bool low_parts, bool on
   return (d_model <= 1024 && d_ff <= 4096) || on_request ? HANDOVER_WHOLE : HANDOVER_NONE;
 }
 
-// Room for the row sums (two values each) that projections of at most 128 rows leave: of every 16 columns or, at most 16 rows, of
-// every 8.
+// Room for the row sums (two values each) that projections of at most 128 rows leave: of every 16 columns and, at most 16 rows,
+// behind 16 such rows of every 8.
+constexpr size_t half_sums_at(int d_model) { return (size_t)16 * (d_model / 16); }
 constexpr size_t norm_sums(int rows, int d_model) {
-  const size_t whole = (size_t)(rows < 128 ? rows : 128) * (d_model / 16), halves = (size_t)16 * (d_model / 8);
+  const size_t whole = (size_t)(rows < 128 ? rows : 128) * (d_model / 16), halves = half_sums_at(d_model) + (size_t)16 * (d_model / 8);
   return whole > halves ? whole : halves;
 }
 

@@ -60,7 +60,8 @@ int mfma_qkv(pd_ctx *c, GemmArgs &a, const bf16_t *W, int n_tiles, int sec0, voi
   a.kc = (f16_t *)kc; a.vc = (f16_t *)vc; a.rope_cs = c->rope_cs;
   a.kc_lo = (f16_t *)kc_lo; a.vc_lo = (f16_t *)vc_lo; a.kv_sat = c->kv_sat;
   if (c1) {
-    a.stats_in = c->nstats; a.stats_tiles = c->norm_halves ? d / 8 : d / 16; a.c1 = c1; a.c2 = g.norm_kind == 0 ? c2 : nullptr;
+    a.stats_in = c->norm_halves ? c->nstats + half_sums_at(d) : c->nstats; a.stats_tiles = c->norm_halves ? d / 8 : d / 16;
+    a.c1 = c1; a.c2 = g.norm_kind == 0 ? c2 : nullptr;
     a.norm_kind = g.norm_kind; a.norm_d = d; a.norm_eps = g.norm_eps;
   }
   const int rc = mfma_gemm(g.pos_kind == 1 ? EPI_QKV_ROPE : EPI_QKV, a, R, s);
@@ -123,11 +124,13 @@ int mfma_out_ffn(pd_ctx *c, GemmArgs &a, const bf16_t *p_wo, const LayerPtrs &lw
   a.stats_in = nullptr;
   set_weights(c, a, lw.p_w2, d, ff);
   a.xn = (const bf16_t *)c->hb; a.xn_lo = mfma_lo(c, c->hb, ff); a.K = ff; a.n_tiles = d / 16; a.x = c->ypart; a.ld = d;
-  const NormHandover over = next_gain && R <= 16 && mfma_can_fuse_norm(c, R) ? ffn2_handover(d, ff, c->opt_split, c->opt_fuse_norm == 2) : HANDOVER_NONE;
+  // (at most 16 rows: the output projection left its sums above, where a layer has c1)
+  const NormHandover over = next_gain && R <= 16 && fuse ? ffn2_handover(d, ff, c->opt_split, c->opt_fuse_norm == 2) : HANDOVER_NONE;
   if (over != HANDOVER_NONE) {
     a.half_tiles = c->norm_halves = over == HANDOVER_HALVES;
+    a.sums_before = a.half_tiles && g.norm_kind == 0 ? c->nstats : nullptr;
     // completes x itself and leaves gain * x with the row sums for the next layer's QKV projection
-    a.x_res = c->x; a.gain = next_gain; a.stats_out = c->nstats;
+    a.x_res = c->x; a.gain = next_gain; a.stats_out = a.half_tiles ? c->nstats + half_sums_at(d) : c->nstats;
     a.out_bf = (bf16_t *)c->xn; a.out_lo = mfma_lo(c, c->xn, d);
     c->norm_fused = true;
     return mfma_gemm(EPI_RESID_NORM, a, R, s);

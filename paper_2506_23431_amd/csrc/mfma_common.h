@@ -133,6 +133,8 @@ struct GemmArgs {
   // over the tile's 16 columns
   float *x_res; const float *gain; float2 *stats_out;
   int half_tiles;        // 1: blocks of 8 columns (with low parts or packed), row sums per 8 columns
+  const float2 *sums_before;  // ... or NULL; the sums [16][tiles] of x_res as it was: what is handed over, and its sums, are then
+                              // x_res less a mean taken from them
   // EPI_GELU / EPI_SWIGLU / EPI_QKV* with stats_in != NULL: the activations are gain * x (not normalised); the
   // epilogue applies the norm, y = rstd * (acc - mean * c1[n]) + c2[n], with mean and rstd of every row
   // from stats_in[row][stats_tiles] and c1 = W gain, c2 = W bias (c2 NULL: no bias)

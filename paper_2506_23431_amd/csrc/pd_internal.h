@@ -220,8 +220,8 @@ struct pd_ctx : RowSet {    // (the set in use: decode steps, passes over one re
   // workspace carve-up
   char *ws; size_t ws_bytes;
   int pend_parts;           // slices of ypart the next norm kernel has to add to x
-  float2 *nstats;           // row sums left by a residual projection for the next norm: [up to 128][d/16] by tiles of 16 columns, or
-                            // [16][d/8] by halves of them (norm_sums values)
+  float2 *nstats;           // row sums left by a residual projection for the next norm: [up to 128][d/16] by tiles of 16 columns;
+                            // half_sums_at behind, [16][d/8] by halves of tiles
   bool packed;              // this launch sequence keeps activations as packed pairs (at most 8 rows):
                             // high parts in rows 0-7 of a 16-row fragment, low parts in rows 8-15
   bool embed_pending;       // matrix-core path: the next norm kernel gathers x from the embedding tables

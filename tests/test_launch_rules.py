@@ -340,8 +340,8 @@ def test_room_for_row_sums(rules):
     rules.sums.restype = C.c_int64
     for rows, d in itertools.product((16, 32, 64, 80, 112, 128, 256, 4096), (32, 64, 1056, 2048, 8192)):
         room = rules.sums(rows, d)
-        assert room >= min(rows, 128) * (d // 16) and room >= 16 * (d // 8)
-        assert room == max(min(rows, 128), 32) * (d // 16)
+        assert room >= min(rows, 128) * (d // 16) and room >= 16 * (d // 16) + 16 * (d // 8)
+        assert room == max(min(rows, 128), 48) * (d // 16)
 
 
 def test_words_tell_row_sums_of_half_tiles(rules):
