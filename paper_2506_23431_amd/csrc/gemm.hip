@@ -1,5 +1,6 @@
 // Weight re-packing, normalisation and the skinny bf16 GEMM with fused epilogues
 // (QKV + rotary + KV append, residual add, GELU, SwiGLU, vocabulary argmax).
+#include "gelu_poly.h"
 #include "mfma_common.h"
 
 #include <algorithm>
@@ -473,19 +474,15 @@ struct NormPre { float4 c1, c2; };
 struct Winner { float best; int idx; };
 constexpr int NO_WINNER = 0x7fffffff;
 
-// t Phi(t) = max(t, 0) - |t| Phi(-|t|), Phi the normal distribution: Phi(-a) = 2^-(1 + a P(a)) with a polynomial P of degree 9
-// for the logarithm, fitted by weighted least squares to the least largest error of a Phi(-a) over [0, 8] (1.6e-10), where
-// Phi(-8) is 6e-16.  One form for every t, 14 instructions where erff has two branches of 42 together, and closer: over
-// normal t of deviation 0.1, 1 and 4 the error is 3.1e-8, 2.7e-8 and 1.7e-8 (2-norm, relative), with 0.5 t (1 + erff) 3.8e-8,
+// t Phi(t) = max(t, 0) - |t| Phi(-|t|), Phi the normal distribution, by a polynomial for the logarithm of its tail
+// (gelu_coefficient).  One form for every t, 14 instructions where erff has two branches of 42 together, and closer: over normal t of deviation 0.1, 1 and 4 the error is 3.1e-8, 2.7e-8 and 1.7e-8 (2-norm, relative), with 0.5 t (1 + erff) 3.8e-8,
 // 3.8e-8 and 2.3e-8 (for t < 0 that sum cancels: 1e-5 at t = -3, here 8e-7).  4096 rows, 8192 columns,
 // K 2048: 258 -> 237 us; 2048 rows, 3072 columns, K 768: 29.5 -> 26.0.
 __device__ __forceinline__ float gelu(float t) {
-  constexpr float P[10] = {1.1511042f, 0.45922282f, 0.052425109f, -0.0069032288f, -5.6824283e-5f,
-                           0.00032017249f, -9.3072435e-5f, 1.4872334e-5f, -1.3470777e-6f, 5.3995802e-8f};
   const float b = fabsf(t), a = b > 8.f ? 8.f : b;          // (NaN stays NaN)
-  float r = P[9];
+  float r = gelu_coefficient(GELU_TERMS - 1);
 #pragma unroll
-  for (int i = 8; i >= 0; --i) r = fmaf(r, a, P[i]);
+  for (int i = GELU_TERMS - 2; i >= 0; --i) r = fmaf(r, a, gelu_coefficient(i));
   return fmaf(-0.5f * a, __builtin_amdgcn_exp2f(-(r * a)), t > 0.f ? t : 0.f);
 }
 
