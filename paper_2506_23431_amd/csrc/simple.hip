@@ -567,9 +567,11 @@ __global__ void k_qkv_post(float *qkv, KT *kc, KT *vc, KT *kc_lo, KT *vc_lo, Row
 // generated-side slot (j >= L, j < n) whose subsequence index is <= the row's (Section 3.2).
 // Per key tile: S^T (16 keys x 16 queries) from the keys' rows and the queries, mask, online softmax per query,
 // O^T += V^T P^T; the score tile's registers are the operand of the second product.  Keys and values are requested
-// together, before either is used.  Bound by the one compute unit a (request, head) runs on: 32 products of 32 clocks
-// per key tile, so 16 waves and a tile or two each, and two blocks per unit where that pays (attn_f32_halves; 12 rows,
-// 16 units of 64 dims, 330 keys: 8.7 us, 11.7 with one block, 12 more with all waves merging and expf; a thread per key over uncoalesced key rows took 31; requesting the next tile ahead costs the registers of half
+// together, before either is used.  Bound by its chain, queries and keys to scores to values to the merge of the waves (6-7 us
+// however few the keys), then by the one or two compute units that draw a unit's keys and values (10.6 us per 1000 keys of 64 dims in
+// two blocks, of which 5 are the products: 24 of 32 clocks per key tile), so 16 waves and a tile or two each, and two blocks
+// per unit where that pays (attn_f32_halves; 12 rows, 16 units of 64 dims, 330 keys: 8.7 us, 11.7 with one block, 12 more with all waves
+// merging and expf; a thread per key over uncoalesced key rows took 31; requesting the next tile ahead costs the registers of half
 // the waves, 13-17 us).
 // ---------------------------------------------------------------------------
 struct AttnF32Args {
